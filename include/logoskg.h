@@ -367,9 +367,10 @@ void logoskg_result_free(logoskg_result *r);
  * path_count[i] = number written (0 if the target is not reached; 1 empty
  * path if it is a seed).  All four arrays are device memory; path_edges is
  * int32[n_pairs][max_paths][k].  On a sharded graph the kernel reads the
- * object rows it walks from pinned host memory, in place.  The call takes its
- * working memory from the graph's pool and returns after `stream` has been
- * synchronised.
+ * object rows it walks from pinned host memory, in place.  On a resident graph
+ * the first call builds the triple indices of SUB's rows (4 bytes per triple in
+ * device memory, freed with the graph; without room for them the call does
+ * without).  The call returns after `stream` has been synchronised.
  */
 logoskg_status logoskg_paths(logoskg_graph *g, const logoskg_result *r, const int32_t *query_idx,
                              const int32_t *target, int64_t n_pairs, int32_t max_paths,
@@ -422,16 +423,11 @@ logoskg_status logoskg_result_walks_fetch(logoskg_result *r, int32_t query, int3
 /*
  * For callers that cannot allocate device memory (code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): logoskg_paths with the
- * same arguments, results and order, whose only working memory - three int32
- * depth-first stacks of n_pairs * max(k, 1) entries - lives in an array that is
- * part of the library's device image (12 MiB per GPU, held until the process
- * ends) instead of a block of the graph's pool.  The call allocates and frees
- * nothing on the device and does not synchronise: it is asynchronous on
- * `stream`.  n_pairs * max(k, 1) above LOGOSKG_STATIC_PATH_SLOTS is refused
- * with LOGOSKG_ERANGE (nothing is launched).  Every call on a GPU uses that
- * GPU's one array: calls that overlap on one GPU (two streams, two threads,
- * two graphs) race; issue them on one stream or wait in between.  Nothing
- * needs clearing between calls (a stack entry is written before it is read).
+ * same arguments, results and order.  The call allocates and frees nothing on
+ * the device and does not synchronise: it is asynchronous on `stream`.  The
+ * depth-first stacks live in the LDS of each pair's block, so calls may overlap.
+ * n_pairs * max(k, 1) above LOGOSKG_STATIC_PATH_SLOTS is refused with
+ * LOGOSKG_ERANGE (nothing is launched).
  */
 #define LOGOSKG_STATIC_PATH_SLOTS (1ll << 20)
 logoskg_status logoskg_paths_static(logoskg_graph *g, const logoskg_result *r, const int32_t *query_idx,

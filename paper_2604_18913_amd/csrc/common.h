@@ -238,6 +238,8 @@ struct logoskg_result {
     uint32_t *act = nullptr;      // [k+1][Epad/32]: entity has a non-zero line in that level
     unsigned long long *allow = nullptr;    // [R][W] relation -> queries that may follow it
     unsigned long long *live = nullptr;     // [k+1][16] queries whose level-h frontier has an out-edge
+    long long *seed_off = nullptr;  // [Q+1] and the batch's seeds behind it (k_seed's copy), for the path listing
+    int32_t *seeds = nullptr;
     // result-list bookkeeping (count pass): for every query, the number of reached
     // entities below a tile, as three nested exclusive prefixes
     uint16_t *tile_base = nullptr;  // [ntiles][64W]  tiles (64 entities) inside their super tile

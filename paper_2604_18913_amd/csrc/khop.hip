@@ -31,10 +31,12 @@ namespace lkg {
 __global__ void k_seed(int Q, long long num_seeds, const long long *__restrict__ seed_off,
                        const int32_t *__restrict__ seeds, int32_t E, int W,
                        unsigned long long *level0, unsigned long long *visited, uint32_t *act0,
-                       unsigned long long *ctr) {
+                       unsigned long long *ctr, long long *kept_off, int32_t *kept_seeds) {
     int q = blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= Q) return;
     long long a = seed_off[q], b = seed_off[q + 1];
+    kept_off[q] = a;  // the result keeps a copy: the caller's arrays are borrowed for the call only
+    if (q == Q - 1) kept_off[Q] = b;
     if (a < 0 || b < a || b > num_seeds || (q == 0 && a != 0) || (q == Q - 1 && b != num_seeds)) {
         atomicOr(&ctr[C_ERR], 1ull);
         return;
@@ -42,6 +44,7 @@ __global__ void k_seed(int Q, long long num_seeds, const long long *__restrict__
     unsigned long long bit = 1ull << (q & 63);
     for (long long i = a; i < b; ++i) {
         int32_t e = seeds[i];
+        kept_seeds[i] = e;
         if ((uint32_t)e >= (uint32_t)E) {
             atomicOr(&ctr[C_ERR], 2ull);
             continue;
@@ -991,7 +994,7 @@ extern "C" void logoskg_result_free(logoskg_result *r) {
     (void)hipSetDevice(g->device);
     drop_walk_tables(r);
     // levels follows visited and live follows act in one allocation each
-    void *ptrs[] = {r->visited, r->act, r->allow, r->tile_base,
+    void *ptrs[] = {r->visited, r->act, r->allow, r->seed_off, r->tile_base,
                     r->super_base, r->mega_base, r->d_reached_off, r->lvl_tile_base, r->lvl_super_base,
                     r->lvl_mega_base, r->d_level_off, r->trip_ent, r->trip_off,
                     r->trip_chunk_entry, r->trip_chunk_first, r->tile_ent, r->cpos, r->act_chunk};
@@ -1059,6 +1062,10 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
     r->live = reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(r->act) + act_bytes);
     if (r->has_mask && (s = g->pool.alloc((void **)&r->allow, (size_t)g->R * W * 8, st)) != LOGOSKG_OK) return fail(s);
 
+    // (offsets, then the seeds)
+    if ((s = g->pool.alloc((void **)&r->seed_off, ((size_t)r->Q + 1) * 8 + (size_t)b->num_seeds * 4, st)) != LOGOSKG_OK) return fail(s);
+    r->seeds = reinterpret_cast<int32_t *>(r->seed_off + r->Q + 1);
+
 #define KH(call)                                  \
     do {                                          \
         logoskg_status s2_ = [&]() -> logoskg_status { LKG_HIP(call); return LOGOSKG_OK; }(); \
@@ -1084,7 +1091,8 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
     k_seed<<<dim3((r->Q + 255) / 256), dim3(256), 0, st>>>(r->Q, (long long)b->num_seeds,
                                                            (const long long *)b->seed_off, b->seeds, g->E, W,
                                                            (unsigned long long *)r->levels,
-                                                           (unsigned long long *)r->visited, r->act, g->d_ctr);
+                                                           (unsigned long long *)r->visited, r->act, g->d_ctr,
+                                                           r->seed_off, r->seeds);
     g->prof.end(st);
     KH(hipGetLastError());
     const bool want_stats = g->prof.counters;

@@ -12,135 +12,281 @@
 // target through levels d-1 .. 0 meets exactly the walks of d allowed triples
 // from a seed (Sec. 3.3: complete paths, extended hop by hop).
 #include <algorithm>
-#include <mutex>
 
 #include "common.h"
 
 namespace lkg {
 
-// One wavefront per (query, target) pair.  The depth-first state is the same in every lane: all
-// lanes compute it, write it to the pair's three stacks (same address, same value) and read it
-// back, so a lane only ever reads what it has written itself.  An object row is scanned 64
-// entries at a time: every lane tests one entry (subject one level closer for the query, relation
-// allowed) and a ballot gives the admissible entries in ascending position = ascending edge id,
-// so a row of a hundred thousand entries is not a single lane's loop.
-__global__ void __launch_bounds__(256)
-k_paths(long long n_pairs, int Q, int k, int W, int32_t E, long long plane,
-        const unsigned long long *__restrict__ levels, const unsigned long long *__restrict__ allow,
-        const uint32_t *__restrict__ in_off, const int32_t *__restrict__ in_sub,
-        const uint16_t *__restrict__ in_rel, const int32_t *__restrict__ in_eid,
-        const int32_t *__restrict__ query_idx, const int32_t *__restrict__ target,
-        const int32_t *__restrict__ length, int max_paths, int32_t *path_count, int32_t *path_edges,
-        int32_t *stk_vertex, uint32_t *stk_pos, int32_t *stk_edge) {
-    const long long i = (long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    if (i >= n_pairs) return;  // wave-uniform
-    const int v_lane = lane();
-    int32_t *out = path_edges + (size_t)i * max_paths * k;
-    for (long long x = v_lane; x < (long long)max_paths * k; x += 64) out[x] = -1;
-    const int q = query_idx[i], v = target[i];
-    if ((uint32_t)q >= (uint32_t)Q || (uint32_t)v >= (uint32_t)E) {
-        if (v_lane == 0) path_count[i] = 0;
+// What the listing kernel needs besides the level planes.
+struct PathArgs {
+    long long first_pair;  // of this launch
+    int Q, k, W;
+    int32_t E;
+    long long plane, actw;
+    const unsigned long long *levels, *allow;
+    const uint32_t *act;
+    const uint32_t *in_off;
+    const int32_t *in_sub;
+    const uint16_t *in_rel;
+    const int32_t *in_eid;
+    // the queries' seeds and SUB's rows with their triple indices, or NULL out_eid
+    const long long *seed_off;
+    const int32_t *seeds;
+    const uint32_t *out_off;
+    const int32_t *out_obj;
+    const uint16_t *out_rel;
+    const int32_t *out_eid;
+    const int32_t *query_idx, *target, *length;
+    int max_paths;
+    int32_t *path_count, *path_edges;
+};
+
+constexpr int64_t kPathWidePairs = 1024;    // up to here 16 wavefronts per pair,
+constexpr int64_t kPathNarrowPairs = 65536; // up to here 4, then one
+constexpr int kPathSeeds = 64;    // queries with more seeds than this keep to the object rows at level 1
+constexpr int kPathMatches = 256; // triples from the seeds into one entity that are sorted in LDS
+
+// NW wavefronts (one block) per (query, target) pair.  The depth-first state - per level the vertex,
+// the next row position and the chosen edge - is block-uniform and lives in LDS (k <= 254).
+//
+// An object row is scanned in steps of NT = 64 NW entries (the first step after a descent) or four
+// times as many: every lane tests its entries (relation allowed, the subject's bit in the level's
+// active bitmap, then the query's bit in the subject's level line - each test spares the rest the
+// next, dearer gather), and the ballots of all wavefronts give the admissible entries in ascending
+// position = ascending edge id.  At level 1 every admissible entry ends a path and the entries' own
+// lanes write them; above, the first one is descended into.
+//
+// The last triple on the way down leaves a seed, and a query has few seeds: when their out-rows
+// together are shorter than the vertex's object row, the block walks those instead and sorts the
+// matches by edge id.  What bounds the kernel are hub targets and the hub subjects of level 1, whose
+// rows hold 10^5 entries.  4,096 pairs of a 30M-triple graph with whitelists, k = 2, 16 paths each:
+// 19.1 ms with one wavefront per pair and 64 entries per step (every path scanned the whole object
+// row of its level-1 subject for a seed), 0.65 ms now, with the rows' entries and the gathers of their
+// subjects' bits for a floor: sixteen wavefronts per pair took 0.96 ms there (the short rows leave them
+// idle), so it is the scans' work and no longer one block's chain of steps that counts.
+template <int NW>
+__global__ void __launch_bounds__(64 * NW) k_paths(PathArgs a) {
+    constexpr int NT = 64 * NW, U = 4;
+    __shared__ int32_t sv[LOGOSKG_MAX_K + 1], se[LOGOSKG_MAX_K + 1];
+    __shared__ uint32_t sp[LOGOSKG_MAX_K + 1];
+    __shared__ unsigned long long hit[2][U][NW];
+    __shared__ uint32_t s_lo[kPathSeeds], s_end[kPathSeeds];  // out-rows of the seeds: begin, running total of the lengths
+    __shared__ int32_t s_id[kPathSeeds];
+    __shared__ int32_t match[kPathMatches];
+    __shared__ int n_match;
+    const long long i = a.first_pair + blockIdx.x;
+    const int t = threadIdx.x, wave = t >> 6, k = a.k, W = a.W, max_paths = a.max_paths;
+    int32_t *out = a.path_edges + (size_t)i * max_paths * k;
+    for (long long x = t; x < (long long)max_paths * k; x += NT) out[x] = -1;
+    const int q = a.query_idx[i], v = a.target[i];
+    if ((uint32_t)q >= (uint32_t)a.Q || (uint32_t)v >= (uint32_t)a.E) {
+        if (t == 0) a.path_count[i] = 0;
         return;
     }
     const int w = q >> 6;
     const unsigned long long bit = 1ull << (q & 63);
     int d = -1;
-    if (length) {  // walks of exactly that many triples: the target has to sit in that level
-        const int want = length[i];
-        if (want >= 0 && want <= k && (levels[(size_t)want * plane + (size_t)v * W + w] & bit)) d = want;
-    } else {       // shortest paths: the first level that holds the target
+    if (a.length) {  // walks of exactly that many triples: the target has to sit in that level
+        const int want = a.length[i];
+        if (want >= 0 && want <= k && (a.levels[(size_t)want * a.plane + (size_t)v * W + w] & bit)) d = want;
+    } else {         // shortest paths: the first level that holds the target
         for (int h = 0; h <= k; ++h)
-            if (levels[(size_t)h * plane + (size_t)v * W + w] & bit) { d = h; break; }
+            if (a.levels[(size_t)h * a.plane + (size_t)v * W + w] & bit) { d = h; break; }
     }
     if (d <= 0) {  // not reached: no path; a seed: one empty path
-        if (v_lane == 0) path_count[i] = d == 0 ? 1 : 0;
+        if (t == 0) a.path_count[i] = d == 0 ? 1 : 0;
         return;
     }
-    // explicit stack, entry l (1..d) = the vertex at hop l of the partial path, the next
-    // in-edge position to try for it, and the edge chosen into it
-    int32_t *sv = stk_vertex + (size_t)i * k - 1;
-    uint32_t *sp = stk_pos + (size_t)i * k - 1;
-    int32_t *se = stk_edge + (size_t)i * k - 1;
-    int found = 0, l = d;
-    sv[d] = v;
-    sp[d] = in_off[v];
+    // the seeds' out-rows (a repeated seed counts once); n_seeds = 0: not usable for this query
+    int n_seeds = 0;
+    uint32_t seed_edges = 0;
+    if (a.out_eid) {  // block-uniform
+        const long long b0 = a.seed_off[q], n = a.seed_off[q + 1] - b0;
+        if (n > 0 && n <= kPathSeeds) {
+            n_seeds = (int)n;
+            if (t < n_seeds) s_id[t] = a.seeds[b0 + t];
+            __syncthreads();
+            if (t < n_seeds) {
+                const int32_t s = s_id[t];
+                bool again = false;
+                for (int x = 0; x < t; ++x) again |= s_id[x] == s;
+                s_lo[t] = a.out_off[s];
+                s_end[t] = again ? 0u : a.out_off[s + 1] - s_lo[t];
+            }
+            __syncthreads();
+            if (t == 0) {
+                uint32_t sum = 0;
+                for (int x = 0; x < n_seeds; ++x) s_end[x] = sum += s_end[x];  // < 2^31: distinct rows of one graph
+            }
+            __syncthreads();
+            seed_edges = s_end[n_seeds - 1];
+        }
+    }
+    int found = 0, l = d, buf = 0;
+    if (t == 0) {
+        sv[d] = v;
+        sp[d] = a.in_off[v];
+    }
+    __syncthreads();
+    // writes path number `at`: the edges chosen at levels d .. 2, and `eid` in front of them
+    auto write_path = [&](int at, int32_t eid) {
+        int32_t *row = out + (size_t)at * k;
+        row[0] = eid;
+        for (int x = 2; x <= d; ++x) row[x - 1] = se[x];
+    };
     while (l <= d && found < max_paths) {
         const int x = sv[l];
         uint32_t j = sp[l];
-        const uint32_t hi = in_off[x + 1];
+        const uint32_t hi = a.in_off[x + 1];
         bool descended = false;
-        const unsigned long long *lv = levels + (size_t)(l - 1) * plane;
-        while (j < hi && found < max_paths) {
-            const uint32_t jj = j + (uint32_t)v_lane;
-            int s = 0, eid = 0;
-            bool ok = false;
-            if (jj < hi) {
-                s = in_sub[jj];
-                ok = (lv[(size_t)s * W + w] & bit) != 0ull;
-                if (ok && allow) ok = (allow[(size_t)in_rel[jj] * W + w] & bit) != 0ull;
-                if (ok) eid = in_eid[jj];
+        if (l == 1 && n_seeds > 0 && seed_edges < hi - j) {
+            __syncthreads();  // (the last reads of n_match and match)
+            if (t == 0) n_match = 0;
+            __syncthreads();
+            for (uint32_t p = t; p < seed_edges; p += NT) {
+                int r = 0;
+                while (s_end[r] <= p) ++r;
+                const uint32_t jj = s_lo[r] + (p - (r ? s_end[r - 1] : 0u));
+                if (a.out_obj[jj] != x) continue;
+                if (a.allow && !(a.allow[(size_t)a.out_rel[jj] * W + w] & bit)) continue;
+                const int m = atomicAdd(&n_match, 1);
+                if (m < kPathMatches) match[m] = a.out_eid[jj];
             }
-            unsigned long long m = __ballot(ok);
-            if (m == 0ull) {
-                j += 64;
+            __syncthreads();
+            const int n = n_match;
+            if (n <= kPathMatches) {
+                for (int m = t; m < n; m += NT) {
+                    const int32_t eid = match[m];
+                    int rank = 0;
+                    for (int y = 0; y < n; ++y) rank += match[y] < eid;
+                    if (found + rank < max_paths) write_path(found + rank, eid);
+                }
+                found = min(max_paths, found + n);
+                ++l;
                 continue;
             }
-            if (l == 1) {  // every admissible entry of the chunk ends a path, in this order
-                while (m && found < max_paths) {
-                    const int f = __builtin_ctzll(m);
-                    m &= m - 1;
-                    int32_t *row = out + (size_t)found * k;
-                    for (int a = 2 + v_lane; a <= d; a += 64) row[a - 1] = se[a];
-                    const int ef = __shfl(eid, f);
-                    if (v_lane == 0) row[0] = ef;
-                    ++found;
-                }
-                j += 64;
-            } else {  // take the first one and go down; the rest of the row is tried after coming back
-                const int f = __builtin_ctzll(m);
-                se[l] = __shfl(eid, f);
-                sp[l] = j + (uint32_t)f + 1u;
-                const int sf = __shfl(s, f);
-                sv[l - 1] = sf;
-                sp[l - 1] = in_off[sf];
-                --l;
-                descended = true;
-                break;
+        }
+        const unsigned long long *lv = a.levels + (size_t)(l - 1) * a.plane;
+        const uint32_t *act = a.act + (size_t)(l - 1) * a.actw;
+        int steps = 1;  // entries per lane of the next step
+        while (j < hi && found < max_paths) {
+            int32_t s[U];
+            bool ok[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t jj = j + (uint32_t)(u * NT + t);
+                ok[u] = u < steps && jj < hi;
+                s[u] = ok[u] ? a.in_sub[jj] : 0;
             }
+            if (a.allow) {
+                int r[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) r[u] = ok[u] ? a.in_rel[j + (uint32_t)(u * NT + t)] : 0;
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (ok[u]) ok[u] = (a.allow[(size_t)r[u] * W + w] & bit) != 0ull;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (ok[u]) ok[u] = (act[s[u] >> 5] >> (s[u] & 31)) & 1u;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (ok[u]) ok[u] = (lv[(size_t)s[u] * W + w] & bit) != 0ull;
+            unsigned long long mine[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                mine[u] = __ballot(ok[u]);
+                if (lane() == 0) hit[buf][u][wave] = mine[u];
+            }
+            __syncthreads();  // the other half of `hit` is written next: no barrier needed after the reads
+            if (l == 1) {
+                int before = found;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    int at = before;
+                    for (int y = 0; y < NW; ++y) {
+                        const int c = __popcll(hit[buf][u][y]);
+                        if (y < wave) at += c;
+                        before += c;
+                    }
+                    if (ok[u]) {
+                        at += __popcll(mine[u] & ((1ull << lane()) - 1ull));
+                        if (at < max_paths) write_path(at, a.in_eid[j + (uint32_t)(u * NT + t)]);
+                    }
+                }
+                found = min(max_paths, before);
+            } else {  // take the first one and go down; the rest of the row is tried after coming back
+                int pos = -1;
+                for (int y = U * NW - 1; y >= 0; --y) {
+                    const unsigned long long m = hit[buf][y / NW][y % NW];
+                    if (m) pos = y * 64 + __builtin_ctzll(m);
+                }
+                if (pos >= 0) {
+                    if (t == 0) {
+                        const uint32_t jj = j + (uint32_t)pos;
+                        const int32_t sf = a.in_sub[jj];
+                        se[l] = a.in_eid[jj];
+                        sp[l] = jj + 1u;
+                        sv[l - 1] = sf;
+                        sp[l - 1] = a.in_off[sf];
+                    }
+                    buf ^= 1;
+                    --l;
+                    descended = true;
+                    __syncthreads();
+                    break;
+                }
+            }
+            buf ^= 1;
+            j += (uint32_t)(steps * NT);
+            steps = U;
         }
         if (!descended) ++l;  // this vertex's row is exhausted: back to the vertex after it
     }
-    if (v_lane == 0) path_count[i] = found;
+    if (t == 0) a.path_count[i] = found;
 }
 
 }  // namespace lkg
 
 using namespace lkg;
 
-// Launches the listing kernel with the three depth-first stacks (vertex, next row position,
-// chosen edge; n_pairs * max(k, 1) int32 each) laid out one after another in `ws`.
+// `may_allocate`: the triple indices of SUB's rows may be built on this call (4 bytes per triple, kept
+// with the graph); without them the seeds' side is not used.
 static logoskg_status launch_paths(logoskg_graph *g, const logoskg_result *r, const int32_t *query_idx,
                                    const int32_t *target, const int32_t *length, int64_t n_pairs, int32_t max_paths,
-                                   int32_t *path_count, int32_t *path_edges, void *ws, hipStream_t st) {
-    const int k = r->k;
+                                   int32_t *path_count, int32_t *path_edges, bool may_allocate, hipStream_t st) {
     r->last_stream = st;
-    const size_t per = (size_t)n_pairs * (size_t)std::max(k, 1) * 4;
-    int32_t *sv = (int32_t *)ws;
-    uint32_t *sp = (uint32_t *)((char *)ws + per);
-    int32_t *se = (int32_t *)((char *)ws + 2 * per);
+    PathArgs a = {};
     // a sharded graph keeps its object-sorted triples in pinned host memory: the kernel reads the
     // rows it walks from there
-    const int32_t *in_sub = g->in_sub, *in_eid = g->in_eid;
-    const uint16_t *in_rel = g->in_rel;
-    if (g->num_shards > 1 && !shard_in_arrays(g, &in_sub, &in_rel, &in_eid)) {
+    a.in_sub = g->in_sub; a.in_eid = g->in_eid; a.in_rel = g->in_rel;
+    if (g->num_shards > 1 && !shard_in_arrays(g, &a.in_sub, &a.in_rel, &a.in_eid)) {
         set_error("the object-sorted triples of the sharded graph are not available");
         return LOGOSKG_EINTERNAL;
     }
+    if (g->num_shards <= 1 && r->seeds) {
+        if (may_allocate && ensure_out_eid(g, st) != LOGOSKG_OK) (void)hipGetLastError();  // no room: the object rows serve
+        a.seed_off = r->seed_off; a.seeds = r->seeds;
+        a.out_off = g->out_off; a.out_obj = g->out_obj; a.out_rel = g->out_rel; a.out_eid = g->out_eid;
+    }
+    a.Q = r->Q; a.k = r->k; a.W = r->W; a.E = g->E;
+    a.plane = r->Epad * r->W; a.actw = r->Epad / 32;
+    a.levels = r->levels; a.act = r->act; a.allow = r->has_mask ? r->allow : nullptr;
+    a.in_off = g->in_off;
+    a.query_idx = query_idx; a.target = target; a.length = length;
+    a.max_paths = max_paths; a.path_count = path_count; a.path_edges = path_edges;
     ProfScope ps(g->prof, KK_PATHS, st);
-    k_paths<<<dim3((unsigned)((n_pairs + 3) / 4)), dim3(256), 0, st>>>(
-        n_pairs, r->Q, k, r->W, g->E, r->Epad * r->W, (const unsigned long long *)r->levels,
-        r->has_mask ? (const unsigned long long *)r->allow : nullptr, g->in_off, in_sub, in_rel, in_eid,
-        query_idx, target, length, max_paths, path_count, path_edges, sv, sp, se);
+    // Wavefronts per pair.  The GPU holds 8,192 wavefronts: few pairs get many each (a hub row is then
+    // scanned by all of them), many pairs fill it with one each and short rows waste nothing.  (4,096
+    // pairs: 0.65 ms with four each, 0.96 ms with sixteen.)
+    // (a launch takes fewer than 2^32 threads)
+    for (int64_t first = 0; first < n_pairs; first += 1ll << 25) {
+        const dim3 grid((unsigned)std::min<int64_t>(n_pairs - first, 1ll << 25));
+        a.first_pair = first;
+        if (n_pairs <= kPathWidePairs) k_paths<16><<<grid, dim3(1024), 0, st>>>(a);
+        else if (n_pairs <= kPathNarrowPairs) k_paths<4><<<grid, dim3(256), 0, st>>>(a);
+        else k_paths<1><<<grid, dim3(64), 0, st>>>(a);
+    }
     LKG_HIP(hipGetLastError());
     return LOGOSKG_OK;
 }
@@ -166,44 +312,14 @@ static logoskg_status list_paths(logoskg_graph *g, const logoskg_result *r, cons
     if (n_pairs == 0) return LOGOSKG_OK;
     LKG_HIP(hipSetDevice(g->device));
     hipStream_t st = (hipStream_t)stream;
-    void *ws = nullptr;
-    LKG_TRY(g->pool.alloc(&ws, (size_t)n_pairs * (size_t)std::max(r->k, 1) * 4 * 3));
-    logoskg_status s = launch_paths(g, r, query_idx, target, length, n_pairs, max_paths, path_count, path_edges, ws, st);
-    hipError_t e2 = hipStreamSynchronize(st);  // the workspace goes back to the pool below
-    g->pool.release(ws);
-    LKG_TRY(s);
-    LKG_HIP(e2);
+    LKG_TRY(launch_paths(g, r, query_idx, target, length, n_pairs, max_paths, path_count, path_edges, true, st));
+    LKG_HIP(hipStreamSynchronize(st));
     return LOGOSKG_OK;
 }
 
 // ---------------------------------------------------------------- listing without any allocation
-// The depth-first stacks of logoskg_paths_static live in this array instead of a block from the
-// graph's pool.  Every GPU the library runs on holds its own copy until the process ends; in host
-// code the array's name is only a handle for hipGetSymbolAddress, the address that kernels and
-// copies use is looked up once per device and kept in static_stack_ptr.
-static __device__ __align__(256) unsigned char static_stacks[LOGOSKG_STATIC_PATH_SLOTS * 4 * 3];
-
-constexpr int kMaxDevices = 64;
-static void *static_stack_ptr[kMaxDevices];
-static std::mutex static_stack_lock;
-
-// Address of the calling device's copy of static_stacks (`device` must be current).
-static logoskg_status static_stack_address(int device, void **out) {
-    if (device < 0 || device >= kMaxDevices) {
-        set_error("device ordinal %d is outside [0, %d)", device, kMaxDevices);
-        return LOGOSKG_EINVAL;
-    }
-    std::lock_guard<std::mutex> lock(static_stack_lock);
-    if (!static_stack_ptr[device]) {
-        void *p = nullptr;
-        LKG_HIP(hipGetSymbolAddress(&p, HIP_SYMBOL(static_stacks)));
-        if (!p) { set_error("hipGetSymbolAddress returned a null address"); return LOGOSKG_EDEVICE; }
-        static_stack_ptr[device] = p;
-    }
-    *out = static_stack_ptr[device];
-    return LOGOSKG_OK;
-}
-
+// logoskg_paths needs no working memory beside the block's LDS, but may build the triple indices of
+// SUB's rows on first use and waits for the stream; logoskg_paths_static does neither.
 extern "C" logoskg_status logoskg_paths_static(logoskg_graph *g, const logoskg_result *r, const int32_t *query_idx,
                                                const int32_t *target, int64_t n_pairs, int32_t max_paths,
                                                int32_t *path_count, int32_t *path_edges, void *stream) {
@@ -221,10 +337,7 @@ extern "C" logoskg_status logoskg_paths_static(logoskg_graph *g, const logoskg_r
     }
     if (n_pairs == 0) return LOGOSKG_OK;
     LKG_HIP(hipSetDevice(g->device));
-    void *ws = nullptr;
-    LKG_TRY(static_stack_address(g->device, &ws));
-    // every stack entry is written before it is read, so nothing has to be cleared between calls
-    return launch_paths(g, r, query_idx, target, nullptr, n_pairs, max_paths, path_count, path_edges, ws,
+    return launch_paths(g, r, query_idx, target, nullptr, n_pairs, max_paths, path_count, path_edges, false,
                         (hipStream_t)stream);
 }
 

@@ -1,0 +1,60 @@
+"""Path listing where it can go wrong: rows longer than a scan step, each number of wavefronts per
+pair, the seeds' side with repeated seeds, too many seeds and more matches than its table holds."""
+import numpy as np
+import pytest
+
+import kggen
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def hub_graph(rng, E, R, T):
+    """Half of the triples end in four hubs (rows of thousands of entries); entity 0 reaches hub 1 through
+    300 relations."""
+    s, r, o = rng.integers(0, E, T), rng.integers(0, R, T), rng.integers(0, E, T)
+    o[: T // 2] = 1 + rng.integers(0, 4, T // 2)
+    s[: T // 4] = 1 + rng.integers(0, 40, T // 4)
+    s = np.concatenate([s, np.zeros(300, np.int64)])
+    r = np.concatenate([r, np.arange(300)])
+    o = np.concatenate([o, np.ones(300, np.int64)])
+    perm = rng.permutation(s.shape[0])
+    return s[perm].astype(np.int32), r[perm].astype(np.int32), o[perm].astype(np.int32)
+
+
+@pytest.mark.parametrize("share", [None, 0.5, 0.02])  # of the relations on a query's whitelist
+@pytest.mark.parametrize("max_paths", [16, 3])
+def test_long_rows_every_width_and_both_sides(share, max_paths):
+    import paper_2604_18913_amd as lkg
+    rng = np.random.default_rng(11)
+    E, R, T, Q, k = 3000, 600, 40000, 70, 3
+    s, r, o = hub_graph(rng, E, R, T)
+    lists = [np.array([0, 0, 7]), np.array([0])]                       # a repeated seed; the parallel triples
+    lists += [rng.integers(0, E, 100) for _ in range(4)]               # more seeds than the seeds' side takes
+    lists += [rng.integers(0, E, rng.integers(1, 4)) for _ in range(Q - len(lists))]
+    off = np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int64)
+    seeds = np.concatenate(lists).astype(np.int32)
+    mask = None
+    if share is not None:
+        keep = rng.random((Q, R)) < share
+        keep[:2, :300] = True
+        mask = np.zeros((Q, (R + 63) // 64), np.uint64)
+        for w in range(R):
+            mask[:, w // 64] |= keep[:, w].astype(np.uint64) << np.uint64(w % 64)
+    g = lkg.Graph(s, r, o, E, R)
+    res = g.khop(off, seeds, k, mask)
+    ent, _, _ = res.fetch()
+    reached = res.offsets()
+    pq, pt = kggen.sample_reached_pairs(3, reached, ent.cpu().numpy(), 1500)
+    pq = np.concatenate([pq, [0, 0, 1, 1, 2, 3], rng.integers(0, Q, 200)]).astype(np.int32)
+    pt = np.concatenate([pt, [1, 2, 1, 3, 1, 1], rng.integers(0, E, 200)]).astype(np.int32)
+    cnt_o, edges_o = oracle.paths(E, s, r, o, off, seeds, k, pq, pt, max_paths, mask)
+    for n in (5, 1024, len(pq), 65536 + 7):  # 16, 16, 4 and 1 wavefronts per pair
+        at = np.arange(n) % len(pq)
+        if n == 5:
+            at = len(pq) - 201 - np.arange(5)
+        cnt, edges = g.paths(res, pq[at], pt[at], max_paths)
+        assert np.array_equal(cnt.cpu().numpy(), cnt_o[at])
+        assert np.array_equal(edges.cpu().numpy(), edges_o[at])
+    res.close()
+    g.close()
