@@ -293,8 +293,9 @@ logoskg_status logoskg_result_offsets(const logoskg_result *r, int64_t *reached_
  * process ends - and join `stream` before the call returns; measured, no gain.)  The
  * first call on a graph that asks for pred_edge with more than 256 queries
  * allocates a buffer of 4 KiB per object row of more than 32 entries (not
- * above 8 GiB; freed with the graph) and, on a resident graph, 4 bytes per
- * triple for the triple index of every entry of SUB.  On a sharded graph pred_edge streams the
+ * above 8 GiB; freed with the graph) and, on a resident graph built with
+ * host_build, 4 bytes per triple for the triple index of every entry of SUB
+ * (a device build keeps them).  On a sharded graph pred_edge streams the
  * object-sorted triples from pinned host memory.
  */
 logoskg_status logoskg_result_fetch(logoskg_result *r, int32_t q_begin, int32_t q_end,
@@ -333,9 +334,9 @@ logoskg_status logoskg_result_level_fetch(logoskg_result *r, int32_t h, int32_t 
  * count level h-1 (they replace the level counted by
  * logoskg_result_level_offsets) and keep the level's entity list, one int64
  * per entry and one or two int64 per 256 triples in device memory until the
- * result is freed or another range is prepared.  The first call on a graph
- * builds the triple indices of SUB's rows (4 bytes per triple in device
- * memory, freed with the graph).  On a sharded graph the kernels read SUB's
+ * result is freed or another range is prepared.  On a sharded or host-built
+ * graph the first call builds the triple indices of SUB's rows (4 bytes per
+ * triple in device memory, freed with the graph).  On a sharded graph the kernels read SUB's
  * rows from the pinned host copy of the shards in place; shards kept in files
  * (shard_dir) have no such copy: LOGOSKG_EINVAL.
  */
@@ -367,8 +368,8 @@ void logoskg_result_free(logoskg_result *r);
  * path_count[i] = number written (0 if the target is not reached; 1 empty
  * path if it is a seed).  All four arrays are device memory; path_edges is
  * int32[n_pairs][max_paths][k].  On a sharded graph the kernel reads the
- * object rows it walks from pinned host memory, in place.  On a resident graph
- * the first call builds the triple indices of SUB's rows (4 bytes per triple in
+ * object rows it walks from pinned host memory, in place.  On a host-built
+ * resident graph the first call builds the triple indices of SUB's rows (4 bytes per triple in
  * device memory, freed with the graph; without room for them the call does
  * without).  The call returns after `stream` has been synchronised.
  */

@@ -404,6 +404,10 @@ extern "C" logoskg_status logoskg_build(const int32_t *subj, const int32_t *rel,
         set_error("hipHostMalloc failed");
         return fail(LOGOSKG_ENOMEM);
     }
+    if (hipHostMalloc((void **)&g->h_small, sizeof(SmallReport), hipHostMallocDefault) != hipSuccess) {
+        set_error("hipHostMalloc failed");
+        return fail(LOGOSKG_ENOMEM);
+    }
     for (int i = 0; i < 2; ++i) {
         if (!(g->side[i] = helper_stream(g->device, i)) ||
             hipEventCreateWithFlags(&g->ev_join[i], hipEventDisableTiming) != hipSuccess) {
@@ -440,6 +444,7 @@ extern "C" void logoskg_graph_free(logoskg_graph *g) {
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     if (g->h_ctr) (void)hipHostFree(g->h_ctr);
+    if (g->h_small) (void)hipHostFree(g->h_small);
     g->pool.trim();
     delete g;
 }

@@ -101,7 +101,7 @@ logoskg_status sort_by(const int32_t *d_key, int64_t T, int32_t E, unsigned key_
 
 }  // namespace
 
-// Fills g->out_off/out_obj/out_rel and g->in_off/in_sub/in_rel/in_eid from host triple arrays;
+// Fills g->out_off/out_obj/out_rel/out_eid and g->in_off/in_sub/in_rel/in_eid from host triple arrays;
 // returns the two offset arrays to the host as well (row classes are built there).
 logoskg_status build_csr_on_device(logoskg_graph *g, const int32_t *subj, const int32_t *rel, const int32_t *obj,
                                    std::vector<uint32_t> *ooff, std::vector<uint32_t> *ioff) {
@@ -156,8 +156,10 @@ logoskg_status build_csr_on_device(logoskg_graph *g, const int32_t *subj, const 
     LKG_TRY(keep((void **)&g->out_off, ((size_t)E + 1) * 4));
     LKG_TRY(keep((void **)&g->out_obj, (size_t)T * 4));
     LKG_TRY(keep((void **)&g->out_rel, (size_t)T * 2));
-    LKG_TRY(sort_by(d_subj, T, E, key_bits, d_iota, d_keys, d_eid, g->out_off, d_tmp, tmp_bytes));
-    if (T > 0) k_gather_sub_rows<<<dim3(grid_for(T)), dim3(kBlock)>>>(d_eid, T, d_obj, d_rel, g->out_obj, g->out_rel);
+    LKG_TRY(keep((void **)&g->out_eid, (size_t)T * 4));
+    uint32_t *const d_out_eid = reinterpret_cast<uint32_t *>(g->out_eid);
+    LKG_TRY(sort_by(d_subj, T, E, key_bits, d_iota, d_keys, d_out_eid, g->out_off, d_tmp, tmp_bytes));
+    if (T > 0) k_gather_sub_rows<<<dim3(grid_for(T)), dim3(kBlock)>>>(d_out_eid, T, d_obj, d_rel, g->out_obj, g->out_rel);
     // OBJ: rows by object, triple indices kept as edge ids
     LKG_TRY(keep((void **)&g->in_off, ((size_t)E + 1) * 4));
     LKG_TRY(keep((void **)&g->in_sub, (size_t)T * 4));

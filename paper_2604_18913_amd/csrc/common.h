@@ -117,6 +117,20 @@ struct ShortRow {  // a CSR row with its bounds, so that a kernel needs no look-
     uint32_t begin, end;
 };
 
+// Small searches (small.hip): limits of what one block takes, and its report to the host.
+constexpr int kSmallEdges = 2048;     // triples pushed per hop (and seeds)
+constexpr int kSmallPairs = 1 << 15;  // (triple, query) pairs per hop
+constexpr int kSmallEntities = 4096;  // reached entities (a power of two)
+constexpr int kSmallHops = 16;
+enum { kSmallDone = 0, kSmallGoOn = 1, kSmallBad = 2 };
+struct SmallReport {
+    int status, err, hops, n_all;
+    int n_tail, n_seg;  // kSmallGoOn: rows of the frontier the general path goes on with
+    int rows[kSmallHops + 1], reached[kSmallHops + 1];
+    long long edges[kSmallHops + 1];
+    long long off[65];
+};
+
 struct RowClasses {             // device work lists over the object rows, split by degree
     ShortRow *tail = nullptr;   // rows with 1 .. kTailMaxDegree entries, descending degree
     PullSegment *seg = nullptr;  // segments of the longer rows, longest rows first
@@ -189,8 +203,8 @@ struct logoskg_graph {
     int32_t *in_sub = nullptr;   // [T]
     uint16_t *in_rel = nullptr;  // [T]
     int32_t *in_eid = nullptr;   // [T]
-    int32_t *out_eid = nullptr;  // [T] triple index of every entry of the subject-sorted CSR; built on
-                                 // first use by the active-triple export
+    int32_t *out_eid = nullptr;  // [T] triple index of every entry of the subject-sorted CSR: what the
+                                 // device build sorts by; else built on first use (ensure_out_eid)
     lkg::RowClasses in_rows;     // static row lists for the pull kernels
     int64_t n_out_rows = 0, n_out_hubs = 0;
 
@@ -200,6 +214,7 @@ struct logoskg_graph {
     int64_t fr_seg_cap = 0;
     unsigned long long *d_ctr = nullptr;  // device counters (see khop.hip)
     unsigned long long *h_ctr = nullptr;  // pinned host mirror
+    lkg::SmallReport *h_small = nullptr;  // pinned: written by k_small_search
 
     std::vector<int32_t> shard_of;  // host copy of the map P (empty when unsharded)
     std::vector<int64_t> shard_triples;
@@ -254,6 +269,11 @@ struct logoskg_result {
     unsigned long long *d_nact = nullptr;
     long long n_active = -1;       // length of the list (known after the count pass)
     std::vector<int64_t> reached_off;  // host copy [Q+1]
+    // a small search that ended in k_small_search: reached entities (ascending), offsets of the lists;
+    // small_n < 0 for every other result
+    long long *small_off = nullptr;
+    int32_t *small_ent = nullptr;
+    int small_n = -1, small_levels = 0;
     // the same bookkeeping for one level plane (logoskg_result_level_offsets)
     int level_counted = -1;
     uint16_t *lvl_tile_base = nullptr;
@@ -417,6 +437,11 @@ logoskg_status sorter_offsets(TripleSorter *s, bool by_object, std::vector<uint3
 logoskg_status sorter_subject_order(TripleSorter *s, const uint32_t *d_row_begin, int32_t *h_obj, uint16_t *h_rel);
 logoskg_status sorter_object_order(TripleSorter *s, int32_t *h_sub, uint16_t *h_rel, int32_t *h_eid);
 logoskg_status ensure_out_eid(logoskg_graph *g, hipStream_t st);
+// small.hip: *next_hop = the hop the general path goes on with (k + 1: none), the frontier's counters in g->h_ctr
+logoskg_status small_search(logoskg_graph *g, logoskg_result *r, const logoskg_query_batch *b, bool want_counts,
+                            bool force_push, int *next_hop, hipStream_t st);
+logoskg_status small_fetch(logoskg_result *r, int q0, int q1, int32_t *entity, uint8_t *hop, int32_t *pred,
+                           hipStream_t st);
 void drop_walk_tables(logoskg_result *r);
 void launch_lists(Profiler &prof, const FillArgs &a, int W, hipStream_t st);
 void launch_pred(Profiler &prof, const FillArgs &a, int W, long long n_hub_rows, long long n_other_rows, bool mask,

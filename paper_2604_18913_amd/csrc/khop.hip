@@ -994,7 +994,7 @@ extern "C" void logoskg_result_free(logoskg_result *r) {
     (void)hipSetDevice(g->device);
     drop_walk_tables(r);
     // levels follows visited and live follows act in one allocation each
-    void *ptrs[] = {r->visited, r->act, r->allow, r->seed_off, r->tile_base,
+    void *ptrs[] = {r->visited, r->act, r->allow, r->seed_off, r->small_off, r->tile_base,
                     r->super_base, r->mega_base, r->d_reached_off, r->lvl_tile_base, r->lvl_super_base,
                     r->lvl_mega_base, r->d_level_off, r->trip_ent, r->trip_off,
                     r->trip_chunk_entry, r->trip_chunk_first, r->tile_ent, r->cpos, r->act_chunk};
@@ -1079,29 +1079,39 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
             g->prof.acc[KK_CLEAR].units[3] += g->prof.on ? (long long)(plane * (size_t)(k + 2)) : 0;
         }
         if (!act_zero) KH(hipMemsetAsync(r->act, 0, act_bytes + live_bytes, st));
-        KH(hipMemsetAsync(g->d_ctr, 0, C_TOTAL * sizeof(unsigned long long), st));
     }
-    g->prof.begin(KK_SEED, st);
+    // Up to 64 queries with few seeds: the first hops - all of them when the search stays small - run in one
+    // launch (not where the caller asked for pulled hops or for the kernels' work counters).
+    const bool want_stats = g->prof.counters;
+    const bool want_counts = !(b->flags & LOGOSKG_NO_COUNTS);
+    const bool small = W == 1 && g->num_shards <= 1 && !want_stats && dir != LOGOSKG_DIR_PULL &&
+                       b->num_seeds <= kSmallEdges;
     if (r->has_mask) {
+        ProfScope ps(g->prof, KK_SEED, st);
         int n = g->R * W;
         k_allow<<<dim3((n + 255) / 256), dim3(256), 0, st>>>(r->Q, g->R, W, (g->R + 63) / 64,
                                                              (const unsigned long long *)b->rel_mask,
                                                              (unsigned long long *)r->allow);
     }
-    k_seed<<<dim3((r->Q + 255) / 256), dim3(256), 0, st>>>(r->Q, (long long)b->num_seeds,
-                                                           (const long long *)b->seed_off, b->seeds, g->E, W,
-                                                           (unsigned long long *)r->levels,
-                                                           (unsigned long long *)r->visited, r->act, g->d_ctr,
-                                                           r->seed_off, r->seeds);
-    g->prof.end(st);
-    KH(hipGetLastError());
-    const bool want_stats = g->prof.counters;
-    if ((s = census(g, r, 0, -1, false, st)) != LOGOSKG_OK) return fail(s);
-    if (g->h_ctr[C_ERR]) {
-        set_error("seed_off / seeds are inconsistent or out of range (device check, code %llu)", g->h_ctr[C_ERR]);
-        return fail(LOGOSKG_EINVAL);
+    int first_hop = 1;
+    if (small && (s = small_search(g, r, b, want_counts, dir == LOGOSKG_DIR_PUSH, &first_hop, st)) != LOGOSKG_OK) return fail(s);
+    if (first_hop <= k || !small) KH(hipMemsetAsync(g->d_ctr, 0, C_TOTAL * sizeof(unsigned long long), st));
+    if (!small) {
+        g->prof.begin(KK_SEED, st);
+        k_seed<<<dim3((r->Q + 255) / 256), dim3(256), 0, st>>>(r->Q, (long long)b->num_seeds,
+                                                               (const long long *)b->seed_off, b->seeds, g->E, W,
+                                                               (unsigned long long *)r->levels,
+                                                               (unsigned long long *)r->visited, r->act, g->d_ctr,
+                                                               r->seed_off, r->seeds);
+        g->prof.end(st);
+        KH(hipGetLastError());
+        if ((s = census(g, r, 0, -1, false, st)) != LOGOSKG_OK) return fail(s);
+        if (g->h_ctr[C_ERR]) {
+            set_error("seed_off / seeds are inconsistent or out of range (device check, code %llu)", g->h_ctr[C_ERR]);
+            return fail(LOGOSKG_EINVAL);
+        }
     }
-    for (int h = 1; h <= k; ++h) {
+    for (int h = first_hop; h <= k; ++h) {
         logoskg_hop_stats &hs = r->stats[h - 1];
         long long rows = (long long)g->h_ctr[C_NROWS];
         long long fedges = (long long)g->h_ctr[C_FEDGES];
@@ -1142,7 +1152,7 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
             hs.lines_gathered = fedges;
         }
     }
-    if (!(b->flags & LOGOSKG_NO_COUNTS)) {
+    if (want_counts && !r->has_counts) {
         if ((s = count_reached(r, st)) != LOGOSKG_OK) return fail(s);
     }
 #undef KH

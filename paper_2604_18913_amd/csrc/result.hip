@@ -1623,6 +1623,11 @@ extern "C" logoskg_status logoskg_result_fetch(logoskg_result *r, int32_t q0, in
     LKG_HIP(hipSetDevice(g->device));
     hipStream_t st = (hipStream_t)stream;
     r->last_stream = st;
+    if (r->small_n >= 0) {
+        if (!g->prof.counters && (!pred || ensure_out_eid(g, st) == LOGOSKG_OK))
+            return small_fetch(r, q0, q1, entity, hop, pred, st);
+        if (!r->tile_base) LKG_TRY(count_reached(r, st));  // the general kernels' tables (same offsets)
+    }
     const int W = r->W;
     FillArgs a = {};
     a.E = g->E; a.Q = r->Q; a.k = r->k; a.q0 = q0; a.q1 = q1; a.hub_min = g->hub_min;

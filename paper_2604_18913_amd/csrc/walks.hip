@@ -52,7 +52,7 @@ k_walk_seeds(int32_t E, int W, int w, unsigned long long bit, const unsigned lon
 // together (neighbouring rows are contiguous in OBJ, so a wavefront's loads share their lines).
 // Longer rows are left to k_walk_count_long.  One wavefront per 64 entities, row after row, took 1.0 ms
 // a hop on a 3.4M-triple graph whatever the level held (a 10^5-entry row is 1,500 turns of one
-// wavefront); count and page of 10^6 chains of three triples together went from 3.2 ms to 0.41 ms there.
+// wavefront); count and page of 10^6 chains of three triples together went from 3.2 ms to 0.68 ms there.
 template <bool MASK>
 __device__ __forceinline__ unsigned long long walk_entry(uint32_t j, int W, int w, unsigned long long bit,
                                                          const unsigned long long *__restrict__ allow,
