@@ -1179,6 +1179,25 @@ __global__ void __launch_bounds__(1024) k_pred_row(FillArgs a, long long first_r
     }
 }
 
+// Without the bit-sliced pass (W < 16, or k > 6) the row kernels write the lists themselves, and the
+// segments of a giant row cannot merge there: they merge in a buffer of the giant rows' lines (row_pred
+// of this launch), which this kernel moves to the list positions, a block per row.  (One block per
+// giant row instead: 350 us of a 1.06 ms call of 200 queries with whitelists on 3.4M triples; 80 us now, the call 0.80 ms.)
+template <int W>
+__global__ void __launch_bounds__(256) k_giant_lists(FillArgs a) {
+    constexpr int Qp = 64 * W;
+    __shared__ long long slot[Qp];
+    const int ev = a.rows[blockIdx.x];
+    row_slots<W>(a, ev, threadIdx.x >> 6, 4, slot);
+    __syncthreads();
+    const int32_t *line = a.row_pred + (size_t)blockIdx.x * Qp;
+    for (int q = threadIdx.x; q < Qp; q += 256) {
+        const int w = q >> 6;
+        const unsigned long long x = a.visited[(size_t)ev * W + w] & ~a.levels[(size_t)ev * W + w] & range_bits(a.q0, a.q1, w);
+        if ((x >> (q & 63)) & 1ull) a.pred[slot[q]] = line[q];  // (seeds have their -1 from the tile kernel)
+    }
+}
+
 // ---------------------------------------------------------------- traversed
 // traversed[q][h] += out-degree of every entity whose level-h bit of q is set
 template <int W>
@@ -1445,7 +1464,7 @@ static void launch_pred_wms(Profiler &prof, const FillArgs &a0, long long n_hub_
         // 16 wavefronts per row for the longest rows, 4 for the others: a row of a thousand entries
         // leaves most of a large block waiting at its barriers, and the smaller blocks disturb the
         // tile kernel less while both run
-        const long long giants = a.n_giant_rows < 0 ? n_hub_rows : std::min(a.n_giant_rows, n_hub_rows);
+        const long long giants = std::min(a.n_giant_rows, n_hub_rows);
         // and one block per hop level of a row: the levels are independent, and the longest row
         // sets the duration of the launch
         const unsigned levels = (unsigned)std::max(a.k, 1);
@@ -1461,8 +1480,20 @@ static void launch_pred_wms(Profiler &prof, const FillArgs &a0, long long n_hub_
                 if (n_hub_rows > giants)
                     k_pred_row<W, MASK, STATS, true, false, ONE><<<dim3((unsigned)(n_hub_rows - giants), levels), dim3(256), 0, st_hub>>>(
                         a, giants);
-            } else {  // straight into the lists
-                if (giants > 0)
+            } else {  // straight into the lists; the giant rows' segments merge in a buffer of their own first
+                logoskg_graph *g = static_cast<logoskg_graph *>(a.host_graph);
+                FillArgs b = a;
+                void *buf = nullptr;
+                if (giants > 0 && a.giant_seg_first && giants == a.n_giant_rows &&
+                    g->pool.alloc(&buf, (size_t)giants * Qp_of<W>() * sizeof(int32_t), st_hub) == LOGOSKG_OK) {
+                    b.row_pred = static_cast<int32_t *>(buf);
+                    k_fill_int<<<dim3((unsigned)((giants * Qp_of<W>() + 255) / 256)), dim3(256), 0, st_hub>>>(
+                        b.row_pred, giants * Qp_of<W>(), INT_MAX);
+                    k_pred_row<W, MASK, STATS, true, true, ONE><<<dim3((unsigned)a.n_giant_segs, levels), dim3(1024), 0, st_hub>>>(b, 0);
+                    k_giant_lists<W><<<dim3((unsigned)giants), dim3(256), 0, st_hub>>>(b);
+                    const bool zeroed[1] = {false};
+                    g->pool.release_after(&buf, zeroed, 1, st_hub);
+                } else if (giants > 0)
                     k_pred_row<W, MASK, STATS, false, false, ONE><<<dim3((unsigned)giants, levels), dim3(1024), 0, st_hub>>>(a, 0);
                 if (n_hub_rows > giants)
                     k_pred_row<W, MASK, STATS, false, false, ONE><<<dim3((unsigned)(n_hub_rows - giants), levels), dim3(256), 0, st_hub>>>(
@@ -1646,9 +1677,11 @@ extern "C" logoskg_status logoskg_result_fetch(logoskg_result *r, int32_t q0, in
     for (int h = 1; h <= r->k && h < 32; ++h)
         if ((long long)r->stats[(size_t)h - 1].frontier_edges * 100 >= g->T * (long long)kDensePullPercent)
             a.dense_levels |= 1u << h;
-    a.n_giant_rows = g->num_shards > 1 ? -1 : g->in_rows.n_giant;
-    a.giant_seg_first = g->num_shards > 1 ? nullptr : g->in_rows.giant_seg_first;
-    a.n_giant_segs = g->num_shards > 1 ? 0 : g->in_rows.n_giant_segs;
+    a.n_giant_rows = g->in_rows.n_giant;  // (a sharded graph: set per object range)
+    a.giant_seg_first = g->in_rows.giant_seg_first;
+    a.n_giant_segs = g->in_rows.n_giant_segs;
+    a.host_graph = g;
+    a.host_result = r;
     if (pred && W == 16) {
         LKG_TRY(prepare_row_pred(g, st));
         a.long_index = g->long_index;
@@ -1681,8 +1714,6 @@ extern "C" logoskg_status logoskg_result_fetch(logoskg_result *r, int32_t q0, in
                 levels |= 1u << h;
         if (levels && ensure_out_eid(g, st) == LOGOSKG_OK) {
             a.push_levels = levels;
-            a.host_graph = g;
-            a.host_result = r;
         }
     }
     a.stats_pred = counting ? g->d_ctr + C_STATS + 4 * KK_PRED : nullptr;

@@ -59,8 +59,11 @@ struct ShardSet {
     // staging buffers in chunks of whole 64-entity tiles
     int32_t *h_in_sub = nullptr, *h_in_eid = nullptr;
     uint16_t *h_in_rel = nullptr;
-    struct Chunk { long long tile_begin, tile_count; int64_t edge_begin, edge_count; long long row_begin, hub_count, row_count; };
+    struct Chunk { long long tile_begin, tile_count; int64_t edge_begin, edge_count; long long row_begin, hub_count, row_count;
+                   // its first n_giant long rows (>= kGiantRowMin entries): their segments in d_giant_first from giant_at
+                   long long n_giant = 0, giant_at = 0, n_giant_segs = 0; };
     std::vector<Chunk> chunks;
+    uint32_t *d_giant_first = nullptr;
     // pull work lists of every chunk (object range), concatenated on the device
     std::vector<RowClasses> pull_lists;
     ShortRow *d_tail = nullptr;
@@ -236,6 +239,7 @@ void free_shards(logoskg_graph *g) {
     if (ss->d_tail) (void)hipFree(ss->d_tail);
     if (ss->d_seg) (void)hipFree(ss->d_seg);
     if (ss->d_multi) (void)hipFree(ss->d_multi);
+    if (ss->d_giant_first) (void)hipFree(ss->d_giant_first);
     if (g->row_begin && g->row_begin != g->out_off) (void)hipFree(g->row_begin);
     if (g->shard_of_dev) (void)hipFree(g->shard_of_dev);
     g->row_begin = nullptr;
@@ -363,6 +367,25 @@ static logoskg_status build_in_chunks(logoskg_graph *g, ShardSet *ss, const int3
         g->in_rows.n_seg = (int64_t)seg.size();
         g->in_rows.n_multi = (int64_t)multi.size();
     }
+    {   // segments of every chunk's giant rows, for the predecessor pass (as object_row_classes does for a resident graph)
+        std::vector<uint32_t> first;
+        const uint32_t giant_min = (uint32_t)std::max(kGiantRowMin, g->hub_min);
+        for (ShardSet::Chunk &c : ss->chunks) {
+            c.giant_at = (long long)first.size();
+            first.push_back(0);
+            for (; c.n_giant < c.row_count; ++c.n_giant) {
+                const int32_t v = longrows[(size_t)(c.row_begin + c.n_giant)];
+                const uint32_t d = ioff[(size_t)v + 1] - ioff[v];
+                if (d < giant_min) break;
+                first.push_back(first.back() + (d + kGiantSegment - 1) / kGiantSegment);
+            }
+            c.n_giant_segs = first.back();
+        }
+        LKG_HIP(hipMalloc((void **)&ss->d_giant_first, std::max<size_t>(first.size(), 1) * sizeof(uint32_t)));
+        if (!first.empty())
+            LKG_HIP(hipMemcpy(ss->d_giant_first, first.data(), first.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
+        g->static_bytes += first.size() * sizeof(uint32_t);
+    }
     g->in_rows.n_long = (int64_t)longrows.size();
     LKG_HIP(hipMalloc((void **)&g->in_rows.longrows, std::max<size_t>(longrows.size(), 1) * sizeof(int32_t)));
     if (!longrows.empty())
@@ -415,6 +438,9 @@ logoskg_status sharded_pred(logoskg_graph *g, FillArgs *a, int W, bool mask, hip
         x.tile_count = c.tile_count;
         x.rows = g->in_rows.longrows + c.row_begin;
         x.row_base = c.row_begin;
+        x.n_giant_rows = c.n_giant;
+        x.giant_seg_first = ss->d_giant_first + c.giant_at;
+        x.n_giant_segs = c.n_giant_segs;
         launch_pred(g->prof, x, W, c.hub_count, c.row_count - c.hub_count, mask, st, st);
     };
     if (ss->n_slots >= ss->units()) {
