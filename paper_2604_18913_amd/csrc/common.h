@@ -95,6 +95,7 @@ constexpr int kDensePullPercent = 60;   // from this share of the triples leavin
 constexpr int kPredPushShare = 4;       // a level whose frontier holds at most T / this triples: long rows resolved from the subject side
 constexpr int kGiantSegment = 8192;     // a giant row is walked by one 16-wave block per this many entries
 constexpr int kGiantRowMin = 8192;      // hub rows from this size get a 16-wave block in the predecessor pass, smaller ones 4 waves
+constexpr size_t kRowPredBytes = (size_t)8 << 30;  // most the row buffer of the predecessor pass may take
 constexpr int kTileEntities = 64;       // entities per result tile (one wavefront of lanes)
 constexpr int kSuperTiles = 16;         // tiles per super tile (1024 entities)
 constexpr int kPredTiles = 4;           // tiles per block of the 16-word predecessor kernel
@@ -448,6 +449,7 @@ void launch_pred(Profiler &prof, const FillArgs &a, int W, long long n_hub_rows,
                  hipStream_t st_tiles, hipStream_t st_rows);
 logoskg_status sharded_pred(logoskg_graph *g, FillArgs *a, int W, bool mask, hipStream_t st);
 long long max_chunk_rows(const logoskg_graph *g);
+const RowClasses *joined_rows(const logoskg_graph *g);
 logoskg_status census(logoskg_graph *g, logoskg_result *r, int h, int shard, bool write_lists, hipStream_t st);
 // (prof_kind: the kernel class the launch is timed under)
 logoskg_status census_lists(logoskg_graph *g, logoskg_result *r, int h, int shard, hipStream_t st,

@@ -1228,12 +1228,13 @@ __global__ void k_traversed(int32_t E, int Q, int k, long long plane, long long 
 }
 
 // The list of a result's active entities and their positions in it, built once per result.  The
-// tiles of every count / list / predecessor kernel of a resident graph are cut from this list.
-// A sharded graph keeps tiles of consecutive ids: its predecessor pass works on ranges of ids,
-// the ranges its object-sorted triples are streamed in.
+// tiles of every count / list / predecessor kernel of a resident graph (or of a sharded one whose
+// predecessor pass runs in one piece) are cut from this list.  Other sharded graphs keep tiles of
+// consecutive ids: their predecessor pass works on ranges of ids, the ranges the object-sorted triples
+// are streamed in.
 static logoskg_status ensure_active_list(logoskg_result *r, hipStream_t st) {
     logoskg_graph *g = r->g;
-    if (r->tile_ent || g->num_shards > 1) return LOGOSKG_OK;
+    if (r->tile_ent || (g->num_shards > 1 && !joined_rows(g))) return LOGOSKG_OK;
     const long long actw = r->Epad / 32, nchunks = (actw + kActChunkWords - 1) / kActChunkWords;
     LKG_TRY(g->pool.alloc((void **)&r->tile_ent, ((size_t)r->Epad + 64) * sizeof(int32_t), st));
     LKG_TRY(g->pool.alloc((void **)&r->cpos, (size_t)r->Epad * sizeof(int32_t), st));
@@ -1321,8 +1322,9 @@ logoskg_status prepare_row_pred(logoskg_graph *g, hipStream_t st) {
     }
     LKG_HIP(hipEventCreateWithFlags(&g->ev_rows, hipEventDisableTiming));
 
-    const long long rows = g->num_shards > 1 ? max_chunk_rows(g) : (long long)g->in_rows.n_long;
-    if (rows <= 0 || (size_t)rows * 4096 > ((size_t)8 << 30)) return LOGOSKG_OK;
+    const RowClasses *joined = joined_rows(g);  // (of a sharded graph)
+    const long long rows = g->num_shards > 1 && !joined ? max_chunk_rows(g) : (long long)g->in_rows.n_long;
+    if (rows <= 0 || (size_t)rows * 4096 > kRowPredBytes) return LOGOSKG_OK;
     LKG_HIP(hipMalloc((void **)&g->long_index, (size_t)g->E * sizeof(int32_t)));
     if (hipMalloc((void **)&g->row_pred, (size_t)rows * 4096) != hipSuccess) {
         (void)hipGetLastError();
@@ -1331,8 +1333,8 @@ logoskg_status prepare_row_pred(logoskg_graph *g, hipStream_t st) {
     }
     g->row_pred_rows = rows;
     LKG_HIP(hipMemsetAsync(g->long_index, 0xFF, (size_t)g->E * sizeof(int32_t), st));  // -1: not a long row
-    k_long_index<<<dim3((unsigned)((g->in_rows.n_long + 255) / 256)), dim3(256), 0, st>>>(g->in_rows.longrows,
-                                                                                         g->in_rows.n_long, g->long_index);
+    k_long_index<<<dim3((unsigned)((g->in_rows.n_long + 255) / 256)), dim3(256), 0, st>>>(
+        joined ? joined->longrows : g->in_rows.longrows, g->in_rows.n_long, g->long_index);
     LKG_HIP(hipGetLastError());
     return LOGOSKG_OK;
 }
