@@ -422,7 +422,7 @@ struct FillArgs {
     uint8_t *hop;
     int32_t *pred;
     unsigned long long *stats_pred, *stats_hub, *stats_mid;  // rows / edges / lines counters or NULL
-    int fuse_lists;  // the 16-word tile kernel also writes the entity and hop lists
+    int fuse_lists;  // the tile kernel also writes the entity and hop lists
     long long n_giant_rows;  // hub rows of the launch that get a 16-wave block per segment (the first ones)
     const uint32_t *giant_seg_first;  // [n_giant_rows + 1]
     long long n_giant_segs;

@@ -29,7 +29,6 @@
 #include <algorithm>
 #include <climits>
 #include <cstdlib>
-#include <type_traits>
 
 #include "common.h"
 
@@ -428,36 +427,12 @@ __device__ __forceinline__ int pred_resolve_unordered(uint32_t j0, int s, bool c
     return gathered;
 }
 
-// The same 64 in-edges when the fetched queries sit in one word `wq` of the 16-word lines: lane =
-// entry, every lane gathers that one word of its own candidate, and a 64 x 64 bit transpose turns
-// "entry -> queries it resolves" into "query -> entries that resolve it" (lane = query), whose lowest
-// set bit is the entry with the smallest edge id (edge ids ascend inside a row).  One round of 64
-// eight-byte gathers where the line-wide form needs sixteen rounds of four lines.  `rem` is
-// wavefront-uniform; emit(q, eid) runs on lane q for the queries resolved here.
-template <bool MASK, typename Emit>
-__device__ __forceinline__ int pred_resolve_word(uint32_t j0, int s, bool cand, int wq, const FillArgs &a,
-                                                 const unsigned long long *__restrict__ prev,
-                                                 unsigned long long &rem, Emit emit) {
-    unsigned long long l = 0;
-    if (cand) {
-        l = prev[(size_t)s * 16 + wq];
-        if (MASK) l &= a.allow[(size_t)a.in_rel[j0 + lane()] * 16 + wq];
-        l &= rem;
-    }
-    const int gathered = __popcll(__ballot(cand));
-    if (wave_any(l != 0)) {
-        const unsigned long long from = transpose64(l);  // lane q: the entries whose line holds query q
-        if (from) emit(lane(), a.in_eid[j0 + (uint32_t)(__ffsll((long long)from) - 1)]);
-        rem &= ~__ballot(from != 0);
-    }
-    return gathered;
-}
-
 // List positions of entity `ev` for every query: slot[q] = start of the tile's run in query q's
 // list + rank of the entity inside the tile.  Called by a whole wavefront for the words
-// w = w_first, w_first + w_step, ..
+// w = w_first, w_first + w_step, .. below w_end; slot[0] belongs to query q_first.
 template <int W>
-__device__ __forceinline__ void row_slots(const FillArgs &a, int ev, int w_first, int w_step, long long *slot) {
+__device__ __forceinline__ void row_slots(const FillArgs &a, int ev, int w_first, int w_step, long long *slot,
+                                          int w_end = W, int q_first = 0) {
     constexpr int Qp = 64 * W;
     long long at = ev;  // place of the entity in the tiles
     if (a.cpos) {       // an entity no query reached is not listed: it needs no positions
@@ -468,7 +443,7 @@ __device__ __forceinline__ void row_slots(const FillArgs &a, int ev, int w_first
     const int vi = (int)(at & 63), v = lane();
     const unsigned long long below = (1ull << vi) - 1ull;
     const long long ent_v = tile_entity(a.tile_ent, tile, v, a.E);
-    for (int w = w_first; w < W; w += w_step) {  // lane v = entity v of the tile
+    for (int w = w_first; w < w_end; w += w_step) {  // lane v = entity v of the tile
         unsigned long long x = ent_v >= 0 ? a.visited[(size_t)ent_v * W + w] & range_bits(a.q0, a.q1, w) : 0ull;
         int rank = 0;
         if (shfl64(x, vi) != 0ull)  // only queries that reached this entity matter
@@ -477,7 +452,7 @@ __device__ __forceinline__ void row_slots(const FillArgs &a, int ev, int w_first
         long long b = 0;
         if (q >= a.q0 && q < a.q1)
             b = super_start(a, tile / kSuperTiles, Qp, q) + a.tile_base[(size_t)tile * Qp + q] + rank;
-        slot[q] = b;
+        slot[q - q_first] = b;
     }
 }
 
@@ -494,15 +469,12 @@ __device__ __forceinline__ unsigned long long and_groups(unsigned long long x) {
 // query is kept in a table of the wavefront in LDS; the groups' masks are merged once per 64
 // entries, and after a level the table is written out (one contiguous store per 64 queries in the
 // row-buffer mode) and reset.
-// ONE (16-word lines, the fetched queries inside one word): every lane works on that word and
-// takes an entry of its own (pred_resolve_word).
-template <int W, bool MASK, bool STATS, bool BUF, bool ONE = false>
+template <int W, bool MASK, bool STATS, bool BUF>
 __global__ void __launch_bounds__(256) k_pred_wave(FillArgs a, long long first_row, long long n_rows_total) {
-    static_assert(!ONE || (W == 16 && !STATS), "the one-word form is for 16-word lines");
     constexpr int Qp = 64 * W;
     __shared__ long long slots[BUF ? 1 : 4][BUF ? 1 : Qp];
     __shared__ int smin_all[4][Qp];
-    const int wave = threadIdx.x >> 6, v = lane(), lw = ONE ? (a.q0 >> 6) : (v & (W - 1));
+    const int wave = threadIdx.x >> 6, v = lane(), lw = v & (W - 1);
     const long long idx = (long long)blockIdx.x * 4 + wave;
     long long n_rows = 0, n_edges = 0, n_lines = 0;
     if (idx < n_rows_total) {  // wave-uniform
@@ -530,22 +502,17 @@ __global__ void __launch_bounds__(256) k_pred_wave(FillArgs a, long long first_r
                     s = a.in_sub[j];
                     cand = dense || ((act_prev[s >> 5] >> (s & 31)) & 1u);
                 }
-                if constexpr (ONE) {
-                    n_lines += pred_resolve_word<MASK>(j0, s, cand, lw, a, prev, rem,
-                                                       [&](int q, int eid) { smin[lw * 64 + q] = eid; });
-                } else {
-                    n_lines += pred_resolve_unordered<W, MASK>(j0, s, cand, a, prev, rem, [&](unsigned long long hit, int eid) {
-                        for (unsigned long long m = hit; m; m &= m - 1)
-                            atomicMin(&smin[lw * 64 + (__ffsll((long long)m) - 1)], eid);
-                    });
-                    rem = and_groups<W>(rem);  // what any group has resolved is resolved
-                }
+                n_lines += pred_resolve_unordered<W, MASK>(j0, s, cand, a, prev, rem, [&](unsigned long long hit, int eid) {
+                    for (unsigned long long m = hit; m; m &= m - 1)
+                        atomicMin(&smin[lw * 64 + (__ffsll((long long)m) - 1)], eid);
+                });
+                rem = and_groups<W>(rem);  // what any group has resolved is resolved
                 n_edges += min((uint32_t)64, hi - j0);
                 if (!wave_any(rem != 0)) break;
             }
             __builtin_amdgcn_wave_barrier();
-            for (int i = ONE ? lw : 0; i < (ONE ? lw + 1 : W); ++i) {  // queries 64 i .. 64 i + 63: word i of the level, held by lane i
-                const unsigned long long word = ONE ? level : shfl64(level, i);
+            for (int i = 0; i < W; ++i) {  // queries 64 i .. 64 i + 63: word i of the level, held by lane i
+                const unsigned long long word = shfl64(level, i);
                 const int q = 64 * i + v;
                 if ((word >> v) & 1ull) {
                     out[BUF ? (long long)q : slot[q]] = smin[q];
@@ -562,6 +529,348 @@ __global__ void __launch_bounds__(256) k_pred_wave(FillArgs a, long long first_r
     }
 }
 
+__device__ __forceinline__ unsigned long long wave_or64(unsigned long long x) {
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) x |= shfl_xor64(x, m);
+    return x;
+}
+
+// ---- narrow lines: planes of one and four words, and a page of a 16-word batch that sits in one, two or four
+// aligned words (N words from word `off` of the line).  Such a piece of a line is one lane's load, so lane = entry of
+// the object row: 256 entries of a wavefront are gathered together, and a 64 x 64 bit transpose per chunk of
+// 64 entries and word turns "entry -> queries it resolves" into "query -> entries that resolve it" (lane =
+// query), whose lowest set bit is the entry with the smallest triple index.  No frontier bit is asked for
+// first: it would cost as much as the piece of the line (zero outside the level).
+// What bounds these kernels is the chain of loads per step (ids, pieces, then the next step) of the longest
+// rows, and for a page of a 16-word batch the lines themselves (64 queries of the hub-heavy 300M-triple graph:
+// giant rows 3.4 -> 2.0 ms; 63 queries over two words of 50M triples: row kernels 860 -> 730 us against whole lines).
+constexpr int kNarrowChunks = 4;
+
+template <int N>
+__device__ __forceinline__ void load_words(unsigned long long (&x)[N], const unsigned long long *__restrict__ p) {
+    if constexpr (N == 1) {
+        x[0] = *p;
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; i += 2) {
+            const ulonglong2 y = *reinterpret_cast<const ulonglong2 *>(p + i);  // (off is a multiple of N)
+            x[i] = y.x;
+            x[i + 1] = y.y;
+        }
+    }
+}
+
+__device__ __forceinline__ unsigned long long uniform64(unsigned long long x) {
+    return ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32)) << 32) |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+}
+
+// level h of the row's entity, restricted to the fetched queries; true when something is left of it
+template <int W, int N>
+__device__ __forceinline__ bool narrow_level(const FillArgs &a, int ev, int h, int off, unsigned long long (&lev)[N]) {
+    load_words<N>(lev, a.levels + (size_t)h * a.plane + (size_t)ev * W + off);
+    bool any = false;
+#pragma unroll
+    for (int w = 0; w < N; ++w) {
+        lev[w] = uniform64(lev[w] & range_bits(a.q0, a.q1, off + w));
+        any |= lev[w] != 0ull;
+    }
+    return any && !((a.push_levels >> h) & 1u);
+}
+
+// Entries first + c * stride + lane (below hi), c = 0 .. kNarrowChunks - 1, in ascending order: best[w] = the first
+// one that holds query 64 w + lane while it is in rem[w] (wavefront-uniform, cleared of what is resolved).
+template <int W, int N, bool MASK>
+__device__ __forceinline__ void narrow_resolve(const FillArgs &a, const unsigned long long *__restrict__ prev, int off,
+                                               uint32_t first, uint32_t stride, uint32_t hi,
+                                               unsigned long long (&rem)[N], uint32_t (&best)[N]) {
+    constexpr int C = kNarrowChunks;
+    unsigned long long l[C][N];
+    int s[C], rl[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const uint32_t j = first + c * stride + (uint32_t)lane();
+        s[c] = -1;
+        rl[c] = 0;
+        if (j < hi) {
+            s[c] = a.in_sub[j];
+            if (MASK) rl[c] = a.in_rel[j];
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+#pragma unroll
+        for (int w = 0; w < N; ++w) l[c][w] = 0;
+        if (s[c] >= 0) {
+            load_words<N>(l[c], prev + (size_t)s[c] * W + off);
+            if (MASK) {
+                unsigned long long m[N];
+                load_words<N>(m, a.allow + (size_t)rl[c] * W + off);
+#pragma unroll
+                for (int w = 0; w < N; ++w) l[c][w] &= m[w];
+            }
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+#pragma unroll
+        for (int w = 0; w < N; ++w) {
+            const unsigned long long x = l[c][w] & rem[w];
+            if (!wave_any(x != 0)) continue;
+            const unsigned long long from = transpose64(x);  // lane q: the entries whose line holds query q
+            if (from) best[w] = first + c * stride + (uint32_t)(__ffsll((long long)from) - 1);
+            rem[w] &= ~__ballot(from != 0);
+        }
+    }
+}
+
+template <int N>
+__device__ __forceinline__ bool any_left(const unsigned long long (&rem)[N]) {
+    unsigned long long x = 0;
+#pragma unroll
+    for (int w = 0; w < N; ++w) x |= rem[w];
+    return x != 0ull;
+}
+
+// Object rows of 33 .. hub_min - 1 entries, a wavefront per row (200 queries with whitelists, 3.4M triples:
+// 102 us with 4-lane groups that took every 16th candidate, a chain of five loads per 64 entries; 53 us now).
+template <int W, int N, bool MASK, bool STATS, bool BUF>
+__global__ void __launch_bounds__(256) k_narrow_wave(FillArgs a, long long first_row, long long n_rows_total) {
+    constexpr int Qp = 64 * W;
+    __shared__ long long slots[BUF ? 1 : 4][BUF ? 1 : 64 * N];
+    const int wave = threadIdx.x >> 6, v = lane(), off = W == 16 ? (a.q0 >> 6) & ~(N - 1) : 0;
+    const long long idx = (long long)blockIdx.x * 4 + wave;
+    if (idx >= n_rows_total) return;  // wavefront-uniform
+    const int ev = a.rows[first_row + idx];
+    long long *slot = slots[BUF ? 0 : wave];
+    int32_t *out = BUF ? a.row_pred + (size_t)(first_row + idx) * Qp : a.pred;
+    if (!BUF) row_slots<W>(a, ev, off, 1, slot, off + N, off * 64);
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t lo = a.in_off[ev], hi = a.in_off[ev + 1];
+    long long n_rows = 0, n_edges = 0;
+    for (int h = 1; h <= a.k; ++h) {
+        unsigned long long lev[N], rem[N];
+        uint32_t best[N];
+        if (!narrow_level<W, N>(a, ev, h, off, lev)) continue;
+#pragma unroll
+        for (int w = 0; w < N; ++w) {
+            rem[w] = lev[w];
+            best[w] = lo;
+        }
+        const unsigned long long *prev = a.levels + (size_t)(h - 1) * a.plane;
+        ++n_rows;
+        for (uint32_t j0 = lo; j0 < hi && any_left<N>(rem); j0 += 64 * kNarrowChunks) {
+            narrow_resolve<W, N, MASK>(a, prev, off, j0, 64, hi, rem, best);
+            n_edges += min((uint32_t)(64 * kNarrowChunks), hi - j0);
+        }
+#pragma unroll
+        for (int w = 0; w < N; ++w)
+            if ((lev[w] >> v) & 1ull) out[BUF ? (long long)((off + w) * 64 + v) : slot[w * 64 + v]] = a.in_eid[best[w]];
+    }
+    if (STATS && v == 0) {
+        if (n_rows) atomicAdd(&a.stats_mid[0], (unsigned long long)n_rows);
+        if (n_edges) atomicAdd(&a.stats_mid[1], (unsigned long long)n_edges);
+        if (n_edges) atomicAdd(&a.stats_mid[2], (unsigned long long)n_edges);  // a piece of a line per entry
+    }
+}
+
+// Longer object rows: a block per (row, hop level), or per segment of a giant row, as k_pred_row; the
+// wavefronts take chunks in turn and keep the smallest entry per query in LDS after every step.
+template <int W, int N, bool MASK, bool STATS, bool BUF, bool SEG>
+__global__ void __launch_bounds__(1024) k_narrow_row(FillArgs a, long long first_row) {
+    static_assert(!SEG || BUF, "segments merge in the row buffer");
+    constexpr int Qp = 64 * W, C = kNarrowChunks;
+    __shared__ long long slot[BUF ? 1 : 64 * N];
+    __shared__ unsigned int smin[64 * N];
+    __shared__ unsigned long long srem[N];
+    long long row_i = blockIdx.x;
+    uint32_t seg = 0;
+    if (SEG) {  // the giant row this segment belongs to: last row whose first segment is <= blockIdx.x
+        long long lo_r = 0, hi_r = a.n_giant_rows;
+        while (hi_r - lo_r > 1) {
+            const long long m = (lo_r + hi_r) >> 1;
+            if (a.giant_seg_first[m] <= blockIdx.x) lo_r = m; else hi_r = m;
+        }
+        row_i = lo_r;
+        seg = blockIdx.x - a.giant_seg_first[lo_r];
+    }
+    const int ev = a.rows[first_row + row_i];
+    const int t = threadIdx.x, wave = t >> 6, nw = blockDim.x >> 6, v = lane(), h = (int)blockIdx.y + 1;
+    const int off = W == 16 ? (a.q0 >> 6) & ~(N - 1) : 0;
+    unsigned long long lev[N];
+    if (!narrow_level<W, N>(a, ev, h, off, lev)) return;  // block-uniform
+    if (!BUF) row_slots<W>(a, ev, off + wave, nw, slot, off + N, off * 64);
+    int32_t *out = BUF ? a.row_pred + (size_t)(first_row + row_i) * Qp : a.pred;
+    const uint32_t row_lo = a.in_off[ev], row_hi = a.in_off[ev + 1];
+    const uint32_t lo = SEG ? row_lo + seg * (uint32_t)kGiantSegment : row_lo;
+    const uint32_t hi = SEG ? min(row_hi, lo + (uint32_t)kGiantSegment) : row_hi;
+    for (int q = t; q < 64 * N; q += blockDim.x) smin[q] = ~0u;
+    if (t < N) {
+        unsigned long long x = lev[0];
+#pragma unroll
+        for (int w = 1; w < N; ++w)
+            if (w == t) x = lev[w];
+        srem[t] = x;
+    }
+    __syncthreads();
+    const unsigned long long *prev = a.levels + (size_t)(h - 1) * a.plane;
+    long long n_edges = 0;
+    // the first step is one chunk per wavefront: on a dense frontier it resolves most queries
+    uint32_t span = 64u * nw;
+    for (uint32_t s0 = lo; s0 < hi; s0 += span, span = 64u * C * nw) {
+        unsigned long long rem[N];
+        uint32_t best[N];
+#pragma unroll
+        for (int w = 0; w < N; ++w) {
+            rem[w] = uniform64(srem[w]);
+            best[w] = ~0u;
+        }
+        if (!any_left<N>(rem)) break;  // the same words in every wavefront
+        const uint32_t step_hi = min(hi, s0 + span), first = s0 + 64u * wave;
+        if (first < step_hi) narrow_resolve<W, N, MASK>(a, prev, off, first, 64u * nw, step_hi, rem, best);
+        n_edges += wave == 0 ? (long long)(step_hi - s0) : 0;
+#pragma unroll
+        for (int w = 0; w < N; ++w)
+            if (best[w] != ~0u) atomicMin(&smin[w * 64 + v], best[w]);
+        __syncthreads();
+        if (v == 0) {
+#pragma unroll
+            for (int w = 0; w < N; ++w) atomicAnd(&srem[w], rem[w]);
+        }
+        __syncthreads();
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < N; ++w) {
+        if ((w % nw) != wave || !((lev[w] >> v) & 1ull)) continue;
+        const unsigned int at = smin[w * 64 + v];
+        if (SEG) {
+            if (at != ~0u) atomicMin(&out[(off + w) * 64 + v], a.in_eid[at]);
+        } else {
+            out[BUF ? (long long)((off + w) * 64 + v) : slot[w * 64 + v]] = a.in_eid[at];
+        }
+    }
+    if (STATS && t == 0) {
+        atomicAdd(&a.stats_hub[0], 1ull);
+        atomicAdd(&a.stats_hub[1], (unsigned long long)n_edges);
+        atomicAdd(&a.stats_hub[2], (unsigned long long)n_edges);
+    }
+}
+
+// Tiles of one- and four-word planes: a wavefront per word of a tile writes the entity and hop lists (lane =
+// entity; where a query reached many of the tile's entities, query by query with contiguous stores, else entity
+// by entity), then every entity whose object row has at most 32 entries is walked by a W-lane group, eight
+// entries gathered together and resolved in order.  Longer rows are left to the row kernels.
+template <int W, bool MASK, bool STATS>
+__global__ void __launch_bounds__(256) k_pred_narrow(FillArgs a) {
+    constexpr int TPB = 4 / W, U = 8;
+    static_assert(W == 1 || W == 4, "a block of four wavefronts");
+    __shared__ unsigned long long mT[4][64];  // per wavefront, i.e. (tile, word): entities each query reached
+    __shared__ long long base[4][64];         // and where its run of the tile starts in the lists
+    const int t = threadIdx.x, wave = t >> 6, v = lane();
+    const long long tile_rel = xcd_contiguous(blockIdx.x, gridDim.x) * TPB + wave / W;
+    const bool valid = tile_rel < a.tile_count;
+    const long long tile = a.tile_begin + tile_rel;
+    const int word = wave % W;
+    {
+        const int q = word * 64 + v;
+        long long b = 0;
+        if (valid && q >= a.q0 && q < a.q1)
+            b = super_start(a, tile / kSuperTiles, 64 * W, q) + a.tile_base[(size_t)tile * 64 * W + q];
+        base[wave][v] = b;
+        const long long e = valid ? tile_entity(a.tile_ent, tile, v, a.E) : -1;
+        unsigned long long vis = 0, x = 0;
+        const unsigned long long range = range_bits(a.q0, a.q1, word);
+        if (e >= 0) {
+            vis = a.visited[(size_t)e * W + word] & range;
+            x = a.levels[(size_t)e * W + word] & range;
+        }
+        mT[wave][v] = transpose64(vis);
+        __builtin_amdgcn_wave_barrier();
+        const unsigned long long below = (1ull << v) - 1ull;
+        auto put = [&](int qq, int h) {
+            const long long p = base[wave][qq] + __popcll(mT[wave][qq] & below);
+            a.entity[p] = (int32_t)e;
+            if (a.hop) a.hop[p] = (uint8_t)h;
+            if (h == 0) a.pred[p] = -1;  // seeds have no predecessor
+        };
+        unsigned long long left = vis;
+        for (int h = 0; h <= a.k; ++h) {
+            if (h > 0) {
+                if (!wave_any(left != 0)) break;  // every pair of the tile is written
+                x = left ? a.levels[(size_t)h * a.plane + (size_t)e * W + word] & range : 0ull;
+            }
+            left &= ~x;
+            if (!wave_any(x != 0)) continue;
+            const unsigned long long present = wave_or64(x);
+            if (wave_sum((long long)__popcll(x)) >= 8ll * __popcll(present)) {
+                for (unsigned long long m = present; m; m &= m - 1) {
+                    const int qq = __ffsll((long long)m) - 1;
+                    if ((x >> qq) & 1ull) put(qq, h);
+                }
+            } else {
+                for (unsigned long long m = x; m; m &= m - 1) put(__ffsll((long long)m) - 1, h);
+            }
+        }
+    }
+    __syncthreads();
+    const int part = W == 1 ? wave : (t & (W - 1)), lw = t & (W - 1);  // (tile, word) of the lane from here on
+    const int vi = W == 1 ? v : t / W;
+    const long long ev = valid ? tile_entity(a.tile_ent, tile, vi, a.E) : -1;  // (W = 4: one tile per block)
+    uint32_t lo = 0, hi = 0;
+    if (ev >= 0) {
+        lo = a.in_off[ev];
+        hi = a.in_off[ev + 1];
+    }
+    const unsigned long long below = (1ull << vi) - 1ull;
+    long long n_rows = 0, n_edges = 0;
+    if (hi > lo && hi - lo <= (uint32_t)kTailMaxDegree)
+        for (int h = 1; h <= a.k; ++h) {
+            unsigned long long rem = a.levels[(size_t)h * a.plane + (size_t)ev * W + lw] & range_bits(a.q0, a.q1, lw);
+            if (!group_any<W>(rem != 0)) continue;
+            const unsigned long long *prev = a.levels + (size_t)(h - 1) * a.plane;
+            if (lw == 0) ++n_rows;
+            for (uint32_t j0 = lo; j0 < hi; j0 += U) {
+                int s[U], rl[U];
+                unsigned long long l[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    s[u] = j0 + u < hi ? a.in_sub[j0 + u] : -1;
+                    rl[u] = MASK && j0 + u < hi ? a.in_rel[j0 + u] : 0;
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    l[u] = s[u] >= 0 ? prev[(size_t)s[u] * W + lw] : 0ull;
+                    if (MASK && s[u] >= 0) l[u] &= a.allow[(size_t)rl[u] * W + lw];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const unsigned long long hit = l[u] & rem;
+                    rem &= ~l[u];
+                    if (hit) {
+                        const int eid = a.in_eid[j0 + u];
+                        for (unsigned long long m = hit; m; m &= m - 1) {
+                            const int b = __ffsll((long long)m) - 1;
+                            a.pred[base[part][b] + __popcll(mT[part][b] & below)] = eid;
+                        }
+                    }
+                }
+                if (lw == 0) n_edges += min((uint32_t)U, hi - j0);
+                if (!group_any<W>(rem != 0)) break;
+            }
+        }
+    if (STATS) {
+        n_rows = wave_sum(n_rows);
+        n_edges = wave_sum(n_edges);
+        if (v == 0) {
+            if (n_rows) atomicAdd(&a.stats_pred[0], (unsigned long long)n_rows);
+            if (n_edges) atomicAdd(&a.stats_pred[1], (unsigned long long)n_edges);
+            if (n_edges) atomicAdd(&a.stats_pred[2], (unsigned long long)n_edges);
+        }
+    }
+}
+
+// 16-word planes without the bit-sliced pass (k > 6, or no room for its buffer).
 // One block per tile of 64 entities.  Phase 1: per query of the fetched range, the
 // mask of tile entities it reached (for ranks) and the list position of the
 // tile's run; seeds get -1.  Phase 2: every entity whose object row has at most
@@ -701,12 +1010,6 @@ __global__ void __launch_bounds__(64 * W) k_pred(FillArgs a) {
 // kernels: such an entity's predecessors come from row_pred, which those kernels fill before
 // this one starts (or, without that buffer, the row kernels write them to the lists themselves).
 constexpr int kSlicedMaxK = 6;     // hop + 1 <= 7 fits three bits
-
-__device__ __forceinline__ unsigned long long wave_or64(unsigned long long x) {
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) x |= shfl_xor64(x, m);
-    return x;
-}
 
 // G = lanes per entity: 16 (lane = word of the line), 4 for a fetch whose queries sit in four
 // aligned words or fewer (lane = word wb + lane % 4), which then walks four times as many entities
@@ -1116,11 +1419,9 @@ k_pred_emit(FillArgs a, const unsigned long long *__restrict__ codes, const unsi
 // (atomicMin; the line starts at INT_MAX).  A block that walks a whole 140,000-entry row is a chain
 // of dependent gathers that outlasts everything else in the launch; the segments of a row run side
 // by side, at the price of the early exit between them (it saved a quarter of the entries).
-// ONE: as in k_pred_wave.
-template <int W, bool MASK, bool STATS, bool BUF, bool SEG = false, bool ONE = false>
+template <int W, bool MASK, bool STATS, bool BUF, bool SEG = false>
 __global__ void __launch_bounds__(1024) k_pred_row(FillArgs a, long long first_row) {
     static_assert(!SEG || BUF, "segments merge in the row buffer");
-    static_assert(!ONE || (W == 16 && !STATS), "the one-word form is for 16-word lines");
     constexpr int Qp = 64 * W;
     constexpr int C = 4;  // 64-entry chunks per wavefront and step, loaded together
     __shared__ long long slot[BUF ? 1 : Qp];
@@ -1173,8 +1474,7 @@ __global__ void __launch_bounds__(1024) k_pred_row(FillArgs a, long long first_r
         uint32_t span = 64u * nw;
         for (uint32_t s0 = lo; s0 < hi; s0 += span, span = 64u * C * nw) {
             const uint32_t step_hi = min(hi, s0 + span);
-            const int lr = ONE ? (a.q0 >> 6) : lw;  // the word of the shared mask this lane works on
-            unsigned long long rem = srem[lr];
+            unsigned long long rem = srem[lw];
             if (!wave_any(rem != 0)) break;  // same decision in every wave
             const unsigned long long before = rem;
             // chunk c of this wavefront is chunk c * nw + wave of the step: a row shorter than a
@@ -1196,22 +1496,17 @@ __global__ void __launch_bounds__(1024) k_pred_row(FillArgs a, long long first_r
             for (int c = 0; c < C; ++c) {
                 uint32_t j0 = w0 + 64u * nw * c;
                 if (j0 < step_hi && wave_any(rem != 0)) {
-                    if constexpr (ONE) {
-                        n_lines += pred_resolve_word<MASK>(j0, sj[c], cj[c], lr, a, prev, rem,
-                                                           [&](int q, int eid) { atomicMin(&smin[lr * 64 + q], eid); });
-                    } else {
-                        n_lines += pred_resolve_unordered<W, MASK>(j0, sj[c], cj[c], a, prev, rem,
-                                                                   [&](unsigned long long hit, int eid) {
-                            for (unsigned long long m = hit; m; m &= m - 1)
-                                atomicMin(&smin[lw * 64 + (__ffsll((long long)m) - 1)], eid);
-                        });
-                    }
+                    n_lines += pred_resolve_unordered<W, MASK>(j0, sj[c], cj[c], a, prev, rem,
+                                                               [&](unsigned long long hit, int eid) {
+                        for (unsigned long long m = hit; m; m &= m - 1)
+                            atomicMin(&smin[lw * 64 + (__ffsll((long long)m) - 1)], eid);
+                    });
                     n_edges += min((uint32_t)64, step_hi - j0);
                 }
             }
-            unsigned long long resolved = before & ~rem;  // by this group of lanes (ONE: by this wavefront)
+            unsigned long long resolved = before & ~rem;  // by this group of lanes
             __syncthreads();
-            if (resolved && (!ONE || v == 0)) atomicAnd(&srem[lr], ~resolved);
+            if (resolved) atomicAnd(&srem[lw], ~resolved);
             __syncthreads();
         }
         __syncthreads();
@@ -1484,84 +1779,91 @@ __global__ void k_fill_int(int32_t *p, long long n, int32_t value) {
 template <int W>
 constexpr long long Qp_of() { return 64 * W; }
 
+// The row kernels: N words of the lines (narrow form), or N = 0: whole 16-word lines.
+template <int W, int N, bool MASK, bool STATS>
+static void launch_rows(Profiler &prof, const FillArgs &a, long long n_hub_rows, long long n_other_rows,
+                        hipStream_t st_tiles, hipStream_t st_hub) {
+    if (a.k == 0) return;  // seeds only: no level 1, no predecessors
+    // issued first: the tile kernel waits for it, and launched after the hub kernel it ran half as fast
+    if (n_other_rows > 0) {  // with row_pred: must precede the tile kernel on its stream
+        hipStream_t st = a.row_pred ? st_tiles : st_hub;
+        ProfScope ps(prof, KK_PRED_MID, st);
+        const dim3 grid((unsigned)((n_other_rows + 3) / 4)), block(256);
+        if constexpr (N > 0) {
+            if (a.row_pred) k_narrow_wave<W, N, MASK, STATS, true><<<grid, block, 0, st>>>(a, n_hub_rows, n_other_rows);
+            else k_narrow_wave<W, N, MASK, STATS, false><<<grid, block, 0, st>>>(a, n_hub_rows, n_other_rows);
+        } else {
+            if (a.row_pred) k_pred_wave<W, MASK, STATS, true><<<grid, block, 0, st>>>(a, n_hub_rows, n_other_rows);
+            else k_pred_wave<W, MASK, STATS, false><<<grid, block, 0, st>>>(a, n_hub_rows, n_other_rows);
+        }
+    }
+    if (n_hub_rows <= 0) return;
+    ProfScope ps(prof, KK_PRED_HUB, st_hub);
+    const long long giants = std::min(a.n_giant_rows, n_hub_rows), hubs = n_hub_rows - giants;
+    // one block per hop level of a row: the levels are independent, and the longest row sets the
+    // duration of the launch
+    const unsigned levels = (unsigned)a.k;
+    auto rows = [&](const FillArgs &x, long long first, long long n, unsigned threads) {
+        const dim3 grid((unsigned)n, levels), block(threads);
+        if constexpr (N > 0) {
+            if (x.row_pred) k_narrow_row<W, N, MASK, STATS, true, false><<<grid, block, 0, st_hub>>>(x, first);
+            else k_narrow_row<W, N, MASK, STATS, false, false><<<grid, block, 0, st_hub>>>(x, first);
+        } else {
+            if (x.row_pred) k_pred_row<W, MASK, STATS, true, false><<<grid, block, 0, st_hub>>>(x, first);
+            else k_pred_row<W, MASK, STATS, false, false><<<grid, block, 0, st_hub>>>(x, first);
+        }
+    };
+    if (giants > 0) {
+        // Segments merge in row_pred; without it (the row kernels write the lists themselves) in a buffer of
+        // the giants' own lines.  No room for that: a block per giant row.
+        FillArgs b = a;
+        void *buf = nullptr;
+        logoskg_graph *g = static_cast<logoskg_graph *>(a.host_graph);
+        const bool segments = a.giant_seg_first && giants == a.n_giant_rows;
+        if (segments && !a.row_pred &&
+            g->pool.alloc(&buf, (size_t)giants * Qp_of<W>() * sizeof(int32_t), st_hub) == LOGOSKG_OK)
+            b.row_pred = static_cast<int32_t *>(buf);
+        if (segments && b.row_pred) {
+            k_fill_int<<<dim3((unsigned)((giants * Qp_of<W>() + 255) / 256)), dim3(256), 0, st_hub>>>(
+                b.row_pred, giants * Qp_of<W>(), INT_MAX);
+            const dim3 grid((unsigned)a.n_giant_segs, levels), block(1024);
+            if constexpr (N > 0) k_narrow_row<W, N, MASK, STATS, true, true><<<grid, block, 0, st_hub>>>(b, 0);
+            else k_pred_row<W, MASK, STATS, true, true><<<grid, block, 0, st_hub>>>(b, 0);
+        } else {
+            rows(a, 0, giants, 1024);
+        }
+        if (buf) {
+            k_giant_lists<W><<<dim3((unsigned)giants), dim3(256), 0, st_hub>>>(b);
+            const bool zeroed[1] = {false};
+            g->pool.release_after(&buf, zeroed, 1, st_hub);
+        }
+    }
+    // Four wavefronts per row fill the GPU where there are rows enough (a row of a thousand entries leaves
+    // most of a large block waiting at its barriers); fewer rows than that get sixteen.
+    if (hubs > 0) rows(a, giants, hubs, hubs * levels < 2048 ? 1024u : 256u);
+}
+
 template <int W, bool MASK, bool STATS>
 static void launch_pred_wms(Profiler &prof, const FillArgs &a0, long long n_hub_rows, long long n_other_rows,
                             hipStream_t st_tiles, hipStream_t st_hub) {
     FillArgs a = a0;
     const bool mt = pred_uses_staged_kernel(a, W);
-    if (!mt) {
-        a.row_pred = nullptr;
-        a.fuse_lists = 0;
-    }
+    if (!mt) a.row_pred = nullptr;
     if (!mt || W != 16 || STATS) a.push_levels = 0;
-    // a fetch whose queries sit in one word of 16-word lines: the row kernels take an entry per lane
-    const bool one = W == 16 && !STATS && a.q1 > a.q0 && (a.q0 >> 6) == ((a.q1 - 1) >> 6);
-    // issued first: the tile kernel waits for it, and launched after the hub kernel it ran half as fast
-    if (n_other_rows > 0) {  // with row_pred: must precede the tile kernel on its stream
-        hipStream_t st = a.row_pred ? st_tiles : st_hub;
-        ProfScope ps(prof, KK_PRED_MID, st);
-        const dim3 gw((unsigned)((n_other_rows + 3) / 4));
+    if constexpr (W <= 4) {
+        launch_rows<W, W, MASK, STATS>(prof, a, n_hub_rows, n_other_rows, st_tiles, st_hub);
+    } else {
+        // a page of the batch inside one, two or four aligned words of the lines: the narrow form
         bool done = false;
-        if constexpr (W == 16 && !STATS) {
-            if (one) {
-                if (a.row_pred) k_pred_wave<W, MASK, STATS, true, true><<<gw, dim3(256), 0, st>>>(a, n_hub_rows, n_other_rows);
-                else k_pred_wave<W, MASK, STATS, false, true><<<gw, dim3(256), 0, st>>>(a, n_hub_rows, n_other_rows);
-                done = true;
-            }
+        if constexpr (!STATS) {
+            const int w0 = a.q0 >> 6, w1 = (a.q1 - 1) >> 6;
+            done = true;
+            if (w0 == w1) launch_rows<W, 1, MASK, STATS>(prof, a, n_hub_rows, n_other_rows, st_tiles, st_hub);
+            else if (w0 >> 1 == w1 >> 1) launch_rows<W, 2, MASK, STATS>(prof, a, n_hub_rows, n_other_rows, st_tiles, st_hub);
+            else if (w0 >> 2 == w1 >> 2) launch_rows<W, 4, MASK, STATS>(prof, a, n_hub_rows, n_other_rows, st_tiles, st_hub);
+            else done = false;
         }
-        if (done) {
-        } else if (a.row_pred) k_pred_wave<W, MASK, STATS, true><<<gw, dim3(256), 0, st>>>(a, n_hub_rows, n_other_rows);
-        else k_pred_wave<W, MASK, STATS, false><<<gw, dim3(256), 0, st>>>(a, n_hub_rows, n_other_rows);
-    }
-    if (n_hub_rows > 0) {  // writes the lists itself: independent of the other two kernels
-        ProfScope ps(prof, KK_PRED_HUB, st_hub);
-        // 16 wavefronts per row for the longest rows, 4 for the others: a row of a thousand entries
-        // leaves most of a large block waiting at its barriers, and the smaller blocks disturb the
-        // tile kernel less while both run
-        const long long giants = std::min(a.n_giant_rows, n_hub_rows);
-        // and one block per hop level of a row: the levels are independent, and the longest row
-        // sets the duration of the launch
-        const unsigned levels = (unsigned)std::max(a.k, 1);
-        auto rows = [&](auto one_c) {
-            constexpr bool ONE = decltype(one_c)::value;
-            if (a.row_pred) {  // into the row buffer, from which the list writer takes them
-                if (giants > 0 && a.giant_seg_first && giants == a.n_giant_rows) {
-                    k_fill_int<<<dim3((unsigned)((giants * Qp_of<W>() + 255) / 256)), dim3(256), 0, st_hub>>>(
-                        a.row_pred, giants * Qp_of<W>(), INT_MAX);
-                    k_pred_row<W, MASK, STATS, true, true, ONE><<<dim3((unsigned)a.n_giant_segs, levels), dim3(1024), 0, st_hub>>>(a, 0);
-                } else if (giants > 0)
-                    k_pred_row<W, MASK, STATS, true, false, ONE><<<dim3((unsigned)giants, levels), dim3(1024), 0, st_hub>>>(a, 0);
-                if (n_hub_rows > giants)
-                    k_pred_row<W, MASK, STATS, true, false, ONE><<<dim3((unsigned)(n_hub_rows - giants), levels), dim3(256), 0, st_hub>>>(
-                        a, giants);
-            } else {  // straight into the lists; the giant rows' segments merge in a buffer of their own first
-                logoskg_graph *g = static_cast<logoskg_graph *>(a.host_graph);
-                FillArgs b = a;
-                void *buf = nullptr;
-                if (giants > 0 && a.giant_seg_first && giants == a.n_giant_rows &&
-                    g->pool.alloc(&buf, (size_t)giants * Qp_of<W>() * sizeof(int32_t), st_hub) == LOGOSKG_OK) {
-                    b.row_pred = static_cast<int32_t *>(buf);
-                    k_fill_int<<<dim3((unsigned)((giants * Qp_of<W>() + 255) / 256)), dim3(256), 0, st_hub>>>(
-                        b.row_pred, giants * Qp_of<W>(), INT_MAX);
-                    k_pred_row<W, MASK, STATS, true, true, ONE><<<dim3((unsigned)a.n_giant_segs, levels), dim3(1024), 0, st_hub>>>(b, 0);
-                    k_giant_lists<W><<<dim3((unsigned)giants), dim3(256), 0, st_hub>>>(b);
-                    const bool zeroed[1] = {false};
-                    g->pool.release_after(&buf, zeroed, 1, st_hub);
-                } else if (giants > 0)
-                    k_pred_row<W, MASK, STATS, false, false, ONE><<<dim3((unsigned)giants, levels), dim3(1024), 0, st_hub>>>(a, 0);
-                if (n_hub_rows > giants)
-                    k_pred_row<W, MASK, STATS, false, false, ONE><<<dim3((unsigned)(n_hub_rows - giants), levels), dim3(256), 0, st_hub>>>(
-                        a, giants);
-            }
-        };
-        bool done = false;
-        if constexpr (W == 16 && !STATS) {
-            if (one) {
-                rows(std::true_type{});
-                done = true;
-            }
-        }
-        if (!done) rows(std::false_type{});
+        if (!done) launch_rows<W, 0, MASK, STATS>(prof, a, n_hub_rows, n_other_rows, st_tiles, st_hub);
     }
     if constexpr (W == 16 && !STATS) {
         if (a.push_levels) {  // the pushed levels of the long rows, from the subject side (behind the row kernels:
@@ -1635,8 +1937,12 @@ static void launch_pred_wms(Profiler &prof, const FillArgs &a0, long long n_hub_
         }
     } else if (a.tile_count > 0) {
         ProfScope ps(prof, KK_PRED, st_tiles);
-        dim3 grid((unsigned)((a.tile_count + 7) / 8 * 8)), block(64 * W);
-        k_pred<W, MASK, STATS><<<grid, block, 0, st_tiles>>>(a);
+        if constexpr (W <= 4) {
+            const long long blocks = (a.tile_count * W + 3) / 4;
+            k_pred_narrow<W, MASK, STATS><<<dim3((unsigned)((blocks + 7) / 8 * 8)), dim3(256), 0, st_tiles>>>(a);
+        } else {
+            k_pred<W, MASK, STATS><<<dim3((unsigned)((a.tile_count + 7) / 8 * 8)), dim3(64 * W), 0, st_tiles>>>(a);
+        }
     }
 }
 
@@ -1782,9 +2088,9 @@ extern "C" logoskg_status logoskg_result_fetch(logoskg_result *r, int32_t q0, in
     // fork and join, so it is not the default.
     const char *overlap_env = getenv("LOGOSKG_OVERLAP_FETCH");
     const bool serial = !(overlap_env && overlap_env[0] == '1');
-    // With predecessors on 16-word planes the tile kernel writes all three lists; otherwise the
-    // list kernel runs beside the predecessor kernels.
-    a.fuse_lists = pred && pred_uses_staged_kernel(a, W);
+    // With predecessors the tile kernel writes all three lists, except on 16-word planes without the
+    // bit-sliced pass, where the list kernel runs beside the predecessor kernels.
+    a.fuse_lists = pred && (W <= 4 || pred_uses_staged_kernel(a, W));
     const long long n_hub = g->in_rows.n_hub, n_mid = g->in_rows.n_long - g->in_rows.n_hub;
     // (nothing to fork for when the fused tile pass has no hub rows beside it)
     if (pred && g->num_shards <= 1 && !serial && (n_hub > 0 || !a.fuse_lists)) {
@@ -1817,7 +2123,7 @@ extern "C" logoskg_status logoskg_result_fetch(logoskg_result *r, int32_t q0, in
         LKG_HIP(hipStreamSynchronize(st));
         for (int kind : {KK_PRED, KK_PRED_HUB, KK_PRED_MID})  // (the two-kernel tile pass counts in its first kernel)
             for (int u = 0; u < 3; ++u)
-                g->prof.acc[kind == KK_PRED && a.fuse_lists ? KK_PRED_WALK : kind].units[u] +=
+                g->prof.acc[kind == KK_PRED && pred_uses_staged_kernel(a, W) ? KK_PRED_WALK : kind].units[u] +=
                     (long long)g->h_ctr[C_STATS + 4 * kind + u];
     }
     return LOGOSKG_OK;

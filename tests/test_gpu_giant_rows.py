@@ -18,7 +18,7 @@ def giant_graph(rng, E, R, degrees):
 
 
 @pytest.mark.parametrize("masked", [False, True])
-@pytest.mark.parametrize("Q, k", [(40, 2), (200, 3), (1000, 2), (300, 7)])
+@pytest.mark.parametrize("Q, k", [(40, 2), (200, 3), (1000, 2), (300, 7), (200, 0), (1000, 0)])
 @pytest.mark.parametrize("shards", [0, 3])
 def test_rows_of_several_segments(Q, k, shards, masked):
     import paper_2604_18913_amd as lkg
