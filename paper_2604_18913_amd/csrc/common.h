@@ -406,6 +406,11 @@ struct FillArgs {
     long long plane;   // words per plane
     long long actw;    // uint32 words per active bitmap
     const unsigned long long *visited, *levels, *allow;
+    // the level planes as the kernels of a page read them: `levels` itself, or the page's words of every line packed
+    // (k_page_planes).  Word w of entity e in level h: plv[h * pplane + e * pstride + w - pfirst]
+    const unsigned long long *plv;
+    long long pplane;
+    int pstride, pfirst;
     const uint32_t *act;
     const uint16_t *tile_base;
     const uint32_t *super_base, *mega_base;

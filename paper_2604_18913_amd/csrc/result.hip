@@ -568,7 +568,7 @@ __device__ __forceinline__ unsigned long long uniform64(unsigned long long x) {
 // level h of the row's entity, restricted to the fetched queries; true when something is left of it
 template <int W, int N>
 __device__ __forceinline__ bool narrow_level(const FillArgs &a, int ev, int h, int off, unsigned long long (&lev)[N]) {
-    load_words<N>(lev, a.levels + (size_t)h * a.plane + (size_t)ev * W + off);
+    load_words<N>(lev, a.plv + (size_t)h * a.pplane + (size_t)ev * a.pstride + (off - a.pfirst));
     bool any = false;
 #pragma unroll
     for (int w = 0; w < N; ++w) {
@@ -602,7 +602,7 @@ __device__ __forceinline__ void narrow_resolve(const FillArgs &a, const unsigned
 #pragma unroll
         for (int w = 0; w < N; ++w) l[c][w] = 0;
         if (s[c] >= 0) {
-            load_words<N>(l[c], prev + (size_t)s[c] * W + off);
+            load_words<N>(l[c], prev + (size_t)s[c] * a.pstride + (off - a.pfirst));
             if (MASK) {
                 unsigned long long m[N];
                 load_words<N>(m, a.allow + (size_t)rl[c] * W + off);
@@ -657,7 +657,7 @@ __global__ void __launch_bounds__(256) k_narrow_wave(FillArgs a, long long first
             rem[w] = lev[w];
             best[w] = lo;
         }
-        const unsigned long long *prev = a.levels + (size_t)(h - 1) * a.plane;
+        const unsigned long long *prev = a.plv + (size_t)(h - 1) * a.pplane;
         ++n_rows;
         for (uint32_t j0 = lo; j0 < hi && any_left<N>(rem); j0 += 64 * kNarrowChunks) {
             narrow_resolve<W, N, MASK>(a, prev, off, j0, 64, hi, rem, best);
@@ -713,7 +713,7 @@ __global__ void __launch_bounds__(1024) k_narrow_row(FillArgs a, long long first
         srem[t] = x;
     }
     __syncthreads();
-    const unsigned long long *prev = a.levels + (size_t)(h - 1) * a.plane;
+    const unsigned long long *prev = a.plv + (size_t)(h - 1) * a.pplane;
     long long n_edges = 0;
     // the first step is one chunk per wavefront: on a dense frontier it resolves most queries
     uint32_t span = 64u * nw;
@@ -1011,6 +1011,37 @@ __global__ void __launch_bounds__(64 * W) k_pred(FillArgs a) {
 // this one starts (or, without that buffer, the row kernels write them to the lists themselves).
 constexpr int kSlicedMaxK = 6;     // hop + 1 <= 7 fits three bits
 
+constexpr int kPageEntries = 2;  // entries one lane per entity gathers together (on packed planes 1: 2.4, 2: 2.4, 4: 2.7, 8: 3.3 ms)
+
+// A fetch of a page of a 16-word batch gathers one, two or four words of 128-byte lines, and HBM delivers the
+// line.  When the listed entities' lines are past what the infinity cache holds, the page's words of every level
+// are packed first, and the gathers run on arrays that it does hold: 20M entities, 64 queries, 160 MB instead of
+// 2.5 GB per level - packing 1.3 ms, row walk 4.3 -> 2.4 ms, giant rows 2.0 -> 1.7 ms.  Below that packing costs
+// more than it saves (1.4M listed of 5M entities, four words: 205 us against 60 us saved).
+constexpr long long kPageLines = 4ll << 20;             // listed entities from which the words are packed: 512 MB of lines
+constexpr size_t kPagePlaneBytes = (size_t)4 << 30;     // the packed planes take no more than this
+
+template <int N>
+__global__ void __launch_bounds__(256)
+k_page_planes(const unsigned long long *__restrict__ levels, long long plane, const uint32_t *__restrict__ act,
+              long long actw, long long Epad, int first, unsigned long long *__restrict__ out) {
+    const int h = blockIdx.y;
+    for (long long e = (long long)blockIdx.x * 256 + threadIdx.x; e < Epad; e += (long long)gridDim.x * 256) {
+        unsigned long long x[N];
+#pragma unroll
+        for (int w = 0; w < N; ++w) x[w] = 0;
+        if ((act[(size_t)h * actw + (e >> 5)] >> (e & 31)) & 1u)  // (the lines of the others are zero)
+            load_words<N>(x, levels + (size_t)h * plane + (size_t)e * 16 + first);
+        unsigned long long *dst = out + ((size_t)h * Epad + (size_t)e) * N;
+        if constexpr (N == 1) {
+            dst[0] = x[0];
+        } else {
+#pragma unroll
+            for (int w = 0; w < N; w += 2) *reinterpret_cast<ulonglong2 *>(dst + w) = make_ulonglong2(x[w], x[w + 1]);
+        }
+    }
+}
+
 // G = lanes per entity: 16 (lane = word of the line), 4 for a fetch whose queries sit in four
 // aligned words or fewer (lane = word wb + lane % 4), which then walks four times as many entities
 // per wavefront, or 1 for a fetch inside one word (lane = entity, word wb).
@@ -1031,9 +1062,15 @@ k_pred_walk(FillArgs a, unsigned long long *__restrict__ codes, unsigned long lo
     const unsigned long long range_w = range_bits(a.q0, a.q1, lw);
     unsigned long long visw = 0, lv0 = 0;
     uint32_t lo = 0, hi = 0;
+    // word lw of an entity in a level plane
+    auto level_word = [&](int h, long long e) -> unsigned long long {
+        if constexpr (G <= 4) return a.plv[(size_t)h * a.pplane + (size_t)e * a.pstride + (lw - a.pfirst)];
+        else return a.levels[(size_t)h * a.plane + (size_t)e * W + lw];
+    };
     if (ev >= 0) {
-        visw = a.visited[(size_t)ev * W + lw] & range_w;
-        lv0 = a.levels[(size_t)ev * W + lw] & range_w;
+        lv0 = level_word(0, ev) & range_w;
+        if (G > 4 || a.pstride == W) visw = a.visited[(size_t)ev * W + lw] & range_w;
+        else visw = ~0ull & range_w;  // (packed planes: the level words below decide)
         lo = a.in_off[ev];
         hi = a.in_off[ev + 1];
     }
@@ -1052,13 +1089,13 @@ k_pred_walk(FillArgs a, unsigned long long *__restrict__ codes, unsigned long lo
         unsigned long long pre[PRE];
 #pragma unroll
         for (int h = 1; h <= PRE; ++h)
-            pre[h - 1] = h <= a.k ? a.levels[(size_t)h * a.plane + (size_t)ev * W + lw] & range_w : 0ull;
+            pre[h - 1] = h <= a.k ? level_word(h, ev) & range_w : 0ull;
 #pragma unroll
         for (int h = 1; h <= HMAX; ++h) {
             if (h > a.k) break;
             unsigned long long rem;
             if (h <= PRE) rem = pre[h - 1];
-            else rem = a.levels[(size_t)h * a.plane + (size_t)ev * W + lw] & range_w;
+            else rem = level_word(h, ev) & range_w;
 #pragma unroll
             for (int b = 0; b < NB; ++b)
                 if (((h + 1) >> b) & 1) H[b] |= rem;
@@ -1067,6 +1104,44 @@ k_pred_walk(FillArgs a, unsigned long long *__restrict__ codes, unsigned long lo
             const unsigned long long *prev = a.levels + (size_t)(h - 1) * a.plane;
             const bool dense = !STATS && ((a.dense_levels >> h) & 1u);  // the line of an entity outside the level is zero
             if (STATS && gl == 0) ++n_rows;
+            if constexpr (G <= 4) {
+                // A page of the batch: eight entries of the row are gathered together (the group's lanes take a word
+                // each) and resolved in order.  No frontier bit is asked for first: it costs as much as the piece of a
+                // line.  With two and four lanes eight entries (63 queries over two words, 50M triples: 327 us with
+                // two at a time, 280 us now); a lane per entity takes kPageEntries, because what it gathers past the
+                // entry that resolves the last query is lost and its rate is that of the scattered sectors.
+                constexpr int U = G == 1 ? kPageEntries : 8;
+                for (int i0 = 0; i0 < (int)deg; i0 += U) {  // (i0 is the same in all lanes that are still in the loop)
+                    int sx[U], rx[U];
+                    unsigned long long l[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const bool in = i0 + u < (int)deg;
+                        sx[u] = in ? a.in_sub[lo + i0 + u] : -1;
+                        rx[u] = MASK && in ? a.in_rel[lo + i0 + u] : 0;
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        l[u] = sx[u] >= 0 ? level_word(h - 1, sx[u]) : 0ull;
+                        if (MASK && sx[u] >= 0) l[u] &= a.allow[(size_t)rx[u] * W + lw];
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const unsigned long long hit = l[u] & rem;
+                        rem &= ~l[u];
+                        const int at = i0 + u;
+#pragma unroll
+                        for (int b = 0; b < 5; ++b)
+                            if ((at >> b) & 1) J[b] |= hit;
+                    }
+                    if (STATS && gl == 0) {
+                        n_edges += min(U, (int)deg - i0);
+                        n_lines += min(U, (int)deg - i0);
+                    }
+                    if (!group_any<G>(rem != 0)) break;
+                }
+                continue;
+            }
             for (uint32_t j0 = lo; j0 < hi; j0 += G) {
                 const uint32_t j = j0 + gl;
                 int s = 0;
@@ -1850,6 +1925,7 @@ static void launch_pred_wms(Profiler &prof, const FillArgs &a0, long long n_hub_
     const bool mt = pred_uses_staged_kernel(a, W);
     if (!mt) a.row_pred = nullptr;
     if (!mt || W != 16 || STATS) a.push_levels = 0;
+    void *packed = nullptr;  // a page's words of the level planes
     if constexpr (W <= 4) {
         launch_rows<W, W, MASK, STATS>(prof, a, n_hub_rows, n_other_rows, st_tiles, st_hub);
     } else {
@@ -1857,6 +1933,26 @@ static void launch_pred_wms(Profiler &prof, const FillArgs &a0, long long n_hub_
         bool done = false;
         if constexpr (!STATS) {
             const int w0 = a.q0 >> 6, w1 = (a.q1 - 1) >> 6;
+            const int words = w0 == w1 ? 1 : w0 >> 1 == w1 >> 1 ? 2 : w0 >> 2 == w1 >> 2 ? 4 : 0;
+            // (one stream: the row and tile kernels read the packed planes)
+            if (words && mt && a.row_pred && a.tile_ent && a.n_listed >= kPageLines && st_hub == st_tiles) {
+                logoskg_graph *g = static_cast<logoskg_graph *>(a.host_graph);
+                const long long Epad = a.plane / 16;
+                const size_t bytes = (size_t)(a.k + 1) * Epad * words * 8;
+                if (bytes <= kPagePlaneBytes && g->pool.alloc(&packed, bytes, st_hub) == LOGOSKG_OK) {
+                    unsigned long long *dst = static_cast<unsigned long long *>(packed);
+                    const int first = w0 & ~(words - 1);
+                    ProfScope ps(prof, KK_PRED_WALK, st_hub);
+                    const dim3 grid((unsigned)std::min<long long>(16384, (Epad + 255) / 256), (unsigned)a.k + 1), block(256);
+                    if (words == 1) k_page_planes<1><<<grid, block, 0, st_hub>>>(a.levels, a.plane, a.act, a.actw, Epad, first, dst);
+                    else if (words == 2) k_page_planes<2><<<grid, block, 0, st_hub>>>(a.levels, a.plane, a.act, a.actw, Epad, first, dst);
+                    else k_page_planes<4><<<grid, block, 0, st_hub>>>(a.levels, a.plane, a.act, a.actw, Epad, first, dst);
+                    a.plv = dst;
+                    a.pplane = Epad * words;
+                    a.pstride = words;
+                    a.pfirst = first;
+                }
+            }
             done = true;
             if (w0 == w1) launch_rows<W, 1, MASK, STATS>(prof, a, n_hub_rows, n_other_rows, st_tiles, st_hub);
             else if (w0 >> 1 == w1 >> 1) launch_rows<W, 2, MASK, STATS>(prof, a, n_hub_rows, n_other_rows, st_tiles, st_hub);
@@ -1917,6 +2013,10 @@ static void launch_pred_wms(Profiler &prof, const FillArgs &a0, long long n_hub_
                     dim3 g1((unsigned)(((n + 3) / 4 + 7) / 8 * 8));  // 256 entities per block
                     if (a.k <= 2) k_pred_walk<2, MASK, STATS, 1><<<g1, dim3(256), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, w0);
                     else k_pred_walk<3, MASK, STATS, 1><<<g1, dim3(256), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, w0);
+                } else if (w0 >> 1 == (w0 + nw - 1) >> 1) {  // two aligned words
+                    dim3 g2((unsigned)(((n + 1) / 2 + 7) / 8 * 8));  // 128 entities per block
+                    if (a.k <= 2) k_pred_walk<2, MASK, STATS, 2><<<g2, dim3(256), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, w0 & ~1);
+                    else k_pred_walk<3, MASK, STATS, 2><<<g2, dim3(256), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, w0 & ~1);
                 } else if (w0 + nw <= wb + 4) {
                     dim3 g4((unsigned)((n + 7) / 8 * 8));  // 64 entities per block
                     if (a.k <= 2) k_pred_walk<2, MASK, STATS, 4><<<g4, dim3(256), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, wb);
@@ -1943,6 +2043,10 @@ static void launch_pred_wms(Profiler &prof, const FillArgs &a0, long long n_hub_
         } else {
             k_pred<W, MASK, STATS><<<dim3((unsigned)((a.tile_count + 7) / 8 * 8)), dim3(64 * W), 0, st_tiles>>>(a);
         }
+    }
+    if (packed) {
+        const bool zeroed[1] = {false};
+        static_cast<logoskg_graph *>(a.host_graph)->pool.release_after(&packed, zeroed, 1, st_tiles);
     }
 }
 
@@ -2027,6 +2131,7 @@ extern "C" logoskg_status logoskg_result_fetch(logoskg_result *r, int32_t q0, in
     a.tile_begin = 0; a.tile_count = a.ntiles;
     a.plane = r->Epad * W; a.actw = r->Epad / 32;
     a.visited = r->visited; a.levels = r->levels; a.allow = r->allow;
+    a.plv = a.levels; a.pplane = a.plane; a.pstride = W; a.pfirst = 0;
     a.act = r->act; a.tile_base = r->tile_base; a.super_base = r->super_base; a.mega_base = r->mega_base;
     a.reached_off = r->d_reached_off;
     a.in_off = g->in_off; a.in_sub = g->in_sub; a.in_eid = g->in_eid; a.in_rel = g->in_rel;
