@@ -85,6 +85,8 @@ private:
 };
 
 // ---------------------------------------------------------------- graph
+constexpr int kLevelCounters = 4;
+constexpr unsigned kCensusBlocks = 512;  // at most; three words each behind d_ctr's C_TOTAL
 constexpr int kTailMaxDegree = 32;      // rows up to this degree: one W-lane group per row
 constexpr int kPullSegment = 1024;      // longer object rows are cut into segments of this many
                                         // entries, one wavefront each
@@ -253,7 +255,8 @@ struct logoskg_result {
     unsigned long long *levels = nullptr;   // [k+1][Epad][W]
     uint32_t *act = nullptr;      // [k+1][Epad/32]: entity has a non-zero line in that level
     unsigned long long *allow = nullptr;    // [R][W] relation -> queries that may follow it
-    unsigned long long *live = nullptr;     // [k+1][16] queries whose level-h frontier has an out-edge
+    unsigned long long *live = nullptr;     // [k+1][16] queries whose level-h frontier has an out-edge, then
+                                            // [k+1][kLevelCounters] counters of the levels (khop.hip)
     long long *seed_off = nullptr;  // [Q+1] and the batch's seeds behind it (k_seed's copy), for the path listing
     int32_t *seeds = nullptr;
     // result-list bookkeeping (count pass): for every query, the number of reached
@@ -455,9 +458,8 @@ void launch_pred(Profiler &prof, const FillArgs &a, int W, long long n_hub_rows,
 logoskg_status sharded_pred(logoskg_graph *g, FillArgs *a, int W, bool mask, hipStream_t st);
 long long max_chunk_rows(const logoskg_graph *g);
 const RowClasses *joined_rows(const logoskg_graph *g);
-logoskg_status census(logoskg_graph *g, logoskg_result *r, int h, int shard, bool write_lists, hipStream_t st);
 // (prof_kind: the kernel class the launch is timed under)
-logoskg_status census_lists(logoskg_graph *g, logoskg_result *r, int h, int shard, hipStream_t st,
+logoskg_status census_lists(logoskg_graph *g, logoskg_result *r, int h, unsigned long long *ctr, hipStream_t st,
                             int prof_kind = KK_CENSUS);
 void launch_push_lists(logoskg_graph *g, logoskg_result *r, int h, const unsigned long long *hc,
                        const int32_t *obj, const uint16_t *rel, bool update, const int32_t *list_tail,

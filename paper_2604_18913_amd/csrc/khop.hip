@@ -27,6 +27,12 @@
 
 namespace lkg {
 
+// counters of a level (kLevelCounters words behind the live words): the append cursors of its push lists, the
+// census' sums, the error word of the seeds (level 0) and the blocks that have added theirs
+enum { L_CUR_TAIL = 0, L_CUR_SEG, L_ERR, L_TICKET };
+static_assert(L_TICKET < kLevelCounters && (int)L_CUR_TAIL == (int)C_NTAIL && (int)L_CUR_SEG == (int)C_NSEG,
+              "the push kernels read the cursors as C_NTAIL and C_NSEG");
+
 // ---------------------------------------------------------------- seeds, mask table
 __global__ void k_seed(int Q, long long num_seeds, const long long *__restrict__ seed_off,
                        const int32_t *__restrict__ seeds, int32_t E, int W,
@@ -38,7 +44,7 @@ __global__ void k_seed(int Q, long long num_seeds, const long long *__restrict__
     kept_off[q] = a;  // the result keeps a copy: the caller's arrays are borrowed for the call only
     if (q == Q - 1) kept_off[Q] = b;
     if (a < 0 || b < a || b > num_seeds || (q == 0 && a != 0) || (q == Q - 1 && b != num_seeds)) {
-        atomicOr(&ctr[C_ERR], 1ull);
+        atomicOr(&ctr[L_ERR], 1ull);
         return;
     }
     unsigned long long bit = 1ull << (q & 63);
@@ -46,7 +52,7 @@ __global__ void k_seed(int Q, long long num_seeds, const long long *__restrict__
         int32_t e = seeds[i];
         kept_seeds[i] = e;
         if ((uint32_t)e >= (uint32_t)E) {
-            atomicOr(&ctr[C_ERR], 2ull);
+            atomicOr(&ctr[L_ERR], 2ull);
             continue;
         }
         size_t idx = (size_t)e * W + (q >> 6);
@@ -72,73 +78,169 @@ __global__ void k_allow(int Q, int R, int W, int rel_words, const unsigned long 
 }
 
 // ---------------------------------------------------------------- frontier census
-// Turns the active bitmap of a level into the work lists of a push hop (short
-// subject rows; segments of the longer ones) and the counters the host needs
-// to pick the direction.
+// The census of a level's active bitmap gives the host what it needs to pick the direction: rows, triples and
+// work-list sizes of the frontier.  The lists themselves (short subject rows; segments of the longer ones) are
+// appended by a second kernel when the hop pushes.
 //
-// row_begin[e] is where the triples of subject e start in the edge arrays (equal
-// to out_off for a resident graph; shard-grouped order for a sharded one).  With
-// shard_of != NULL only the subjects of `shard` are listed (Algorithm 1, line 6:
-// restriction of the frontier to one sub-graph).
-__global__ void __launch_bounds__(256)
-k_census(const uint32_t *__restrict__ act, int32_t E, const uint32_t *__restrict__ out_off,
-         const uint32_t *__restrict__ row_begin, const uint8_t *__restrict__ shard_of, int shard, int write_lists,
-         int32_t *list_tail, RowSegment *list_seg, unsigned long long *ctr) {
-    // one thread per entity and step (coalesced offsets); mode 0 counts, mode 1 appends the
-    // lists (C_NTAIL / C_NSEG are then the append cursors)
-    __shared__ long long part[4][5];
-    const long long stride = (long long)gridDim.x * blockDim.x;
-    long long ct = 0, cs = 0, cr = 0, na = 0, deg_sum = 0;
-    for (long long base = (long long)blockIdx.x * blockDim.x; base < E; base += stride) {  // block-uniform trip count
-        const long long e = base + threadIdx.x;
-        bool on = false;
-        uint32_t d = 0;
-        if (e < E) {
-            on = (act[e >> 5] >> (e & 31)) & 1u;
-            if (on && shard_of && shard_of[e] != (uint8_t)shard) on = false;
-            if (on) d = out_off[e + 1] - out_off[e];
-        }
-        const bool tail = d > 0 && d <= (uint32_t)kTailMaxDegree;
-        const int segs = d > (uint32_t)kTailMaxDegree ? (int)((d + kPushSegment - 1) / kPushSegment) : 0;
-        if (!write_lists) {
-            na += on;
-            cr += d > 0;
-            ct += tail;
-            cs += segs;
-            deg_sum += d;
-            continue;
-        }
-        const unsigned long long tmask = __ballot(tail);
-        int ts;
-        const int ps = wave_excl_scan(segs, ts);
-        unsigned long long bt = 0, bs = 0;
-        if (lane() == 0) {
-            if (tmask) bt = atomicAdd(&ctr[C_NTAIL], (unsigned long long)__popcll(tmask));
-            if (ts) bs = atomicAdd(&ctr[C_NSEG], (unsigned long long)ts);
-        }
-        bt = shfl64(bt, 0);
-        bs = shfl64(bs, 0);
-        if (tail) list_tail[bt + __popcll(tmask & ((1ull << lane()) - 1ull))] = (int32_t)e;
-        if (segs) {
-            const uint32_t lo = row_begin[e];
-            for (int i = 0; i < segs; ++i) list_seg[bs + ps + i] = RowSegment{(int32_t)e, lo + (uint32_t)i * kPushSegment};
-        }
+// Both take eight entities per thread: their bits are one byte of the bitmap, and only where one is set are the
+// nine offsets read (two 16-byte loads and one more).  A block sums in LDS; the last block adds the blocks' sums up
+// and writes the totals to pinned host memory, so that no copy runs between the census and the host's wait.  The
+// tickets and cursors lie behind the live words and come zeroed with them: no fill either.  With an entity per thread and step, five atomics per
+// block of 1,024 and a fill before and a copy behind, a census took 17 .. 33 us and its fill and copy 13 us;
+// 12 us now for 3M entities, 7 us for 407,000 (a chain of a few reads and the tickets).
+constexpr int kCensusEntities = 8;  // per thread
+
+// the degrees of the active ones among entities e0 .. e0 + 7 (0 elsewhere), and their bits
+__device__ __forceinline__ unsigned census_degrees(const uint32_t *__restrict__ act, int32_t E,
+                                                   const uint32_t *__restrict__ out_off, long long e0,
+                                                   uint32_t (&d)[kCensusEntities]) {
+#pragma unroll
+    for (int i = 0; i < kCensusEntities; ++i) d[i] = 0;
+    if (e0 >= E) return 0;
+    const unsigned bits = (act[e0 >> 5] >> (e0 & 31)) & 0xffu;
+    if (bits == 0) return 0;
+    uint32_t o[kCensusEntities + 1];
+    if (e0 + kCensusEntities <= E) {  // out_off has E + 1 entries, e0 is a multiple of 8
+        const uint4 a = *reinterpret_cast<const uint4 *>(out_off + e0), b = *reinterpret_cast<const uint4 *>(out_off + e0 + 4);
+        o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w;
+        o[4] = b.x; o[5] = b.y; o[6] = b.z; o[7] = b.w;
+        o[8] = out_off[e0 + 8];
+    } else {
+#pragma unroll
+        for (int i = 0; i <= kCensusEntities; ++i) o[i] = out_off[min(e0 + i, (long long)E)];
     }
-    if (write_lists) return;
-    ct = wave_sum(ct);
-    cs = wave_sum(cs);
-    cr = wave_sum(cr);
-    na = wave_sum(na);
-    deg_sum = wave_sum(deg_sum);
+#pragma unroll
+    for (int i = 0; i < kCensusEntities; ++i)
+        if ((bits >> i) & 1u) d[i] = o[i + 1] - o[i];
+    return bits;
+}
+
+__device__ __forceinline__ unsigned segments_of(uint32_t d) {
+    return d > (uint32_t)kTailMaxDegree ? (d + kPushSegment - 1) / kPushSegment : 0u;
+}
+
+__global__ void __launch_bounds__(1024)
+k_census(const uint32_t *__restrict__ act, int32_t E, const uint32_t *__restrict__ out_off, unsigned long long *ctr,
+         unsigned long long *sums, unsigned long long *host) {
+    __shared__ unsigned long long part[16][3];
+    unsigned long long lists = 0, rows = 0, edges = 0;  // short rows | segments << 32, rows | active entities << 32
+    const long long stride = (long long)gridDim.x * 1024 * kCensusEntities;
+    for (long long e0 = ((long long)blockIdx.x * 1024 + threadIdx.x) * kCensusEntities; e0 < E; e0 += stride) {
+        uint32_t d[kCensusEntities];
+        const unsigned bits = census_degrees(act, E, out_off, e0, d);
+        if (!bits) continue;
+#pragma unroll
+        for (int i = 0; i < kCensusEntities; ++i) {
+            lists += (unsigned long long)(d[i] > 0 && d[i] <= (uint32_t)kTailMaxDegree) | ((unsigned long long)segments_of(d[i]) << 32);
+            rows += d[i] > 0;
+            edges += d[i];
+        }
+        rows += (unsigned long long)__popc(bits) << 32;
+    }
+    lists = (unsigned long long)wave_sum((long long)lists);
+    rows = (unsigned long long)wave_sum((long long)rows);
+    edges = (unsigned long long)wave_sum((long long)edges);
     const int wave = threadIdx.x >> 6;
     if (lane() == 0) {
-        part[wave][0] = ct; part[wave][1] = cs; part[wave][2] = cr; part[wave][3] = deg_sum; part[wave][4] = na;
+        part[wave][0] = lists;
+        part[wave][1] = rows;
+        part[wave][2] = edges;
     }
     __syncthreads();
-    if (threadIdx.x < 5) {
-        long long x = part[0][threadIdx.x] + part[1][threadIdx.x] + part[2][threadIdx.x] + part[3][threadIdx.x];
-        const int slot[5] = {C_NTAIL, C_NSEG, C_NROWS, C_FEDGES, C_NACTIVE};
-        if (x) atomicAdd(&ctr[slot[threadIdx.x]], (unsigned long long)x);
+    // The block's sums go to a line of their own; whoever takes the last ticket adds them all up.  (Three atomics
+    // per block on the level's counters were 6 ns each, one after the other: 16 us with 367 blocks.)
+    __shared__ int last;
+    if (threadIdx.x < 3) {
+        unsigned long long x = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) x += part[w][threadIdx.x];
+        __hip_atomic_store(&sums[(size_t)blockIdx.x * 3 + threadIdx.x], x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the sums (of this wavefront's lanes) are in before the ticket is taken
+    if (threadIdx.x == 0) last = atomicAdd(&ctr[L_TICKET], 1ull) == gridDim.x - 1;
+    __syncthreads();
+    if (!last) return;  // block-uniform
+    lists = rows = edges = 0;
+    if (threadIdx.x < gridDim.x) {  // at most kCensusBlocks = 512 blocks
+        unsigned long long *x = sums + (size_t)threadIdx.x * 3;
+        lists = __hip_atomic_load(x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        rows = __hip_atomic_load(x + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        edges = __hip_atomic_load(x + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    lists = (unsigned long long)wave_sum((long long)lists);
+    rows = (unsigned long long)wave_sum((long long)rows);
+    edges = (unsigned long long)wave_sum((long long)edges);
+    if (lane() == 0) {
+        part[wave][0] = lists;
+        part[wave][1] = rows;
+        part[wave][2] = edges;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    lists = rows = edges = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+        lists += part[w][0];
+        rows += part[w][1];
+        edges += part[w][2];
+    }
+    host[C_NTAIL] = lists & 0xffffffffull;
+    host[C_NSEG] = lists >> 32;
+    host[C_NROWS] = rows & 0xffffffffull;
+    host[C_NACTIVE] = rows >> 32;
+    host[C_FEDGES] = edges;
+    host[C_ERR] = __hip_atomic_load(&ctr[L_ERR], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The push lists of a level; ctr[L_CUR_TAIL] and ctr[L_CUR_SEG] are the append cursors (zero before) and then the
+// lengths that the push kernels read.
+__global__ void __launch_bounds__(1024)
+k_census_lists(const uint32_t *__restrict__ act, int32_t E, const uint32_t *__restrict__ out_off, int32_t *list_tail,
+               RowSegment *list_seg, unsigned long long *ctr) {
+    // a block reserves the places of its entries with one atomic per list
+    __shared__ int wave_n[2][16];
+    __shared__ unsigned long long first[2];
+    const int wave = threadIdx.x >> 6;
+    const long long stride = (long long)gridDim.x * 1024 * kCensusEntities;
+    for (long long base = (long long)blockIdx.x * 1024 * kCensusEntities; base < E; base += stride) {  // block-uniform
+        const long long e0 = base + (long long)threadIdx.x * kCensusEntities;
+        uint32_t d[kCensusEntities];
+        census_degrees(act, E, out_off, e0, d);
+        int nt = 0, ns = 0;
+#pragma unroll
+        for (int i = 0; i < kCensusEntities; ++i) {
+            nt += d[i] > 0 && d[i] <= (uint32_t)kTailMaxDegree;
+            ns += (int)segments_of(d[i]);
+        }
+        int all_t, all_s;
+        const int pt = wave_excl_scan(nt, all_t), ps = wave_excl_scan(ns, all_s);
+        if (lane() == 0) {
+            wave_n[0][wave] = all_t;
+            wave_n[1][wave] = all_s;
+        }
+        __syncthreads();
+        if (threadIdx.x < 2) {
+            int n = 0;
+            for (int w = 0; w < 16; ++w) n += wave_n[threadIdx.x][w];
+            first[threadIdx.x] = n ? atomicAdd(&ctr[threadIdx.x ? L_CUR_SEG : L_CUR_TAIL], (unsigned long long)n) : 0ull;
+        }
+        __syncthreads();
+        unsigned long long bt = first[0] + pt, bs = first[1] + ps;
+        for (int w = 0; w < wave; ++w) {
+            bt += wave_n[0][w];
+            bs += wave_n[1][w];
+        }
+#pragma unroll
+        for (int i = 0; i < kCensusEntities; ++i) {
+            const int32_t e = (int32_t)(e0 + i);
+            if (d[i] > 0 && d[i] <= (uint32_t)kTailMaxDegree) list_tail[bt++] = e;
+            const unsigned n = segments_of(d[i]);
+            if (n) {
+                const uint32_t lo = out_off[e];
+                for (unsigned x = 0; x < n; ++x) list_seg[bs++] = RowSegment{e, lo + x * kPushSegment};
+            }
+        }
+        __syncthreads();  // (the counts are rewritten by the next turn)
     }
 }
 
@@ -754,7 +856,7 @@ __global__ void __launch_bounds__(256)
 k_sparse_clear(long long Epad, int levels, uint32_t *act, long long actw, unsigned long long *visited,
                unsigned long long *level_planes, long long plane, unsigned long long *live) {
     if (blockIdx.x == 0)
-        for (int i = threadIdx.x; i < levels * 16; i += blockDim.x) live[i] = 0ull;
+        for (int i = threadIdx.x; i < levels * (16 + kLevelCounters); i += blockDim.x) live[i] = 0ull;  // (and the counters behind them)
     const long long base = ((long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 64;
     if (base >= Epad) return;  // Epad is a multiple of 64
     constexpr int GPW = 64 / W;
@@ -782,6 +884,10 @@ k_sparse_clear(long long Epad, int levels, uint32_t *act, long long actw, unsign
 // ---------------------------------------------------------------- host side
 static inline unsigned blocks_for(long long threads, int block) {
     return (unsigned)((threads + block - 1) / block);
+}
+
+static unsigned long long *level_counters(const logoskg_result *r, int h) {
+    return r->live + (size_t)16 * (r->k + 1) + (size_t)kLevelCounters * h;
 }
 
 template <int W, bool MASK>
@@ -916,8 +1022,8 @@ static void run_hop(logoskg_graph *g, logoskg_result *r, int h, bool pull, bool 
     if (pull) {
         launch_pull_range(g, r, h, g->in_rows, g->in_sub, g->in_rel, hc, want_stats, true, st);
     } else {
-        if (r->has_mask) launch_push<W, true>(g, r, h, hc, g->out_obj, g->out_rel, true, g->fr_tail, g->fr_seg, g->d_ctr, st);
-        else launch_push<W, false>(g, r, h, hc, g->out_obj, g->out_rel, true, g->fr_tail, g->fr_seg, g->d_ctr, st);
+        if (r->has_mask) launch_push<W, true>(g, r, h, hc, g->out_obj, g->out_rel, true, g->fr_tail, g->fr_seg, level_counters(r, h - 1), st);
+        else launch_push<W, false>(g, r, h, hc, g->out_obj, g->out_rel, true, g->fr_tail, g->fr_seg, level_counters(r, h - 1), st);
     }
 }
 
@@ -952,32 +1058,33 @@ void launch_resident_hop(logoskg_graph *g, logoskg_result *r, int h, bool pull, 
     }
 }
 
-// Census of level h's active bitmap (all subjects, or those of one shard): counts the rows,
-// edges and list entries into g->h_ctr (stream synchronised); with write_lists a second pass
-// appends the push work lists.
-static void launch_census(logoskg_graph *g, logoskg_result *r, int h, int shard, bool lists, hipStream_t st,
-                          int prof_kind = KK_CENSUS) {
-    const long long nwords = r->Epad / 32;
+// Push lists of level h into g->fr_tail / g->fr_seg.  ctr: two words that hold zeros (a level's own counters, once),
+// or NULL for the graph's, which are cleared first.
+logoskg_status census_lists(logoskg_graph *g, logoskg_result *r, int h, unsigned long long *ctr, hipStream_t st, int prof_kind) {
+    if (!ctr) {
+        ctr = g->d_ctr;
+        LKG_HIP(hipMemsetAsync(ctr, 0, 2 * sizeof(unsigned long long), st));
+    }
     ProfScope ps(g->prof, prof_kind, st);
-    const unsigned nb = std::min<unsigned>(1024u, std::max(1u, blocks_for(g->E, 256)));
-    k_census<<<dim3(nb), dim3(256), 0, st>>>(r->act + (size_t)nwords * h, g->E, g->out_off, g->row_begin,
-                                             shard >= 0 ? g->shard_of_dev : nullptr, shard, lists ? 1 : 0,
-                                             g->fr_tail, g->fr_seg, g->d_ctr);
-}
-
-logoskg_status census_lists(logoskg_graph *g, logoskg_result *r, int h, int shard, hipStream_t st, int prof_kind) {
-    LKG_HIP(hipMemsetAsync(g->d_ctr, 0, 2 * sizeof(unsigned long long), st));  // C_NTAIL, C_NSEG: append cursors
-    launch_census(g, r, h, shard, true, st, prof_kind);
+    const unsigned nb = std::min<unsigned>(512u, std::max(1u, blocks_for(g->E, 1024 * kCensusEntities)));
+    k_census_lists<<<dim3(nb), dim3(1024), 0, st>>>(r->act + (size_t)(r->Epad / 32) * h, g->E, g->out_off, g->fr_tail,
+                                                   g->fr_seg, ctr);
     LKG_HIP(hipGetLastError());
     return LOGOSKG_OK;
 }
 
-logoskg_status census(logoskg_graph *g, logoskg_result *r, int h, int shard, bool write_lists, hipStream_t st) {
-    LKG_HIP(hipMemsetAsync(g->d_ctr, 0, 5 * sizeof(unsigned long long), st));
-    launch_census(g, r, h, shard, false, st);
+// Census of level h into g->h_ctr; synchronises the stream.
+static logoskg_status census(logoskg_graph *g, logoskg_result *r, int h, hipStream_t st) {
+    {
+        ProfScope ps(g->prof, KK_CENSUS, st);
+        const unsigned nb = std::min<unsigned>(kCensusBlocks, std::max(1u, blocks_for(g->E, 1024 * kCensusEntities)));
+        k_census<<<dim3(nb), dim3(1024), 0, st>>>(r->act + (size_t)(r->Epad / 32) * h, g->E, g->out_off,
+                                                  level_counters(r, h), g->d_ctr + C_TOTAL, g->h_ctr);
+    }
     LKG_HIP(hipGetLastError());
-    LKG_HIP(hipMemcpyAsync(g->h_ctr, g->d_ctr, C_TOTAL * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
-    if (write_lists) LKG_TRY(census_lists(g, r, h, shard, st));
+    if (g->prof.counters)
+        LKG_HIP(hipMemcpyAsync(g->h_ctr + C_STATS, g->d_ctr + C_STATS, 4 * KK_NUM * sizeof(unsigned long long),
+                               hipMemcpyDeviceToHost, st));
     LKG_HIP(hipStreamSynchronize(st));
     return LOGOSKG_OK;
 }
@@ -1051,9 +1158,9 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
     const size_t actw = (size_t)r->Epad / 32;
     logoskg_status s;
     auto fail = [&](logoskg_status e) { logoskg_result_free(r); return e; };
-    // visited and the level planes are one allocation, the active bitmaps and the live words
-    // another: each is cleared by one fill
-    const size_t act_bytes = actw * 4 * (size_t)(k + 1), live_bytes = (size_t)16 * 8 * (size_t)(k + 1);
+    // visited and the level planes are one allocation, the active bitmaps, the live words and the levels'
+    // counters another: each is cleared by one fill
+    const size_t act_bytes = actw * 4 * (size_t)(k + 1), live_bytes = (size_t)(16 + kLevelCounters) * 8 * (size_t)(k + 1);
     r->last_stream = st;
     bool planes_zero = false, act_zero = false;  // a block released by an earlier result comes back cleared
     if ((s = g->pool.alloc((void **)&r->visited, plane * 8 * (size_t)(k + 2), st, &planes_zero)) != LOGOSKG_OK) return fail(s);
@@ -1095,17 +1202,16 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
     }
     int first_hop = 1;
     if (small && (s = small_search(g, r, b, want_counts, dir == LOGOSKG_DIR_PUSH, &first_hop, st)) != LOGOSKG_OK) return fail(s);
-    if (first_hop <= k || !small) KH(hipMemsetAsync(g->d_ctr, 0, C_TOTAL * sizeof(unsigned long long), st));
     if (!small) {
         g->prof.begin(KK_SEED, st);
         k_seed<<<dim3((r->Q + 255) / 256), dim3(256), 0, st>>>(r->Q, (long long)b->num_seeds,
                                                                (const long long *)b->seed_off, b->seeds, g->E, W,
                                                                (unsigned long long *)r->levels,
-                                                               (unsigned long long *)r->visited, r->act, g->d_ctr,
+                                                               (unsigned long long *)r->visited, r->act, level_counters(r, 0),
                                                                r->seed_off, r->seeds);
         g->prof.end(st);
         KH(hipGetLastError());
-        if ((s = census(g, r, 0, -1, false, st)) != LOGOSKG_OK) return fail(s);
+        if ((s = census(g, r, 0, st)) != LOGOSKG_OK) return fail(s);
         if (g->h_ctr[C_ERR]) {
             set_error("seed_off / seeds are inconsistent or out of range (device check, code %llu)", g->h_ctr[C_ERR]);
             return fail(LOGOSKG_EINVAL);
@@ -1120,8 +1226,8 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
         hs.frontier_edges = fedges;
         const bool pull = dir == LOGOSKG_DIR_PULL || (dir == LOGOSKG_DIR_AUTO && fedges * 12 > g->T);
         hs.direction = pull ? LOGOSKG_DIR_PULL : LOGOSKG_DIR_PUSH;
-        unsigned long long hc[C_TOTAL];
-        memcpy(hc, g->h_ctr, sizeof(hc));
+        unsigned long long hc[C_TOTAL] = {};
+        memcpy(hc, g->h_ctr, C_STATS * sizeof(hc[0]));
         if (want_stats)
             KH(hipMemsetAsync(g->d_ctr + C_STATS, 0, 4 * KK_NUM * sizeof(unsigned long long), st));
         if (g->num_shards > 1) {
@@ -1131,14 +1237,14 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
             KH(hipGetLastError());
         } else {
             hs.shards_touched = 1;
-            if (!pull && (s = census_lists(g, r, h - 1, -1, st)) != LOGOSKG_OK) return fail(s);
+            if (!pull && (s = census_lists(g, r, h - 1, level_counters(r, h - 1), st)) != LOGOSKG_OK) return fail(s);
             launch_resident_hop(g, r, h, pull, want_stats, hc, st);
             KH(hipGetLastError());
         }
-        if ((s = census(g, r, h, -1, false, st)) != LOGOSKG_OK) return fail(s);
+        if ((s = census(g, r, h, st)) != LOGOSKG_OK) return fail(s);
         hs.entities_reached = (long long)g->h_ctr[C_NACTIVE];
         if (hs.direction == LOGOSKG_DIR_PULL) {
-            for (int kind : {KK_PULL_TAIL, KK_PULL_SEG}) {
+            if (want_stats) for (int kind : {KK_PULL_TAIL, KK_PULL_SEG}) {
                 const unsigned long long *c = g->h_ctr + C_STATS + 4 * kind;
                 hs.rows_scanned += (long long)c[0];
                 hs.edges_scanned += (long long)c[1];
