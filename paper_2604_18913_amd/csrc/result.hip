@@ -366,65 +366,75 @@ __global__ void __launch_bounds__(64 * W) k_lists(FillArgs a) {
 }
 
 // ---------------------------------------------------------------- predecessor edges
-// Removes up to 64/W candidates from the wave-uniform mask; group g gets the
-// g-th of them (lane position) or -1.
-template <int W>
-__device__ __forceinline__ int next_candidates(unsigned long long &rest) {
-    constexpr int GPW = 64 / W;
-    int g = lane() / W, mine = -1;
-#pragma unroll
-    for (int t = 0; t < GPW; ++t) {
-        if (rest) {
-            int p = __ffsll((long long)rest) - 1;
-            rest &= rest - 1;
-            if (t == g) mine = p;
-        }
-    }
-    return mine;
+// 64 in-edges of an object row for a caller that merges claims with a minimum over entries (the row
+// kernels): every W-lane group keeps a mask `rem` of its own (word lw of the queries it has not resolved),
+// takes every (64/W)-th candidate subject, gathers its line and claims whatever its mask still holds, with no
+// exchange between the groups.  (An ordered walk - a candidate claims only what no earlier candidate of the
+// round has, found with an exclusive prefix-OR across the groups - costs ten dependent LDS permutes per
+// round, which is what these kernels then wait on.)  A query may be claimed by several groups; the smallest
+// entry wins.
+//
+// The candidates are compacted into a queue of the wavefront in LDS (subject, relation, place in the chunk), so
+// that a round costs a group one LDS read.  Picking them out of the ballot mask one after the other was half of
+// the kernels' vector and nearly all of their scalar instructions, and they are bound by instruction issue
+// (30M triples, 1,024 queries: mid rows 354 us, giants 439 us, other hubs 200 us; 309, 280 and 131 us with the queue).
+// emit(hit, at) runs on lanes whose word has newly claimed bits, at = the entry's place in the chunk;
+// returns the lines gathered.
+// smin[b] = min(smin[b], at) for every bit b of hit, in 32-bit halves: a turn is then six vector instructions where
+// the 64-bit form took a dozen, and these turns are most of what the row kernels issue.
+__device__ __forceinline__ void claim(unsigned int *smin, unsigned long long hit, unsigned int at) {
+    for (uint32_t m = (uint32_t)hit; m; m &= m - 1u) atomicMin(&smin[__builtin_ctz(m)], at);
+    for (uint32_t m = (uint32_t)(hit >> 32); m; m &= m - 1u) atomicMin(&smin[32 + __builtin_ctz(m)], at);
 }
 
-// The 64 in-edges [j0, j0+64) of an object row for a caller that merges claims with a minimum over
-// edge ids (the row kernels): every W-lane group keeps a mask `rem` of its own (word lw of the
-// queries it has not resolved), takes every (64/W)-th candidate subject, gathers its line and
-// claims whatever its mask still holds, with no exchange between the groups.  (An ordered walk -
-// a candidate claims only what no earlier candidate of the round has, found with an exclusive
-// prefix-OR across the groups - costs ten dependent LDS permutes per round, which is what these
-// kernels then wait on.)  A query may be claimed by several groups; the smallest edge id wins.
-// emit(hit, eid) runs on lanes whose word has newly claimed bits; returns the lines gathered.
+// The 64 entries of a word lie kClaimStride apart: lanes of one round mostly claim the same bits of their words, and
+// with 64 apart all of them met in one LDS bank.
+constexpr int kClaimStride = 65;
+
+struct PredQueue {
+    int s[64];
+    uint16_t r[64];
+    uint8_t at[64];
+};
+
 template <int W, bool MASK, typename Emit>
-__device__ __forceinline__ int pred_resolve_unordered(uint32_t j0, int s, bool cand, const FillArgs &a,
-                                                      const unsigned long long *__restrict__ prev,
+__device__ __forceinline__ int pred_resolve_unordered(int s, int r, bool cand, const FillArgs &a,
+                                                      const unsigned long long *__restrict__ prev, PredQueue &queue,
                                                       unsigned long long &rem, Emit emit) {
-    const int lw = lane() & (W - 1);
-    unsigned long long cm = __ballot(cand);
-    int gathered = 0;
-    constexpr int NR = 4;
-    while (cm) {
-        gathered += min(__popcll(cm), NR * (64 / W));
-        int p[NR];
+    const int lw = lane() & (W - 1), g = lane() / W;
+    const unsigned long long cm = __ballot(cand);
+    const int n = __popcll(cm);
+    if (n == 0) return 0;
+    if (cand) {
+        const int at = __popcll(cm & ((1ull << lane()) - 1ull));
+        queue.s[at] = s;
+        if (MASK) queue.r[at] = (uint16_t)r;
+        queue.at[at] = (uint8_t)lane();
+    }
+    __builtin_amdgcn_wave_barrier();
+    constexpr int NR = 4, GPW = 64 / W;
+    int base = 0;
+    for (; base < n; base += NR * GPW) {
         unsigned long long l[NR];
 #pragma unroll
-        for (int x = 0; x < NR; ++x) p[x] = next_candidates<W>(cm);
-#pragma unroll
         for (int x = 0; x < NR; ++x) {
-            const int sx = __shfl(s, p[x] < 0 ? 0 : p[x]);
+            const int i = base + x * GPW + g;
             l[x] = 0;
-            if (p[x] >= 0) l[x] = prev[(size_t)sx * W + lw];
-        }
-        if (MASK) {
-#pragma unroll
-            for (int x = 0; x < NR; ++x)
-                if (p[x] >= 0) l[x] &= a.allow[(size_t)a.in_rel[j0 + p[x]] * W + lw];
+            if (i < n) {
+                l[x] = prev[(size_t)queue.s[i] * W + lw];
+                if (MASK) l[x] &= a.allow[(size_t)queue.r[i] * W + lw];
+            }
         }
 #pragma unroll
         for (int x = 0; x < NR; ++x) {
             const unsigned long long hit = l[x] & rem;
             rem &= ~l[x];
-            if (hit) emit(hit, a.in_eid[j0 + p[x]]);
+            if (hit) emit(hit, (int)queue.at[base + x * GPW + g]);
         }
         if (!wave_any(rem != 0)) break;
     }
-    return gathered;
+    __builtin_amdgcn_wave_barrier();  // the queue is rewritten by the next chunk
+    return min(n, base + NR * GPW);
 }
 
 // List positions of entity `ev` for every query: slot[q] = start of the tile's run in query q's
@@ -456,6 +466,9 @@ __device__ __forceinline__ void row_slots(const FillArgs &a, int ev, int w_first
     }
 }
 
+// Triple index of a row entry; ~0: none was found (a reached pair has one, so only a broken input leads here).
+__device__ __forceinline__ int32_t entry_id(const FillArgs &a, unsigned int at) { return at == ~0u ? INT_MAX : a.in_eid[at]; }
+
 // AND over the 64/W groups of a wavefront (word lw of each group).
 template <int W>
 __device__ __forceinline__ unsigned long long and_groups(unsigned long long x) {
@@ -473,17 +486,18 @@ template <int W, bool MASK, bool STATS, bool BUF>
 __global__ void __launch_bounds__(256) k_pred_wave(FillArgs a, long long first_row, long long n_rows_total) {
     constexpr int Qp = 64 * W;
     __shared__ long long slots[BUF ? 1 : 4][BUF ? 1 : Qp];
-    __shared__ int smin_all[4][Qp];
+    __shared__ unsigned int smin_all[4][W * kClaimStride];  // smallest entry per query (index into in_sub)
+    __shared__ PredQueue queue[4];
     const int wave = threadIdx.x >> 6, v = lane(), lw = v & (W - 1);
     const long long idx = (long long)blockIdx.x * 4 + wave;
     long long n_rows = 0, n_edges = 0, n_lines = 0;
     if (idx < n_rows_total) {  // wave-uniform
         const int ev = a.rows[first_row + idx];
         long long *slot = slots[BUF ? 0 : wave];
-        int *smin = smin_all[wave];
+        unsigned int *smin = smin_all[wave];
         int32_t *out = BUF ? a.row_pred + (size_t)(first_row + idx) * Qp : a.pred;
         if (!BUF) row_slots<W>(a, ev, 0, 1, slot);
-        for (int q = v; q < Qp; q += 64) smin[q] = INT_MAX;
+        for (int w = 0; w < W; ++w) smin[w * kClaimStride + v] = ~0u;
         __builtin_amdgcn_wave_barrier();
         const uint32_t lo = a.in_off[ev], hi = a.in_off[ev + 1];
         for (int h = 1; h <= a.k; ++h) {
@@ -494,31 +508,38 @@ __global__ void __launch_bounds__(256) k_pred_wave(FillArgs a, long long first_r
             const unsigned long long *prev = a.levels + (size_t)(h - 1) * a.plane;
             const bool dense = !STATS && ((a.dense_levels >> h) & 1u);  // the line of an entity outside the level is zero
             ++n_rows;
+            // the subjects of the next 64 entries are requested while the lines of these are gathered
+            int s_next = lo + v < hi ? a.in_sub[lo + v] : -1, r_next = MASK && lo + v < hi ? a.in_rel[lo + v] : 0;
             for (uint32_t j0 = lo; j0 < hi; j0 += 64) {
-                const uint32_t j = j0 + v;
-                int s = 0;
-                bool cand = false;
-                if (j < hi) {
-                    s = a.in_sub[j];
-                    cand = dense || ((act_prev[s >> 5] >> (s & 31)) & 1u);
-                }
-                n_lines += pred_resolve_unordered<W, MASK>(j0, s, cand, a, prev, rem, [&](unsigned long long hit, int eid) {
-                    for (unsigned long long m = hit; m; m &= m - 1)
-                        atomicMin(&smin[lw * 64 + (__ffsll((long long)m) - 1)], eid);
+                const int s = s_next, r = r_next;
+                const uint32_t jn = j0 + 64 + v;
+                s_next = jn < hi ? a.in_sub[jn] : -1;
+                r_next = MASK && jn < hi ? a.in_rel[jn] : 0;
+                const bool cand = s >= 0 && (dense || ((act_prev[s >> 5] >> (s & 31)) & 1u));
+                n_lines += pred_resolve_unordered<W, MASK>(s, r, cand, a, prev, queue[wave], rem, [&](unsigned long long hit, int at) {
+                    claim(&smin[lw * kClaimStride], hit, j0 + (uint32_t)at);
                 });
                 rem = and_groups<W>(rem);  // what any group has resolved is resolved
                 n_edges += min((uint32_t)64, hi - j0);
                 if (!wave_any(rem != 0)) break;
             }
             __builtin_amdgcn_wave_barrier();
-            for (int i = 0; i < W; ++i) {  // queries 64 i .. 64 i + 63: word i of the level, held by lane i
-                const unsigned long long word = shfl64(level, i);
-                const int q = 64 * i + v;
-                if ((word >> v) & 1ull) {
-                    out[BUF ? (long long)q : slot[q]] = smin[q];
-                    smin[q] = INT_MAX;
-                }
+            // Queries 64 i .. 64 i + 63: word i of the level, held by lane i.  All triple indices are requested before the
+            // first is stored (a load behind a store, sixteen times over, was a third of a row's time).
+            int32_t eid[W];
+            bool on[W];
+#pragma unroll
+            for (int i = 0; i < W; ++i) {
+                on[i] = (shfl64(level, i) >> v) & 1ull;
+                eid[i] = 0;
+                if (on[i]) eid[i] = entry_id(a, smin[i * kClaimStride + v]);
             }
+#pragma unroll
+            for (int i = 0; i < W; ++i)
+                if (on[i]) {
+                    out[BUF ? (long long)(64 * i + v) : slot[64 * i + v]] = eid[i];
+                    smin[i * kClaimStride + v] = ~0u;
+                }
             __builtin_amdgcn_wave_barrier();
         }
     }
@@ -663,9 +684,12 @@ __global__ void __launch_bounds__(256) k_narrow_wave(FillArgs a, long long first
             narrow_resolve<W, N, MASK>(a, prev, off, j0, 64, hi, rem, best);
             n_edges += min((uint32_t)(64 * kNarrowChunks), hi - j0);
         }
+        int32_t eid[N];
+#pragma unroll
+        for (int w = 0; w < N; ++w) eid[w] = (lev[w] >> v) & 1ull ? a.in_eid[best[w]] : 0;
 #pragma unroll
         for (int w = 0; w < N; ++w)
-            if ((lev[w] >> v) & 1ull) out[BUF ? (long long)((off + w) * 64 + v) : slot[w * 64 + v]] = a.in_eid[best[w]];
+            if ((lev[w] >> v) & 1ull) out[BUF ? (long long)((off + w) * 64 + v) : slot[w * 64 + v]] = eid[w];
     }
     if (STATS && v == 0) {
         if (n_rows) atomicAdd(&a.stats_mid[0], (unsigned long long)n_rows);
@@ -747,7 +771,7 @@ __global__ void __launch_bounds__(1024) k_narrow_row(FillArgs a, long long first
         if (SEG) {
             if (at != ~0u) atomicMin(&out[(off + w) * 64 + v], a.in_eid[at]);
         } else {
-            out[BUF ? (long long)((off + w) * 64 + v) : slot[w * 64 + v]] = a.in_eid[at];
+            out[BUF ? (long long)((off + w) * 64 + v) : slot[w * 64 + v]] = entry_id(a, at);
         }
     }
     if (STATS && t == 0) {
@@ -1500,7 +1524,8 @@ __global__ void __launch_bounds__(1024) k_pred_row(FillArgs a, long long first_r
     constexpr int Qp = 64 * W;
     constexpr int C = 4;  // 64-entry chunks per wavefront and step, loaded together
     __shared__ long long slot[BUF ? 1 : Qp];
-    __shared__ int smin[Qp];
+    __shared__ unsigned int smin[W * kClaimStride];  // smallest entry per query (index into in_sub)
+    __shared__ PredQueue queue[16];
     __shared__ unsigned long long srem[16], slevel[16];
     long long row_i = blockIdx.x;
     uint32_t seg = 0;
@@ -1536,7 +1561,7 @@ __global__ void __launch_bounds__(1024) k_pred_row(FillArgs a, long long first_r
             srem[t] = x;
             slevel[t] = x;
         }
-        for (int q = t; q < Qp; q += blockDim.x) smin[q] = INT_MAX;
+        for (int q = t; q < Qp; q += blockDim.x) smin[(q >> 6) * kClaimStride + (q & 63)] = ~0u;
         __syncthreads();
         if (!wave_any(slevel[lw] != 0) || ((a.push_levels >> h) & 1u)) continue;  // block-uniform
         const uint32_t *act_prev = a.act + (size_t)(h - 1) * a.actw;
@@ -1555,15 +1580,16 @@ __global__ void __launch_bounds__(1024) k_pred_row(FillArgs a, long long first_r
             // chunk c of this wavefront is chunk c * nw + wave of the step: a row shorter than a
             // step still spreads over all wavefronts
             const uint32_t w0 = s0 + 64u * wave;
-            int sj[C];
+            int sj[C], rj[C];
             bool cj[C];
 #pragma unroll
             for (int c = 0; c < C; ++c) {  // all loads of the step first
                 uint32_t j = w0 + 64u * nw * c + v;
-                sj[c] = 0;
+                sj[c] = rj[c] = 0;
                 cj[c] = false;
                 if (j < step_hi) {
                     sj[c] = a.in_sub[j];
+                    if (MASK) rj[c] = a.in_rel[j];
                     cj[c] = dense || ((act_prev[sj[c] >> 5] >> (sj[c] & 31)) & 1u);
                 }
             }
@@ -1571,10 +1597,9 @@ __global__ void __launch_bounds__(1024) k_pred_row(FillArgs a, long long first_r
             for (int c = 0; c < C; ++c) {
                 uint32_t j0 = w0 + 64u * nw * c;
                 if (j0 < step_hi && wave_any(rem != 0)) {
-                    n_lines += pred_resolve_unordered<W, MASK>(j0, sj[c], cj[c], a, prev, rem,
-                                                               [&](unsigned long long hit, int eid) {
-                        for (unsigned long long m = hit; m; m &= m - 1)
-                            atomicMin(&smin[lw * 64 + (__ffsll((long long)m) - 1)], eid);
+                    n_lines += pred_resolve_unordered<W, MASK>(sj[c], rj[c], cj[c], a, prev, queue[wave], rem,
+                                                               [&](unsigned long long hit, int at) {
+                        claim(&smin[lw * kClaimStride], hit, j0 + (uint32_t)at);
                     });
                     n_edges += min((uint32_t)64, step_hi - j0);
                 }
@@ -1585,14 +1610,24 @@ __global__ void __launch_bounds__(1024) k_pred_row(FillArgs a, long long first_r
             __syncthreads();
         }
         __syncthreads();
-        for (int q = t; q < Qp; q += blockDim.x)
-            if ((slevel[q >> 6] >> (q & 63)) & 1ull) {
-                if (SEG) {
-                    if (smin[q] != INT_MAX) atomicMin(&out[q], smin[q]);
-                } else {
-                    out[BUF ? (long long)q : slot[q]] = smin[q];
-                }
+        for (int q1 = t; q1 < Qp; q1 += 4 * blockDim.x) {  // four triple indices are requested before the first is stored
+            int32_t eid[4];
+            bool on[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const int q = q1 + x * (int)blockDim.x;
+                on[x] = q < Qp && ((slevel[q >> 6] >> (q & 63)) & 1ull);
+                eid[x] = INT_MAX;
+                if (on[x]) eid[x] = entry_id(a, smin[(q >> 6) * kClaimStride + (q & 63)]);
             }
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const int q = q1 + x * (int)blockDim.x;
+                if (!on[x]) continue;
+                if (!SEG) out[BUF ? (long long)q : slot[q]] = eid[x];
+                else if (eid[x] != INT_MAX) atomicMin(&out[q], eid[x]);
+            }
+        }
     }
     if (STATS && v == 0) {
         if (n_rows) atomicAdd(&a.stats_hub[0], (unsigned long long)n_rows);
