@@ -404,7 +404,8 @@ extern "C" logoskg_status logoskg_build(const int32_t *subj, const int32_t *rel,
         set_error("hipHostMalloc failed");
         return fail(LOGOSKG_ENOMEM);
     }
-    if (hipHostMalloc((void **)&g->h_small, sizeof(SmallReport), hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc((void **)&g->h_small, sizeof(SmallReport), hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc((void **)&g->h_off, (LOGOSKG_MAX_QUERIES + 1) * sizeof(long long), hipHostMallocDefault) != hipSuccess) {
         set_error("hipHostMalloc failed");
         return fail(LOGOSKG_ENOMEM);
     }
@@ -445,6 +446,7 @@ extern "C" void logoskg_graph_free(logoskg_graph *g) {
         if (p) (void)hipFree(p);
     if (g->h_ctr) (void)hipHostFree(g->h_ctr);
     if (g->h_small) (void)hipHostFree(g->h_small);
+    if (g->h_off) (void)hipHostFree(g->h_off);
     g->pool.trim();
     delete g;
 }

@@ -217,6 +217,7 @@ struct logoskg_graph {
     int64_t fr_seg_cap = 0;
     unsigned long long *d_ctr = nullptr;  // device counters (see khop.hip)
     unsigned long long *h_ctr = nullptr;  // pinned host mirror
+    long long *h_off = nullptr;           // pinned [LOGOSKG_MAX_QUERIES + 1]: offsets of the last count
     lkg::SmallReport *h_small = nullptr;  // pinned: written by k_small_search
 
     std::vector<int32_t> shard_of;  // host copy of the map P (empty when unsharded)

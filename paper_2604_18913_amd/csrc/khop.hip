@@ -64,17 +64,16 @@ __global__ void k_seed(int Q, long long num_seeds, const long long *__restrict__
 
 // allow[r][w]: bit b set when query 64w+b may follow relation r (the vector REL.m
 // of every query, transposed so that one triple's relation selects a whole line).
-__global__ void k_allow(int Q, int R, int W, int rel_words, const unsigned long long *__restrict__ rel_mask,
-                        unsigned long long *allow) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= R * W) return;
-    int r = i / W, w = i % W;
-    unsigned long long v = 0;
-    for (int b = 0; b < 64; ++b) {
-        int q = w * 64 + b;
-        if (q < Q && ((rel_mask[(size_t)q * rel_words + (r >> 6)] >> (r & 63)) & 1ull)) v |= 1ull << b;
-    }
-    allow[i] = v;
+// A wavefront per 64 queries and 64 relations: lane = query, one word of its mask, and a 64 x 64 bit transpose
+// gives lane = relation.  (A thread per (relation, word) that collected its 64 bits one load after the other took
+// 16 us for 200 queries and 500 relations and 21 us for 1,024; 4 us now.)
+__global__ void __launch_bounds__(256)
+k_allow(int Q, int R, int W, int rel_words, const unsigned long long *__restrict__ rel_mask, unsigned long long *allow) {
+    const int item = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (item >= rel_words * W) return;  // wavefront-uniform
+    const int w = item % W, rw = item / W, q = w * 64 + lane(), r = rw * 64 + lane();
+    const unsigned long long x = transpose64(q < Q ? rel_mask[(size_t)q * rel_words + rw] : 0ull);
+    if (r < R) allow[(size_t)r * W + w] = x;
 }
 
 // ---------------------------------------------------------------- frontier census
@@ -1195,10 +1194,10 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
                        b->num_seeds <= kSmallEdges;
     if (r->has_mask) {
         ProfScope ps(g->prof, KK_SEED, st);
-        int n = g->R * W;
-        k_allow<<<dim3((n + 255) / 256), dim3(256), 0, st>>>(r->Q, g->R, W, (g->R + 63) / 64,
-                                                             (const unsigned long long *)b->rel_mask,
-                                                             (unsigned long long *)r->allow);
+        const int rel_words = (g->R + 63) / 64;
+        k_allow<<<dim3(blocks_for(rel_words * W, 4)), dim3(256), 0, st>>>(r->Q, g->R, W, rel_words,
+                                                                          (const unsigned long long *)b->rel_mask,
+                                                                          (unsigned long long *)r->allow);
     }
     int first_hop = 1;
     if (small && (s = small_search(g, r, b, want_counts, dir == LOGOSKG_DIR_PUSH, &first_hop, st)) != LOGOSKG_OK) return fail(s);

@@ -243,16 +243,25 @@ __global__ void k_scan_level(long long nrows, int group, int Qp, uint32_t *sum_t
     up[(size_t)g * Qp + q] = run;
 }
 
-// one block of Qp threads: prefix over mega tiles for every query, then the prefix over queries
-// (Hillis-Steele steps in LDS)
-__global__ void k_scan_top(long long nmega, int Q, int Qp, uint32_t *mega_base, long long *reached_off) {
+// One block of Qp threads: prefix over mega tiles for every query (eight rows requested before any is
+// rewritten), then the prefix over queries (Hillis-Steele steps in LDS).  The offsets and, with a list, the number
+// of listed entities go to pinned host memory as well: two copies behind the kernel and the gaps around them
+// were 20 us of every count.
+__global__ void k_scan_top(long long nmega, int Q, int Qp, uint32_t *mega_base, long long *reached_off,
+                           const unsigned long long *__restrict__ n_active, long long *host_off,
+                           unsigned long long *host_n_active) {
     __shared__ long long total[2][1024];
     const int q = threadIdx.x;
     long long run = 0;
-    for (long long m = 0; m < nmega; ++m) {
-        uint32_t x = mega_base[(size_t)m * Qp + q];
-        mega_base[(size_t)m * Qp + q] = (uint32_t)run;
-        run += x;
+    for (long long m0 = 0; m0 < nmega; m0 += 8) {
+        uint32_t x[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = m0 + i < nmega ? mega_base[(size_t)(m0 + i) * Qp + q] : 0u;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (m0 + i < nmega) mega_base[(size_t)(m0 + i) * Qp + q] = (uint32_t)run;
+            run += x[i];
+        }
     }
     const long long mine = q < Q ? run : 0;
     int cur = 0;
@@ -265,8 +274,9 @@ __global__ void k_scan_top(long long nmega, int Q, int Qp, uint32_t *mega_base, 
         cur ^= 1;
         __syncthreads();
     }
-    reached_off[q] = total[cur][q] - mine;  // exclusive
-    if (q == Qp - 1) reached_off[Qp] = total[cur][q];
+    reached_off[q] = host_off[q] = total[cur][q] - mine;  // exclusive
+    if (q == Qp - 1) reached_off[Qp] = host_off[Qp] = total[cur][q];
+    if (q == 0 && n_active) *host_n_active = *n_active;
 }
 
 __device__ __forceinline__ unsigned long long range_bits(int q0, int q1, int w) {
@@ -1737,16 +1747,13 @@ static logoskg_status count_plane(logoskg_result *r, const unsigned long long *p
         const int threads = std::min(Qp, 256);
         k_scan_level<<<dim3((unsigned)nmega, (unsigned)(Qp / threads)), dim3(threads), 0, st>>>(
             nsuper, kMegaSupers, Qp, *super_base, *mega_base);
-        k_scan_top<<<dim3(1), dim3(Qp), 0, st>>>(nmega, r->Q, Qp, *mega_base, *d_off);
+        k_scan_top<<<dim3(1), dim3(Qp), 0, st>>>(nmega, r->Q, Qp, *mega_base, *d_off, r->tile_ent ? r->d_nact : nullptr,
+                                                 g->h_off, g->h_ctr + C_TOTAL);
     }
     LKG_HIP(hipGetLastError());
-    off->assign((size_t)r->Q + 1, 0);
-    LKG_HIP(hipMemcpyAsync(off->data(), *d_off, (size_t)(r->Q + 1) * 8, hipMemcpyDeviceToHost, st));
-    unsigned long long *h_nact = g->h_ctr + C_TOTAL;  // one more pinned word behind the counters' mirror
-    if (r->tile_ent && r->n_active < 0)
-        LKG_HIP(hipMemcpyAsync(h_nact, r->d_nact, 8, hipMemcpyDeviceToHost, st));
     LKG_HIP(hipStreamSynchronize(st));
-    if (r->tile_ent && r->n_active < 0) r->n_active = (long long)*h_nact;
+    off->assign(g->h_off, g->h_off + r->Q + 1);
+    if (r->tile_ent && r->n_active < 0) r->n_active = (long long)g->h_ctr[C_TOTAL];  // (one word behind the counters' mirror)
     if (g->prof.on) g->prof.acc[KK_COUNT].units[3] += (r->tile_ent ? (r->n_active + 63) / 64 * 64 : r->Epad) * W;
     return LOGOSKG_OK;
 }
