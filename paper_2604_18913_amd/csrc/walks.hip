@@ -52,7 +52,7 @@ k_walk_seeds(int32_t E, int W, int w, unsigned long long bit, const unsigned lon
 // together (neighbouring rows are contiguous in OBJ, so a wavefront's loads share their lines).
 // Longer rows are left to k_walk_count_long.  One wavefront per 64 entities, row after row, took 1.0 ms
 // a hop on a 3.4M-triple graph whatever the level held (a 10^5-entry row is 1,500 turns of one
-// wavefront); count and page of 10^6 chains of three triples together went from 3.2 ms to 0.68 ms there.
+// wavefront); count and page of 10^6 chains of three triples together went from 3.2 ms to 0.30 ms there.
 template <bool MASK>
 __device__ __forceinline__ unsigned long long walk_entry(uint32_t j, int W, int w, unsigned long long bit,
                                                          const unsigned long long *__restrict__ allow,
@@ -97,26 +97,21 @@ k_walk_count_short(int32_t E, int W, int w, unsigned long long bit, const unsign
     cnt_cur[e] = capped(running, overflow);
 }
 
-// A block of NW wavefronts per longer row, U entries per lane and turn: each lane sums consecutive
-// entries of its own, a wavefront scan and the wavefronts' totals place them.
+// Entries [lo, hi) of one row by a block of NW wavefronts, U entries per lane and turn (one wavefront apart, so
+// that every load and store is contiguous): cum = running sums from `running` on; returns the capped total.
 template <bool MASK, int NW>
-__global__ void __launch_bounds__(64 * NW)
-k_walk_count_long(const int32_t *__restrict__ rows, int W, int w, unsigned long long bit,
-                  const unsigned long long *__restrict__ level_h, const unsigned long long *__restrict__ allow,
-                  const uint32_t *__restrict__ in_off, const int32_t *__restrict__ in_sub,
-                  const uint16_t *__restrict__ in_rel, const unsigned long long *__restrict__ cnt_prev,
-                  unsigned long long *__restrict__ cnt_cur, unsigned long long *__restrict__ cum,
-                  unsigned int *overflow) {
+__device__ __forceinline__ unsigned long long walk_count_span(uint32_t lo, uint32_t hi, unsigned long long running, int W, int w,
+                                                              unsigned long long bit,
+                                                              const unsigned long long *__restrict__ allow,
+                                                              const int32_t *__restrict__ in_sub,
+                                                              const uint16_t *__restrict__ in_rel,
+                                                              const unsigned long long *__restrict__ cnt_prev,
+                                                              unsigned long long *__restrict__ cum,
+                                                              unsigned long long (*part)[NW]) {
     constexpr int U = NW >= 16 ? 4 : 2, NT = 64 * NW;
-    __shared__ unsigned long long part[2][NW];
-    const int t = threadIdx.x, wave = t >> 6;
-    const int32_t v = rows[blockIdx.x];
-    if (!(level_h[(size_t)v * W + w] & bit)) return;  // block-uniform
-    const uint32_t lo = in_off[v], hi = in_off[v + 1];
-    unsigned long long running = 0;
+    const int wave = threadIdx.x >> 6;
     int buf = 0;
     for (uint32_t j0 = lo; j0 < hi; j0 += NT * U, buf ^= 1) {
-        // a lane's U entries are one wavefront apart, so every load and store is contiguous
         const uint32_t base = j0 + (uint32_t)(wave * 64 * U + lane());
         unsigned long long c[U], incl[U], sum = 0;
 #pragma unroll
@@ -142,7 +137,74 @@ k_walk_count_long(const int32_t *__restrict__ rows, int W, int w, unsigned long 
             if (base + u * 64 < hi) cum[base + u * 64] = before + (incl[u] - c[u]);
         running = total;
     }
-    if (t == 0) cnt_cur[v] = capped(running, overflow);
+    return running;
+}
+
+// A block of four wavefronts per longer row.
+template <bool MASK>
+__global__ void __launch_bounds__(256)
+k_walk_count_long(const int32_t *__restrict__ rows, int W, int w, unsigned long long bit,
+                  const unsigned long long *__restrict__ level_h, const unsigned long long *__restrict__ allow,
+                  const uint32_t *__restrict__ in_off, const int32_t *__restrict__ in_sub,
+                  const uint16_t *__restrict__ in_rel, const unsigned long long *__restrict__ cnt_prev,
+                  unsigned long long *__restrict__ cnt_cur, unsigned long long *__restrict__ cum,
+                  unsigned int *overflow) {
+    __shared__ unsigned long long part[2][4];
+    const int32_t v = rows[blockIdx.x];
+    if (!(level_h[(size_t)v * W + w] & bit)) return;  // block-uniform
+    const unsigned long long total =
+        walk_count_span<MASK, 4>(in_off[v], in_off[v + 1], 0ull, W, w, bit, allow, in_sub, in_rel, cnt_prev, cum, part);
+    if (threadIdx.x == 0) cnt_cur[v] = capped(total, overflow);
+}
+
+// The giant rows (the first in the list of a resident graph) by segments of kGiantSegment entries, a block of sixteen
+// wavefronts each: the segments' own running sums and totals first, then every segment adds what lies before it in its
+// row.  A block per giant row was a chain of 4,096-entry turns, 140 .. 176 us a hop on 3.4M triples; 25 us now (19 + 6).
+__device__ __forceinline__ long long giant_row_of(const uint32_t *__restrict__ seg_first, long long n, uint32_t seg) {
+    long long lo = 0, hi = n;  // the last row whose first segment is <= seg
+    while (hi - lo > 1) {
+        const long long m = (lo + hi) >> 1;
+        if (seg_first[m] <= seg) lo = m; else hi = m;
+    }
+    return lo;
+}
+
+template <bool MASK>
+__global__ void __launch_bounds__(1024)
+k_walk_count_giant(const int32_t *__restrict__ rows, const uint32_t *__restrict__ seg_first, long long n_rows, int W, int w,
+                   unsigned long long bit, const unsigned long long *__restrict__ level_h,
+                   const unsigned long long *__restrict__ allow, const uint32_t *__restrict__ in_off,
+                   const int32_t *__restrict__ in_sub, const uint16_t *__restrict__ in_rel,
+                   const unsigned long long *__restrict__ cnt_prev, unsigned long long *__restrict__ cum,
+                   unsigned long long *__restrict__ seg_total) {
+    __shared__ unsigned long long part[2][16];
+    const long long i = giant_row_of(seg_first, n_rows, blockIdx.x);
+    const int32_t v = rows[i];
+    if (!(level_h[(size_t)v * W + w] & bit)) return;  // block-uniform
+    const uint32_t lo = in_off[v] + (blockIdx.x - seg_first[i]) * (uint32_t)kGiantSegment;
+    const uint32_t hi = min(lo + (uint32_t)kGiantSegment, in_off[v + 1]);
+    const unsigned long long total =
+        walk_count_span<MASK, 16>(lo, hi, 0ull, W, w, bit, allow, in_sub, in_rel, cnt_prev, cum, part);
+    if (threadIdx.x == 0) seg_total[blockIdx.x] = total;
+}
+
+__global__ void __launch_bounds__(1024)
+k_walk_join_giant(const int32_t *__restrict__ rows, const uint32_t *__restrict__ seg_first, long long n_rows, int W, int w,
+                  unsigned long long bit, const unsigned long long *__restrict__ level_h,
+                  const uint32_t *__restrict__ in_off, const unsigned long long *__restrict__ seg_total,
+                  unsigned long long *__restrict__ cnt_cur, unsigned long long *__restrict__ cum, unsigned int *overflow) {
+    const long long i = giant_row_of(seg_first, n_rows, blockIdx.x);
+    const int32_t v = rows[i];
+    if (!(level_h[(size_t)v * W + w] & bit)) return;  // block-uniform
+    unsigned long long before = 0;  // segments of a row: at most 2^31 / 8192, capped at every addition
+    for (uint32_t x = seg_first[i]; x < blockIdx.x; ++x) before = min(before + seg_total[x], kWalkCountLimit);
+    const uint32_t lo = in_off[v] + (blockIdx.x - seg_first[i]) * (uint32_t)kGiantSegment;
+    const uint32_t hi = min(lo + (uint32_t)kGiantSegment, in_off[v + 1]);
+    if (before)
+        for (uint32_t j = lo + threadIdx.x; j < hi; j += 1024) cum[j] += before;
+    if (threadIdx.x == 0 && blockIdx.x + 1 == seg_first[i + 1])
+        cnt_cur[v] = capped(before + seg_total[blockIdx.x], overflow);  // (two terms of at most 2^56; no min() here: the
+                                                                              // compiler folded one with capped()'s compare into a select on a stale condition)
 }
 
 // pref[0] = 0 and the running sum over the entities must not have wrapped
@@ -200,15 +262,18 @@ template <bool MASK>
 static void launch_walk_hop(logoskg_graph *g, int W, int w, unsigned long long bit, const unsigned long long *level_h,
                             const unsigned long long *allow, const int32_t *in_sub, const uint16_t *in_rel,
                             const unsigned long long *prev, unsigned long long *cur, unsigned long long *cum,
-                            unsigned int *overflow, hipStream_t st) {
-    // the giant rows (first in the list of a resident graph) get sixteen wavefronts
+                            unsigned int *overflow, unsigned long long *seg_total, hipStream_t st) {
     const RowClasses &rc = g->in_rows;
-    const int64_t giants = g->num_shards > 1 ? 0 : rc.n_giant;
-    if (giants > 0)
-        k_walk_count_long<MASK, 16><<<dim3((unsigned)giants), dim3(1024), 0, st>>>(
-            rc.longrows, W, w, bit, level_h, allow, g->in_off, in_sub, in_rel, prev, cur, cum, overflow);
+    const int64_t giants = seg_total ? rc.n_giant : 0;
+    if (giants > 0) {
+        const dim3 grid((unsigned)rc.n_giant_segs), block(1024);
+        k_walk_count_giant<MASK><<<grid, block, 0, st>>>(rc.longrows, rc.giant_seg_first, giants, W, w, bit, level_h, allow,
+                                                         g->in_off, in_sub, in_rel, prev, cum, seg_total);
+        k_walk_join_giant<<<grid, block, 0, st>>>(rc.longrows, rc.giant_seg_first, giants, W, w, bit, level_h, g->in_off,
+                                                  seg_total, cur, cum, overflow);
+    }
     if (rc.n_long > giants)
-        k_walk_count_long<MASK, 4><<<dim3((unsigned)(rc.n_long - giants)), dim3(256), 0, st>>>(
+        k_walk_count_long<MASK><<<dim3((unsigned)(rc.n_long - giants)), dim3(256), 0, st>>>(
             rc.longrows + giants, W, w, bit, level_h, allow, g->in_off, in_sub, in_rel, prev, cur, cum, overflow);
     k_walk_count_short<MASK><<<dim3((unsigned)((g->E + 255) / 256)), dim3(256), 0, st>>>(
         g->E, W, w, bit, level_h, allow, g->in_off, in_sub, in_rel, prev, cur, cum, overflow);
@@ -228,11 +293,14 @@ static logoskg_status prepare_walk_tables(logoskg_result *r, int q, int d, hipSt
         set_error("the object-sorted triples of the sharded graph are not available");
         return LOGOSKG_EINTERNAL;
     }
-    // cnt: d + 1 levels, then one word of flags; cum: d rows of T; pref: E + 1
-    LKG_TRY(g->pool.alloc((void **)&r->walk_cnt, ((size_t)(d + 1) * Epad + 8) * 8, st));
+    // cnt: d + 1 levels, then one word of flags and the giant rows' segment totals; cum: d rows of T; pref: E + 1
+    // (a sharded graph has no list of all its giant rows: they are long rows like the others)
+    const size_t segs = g->num_shards > 1 ? 0 : (size_t)g->in_rows.n_giant_segs;
+    LKG_TRY(g->pool.alloc((void **)&r->walk_cnt, ((size_t)(d + 1) * Epad + 8 + segs) * 8, st));
     LKG_TRY(g->pool.alloc((void **)&r->walk_cum, (size_t)std::max(d, 1) * T * 8, st));
     LKG_TRY(g->pool.alloc((void **)&r->walk_pref, (Epad + 8) * 8, st));
     unsigned int *overflow = (unsigned int *)(r->walk_cnt + (size_t)(d + 1) * Epad);
+    unsigned long long *seg_total = segs ? r->walk_cnt + (size_t)(d + 1) * Epad + 8 : nullptr;
     LKG_HIP(hipMemsetAsync(r->walk_cnt, 0, ((size_t)(d + 1) * Epad + 8) * 8, st));
     const size_t plane = Epad * (size_t)W;
     {
@@ -242,8 +310,8 @@ static logoskg_status prepare_walk_tables(logoskg_result *r, int q, int d, hipSt
             const unsigned long long *lvl = r->levels + plane * (size_t)h;
             unsigned long long *prev = r->walk_cnt + (size_t)(h - 1) * Epad, *cur = r->walk_cnt + (size_t)h * Epad;
             unsigned long long *cum = r->walk_cum + (size_t)(h - 1) * T;
-            if (r->has_mask) launch_walk_hop<true>(g, W, w, bit, lvl, r->allow, in_sub, in_rel, prev, cur, cum, overflow, st);
-            else launch_walk_hop<false>(g, W, w, bit, lvl, nullptr, in_sub, in_rel, prev, cur, cum, overflow, st);
+            if (r->has_mask) launch_walk_hop<true>(g, W, w, bit, lvl, r->allow, in_sub, in_rel, prev, cur, cum, overflow, seg_total, st);
+            else launch_walk_hop<false>(g, W, w, bit, lvl, nullptr, in_sub, in_rel, prev, cur, cum, overflow, seg_total, st);
         }
     }
     LKG_HIP(hipGetLastError());
