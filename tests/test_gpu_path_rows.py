@@ -58,3 +58,31 @@ def test_long_rows_every_width_and_both_sides(share, max_paths):
         assert np.array_equal(edges.cpu().numpy(), edges_o[at])
     res.close()
     g.close()
+
+
+@pytest.mark.parametrize("R", [1, 63, 64, 65, 2047, 2048, 2049])  # the LDS whitelist's words and its limit
+def test_whitelist_in_lds_and_gathered(R):
+    import paper_2604_18913_amd as lkg
+    rng = np.random.default_rng(R)
+    E, Q, k, rows = 400, 5, 2, (R - 1, R, R + 1, 3 * R + 7)  # triples ending in the entities 0 .. 3
+    o = np.concatenate([np.full(n, v) for v, n in enumerate(rows)] + [rng.integers(4, E, 3000)]).astype(np.int32)
+    s = rng.integers(4, 60, o.shape[0]).astype(np.int32)
+    r = rng.integers(0, R, o.shape[0]).astype(np.int32)
+    off = np.arange(0, 70 * Q + 1, 70).astype(np.int64)  # more seeds than the seeds' side takes: rows are scanned
+    seeds = rng.integers(4, E, 70 * Q).astype(np.int32)
+    keep = rng.random((Q, R)) < 0.3
+    keep[:, -1] = True
+    mask = np.zeros((Q, (R + 63) // 64), np.uint64)
+    for w in range(R):
+        mask[:, w // 64] |= keep[:, w].astype(np.uint64) << np.uint64(w % 64)
+    pq = np.repeat(np.arange(Q), 5).astype(np.int32)
+    pt = np.tile([0, 1, 2, 3, 4], Q).astype(np.int32)
+    cnt_o, edges_o = oracle.paths(E, s, r, o, off, seeds, k, pq, pt, 16, mask)
+    assert cnt_o.max() > 0
+    g = lkg.Graph(s, r, o, E, R)
+    res = g.khop(off, seeds, k, mask)
+    cnt, edges = g.paths(res, pq, pt, 16)
+    assert np.array_equal(cnt.cpu().numpy(), cnt_o)
+    assert np.array_equal(edges.cpu().numpy(), edges_o)
+    res.close()
+    g.close()
