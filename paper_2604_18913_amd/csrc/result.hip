@@ -51,10 +51,10 @@ __device__ __forceinline__ unsigned long long stage_word(unsigned long long (*st
                                                          const int32_t *__restrict__ tile_ent, long long tile,
                                                          int32_t E, int wave) {
     // Lane v takes word `wave` of the tile's entity v.  Lines of one and four words are read that way (a
-    // wavefront's lanes cover neighbouring 8- or 32-byte lines), with nothing shared between the
-    // wavefronts, so a caller's loads over several tiles are in flight together; through LDS with two
-    // barriers each, they were a chain of 64 dependent rounds in a block of the list kernel (31 us for the
-    // lists of one query on 407,000 entities, 27 us now).  A 16-word line is 128 bytes: loaded with W
+    // wavefront's lanes cover neighbouring 8- or 32-byte lines), without LDS and without a barrier (a caller
+    // whose wavefronts share something needs one of its own), so a caller's loads over several tiles are in
+    // flight together; through LDS with two barriers each, they were a chain of 64 dependent rounds in a block
+    // of the list kernel (31 us for the lists of one query on 407,000 entities, 27 us now).  A 16-word line is 128 bytes: loaded with W
     // consecutive lanes per line and handed over through LDS.
     if constexpr (W <= 4) {
         const long long e = tile_entity(tile_ent, tile, lane(), E);
@@ -345,6 +345,9 @@ __global__ void __launch_bounds__(64 * W) k_lists(FillArgs a) {
     }
     uint16_t *ent = s_ent[wave];
     uint8_t *hp = s_hop[NB > 0 ? wave : 0];
+    // blk_ent is written by all wavefronts and read by each (here, behind the plane loads, so that they do not wait
+    // for the ids).  stage_word has barriers of its own only for 16-word lines.
+    if constexpr (W <= 4) __syncthreads();
     while (present) {
         const int qq = __ffsll((long long)present) - 1;
         present &= present - 1;

@@ -85,3 +85,23 @@ def test_min_hop_levels_and_error_paths():
     assert np.array_equal(e.cpu().numpy(), want_ent[want_off[Q + 5]:want_off[Q + 70]])
     res.close()
     g.close()
+
+
+@pytest.mark.parametrize("num_queries", [65, 128, 200, 256])
+def test_levels_and_lists_without_predecessors_of_four_word_planes(num_queries):
+    m = lkg()
+    w = kggen.config2(0.02, num_queries=num_queries)
+    off, ent, hop, _, _ = oracle.khop(w.num_entities, w.subj, w.rel, w.obj, w.seed_off, w.seeds, w.k)
+    g = m.Graph(w.subj, w.rel, w.obj, w.num_entities, w.num_relations)
+    res = g.khop(w.seed_off, w.seeds, w.k)
+    for q0, q1 in ((0, num_queries), (3, num_queries - 1)):
+        a, b = off[q0], off[q1]
+        for want_hop in (False, True):
+            e, h, _ = res.fetch(q0, q1, want_hop=want_hop, want_pred=False)
+            assert np.array_equal(e.cpu().numpy(), ent[a:b])
+            assert h is None or np.array_equal(h.cpu().numpy(), hop[a:b])
+        for level in range(w.k + 1):
+            _, e = res.level(level, q0, q1)
+            assert np.array_equal(e.cpu().numpy(), ent[a:b][hop[a:b] == level])
+    res.close()
+    g.close()

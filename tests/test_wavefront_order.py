@@ -1,0 +1,129 @@
+"""Kernels whose wavefronts hand data over in LDS, run on the CPU (wavefronts.h) with the wavefronts of a
+block one after the other between two barriers, first to last and last to first: the results may not depend
+on it."""
+import os
+import re
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2604_18913_amd", "csrc")
+
+
+def text(name):
+    with open(os.path.join(CSRC, name)) as f:
+        return f.read()
+
+
+def between(src, first, last):
+    at = src.index(first)
+    return src[at:src.index(last, at)]
+
+
+def definition(src, head):
+    """From `head` (the start of a definition) to its closing brace."""
+    at = src.index(head)
+    i = src.index("{", at)
+    depth = 0
+    while True:
+        depth += {"{": 1, "}": -1}.get(src[i], 0)
+        i += 1
+        if depth == 0:
+            return src[at:i] + (";" if src[i] == ";" else "") + "\n"
+
+
+def run(tmp_path, code):
+    code = re.sub(r"asm volatile\([^;]*\);", "", code)
+    cpp = tmp_path / "kernel.cpp"
+    cpp.write_text('#include "wavefronts.h"\n' + code)
+    exe = tmp_path / "kernel"
+    p = subprocess.run(["g++", "-std=c++17", "-O1", "-w", "-I", HERE, "-o", str(exe), str(cpp)],
+                       capture_output=True, text=True, timeout=300)
+    assert p.returncode == 0, p.stderr[-4000:]
+    p = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
+    assert p.returncode == 0, p.stdout + p.stderr
+
+
+def device_helpers():
+    common = text("common.h")
+    return between(common, "__device__ __forceinline__ int lane()", "inline int words_for_queries")
+
+
+LISTS_MAIN = """
+template <int W, int NB> int check(const std::vector<int> &waves, bool listed) {
+    constexpr int Qp = 64 * W;
+    const int E = 2500, k = 3, Q = W == 1 ? 50 : 230, Epad = (E + 63) / 64 * 64;
+    unsigned long long rng = 7 + W;
+    auto next = [&]() { rng = rng * 6364136223846793005ull + 1442695040888963407ull; return (unsigned)(rng >> 33); };
+    std::vector<unsigned long long> levels((size_t)(k + 1) * Epad * W), visited((size_t)Epad * W);
+    std::vector<int> ent;
+    for (int e = 0; e < E; ++e) {
+        if (listed && next() % 3 == 0) continue;
+        ent.push_back(e);
+        for (int q = 0; q < Q; ++q)
+            if (next() % 4 == 0) {
+                levels[((size_t)(next() % (k + 1)) * Epad + e) * W + q / 64] |= 1ull << (q & 63);
+                visited[(size_t)e * W + q / 64] |= 1ull << (q & 63);
+            }
+    }
+    const int n = (int)ent.size(), tiles = (n + 63) / 64, supers = (tiles + 15) / 16;
+    ent.resize(n + 64, -1);
+    std::vector<uint16_t> tile_base((size_t)tiles * Qp);
+    std::vector<uint32_t> super_base((size_t)supers * Qp), mega_base(Qp);
+    std::vector<long long> off(Qp + 1);
+    std::vector<int> want_ent, want_hop;
+    for (int q = 0; q < Qp; ++q) {
+        off[q] = (long long)want_ent.size();
+        for (int i = 0; i < n; ++i) {
+            const long long before = (long long)want_ent.size() - off[q];
+            if (i % 1024 == 0) super_base[(size_t)(i / 1024) * Qp + q] = (uint32_t)before;
+            if (i % 64 == 0) tile_base[(size_t)(i / 64) * Qp + q] = (uint16_t)(before - super_base[(size_t)(i / 1024) * Qp + q]);
+            if (!((visited[(size_t)ent[i] * W + q / 64] >> (q & 63)) & 1)) continue;
+            int h = 0;
+            while (!((levels[((size_t)h * Epad + ent[i]) * W + q / 64] >> (q & 63)) & 1)) ++h;
+            want_ent.push_back(ent[i]);
+            want_hop.push_back(h);
+        }
+    }
+    off[Qp] = (long long)want_ent.size();
+    std::vector<int32_t> entity(want_ent.size(), -7);
+    std::vector<uint8_t> hop(want_ent.size(), 99);
+    FillArgs a;
+    memset((void *)&a, 0, sizeof(a));
+    a.E = E; a.Q = Q; a.k = k; a.q0 = 0; a.q1 = Q;
+    a.ntiles = tiles; a.tile_ent = listed ? ent.data() : nullptr;
+    a.plane = (long long)Epad * W; a.visited = visited.data(); a.levels = levels.data();
+    a.tile_base = tile_base.data(); a.super_base = super_base.data(); a.mega_base = mega_base.data();
+    a.reached_off = off.data(); a.entity = entity.data(); a.hop = hop.data();
+    run_grid((unsigned)supers, 64 * W, waves, [&] { k_lists<W, NB, 16>(a); });
+    int bad = 0;
+    for (size_t i = 0; i < want_ent.size(); ++i) bad += entity[i] != want_ent[i] || (NB && hop[i] != want_hop[i]);
+    printf("%d words, %d hop bits, list %d: %d of %zu entries wrong\\n", W, NB, listed, bad, want_ent.size());
+    return bad;
+}
+
+int main() {
+    int bad = 0;
+    for (bool listed : {false, true}) {
+        bad += check<1, 0>({0}, listed) + check<1, 2>({0}, listed);
+        for (const std::vector<int> &waves : {std::vector<int>{0, 1, 2, 3}, std::vector<int>{3, 2, 1, 0}})
+            bad += check<4, 0>(waves, listed) + check<4, 2>(waves, listed);
+    }
+    return bad != 0;
+}
+"""
+
+
+def test_lists_of_narrow_planes(tmp_path):
+    common, result = text("common.h"), text("result.hip")
+    run(tmp_path, "\n".join([
+        between(common, "constexpr int kTileEntities", "struct RowSegment"),
+        device_helpers(),
+        definition(common, "struct FillArgs {"),
+        definition(result, "__device__ __forceinline__ long long tile_entity("),
+        "template <int W>\n" + definition(result, "__device__ __forceinline__ unsigned long long stage_word("),
+        definition(result, "__device__ __forceinline__ unsigned long long range_bits("),
+        definition(result, "__device__ __forceinline__ long long super_start("),
+        "template <int W, int NB, int TILES>\n" + definition(result, "__global__ void __launch_bounds__(64 * W) k_lists("),
+        LISTS_MAIN]))
