@@ -152,7 +152,9 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_search(SmallArgs a) {
     // ---- hops
     for (;; ++h) {
         // the frontier's rows: where each starts in their concatenation, and what a general hop wants to know
-        const int n = s_n[cur];
+        // (the length of s_all is read ahead of the barriers below: the pushes behind them grow it, and the
+        // decision between them has to be the same in every wavefront)
+        const int n = s_n[cur], n_all = s_nall;
         int edges = 0;
         __syncthreads();
         if (t == 0) {
@@ -183,7 +185,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_search(SmallArgs a) {
         if (t == 0) a.rep->reached[h] = n;
         const bool last = h == a.hops;
         if (rows == 0 || (last && !a.more)) break;
-        large = last || edges > kSmallEdges || s_work > (unsigned)kSmallPairs || s_nall + edges > kSmallEntities ||
+        large = last || edges > kSmallEdges || s_work > (unsigned)kSmallPairs || n_all + edges > kSmallEntities ||
                 (!a.force_push && (long long)edges * 12 > a.T);
         if (large) {
             // the general path goes on with this frontier: its exact size

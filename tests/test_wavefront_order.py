@@ -127,3 +127,65 @@ def test_lists_of_narrow_planes(tmp_path):
         definition(result, "__device__ __forceinline__ long long super_start("),
         "template <int W, int NB, int TILES>\n" + definition(result, "__global__ void __launch_bounds__(64 * W) k_lists("),
         LISTS_MAIN]))
+
+
+SMALL_MAIN = """
+// n_seeds seeds with `fan` triples each into objects of their own: the search takes one hop
+static int check(const std::vector<int> &waves, int n_seeds, int fan, bool whole) {
+    const int edges = n_seeds * fan, E = n_seeds + edges;
+    std::vector<uint32_t> off(E + 1, edges);
+    std::vector<int32_t> obj(edges), seeds(n_seeds), kept(n_seeds), ent(kSmallEntities, -1);
+    std::vector<uint16_t> rel(edges);
+    for (int i = 0; i < n_seeds; ++i) {
+        seeds[i] = i;
+        off[i] = (uint32_t)(i * fan);
+    }
+    for (int j = 0; j < edges; ++j) obj[j] = E - 1 - j;
+    const int actw = (E + 63) / 64 * 2;
+    std::vector<unsigned long long> visited(E + 64), levels(2 * (size_t)(E + 64));
+    std::vector<uint32_t> act(2 * actw);
+    long long seed_off[2] = {0, n_seeds}, kept_off[2], list_off[65];
+    SmallReport rep;
+    memset((void *)&rep, 0xee, sizeof(rep));
+    SmallArgs a;
+    memset((void *)&a, 0, sizeof(a));
+    a.Q = 1; a.hops = 1; a.want_counts = 1; a.force_push = 1;
+    a.E = E; a.T = edges; a.num_seeds = n_seeds; a.plane = E + 64; a.actw = actw;
+    a.seed_off = seed_off; a.seeds = seeds.data(); a.out_off = off.data(); a.out_obj = obj.data(); a.out_rel = rel.data();
+    a.visited = visited.data(); a.levels = levels.data(); a.act = act.data();
+    a.kept_off = kept_off; a.kept_seeds = kept.data(); a.ent = ent.data(); a.off = list_off; a.rep = &rep;
+    run_grid(1, kSmallThreads, waves, [&] { k_small_search(a); });
+    int bad = 0;
+    if (whole) {
+        bad = rep.status != kSmallDone || rep.hops != 1 || rep.n_all != E || rep.off[64] != E || rep.reached[1] != edges;
+        for (int e = 0; e < E; ++e)
+            bad += ent[e] != e || visited[e] != 1 || levels[e] != (e < n_seeds) || levels[(size_t)a.plane + e] != (e >= n_seeds);
+    } else {  // handed over before the hop, nothing of which may have been taken
+        bad = rep.status != kSmallGoOn || rep.hops != 0 || rep.n_all != n_seeds || rep.edges[0] != edges || rep.rows[0] != n_seeds;
+        for (int e = 0; e < E; ++e) bad += visited[e] != (e < n_seeds) || levels[(size_t)a.plane + e] != 0;
+    }
+    printf("%d seeds, %d triples: status %d, %d entities, %d wrong\\n", n_seeds, edges, rep.status, rep.n_all, bad);
+    return bad;
+}
+
+int main() {
+    std::vector<int> forward(kSmallThreads / 64), backward;
+    std::iota(forward.begin(), forward.end(), 0);
+    backward.assign(forward.rbegin(), forward.rend());
+    int bad = 0;
+    for (const auto &waves : {forward, backward})
+        bad += check(waves, 2048, 1, true) + check(waves, 683, 3, false) + check(waves, 682, 3, true) + check(waves, 1, 2048, true);
+    return bad != 0;
+}
+"""
+
+
+def test_a_small_search_at_the_limit_of_its_list(tmp_path):
+    # 2,048 seeds and 2,048 triples: the hop fills the list of 4,096 reached entities exactly
+    common, small = text("common.h"), text("small.hip")
+    run(tmp_path, "\n".join([
+        between(common, "constexpr int kTailMaxDegree", "struct RowSegment"),
+        between(common, "constexpr int kSmallEdges", "struct RowClasses"),
+        device_helpers(),
+        between(small, "constexpr int kSmallThreads", "// One block per fetched query"),
+        SMALL_MAIN]))
