@@ -24,9 +24,13 @@
 
 namespace lkg {
 
-// counts stay below 2^56 (7.2 x 10^16): 64 of them add up without wrapping, so one check per
-// 64 row entries is enough
+// Counts stay below 2^56 (7.2 x 10^16), so up to 256 of them add up without wrapping.  Whoever adds more looks at
+// the sums in between: `high` collects the upper halves of all of them, and a bit from 24 on in it says that one
+// reached the limit (the tables are not used then, so what wrapped later does not matter).  No min() with the limit:
+// where a min and a branch on the same comparison of two uniform 64-bit values met, the compiler's scalar select read
+// a condition bit that the comparison had not written.
 constexpr unsigned long long kWalkCountLimit = 1ull << 56;
+constexpr int kWalkSummands = 256;
 
 __device__ __forceinline__ unsigned long long wave_incl_scan64(unsigned long long v) {
 #pragma unroll
@@ -63,9 +67,12 @@ __device__ __forceinline__ unsigned long long walk_entry(uint32_t j, int W, int 
     return cnt_prev[in_sub[j]];
 }
 
-// the row's total is past the limit: reported by the host, the tables are not used then
-__device__ __forceinline__ unsigned long long capped(unsigned long long running, unsigned int *overflow) {
-    if (running < kWalkCountLimit) return running;
+__device__ __forceinline__ uint32_t upper_half(unsigned long long x) { return (uint32_t)(x >> 32); }
+
+// a sum on the way was past the limit: reported by the host
+__device__ __forceinline__ unsigned long long capped(unsigned long long total, uint32_t high, unsigned int *overflow) {
+    static_assert(kWalkCountLimit >> 32 == 1ull << 24, "the bits of `high` from 24 on");
+    if ((high >> 24) == 0u) return total;
     atomicOr(overflow, 1u);
     return kWalkCountLimit - 1;
 }
@@ -82,7 +89,8 @@ k_walk_count_short(int32_t E, int W, int w, unsigned long long bit, const unsign
     const uint32_t lo = in_off[e], hi = in_off[e + 1];
     if (hi - lo > (uint32_t)kTailMaxDegree) return;
     constexpr int U = 4;
-    unsigned long long running = 0;  // at most 32 counts below 2^56: cannot wrap
+    static_assert(kTailMaxDegree <= kWalkSummands, "a short row's sum cannot wrap");
+    unsigned long long running = 0;
     for (uint32_t j0 = lo; j0 < hi; j0 += U) {
         unsigned long long c[U];
 #pragma unroll
@@ -94,22 +102,24 @@ k_walk_count_short(int32_t E, int W, int w, unsigned long long bit, const unsign
             running += c[u];
         }
     }
-    cnt_cur[e] = capped(running, overflow);
+    cnt_cur[e] = capped(running, upper_half(running), overflow);
 }
 
 // Entries [lo, hi) of one row by a block of NW wavefronts, U entries per lane and turn (one wavefront apart, so
-// that every load and store is contiguous): cum = running sums from `running` on; returns the capped total.
+// that every load and store is contiguous): cum = running sums from the first one on; returns the total.
 template <bool MASK, int NW>
-__device__ __forceinline__ unsigned long long walk_count_span(uint32_t lo, uint32_t hi, unsigned long long running, int W, int w,
-                                                              unsigned long long bit,
+__device__ __forceinline__ unsigned long long walk_count_span(uint32_t lo, uint32_t hi, int W, int w, unsigned long long bit,
                                                               const unsigned long long *__restrict__ allow,
                                                               const int32_t *__restrict__ in_sub,
                                                               const uint16_t *__restrict__ in_rel,
                                                               const unsigned long long *__restrict__ cnt_prev,
                                                               unsigned long long *__restrict__ cum,
-                                                              unsigned long long (*part)[NW]) {
+                                                              unsigned long long (*part)[NW], uint32_t &high) {
     constexpr int U = NW >= 16 ? 4 : 2, NT = 64 * NW;
+    static_assert(64 * U <= kWalkSummands, "a wavefront's sum of one turn cannot wrap");
+    static_assert(NW + 1 <= kWalkSummands, "nor can the turn's, while its parts are below the limit");
     const int wave = threadIdx.x >> 6;
+    unsigned long long running = 0;
     int buf = 0;
     for (uint32_t j0 = lo; j0 < hi; j0 += NT * U, buf ^= 1) {
         const uint32_t base = j0 + (uint32_t)(wave * 64 * U + lane());
@@ -129,9 +139,10 @@ __device__ __forceinline__ unsigned long long walk_count_span(uint32_t lo, uint3
         for (int x = 0; x < NW; ++x) {
             const unsigned long long p = part[buf][x];
             if (x < wave) before += p;
-            // 4,096 counts below 2^56 stay below 2^68: the turn's sum is capped piece by piece instead of wrapping
-            total = min(total + min(p, kWalkCountLimit), kWalkCountLimit);
+            total += p;
+            high |= upper_half(p);
         }
+        high |= upper_half(total);
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (base + u * 64 < hi) cum[base + u * 64] = before + (incl[u] - c[u]);
@@ -152,9 +163,10 @@ k_walk_count_long(const int32_t *__restrict__ rows, int W, int w, unsigned long 
     __shared__ unsigned long long part[2][4];
     const int32_t v = rows[blockIdx.x];
     if (!(level_h[(size_t)v * W + w] & bit)) return;  // block-uniform
+    uint32_t high = 0;
     const unsigned long long total =
-        walk_count_span<MASK, 4>(in_off[v], in_off[v + 1], 0ull, W, w, bit, allow, in_sub, in_rel, cnt_prev, cum, part);
-    if (threadIdx.x == 0) cnt_cur[v] = capped(total, overflow);
+        walk_count_span<MASK, 4>(in_off[v], in_off[v + 1], W, w, bit, allow, in_sub, in_rel, cnt_prev, cum, part, high);
+    if (threadIdx.x == 0) cnt_cur[v] = capped(total, high, overflow);
 }
 
 // The giant rows (the first in the list of a resident graph) by segments of kGiantSegment entries, a block of sixteen
@@ -176,16 +188,17 @@ k_walk_count_giant(const int32_t *__restrict__ rows, const uint32_t *__restrict_
                    const unsigned long long *__restrict__ allow, const uint32_t *__restrict__ in_off,
                    const int32_t *__restrict__ in_sub, const uint16_t *__restrict__ in_rel,
                    const unsigned long long *__restrict__ cnt_prev, unsigned long long *__restrict__ cum,
-                   unsigned long long *__restrict__ seg_total) {
+                   unsigned long long *__restrict__ seg_total, unsigned int *overflow) {
     __shared__ unsigned long long part[2][16];
     const long long i = giant_row_of(seg_first, n_rows, blockIdx.x);
     const int32_t v = rows[i];
     if (!(level_h[(size_t)v * W + w] & bit)) return;  // block-uniform
     const uint32_t lo = in_off[v] + (blockIdx.x - seg_first[i]) * (uint32_t)kGiantSegment;
     const uint32_t hi = min(lo + (uint32_t)kGiantSegment, in_off[v + 1]);
+    uint32_t high = 0;
     const unsigned long long total =
-        walk_count_span<MASK, 16>(lo, hi, 0ull, W, w, bit, allow, in_sub, in_rel, cnt_prev, cum, part);
-    if (threadIdx.x == 0) seg_total[blockIdx.x] = total;
+        walk_count_span<MASK, 16>(lo, hi, W, w, bit, allow, in_sub, in_rel, cnt_prev, cum, part, high);
+    if (threadIdx.x == 0) seg_total[blockIdx.x] = capped(total, high, overflow);
 }
 
 __global__ void __launch_bounds__(1024)
@@ -196,15 +209,20 @@ k_walk_join_giant(const int32_t *__restrict__ rows, const uint32_t *__restrict__
     const long long i = giant_row_of(seg_first, n_rows, blockIdx.x);
     const int32_t v = rows[i];
     if (!(level_h[(size_t)v * W + w] & bit)) return;  // block-uniform
-    unsigned long long before = 0;  // segments of a row: at most 2^31 / 8192, capped at every addition
-    for (uint32_t x = seg_first[i]; x < blockIdx.x; ++x) before = min(before + seg_total[x], kWalkCountLimit);
+    unsigned long long before = 0;
+    uint32_t high = 0;
+    for (uint32_t x = seg_first[i]; x < blockIdx.x; ++x) {
+        before += seg_total[x];
+        high |= upper_half(before);
+    }
     const uint32_t lo = in_off[v] + (blockIdx.x - seg_first[i]) * (uint32_t)kGiantSegment;
     const uint32_t hi = min(lo + (uint32_t)kGiantSegment, in_off[v + 1]);
     if (before)
         for (uint32_t j = lo + threadIdx.x; j < hi; j += 1024) cum[j] += before;
-    if (threadIdx.x == 0 && blockIdx.x + 1 == seg_first[i + 1])
-        cnt_cur[v] = capped(before + seg_total[blockIdx.x], overflow);  // (two terms of at most 2^56; no min() here: the
-                                                                              // compiler folded one with capped()'s compare into a select on a stale condition)
+    if (threadIdx.x == 0 && blockIdx.x + 1 == seg_first[i + 1]) {
+        const unsigned long long total = before + seg_total[blockIdx.x];
+        cnt_cur[v] = capped(total, high | upper_half(total), overflow);
+    }
 }
 
 // pref[0] = 0 and the running sum over the entities must not have wrapped
@@ -268,7 +286,7 @@ static void launch_walk_hop(logoskg_graph *g, int W, int w, unsigned long long b
     if (giants > 0) {
         const dim3 grid((unsigned)rc.n_giant_segs), block(1024);
         k_walk_count_giant<MASK><<<grid, block, 0, st>>>(rc.longrows, rc.giant_seg_first, giants, W, w, bit, level_h, allow,
-                                                         g->in_off, in_sub, in_rel, prev, cum, seg_total);
+                                                         g->in_off, in_sub, in_rel, prev, cum, seg_total, overflow);
         k_walk_join_giant<<<grid, block, 0, st>>>(rc.longrows, rc.giant_seg_first, giants, W, w, bit, level_h, g->in_off,
                                                   seg_total, cur, cum, overflow);
     }

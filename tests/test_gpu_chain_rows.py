@@ -55,3 +55,28 @@ def test_too_many_chains_are_refused_whatever_the_row(parallel, last_that_fits):
     assert err.value.status == 4
     res.close()
     g.close()
+
+
+@pytest.mark.parametrize("parallel, hops, last", [(8192, 4, 16), (4096, 4, 256), (1 << 14, 3, 1 << 14)])
+@pytest.mark.parametrize("missing", [0, 1])
+def test_the_sum_of_a_row_at_the_limit(parallel, hops, last, missing):
+    import paper_2604_18913_amd as lkg
+    # entities 0 .. hops, neighbours joined by `parallel` triples, then a row of `last` triples from the last of
+    # them: parallel^hops * last = 2^56 chains end in it, which is one entry too many
+    assert parallel ** hops * last == 1 << 56
+    n = last - missing
+    s = np.concatenate([np.repeat(np.arange(hops), parallel), np.full(n, hops)]).astype(np.int32)
+    r = np.concatenate([np.tile(np.arange(parallel), hops), np.arange(n)]).astype(np.int32)
+    g = lkg.Graph(s, r, s + 1, hops + 2, max(parallel, last))
+    res = g.khop(np.array([0, 1], np.int64), np.zeros(1, np.int32), hops + 1, walk_exact=True)
+    if missing:
+        assert res.walks_count(0, hops + 1) == parallel ** hops * n
+        edges, target = res.walks_fetch(0, hops + 1, parallel ** hops * n - 3, 3)
+        assert np.array_equal(target.cpu().numpy(), np.full(3, hops + 1))
+        assert edges.cpu().numpy()[:, -1].tolist() == [parallel * hops + n - 1] * 3
+    else:
+        with pytest.raises(lkg.LogosKGError) as err:
+            res.walks_count(0, hops + 1)
+        assert err.value.status == 4
+    res.close()
+    g.close()
