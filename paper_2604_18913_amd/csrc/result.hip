@@ -2164,9 +2164,8 @@ extern "C" logoskg_status logoskg_result_fetch(logoskg_result *r, int32_t q0, in
     hipStream_t st = (hipStream_t)stream;
     r->last_stream = st;
     if (r->small_n >= 0) {
-        if (!g->prof.counters && (!pred || ensure_out_eid(g, st) == LOGOSKG_OK))
-            return small_fetch(r, q0, q1, entity, hop, pred, st);
-        if (!r->tile_base) LKG_TRY(count_reached(r, st));  // the general kernels' tables (same offsets)
+        if (!g->prof.counters) return small_fetch(r, q0, q1, entity, hop, pred, st);
+        if (!r->tile_base) LKG_TRY(count_reached(r, st));  // measured kernels: the general ones and their tables (same offsets)
     }
     const int W = r->W;
     FillArgs a = {};

@@ -372,7 +372,9 @@ logoskg_status small_search(logoskg_graph *g, logoskg_result *r, const logoskg_q
     r->small_ent = reinterpret_cast<int32_t *>(r->small_off + 65);
     SmallArgs a = {};
     a.Q = r->Q; a.hops = std::min(r->k, kSmallHops); a.more = r->k > kSmallHops;
-    a.want_counts = want_counts && !a.more;
+    // (the lists' predecessors come from SUB's triple indices: a graph that does not hold them - built on the host -
+    // keeps to the general kernels' tables, so that a fetch allocates nothing and waits for nothing)
+    a.want_counts = want_counts && !a.more && g->out_eid;
     a.walk_exact = r->walk_exact; a.force_push = force_push;
     a.E = g->E; a.T = g->T; a.num_seeds = b->num_seeds; a.plane = r->Epad; a.actw = r->Epad / 32;
     a.seed_off = reinterpret_cast<const long long *>(b->seed_off); a.seeds = b->seeds;

@@ -112,3 +112,27 @@ def test_bad_seeds_are_refused():
     assert list(res.offsets()) == [0, 3]
     res.close()
     g.close()
+
+
+def test_lists_of_a_host_built_graph_take_no_memory():
+    import paper_2604_18913_amd as lkg
+    rng = np.random.default_rng(3)
+    E, T, R = 9001, 14000, 5
+    s, o, r = (rng.integers(0, n, T).astype(np.int32) for n in (E, E, R))
+    off, seeds = seed_lists([rng.integers(0, E, 2) for _ in range(30)])
+    want = oracle.khop(E, s, r, o, off, seeds, 2)
+    g = lkg.Graph(s, r, o, E, R, host_build=True)
+    for triple_indices in (False, True):  # (the path listing builds them)
+        if triple_indices:
+            g.paths(res, np.zeros(1, np.int32), want[1][:1])
+            res.close()
+        res = g.khop(off, seeds, 2)
+        assert np.array_equal(res.offsets(), want[0])
+        held = g.info()["device_bytes"]
+        for q0, q1 in ((0, 30), (4, 9)):
+            got = res.fetch(q0, q1)
+            assert g.info()["device_bytes"] == held
+            for x, y in zip(got, want[1:4]):
+                assert np.array_equal(x.cpu().numpy(), y[want[0][q0]:want[0][q1]])
+    res.close()
+    g.close()
