@@ -51,6 +51,7 @@ __global__ void k_gather_sub_rows(const uint32_t *__restrict__ eid, long long T,
     out_rel[p] = (uint16_t)rel[t];
 }
 
+// (in_eid NULL: the triple indices stay in eid)
 __global__ void k_gather_obj_rows(const uint32_t *__restrict__ eid, long long T, const int32_t *__restrict__ subj,
                                   const int32_t *__restrict__ rel, int32_t *in_sub, uint16_t *in_rel,
                                   int32_t *in_eid) {
@@ -59,7 +60,7 @@ __global__ void k_gather_obj_rows(const uint32_t *__restrict__ eid, long long T,
     const uint32_t t = eid[p];
     in_sub[p] = subj[t];
     in_rel[p] = (uint16_t)rel[t];
-    in_eid[p] = (int32_t)t;
+    if (in_eid) in_eid[p] = (int32_t)t;
 }
 
 // subject_of[t] = subject of triple t, from the object-sorted arrays (which keep the triple index)
@@ -109,14 +110,13 @@ logoskg_status build_csr_on_device(logoskg_graph *g, const int32_t *subj, const 
     const int32_t E = g->E;
     Scratch tmp;
     int32_t *d_subj = nullptr, *d_rel = nullptr, *d_obj = nullptr;
-    uint32_t *d_iota = nullptr, *d_keys = nullptr, *d_eid = nullptr;
+    uint32_t *d_iota = nullptr, *d_keys = nullptr;
     unsigned long long *d_bad = nullptr;
     LKG_TRY(tmp.get(&d_subj, (size_t)T));
     LKG_TRY(tmp.get(&d_rel, (size_t)T));
     LKG_TRY(tmp.get(&d_obj, (size_t)T));
     LKG_TRY(tmp.get(&d_iota, (size_t)T));
     LKG_TRY(tmp.get(&d_keys, (size_t)T));
-    LKG_TRY(tmp.get(&d_eid, (size_t)T));
     LKG_TRY(tmp.get(&d_bad, 1));
     if (T > 0) {
         LKG_HIP(hipMemcpy(d_subj, subj, (size_t)T * 4, hipMemcpyHostToDevice));
@@ -140,7 +140,7 @@ logoskg_status build_csr_on_device(logoskg_graph *g, const int32_t *subj, const 
     // one temporary buffer that serves the sort and the scan
     size_t sort_bytes = 0, scan_bytes = 0;
     LKG_HIP(rocprim::radix_sort_pairs(nullptr, sort_bytes, reinterpret_cast<const uint32_t *>(d_subj), d_keys, d_iota,
-                                      d_eid, (size_t)std::max<int64_t>(T, 1), 0u, key_bits));
+                                      d_iota, (size_t)std::max<int64_t>(T, 1), 0u, key_bits));
     LKG_HIP(rocprim::inclusive_scan(nullptr, scan_bytes, (uint32_t *)nullptr, (uint32_t *)nullptr, (size_t)E + 1,
                                     rocprim::plus<uint32_t>()));
     const size_t tmp_bytes = std::max(sort_bytes, scan_bytes);
@@ -152,6 +152,8 @@ logoskg_status build_csr_on_device(logoskg_graph *g, const int32_t *subj, const 
         g->static_bytes += std::max<size_t>(bytes, 4);
         return LOGOSKG_OK;
     };
+    // Both sorts leave the triple indices where the graph keeps them, so that they need no column of their own beside
+    // it (40 bytes per triple and the sort's buffers at the peak; 44 with one).
     // SUB: rows by subject
     LKG_TRY(keep((void **)&g->out_off, ((size_t)E + 1) * 4));
     LKG_TRY(keep((void **)&g->out_obj, (size_t)T * 4));
@@ -165,9 +167,10 @@ logoskg_status build_csr_on_device(logoskg_graph *g, const int32_t *subj, const 
     LKG_TRY(keep((void **)&g->in_sub, (size_t)T * 4));
     LKG_TRY(keep((void **)&g->in_rel, (size_t)T * 2));
     LKG_TRY(keep((void **)&g->in_eid, (size_t)T * 4));
-    LKG_TRY(sort_by(d_obj, T, E, key_bits, d_iota, d_keys, d_eid, g->in_off, d_tmp, tmp_bytes));
+    uint32_t *const d_in_eid = reinterpret_cast<uint32_t *>(g->in_eid);
+    LKG_TRY(sort_by(d_obj, T, E, key_bits, d_iota, d_keys, d_in_eid, g->in_off, d_tmp, tmp_bytes));
     if (T > 0)
-        k_gather_obj_rows<<<dim3(grid_for(T)), dim3(kBlock)>>>(d_eid, T, d_subj, d_rel, g->in_sub, g->in_rel, g->in_eid);
+        k_gather_obj_rows<<<dim3(grid_for(T)), dim3(kBlock)>>>(d_in_eid, T, d_subj, d_rel, g->in_sub, g->in_rel, nullptr);
     LKG_HIP(hipGetLastError());
     ooff->resize((size_t)E + 1);
     ioff->resize((size_t)E + 1);
