@@ -54,3 +54,15 @@ res = g.khop(np.array([0, 2], np.int64), np.array([5, 7], np.int32), 2)
 want = oracle.khop(E, s, r, o, np.array([0, 2], np.int64), np.array([5, 7], np.int32), 2)
 assert all(np.array_equal(x.cpu().numpy(), y) for x, y in zip(res.fetch(), want[1:4]))
 """)
+
+
+def test_a_resident_graph_takes_one_block_of_pinned_memory(tmp_path):
+    run(tmp_path, """
+E, T, R = 10_000, 50_000, 20
+_, s, r, o = graph(E, T, R, 2)
+lkg.Graph(s, r, o, E, R).close()
+mem.memory_watch(0)
+g = lkg.Graph(s, r, o, E, R)
+print(mem.memory_host_calls(), mem.memory_device_calls())
+assert mem.memory_host_calls() == 1
+""")
