@@ -298,8 +298,7 @@ logoskg_status sorter_object_order(TripleSorter *s, int32_t *h_sub, uint16_t *h_
 // g->out_eid[p] = index of the triple behind entry p of the subject-sorted CSR (SUB's rows, Eq. 1).
 // The build keeps triple indices only with the object-sorted arrays; this repeats the stable sort
 // by subject on (subject, triple index) pairs, so the order is the one of out_obj / out_rel.
-logoskg_status ensure_out_eid(logoskg_graph *g, hipStream_t st) {
-    if (g->out_eid) return LOGOSKG_OK;
+static logoskg_status build_out_eid(logoskg_graph *g, hipStream_t st) {
     // a sharded graph keeps the object-sorted triples in pinned host memory (read in place here) and
     // its rows of SUB in the shard-grouped order: the sort key is the place where a subject's run begins
     const int32_t *in_sub = g->in_sub, *in_eid = g->in_eid;
@@ -344,6 +343,15 @@ logoskg_status ensure_out_eid(logoskg_graph *g, hipStream_t st) {
     g->out_eid = eid;
     g->static_bytes += std::max<size_t>((size_t)T, 1) * 4;
     return LOGOSKG_OK;
+}
+
+// Callers that can do without them go on after a failure, so it must not be what their own look at the runtime's
+// last error finds.
+logoskg_status ensure_out_eid(logoskg_graph *g, hipStream_t st) {
+    if (g->out_eid) return LOGOSKG_OK;
+    const logoskg_status s = build_out_eid(g, st);
+    if (s != LOGOSKG_OK) (void)hipGetLastError();
+    return s;
 }
 
 }  // namespace lkg

@@ -66,3 +66,28 @@ g = lkg.Graph(s, r, o, E, R)
 print(mem.memory_host_calls(), mem.memory_device_calls())
 assert mem.memory_host_calls() == 1
 """)
+
+
+def test_no_room_for_the_triple_indices_of_a_host_built_graph(tmp_path):
+    run(tmp_path, """
+E, T, R = 9_000, 60_011, 7
+rng, s, r, o = graph(E, T, R, 3)
+o[:20_000] = rng.integers(0, 300, 20_000)      # object rows of more than 32 entries
+for Q in (20, 300):                            # one- and sixteen-word planes
+    off = np.arange(Q + 1, dtype=np.int64)
+    seeds = rng.integers(0, E, Q).astype(np.int32)
+    want = oracle.khop(E, s, r, o, off, seeds, 2)
+    g = lkg.Graph(s, r, o, E, R, host_build=True)
+    mem.memory_watch(4 * T)
+    res = g.khop(off, seeds, 2)
+    assert all(np.array_equal(x.cpu().numpy(), y) for x, y in zip(res.fetch(), want[1:4]))
+    q, t = np.zeros(1, np.int32), want[1][want[0][1] - 1:want[0][1]]
+    count, edges = g.paths(res, q, t)
+    assert mem.memory_refusals() > 0
+    mem.memory_watch(0)
+    assert all(np.array_equal(x.cpu().numpy(), y) for x, y in zip(res.fetch(), want[1:4]))
+    count2, edges2 = g.paths(res, q, t)
+    assert int(count[0]) > 0 and torch.equal(count, count2) and torch.equal(edges, edges2)
+    res.close()
+    g.close()
+""")
