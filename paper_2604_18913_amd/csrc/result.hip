@@ -1899,6 +1899,15 @@ __global__ void k_fill_int(int32_t *p, long long n, int32_t value) {
 template <int W>
 constexpr long long Qp_of() { return 64 * W; }
 
+// A block of the pool may not be taken or given back inside a sequence that a stream capture records: the replays
+// would use it after the pool has handed it on.  Kernels that are better with one have a form without.
+static bool captured(hipStream_t st) {
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &s) == hipSuccess) return s != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 // The row kernels: N words of the lines (narrow form), or N = 0: whole 16-word lines.
 template <int W, int N, bool MASK, bool STATS>
 static void launch_rows(Profiler &prof, const FillArgs &a, long long n_hub_rows, long long n_other_rows,
@@ -1935,12 +1944,12 @@ static void launch_rows(Profiler &prof, const FillArgs &a, long long n_hub_rows,
     };
     if (giants > 0) {
         // Segments merge in row_pred; without it (the row kernels write the lists themselves) in a buffer of
-        // the giants' own lines.  No room for that: a block per giant row.
+        // the giants' own lines.  No room for that, or a capture: a block per giant row.
         FillArgs b = a;
         void *buf = nullptr;
         logoskg_graph *g = static_cast<logoskg_graph *>(a.host_graph);
         const bool segments = a.giant_seg_first && giants == a.n_giant_rows;
-        if (segments && !a.row_pred &&
+        if (segments && !a.row_pred && !captured(st_hub) &&
             g->pool.alloc(&buf, (size_t)giants * Qp_of<W>() * sizeof(int32_t), st_hub) == LOGOSKG_OK)
             b.row_pred = static_cast<int32_t *>(buf);
         if (segments && b.row_pred) {
@@ -1980,7 +1989,7 @@ static void launch_pred_wms(Profiler &prof, const FillArgs &a0, long long n_hub_
             const int w0 = a.q0 >> 6, w1 = (a.q1 - 1) >> 6;
             const int words = w0 == w1 ? 1 : w0 >> 1 == w1 >> 1 ? 2 : w0 >> 2 == w1 >> 2 ? 4 : 0;
             // (one stream: the row and tile kernels read the packed planes)
-            if (words && mt && a.row_pred && a.tile_ent && a.n_listed >= kPageLines && st_hub == st_tiles) {
+            if (words && mt && a.row_pred && a.tile_ent && a.n_listed >= kPageLines && st_hub == st_tiles && !captured(st_hub)) {
                 logoskg_graph *g = static_cast<logoskg_graph *>(a.host_graph);
                 const long long Epad = a.plane / 16;
                 const size_t bytes = (size_t)(a.k + 1) * Epad * words * 8;
