@@ -1057,12 +1057,16 @@ void launch_resident_hop(logoskg_graph *g, logoskg_result *r, int h, bool pull, 
     }
 }
 
+__global__ void k_clear_cursors(unsigned long long *ctr) { ctr[threadIdx.x] = 0ull; }
+
 // Push lists of level h into g->fr_tail / g->fr_seg.  ctr: two words that hold zeros (a level's own counters, once),
 // or NULL for the graph's, which are cleared first.
 logoskg_status census_lists(logoskg_graph *g, logoskg_result *r, int h, unsigned long long *ctr, hipStream_t st, int prof_kind) {
     if (!ctr) {
         ctr = g->d_ctr;
-        LKG_HIP(hipMemsetAsync(ctr, 0, 2 * sizeof(unsigned long long), st));
+        // (a kernel: a fetch that a stream capture records comes by here, and a memset node that is not run again in
+        // a later replay would let the lists grow past their ends)
+        k_clear_cursors<<<dim3(1), dim3(2), 0, st>>>(ctr);
     }
     ProfScope ps(g->prof, prof_kind, st);
     const unsigned nb = std::min<unsigned>(512u, std::max(1u, blocks_for(g->E, 1024 * kCensusEntities)));

@@ -104,3 +104,22 @@ def test_a_page_whose_words_an_eager_fetch_packs():
             assert all(np.array_equal(x, y) for x, y in zip(got, want))
     res.close()
     g.close()
+
+
+def test_levels_resolved_from_the_subject_side():
+    import kggen
+    import paper_2604_18913_amd as lkg
+    w = kggen.config2(0.01, num_queries=300)
+    want = oracle.khop(w.num_entities, w.subj, w.rel, w.obj, w.seed_off, w.seeds, w.k)
+    arena = Arena(1 << 30)
+    g = lkg.Graph(w.subj, w.rel, w.obj, w.num_entities, w.num_relations, hub_min_degree=100, dev_alloc=arena.alloc,
+                  dev_free=arena.free)
+    res = g.khop(w.seed_off, w.seeds, w.k)
+    assert any(4 * h["frontier_edges"] <= w.num_triples for h in res.hop_stats())
+    res.fetch()
+    for q0, q1 in ((0, 300), (60, 140)):
+        for got in captured_fetch(res, arena, q0, q1):
+            for x, y in zip(got, want[1:4]):
+                assert np.array_equal(x, y[want[0][q0]:want[0][q1]])
+    res.close()
+    g.close()
