@@ -54,7 +54,7 @@ k_walk_seeds(int32_t E, int W, int w, unsigned long long bit, const unsigned lon
 //
 // Rows of up to kTailMaxDegree entries: a thread per entity walks its row, four entries' loads
 // together (neighbouring rows are contiguous in OBJ, so a wavefront's loads share their lines).
-// Longer rows are left to k_walk_count_long.  One wavefront per 64 entities, row after row, took 1.0 ms
+// Longer rows have a block each.  One wavefront per 64 entities, row after row, took 1.0 ms
 // a hop on a 3.4M-triple graph whatever the level held (a 10^5-entry row is 1,500 turns of one
 // wavefront); count and page of 10^6 chains of three triples together went from 3.2 ms to 0.30 ms there.
 template <bool MASK>
@@ -78,13 +78,14 @@ __device__ __forceinline__ unsigned long long capped(unsigned long long total, u
 }
 
 template <bool MASK>
-__global__ void __launch_bounds__(256)
-k_walk_count_short(int32_t E, int W, int w, unsigned long long bit, const unsigned long long *__restrict__ level_h,
-                   const unsigned long long *__restrict__ allow, const uint32_t *__restrict__ in_off,
-                   const int32_t *__restrict__ in_sub, const uint16_t *__restrict__ in_rel,
-                   const unsigned long long *__restrict__ cnt_prev, unsigned long long *__restrict__ cnt_cur,
-                   unsigned long long *__restrict__ cum, unsigned int *overflow) {
-    const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void walk_count_short(long long e, int32_t E, int W, int w, unsigned long long bit,
+                                                 const unsigned long long *__restrict__ level_h,
+                                                 const unsigned long long *__restrict__ allow,
+                                                 const uint32_t *__restrict__ in_off, const int32_t *__restrict__ in_sub,
+                                                 const uint16_t *__restrict__ in_rel,
+                                                 const unsigned long long *__restrict__ cnt_prev,
+                                                 unsigned long long *__restrict__ cnt_cur,
+                                                 unsigned long long *__restrict__ cum, unsigned int *overflow) {
     if (e >= E || !(level_h[(size_t)e * W + w] & bit)) return;
     const uint32_t lo = in_off[e], hi = in_off[e + 1];
     if (hi - lo > (uint32_t)kTailMaxDegree) return;
@@ -107,7 +108,7 @@ k_walk_count_short(int32_t E, int W, int w, unsigned long long bit, const unsign
 
 // Entries [lo, hi) of one row by a block of NW wavefronts, U entries per lane and turn (one wavefront apart, so
 // that every load and store is contiguous): cum = running sums from the first one on; returns the total.
-template <bool MASK, int NW>
+template <bool MASK, int NW, int U>
 __device__ __forceinline__ unsigned long long walk_count_span(uint32_t lo, uint32_t hi, int W, int w, unsigned long long bit,
                                                               const unsigned long long *__restrict__ allow,
                                                               const int32_t *__restrict__ in_sub,
@@ -115,7 +116,7 @@ __device__ __forceinline__ unsigned long long walk_count_span(uint32_t lo, uint3
                                                               const unsigned long long *__restrict__ cnt_prev,
                                                               unsigned long long *__restrict__ cum,
                                                               unsigned long long (*part)[NW], uint32_t &high) {
-    constexpr int U = NW >= 16 ? 4 : 2, NT = 64 * NW;
+    constexpr int NT = 64 * NW;
     static_assert(64 * U <= kWalkSummands, "a wavefront's sum of one turn cannot wrap");
     static_assert(NW + 1 <= kWalkSummands, "nor can the turn's, while its parts are below the limit");
     const int wave = threadIdx.x >> 6;
@@ -151,27 +152,6 @@ __device__ __forceinline__ unsigned long long walk_count_span(uint32_t lo, uint3
     return running;
 }
 
-// A block of four wavefronts per longer row.
-template <bool MASK>
-__global__ void __launch_bounds__(256)
-k_walk_count_long(const int32_t *__restrict__ rows, int W, int w, unsigned long long bit,
-                  const unsigned long long *__restrict__ level_h, const unsigned long long *__restrict__ allow,
-                  const uint32_t *__restrict__ in_off, const int32_t *__restrict__ in_sub,
-                  const uint16_t *__restrict__ in_rel, const unsigned long long *__restrict__ cnt_prev,
-                  unsigned long long *__restrict__ cnt_cur, unsigned long long *__restrict__ cum,
-                  unsigned int *overflow) {
-    __shared__ unsigned long long part[2][4];
-    const int32_t v = rows[blockIdx.x];
-    if (!(level_h[(size_t)v * W + w] & bit)) return;  // block-uniform
-    uint32_t high = 0;
-    const unsigned long long total =
-        walk_count_span<MASK, 4>(in_off[v], in_off[v + 1], W, w, bit, allow, in_sub, in_rel, cnt_prev, cum, part, high);
-    if (threadIdx.x == 0) cnt_cur[v] = capped(total, high, overflow);
-}
-
-// The giant rows (the first in the list of a resident graph) by segments of kGiantSegment entries, a block of sixteen
-// wavefronts each: the segments' own running sums and totals first, then every segment adds what lies before it in its
-// row.  A block per giant row was a chain of 4,096-entry turns, 140 .. 176 us a hop on 3.4M triples; 25 us now (19 + 6).
 __device__ __forceinline__ long long giant_row_of(const uint32_t *__restrict__ seg_first, long long n, uint32_t seg) {
     long long lo = 0, hi = n;  // the last row whose first segment is <= seg
     while (hi - lo > 1) {
@@ -181,34 +161,60 @@ __device__ __forceinline__ long long giant_row_of(const uint32_t *__restrict__ s
     return lo;
 }
 
+// One launch for all rows, blocks of four wavefronts: the first n_segs take a segment of kGiantSegment entries of a
+// giant row each (the first n_giant rows of the list; the segment's own running sums, its total to seg_total and to the
+// row's count), the next n_long a longer row, the others 256 entities, a thread for each short row.  The giants' running
+// sums are joined over their segments once, behind the last hop (k_walk_join_giant): the hops need the counts only.
+// A block per giant row was a chain of 4,096-entry turns, 140 .. 176 us a hop on 3.4M triples.  Segments, their join,
+// longer and short rows in a launch each were 4 launches a hop: the whole call of three hops there 583 us, 495 us now,
+// and two counts (2 and 3 hops) of a query that reaches nothing 258 us, 205 us now.
 template <bool MASK>
-__global__ void __launch_bounds__(1024)
-k_walk_count_giant(const int32_t *__restrict__ rows, const uint32_t *__restrict__ seg_first, long long n_rows, int W, int w,
-                   unsigned long long bit, const unsigned long long *__restrict__ level_h,
-                   const unsigned long long *__restrict__ allow, const uint32_t *__restrict__ in_off,
-                   const int32_t *__restrict__ in_sub, const uint16_t *__restrict__ in_rel,
-                   const unsigned long long *__restrict__ cnt_prev, unsigned long long *__restrict__ cum,
-                   unsigned long long *__restrict__ seg_total, unsigned int *overflow) {
-    __shared__ unsigned long long part[2][16];
-    const long long i = giant_row_of(seg_first, n_rows, blockIdx.x);
+__global__ void __launch_bounds__(256)
+k_walk_count(const int32_t *__restrict__ rows, const uint32_t *__restrict__ seg_first, unsigned n_giant, unsigned n_segs,
+             unsigned n_long, int32_t E, int W, int w, unsigned long long bit,
+             const unsigned long long *__restrict__ level_h, const unsigned long long *__restrict__ allow,
+             const uint32_t *__restrict__ in_off, const int32_t *__restrict__ in_sub, const uint16_t *__restrict__ in_rel,
+             const unsigned long long *__restrict__ cnt_prev, unsigned long long *__restrict__ cnt_cur,
+             unsigned long long *__restrict__ cum, unsigned long long *__restrict__ seg_total, unsigned int *overflow) {
+    __shared__ unsigned long long part[2][4];
+    const unsigned b = blockIdx.x;
+    if (b >= n_segs + n_long) {
+        walk_count_short<MASK>((long long)(b - n_segs - n_long) * 256 + threadIdx.x, E, W, w, bit, level_h, allow, in_off,
+                               in_sub, in_rel, cnt_prev, cnt_cur, cum, overflow);
+        return;
+    }
+    const long long i = b < n_segs ? giant_row_of(seg_first, n_giant, b) : (long long)n_giant + (b - n_segs);
     const int32_t v = rows[i];
     if (!(level_h[(size_t)v * W + w] & bit)) return;  // block-uniform
-    const uint32_t lo = in_off[v] + (blockIdx.x - seg_first[i]) * (uint32_t)kGiantSegment;
-    const uint32_t hi = min(lo + (uint32_t)kGiantSegment, in_off[v + 1]);
-    uint32_t high = 0;
-    const unsigned long long total =
-        walk_count_span<MASK, 16>(lo, hi, W, w, bit, allow, in_sub, in_rel, cnt_prev, cum, part, high);
-    if (threadIdx.x == 0) seg_total[blockIdx.x] = capped(total, high, overflow);
+    uint32_t lo = in_off[v], hi = in_off[v + 1], high = 0;
+    if (b < n_segs) {
+        lo += (b - seg_first[i]) * (uint32_t)kGiantSegment;
+        hi = min(lo + (uint32_t)kGiantSegment, hi);
+        const unsigned long long total =
+            walk_count_span<MASK, 4, 4>(lo, hi, W, w, bit, allow, in_sub, in_rel, cnt_prev, cum, part, high);
+        if (threadIdx.x == 0) {
+            const unsigned long long x = capped(total, high, overflow);
+            seg_total[b] = x;
+            atomicAdd(&cnt_cur[v], x);  // (whether the row's sum passed the limit shows in the join)
+        }
+    } else {
+        const unsigned long long total =
+            walk_count_span<MASK, 4, 2>(lo, hi, W, w, bit, allow, in_sub, in_rel, cnt_prev, cum, part, high);
+        if (threadIdx.x == 0) cnt_cur[v] = capped(total, high, overflow);
+    }
 }
 
+// Every segment of a giant row adds what lies before it in its row; blockIdx.y = hop - 1.
 __global__ void __launch_bounds__(1024)
 k_walk_join_giant(const int32_t *__restrict__ rows, const uint32_t *__restrict__ seg_first, long long n_rows, int W, int w,
-                  unsigned long long bit, const unsigned long long *__restrict__ level_h,
-                  const uint32_t *__restrict__ in_off, const unsigned long long *__restrict__ seg_total,
-                  unsigned long long *__restrict__ cnt_cur, unsigned long long *__restrict__ cum, unsigned int *overflow) {
+                  unsigned long long bit, const unsigned long long *__restrict__ levels, size_t plane,
+                  const uint32_t *__restrict__ in_off, const unsigned long long *__restrict__ seg_totals, long long T,
+                  unsigned long long *__restrict__ cums, unsigned int *overflow) {
     const long long i = giant_row_of(seg_first, n_rows, blockIdx.x);
     const int32_t v = rows[i];
-    if (!(level_h[(size_t)v * W + w] & bit)) return;  // block-uniform
+    if (!(levels[(blockIdx.y + 1) * plane + (size_t)v * W + w] & bit)) return;  // block-uniform
+    const unsigned long long *seg_total = seg_totals + (size_t)blockIdx.y * gridDim.x;
+    unsigned long long *cum = cums + (size_t)blockIdx.y * T;
     unsigned long long before = 0;
     uint32_t high = 0;
     for (uint32_t x = seg_first[i]; x < blockIdx.x; ++x) {
@@ -219,10 +225,7 @@ k_walk_join_giant(const int32_t *__restrict__ rows, const uint32_t *__restrict__
     const uint32_t hi = min(lo + (uint32_t)kGiantSegment, in_off[v + 1]);
     if (before)
         for (uint32_t j = lo + threadIdx.x; j < hi; j += 1024) cum[j] += before;
-    if (threadIdx.x == 0 && blockIdx.x + 1 == seg_first[i + 1]) {
-        const unsigned long long total = before + seg_total[blockIdx.x];
-        cnt_cur[v] = capped(total, high | upper_half(total), overflow);
-    }
+    if (threadIdx.x == 0) (void)capped(before, high | upper_half(before + seg_total[blockIdx.x]), overflow);
 }
 
 // pref[0] = 0 and the running sum over the entities must not have wrapped
@@ -282,19 +285,12 @@ static void launch_walk_hop(logoskg_graph *g, int W, int w, unsigned long long b
                             const unsigned long long *prev, unsigned long long *cur, unsigned long long *cum,
                             unsigned int *overflow, unsigned long long *seg_total, hipStream_t st) {
     const RowClasses &rc = g->in_rows;
-    const int64_t giants = seg_total ? rc.n_giant : 0;
-    if (giants > 0) {
-        const dim3 grid((unsigned)rc.n_giant_segs), block(1024);
-        k_walk_count_giant<MASK><<<grid, block, 0, st>>>(rc.longrows, rc.giant_seg_first, giants, W, w, bit, level_h, allow,
-                                                         g->in_off, in_sub, in_rel, prev, cum, seg_total, overflow);
-        k_walk_join_giant<<<grid, block, 0, st>>>(rc.longrows, rc.giant_seg_first, giants, W, w, bit, level_h, g->in_off,
-                                                  seg_total, cur, cum, overflow);
-    }
-    if (rc.n_long > giants)
-        k_walk_count_long<MASK><<<dim3((unsigned)(rc.n_long - giants)), dim3(256), 0, st>>>(
-            rc.longrows + giants, W, w, bit, level_h, allow, g->in_off, in_sub, in_rel, prev, cur, cum, overflow);
-    k_walk_count_short<MASK><<<dim3((unsigned)((g->E + 255) / 256)), dim3(256), 0, st>>>(
-        g->E, W, w, bit, level_h, allow, g->in_off, in_sub, in_rel, prev, cur, cum, overflow);
+    const unsigned giants = seg_total ? (unsigned)rc.n_giant : 0u, segs = giants ? (unsigned)rc.n_giant_segs : 0u;
+    // (at most T / 8192 + n_giant segments, T / 33 rows and E / 256 blocks: below the grid's limit)
+    const unsigned n_long = (unsigned)rc.n_long - giants;
+    k_walk_count<MASK><<<dim3(segs + n_long + (unsigned)((g->E + 255) / 256)), dim3(256), 0, st>>>(
+        rc.longrows, rc.giant_seg_first, giants, segs, n_long, g->E, W, w, bit, level_h, allow, g->in_off, in_sub, in_rel,
+        prev, cur, cum, seg_total, overflow);
 }
 
 static logoskg_status prepare_walk_tables(logoskg_result *r, int q, int d, hipStream_t st) {
@@ -311,10 +307,10 @@ static logoskg_status prepare_walk_tables(logoskg_result *r, int q, int d, hipSt
         set_error("the object-sorted triples of the sharded graph are not available");
         return LOGOSKG_EINTERNAL;
     }
-    // cnt: d + 1 levels, then one word of flags and the giant rows' segment totals; cum: d rows of T; pref: E + 1
+    // cnt: d + 1 levels, then one word of flags and the giant rows' segment totals of d hops; cum: d rows of T; pref: E + 1
     // (a sharded graph has no list of all its giant rows: they are long rows like the others)
     const size_t segs = g->num_shards > 1 ? 0 : (size_t)g->in_rows.n_giant_segs;
-    LKG_TRY(g->pool.alloc((void **)&r->walk_cnt, ((size_t)(d + 1) * Epad + 8 + segs) * 8, st));
+    LKG_TRY(g->pool.alloc((void **)&r->walk_cnt, ((size_t)(d + 1) * Epad + 8 + (size_t)d * segs) * 8, st));
     LKG_TRY(g->pool.alloc((void **)&r->walk_cum, (size_t)std::max(d, 1) * T * 8, st));
     LKG_TRY(g->pool.alloc((void **)&r->walk_pref, (Epad + 8) * 8, st));
     unsigned int *overflow = (unsigned int *)(r->walk_cnt + (size_t)(d + 1) * Epad);
@@ -328,9 +324,14 @@ static logoskg_status prepare_walk_tables(logoskg_result *r, int q, int d, hipSt
             const unsigned long long *lvl = r->levels + plane * (size_t)h;
             unsigned long long *prev = r->walk_cnt + (size_t)(h - 1) * Epad, *cur = r->walk_cnt + (size_t)h * Epad;
             unsigned long long *cum = r->walk_cum + (size_t)(h - 1) * T;
-            if (r->has_mask) launch_walk_hop<true>(g, W, w, bit, lvl, r->allow, in_sub, in_rel, prev, cur, cum, overflow, seg_total, st);
-            else launch_walk_hop<false>(g, W, w, bit, lvl, nullptr, in_sub, in_rel, prev, cur, cum, overflow, seg_total, st);
+            unsigned long long *totals = seg_total ? seg_total + (size_t)(h - 1) * segs : nullptr;
+            if (r->has_mask) launch_walk_hop<true>(g, W, w, bit, lvl, r->allow, in_sub, in_rel, prev, cur, cum, overflow, totals, st);
+            else launch_walk_hop<false>(g, W, w, bit, lvl, nullptr, in_sub, in_rel, prev, cur, cum, overflow, totals, st);
         }
+        if (seg_total && d > 0)
+            k_walk_join_giant<<<dim3((unsigned)segs, (unsigned)d), dim3(1024), 0, st>>>(
+                g->in_rows.longrows, g->in_rows.giant_seg_first, g->in_rows.n_giant, W, w, bit, r->levels, plane, g->in_off,
+                seg_total, (long long)T, r->walk_cum, overflow);
     }
     LKG_HIP(hipGetLastError());
     // pref[e + 1] = chains that end in an entity <= e
