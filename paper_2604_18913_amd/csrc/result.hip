@@ -54,7 +54,7 @@ __device__ __forceinline__ unsigned long long stage_word(unsigned long long (*st
     // wavefront's lanes cover neighbouring 8- or 32-byte lines), without LDS and without a barrier (a caller
     // whose wavefronts share something needs one of its own), so a caller's loads over several tiles are in
     // flight together; through LDS with two barriers each, they were a chain of 64 dependent rounds in a block
-    // of the list kernel (31 us for the lists of one query on 407,000 entities, 27 us now).  A 16-word line is 128 bytes: loaded with W
+    // of the list kernel (31 us for the lists of one query on 407,000 entities, 27 us without).  A 16-word line is 128 bytes: loaded with W
     // consecutive lanes per line and handed over through LDS.
     if constexpr (W <= 4) {
         const long long e = tile_entity(tile_ent, tile, lane(), E);
@@ -290,13 +290,13 @@ __device__ __forceinline__ long long super_start(const FillArgs &a, long long st
 }
 
 // ---------------------------------------------------------------- entity / hop lists
-// One block per super tile (1024 entities), one wavefront per word.  The wave
-// keeps its word of all 16 tiles in registers (visited and the bit-sliced hop
+// One block per super tile (1024 entities) or part of one, one wavefront per word.  The wave
+// keeps its word of all the block's tiles in registers (visited and the bit-sliced hop
 // number), and for one query at a time compacts the reached entities into LDS,
 // then streams them out with full-width stores.
-// NB = words of the bit-sliced hop number (0: entity ids only); TILES = tiles per block: a
-// whole super tile, or half of one where the registers of a whole one would not leave room for
-// two blocks per CU.
+// NB = words of the bit-sliced hop number (0: entity ids only); TILES = tiles per block: half a
+// super tile on 16-word planes, where the registers of a whole one would not leave room for
+// two blocks per CU; a whole or a quarter on narrower ones (launch_lists_w).
 template <int W, int NB, int TILES>
 __global__ void __launch_bounds__(64 * W) k_lists(FillArgs a) {
     constexpr int Qp = 64 * W, NBX = NB > 0 ? NB : 1;
@@ -1806,9 +1806,8 @@ logoskg_status prepare_row_pred(logoskg_graph *g, hipStream_t st) {
     return LOGOSKG_OK;
 }
 
-template <int W>
-static void launch_lists_w(Profiler &prof, const FillArgs &a, hipStream_t st) {
-    constexpr int TILES = W == 16 ? kSuperTiles / 2 : kSuperTiles;
+template <int W, int TILES>
+static void launch_lists_t(Profiler &prof, const FillArgs &a, hipStream_t st) {
     const long long nblocks = (a.ntiles + TILES - 1) / TILES;
     ProfScope ps(prof, KK_LISTS, st);
     int nb = 1;
@@ -1818,6 +1817,22 @@ static void launch_lists_w(Profiler &prof, const FillArgs &a, hipStream_t st) {
     else if (nb <= 2) k_lists<W, 2, TILES><<<grid, block, 0, st>>>(a);
     else if (nb <= 4) k_lists<W, 4, TILES><<<grid, block, 0, st>>>(a);
     else k_lists<W, 8, TILES><<<grid, block, 0, st>>>(a);
+}
+
+// Tiles per block.  A wavefront takes the queries of its word one after the other through all tiles of the block, so
+// on narrow planes, where a block has few wavefronts, a whole super tile is a long chain on a GPU that is nearly
+// empty (64 queries, 108,000 listed entities, no hops: 16 tiles 148 us, 8: 89, 4: 59, 2: 44).  One-word planes take
+// four (128M entries on 2M listed entities: 175 us with 16, 172 with 4, 187 with 2).  On four-word planes the shorter
+// runs of a small block cost 10 % where the GPU is full (200 queries, 2M listed: 439 us with 16, 482 with 4), so
+// they take four tiles only below 2 blocks of 16 per CU (108,000 listed: 94 us with 16, 46 with 4; 870,000 listed, 850
+// blocks of 16: 159 and 154 without hops, 177 and 199 for a level).
+constexpr long long kListsFullBlocks = 512;
+
+template <int W>
+static void launch_lists_w(Profiler &prof, const FillArgs &a, hipStream_t st) {
+    if constexpr (W == 16) launch_lists_t<W, kSuperTiles / 2>(prof, a, st);
+    else if (W == 1 || a.ntiles < kListsFullBlocks * kSuperTiles) launch_lists_t<W, 4>(prof, a, st);
+    else launch_lists_t<W, kSuperTiles>(prof, a, st);
 }
 
 // True when the 16-word tile kernel can serve this launch (it then can also write the entity and

@@ -105,3 +105,24 @@ def test_levels_and_lists_without_predecessors_of_four_word_planes(num_queries):
             assert np.array_equal(e.cpu().numpy(), ent[a:b][hop[a:b] == level])
     res.close()
     g.close()
+
+
+@pytest.mark.parametrize("listed", [524_288 - 64, 524_288 - 63, 524_288, 530_001])
+def test_lists_of_four_word_planes_at_the_change_of_the_block(listed):
+    # one question seeds `listed` entities, none of which has a triple: 8,191 and 8,192 tiles and more
+    m = lkg()
+    E, Q = 600_000, 100
+    rng = np.random.default_rng(listed)
+    ids = np.sort(rng.permutation(E - 10)[:listed]).astype(np.int32)
+    lists = [ids[q::50] for q in range(Q - 1)] + [ids]
+    off = np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int64)
+    g = m.Graph([E - 1], [0], [E - 2], E, 1)
+    res = g.khop(off, np.concatenate(lists).astype(np.int32), 1)
+    for want_hop in (False, True):
+        ent, hop, _ = res.fetch(want_hop=want_hop, want_pred=False)
+        assert np.array_equal(ent.cpu().numpy(), np.concatenate(lists))
+        assert hop is None or int(hop.max()) == 0
+    _, ent = res.level(0, 60, Q)
+    assert np.array_equal(ent.cpu().numpy(), np.concatenate(lists[60:]))
+    res.close()
+    g.close()

@@ -51,7 +51,7 @@ def device_helpers():
 
 
 LISTS_MAIN = """
-template <int W, int NB> int check(const std::vector<int> &waves, bool listed) {
+template <int W, int NB, int TILES> int check(const std::vector<int> &waves, bool listed) {
     constexpr int Qp = 64 * W;
     const int E = 2500, k = 3, Q = W == 1 ? 50 : 230, Epad = (E + 63) / 64 * 64;
     unsigned long long rng = 7 + W;
@@ -96,19 +96,19 @@ template <int W, int NB> int check(const std::vector<int> &waves, bool listed) {
     a.plane = (long long)Epad * W; a.visited = visited.data(); a.levels = levels.data();
     a.tile_base = tile_base.data(); a.super_base = super_base.data(); a.mega_base = mega_base.data();
     a.reached_off = off.data(); a.entity = entity.data(); a.hop = hop.data();
-    run_grid((unsigned)supers, 64 * W, waves, [&] { k_lists<W, NB, 16>(a); });
+    run_grid((unsigned)((tiles + TILES - 1) / TILES), 64 * W, waves, [&] { k_lists<W, NB, TILES>(a); });
     int bad = 0;
     for (size_t i = 0; i < want_ent.size(); ++i) bad += entity[i] != want_ent[i] || (NB && hop[i] != want_hop[i]);
-    printf("%d words, %d hop bits, list %d: %d of %zu entries wrong\\n", W, NB, listed, bad, want_ent.size());
+    printf("%d words, %d hop bits, %d tiles, list %d: %d of %zu entries wrong\\n", W, NB, TILES, listed, bad, want_ent.size());
     return bad;
 }
 
 int main() {
     int bad = 0;
     for (bool listed : {false, true}) {
-        bad += check<1, 0>({0}, listed) + check<1, 2>({0}, listed);
+        bad += check<1, 0, 4>({0}, listed) + check<1, 2, 4>({0}, listed);
         for (const std::vector<int> &waves : {std::vector<int>{0, 1, 2, 3}, std::vector<int>{3, 2, 1, 0}})
-            bad += check<4, 0>(waves, listed) + check<4, 2>(waves, listed);
+            bad += check<4, 0, 16>(waves, listed) + check<4, 2, 16>(waves, listed) + check<4, 2, 4>(waves, listed);
     }
     return bad != 0;
 }
