@@ -41,11 +41,25 @@ struct PathArgs {
     int32_t *path_count, *path_edges;
 };
 
-constexpr int64_t kPathWidePairs = 1024;    // up to here 16 wavefronts per pair,
-constexpr int64_t kPathNarrowPairs = 65536; // up to here 4, then one
+// Wavefronts per pair: 16 up to kPathWidePairs pairs, 4 up to kPathNarrowPairs, then one.  What counts are the scans of
+// long rows: few pairs need many wavefronts each to fill the GPU, many pairs fill it by themselves.  us for 16 paths
+// each on a 30M-triple graph (k = 3 with whitelists; without):
+//    pairs     16 wavefronts       4               1
+//       64       749     250      982     172     3,161     449
+//      256     1,777     614    2,262     753     6,769   2,344
+//    1,024     2,600   1,973    2,579   2,253     8,003   6,880
+//    4,096     5,216   3,504    3,301   2,395     9,810   6,671
+//   65,536    69,857  38,151   18,755   9,009    21,416  14,278
+//  131,072   138,171  74,066   37,363  15,773    40,212  19,234
+//  262,144   276,567 147,159   70,130  29,416    67,812  29,837
+// With k = 2 the rows of a pair are fewer: 4 are better than 16 from 512 pairs on (without whitelists from 64 on: 46
+// against 117 us), one than 4 from 131,072 on.
+constexpr int64_t kPathWidePairs = 1024;
+constexpr int64_t kPathNarrowPairs = 65536;
 constexpr int kPathSeeds = 64;    // queries with more seeds than this keep to the object rows at level 1
 constexpr int kPathRelations = 2048; // up to so many relations the query's whitelist is held in LDS
 constexpr int kPathMatches = 256; // triples from the seeds into one entity that are sorted in LDS
+constexpr uint32_t kPathShortRow = 128;  // what is left of a row up to this length: one wavefront, two entries per lane
 
 // NW wavefronts (one block) per (query, target) pair.  The depth-first state - per level the vertex,
 // the next row position and the chosen edge - is block-uniform and lives in LDS (k <= 254).
@@ -56,6 +70,11 @@ constexpr int kPathMatches = 256; // triples from the seeds into one entity that
 // next, dearer gather), and the ballots of all wavefronts give the admissible entries in ascending
 // position = ascending edge id.  At level 1 every admissible entry ends a path and the entries' own
 // lanes write them; above, the first one is descended into.
+//
+// Where at most kPathShortRow entries of a row are left, the block's barriers and its steps would be all that
+// it costs: one wavefront goes on alone then, two entries per lane, until the next long row.  (16 paths of up to 40
+// triples through rows of two entries: 228 us with a wavefront per pair, 1,810 us with sixteen that take every
+// row together, 230 us now.)
 //
 // The last triple on the way down leaves a seed, and a query has few seeds: when their out-rows
 // together are shorter than the vertex's object row, the block walks those instead and sorts the
@@ -76,7 +95,7 @@ __global__ void __launch_bounds__(64 * NW) k_paths(PathArgs a) {
     __shared__ int32_t s_id[kPathSeeds];
     __shared__ int32_t match[kPathMatches];
     __shared__ unsigned long long s_allow[kPathRelations / 64];
-    __shared__ int n_match;
+    __shared__ int n_match, s_l, s_found;
     const long long i = a.first_pair + blockIdx.x;
     const int t = threadIdx.x, wave = t >> 6, k = a.k, W = a.W, max_paths = a.max_paths;
     int32_t *out = a.path_edges + (size_t)i * max_paths * k;
@@ -92,9 +111,12 @@ __global__ void __launch_bounds__(64 * NW) k_paths(PathArgs a) {
     if (a.length) {  // walks of exactly that many triples: the target has to sit in that level
         const int want = a.length[i];
         if (want >= 0 && want <= k && (a.levels[(size_t)want * a.plane + (size_t)v * W + w] & bit)) d = want;
-    } else {         // shortest paths: the first level that holds the target
-        for (int h = 0; h <= k; ++h)
-            if (a.levels[(size_t)h * a.plane + (size_t)v * W + w] & bit) { d = h; break; }
+    } else {         // shortest paths: the first level that holds the target, 64 levels at a time
+        for (int h0 = 0; h0 <= k && d < 0; h0 += 64) {
+            const int h = h0 + lane();
+            const unsigned long long m = __ballot(h <= k && (a.levels[(size_t)min(h, k) * a.plane + (size_t)v * W + w] & bit));
+            if (m) d = h0 + __builtin_ctzll(m);
+        }
     }
     if (d <= 0) {  // not reached: no path; a seed: one empty path
         if (t == 0) a.path_count[i] = d == 0 ? 1 : 0;
@@ -115,32 +137,8 @@ __global__ void __launch_bounds__(64 * NW) k_paths(PathArgs a) {
     auto allowed = [&](int r) -> bool {
         return lds_allow ? (s_allow[r >> 6] >> (r & 63)) & 1ull : (a.allow[(size_t)r * W + w] & bit) != 0ull;
     };
-    // the seeds' out-rows (a repeated seed counts once); n_seeds = 0: not usable for this query
-    int n_seeds = 0;
+    int found = 0, l = d, buf = 0, n_seeds = -1;
     uint32_t seed_edges = 0;
-    if (a.out_eid) {  // block-uniform
-        const long long b0 = a.seed_off[q], n = a.seed_off[q + 1] - b0;
-        if (n > 0 && n <= kPathSeeds) {
-            n_seeds = (int)n;
-            if (t < n_seeds) s_id[t] = a.seeds[b0 + t];
-            __syncthreads();
-            if (t < n_seeds) {
-                const int32_t s = s_id[t];
-                bool again = false;
-                for (int x = 0; x < t; ++x) again |= s_id[x] == s;
-                s_lo[t] = a.out_off[s];
-                s_end[t] = again ? 0u : a.out_off[s + 1] - s_lo[t];
-            }
-            __syncthreads();
-            if (t == 0) {
-                uint32_t sum = 0;
-                for (int x = 0; x < n_seeds; ++x) s_end[x] = sum += s_end[x];  // < 2^31: distinct rows of one graph
-            }
-            __syncthreads();
-            seed_edges = s_end[n_seeds - 1];
-        }
-    }
-    int found = 0, l = d, buf = 0;
     if (t == 0) {
         sv[d] = v;
         sp[d] = a.in_off[v];
@@ -152,11 +150,110 @@ __global__ void __launch_bounds__(64 * NW) k_paths(PathArgs a) {
         row[0] = eid;
         for (int x = 2; x <= d; ++x) row[x - 1] = se[x];
     };
-    while (l <= d && found < max_paths) {
+    // The search from entry j of vertex x's row on by one wavefront alone, until it is over or the next row is a long one:
+    // subject, relation and triple index of two entries per lane are requested together, then the subjects' level words.
+    // The stacks hold every entry but the current one (x, j) while this runs.
+    auto short_rows = [&](int x, uint32_t j, uint32_t hi, int lev, int n) {
+        while (true) {
+            if (hi - j > kPathShortRow) break;
+            const unsigned long long *lv = a.levels + (size_t)(lev - 1) * a.plane;
+            const uint32_t at0 = j + (uint32_t)lane(), at1 = at0 + 64u;
+            const bool in0 = at0 < hi, in1 = at1 < hi;
+            const int32_t s0 = in0 ? a.in_sub[at0] : 0, s1 = in1 ? a.in_sub[at1] : 0;
+            const int32_t e0 = in0 ? a.in_eid[at0] : 0, e1 = in1 ? a.in_eid[at1] : 0;
+            int r0 = 0, r1 = 0;
+            if (a.allow) {
+                r0 = in0 ? a.in_rel[at0] : 0;
+                r1 = in1 ? a.in_rel[at1] : 0;
+            }
+            const unsigned long long w0 = in0 ? lv[(size_t)s0 * W + w] : 0ull, w1 = in1 ? lv[(size_t)s1 * W + w] : 0ull;
+            bool ok0 = (w0 & bit) != 0ull, ok1 = (w1 & bit) != 0ull;
+            if (a.allow) {
+                ok0 &= allowed(r0);
+                ok1 &= allowed(r1);
+            }
+            const unsigned long long m0 = __ballot(ok0), m1 = __ballot(ok1);
+            if (lev == 1) {  // every admissible entry ends a path
+                if (d > 8) {  // long paths: one after the other, their entries by all lanes
+                    for (int half = 0, at = n; half < 2; ++half)
+                        for (unsigned long long m = half ? m1 : m0; m && at < max_paths; m &= m - 1, ++at) {
+                            const int32_t eid = __shfl(half ? e1 : e0, __builtin_ctzll(m));
+                            int32_t *row = out + (size_t)at * k;
+                            for (int x = lane(); x < d; x += 64) row[x] = x ? se[x + 1] : eid;
+                        }
+                } else {
+                    const unsigned long long below = (1ull << lane()) - 1ull;
+                    const int p0 = n + __popcll(m0 & below), p1 = n + __popcll(m0) + __popcll(m1 & below);
+                    if (ok0 && p0 < max_paths) write_path(p0, e0);
+                    if (ok1 && p1 < max_paths) write_path(p1, e1);
+                }
+                n = min(max_paths, n + __popcll(m0) + __popcll(m1));
+            } else if (m0 | m1) {  // the first one is descended into
+                const int f = m0 ? __builtin_ctzll(m0) : __builtin_ctzll(m1);
+                const int32_t sf = __shfl(m0 ? s0 : s1, f), ef = __shfl(m0 ? e0 : e1, f);
+                se[lev] = ef;  // (all lanes write the same)
+                sv[lev] = x;
+                sp[lev] = j + (m0 ? 0u : 64u) + (uint32_t)f + 1u;
+                --lev;
+                x = sf;
+                j = a.in_off[sf];
+                hi = a.in_off[sf + 1];
+                continue;
+            }
+            // this vertex's row is exhausted: back to the vertex after it
+            ++lev;
+            if (lev > d || n >= max_paths) break;
+            x = sv[lev];
+            j = sp[lev];
+            hi = a.in_off[x + 1];
+        }
+        if (lev <= d) {
+            sv[lev] = x;
+            sp[lev] = j;
+        }
+        s_l = lev;
+        s_found = n;
+    };
+    while (l <= d && found < max_paths) {  // (all wavefronts have the same l and found)
         const int x = sv[l];
         uint32_t j = sp[l];
         const uint32_t hi = a.in_off[x + 1];
+        if (hi - j <= kPathShortRow) {
+            __syncthreads();  // (the last reads of the stacks)
+            if (wave == 0) short_rows(x, j, hi, l, found);
+            __syncthreads();
+            l = s_l;
+            found = s_found;
+            continue;
+        }
         bool descended = false;
+        if (l == 1 && n_seeds < 0) {
+            // the seeds' out-rows (a repeated seed counts once), looked at when the first long row asks for them;
+            // n_seeds = 0: not usable for this query
+            n_seeds = 0;
+            if (a.out_eid) {  // block-uniform
+                const long long b0 = a.seed_off[q], n = a.seed_off[q + 1] - b0;
+                if (n > 0 && n <= kPathSeeds) {
+                    n_seeds = (int)n;
+                    if (t < n_seeds) s_id[t] = a.seeds[b0 + t];
+                    __syncthreads();
+                    if (t < n_seeds) {
+                        const int32_t s = s_id[t];
+                        bool again = false;
+                        for (int x = 0; x < t; ++x) again |= s_id[x] == s;
+                        s_lo[t] = a.out_off[s];
+                        s_end[t] = again ? 0u : a.out_off[s + 1] - s_lo[t];
+                    }
+                    __syncthreads();
+                    if (t == 0) {
+                        uint32_t sum = 0;
+                        for (int x = 0; x < n_seeds; ++x) s_end[x] = sum += s_end[x];  // < 2^31: distinct rows of one graph
+                    }
+                    __syncthreads();
+                    seed_edges = s_end[n_seeds - 1];
+                }
+            }
+        }
         if (l == 1 && n_seeds > 0 && seed_edges < hi - j) {
             __syncthreads();  // (the last reads of n_match and match)
             if (t == 0) n_match = 0;
@@ -294,9 +391,6 @@ static logoskg_status launch_paths(logoskg_graph *g, const logoskg_result *r, co
     a.query_idx = query_idx; a.target = target; a.length = length;
     a.max_paths = max_paths; a.path_count = path_count; a.path_edges = path_edges;
     ProfScope ps(g->prof, KK_PATHS, st);
-    // Wavefronts per pair.  The GPU holds 8,192 wavefronts: few pairs get many each (a hub row is then
-    // scanned by all of them), many pairs fill it with one each and short rows waste nothing.  (4,096
-    // pairs: 0.65 ms with four each, 0.96 ms with sixteen, both with the whitelists gathered.)
     // (a launch takes fewer than 2^32 threads)
     for (int64_t first = 0; first < n_pairs; first += 1ll << 25) {
         const dim3 grid((unsigned)std::min<int64_t>(n_pairs - first, 1ll << 25));

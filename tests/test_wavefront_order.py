@@ -189,3 +189,145 @@ def test_a_small_search_at_the_limit_of_its_list(tmp_path):
         device_helpers(),
         between(small, "constexpr int kSmallThreads", "// One block per fetched query"),
         SMALL_MAIN]))
+
+
+PATHS_MAIN = """
+struct Graph {
+    int E, k, R;
+    std::vector<uint32_t> in_off, out_off;
+    std::vector<int32_t> in_sub, in_eid, out_obj, out_eid, seeds;
+    std::vector<uint16_t> in_rel, out_rel;
+    std::vector<std::vector<int>> level;  // [k + 1][E] of the one query
+    std::vector<bool> keep;
+    // every shortest path, ordered by the triples read from the target
+    void search(int v, int h, std::vector<int> &path, std::vector<std::vector<int>> &all, size_t most) const {
+        if (all.size() >= most) return;
+        if (h == 0) {
+            all.push_back(std::vector<int>(path.rbegin(), path.rend()));
+            return;
+        }
+        for (uint32_t j = in_off[v]; j < in_off[v + 1]; ++j)
+            if (keep[in_rel[j]] && level[h - 1][in_sub[j]]) {
+                path.push_back(in_eid[j]);
+                search(in_sub[j], h - 1, path, all, most);
+                path.pop_back();
+            }
+    }
+};
+
+// k > 8: a band of entities, and the levels of the walks of exactly h triples
+static Graph make(unsigned seed, bool masked, int k) {
+    unsigned long long rng = seed;
+    auto next = [&]() { rng = rng * 6364136223846793005ull + 1442695040888963407ull; return (unsigned)(rng >> 33); };
+    Graph g;
+    g.E = 900;
+    g.k = k;
+    g.R = 5;
+    std::vector<std::array<int, 3>> t;
+    const int rows[] = {1, 127, 128, 129, 130, 300, 1025, 2500};  // objects 0 .. 7, and short rows behind them
+    for (int o = 0; o < g.E; ++o)
+        for (int i = o < 8 ? rows[o] : (int)(next() % 6); i > 0; --i)
+            t.push_back({(int)(k > 8 && o >= 8 ? (o + g.E - 1 - next() % 3) % g.E : next() % g.E), (int)(next() % g.R), o});
+    for (size_t i = t.size(); i > 1; --i) std::swap(t[i - 1], t[next() % i]);
+    const size_t T = t.size();
+    auto csr = [&](int key, std::vector<uint32_t> &off, std::vector<int32_t> &other, std::vector<uint16_t> &rel, std::vector<int32_t> &eid) {
+        off.assign(g.E + 1, 0);
+        other.resize(T); rel.resize(T); eid.resize(T);
+        for (auto &x : t) off[x[key] + 1]++;
+        for (int e = 0; e < g.E; ++e) off[e + 1] += off[e];
+        auto cur = off;
+        for (size_t i = 0; i < T; ++i) {
+            const uint32_t p = cur[t[i][key]]++;
+            other[p] = t[i][2 - key]; rel[p] = (uint16_t)t[i][1]; eid[p] = (int32_t)i;
+        }
+    };
+    csr(2, g.in_off, g.in_sub, g.in_rel, g.in_eid);
+    csr(0, g.out_off, g.out_obj, g.out_rel, g.out_eid);
+    for (int r = 0; r < g.R; ++r) g.keep.push_back(!masked || r % 2 == 0);
+    g.seeds = {(int)(next() % g.E), 9, 9, 700};
+    g.level.assign(g.k + 1, std::vector<int>(g.E));
+    std::vector<int> seen(g.E);
+    for (int s : g.seeds) g.level[0][s] = seen[s] = 1;
+    for (int h = 1; h <= g.k; ++h) {
+        for (auto &x : t)
+            if (g.level[h - 1][x[0]] && g.keep[x[1]] && (k > 8 || !seen[x[2]])) g.level[h][x[2]] = 1;
+        for (int e = 0; e < g.E; ++e) seen[e] |= g.level[h][e];
+    }
+    return g;
+}
+
+template <int NW> int check(unsigned seed, bool masked, bool seeds_side, int max_paths, const std::vector<int> &waves, int k = 5) {
+    const Graph g = make(seed, masked, k);
+    const int q = 3, Epad = (g.E + 63) / 64 * 64, actw = Epad / 32;
+    std::vector<unsigned long long> levels((size_t)(g.k + 1) * Epad), allow(g.R);
+    std::vector<uint32_t> act((size_t)(g.k + 1) * actw);
+    for (int h = 0; h <= g.k; ++h)
+        for (int e = 0; e < g.E; ++e)
+            if (g.level[h][e]) {
+                levels[(size_t)h * Epad + e] = 1ull << q;
+                act[(size_t)h * actw + e / 32] |= 1u << (e % 32);
+            }
+    for (int r = 0; r < g.R; ++r) allow[r] = g.keep[r] ? 1ull << q : 0;
+    const long long n = (long long)g.seeds.size(), seed_off[] = {0, 0, 0, 0, n};
+    std::vector<int32_t> query, target, length;
+    for (int e = 0; e < g.E; e += e < 12 ? 1 : 19) {
+        query.push_back(q);
+        target.push_back(e);
+        length.push_back(e % (g.k + 1));
+    }
+    const int pairs = (int)target.size();
+    std::vector<int32_t> count(pairs, -7), edges((size_t)pairs * max_paths * g.k, -7);
+    PathArgs a;
+    memset((void *)&a, 0, sizeof(a));
+    a.Q = 4; a.k = g.k; a.W = 1; a.E = g.E; a.R = g.R; a.plane = Epad; a.actw = actw;
+    a.levels = levels.data(); a.act = act.data(); a.allow = masked ? allow.data() : nullptr;
+    a.in_off = g.in_off.data(); a.in_sub = g.in_sub.data(); a.in_rel = g.in_rel.data(); a.in_eid = g.in_eid.data();
+    a.seed_off = seed_off; a.seeds = g.seeds.data(); a.out_off = g.out_off.data(); a.out_obj = g.out_obj.data();
+    a.out_rel = g.out_rel.data(); a.out_eid = seeds_side ? g.out_eid.data() : nullptr;
+    a.query_idx = query.data(); a.target = target.data(); a.length = k > 8 ? length.data() : nullptr; a.max_paths = max_paths;
+    a.path_count = count.data(); a.path_edges = edges.data();
+    run_grid(pairs, 64 * NW, waves, [&] { k_paths<NW>(a); });
+    int bad = 0, total = 0, longest = 0;
+    for (int i = 0; i < pairs; ++i) {
+        int d = 0;
+        if (k > 8) d = g.level[length[i]][target[i]] ? length[i] : g.k + 1;
+        else while (d <= g.k && !g.level[d][target[i]]) ++d;
+        std::vector<std::vector<int>> all;
+        std::vector<int> path;
+        if (d <= g.k) g.search(target[i], d, path, all, max_paths);
+        bad += count[i] != (int)all.size();
+        total += (int)all.size();
+        if (!all.empty()) longest = std::max(longest, d);
+        for (int p = 0; p < max_paths; ++p)
+            for (int x = 0; x < g.k; ++x) {
+                const int want = p < (int)all.size() && x < (int)all[p].size() ? all[p][x] : -1;
+                bad += edges[((size_t)i * max_paths + p) * g.k + x] != want;
+            }
+    }
+    printf("%d wavefronts, masked %d, seeds' side %d, %d paths: %d found, of up to %d triples, %d wrong\\n", NW, masked, seeds_side, max_paths, total, longest, bad);
+    return bad;
+}
+
+int main() {
+    int bad = 0;
+    for (bool masked : {false, true})
+        for (bool seeds_side : {false, true})
+            for (int most : {16, 2}) {
+                bad += check<1>(5, masked, seeds_side, most, {0}) + check<4>(6, masked, seeds_side, most, {1, 2, 0, 3}, 40);
+                for (const std::vector<int> &waves : {std::vector<int>{0, 1, 2, 3}, std::vector<int>{3, 2, 1, 0}, std::vector<int>{2, 0, 3, 1}})
+                    bad += check<4>(5 + most, masked, seeds_side, most, waves);
+            }
+    return bad != 0;
+}
+"""
+
+
+def test_path_listing_between_one_wavefront_and_the_block(tmp_path):
+    # rows around the length up to which one wavefront goes on alone, and long ones on all levels
+    common, paths = text("common.h"), text("paths.hip")
+    run(tmp_path, "\n".join([
+        "#include <array>\n#define LOGOSKG_MAX_K 254",
+        device_helpers(),
+        between(paths, "struct PathArgs {", "// NW wavefronts (one block)"),
+        "template <int NW>\n" + definition(paths, "__global__ void __launch_bounds__(64 * NW) k_paths("),
+        PATHS_MAIN]))
