@@ -835,7 +835,8 @@ __global__ void __launch_bounds__(256) k_pred_narrow(FillArgs a) {
         for (int h = 0; h <= a.k; ++h) {
             if (h > 0) {
                 if (!wave_any(left != 0)) break;  // every pair of the tile is written
-                x = left ? a.levels[(size_t)h * a.plane + (size_t)e * W + word] & range : 0ull;
+                if (!a.hop) x = left;             // no hop numbers: all others at once
+                else x = left ? a.levels[(size_t)h * a.plane + (size_t)e * W + word] & range : 0ull;
             }
             left &= ~x;
             if (!wave_any(x != 0)) continue;

@@ -322,7 +322,8 @@ k_small_fetch(int q0, int n_all, int k, int last_level, long long plane, const i
         n += total;
         if (in) {
             int h = 0;
-            while (h < last_level && !(levels[(size_t)h * plane + e] & bit)) ++h;
+            if (hop || pred)  // (entities alone: no look at the levels)
+                while (h < last_level && !(levels[(size_t)h * plane + e] & bit)) ++h;
             s_ent[at] = e;
             s_hop[at] = (uint8_t)h;
             s_pred[at] = h == 0 ? -1 : INT_MAX;

@@ -425,3 +425,22 @@ def test_gather_probe_ors_the_lines_of_all_subjects():
     want = np.bitwise_or.reduce(lines[np.unique(w.subj)], axis=0)
     assert np.array_equal(out.cpu().numpy(), want)
     g.close()
+
+
+@pytest.mark.parametrize("Q, k", [(1, 3), (1, 40), (50, 3), (200, 3), (200, 9)])
+def test_narrow_planes_without_hop_numbers(Q, k):
+    m = lkg()
+    w = kggen.config2(0.004, num_queries=Q)
+    want = run_oracle(w, k=k)
+    g = m.Graph(w.subj, w.rel, w.obj, w.num_entities, w.num_relations, hub_min_degree=100)
+    for direction in ("auto", "pull"):  # (pulled searches never take the one-block path)
+        res = g.khop(w.seed_off, w.seeds, k, direction=direction)
+        ent, hop, pred = res.fetch(want_hop=False)
+        assert hop is None
+        assert np.array_equal(ent.cpu().numpy(), want[1]) and np.array_equal(pred.cpu().numpy(), want[3])
+        ent, hop, _ = res.fetch(want_pred=False)
+        assert np.array_equal(ent.cpu().numpy(), want[1]) and np.array_equal(hop.cpu().numpy(), want[2])
+        ent, _, _ = res.fetch(want_hop=False, want_pred=False)
+        assert np.array_equal(ent.cpu().numpy(), want[1])
+        res.close()
+    g.close()
