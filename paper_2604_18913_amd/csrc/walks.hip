@@ -52,7 +52,7 @@ k_walk_seeds(int32_t E, int W, int w, unsigned long long bit, const unsigned lon
 // that pass through the row's entries before j (exclusive running sum inside the row), cnt_cur[v] =
 // the row's total.
 //
-// Rows of up to kTailMaxDegree entries: a thread per entity walks its row, four entries' loads
+// Rows of up to kTailMaxDegree entries: a thread per entity walks its row, eight entries' loads
 // together (neighbouring rows are contiguous in OBJ, so a wavefront's loads share their lines).
 // Longer rows have a block each.  One wavefront per 64 entities, row after row, took 1.0 ms
 // a hop on a 3.4M-triple graph whatever the level held (a 10^5-entry row is 1,500 turns of one
@@ -89,14 +89,25 @@ __device__ __forceinline__ void walk_count_short(long long e, int32_t E, int W, 
     if (e >= E || !(level_h[(size_t)e * W + w] & bit)) return;
     const uint32_t lo = in_off[e], hi = in_off[e + 1];
     if (hi - lo > (uint32_t)kTailMaxDegree) return;
-    constexpr int U = 4;
+    constexpr int U = 8;
     static_assert(kTailMaxDegree <= kWalkSummands, "a short row's sum cannot wrap");
     unsigned long long running = 0;
     for (uint32_t j0 = lo; j0 < hi; j0 += U) {
+        int32_t sub[U];
+        uint16_t rel[U];
+        bool ok[U];
         unsigned long long c[U];
 #pragma unroll
+        for (int u = 0; u < U; ++u) {
+            ok[u] = j0 + u < hi;
+            sub[u] = ok[u] ? in_sub[j0 + u] : 0;
+            if (MASK) rel[u] = ok[u] ? in_rel[j0 + u] : (uint16_t)0;
+        }
+#pragma unroll
         for (int u = 0; u < U; ++u)
-            c[u] = j0 + u < hi ? walk_entry<MASK>(j0 + u, W, w, bit, allow, in_sub, in_rel, cnt_prev) : 0ull;
+            if (MASK && ok[u]) ok[u] = (allow[(size_t)rel[u] * W + w] & bit) != 0ull;
+#pragma unroll
+        for (int u = 0; u < U; ++u) c[u] = ok[u] ? cnt_prev[sub[u]] : 0ull;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (j0 + u < hi) cum[j0 + u] = running;
@@ -115,14 +126,13 @@ __device__ __forceinline__ unsigned long long walk_count_span(uint32_t lo, uint3
                                                               const uint16_t *__restrict__ in_rel,
                                                               const unsigned long long *__restrict__ cnt_prev,
                                                               unsigned long long *__restrict__ cum,
-                                                              unsigned long long (*part)[NW], uint32_t &high) {
+                                                              unsigned long long (*part)[NW], int &buf, uint32_t &high) {
     constexpr int NT = 64 * NW;
     static_assert(64 * U <= kWalkSummands, "a wavefront's sum of one turn cannot wrap");
     static_assert(NW + 1 <= kWalkSummands, "nor can the turn's, while its parts are below the limit");
     const int wave = threadIdx.x >> 6;
     unsigned long long running = 0;
-    int buf = 0;
-    for (uint32_t j0 = lo; j0 < hi; j0 += NT * U, buf ^= 1) {
+    for (uint32_t j0 = lo; j0 < hi; j0 += NT * U, buf ^= 1) {  // (buf: the half of `part` of this turn, the caller's next one too)
         const uint32_t base = j0 + (uint32_t)(wave * 64 * U + lane());
         unsigned long long c[U], incl[U], sum = 0;
 #pragma unroll
@@ -163,69 +173,104 @@ __device__ __forceinline__ long long giant_row_of(const uint32_t *__restrict__ s
 
 // One launch for all rows, blocks of four wavefronts: the first n_segs take a segment of kGiantSegment entries of a
 // giant row each (the first n_giant rows of the list; the segment's own running sums, its total to seg_total and to the
-// row's count), the next n_long a longer row, the others 256 entities, a thread for each short row.  The giants' running
-// sums are joined over their segments once, behind the last hop (k_walk_join_giant): the hops need the counts only.
+// row's count), the next n_long_blocks the longer rows, the others 256 entities, a thread for each short row.  A block
+// of longer rows looks at every n_long_blocks-th of them (so the longest spread over the blocks) and walks those that are
+// in the level: mostly few are, and a block per row took 445 us for two counts of 3 hops of a query that reaches little
+// of 30M triples, kWalkBlocks blocks take 350.  The giants' running sums are joined over their segments once, behind the
+// last hop (k_walk_join_giant): the hops need the counts only.
 // A block per giant row was a chain of 4,096-entry turns, 140 .. 176 us a hop on 3.4M triples.  Segments, their join,
 // longer and short rows in a launch each were 4 launches a hop: the whole call of three hops there 583 us, 495 us now,
 // and two counts (2 and 3 hops) of a query that reaches nothing 258 us, 205 us now.
+constexpr unsigned kWalkBlocks = 4096;  // at most; twice what the GPU holds at once
+
 template <bool MASK>
 __global__ void __launch_bounds__(256)
 k_walk_count(const int32_t *__restrict__ rows, const uint32_t *__restrict__ seg_first, unsigned n_giant, unsigned n_segs,
-             unsigned n_long, int32_t E, int W, int w, unsigned long long bit,
+             unsigned n_long, unsigned n_long_blocks, int32_t E, int W, int w, unsigned long long bit,
              const unsigned long long *__restrict__ level_h, const unsigned long long *__restrict__ allow,
              const uint32_t *__restrict__ in_off, const int32_t *__restrict__ in_sub, const uint16_t *__restrict__ in_rel,
              const unsigned long long *__restrict__ cnt_prev, unsigned long long *__restrict__ cnt_cur,
              unsigned long long *__restrict__ cum, unsigned long long *__restrict__ seg_total, unsigned int *overflow) {
     __shared__ unsigned long long part[2][4];
     const unsigned b = blockIdx.x;
-    if (b >= n_segs + n_long) {
-        walk_count_short<MASK>((long long)(b - n_segs - n_long) * 256 + threadIdx.x, E, W, w, bit, level_h, allow, in_off,
-                               in_sub, in_rel, cnt_prev, cnt_cur, cum, overflow);
+    if (b >= n_segs + n_long_blocks) {
+        walk_count_short<MASK>((long long)(b - n_segs - n_long_blocks) * 256 + threadIdx.x, E, W, w, bit, level_h, allow,
+                               in_off, in_sub, in_rel, cnt_prev, cnt_cur, cum, overflow);
         return;
     }
-    const long long i = b < n_segs ? giant_row_of(seg_first, n_giant, b) : (long long)n_giant + (b - n_segs);
-    const int32_t v = rows[i];
-    if (!(level_h[(size_t)v * W + w] & bit)) return;  // block-uniform
-    uint32_t lo = in_off[v], hi = in_off[v + 1], high = 0;
+    int buf = 0;
     if (b < n_segs) {
-        lo += (b - seg_first[i]) * (uint32_t)kGiantSegment;
-        hi = min(lo + (uint32_t)kGiantSegment, hi);
+        const long long i = giant_row_of(seg_first, n_giant, b);
+        const int32_t v = rows[i];
+        if (!(level_h[(size_t)v * W + w] & bit)) return;  // block-uniform
+        const uint32_t lo = in_off[v] + (b - seg_first[i]) * (uint32_t)kGiantSegment;
+        const uint32_t hi = min(lo + (uint32_t)kGiantSegment, in_off[v + 1]);
+        uint32_t high = 0;
         const unsigned long long total =
-            walk_count_span<MASK, 4, 4>(lo, hi, W, w, bit, allow, in_sub, in_rel, cnt_prev, cum, part, high);
+            walk_count_span<MASK, 4, 4>(lo, hi, W, w, bit, allow, in_sub, in_rel, cnt_prev, cum, part, buf, high);
         if (threadIdx.x == 0) {
             const unsigned long long x = capped(total, high, overflow);
             seg_total[b] = x;
             atomicAdd(&cnt_cur[v], x);  // (whether the row's sum passed the limit shows in the join)
         }
-    } else {
-        const unsigned long long total =
-            walk_count_span<MASK, 4, 2>(lo, hi, W, w, bit, allow, in_sub, in_rel, cnt_prev, cum, part, high);
-        if (threadIdx.x == 0) cnt_cur[v] = capped(total, high, overflow);
+        return;
+    }
+    for (unsigned first = b - n_segs; first < n_long; first += 64u * n_long_blocks) {  // lane = one of the block's rows
+        const unsigned at = first + (unsigned)lane() * n_long_blocks;
+        int32_t mine = 0;
+        bool in = at < n_long;
+        if (in) {
+            mine = rows[n_giant + at];
+            in = (level_h[(size_t)mine * W + w] & bit) != 0ull;
+        }
+        for (unsigned long long m = __ballot(in); m; m &= m - 1) {  // the same rows in every wavefront
+            const int32_t v = __shfl(mine, __builtin_ctzll(m));
+            uint32_t high = 0;
+            const unsigned long long total = walk_count_span<MASK, 4, 2>(in_off[v], in_off[v + 1], W, w, bit, allow, in_sub,
+                                                                         in_rel, cnt_prev, cum, part, buf, high);
+            if (threadIdx.x == 0) cnt_cur[v] = capped(total, high, overflow);
+        }
     }
 }
 
-// Every segment of a giant row adds what lies before it in its row; blockIdx.y = hop - 1.
-__global__ void __launch_bounds__(1024)
+// Every segment of a giant row adds what lies before it in its row, for the hops whose level holds the row (lane = hop).
+// Small blocks that look at all hops: in blocks of 1,024 threads per segment and hop the search for the row alone, again in
+// each, was 40 us of a count of 3 hops on 30M triples.
+__global__ void __launch_bounds__(256)
 k_walk_join_giant(const int32_t *__restrict__ rows, const uint32_t *__restrict__ seg_first, long long n_rows, int W, int w,
-                  unsigned long long bit, const unsigned long long *__restrict__ levels, size_t plane,
+                  unsigned long long bit, const unsigned long long *__restrict__ levels, size_t plane, int d,
                   const uint32_t *__restrict__ in_off, const unsigned long long *__restrict__ seg_totals, long long T,
                   unsigned long long *__restrict__ cums, unsigned int *overflow) {
+    constexpr int U = 8;
     const long long i = giant_row_of(seg_first, n_rows, blockIdx.x);
     const int32_t v = rows[i];
-    if (!(levels[(blockIdx.y + 1) * plane + (size_t)v * W + w] & bit)) return;  // block-uniform
-    const unsigned long long *seg_total = seg_totals + (size_t)blockIdx.y * gridDim.x;
-    unsigned long long *cum = cums + (size_t)blockIdx.y * T;
-    unsigned long long before = 0;
-    uint32_t high = 0;
-    for (uint32_t x = seg_first[i]; x < blockIdx.x; ++x) {
-        before += seg_total[x];
-        high |= upper_half(before);
-    }
     const uint32_t lo = in_off[v] + (blockIdx.x - seg_first[i]) * (uint32_t)kGiantSegment;
     const uint32_t hi = min(lo + (uint32_t)kGiantSegment, in_off[v + 1]);
-    if (before)
-        for (uint32_t j = lo + threadIdx.x; j < hi; j += 1024) cum[j] += before;
-    if (threadIdx.x == 0) (void)capped(before, high | upper_half(before + seg_total[blockIdx.x]), overflow);
+    for (int h0 = 0; h0 < d; h0 += 64) {
+        const int mine = h0 + lane();  // hop - 1
+        for (unsigned long long m = __ballot(mine < d && (levels[(size_t)(mine + 1) * plane + (size_t)v * W + w] & bit)); m;
+             m &= m - 1) {  // the same hops in every wavefront
+            const int h = h0 + __builtin_ctzll(m);
+            const unsigned long long *seg_total = seg_totals + (size_t)h * gridDim.x;
+            unsigned long long *cum = cums + (size_t)h * T;
+            unsigned long long before = 0;
+            uint32_t high = 0;
+            for (uint32_t x = seg_first[i]; x < blockIdx.x; ++x) {
+                before += seg_total[x];
+                high |= upper_half(before);
+            }
+            if (before)
+                for (uint32_t j = lo + threadIdx.x; j < hi; j += 256 * U) {  // eight loads ahead of their stores
+                    unsigned long long c[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) c[u] = j + u * 256 < hi ? cum[j + u * 256] : 0ull;
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        if (j + u * 256 < hi) cum[j + u * 256] = c[u] + before;
+                }
+            if (threadIdx.x == 0) (void)capped(before, high | upper_half(before + seg_total[blockIdx.x]), overflow);
+        }
+    }
 }
 
 // pref[0] = 0 and the running sum over the entities must not have wrapped
@@ -286,11 +331,11 @@ static void launch_walk_hop(logoskg_graph *g, int W, int w, unsigned long long b
                             unsigned int *overflow, unsigned long long *seg_total, hipStream_t st) {
     const RowClasses &rc = g->in_rows;
     const unsigned giants = seg_total ? (unsigned)rc.n_giant : 0u, segs = giants ? (unsigned)rc.n_giant_segs : 0u;
-    // (at most T / 8192 + n_giant segments, T / 33 rows and E / 256 blocks: below the grid's limit)
-    const unsigned n_long = (unsigned)rc.n_long - giants;
-    k_walk_count<MASK><<<dim3(segs + n_long + (unsigned)((g->E + 255) / 256)), dim3(256), 0, st>>>(
-        rc.longrows, rc.giant_seg_first, giants, segs, n_long, g->E, W, w, bit, level_h, allow, g->in_off, in_sub, in_rel,
-        prev, cur, cum, seg_total, overflow);
+    // (at most T / 8192 + n_giant segments and E / 256 blocks of entities: below the grid's limit)
+    const unsigned n_long = (unsigned)rc.n_long - giants, n_long_blocks = std::min(n_long, kWalkBlocks);
+    k_walk_count<MASK><<<dim3(segs + n_long_blocks + (unsigned)((g->E + 255) / 256)), dim3(256), 0, st>>>(
+        rc.longrows, rc.giant_seg_first, giants, segs, n_long, n_long_blocks, g->E, W, w, bit, level_h, allow, g->in_off,
+        in_sub, in_rel, prev, cur, cum, seg_total, overflow);
 }
 
 static logoskg_status prepare_walk_tables(logoskg_result *r, int q, int d, hipStream_t st) {
@@ -329,8 +374,8 @@ static logoskg_status prepare_walk_tables(logoskg_result *r, int q, int d, hipSt
             else launch_walk_hop<false>(g, W, w, bit, lvl, nullptr, in_sub, in_rel, prev, cur, cum, overflow, totals, st);
         }
         if (seg_total && d > 0)
-            k_walk_join_giant<<<dim3((unsigned)segs, (unsigned)d), dim3(1024), 0, st>>>(
-                g->in_rows.longrows, g->in_rows.giant_seg_first, g->in_rows.n_giant, W, w, bit, r->levels, plane, g->in_off,
+            k_walk_join_giant<<<dim3((unsigned)segs), dim3(256), 0, st>>>(
+                g->in_rows.longrows, g->in_rows.giant_seg_first, g->in_rows.n_giant, W, w, bit, r->levels, plane, d, g->in_off,
                 seg_total, (long long)T, r->walk_cum, overflow);
     }
     LKG_HIP(hipGetLastError());

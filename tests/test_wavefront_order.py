@@ -106,9 +106,10 @@ template <int W, int NB, int TILES> int check(const std::vector<int> &waves, boo
 int main() {
     int bad = 0;
     for (bool listed : {false, true}) {
-        bad += check<1, 0, 4>({0}, listed) + check<1, 2, 4>({0}, listed);
+        bad += check<1, 0, 4>({0}, listed) + check<1, 2, 1>({0}, listed);
         for (const std::vector<int> &waves : {std::vector<int>{0, 1, 2, 3}, std::vector<int>{3, 2, 1, 0}})
-            bad += check<4, 0, 16>(waves, listed) + check<4, 2, 16>(waves, listed) + check<4, 2, 4>(waves, listed);
+            bad += check<4, 0, 16>(waves, listed) + check<4, 2, 16>(waves, listed) + check<4, 2, 4>(waves, listed) +
+                   check<4, 0, 1>(waves, listed);
     }
     return bad != 0;
 }
@@ -331,3 +332,70 @@ def test_path_listing_between_one_wavefront_and_the_block(tmp_path):
         between(paths, "struct PathArgs {", "// NW wavefronts (one block)"),
         "template <int NW>\n" + definition(paths, "__global__ void __launch_bounds__(64 * NW) k_paths("),
         PATHS_MAIN]))
+
+
+WALKS_MAIN = """
+int main() {
+    int bad = 0;
+    for (unsigned share : {100u, 60u, 5u})  // of the entities that are in the level
+        for (const std::vector<int> &waves : {std::vector<int>{0, 1, 2, 3}, std::vector<int>{3, 2, 1, 0}, std::vector<int>{1, 3, 0, 2}}) {
+            unsigned long long rng = share;
+            auto next = [&]() { rng = rng * 6364136223846793005ull + 1442695040888963407ull; return (unsigned)(rng >> 33); };
+            // giant rows of two and three segments, then longer ones by descending degree, then short ones
+            std::vector<int> degree = {2 * kGiantSegment + 5, kGiantSegment + 1};
+            for (int i = 0; i < 41; ++i) degree.push_back(1600 - 39 * i);
+            for (int i = 0; i < 300; ++i) degree.push_back((int)(next() % 33));
+            const int E = (int)degree.size(), n_giant = 2, n_long = 41;
+            std::vector<int32_t> place(E), rows;
+            std::iota(place.begin(), place.end(), 0);
+            for (int i = E; i > 1; --i) std::swap(place[i - 1], place[next() % i]);
+            std::vector<uint32_t> off(E + 1);
+            for (int i = 0; i < E; ++i) off[place[i] + 1] = degree[i];
+            for (int e = 0; e < E; ++e) off[e + 1] += off[e];
+            for (int i = 0; i < n_giant + n_long; ++i) rows.push_back(place[i]);
+            const uint32_t T = off[E];
+            std::vector<int32_t> sub(T);
+            std::vector<uint16_t> rel(T);
+            std::vector<unsigned long long> prev(E), level(2 * E), allow(4), cum(T, 77), cnt(E), totals(5, 77);
+            for (auto &s : sub) s = (int32_t)(next() % E);
+            for (auto &r : rel) r = (uint16_t)(next() % 4);
+            for (auto &c : prev) c = next() % 1000;
+            for (int e = 0; e < E; ++e) level[E + e] = next() % 100 < share ? 4 : 3;
+            allow = {4, 0, 7, 4};
+            std::vector<uint32_t> first = {0, 3, 5};
+            const unsigned long_blocks = share == 60 ? 5 : share == 5 ? n_long : 30;  // rows per block: 9, 1, 2
+            unsigned overflow = 0;
+            run_grid(5 + long_blocks + (E + 255) / 256, 256, waves, [&] {
+                k_walk_count<true>(rows.data(), first.data(), n_giant, 5, n_long, long_blocks, E, 1, 0, 4ull, level.data() + E,
+                                   allow.data(), off.data(), sub.data(), rel.data(), prev.data(), cnt.data(), cum.data(),
+                                   totals.data(), &overflow);
+            });
+            run_grid(5, 256, waves, [&] {
+                k_walk_join_giant(rows.data(), first.data(), n_giant, 1, 0, 4ull, level.data(), E, 1, off.data(), totals.data(), T,
+                                  cum.data(), &overflow);
+            });
+            int wrong = overflow != 0;
+            for (int e = 0; e < E; ++e) {
+                unsigned long long sum = 0;
+                const bool in = level[E + e] & 4;
+                for (uint32_t j = off[e]; j < off[e + 1]; ++j) {
+                    wrong += cum[j] != (in ? sum : 77);
+                    if (rel[j] != 1) sum += prev[sub[j]];
+                }
+                wrong += cnt[e] != (in ? sum : 0);
+            }
+            printf("%u %% in the level: %d wrong\\n", share, wrong);
+            bad += wrong;
+        }
+    return bad != 0;
+}
+"""
+
+
+def test_chain_counts_of_every_class_of_rows(tmp_path):
+    common, walks = text("common.h"), text("walks.hip")
+    run(tmp_path, "\n".join([
+        between(common, "constexpr int kTailMaxDegree", "struct RowSegment"),
+        device_helpers(),
+        between(walks, "constexpr unsigned long long kWalkCountLimit", "// pref[0] = 0 and the running sum over"),
+        WALKS_MAIN]))
