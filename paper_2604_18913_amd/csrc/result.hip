@@ -294,9 +294,9 @@ __device__ __forceinline__ long long super_start(const FillArgs &a, long long st
 // keeps its word of all the block's tiles in registers (visited and the bit-sliced hop
 // number), and for one query at a time compacts the reached entities into LDS,
 // then streams them out with full-width stores.
-// NB = words of the bit-sliced hop number (0: entity ids only); TILES = tiles per block: half a
-// super tile on 16-word planes, where the registers of a whole one would not leave room for
-// two blocks per CU; a whole or a quarter on narrower ones (launch_lists_w).
+// NB = words of the bit-sliced hop number (0: entity ids only); TILES = tiles per block
+// (launch_lists_w), at most half a super tile on 16-word planes, where the registers of a whole one
+// would not leave room for two blocks per CU.
 template <int W, int NB, int TILES>
 __global__ void __launch_bounds__(64 * W) k_lists(FillArgs a) {
     constexpr int Qp = 64 * W, NBX = NB > 0 ? NB : 1;
@@ -1820,20 +1820,27 @@ static void launch_lists_t(Profiler &prof, const FillArgs &a, hipStream_t st) {
     else k_lists<W, 8, TILES><<<grid, block, 0, st>>>(a);
 }
 
-// Tiles per block.  A wavefront takes the queries of its word one after the other through all tiles of the block, so
-// on narrow planes, where a block has few wavefronts, a whole super tile is a long chain on a GPU that is nearly
-// empty (64 queries, 108,000 listed entities, no hops: 16 tiles 148 us, 8: 89, 4: 59, 2: 44).  One-word planes take
-// four (128M entries on 2M listed entities: 175 us with 16, 172 with 4, 187 with 2).  On four-word planes the shorter
-// runs of a small block cost 10 % where the GPU is full (200 queries, 2M listed: 439 us with 16, 482 with 4), so
-// they take four tiles only below 2 blocks of 16 per CU (108,000 listed: 94 us with 16, 46 with 4; 870,000 listed, 850
-// blocks of 16: 159 and 154 without hops, 177 and 199 for a level).
-constexpr long long kListsFullBlocks = 512;
+// Tiles per block.  A wavefront takes the queries of its word one after the other through all tiles of the block, so a
+// block of many tiles is a long chain, and until the GPU's wavefront slots are full nothing speaks for more than one
+// tile: one while all tiles' wavefronts fit the slots, four while the blocks' do.  Behind that the longer runs of a
+// large block are worth more: a super tile on four-word planes, half of one on 16-word planes; one-word planes stay at
+// four.  us without / with hop numbers (words, tiles; by tiles per block):
+//    1 word,     718 tiles      1:  34 /  38     4:  55 /  64     8:  84 / 100    16: 142 / 176
+//    1 word,  15,203 tiles      1:  78 / 128     4:  71 / 109     8:  95 / 137    16: 151 / 226
+//    4 words,  1,689 tiles      1:  52 /  62     4:  60 /  75     8:  89 / 110    16: 153 / 198
+//    4 words,  4,591 tiles      1: 115 / 167     4:  79 / 145     8: 103 / 159    16: 168 / 275
+//    4 words, 15,262 tiles      1: 429 / 645     4: 308 / 437     8: 294 / 424    16: 284 / 508
+//   16 words,    719 tiles      1:  41 /  49     4:  59 /  74     8:  89 / 120
+//   16 words,  1,670 tiles      1:  58 /  73     4:  55 /  71     8:  74 /  97
+//   16 words, 13,676 tiles      1: 252 / 360     4: 138 / 280     8: 138 / 305
+constexpr long long kListsWaves = 8192;
 
 template <int W>
 static void launch_lists_w(Profiler &prof, const FillArgs &a, hipStream_t st) {
-    if constexpr (W == 16) launch_lists_t<W, kSuperTiles / 2>(prof, a, st);
-    else if (W == 1 || a.ntiles < kListsFullBlocks * kSuperTiles) launch_lists_t<W, 4>(prof, a, st);
-    else launch_lists_t<W, kSuperTiles>(prof, a, st);
+    constexpr int most = W == 16 ? kSuperTiles / 2 : W == 4 ? kSuperTiles : 4;
+    if (a.ntiles * W <= kListsWaves) launch_lists_t<W, 1>(prof, a, st);
+    else if (a.ntiles * W <= 4 * kListsWaves) launch_lists_t<W, 4>(prof, a, st);
+    else launch_lists_t<W, most>(prof, a, st);
 }
 
 // True when the 16-word tile kernel can serve this launch (it then can also write the entity and

@@ -107,11 +107,12 @@ def test_levels_and_lists_without_predecessors_of_four_word_planes(num_queries):
     g.close()
 
 
-@pytest.mark.parametrize("listed", [524_288 - 64, 524_288 - 63, 524_288, 530_001])
-def test_lists_of_four_word_planes_at_the_change_of_the_block(listed):
-    # one question seeds `listed` entities, none of which has a triple: 8,191 and 8,192 tiles and more
+@pytest.mark.parametrize("Q, tiles", [(40, 8192), (100, 2048), (100, 8192), (300, 512), (300, 2048)])
+@pytest.mark.parametrize("more", [0, 1, 900])
+def test_lists_at_the_changes_of_the_block(Q, tiles, more):
+    # one question seeds 64 `tiles` + `more` entities, none of which has a triple
     m = lkg()
-    E, Q = 600_000, 100
+    E, listed = 600_000, 64 * tiles + more
     rng = np.random.default_rng(listed)
     ids = np.sort(rng.permutation(E - 10)[:listed]).astype(np.int32)
     lists = [ids[q::50] for q in range(Q - 1)] + [ids]
@@ -122,7 +123,7 @@ def test_lists_of_four_word_planes_at_the_change_of_the_block(listed):
         ent, hop, _ = res.fetch(want_hop=want_hop, want_pred=False)
         assert np.array_equal(ent.cpu().numpy(), np.concatenate(lists))
         assert hop is None or int(hop.max()) == 0
-    _, ent = res.level(0, 60, Q)
-    assert np.array_equal(ent.cpu().numpy(), np.concatenate(lists[60:]))
+    _, ent = res.level(0, Q - 30, Q)
+    assert np.array_equal(ent.cpu().numpy(), np.concatenate(lists[Q - 30:]))
     res.close()
     g.close()
