@@ -796,11 +796,11 @@ __global__ void __launch_bounds__(1024) k_narrow_row(FillArgs a, long long first
 
 // Tiles of one- and four-word planes: a wavefront per word of a tile writes the entity and hop lists (lane =
 // entity; where a query reached many of the tile's entities, query by query with contiguous stores, else entity
-// by entity), then every entity whose object row has at most 32 entries is walked by a W-lane group, eight
+// by entity), then every entity whose object row has at most 32 entries is walked by a W-lane group, U
 // entries gathered together and resolved in order.  Longer rows are left to the row kernels.
 template <int W, bool MASK, bool STATS>
 __global__ void __launch_bounds__(256) k_pred_narrow(FillArgs a) {
-    constexpr int TPB = 4 / W, U = 8;
+    constexpr int TPB = 4 / W, U = MASK ? 2 : 8;  // (65 queries with whitelists, 20M triples: call 587 us with eight, 549 with four, 547 with two)
     static_assert(W == 1 || W == 4, "a block of four wavefronts");
     __shared__ unsigned long long mT[4][64];  // per wavefront, i.e. (tile, word): entities each query reached
     __shared__ long long base[4][64];         // and where its run of the tile starts in the lists
@@ -1146,9 +1146,11 @@ k_pred_walk(FillArgs a, unsigned long long *__restrict__ codes, unsigned long lo
                 // A page of the batch: eight entries of the row are gathered together (the group's lanes take a word
                 // each) and resolved in order.  No frontier bit is asked for first: it costs as much as the piece of a
                 // line.  With two and four lanes eight entries (63 queries over two words, 50M triples: 327 us with
-                // two at a time, 280 us now); a lane per entity takes kPageEntries, because what it gathers past the
+                // two at a time, 280 us now).  Under whitelists every entry costs a second gather: two (70 queries of a
+                // hub-heavy graph of 20M triples: call 840 us with eight, 796 with four, 781 with two; of 30M triples of
+                // concepts 915, 879 and 882).  A lane per entity takes kPageEntries as well, because what it gathers past the
                 // entry that resolves the last query is lost and its rate is that of the scattered sectors.
-                constexpr int U = G == 1 ? kPageEntries : 8;
+                constexpr int U = G == 1 || MASK ? kPageEntries : 8;
                 for (int i0 = 0; i0 < (int)deg; i0 += U) {  // (i0 is the same in all lanes that are still in the loop)
                     int sx[U], rx[U];
                     unsigned long long l[U];
