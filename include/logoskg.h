@@ -290,13 +290,25 @@ logoskg_status logoskg_result_offsets(const logoskg_result *r, int64_t *reached_
  * Asynchronous on `stream`: the kernels of a fetch run in turn on it.  (With
  * LOGOSKG_OVERLAP_FETCH=1 in the environment the independent ones run on helper
  * streams - made once per device, shared by all graphs on it, kept until the
- * process ends - and join `stream` before the call returns; measured, no gain.)  The
- * first call on a graph that asks for pred_edge with more than 256 queries
- * allocates a buffer of 4 KiB per object row of more than 32 entries (not
- * above 8 GiB; freed with the graph) and, on a resident graph built with
+ * process ends - and join `stream` before the call returns; measured, no gain.)
+ * Memory: the first call on a graph that asks for pred_edge with more than 256
+ * queries allocates a buffer of 4 KiB per object row of more than 32 entries
+ * (not above 8 GiB; freed with the graph) and, on a resident graph built with
  * host_build, 4 bytes per triple for the triple index of every entry of SUB
- * (a device build keeps them).  On a sharded graph pred_edge streams the
- * object-sorted triples from pinned host memory.
+ * (12 more and a synchronisation while they are sorted; a device build holds
+ * them from the start, logoskg_graph_info.device_bytes; without room for them
+ * the call does without).  From the graph's pool, given back to it behind the
+ * call's work, a call with pred_edge takes
+ *   - with at most 256 queries, or k > 6: 256, 1,024 or 4,096 bytes (for 64, 256
+ *     and more queries) per object row of at least 8,192 entries;
+ *   - for a page of more than 256 queries whose words are one, two or four
+ *     aligned ones, on a result that lists at least 4 M entities: 8, 16 or 32
+ *     bytes per entity and level (no more than 4 GiB; not packed otherwise).
+ * Without room for either the call does without, and so does one that a stream
+ * capture records: it takes nothing and may be captured (more than 256
+ * queries: after a first call outside a capture).  On a sharded graph pred_edge
+ * streams the object-sorted triples from pinned host memory, or, when the cache
+ * holds every unit, from the cache.
  */
 logoskg_status logoskg_result_fetch(logoskg_result *r, int32_t q_begin, int32_t q_end,
                                     int64_t capacity, int32_t *entity, uint8_t *hop,

@@ -20,12 +20,16 @@
 //           row of the entity with a mask of still unresolved queries, so every
 //           (query, entity) pair is written once.  Object rows of up to 32
 //           entries belong to the tile kernels that walk them in ascending
-//           edge id (for 16-word planes and k <= 6 the pair k_pred_walk /
-//           k_pred_emit, which writes the entity and hop lists as well;
-//           k_pred otherwise); rows of 33 .. hub_min-1 entries belong to
+//           edge id and write the entity and hop lists as well (k_pred_narrow
+//           on planes of one and four words, the pair k_pred_walk / k_pred_emit
+//           on 16-word planes with k <= 6; k_pred, beside k_lists, for deeper
+//           searches there); rows of 33 .. hub_min-1 entries belong to
 //           k_pred_wave and longer ones to k_pred_row, whose lanes claim in
-//           parallel and keep the minimum.  A level with a small frontier is
-//           taken from the subject side for these longer rows (k_pred_push).
+//           parallel and keep the minimum, or, where a line has one or four
+//           words or the fetched queries sit in one, two or four aligned words
+//           of it, to k_narrow_wave and k_narrow_row with a lane per entry.  A
+//           level with a small frontier is taken from the subject side for the
+//           longer rows of 16-word planes (k_pred_push).
 #include <algorithm>
 #include <climits>
 #include <cstdlib>
@@ -147,16 +151,15 @@ __device__ __forceinline__ long long xcd_contiguous(long long block, long long n
 }
 
 // ---------------------------------------------------------------- counts
-// One block per super tile, one wavefront per word: tile_base[tile][q] = entities
+// 16-word planes: one block per super tile, one wavefront per word: tile_base[tile][q] = entities
 // query q reached in the earlier tiles of the super tile, super_sum[st][q] = in
 // the whole super tile.
 // With a list the number of tiles follows from *n_active (the grid covers the largest possible
 // number of super tiles; those behind the list write zero sums).
-template <int W>
-__global__ void k_count(const unsigned long long *__restrict__ visited, long long ntiles, int32_t E,
-                        const int32_t *__restrict__ tile_ent, const unsigned long long *__restrict__ n_active,
-                        uint16_t *tile_base, uint32_t *super_sum) {
-    constexpr int Qp = 64 * W;
+__global__ void __launch_bounds__(1024)
+k_count(const unsigned long long *__restrict__ visited, long long ntiles, int32_t E, const int32_t *__restrict__ tile_ent,
+        const unsigned long long *__restrict__ n_active, uint16_t *tile_base, uint32_t *super_sum) {
+    constexpr int W = 16, Qp = 64 * W;
     __shared__ unsigned long long stage[64][W + 1];
     const long long st = blockIdx.x;
     const int wave = threadIdx.x >> 6;
@@ -410,10 +413,11 @@ struct PredQueue {
     uint8_t at[64];
 };
 
-template <int W, bool MASK, typename Emit>
+template <bool MASK, typename Emit>
 __device__ __forceinline__ int pred_resolve_unordered(int s, int r, bool cand, const FillArgs &a,
                                                       const unsigned long long *__restrict__ prev, PredQueue &queue,
                                                       unsigned long long &rem, Emit emit) {
+    constexpr int W = 16;
     const int lw = lane() & (W - 1), g = lane() / W;
     const unsigned long long cm = __ballot(cand);
     const int n = __popcll(cm);
@@ -495,9 +499,9 @@ __device__ __forceinline__ unsigned long long and_groups(unsigned long long x) {
 // query is kept in a table of the wavefront in LDS; the groups' masks are merged once per 64
 // entries, and after a level the table is written out (one contiguous store per 64 queries in the
 // row-buffer mode) and reset.
-template <int W, bool MASK, bool STATS, bool BUF>
+template <bool MASK, bool STATS, bool BUF>
 __global__ void __launch_bounds__(256) k_pred_wave(FillArgs a, long long first_row, long long n_rows_total) {
-    constexpr int Qp = 64 * W;
+    constexpr int W = 16, Qp = 64 * W;
     __shared__ long long slots[BUF ? 1 : 4][BUF ? 1 : Qp];
     __shared__ unsigned int smin_all[4][W * kClaimStride];  // smallest entry per query (index into in_sub)
     __shared__ PredQueue queue[4];
@@ -529,7 +533,7 @@ __global__ void __launch_bounds__(256) k_pred_wave(FillArgs a, long long first_r
                 s_next = jn < hi ? a.in_sub[jn] : -1;
                 r_next = MASK && jn < hi ? a.in_rel[jn] : 0;
                 const bool cand = s >= 0 && (dense || ((act_prev[s >> 5] >> (s & 31)) & 1u));
-                n_lines += pred_resolve_unordered<W, MASK>(s, r, cand, a, prev, queue[wave], rem, [&](unsigned long long hit, int at) {
+                n_lines += pred_resolve_unordered<MASK>(s, r, cand, a, prev, queue[wave], rem, [&](unsigned long long hit, int at) {
                     claim(&smin[lw * kClaimStride], hit, j0 + (uint32_t)at);
                 });
                 rem = and_groups<W>(rem);  // what any group has resolved is resolved
@@ -841,6 +845,10 @@ __global__ void __launch_bounds__(256) k_pred_narrow(FillArgs a) {
             left &= ~x;
             if (!wave_any(x != 0)) continue;
             const unsigned long long present = wave_or64(x);
+            // Query by query a store instruction covers neighbouring places of one list, entity by entity every lane
+            // has a turn per query of its own: the first where a query has eight and more of the tile's entities.
+            // Kernel, us all entity by entity / all query by query / so: 250 queries on 5M hub-heavy triples 1,822 /
+            // 1,263 / 1,318, 200 on 3.4M 122 / 99 / 99, 64 on a sparse graph of 500,000 19.7 / 23.3 / 20.3.
             if (wave_sum((long long)__popcll(x)) >= 8ll * __popcll(present)) {
                 for (unsigned long long m = present; m; m &= m - 1) {
                     const int qq = __ffsll((long long)m) - 1;
@@ -914,9 +922,9 @@ __global__ void __launch_bounds__(256) k_pred_narrow(FillArgs a) {
 // tile's run; seeds get -1.  Phase 2: every entity whose object row has at most
 // 32 entries is walked by one W-lane group, two candidate lines in flight.
 // Longer rows are left to k_pred_row.
-template <int W, bool MASK, bool STATS>
-__global__ void __launch_bounds__(64 * W) k_pred(FillArgs a) {
-    constexpr int Qp = 64 * W;
+template <bool MASK, bool STATS>
+__global__ void __launch_bounds__(1024) k_pred(FillArgs a) {
+    constexpr int W = 16, Qp = 64 * W;
     __shared__ unsigned long long stage[64][W + 1];
     __shared__ unsigned long long mT[Qp];
     __shared__ long long base[Qp];
@@ -972,9 +980,7 @@ __global__ void __launch_bounds__(64 * W) k_pred(FillArgs a) {
                     s = a.in_sub[j];
                     cand = (act_prev[s >> 5] >> (s & 31)) & 1u;
                 }
-                unsigned gm = 0;
-                if constexpr (W == 1) gm = cand ? 1u : 0u;
-                else gm = (unsigned)((__ballot(cand) >> g0) & ((1ull << W) - 1ull));
+                unsigned gm = (unsigned)((__ballot(cand) >> g0) & ((1ull << W) - 1ull));
                 if (lw == 0) {
                     n_edges += min((uint32_t)W, hi - j0);
                     n_lines += __popc(gm);
@@ -1055,7 +1061,15 @@ constexpr int kPageEntries = 2;  // entries one lane per entity gathers together
 // line.  When the listed entities' lines are past what the infinity cache holds, the page's words of every level
 // are packed first, and the gathers run on arrays that it does hold: 20M entities, 64 queries, 160 MB instead of
 // 2.5 GB per level - packing 1.3 ms, row walk 4.3 -> 2.4 ms, giant rows 2.0 -> 1.7 ms.  Below that packing costs
-// more than it saves (1.4M listed of 5M entities, four words: 205 us against 60 us saved).
+// more than it saves where few entities are listed, because it goes over all of them (1.4M listed of 5M, four words: 205
+// us against 60 us saved), and with four words also where nearly all are.  Page calls of hub-heavy graphs that list
+// 99 % of their entities, us unpacked / packed (one, two, four words):
+//     3.0M   1,474 / 1,325   2,007 / 1,909    3,107 / 3,199
+//     4.0M   2,002 / 1,779   2,659 / 2,524    4,191 / 4,276
+//     4.9M   2,400 / 1,999   3,241 / 2,885    4,953 / 4,838
+//     7.9M   3,709 / 3,120   5,115 / 4,757    7,911 / 7,531
+//    15.8M   6,876 / 5,814  10,139 / 9,026   14,483 / 13,958
+// so the line lies where four words begin to gain.  (A capture packs nothing: see captured().)
 constexpr long long kPageLines = 4ll << 20;             // listed entities from which the words are packed: 512 MB of lines
 constexpr size_t kPagePlaneBytes = (size_t)4 << 30;     // the packed planes take no more than this
 
@@ -1534,15 +1548,15 @@ k_pred_emit(FillArgs a, const unsigned long long *__restrict__ codes, const unsi
 // (atomicMin; the line starts at INT_MAX).  A block that walks a whole 140,000-entry row is a chain
 // of dependent gathers that outlasts everything else in the launch; the segments of a row run side
 // by side, at the price of the early exit between them (it saved a quarter of the entries).
-template <int W, bool MASK, bool STATS, bool BUF, bool SEG = false>
+template <bool MASK, bool STATS, bool BUF, bool SEG = false>
 __global__ void __launch_bounds__(1024) k_pred_row(FillArgs a, long long first_row) {
     static_assert(!SEG || BUF, "segments merge in the row buffer");
-    constexpr int Qp = 64 * W;
+    constexpr int W = 16, Qp = 64 * W;
     constexpr int C = 4;  // 64-entry chunks per wavefront and step, loaded together
     __shared__ long long slot[BUF ? 1 : Qp];
     __shared__ unsigned int smin[W * kClaimStride];  // smallest entry per query (index into in_sub)
     __shared__ PredQueue queue[16];
-    __shared__ unsigned long long srem[16], slevel[16];
+    __shared__ unsigned long long srem[W], slevel[W];
     long long row_i = blockIdx.x;
     uint32_t seg = 0;
     if (SEG) {  // the giant row this segment belongs to: last row whose first segment is <= blockIdx.x
@@ -1559,8 +1573,7 @@ __global__ void __launch_bounds__(1024) k_pred_row(FillArgs a, long long first_r
     // gridDim.y > 1: one block per (row, hop level), so the levels of a long row run side by side
     const int h_first = gridDim.y > 1 ? (int)blockIdx.y + 1 : 1, h_last = gridDim.y > 1 ? h_first : a.k;
     if (gridDim.y > 1) {  // nothing of this level in the row's entity: leave before the list positions
-        const unsigned long long x =
-            lw < W ? a.levels[(size_t)h_first * a.plane + (size_t)ev * W + lw] & range_bits(a.q0, a.q1, lw) : 0ull;
+        const unsigned long long x = a.levels[(size_t)h_first * a.plane + (size_t)ev * W + lw] & range_bits(a.q0, a.q1, lw);
         if (!wave_any(x != 0) || ((a.push_levels >> h_first) & 1u)) return;  // the same words in every wavefront
     }
     if (!BUF) row_slots<W>(a, ev, wave, nw, slot);
@@ -1571,9 +1584,8 @@ __global__ void __launch_bounds__(1024) k_pred_row(FillArgs a, long long first_r
     long long n_rows = 0, n_edges = 0, n_lines = 0;
     for (int h = h_first; h <= h_last; ++h) {
         __syncthreads();
-        if (t < 16) {
-            unsigned long long x =
-                t < W ? a.levels[(size_t)h * a.plane + (size_t)ev * W + t] & range_bits(a.q0, a.q1, t) : 0ull;
+        if (t < W) {
+            const unsigned long long x = a.levels[(size_t)h * a.plane + (size_t)ev * W + t] & range_bits(a.q0, a.q1, t);
             srem[t] = x;
             slevel[t] = x;
         }
@@ -1613,7 +1625,7 @@ __global__ void __launch_bounds__(1024) k_pred_row(FillArgs a, long long first_r
             for (int c = 0; c < C; ++c) {
                 uint32_t j0 = w0 + 64u * nw * c;
                 if (j0 < step_hi && wave_any(rem != 0)) {
-                    n_lines += pred_resolve_unordered<W, MASK>(sj[c], rj[c], cj[c], a, prev, queue[wave], rem,
+                    n_lines += pred_resolve_unordered<MASK>(sj[c], rj[c], cj[c], a, prev, queue[wave], rem,
                                                                [&](unsigned long long hit, int at) {
                         claim(&smin[lw * kClaimStride], hit, j0 + (uint32_t)at);
                     });
@@ -1745,7 +1757,7 @@ static logoskg_status count_plane(logoskg_result *r, const unsigned long long *p
         switch (W) {
             case 1: k_count_narrow<1><<<grid, dim3(64 * kSuperTiles), 0, st>>>(plane_bits, ntiles, g->E, r->tile_ent, r->d_nact, *tile_base, *super_base); break;
             case 4: k_count_narrow<4><<<grid, dim3(64 * kSuperTiles), 0, st>>>(plane_bits, ntiles, g->E, r->tile_ent, r->d_nact, *tile_base, *super_base); break;
-            default: k_count<16><<<grid, block, 0, st>>>(plane_bits, ntiles, g->E, r->tile_ent, r->d_nact, *tile_base, *super_base); break;
+            default: k_count<<<grid, block, 0, st>>>(plane_bits, ntiles, g->E, r->tile_ent, r->d_nact, *tile_base, *super_base); break;
         }
     }
     {
@@ -1947,8 +1959,8 @@ static void launch_rows(Profiler &prof, const FillArgs &a, long long n_hub_rows,
             if (a.row_pred) k_narrow_wave<W, N, MASK, STATS, true><<<grid, block, 0, st>>>(a, n_hub_rows, n_other_rows);
             else k_narrow_wave<W, N, MASK, STATS, false><<<grid, block, 0, st>>>(a, n_hub_rows, n_other_rows);
         } else {
-            if (a.row_pred) k_pred_wave<W, MASK, STATS, true><<<grid, block, 0, st>>>(a, n_hub_rows, n_other_rows);
-            else k_pred_wave<W, MASK, STATS, false><<<grid, block, 0, st>>>(a, n_hub_rows, n_other_rows);
+            if (a.row_pred) k_pred_wave<MASK, STATS, true><<<grid, block, 0, st>>>(a, n_hub_rows, n_other_rows);
+            else k_pred_wave<MASK, STATS, false><<<grid, block, 0, st>>>(a, n_hub_rows, n_other_rows);
         }
     }
     if (n_hub_rows <= 0) return;
@@ -1963,8 +1975,8 @@ static void launch_rows(Profiler &prof, const FillArgs &a, long long n_hub_rows,
             if (x.row_pred) k_narrow_row<W, N, MASK, STATS, true, false><<<grid, block, 0, st_hub>>>(x, first);
             else k_narrow_row<W, N, MASK, STATS, false, false><<<grid, block, 0, st_hub>>>(x, first);
         } else {
-            if (x.row_pred) k_pred_row<W, MASK, STATS, true, false><<<grid, block, 0, st_hub>>>(x, first);
-            else k_pred_row<W, MASK, STATS, false, false><<<grid, block, 0, st_hub>>>(x, first);
+            if (x.row_pred) k_pred_row<MASK, STATS, true, false><<<grid, block, 0, st_hub>>>(x, first);
+            else k_pred_row<MASK, STATS, false, false><<<grid, block, 0, st_hub>>>(x, first);
         }
     };
     if (giants > 0) {
@@ -1982,7 +1994,7 @@ static void launch_rows(Profiler &prof, const FillArgs &a, long long n_hub_rows,
                 b.row_pred, giants * Qp_of<W>(), INT_MAX);
             const dim3 grid((unsigned)a.n_giant_segs, levels), block(1024);
             if constexpr (N > 0) k_narrow_row<W, N, MASK, STATS, true, true><<<grid, block, 0, st_hub>>>(b, 0);
-            else k_pred_row<W, MASK, STATS, true, true><<<grid, block, 0, st_hub>>>(b, 0);
+            else k_pred_row<MASK, STATS, true, true><<<grid, block, 0, st_hub>>>(b, 0);
         } else {
             rows(a, 0, giants, 1024);
         }
@@ -2120,7 +2132,7 @@ static void launch_pred_wms(Profiler &prof, const FillArgs &a0, long long n_hub_
             const long long blocks = (a.tile_count * W + 3) / 4;
             k_pred_narrow<W, MASK, STATS><<<dim3((unsigned)((blocks + 7) / 8 * 8)), dim3(256), 0, st_tiles>>>(a);
         } else {
-            k_pred<W, MASK, STATS><<<dim3((unsigned)((a.tile_count + 7) / 8 * 8)), dim3(64 * W), 0, st_tiles>>>(a);
+            k_pred<MASK, STATS><<<dim3((unsigned)((a.tile_count + 7) / 8 * 8)), dim3(64 * W), 0, st_tiles>>>(a);
         }
     }
     if (packed) {

@@ -15,8 +15,8 @@
 // costs the triples of the search and not the object rows of what it reached - one reached hub has
 // 10^5 entries in its object row.
 //
-// One question, two hops, 10,000 entities: 30 launches and 4 read-backs, 242 us with the lists; now 3
-// launches and one read-back, 113 us.  64 questions: 306 -> 82 us (k_small_search 17 .. 42 us, a chain of
+// One question, two hops, 10,000 entities: 30 launches and 4 read-backs, 216 .. 242 us with the lists; now 3
+// launches and one read-back, 55 us.  64 questions: 306 .. 322 -> 77 us (k_small_search 17 .. 42 us, a chain of
 // dependent reads per hop; k_small_fetch 5 .. 16 us; the rest is the binding and the read-back).
 #include <algorithm>
 #include <climits>

@@ -55,7 +55,7 @@ def captured_fetch(res, arena, q0, q1):
 
 
 @pytest.mark.parametrize("masked", [False, True])
-@pytest.mark.parametrize("Q, overlap", [(40, False), (200, False), (200, True)])
+@pytest.mark.parametrize("Q, overlap", [(40, False), (40, True), (200, False), (200, True)])
 def test_giant_rows_on_narrow_planes(Q, overlap, masked, monkeypatch):
     import paper_2604_18913_amd as lkg
     if overlap:
