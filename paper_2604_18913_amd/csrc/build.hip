@@ -312,6 +312,7 @@ extern "C" logoskg_status logoskg_build(const int32_t *subj, const int32_t *rel,
             g->in_rows.n_seg = (int64_t)seg.size();
             g->in_rows.n_multi = (int64_t)multi.size();
             g->in_rows.n_long = (int64_t)longer.size();
+            if (!longer.empty()) g->in_rows.longest = ioff[(size_t)longer[0] + 1] - ioff[longer[0]];
             LKG_TRY(upload(&g->in_rows.tail, tail, &g->static_bytes));
             LKG_TRY(upload(&g->in_rows.seg, seg, &g->static_bytes));
             LKG_TRY(upload(&g->in_rows.multi, multi, &g->static_bytes));

@@ -142,6 +142,7 @@ struct RowClasses {             // device work lists over the object rows, split
                                   // (per streamed chunk when sharded); the first n_hub of them
                                   // have >= hub_min entries
     int64_t n_tail = 0, n_seg = 0, n_multi = 0, n_hub = 0, n_long = 0;
+    uint32_t longest = 0;  // entries of the longest row if it has more than kTailMaxDegree (of a graph's in_rows)
     int64_t n_giant = 0;  // the first n_giant long rows have >= kGiantRowMin entries
     uint32_t *giant_seg_first = nullptr;  // [n_giant + 1] segments of kGiantSegment entries before every giant row
     int64_t n_giant_segs = 0;

@@ -41,9 +41,9 @@ struct PathArgs {
     int32_t *path_count, *path_edges;
 };
 
-// Wavefronts per pair: 16 up to kPathWidePairs pairs, 4 up to kPathNarrowPairs, then one.  What counts are the scans of
-// long rows: few pairs need many wavefronts each to fill the GPU, many pairs fill it by themselves.  us for 16 paths
-// each on a 30M-triple graph (k = 3 with whitelists; without):
+// Wavefronts per pair on graphs with rows longer than kPathShortRow: 16 up to kPathWidePairs pairs, 4 up to
+// kPathNarrowPairs, then one.  What counts are the scans of long rows: few pairs need many wavefronts each to fill the
+// GPU, many pairs fill it by themselves.  us for 16 paths each on a 30M-triple graph (k = 3 with whitelists; without):
 //    pairs     16 wavefronts       4               1
 //       64       749     250      982     172     3,161     449
 //      256     1,777     614    2,262     753     6,769   2,344
@@ -60,6 +60,122 @@ constexpr int kPathSeeds = 64;    // queries with more seeds than this keep to t
 constexpr int kPathRelations = 2048; // up to so many relations the query's whitelist is held in LDS
 constexpr int kPathMatches = 256; // triples from the seeds into one entity that are sorted in LDS
 constexpr uint32_t kPathShortRow = 128;  // what is left of a row up to this length: one wavefront, two entries per lane
+
+// Triples of the pair's paths: -1 = none, 0 = the target is a seed.
+__device__ __forceinline__ int path_length(const PathArgs &a, long long i, int v, int w, unsigned long long bit) {
+    if (a.length) {  // walks of exactly that many triples: the target has to sit in that level
+        const int want = a.length[i];
+        return want >= 0 && want <= a.k && (a.levels[(size_t)want * a.plane + (size_t)v * a.W + w] & bit) ? want : -1;
+    }
+    for (int h0 = 0; h0 <= a.k; h0 += 64) {  // shortest paths: the first level that holds the target, 64 levels at a time
+        const int h = h0 + lane();
+        const unsigned long long m = __ballot(h <= a.k && (a.levels[(size_t)min(h, a.k) * a.plane + (size_t)v * a.W + w] & bit));
+        if (m) return h0 + __builtin_ctzll(m);
+    }
+    return -1;
+}
+
+// writes path number `at`: the edges chosen at levels d .. 2, and `eid` in front of them
+__device__ __forceinline__ void write_path(int32_t *out, int k, int d, const int32_t *se, int at, int32_t eid) {
+    int32_t *row = out + (size_t)at * k;
+    row[0] = eid;
+    for (int x = 2; x <= d; ++x) row[x - 1] = se[x];
+}
+
+// The search from entry j of vertex x's row at level lev on by one wavefront alone, until it is over or the next row is a
+// long one: subject, relation and triple index of two entries per lane are requested together, then the subjects' level
+// words.  The stacks hold every entry but the current one (x, j) while this runs; n = paths found.
+template <typename Allowed>
+__device__ __forceinline__ void path_short_rows(const PathArgs &a, int w, unsigned long long bit, int d, int32_t *out,
+                                                int32_t *sv, uint32_t *sp, int32_t *se, Allowed allowed, int x, uint32_t j,
+                                                uint32_t hi, int &lev, int &n) {
+    const int k = a.k, W = a.W, max_paths = a.max_paths;
+    while (true) {
+        if (hi - j > kPathShortRow) break;
+        const unsigned long long *lv = a.levels + (size_t)(lev - 1) * a.plane;
+        const uint32_t at0 = j + (uint32_t)lane(), at1 = at0 + 64u;
+        const bool in0 = at0 < hi, in1 = at1 < hi;
+        const int32_t s0 = in0 ? a.in_sub[at0] : 0, s1 = in1 ? a.in_sub[at1] : 0;
+        const int32_t e0 = in0 ? a.in_eid[at0] : 0, e1 = in1 ? a.in_eid[at1] : 0;
+        int r0 = 0, r1 = 0;
+        if (a.allow) {
+            r0 = in0 ? a.in_rel[at0] : 0;
+            r1 = in1 ? a.in_rel[at1] : 0;
+        }
+        const unsigned long long w0 = in0 ? lv[(size_t)s0 * W + w] : 0ull, w1 = in1 ? lv[(size_t)s1 * W + w] : 0ull;
+        bool ok0 = (w0 & bit) != 0ull, ok1 = (w1 & bit) != 0ull;
+        if (a.allow) {
+            ok0 &= allowed(r0);
+            ok1 &= allowed(r1);
+        }
+        const unsigned long long m0 = __ballot(ok0), m1 = __ballot(ok1);
+        if (lev == 1) {  // every admissible entry ends a path
+            if (d > 8) {  // long paths: one after the other, their entries by all lanes
+                for (int half = 0, at = n; half < 2; ++half)
+                    for (unsigned long long m = half ? m1 : m0; m && at < max_paths; m &= m - 1, ++at) {
+                        const int32_t eid = __shfl(half ? e1 : e0, __builtin_ctzll(m));
+                        int32_t *row = out + (size_t)at * k;
+                        for (int x = lane(); x < d; x += 64) row[x] = x ? se[x + 1] : eid;
+                    }
+            } else {
+                const unsigned long long below = (1ull << lane()) - 1ull;
+                const int p0 = n + __popcll(m0 & below), p1 = n + __popcll(m0) + __popcll(m1 & below);
+                if (ok0 && p0 < max_paths) write_path(out, k, d, se, p0, e0);
+                if (ok1 && p1 < max_paths) write_path(out, k, d, se, p1, e1);
+            }
+            n = min(max_paths, n + __popcll(m0) + __popcll(m1));
+        } else if (m0 | m1) {  // the first one is descended into
+            const int f = m0 ? __builtin_ctzll(m0) : __builtin_ctzll(m1);
+            const int32_t sf = __shfl(m0 ? s0 : s1, f), ef = __shfl(m0 ? e0 : e1, f);
+            se[lev] = ef;  // (all lanes write the same)
+            sv[lev] = x;
+            sp[lev] = j + (m0 ? 0u : 64u) + (uint32_t)f + 1u;
+            --lev;
+            x = sf;
+            j = a.in_off[sf];
+            hi = a.in_off[sf + 1];
+            continue;
+        }
+        // this vertex's row is exhausted: back to the vertex after it
+        ++lev;
+        if (lev > d || n >= max_paths) break;
+        x = sv[lev];
+        j = sp[lev];
+        hi = a.in_off[x + 1];
+    }
+    if (lev <= d) {
+        sv[lev] = x;
+        sp[lev] = j;
+    }
+}
+
+// A graph whose object rows are all short: a wavefront per pair, four pairs per block, nothing shared between them.
+// What bounds it is the chain of gathers down a path and, with many pairs, the rows of -1 that are written first (80,000
+// pairs on 50,000 entities and 250,000 triples, 16 paths of up to four triples: 20 MB in 89 us; 113 us with a block of
+// one wavefront for every pair).
+__global__ void __launch_bounds__(256) k_paths_short(PathArgs a, long long n_pairs) {
+    __shared__ int32_t sv_all[4][LOGOSKG_MAX_K + 1], se_all[4][LOGOSKG_MAX_K + 1];
+    __shared__ uint32_t sp_all[4][LOGOSKG_MAX_K + 1];
+    const int wave = threadIdx.x >> 6;
+    const long long i = a.first_pair + (long long)blockIdx.x * 4 + wave;
+    if (i >= n_pairs) return;  // wavefront-uniform
+    int32_t *out = a.path_edges + (size_t)i * a.max_paths * a.k;
+    for (long long x = lane(); x < (long long)a.max_paths * a.k; x += 64) out[x] = -1;
+    const int q = a.query_idx[i], v = a.target[i];
+    int n = 0;
+    if ((uint32_t)q < (uint32_t)a.Q && (uint32_t)v < (uint32_t)a.E) {
+        const int w = q >> 6;
+        const unsigned long long bit = 1ull << (q & 63);
+        const int d = path_length(a, i, v, w, bit);
+        if (d == 0) n = 1;  // a seed: one empty path
+        auto allowed = [&](int r) -> bool { return (a.allow[(size_t)r * a.W + w] & bit) != 0ull; };
+        int lev = d;
+        if (d > 0)
+            path_short_rows(a, w, bit, d, out, sv_all[wave], sp_all[wave], se_all[wave], allowed, v, a.in_off[v],
+                            a.in_off[v + 1], lev, n);
+    }
+    if (lane() == 0) a.path_count[i] = n;
+}
 
 // NW wavefronts (one block) per (query, target) pair.  The depth-first state - per level the vertex,
 // the next row position and the chosen edge - is block-uniform and lives in LDS (k <= 254).
@@ -107,17 +223,7 @@ __global__ void __launch_bounds__(64 * NW) k_paths(PathArgs a) {
     }
     const int w = q >> 6;
     const unsigned long long bit = 1ull << (q & 63);
-    int d = -1;
-    if (a.length) {  // walks of exactly that many triples: the target has to sit in that level
-        const int want = a.length[i];
-        if (want >= 0 && want <= k && (a.levels[(size_t)want * a.plane + (size_t)v * W + w] & bit)) d = want;
-    } else {         // shortest paths: the first level that holds the target, 64 levels at a time
-        for (int h0 = 0; h0 <= k && d < 0; h0 += 64) {
-            const int h = h0 + lane();
-            const unsigned long long m = __ballot(h <= k && (a.levels[(size_t)min(h, k) * a.plane + (size_t)v * W + w] & bit));
-            if (m) d = h0 + __builtin_ctzll(m);
-        }
-    }
+    const int d = path_length(a, i, v, w, bit);
     if (d <= 0) {  // not reached: no path; a seed: one empty path
         if (t == 0) a.path_count[i] = d == 0 ? 1 : 0;
         return;
@@ -144,83 +250,18 @@ __global__ void __launch_bounds__(64 * NW) k_paths(PathArgs a) {
         sp[d] = a.in_off[v];
     }
     __syncthreads();
-    // writes path number `at`: the edges chosen at levels d .. 2, and `eid` in front of them
-    auto write_path = [&](int at, int32_t eid) {
-        int32_t *row = out + (size_t)at * k;
-        row[0] = eid;
-        for (int x = 2; x <= d; ++x) row[x - 1] = se[x];
-    };
-    // The search from entry j of vertex x's row on by one wavefront alone, until it is over or the next row is a long one:
-    // subject, relation and triple index of two entries per lane are requested together, then the subjects' level words.
-    // The stacks hold every entry but the current one (x, j) while this runs.
-    auto short_rows = [&](int x, uint32_t j, uint32_t hi, int lev, int n) {
-        while (true) {
-            if (hi - j > kPathShortRow) break;
-            const unsigned long long *lv = a.levels + (size_t)(lev - 1) * a.plane;
-            const uint32_t at0 = j + (uint32_t)lane(), at1 = at0 + 64u;
-            const bool in0 = at0 < hi, in1 = at1 < hi;
-            const int32_t s0 = in0 ? a.in_sub[at0] : 0, s1 = in1 ? a.in_sub[at1] : 0;
-            const int32_t e0 = in0 ? a.in_eid[at0] : 0, e1 = in1 ? a.in_eid[at1] : 0;
-            int r0 = 0, r1 = 0;
-            if (a.allow) {
-                r0 = in0 ? a.in_rel[at0] : 0;
-                r1 = in1 ? a.in_rel[at1] : 0;
-            }
-            const unsigned long long w0 = in0 ? lv[(size_t)s0 * W + w] : 0ull, w1 = in1 ? lv[(size_t)s1 * W + w] : 0ull;
-            bool ok0 = (w0 & bit) != 0ull, ok1 = (w1 & bit) != 0ull;
-            if (a.allow) {
-                ok0 &= allowed(r0);
-                ok1 &= allowed(r1);
-            }
-            const unsigned long long m0 = __ballot(ok0), m1 = __ballot(ok1);
-            if (lev == 1) {  // every admissible entry ends a path
-                if (d > 8) {  // long paths: one after the other, their entries by all lanes
-                    for (int half = 0, at = n; half < 2; ++half)
-                        for (unsigned long long m = half ? m1 : m0; m && at < max_paths; m &= m - 1, ++at) {
-                            const int32_t eid = __shfl(half ? e1 : e0, __builtin_ctzll(m));
-                            int32_t *row = out + (size_t)at * k;
-                            for (int x = lane(); x < d; x += 64) row[x] = x ? se[x + 1] : eid;
-                        }
-                } else {
-                    const unsigned long long below = (1ull << lane()) - 1ull;
-                    const int p0 = n + __popcll(m0 & below), p1 = n + __popcll(m0) + __popcll(m1 & below);
-                    if (ok0 && p0 < max_paths) write_path(p0, e0);
-                    if (ok1 && p1 < max_paths) write_path(p1, e1);
-                }
-                n = min(max_paths, n + __popcll(m0) + __popcll(m1));
-            } else if (m0 | m1) {  // the first one is descended into
-                const int f = m0 ? __builtin_ctzll(m0) : __builtin_ctzll(m1);
-                const int32_t sf = __shfl(m0 ? s0 : s1, f), ef = __shfl(m0 ? e0 : e1, f);
-                se[lev] = ef;  // (all lanes write the same)
-                sv[lev] = x;
-                sp[lev] = j + (m0 ? 0u : 64u) + (uint32_t)f + 1u;
-                --lev;
-                x = sf;
-                j = a.in_off[sf];
-                hi = a.in_off[sf + 1];
-                continue;
-            }
-            // this vertex's row is exhausted: back to the vertex after it
-            ++lev;
-            if (lev > d || n >= max_paths) break;
-            x = sv[lev];
-            j = sp[lev];
-            hi = a.in_off[x + 1];
-        }
-        if (lev <= d) {
-            sv[lev] = x;
-            sp[lev] = j;
-        }
-        s_l = lev;
-        s_found = n;
-    };
     while (l <= d && found < max_paths) {  // (all wavefronts have the same l and found)
         const int x = sv[l];
         uint32_t j = sp[l];
         const uint32_t hi = a.in_off[x + 1];
         if (hi - j <= kPathShortRow) {
             __syncthreads();  // (the last reads of the stacks)
-            if (wave == 0) short_rows(x, j, hi, l, found);
+            if (wave == 0) {
+                int lev = l, n = found;
+                path_short_rows(a, w, bit, d, out, sv, sp, se, allowed, x, j, hi, lev, n);
+                s_l = lev;  // (all lanes write the same)
+                s_found = n;
+            }
             __syncthreads();
             l = s_l;
             found = s_found;
@@ -274,7 +315,7 @@ __global__ void __launch_bounds__(64 * NW) k_paths(PathArgs a) {
                     const int32_t eid = match[m];
                     int rank = 0;
                     for (int y = 0; y < n; ++y) rank += match[y] < eid;
-                    if (found + rank < max_paths) write_path(found + rank, eid);
+                    if (found + rank < max_paths) write_path(out, k, d, se, found + rank, eid);
                 }
                 found = min(max_paths, found + n);
                 ++l;
@@ -326,7 +367,7 @@ __global__ void __launch_bounds__(64 * NW) k_paths(PathArgs a) {
                     }
                     if (ok[u]) {
                         at += __popcll(mine[u] & ((1ull << lane()) - 1ull));
-                        if (at < max_paths) write_path(at, a.in_eid[j + (uint32_t)(u * NT + t)]);
+                        if (at < max_paths) write_path(out, k, d, se, at, a.in_eid[j + (uint32_t)(u * NT + t)]);
                     }
                 }
                 found = min(max_paths, before);
@@ -391,11 +432,16 @@ static logoskg_status launch_paths(logoskg_graph *g, const logoskg_result *r, co
     a.query_idx = query_idx; a.target = target; a.length = length;
     a.max_paths = max_paths; a.path_count = path_count; a.path_edges = path_edges;
     ProfScope ps(g->prof, KK_PATHS, st);
+    // A graph without a row for the whole block: k_paths_short, whatever the pairs' number (10,000 pairs on that graph, whose
+    // rows have up to 14 entries: 61 us with four wavefronts per pair, of which three wait, 38 with one, 35 with four pairs
+    // to a block).
+    const bool short_rows = g->in_rows.longest <= kPathShortRow;
     // (a launch takes fewer than 2^32 threads)
     for (int64_t first = 0; first < n_pairs; first += 1ll << 25) {
         const dim3 grid((unsigned)std::min<int64_t>(n_pairs - first, 1ll << 25));
         a.first_pair = first;
-        if (n_pairs <= kPathWidePairs) k_paths<16><<<grid, dim3(1024), 0, st>>>(a);
+        if (short_rows) k_paths_short<<<dim3((grid.x + 3) / 4), dim3(256), 0, st>>>(a, n_pairs);
+        else if (n_pairs <= kPathWidePairs) k_paths<16><<<grid, dim3(1024), 0, st>>>(a);
         else if (n_pairs <= kPathNarrowPairs) k_paths<4><<<grid, dim3(256), 0, st>>>(a);
         else k_paths<1><<<grid, dim3(64), 0, st>>>(a);
     }

@@ -418,6 +418,7 @@ static logoskg_status build_in_chunks(logoskg_graph *g, ShardSet *ss, const int3
         g->static_bytes += first.size() * sizeof(uint32_t);
     }
     g->in_rows.n_long = (int64_t)longrows.size();
+    for (int32_t v : longrows) g->in_rows.longest = std::max(g->in_rows.longest, ioff[(size_t)v + 1] - ioff[v]);
     LKG_HIP(hipMalloc((void **)&g->in_rows.longrows, std::max<size_t>(longrows.size(), 1) * sizeof(int32_t)));
     if (!longrows.empty())
         LKG_HIP(hipMemcpy(g->in_rows.longrows, longrows.data(), longrows.size() * sizeof(int32_t),

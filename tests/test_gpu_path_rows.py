@@ -86,3 +86,45 @@ def test_whitelist_in_lds_and_gathered(R):
     assert np.array_equal(edges.cpu().numpy(), edges_o)
     res.close()
     g.close()
+
+
+@pytest.mark.parametrize("longest", [20, 127, 128, 129])  # up to 128 entries every pair is one wavefront's, four to a block
+@pytest.mark.parametrize("shards", [1, 3])
+@pytest.mark.parametrize("share", [None, 0.5])
+def test_graphs_of_short_rows(longest, shards, share):
+    import paper_2604_18913_amd as lkg
+    rng = np.random.default_rng(longest)
+    E, R, Q, k = 400, 70, 70, 4
+    o = np.concatenate([np.repeat([0, 1], [longest, max(longest - 64, 1)]),
+                        np.repeat(np.arange(2, E), rng.integers(0, 16, E - 2))]).astype(np.int32)
+    s = rng.integers(0, E, o.shape[0]).astype(np.int32)
+    r = rng.integers(0, R, o.shape[0]).astype(np.int32)
+    perm = rng.permutation(o.shape[0])
+    s, r, o = s[perm], r[perm], o[perm]
+    off = np.arange(0, 3 * Q + 1, 3).astype(np.int64)
+    seeds = rng.integers(0, E, 3 * Q).astype(np.int32)
+    mask = None
+    if share is not None:
+        keep = rng.random((Q, R)) < share
+        mask = np.zeros((Q, 2), np.uint64)
+        for w in range(R):
+            mask[:, w // 64] |= keep[:, w].astype(np.uint64) << np.uint64(w % 64)
+    g = lkg.Graph(s, r, o, E, R, num_shards=shards)
+    res = g.khop(off, seeds, k, mask)
+    ent, _, _ = res.fetch()
+    pq, pt = kggen.sample_reached_pairs(5, res.offsets(), ent.cpu().numpy(), 1200)
+    pq = np.concatenate([pq, np.arange(Q), np.arange(Q), rng.integers(0, Q, 60), [-1, Q, 0, 0]]).astype(np.int32)
+    pt = np.concatenate([pt, np.zeros(Q), np.ones(Q), rng.integers(0, E, 60), [0, 0, -1, E]]).astype(np.int32)
+    inside = slice(0, len(pq) - 4)  # (the last four lie outside the batch or the graph: no paths)
+    for max_paths in (1, 16):
+        cnt_o, edges_o = oracle.paths(E, s, r, o, off, seeds, k, pq[inside], pt[inside], max_paths, mask)
+        assert cnt_o.max() == max_paths or share is not None
+        cnt_o = np.concatenate([cnt_o, np.zeros(4, cnt_o.dtype)])
+        edges_o = np.concatenate([edges_o, np.full((4, max_paths, k), -1, edges_o.dtype)])
+        for n in (1, 2, 3, 5, len(pq)):
+            at = len(pq) - n + np.arange(n)
+            cnt, edges = g.paths(res, pq[at], pt[at], max_paths)
+            assert np.array_equal(cnt.cpu().numpy(), cnt_o[at])
+            assert np.array_equal(edges.cpu().numpy().reshape(edges_o[at].shape), edges_o[at])
+    res.close()
+    g.close()
