@@ -400,7 +400,7 @@ extern "C" logoskg_status logoskg_build(const int32_t *subj, const int32_t *rel,
     g->fr_seg_cap = (int64_t)E + T / kPushSegment + 64;  // every long row adds < deg/segment + 1 items
     if ((st = dev_alloc((void **)&g->fr_tail, (size_t)E * sizeof(int32_t))) != LOGOSKG_OK) return fail(st);
     if ((st = dev_alloc((void **)&g->fr_seg, (size_t)g->fr_seg_cap * sizeof(RowSegment))) != LOGOSKG_OK) return fail(st);
-    if ((st = dev_alloc((void **)&g->d_ctr, (C_TOTAL + 3 * kCensusBlocks) * sizeof(unsigned long long))) != LOGOSKG_OK) return fail(st);
+    if ((st = dev_alloc((void **)&g->d_ctr, (C_TOTAL + kCensusWords * kCensusBlocks) * sizeof(unsigned long long))) != LOGOSKG_OK) return fail(st);
     constexpr size_t ctr_bytes = (C_TOTAL + 1) * sizeof(unsigned long long), off_bytes = (LOGOSKG_MAX_QUERIES + 1) * sizeof(long long);
     static_assert(alignof(SmallReport) <= 8, "it lies behind 8-byte words");
     if (hipHostMalloc((void **)&g->h_ctr, ctr_bytes + off_bytes + sizeof(SmallReport), hipHostMallocDefault) != hipSuccess) {

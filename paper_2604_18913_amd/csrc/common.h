@@ -86,7 +86,8 @@ private:
 
 // ---------------------------------------------------------------- graph
 constexpr int kLevelCounters = 4;
-constexpr unsigned kCensusBlocks = 512;  // at most; three words each behind d_ctr's C_TOTAL
+constexpr unsigned kCensusBlocks = 512;  // at most; kCensusWords each behind d_ctr's C_TOTAL
+constexpr unsigned kCensusWords = 7;     // three sums, and up to four live words
 constexpr int kTailMaxDegree = 32;      // rows up to this degree: one W-lane group per row
 constexpr int kPullSegment = 1024;      // longer object rows are cut into segments of this many
                                         // entries, one wavefront each

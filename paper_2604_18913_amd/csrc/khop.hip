@@ -118,76 +118,170 @@ __device__ __forceinline__ unsigned segments_of(uint32_t d) {
     return d > (uint32_t)kTailMaxDegree ? (d + kPushSegment - 1) / kPushSegment : 0u;
 }
 
-__global__ void __launch_bounds__(1024)
-k_census(const uint32_t *__restrict__ act, int32_t E, const uint32_t *__restrict__ out_off, unsigned long long *ctr,
-         unsigned long long *sums, unsigned long long *host) {
-    __shared__ unsigned long long part[16][3];
-    unsigned long long lists = 0, rows = 0, edges = 0;  // short rows | segments << 32, rows | active entities << 32
-    const long long stride = (long long)gridDim.x * 1024 * kCensusEntities;
-    for (long long e0 = ((long long)blockIdx.x * 1024 + threadIdx.x) * kCensusEntities; e0 < E; e0 += stride) {
-        uint32_t d[kCensusEntities];
-        const unsigned bits = census_degrees(act, E, out_off, e0, d);
-        if (!bits) continue;
+// The OR over the 64 lanes of a wavefront of x[0 .. W - 1], word by word: lane l returns word own_word<W>(l).  Four
+// words are split between the quarters of the wavefront first (seven exchanges instead of 24).
+template <int W>
+__device__ __forceinline__ int own_word() { return W == 1 ? 0 : lane() >> 4; }
+
+template <int W>
+__device__ __forceinline__ unsigned long long wave_or_words(const unsigned long long (&x)[W]) {
+    static_assert(W == 1 || W == 4, "narrow planes");
+    unsigned long long r = x[0];
+    if constexpr (W == 4) {
+        const bool hi = lane() & 32, odd = lane() & 16;
+        const unsigned long long a = (hi ? x[2] : x[0]) | shfl_xor64(hi ? x[0] : x[2], 32);
+        const unsigned long long b = (hi ? x[3] : x[1]) | shfl_xor64(hi ? x[1] : x[3], 32);
+        r = (odd ? b : a) | shfl_xor64(odd ? a : b, 16);
+    }
 #pragma unroll
-        for (int i = 0; i < kCensusEntities; ++i) {
-            lists += (unsigned long long)(d[i] > 0 && d[i] <= (uint32_t)kTailMaxDegree) | ((unsigned long long)segments_of(d[i]) << 32);
-            rows += d[i] > 0;
-            edges += d[i];
+    for (int m = W == 1 ? 32 : 8; m >= 1; m >>= 1) r |= shfl_xor64(r, m);
+    return r;
+}
+
+template <int W>
+__device__ __forceinline__ void load_line(unsigned long long (&x)[W], const unsigned long long *__restrict__ p) {
+    if constexpr (W == 1) {
+        x[0] = *p;
+    } else {
+#pragma unroll
+        for (int i = 0; i < W; i += 2) {
+            const ulonglong2 y = *reinterpret_cast<const ulonglong2 *>(p + i);
+            x[i] = y.x;
+            x[i + 1] = y.y;
         }
-        rows += (unsigned long long)__popc(bits) << 32;
     }
-    lists = (unsigned long long)wave_sum((long long)lists);
-    rows = (unsigned long long)wave_sum((long long)rows);
-    edges = (unsigned long long)wave_sum((long long)edges);
+}
+
+// Planes of one and four words (LW > 0): the same pass collects the level's live words (see k_live) from the lines of the
+// active rows.  A launch of its own for them was 6 us per pulled hop; without them a row could not stop early where
+// some queries of the batch have nothing left to expand.  Behind a pulled hop (PULLED) the pass reads the level's lines
+// in order, lane = entity, and makes the bitmap from them: set by the pull kernels, a bit was an atomic per row, and they
+// were half of a hop's time on 407,000 entities.
+template <int LW, bool PULLED>
+__global__ void __launch_bounds__(LW ? 512 : 1024)
+k_census(uint32_t *act, int32_t E, const uint32_t *__restrict__ out_off, unsigned long long *ctr,
+         unsigned long long *sums, unsigned long long *host, const unsigned long long *__restrict__ lines,
+         unsigned long long *live) {
+    static_assert(!PULLED || LW > 0, "16-word lines are not read for their bits");
+    constexpr int NT = LW ? 512 : 1024, NS = 3 + LW;  // threads, words per block
+    constexpr int G = 4;                              // PULLED: entities per lane
+    __shared__ unsigned long long part[NT / 64][NS];
+    unsigned long long lists = 0, rows = 0, edges = 0;  // short rows | segments << 32, rows | active entities << 32
+    unsigned long long lv[LW > 0 ? LW : 1] = {};
     const int wave = threadIdx.x >> 6;
-    if (lane() == 0) {
-        part[wave][0] = lists;
-        part[wave][1] = rows;
-        part[wave][2] = edges;
+    auto add = [&](uint32_t d) {
+        lists += (unsigned long long)(d > 0 && d <= (uint32_t)kTailMaxDegree) | ((unsigned long long)segments_of(d) << 32);
+        rows += d > 0;
+        edges += d;
+    };
+    if constexpr (PULLED) {
+        const long long stride = (long long)gridDim.x * NT * G;
+        for (long long base = ((long long)blockIdx.x * NT + 64 * wave) * G; base < E; base += stride) {  // wavefront-uniform
+            unsigned long long x[G][LW];
+            uint32_t a[G], b[G];
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const long long e = base + 64 * g + lane();
+                a[g] = b[g] = 0;
+#pragma unroll
+                for (int w = 0; w < LW; ++w) x[g][w] = 0;
+                if (e < E) {
+                    load_line<LW>(x[g], lines + (size_t)e * LW);
+                    a[g] = out_off[e];
+                    b[g] = out_off[e + 1];
+                }
+            }
+            unsigned long long mine = 0;
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                unsigned long long any = x[g][0];
+#pragma unroll
+                for (int w = 1; w < LW; ++w) any |= x[g][w];
+                const unsigned long long m = __ballot(any != 0);
+                if (lane() == g) mine = m;
+                rows += (unsigned long long)(any != 0) << 32;
+                if (any != 0 && b[g] > a[g]) {
+                    add(b[g] - a[g]);
+#pragma unroll
+                    for (int w = 0; w < LW; ++w) lv[w] |= x[g][w];
+                }
+            }
+            // (the bitmap covers E rounded up to a multiple of 64 entities)
+            if (lane() < G && base + 64 * lane() < E) *reinterpret_cast<unsigned long long *>(act + base / 32 + 2 * lane()) = mine;
+        }
+    } else {
+        const long long stride = (long long)gridDim.x * NT * kCensusEntities;
+        for (long long e0 = ((long long)blockIdx.x * NT + threadIdx.x) * kCensusEntities; e0 < E; e0 += stride) {
+            uint32_t d[kCensusEntities];
+            const unsigned bits = census_degrees(act, E, out_off, e0, d);
+            if (!bits) continue;
+#pragma unroll
+            for (int i = 0; i < kCensusEntities; ++i) add(d[i]);
+            rows += (unsigned long long)__popc(bits) << 32;
+            if constexpr (LW > 0) {
+#pragma unroll
+                for (int i = 0; i < kCensusEntities; ++i)
+                    if (d[i] > 0)
+#pragma unroll
+                        for (int w = 0; w < LW; ++w) lv[w] |= lines[(size_t)(e0 + i) * LW + w];
+            }
+        }
     }
+    // the block's sums (and live words) in part[0 ..][] and, by thread, of thread i in the last block
+    auto put_part = [&]() {
+        lists = (unsigned long long)wave_sum((long long)lists);
+        rows = (unsigned long long)wave_sum((long long)rows);
+        edges = (unsigned long long)wave_sum((long long)edges);
+        if constexpr (LW > 0) {
+            const unsigned long long x = wave_or_words<LW>(lv);
+            if ((lane() & (64 / LW - 1)) == 0) part[wave][3 + own_word<LW>()] = x;
+        }
+        if (lane() == 0) {
+            part[wave][0] = lists;
+            part[wave][1] = rows;
+            part[wave][2] = edges;
+        }
+    };
+    auto total = [&](int i) {
+        unsigned long long x = 0;
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) x = i < 3 ? x + part[w][i] : x | part[w][i];
+        return x;
+    };
+    put_part();
     __syncthreads();
     // The block's sums go to a line of their own; whoever takes the last ticket adds them all up.  (Three atomics
     // per block on the level's counters were 6 ns each, one after the other: 16 us with 367 blocks.)
     __shared__ int last;
-    if (threadIdx.x < 3) {
-        unsigned long long x = 0;
-#pragma unroll
-        for (int w = 0; w < 16; ++w) x += part[w][threadIdx.x];
-        __hip_atomic_store(&sums[(size_t)blockIdx.x * 3 + threadIdx.x], x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    if (threadIdx.x < NS)
+        __hip_atomic_store(&sums[(size_t)blockIdx.x * NS + threadIdx.x], total((int)threadIdx.x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the sums (of this wavefront's lanes) are in before the ticket is taken
     if (threadIdx.x == 0) last = atomicAdd(&ctr[L_TICKET], 1ull) == gridDim.x - 1;
     __syncthreads();
     if (!last) return;  // block-uniform
     lists = rows = edges = 0;
+#pragma unroll
+    for (int w = 0; w < LW; ++w) lv[w] = 0;
     if (threadIdx.x < gridDim.x) {  // at most kCensusBlocks = 512 blocks
-        unsigned long long *x = sums + (size_t)threadIdx.x * 3;
+        unsigned long long *x = sums + (size_t)threadIdx.x * NS;
         lists = __hip_atomic_load(x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         rows = __hip_atomic_load(x + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         edges = __hip_atomic_load(x + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    lists = (unsigned long long)wave_sum((long long)lists);
-    rows = (unsigned long long)wave_sum((long long)rows);
-    edges = (unsigned long long)wave_sum((long long)edges);
-    if (lane() == 0) {
-        part[wave][0] = lists;
-        part[wave][1] = rows;
-        part[wave][2] = edges;
-    }
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    lists = rows = edges = 0;
 #pragma unroll
-    for (int w = 0; w < 16; ++w) {
-        lists += part[w][0];
-        rows += part[w][1];
-        edges += part[w][2];
+        for (int w = 0; w < LW; ++w) lv[w] = __hip_atomic_load(x + 3 + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    put_part();
+    __syncthreads();
+    if constexpr (LW > 0)
+        if (threadIdx.x >= 3 && threadIdx.x < NS) live[threadIdx.x - 3] = total((int)threadIdx.x);
+    if (threadIdx.x != 0) return;
+    lists = total(0);
+    rows = total(1);
     host[C_NTAIL] = lists & 0xffffffffull;
     host[C_NSEG] = lists >> 32;
     host[C_NROWS] = rows & 0xffffffffull;
     host[C_NACTIVE] = rows >> 32;
-    host[C_FEDGES] = edges;
+    host[C_FEDGES] = total(2);
     host[C_ERR] = __hip_atomic_load(&ctr[L_ERR], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -252,7 +346,7 @@ __device__ __forceinline__ unsigned long long or_across_groups(unsigned long lon
 
 // live[w] = OR of the frontier lines of every subject row that has a triple:
 // the queries for which this hop can still reach something.  A pull row stops
-// as soon as it has all of them.
+// as soon as it has all of them.  (Narrow planes: by the census.)
 template <int W>
 __device__ __forceinline__ int take_candidates(unsigned long long &rest);
 
@@ -845,6 +939,130 @@ k_pull_finish(const int32_t *__restrict__ rows, long long n, unsigned long long 
     }
 }
 
+// ---- narrow planes (one and four words): lane = entry.  A lane loads the whole line of a subject (8 or 32 bytes), so the
+// entries of a row need no hand-over between lanes; a wavefront takes a segment of a long row, eight lanes a short one,
+// and the words are put together at the end.  Long and short rows share one launch, a row of several segments is merged
+// through atomics on the level and on visited, and the census behind the hop makes the bitmap: no other kernel follows.
+// What bounds it is the chain of loads of a row (record, visited and ids, lines) with everything in the caches, so
+// each lane keeps several entries in flight.  One-word lines are gathered without asking for the frontier bit first,
+// whatever the frontier's size: the bit costs as much as the line, which is zero outside the level.
+// (Two hops on 3.4M triples, us, three kernels as for 16-word planes against this one: one question 60 -> 22, 8 walk-exact
+// ones 90 -> 34, 200 questions with whitelists 125 -> 60.)
+// acc |= the lines of entries j, j + step, .. (U of them, those below hi)
+template <int W, int U, bool MASK, bool DENSE>
+__device__ __forceinline__ void pull_entries(uint32_t j, uint32_t step, uint32_t hi, const int32_t *__restrict__ in_sub,
+                                             const uint16_t *__restrict__ in_rel, const unsigned long long *__restrict__ allow,
+                                             const uint32_t *__restrict__ act_prev,
+                                             const unsigned long long *__restrict__ prev, unsigned long long (&acc)[W]) {
+    int s[U], r[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint32_t at = j + (uint32_t)u * step;
+        s[u] = -1;
+        r[u] = 0;
+        if (at < hi) {
+            s[u] = in_sub[at];
+            if (MASK) r[u] = in_rel[at];
+        }
+    }
+    bool on[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) on[u] = s[u] >= 0 && (DENSE || ((act_prev[s[u] >> 5] >> (s[u] & 31)) & 1u));
+    unsigned long long l[U][W];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+        for (int w = 0; w < W; ++w) l[u][w] = 0;
+        if (on[u]) {
+            load_line<W>(l[u], prev + (size_t)s[u] * W);
+            if (MASK) {
+                unsigned long long m[W];
+                load_line<W>(m, allow + (size_t)r[u] * W);
+#pragma unroll
+                for (int w = 0; w < W; ++w) l[u][w] &= m[w];
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int w = 0; w < W; ++w) acc[w] |= l[u][w];
+}
+
+// word lane % W of the OR over a group of G lanes
+template <int W, int G>
+__device__ __forceinline__ unsigned long long group_or_words(const unsigned long long (&x)[W]) {
+    unsigned long long r = x[0];
+    if constexpr (W == 4) {
+        const bool hi = lane() & 2, odd = lane() & 1;
+        const unsigned long long a = (hi ? x[2] : x[0]) | shfl_xor64(hi ? x[0] : x[2], 2);
+        const unsigned long long b = (hi ? x[3] : x[1]) | shfl_xor64(hi ? x[1] : x[3], 2);
+        r = (odd ? b : a) | shfl_xor64(odd ? a : b, 1);
+    }
+#pragma unroll
+    for (int m = W; m < G; m <<= 1) r |= shfl_xor64(r, m);
+    return r;
+}
+
+// Entries per lane and step, and the lanes of a short row.  Hops of one question / of 8 walk-exact ones / of 200 questions
+// with whitelists on 3.4M triples, us for two hops: eight lanes and two entries 22 / 34 / 60, four lanes and four
+// entries 23 / 36 / 63, one lane and eight entries (W lanes on four words) 35 / 62 / 69: a lane per row is too few wavefronts.
+constexpr int kSegEntries = 4, kTailEntries = 2, kNarrowTailLanes = 8;
+
+template <int W, bool MASK, bool DENSE>
+__global__ void __launch_bounds__(256)
+k_pull_narrow(const PullSegment *__restrict__ segs, long long n_seg, unsigned seg_blocks, const ShortRow *__restrict__ rows,
+              long long n_rows, const int32_t *__restrict__ in_sub, const uint16_t *__restrict__ in_rel,
+              const unsigned long long *__restrict__ allow, const uint32_t *__restrict__ act_prev,
+              const unsigned long long *__restrict__ prev, const unsigned long long *__restrict__ live,
+              unsigned long long *visited, unsigned long long *cur, int walk_exact) {
+    if (blockIdx.x < seg_blocks) {  // block-uniform: the segments first, they take longest
+        const long long item = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+        if (item >= n_seg) return;  // wavefront-uniform
+        const PullSegment sg = segs[item];
+        const bool multi = sg.multi != 0;
+        const size_t mine = (size_t)sg.row * W + own_word<W>();
+        const unsigned long long vis = visited[mine], need = (walk_exact ? ~0ull : ~vis) & live[own_word<W>()];
+        if (!wave_any(need != 0)) return;
+        unsigned long long acc[W] = {}, nw = 0;
+        for (uint32_t j0 = sg.begin; j0 < sg.end; j0 += 64 * kSegEntries) {
+            pull_entries<W, kSegEntries, MASK, DENSE>(j0 + lane(), 64, sg.end, in_sub, in_rel, allow, act_prev, prev, acc);
+            nw = wave_or_words<W>(acc) & need;
+            if (!wave_any((need & ~nw) != 0)) break;
+        }
+        // The segments of a row end about together, and their atomics wait for each other: only what is still missing.
+        // (One that read visited when others had added theirs leaves those bits out: they are in the level already.)
+        if (multi && wave_any(nw != 0)) nw &= ~__hip_atomic_load(&cur[mine], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((lane() & (64 / W - 1)) != 0 || !wave_any(nw != 0)) return;
+        if (!multi) {
+            cur[mine] = nw;
+            visited[mine] = vis | nw;
+        } else if (nw) {
+            atomicOr(&cur[mine], nw);
+            atomicOr(&visited[mine], nw);
+        }
+        return;
+    }
+    constexpr int G = kNarrowTailLanes, U = kTailEntries;
+    const long long group = ((long long)(blockIdx.x - seg_blocks) * 256 + threadIdx.x) / G;
+    if (group >= n_rows) return;  // the lanes of a group together
+    const int lg = threadIdx.x & (G - 1);
+    const ShortRow row = rows[group];
+    const size_t mine = (size_t)row.row * W + (lg & (W - 1));
+    const unsigned long long vis = visited[mine], need = (walk_exact ? ~0ull : ~vis) & live[lg & (W - 1)];
+    if (!group_any<G>(need != 0)) return;
+    unsigned long long acc[W] = {}, found = 0;
+    for (uint32_t j0 = row.begin; j0 < row.end; j0 += U * G) {
+        pull_entries<W, U, MASK, DENSE>(j0 + lg, G, row.end, in_sub, in_rel, allow, act_prev, prev, acc);
+        found = group_or_words<W, G>(acc);
+        if (!group_any<G>((need & ~found) != 0)) break;
+    }
+    const unsigned long long nw = found & need;
+    if (lg >= W || !group_any<W>(nw != 0)) return;
+    cur[mine] = nw;
+    visited[mine] = vis | nw;
+}
+
 // ---------------------------------------------------------------- planes back to zero
 // A finished result's planes are zero except in the lines of entities that have their bit in some
 // level's active bitmap: when the result is released those lines (of the level and of visited) and
@@ -924,16 +1142,15 @@ static inline bool dense_pull(const logoskg_graph *g, const unsigned long long *
     return !want_stats && (long long)hc[C_FEDGES] * 100 >= g->T * (long long)kDensePullPercent;
 }
 
-// live[h-1]: the queries this hop can still reach something for (once per hop).
-template <int W>
+// live[h-1] of 16-word planes: the queries this hop can still reach something for (once per hop).
 static void launch_live(logoskg_graph *g, logoskg_result *r, int h, bool dense, hipStream_t st) {
-    const size_t plane = (size_t)r->Epad * W;
+    const size_t plane = (size_t)r->Epad * 16;
     ProfScope ps(g->prof, KK_LIVE, st);
     unsigned nb = std::min<unsigned>(2048u, std::max(1u, blocks_for(g->E, 256)));
     unsigned long long *live = r->live + (size_t)16 * (h - 1);
-    if (dense) k_live_all<<<dim3(1), dim3(64), 0, st>>>(r->Q, W, live);
-    else k_live<W><<<dim3(nb), dim3(256), 0, st>>>(r->act + (size_t)(r->Epad / 32) * (h - 1), g->E, g->out_off,
-                                                   r->levels + plane * (h - 1), live);
+    if (dense) k_live_all<<<dim3(1), dim3(64), 0, st>>>(r->Q, 16, live);
+    else k_live<16><<<dim3(nb), dim3(256), 0, st>>>(r->act + (size_t)(r->Epad / 32) * (h - 1), g->E, g->out_off,
+                                                    r->levels + plane * (h - 1), live);
 }
 
 // Pull over the object rows of the work lists `rc`, whose entries index in_sub / in_rel (the whole
@@ -949,6 +1166,16 @@ static void launch_pull_rows(logoskg_graph *g, logoskg_result *r, int h, const R
     const unsigned long long *live = r->live + (size_t)16 * (h - 1);
     auto stats = [&](int kind) { return STATS ? g->d_ctr + C_STATS + 4 * kind : nullptr; };
     const int walk = r->walk_exact ? 1 : 0;
+    if constexpr (W <= 4 && !STATS) {
+        if (rc.n_seg + rc.n_tail == 0) return;
+        ProfScope ps(g->prof, KK_PULL_TAIL, st);
+        const unsigned seg_blocks = blocks_for(rc.n_seg, 4);
+        const dim3 grid(seg_blocks + blocks_for(rc.n_tail * kNarrowTailLanes, 256)), block(256);
+        auto *kernel = dense || W == 1 ? k_pull_narrow<W, MASK, true> : k_pull_narrow<W, MASK, W == 1>;
+        kernel<<<grid, block, 0, st>>>(rc.seg, rc.n_seg, seg_blocks, rc.tail, rc.n_tail, in_sub, in_rel, r->allow, act_prev,
+                                       prev, live, r->visited, cur, walk);
+        return;
+    } else {
     if (rc.n_seg > 0) {
         ProfScope ps(g->prof, KK_PULL_SEG, st);
         const dim3 grid(blocks_for(rc.n_seg, 4)), block(256);
@@ -979,6 +1206,7 @@ static void launch_pull_rows(logoskg_graph *g, logoskg_result *r, int h, const R
         k_pull_finish<W><<<dim3(blocks_for(rc.n_multi * W, 256)), dim3(256), 0, st>>>(rc.multi, rc.n_multi,
                                                                                       r->visited, cur, act_cur);
     }
+    }
 }
 
 template <int W>
@@ -1001,15 +1229,13 @@ void launch_pull_range(logoskg_graph *g, logoskg_result *r, int h, const RowClas
     const bool dense = dense_pull(g, hc, want_stats);
     switch (r->W) {
         case 1:
-            if (first) launch_live<1>(g, r, h, dense, st);
             pull_rows_w<1>(g, r, h, rc, in_sub, in_rel, dense, want_stats, st);
             break;
         case 4:
-            if (first) launch_live<4>(g, r, h, dense, st);
             pull_rows_w<4>(g, r, h, rc, in_sub, in_rel, dense, want_stats, st);
             break;
         default:
-            if (first) launch_live<16>(g, r, h, dense, st);
+            if (first) launch_live(g, r, h, dense, st);
             pull_rows_w<16>(g, r, h, rc, in_sub, in_rel, dense, want_stats, st);
             break;
     }
@@ -1076,13 +1302,19 @@ logoskg_status census_lists(logoskg_graph *g, logoskg_result *r, int h, unsigned
     return LOGOSKG_OK;
 }
 
-// Census of level h into g->h_ctr; synchronises the stream.
-static logoskg_status census(logoskg_graph *g, logoskg_result *r, int h, hipStream_t st) {
+// Census of level h into g->h_ctr; synchronises the stream.  pulled: the level comes from the pull kernels
+static logoskg_status census(logoskg_graph *g, logoskg_result *r, int h, bool pulled, hipStream_t st) {
     {
         ProfScope ps(g->prof, KK_CENSUS, st);
-        const unsigned nb = std::min<unsigned>(kCensusBlocks, std::max(1u, blocks_for(g->E, 1024 * kCensusEntities)));
-        k_census<<<dim3(nb), dim3(1024), 0, st>>>(r->act + (size_t)(r->Epad / 32) * h, g->E, g->out_off,
-                                                  level_counters(r, h), g->d_ctr + C_TOTAL, g->h_ctr);
+        auto launch = [&](auto *kernel, int threads, int per_thread) {
+            const unsigned nb = std::min<unsigned>(kCensusBlocks, std::max(1u, blocks_for(g->E, threads * per_thread)));
+            kernel<<<dim3(nb), dim3((unsigned)threads), 0, st>>>(r->act + (size_t)(r->Epad / 32) * h, g->E, g->out_off,
+                                                                 level_counters(r, h), g->d_ctr + C_TOTAL, g->h_ctr,
+                                                                 r->levels + (size_t)r->Epad * r->W * h, r->live + (size_t)16 * h);
+        };
+        if (r->W == 16) launch(k_census<0, false>, 1024, kCensusEntities);
+        else if (pulled) launch(r->W == 1 ? k_census<1, true> : k_census<4, true>, 512, 4);
+        else launch(r->W == 1 ? k_census<1, false> : k_census<4, false>, 512, kCensusEntities);
     }
     LKG_HIP(hipGetLastError());
     if (g->prof.counters)
@@ -1214,7 +1446,7 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
                                                                r->seed_off, r->seeds);
         g->prof.end(st);
         KH(hipGetLastError());
-        if ((s = census(g, r, 0, st)) != LOGOSKG_OK) return fail(s);
+        if ((s = census(g, r, 0, false, st)) != LOGOSKG_OK) return fail(s);
         if (g->h_ctr[C_ERR]) {
             set_error("seed_off / seeds are inconsistent or out of range (device check, code %llu)", g->h_ctr[C_ERR]);
             return fail(LOGOSKG_EINVAL);
@@ -1244,7 +1476,7 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
             launch_resident_hop(g, r, h, pull, want_stats, hc, st);
             KH(hipGetLastError());
         }
-        if ((s = census(g, r, h, st)) != LOGOSKG_OK) return fail(s);
+        if ((s = census(g, r, h, pull, st)) != LOGOSKG_OK) return fail(s);
         hs.entities_reached = (long long)g->h_ctr[C_NACTIVE];
         if (hs.direction == LOGOSKG_DIR_PULL) {
             if (want_stats) for (int kind : {KK_PULL_TAIL, KK_PULL_SEG}) {

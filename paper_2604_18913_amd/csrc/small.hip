@@ -85,6 +85,7 @@ struct SmallArgs {
     int32_t *ent;      // [kSmallEntities] reached entities, ascending
     long long *off;    // [65] offsets of the lists
     SmallReport *rep;  // pinned host memory
+    unsigned long long *live;  // [levels][16] live words, of the level the general path goes on with (or NULL)
 };
 
 // One word per entity.  A level's list is bounded by the triples pushed into it, the list of all
@@ -192,13 +193,25 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_search(SmallArgs a) {
             unsigned long long fe = 0;
             for (int i = t; i < n; i += kSmallThreads) fe += a.out_off[s_list[cur][i] + 1] - a.out_off[s_list[cur][i]];
             fe = (unsigned long long)wave_sum((long long)fe);
+            unsigned long long lv = 0;  // the queries whose frontier has an out-edge
+            for (int i = t; i < n; i += kSmallThreads)
+                if (a.out_off[s_list[cur][i] + 1] > a.out_off[s_list[cur][i]]) lv |= s_line[i];
+#pragma unroll
+            for (int m = 32; m >= 1; m >>= 1) lv |= shfl_xor64(lv, m);
             unsigned long long *sum = s_line;  // (not needed any more)
             __syncthreads();
-            if (lane() == 0) sum[t >> 6] = fe;
+            if (lane() == 0) {
+                sum[t >> 6] = fe;
+                sum[16 + (t >> 6)] = lv;
+            }
             __syncthreads();
             if (t == 0) {
-                fe = 0;
-                for (int i = 0; i < kSmallThreads / 64; ++i) fe += sum[i];
+                fe = lv = 0;
+                for (int i = 0; i < kSmallThreads / 64; ++i) {
+                    fe += sum[i];
+                    lv |= sum[16 + i];
+                }
+                if (a.live) a.live[(size_t)16 * h] = lv;
                 a.rep->rows[h] = rows;
                 a.rep->edges[h] = (long long)fe;
                 a.rep->n_tail = s_tail;
@@ -383,7 +396,7 @@ logoskg_status small_search(logoskg_graph *g, logoskg_result *r, const logoskg_q
     a.allow = r->has_mask ? r->allow : nullptr;
     a.visited = r->visited; a.levels = r->levels; a.act = r->act;
     a.kept_off = r->seed_off; a.kept_seeds = r->seeds;
-    a.ent = r->small_ent; a.off = r->small_off; a.rep = g->h_small;
+    a.ent = r->small_ent; a.off = r->small_off; a.rep = g->h_small; a.live = r->live;
     {
         ProfScope ps(g->prof, KK_SEED, st);
         k_small_search<<<dim3(1), dim3(kSmallThreads), 0, st>>>(a);
