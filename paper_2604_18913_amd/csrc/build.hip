@@ -401,12 +401,13 @@ extern "C" logoskg_status logoskg_build(const int32_t *subj, const int32_t *rel,
     if ((st = dev_alloc((void **)&g->fr_tail, (size_t)E * sizeof(int32_t))) != LOGOSKG_OK) return fail(st);
     if ((st = dev_alloc((void **)&g->fr_seg, (size_t)g->fr_seg_cap * sizeof(RowSegment))) != LOGOSKG_OK) return fail(st);
     if ((st = dev_alloc((void **)&g->d_ctr, (C_TOTAL + kCensusWords * kCensusBlocks) * sizeof(unsigned long long))) != LOGOSKG_OK) return fail(st);
-    constexpr size_t ctr_bytes = (C_TOTAL + 1) * sizeof(unsigned long long), off_bytes = (LOGOSKG_MAX_QUERIES + 1) * sizeof(long long);
+    constexpr size_t ctr_bytes = (C_TOTAL + 1 + 2 * kCensusSlot) * sizeof(unsigned long long), off_bytes = (LOGOSKG_MAX_QUERIES + 1) * sizeof(long long);
     static_assert(alignof(SmallReport) <= 8, "it lies behind 8-byte words");
     if (hipHostMalloc((void **)&g->h_ctr, ctr_bytes + off_bytes + sizeof(SmallReport), hipHostMallocDefault) != hipSuccess) {
         set_error("hipHostMalloc failed");
         return fail(LOGOSKG_ENOMEM);
     }
+    g->h_census = g->h_ctr + C_TOTAL + 1;
     g->h_off = reinterpret_cast<long long *>(reinterpret_cast<char *>(g->h_ctr) + ctr_bytes);
     g->h_small = reinterpret_cast<SmallReport *>(reinterpret_cast<char *>(g->h_off) + off_bytes);
     for (int i = 0; i < 2; ++i) {

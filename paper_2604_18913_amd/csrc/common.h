@@ -85,7 +85,7 @@ private:
 };
 
 // ---------------------------------------------------------------- graph
-constexpr int kLevelCounters = 4;
+constexpr int kLevelCounters = 5;
 constexpr unsigned kCensusBlocks = 512;  // at most; kCensusWords each behind d_ctr's C_TOTAL
 constexpr unsigned kCensusWords = 7;     // three sums, and up to four live words
 constexpr int kTailMaxDegree = 32;      // rows up to this degree: one W-lane group per row
@@ -164,6 +164,10 @@ enum {
     C_STATS = 8, C_TOTAL = C_STATS + 4 * KK_NUM  // the pinned host mirror holds one word more
 };
 
+// where a census of a narrow level leaves its counters in pinned memory: words C_NTAIL .. C_ERR, and one that says
+// they are there
+constexpr int kCensusDone = C_STATS, kCensusSlot = C_STATS + 8;
+
 struct Profiler {
     bool on = false;        // bracket launches with events
     bool counters = false;  // also count rows / edges / lines inside the kernels
@@ -221,6 +225,7 @@ struct logoskg_graph {
     // pinned host memory, one block (three allocations: 0.44 ms for a graph of 50,000 triples, 0.41 with one):
     unsigned long long *h_ctr = nullptr;  // mirror of the counters
     long long *h_off = nullptr;           // [LOGOSKG_MAX_QUERIES + 1]: offsets of the last count
+    unsigned long long *h_census = nullptr;  // [2][kCensusSlot]: counters of the levels of narrow_hops
     lkg::SmallReport *h_small = nullptr;  // written by k_small_search
 
     std::vector<int32_t> shard_of;  // host copy of the map P (empty when unsharded)

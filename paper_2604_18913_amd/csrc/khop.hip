@@ -28,9 +28,11 @@
 namespace lkg {
 
 // counters of a level (kLevelCounters words behind the live words): the append cursors of its push lists, the
-// census' sums, the error word of the seeds (level 0) and the blocks that have added theirs
-enum { L_CUR_TAIL = 0, L_CUR_SEG, L_ERR, L_TICKET };
-static_assert(L_TICKET < kLevelCounters && (int)L_CUR_TAIL == (int)C_NTAIL && (int)L_CUR_SEG == (int)C_NSEG,
+// census' sums, the error word of the seeds (level 0), the blocks that have added theirs, and what the next hop is to
+// do if it was launched ahead of the host's decision: kHopNotPulled, or the form of the pull
+enum { kHopNotPulled = 0, kHopPulled = 1, kHopPulledDense = 2 };
+enum { L_CUR_TAIL = 0, L_CUR_SEG, L_ERR, L_TICKET, L_PULL };
+static_assert(L_PULL < kLevelCounters && (int)L_CUR_TAIL == (int)C_NTAIL && (int)L_CUR_SEG == (int)C_NSEG,
               "the push kernels read the cursors as C_NTAIL and C_NSEG");
 
 // ---------------------------------------------------------------- seeds, mask table
@@ -75,6 +77,10 @@ k_allow(int Q, int R, int W, int rel_words, const unsigned long long *__restrict
     const unsigned long long x = transpose64(q < Q ? rel_mask[(size_t)q * rel_words + rw] : 0ull);
     if (r < R) allow[(size_t)r * W + w] = x;
 }
+
+// A hop pulls when more than a twelfth of the triples leave its frontier, and is dense from kDensePullPercent of them.
+__host__ __device__ inline bool pull_rule(long long edges, long long T) { return edges * 12 > T; }
+__host__ __device__ inline bool dense_rule(long long edges, long long T) { return edges * 100 >= T * kDensePullPercent; }
 
 // ---------------------------------------------------------------- frontier census
 // The census of a level's active bitmap gives the host what it needs to pick the direction: rows, triples and
@@ -161,7 +167,9 @@ template <int LW, bool PULLED>
 __global__ void __launch_bounds__(LW ? 512 : 1024)
 k_census(uint32_t *act, int32_t E, const uint32_t *__restrict__ out_off, unsigned long long *ctr,
          unsigned long long *sums, unsigned long long *host, const unsigned long long *__restrict__ lines,
-         unsigned long long *live) {
+         unsigned long long *live, const unsigned long long *go, long long T) {
+    if constexpr (PULLED)
+        if (go && *go == kHopNotPulled) return;  // launched ahead for a hop that is not taken this way
     static_assert(!PULLED || LW > 0, "16-word lines are not read for their bits");
     constexpr int NT = LW ? 512 : 1024, NS = 3 + LW;  // threads, words per block
     constexpr int G = 4;                              // PULLED: entities per lane
@@ -281,8 +289,13 @@ k_census(uint32_t *act, int32_t E, const uint32_t *__restrict__ out_off, unsigne
     host[C_NSEG] = lists >> 32;
     host[C_NROWS] = rows & 0xffffffffull;
     host[C_NACTIVE] = rows >> 32;
-    host[C_FEDGES] = total(2);
+    host[C_FEDGES] = edges = total(2);
     host[C_ERR] = __hip_atomic_load(&ctr[L_ERR], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if constexpr (LW > 0) {
+        ctr[L_PULL] = !pull_rule((long long)edges, T) ? kHopNotPulled : dense_rule((long long)edges, T) ? kHopPulledDense : kHopPulled;
+        __threadfence_system();
+        __hip_atomic_store(&host[kCensusDone], 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
 // The push lists of a level; ctr[L_CUR_TAIL] and ctr[L_CUR_SEG] are the append cursors (zero before) and then the
@@ -949,9 +962,9 @@ k_pull_finish(const int32_t *__restrict__ rows, long long n, unsigned long long 
 // (Two hops on 3.4M triples, us, three kernels as for 16-word planes against this one: one question 60 -> 22, 8 walk-exact
 // ones 90 -> 34, 200 questions with whitelists 125 -> 60.)
 // acc |= the lines of entries j, j + step, .. (U of them, those below hi)
-template <int W, int U, bool MASK, bool DENSE>
-__device__ __forceinline__ void pull_entries(uint32_t j, uint32_t step, uint32_t hi, const int32_t *__restrict__ in_sub,
-                                             const uint16_t *__restrict__ in_rel, const unsigned long long *__restrict__ allow,
+template <int W, int U, bool MASK>
+__device__ __forceinline__ void pull_entries(bool dense, uint32_t j, uint32_t step, uint32_t hi,
+                                             const int32_t *__restrict__ in_sub, const uint16_t *__restrict__ in_rel, const unsigned long long *__restrict__ allow,
                                              const uint32_t *__restrict__ act_prev,
                                              const unsigned long long *__restrict__ prev, unsigned long long (&acc)[W]) {
     int s[U], r[U];
@@ -967,7 +980,11 @@ __device__ __forceinline__ void pull_entries(uint32_t j, uint32_t step, uint32_t
     }
     bool on[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) on[u] = s[u] >= 0 && (DENSE || ((act_prev[s[u] >> 5] >> (s[u] & 31)) & 1u));
+    for (int u = 0; u < U; ++u) on[u] = s[u] >= 0;
+    if (W > 1 && !dense) {  // (wavefront-uniform)
+#pragma unroll
+        for (int u = 0; u < U; ++u) on[u] = on[u] && ((act_prev[s[u] >> 5] >> (s[u] & 31)) & 1u);
+    }
     unsigned long long l[U][W];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -1009,13 +1026,20 @@ __device__ __forceinline__ unsigned long long group_or_words(const unsigned long
 // entries 23 / 36 / 63, one lane and eight entries (W lanes on four words) 35 / 62 / 69: a lane per row is too few wavefronts.
 constexpr int kSegEntries = 4, kTailEntries = 2, kNarrowTailLanes = 8;
 
-template <int W, bool MASK, bool DENSE>
+// go: NULL, or what the census in front has decided (a hop launched before the host knows; see narrow_hops)
+template <int W, bool MASK>
 __global__ void __launch_bounds__(256)
 k_pull_narrow(const PullSegment *__restrict__ segs, long long n_seg, unsigned seg_blocks, const ShortRow *__restrict__ rows,
               long long n_rows, const int32_t *__restrict__ in_sub, const uint16_t *__restrict__ in_rel,
               const unsigned long long *__restrict__ allow, const uint32_t *__restrict__ act_prev,
               const unsigned long long *__restrict__ prev, const unsigned long long *__restrict__ live,
-              unsigned long long *visited, unsigned long long *cur, int walk_exact) {
+              unsigned long long *visited, unsigned long long *cur, int walk_exact, bool dense,
+              const unsigned long long *go) {
+    if (go) {
+        const unsigned long long form = *go;
+        if (form == kHopNotPulled) return;
+        dense = form == kHopPulledDense;
+    }
     if (blockIdx.x < seg_blocks) {  // block-uniform: the segments first, they take longest
         const long long item = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
         if (item >= n_seg) return;  // wavefront-uniform
@@ -1026,7 +1050,7 @@ k_pull_narrow(const PullSegment *__restrict__ segs, long long n_seg, unsigned se
         if (!wave_any(need != 0)) return;
         unsigned long long acc[W] = {}, nw = 0;
         for (uint32_t j0 = sg.begin; j0 < sg.end; j0 += 64 * kSegEntries) {
-            pull_entries<W, kSegEntries, MASK, DENSE>(j0 + lane(), 64, sg.end, in_sub, in_rel, allow, act_prev, prev, acc);
+            pull_entries<W, kSegEntries, MASK>(dense, j0 + lane(), 64, sg.end, in_sub, in_rel, allow, act_prev, prev, acc);
             nw = wave_or_words<W>(acc) & need;
             if (!wave_any((need & ~nw) != 0)) break;
         }
@@ -1053,7 +1077,7 @@ k_pull_narrow(const PullSegment *__restrict__ segs, long long n_seg, unsigned se
     if (!group_any<G>(need != 0)) return;
     unsigned long long acc[W] = {}, found = 0;
     for (uint32_t j0 = row.begin; j0 < row.end; j0 += U * G) {
-        pull_entries<W, U, MASK, DENSE>(j0 + lg, G, row.end, in_sub, in_rel, allow, act_prev, prev, acc);
+        pull_entries<W, U, MASK>(dense, j0 + lg, G, row.end, in_sub, in_rel, allow, act_prev, prev, acc);
         found = group_or_words<W, G>(acc);
         if (!group_any<G>((need & ~found) != 0)) break;
     }
@@ -1139,7 +1163,7 @@ static void launch_push(logoskg_graph *g, logoskg_result *r, int h, const unsign
 // When most triples leave the frontier the kernels gather every edge's line without asking for
 // its frontier bit first (never in the counting mode: its statistics count frontier lines).
 static inline bool dense_pull(const logoskg_graph *g, const unsigned long long *hc, bool want_stats) {
-    return !want_stats && (long long)hc[C_FEDGES] * 100 >= g->T * (long long)kDensePullPercent;
+    return !want_stats && dense_rule((long long)hc[C_FEDGES], g->T);
 }
 
 // live[h-1] of 16-word planes: the queries this hop can still reach something for (once per hop).
@@ -1157,7 +1181,7 @@ static void launch_live(logoskg_graph *g, logoskg_result *r, int h, bool dense, 
 // object-sorted CSR of a resident graph, or one object range of a sharded one in a cache slot).
 template <int W, bool MASK, bool STATS>
 static void launch_pull_rows(logoskg_graph *g, logoskg_result *r, int h, const RowClasses &rc, const int32_t *in_sub,
-                             const uint16_t *in_rel, bool dense, hipStream_t st) {
+                             const uint16_t *in_rel, bool dense, const unsigned long long *go, hipStream_t st) {
     const size_t plane = (size_t)r->Epad * W;
     const unsigned long long *prev = r->levels + plane * (h - 1);
     unsigned long long *cur = r->levels + plane * h;
@@ -1171,9 +1195,8 @@ static void launch_pull_rows(logoskg_graph *g, logoskg_result *r, int h, const R
         ProfScope ps(g->prof, KK_PULL_TAIL, st);
         const unsigned seg_blocks = blocks_for(rc.n_seg, 4);
         const dim3 grid(seg_blocks + blocks_for(rc.n_tail * kNarrowTailLanes, 256)), block(256);
-        auto *kernel = dense || W == 1 ? k_pull_narrow<W, MASK, true> : k_pull_narrow<W, MASK, W == 1>;
-        kernel<<<grid, block, 0, st>>>(rc.seg, rc.n_seg, seg_blocks, rc.tail, rc.n_tail, in_sub, in_rel, r->allow, act_prev,
-                                       prev, live, r->visited, cur, walk);
+        k_pull_narrow<W, MASK><<<grid, block, 0, st>>>(rc.seg, rc.n_seg, seg_blocks, rc.tail, rc.n_tail, in_sub, in_rel,
+                                                       r->allow, act_prev, prev, live, r->visited, cur, walk, dense, go);
         return;
     } else {
     if (rc.n_seg > 0) {
@@ -1211,13 +1234,14 @@ static void launch_pull_rows(logoskg_graph *g, logoskg_result *r, int h, const R
 
 template <int W>
 static void pull_rows_w(logoskg_graph *g, logoskg_result *r, int h, const RowClasses &rc, const int32_t *in_sub,
-                        const uint16_t *in_rel, bool dense, bool want_stats, hipStream_t st) {
+                        const uint16_t *in_rel, bool dense, bool want_stats, hipStream_t st,
+                        const unsigned long long *go = nullptr) {
     if (r->has_mask) {
-        if (want_stats) launch_pull_rows<W, true, true>(g, r, h, rc, in_sub, in_rel, dense, st);
-        else launch_pull_rows<W, true, false>(g, r, h, rc, in_sub, in_rel, dense, st);
+        if (want_stats) launch_pull_rows<W, true, true>(g, r, h, rc, in_sub, in_rel, dense, go, st);
+        else launch_pull_rows<W, true, false>(g, r, h, rc, in_sub, in_rel, dense, go, st);
     } else {
-        if (want_stats) launch_pull_rows<W, false, true>(g, r, h, rc, in_sub, in_rel, dense, st);
-        else launch_pull_rows<W, false, false>(g, r, h, rc, in_sub, in_rel, dense, st);
+        if (want_stats) launch_pull_rows<W, false, true>(g, r, h, rc, in_sub, in_rel, dense, go, st);
+        else launch_pull_rows<W, false, false>(g, r, h, rc, in_sub, in_rel, dense, go, st);
     }
 }
 
@@ -1283,6 +1307,12 @@ void launch_resident_hop(logoskg_graph *g, logoskg_result *r, int h, bool pull, 
     }
 }
 
+// A pulled hop of a resident graph on narrow planes, for the case that *go says so.
+static void launch_pull_ahead(logoskg_graph *g, logoskg_result *r, int h, const unsigned long long *go, hipStream_t st) {
+    if (r->W == 1) pull_rows_w<1>(g, r, h, g->in_rows, g->in_sub, g->in_rel, false, false, st, go);
+    else pull_rows_w<4>(g, r, h, g->in_rows, g->in_sub, g->in_rel, false, false, st, go);
+}
+
 __global__ void k_clear_cursors(unsigned long long *ctr) { ctr[threadIdx.x] = 0ull; }
 
 // Push lists of level h into g->fr_tail / g->fr_seg.  ctr: two words that hold zeros (a level's own counters, once),
@@ -1302,21 +1332,28 @@ logoskg_status census_lists(logoskg_graph *g, logoskg_result *r, int h, unsigned
     return LOGOSKG_OK;
 }
 
-// Census of level h into g->h_ctr; synchronises the stream.  pulled: the level comes from the pull kernels
-static logoskg_status census(logoskg_graph *g, logoskg_result *r, int h, bool pulled, hipStream_t st) {
-    {
-        ProfScope ps(g->prof, KK_CENSUS, st);
-        auto launch = [&](auto *kernel, int threads, int per_thread) {
-            const unsigned nb = std::min<unsigned>(kCensusBlocks, std::max(1u, blocks_for(g->E, threads * per_thread)));
-            kernel<<<dim3(nb), dim3((unsigned)threads), 0, st>>>(r->act + (size_t)(r->Epad / 32) * h, g->E, g->out_off,
-                                                                 level_counters(r, h), g->d_ctr + C_TOTAL, g->h_ctr,
-                                                                 r->levels + (size_t)r->Epad * r->W * h, r->live + (size_t)16 * h);
-        };
-        if (r->W == 16) launch(k_census<0, false>, 1024, kCensusEntities);
-        else if (pulled) launch(r->W == 1 ? k_census<1, true> : k_census<4, true>, 512, 4);
-        else launch(r->W == 1 ? k_census<1, false> : k_census<4, false>, 512, kCensusEntities);
-    }
+// Census of level h into `host` (pinned).  pulled: the level comes from the pull kernels; go: the hop in front was
+// launched ahead, and so is this.
+static logoskg_status launch_census(logoskg_graph *g, logoskg_result *r, int h, bool pulled, unsigned long long *host,
+                                    const unsigned long long *go, hipStream_t st) {
+    ProfScope ps(g->prof, KK_CENSUS, st);
+    auto launch = [&](auto *kernel, int threads, int per_thread) {
+        const unsigned nb = std::min<unsigned>(kCensusBlocks, std::max(1u, blocks_for(g->E, threads * per_thread)));
+        kernel<<<dim3(nb), dim3((unsigned)threads), 0, st>>>(r->act + (size_t)(r->Epad / 32) * h, g->E, g->out_off,
+                                                             level_counters(r, h), g->d_ctr + C_TOTAL, host,
+                                                             r->levels + (size_t)r->Epad * r->W * h, r->live + (size_t)16 * h,
+                                                             go, (long long)g->T);
+    };
+    if (r->W == 16) launch(k_census<0, false>, 1024, kCensusEntities);
+    else if (pulled) launch(r->W == 1 ? k_census<1, true> : k_census<4, true>, 512, 4);
+    else launch(r->W == 1 ? k_census<1, false> : k_census<4, false>, 512, kCensusEntities);
     LKG_HIP(hipGetLastError());
+    return LOGOSKG_OK;
+}
+
+// ... into g->h_ctr; synchronises the stream.
+static logoskg_status census(logoskg_graph *g, logoskg_result *r, int h, bool pulled, hipStream_t st) {
+    LKG_TRY(launch_census(g, r, h, pulled, g->h_ctr, nullptr, st));
     if (g->prof.counters)
         LKG_HIP(hipMemcpyAsync(g->h_ctr + C_STATS, g->d_ctr + C_STATS, 4 * KK_NUM * sizeof(unsigned long long),
                                hipMemcpyDeviceToHost, st));
@@ -1325,6 +1362,71 @@ static logoskg_status census(logoskg_graph *g, logoskg_result *r, int h, bool pu
 }
 
 logoskg_status count_reached(logoskg_result *r, hipStream_t st);  // result.hip
+
+// The counters that a census has written to `host`: waits for its word kCensusDone and not for the stream, behind whose
+// census the next hop may be running.  (The stream is asked now and then: a launch that failed ends the wait.)
+static logoskg_status await_census(const unsigned long long *host, hipStream_t st) {
+    for (long long turn = 1; !__atomic_load_n(&host[kCensusDone], __ATOMIC_ACQUIRE); ++turn) {
+        if (turn % 2048) continue;
+        const hipError_t e = hipStreamQuery(st);
+        if (e == hipErrorNotReady) {
+            (void)hipGetLastError();  // (launches have been checked)
+            continue;
+        }
+        LKG_HIP(e);
+        if (__atomic_load_n(&host[kCensusDone], __ATOMIC_ACQUIRE)) break;
+        set_error("the frontier census did not run");
+        return LOGOSKG_EINTERNAL;
+    }
+    return LOGOSKG_OK;
+}
+
+// The hops of a narrow batch on a resident graph (direction by rule).  The host needs each level's counters to choose the
+// next hop's direction, and on a graph of a few million triples a hop is 20 us of kernels, about what a wait, a
+// launch and the GPU's way back to work take.  Behind a pulled hop, whose successor nearly always pulls as well, the next
+// one is therefore launched before its turn is known: the census leaves its decision on the device (pull_rule, dense_rule:
+// the host's own), and kernels launched ahead of a hop that is not pulled return at once (about 4 us).  The last level's
+// counters, which only feed the statistics, are read behind the counts of the lists.  `pending`: that is still to be done.
+static logoskg_status narrow_hops(logoskg_graph *g, logoskg_result *r, int first_hop, bool *pending, hipStream_t st) {
+    unsigned long long hc[C_TOTAL] = {};
+    memcpy(hc, g->h_ctr, C_STATS * sizeof(hc[0]));
+    auto slot = [&](int h) { return g->h_census + (h & 1) * kCensusSlot; };
+    bool running = false;  // hop h is on its way already
+    for (int h = first_hop; h <= r->k; ++h) {
+        logoskg_hop_stats &hs = r->stats[(size_t)h - 1];
+        if (hc[C_NROWS] == 0) break;
+        hs.active_rows = (long long)hc[C_NROWS];
+        hs.frontier_edges = (long long)hc[C_FEDGES];
+        hs.shards_touched = 1;
+        const bool pull = pull_rule(hs.frontier_edges, g->T);
+        hs.direction = pull ? LOGOSKG_DIR_PULL : LOGOSKG_DIR_PUSH;
+        if (!pull) hs.edges_scanned = hs.lines_gathered = hs.frontier_edges;
+        if (!running) {
+            if (!pull) LKG_TRY(census_lists(g, r, h - 1, level_counters(r, h - 1), st));
+            launch_resident_hop(g, r, h, pull, false, hc, st);
+            LKG_HIP(hipGetLastError());
+            slot(h)[kCensusDone] = 0;
+            LKG_TRY(launch_census(g, r, h, pull, slot(h), nullptr, st));
+        }
+        const bool ahead = pull && h < r->k;
+        if (ahead) {
+            const unsigned long long *go = level_counters(r, h) + L_PULL;
+            launch_pull_ahead(g, r, h + 1, go, st);
+            LKG_HIP(hipGetLastError());
+            slot(h + 1)[kCensusDone] = 0;
+            LKG_TRY(launch_census(g, r, h + 1, true, slot(h + 1), go, st));
+        }
+        if (h == r->k) {
+            *pending = true;
+            break;
+        }
+        LKG_TRY(await_census(slot(h), st));
+        memcpy(hc, slot(h), C_STATS * sizeof(hc[0]));
+        hs.entities_reached = (long long)hc[C_NACTIVE];
+        running = ahead && pull_rule((long long)hc[C_FEDGES], g->T);
+    }
+    return LOGOSKG_OK;
+}
 
 }  // namespace lkg
 
@@ -1452,14 +1554,20 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
             return fail(LOGOSKG_EINVAL);
         }
     }
-    for (int h = first_hop; h <= k; ++h) {
+    const bool narrow = W <= 4 && g->num_shards <= 1 && !want_stats && dir == LOGOSKG_DIR_AUTO;
+    bool pending = false;
+    if (narrow && (s = narrow_hops(g, r, first_hop, &pending, st)) != LOGOSKG_OK) {
+        (void)hipStreamSynchronize(st);  // (kernels launched ahead may still run on the result's planes)
+        return fail(s);
+    }
+    for (int h = first_hop; !narrow && h <= k; ++h) {
         logoskg_hop_stats &hs = r->stats[h - 1];
         long long rows = (long long)g->h_ctr[C_NROWS];
         long long fedges = (long long)g->h_ctr[C_FEDGES];
         if (rows == 0) break;  // nothing can be reached any more: the remaining levels stay empty
         hs.active_rows = rows;
         hs.frontier_edges = fedges;
-        const bool pull = dir == LOGOSKG_DIR_PULL || (dir == LOGOSKG_DIR_AUTO && fedges * 12 > g->T);
+        const bool pull = dir == LOGOSKG_DIR_PULL || (dir == LOGOSKG_DIR_AUTO && pull_rule(fedges, g->T));
         hs.direction = pull ? LOGOSKG_DIR_PULL : LOGOSKG_DIR_PUSH;
         unsigned long long hc[C_TOTAL] = {};
         memcpy(hc, g->h_ctr, C_STATS * sizeof(hc[0]));
@@ -1495,6 +1603,11 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
     }
     if (want_counts && !r->has_counts) {
         if ((s = count_reached(r, st)) != LOGOSKG_OK) return fail(s);
+    }
+    if (pending) {
+        const unsigned long long *host = g->h_census + (k & 1) * kCensusSlot;
+        if ((s = await_census(host, st)) != LOGOSKG_OK) return fail(s);
+        r->stats[(size_t)k - 1].entities_reached = (long long)host[C_NACTIVE];
     }
 #undef KH
     r->complete = true;
