@@ -226,6 +226,20 @@ static void classify_rows(const std::vector<uint32_t> &off, int32_t E, int hub_m
     }
 }
 
+std::vector<uint32_t> hub_segments(const std::vector<int32_t> &longer, const std::vector<uint32_t> &off, RowClasses *rows) {
+    std::vector<uint32_t> first((size_t)rows->n_hub + 1, 0);
+    rows->n_split = 0;
+    for (size_t i = 0; i + 1 < first.size(); ++i) {
+        const int32_t v = longer[i];
+        const uint32_t n = (off[(size_t)v + 1] - off[v] + kHubSegment - 1) / kHubSegment;
+        first[i + 1] = first[i] + n;
+        rows->n_split += n > 1;
+    }
+    rows->n_hub_segs = first.back();
+    rows->n_split_segs = first[(size_t)rows->n_split];
+    return first;
+}
+
 }  // namespace lkg
 
 using namespace lkg;
@@ -307,6 +321,7 @@ extern "C" logoskg_status logoskg_build(const int32_t *subj, const int32_t *rel,
                 }
                 g->in_rows.n_giant_segs = first.back();
                 LKG_TRY(upload(&g->in_rows.giant_seg_first, first, &g->static_bytes));
+                LKG_TRY(upload(&g->in_rows.hub_seg_first, hub_segments(longer, ioff, &g->in_rows), &g->static_bytes));
             }
             g->in_rows.n_tail = (int64_t)tail.size();
             g->in_rows.n_seg = (int64_t)seg.size();
@@ -441,7 +456,7 @@ extern "C" void logoskg_graph_free(logoskg_graph *g) {
     if (g->ev_rows) (void)hipEventDestroy(g->ev_rows);
 
     void *ptrs[] = {g->out_off, g->out_obj, g->out_rel, g->in_off, g->in_sub, g->in_rel, g->in_eid,
-                    g->in_rows.tail, g->in_rows.seg, g->in_rows.multi, g->in_rows.longrows, g->in_rows.giant_seg_first, g->fr_tail,
+                    g->in_rows.tail, g->in_rows.seg, g->in_rows.multi, g->in_rows.longrows, g->in_rows.giant_seg_first, g->in_rows.hub_seg_first, g->fr_tail,
                     g->fr_seg, g->d_ctr, g->long_index, g->row_pred, g->out_eid, g->plane_buf};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);

@@ -98,6 +98,7 @@ constexpr int kDensePullPercent = 60;   // from this share of the triples leavin
 constexpr int kPredPushShare = 4;       // a level whose frontier holds at most T / this triples: long rows resolved from the subject side
 constexpr int kGiantSegment = 8192;     // a giant row is walked by one 16-wave block per this many entries
 constexpr int kGiantRowMin = 8192;      // hub rows from this size get a 16-wave block in the predecessor pass, smaller ones 4 waves
+constexpr int kHubSegment = 2048;       // hub rows of narrow planes: a block of four wavefronts per this many entries
 constexpr size_t kRowPredBytes = (size_t)8 << 30;  // most the row buffer of the predecessor pass may take
 constexpr int kTileEntities = 64;       // entities per result tile (one wavefront of lanes)
 constexpr int kSuperTiles = 16;         // tiles per super tile (1024 entities)
@@ -147,6 +148,8 @@ struct RowClasses {             // device work lists over the object rows, split
     int64_t n_giant = 0;  // the first n_giant long rows have >= kGiantRowMin entries
     uint32_t *giant_seg_first = nullptr;  // [n_giant + 1] segments of kGiantSegment entries before every giant row
     int64_t n_giant_segs = 0;
+    uint32_t *hub_seg_first = nullptr;  // [n_hub + 1] segments of kHubSegment entries before every hub row
+    int64_t n_hub_segs = 0, n_split = 0, n_split_segs = 0;  // all; rows of several segments (the first ones), and theirs
 };
 
 // ---------------------------------------------------------------- profiling
@@ -443,6 +446,10 @@ struct FillArgs {
     long long n_giant_rows;  // hub rows of the launch that get a 16-wave block per segment (the first ones)
     const uint32_t *giant_seg_first;  // [n_giant_rows + 1]
     long long n_giant_segs;
+    // the hub rows' segments for k_fetch_narrow (hub_seg_first NULL: rows that come range by range)
+    const uint32_t *hub_seg_first;
+    long long n_hub_rows, n_hub_segs, n_split_rows, n_split_segs;
+    int32_t *seg_pred;  // [n_split_segs][64 W]
 };
 
 logoskg_status build_csr_on_device(logoskg_graph *g, const int32_t *subj, const int32_t *rel, const int32_t *obj,
@@ -460,6 +467,9 @@ logoskg_status small_search(logoskg_graph *g, logoskg_result *r, const logoskg_q
                             bool force_push, int *next_hop, hipStream_t st);
 logoskg_status small_fetch(logoskg_result *r, int q0, int q1, int32_t *entity, uint8_t *hop, int32_t *pred,
                            hipStream_t st);
+// the hub rows' segments: the table for rows of these lengths (longest first) and its counts; into the arguments of a fetch
+std::vector<uint32_t> hub_segments(const std::vector<int32_t> &longer, const std::vector<uint32_t> &off, RowClasses *rows);
+void set_hub_segments(FillArgs *a, const RowClasses &rows);
 void drop_walk_tables(logoskg_result *r);
 void launch_lists(Profiler &prof, const FillArgs &a, int W, hipStream_t st);
 void launch_pred(Profiler &prof, const FillArgs &a, int W, long long n_hub_rows, long long n_other_rows, bool mask,

@@ -673,11 +673,11 @@ __device__ __forceinline__ bool any_left(const unsigned long long (&rem)[N]) {
 // Object rows of 33 .. hub_min - 1 entries, a wavefront per row (200 queries with whitelists, 3.4M triples:
 // 102 us with 4-lane groups that took every 16th candidate, a chain of five loads per 64 entries; 53 us now).
 template <int W, int N, bool MASK, bool STATS, bool BUF>
-__global__ void __launch_bounds__(256) k_narrow_wave(FillArgs a, long long first_row, long long n_rows_total) {
+__device__ __forceinline__ void narrow_wave_rows(const FillArgs &a, long long block, long long first_row, long long n_rows_total) {
     constexpr int Qp = 64 * W;
     __shared__ long long slots[BUF ? 1 : 4][BUF ? 1 : 64 * N];
     const int wave = threadIdx.x >> 6, v = lane(), off = W == 16 ? (a.q0 >> 6) & ~(N - 1) : 0;
-    const long long idx = (long long)blockIdx.x * 4 + wave;
+    const long long idx = block * 4 + wave;
     if (idx >= n_rows_total) return;  // wavefront-uniform
     const int ev = a.rows[first_row + idx];
     long long *slot = slots[BUF ? 0 : wave];
@@ -713,6 +713,11 @@ __global__ void __launch_bounds__(256) k_narrow_wave(FillArgs a, long long first
         if (n_edges) atomicAdd(&a.stats_mid[1], (unsigned long long)n_edges);
         if (n_edges) atomicAdd(&a.stats_mid[2], (unsigned long long)n_edges);  // a piece of a line per entry
     }
+}
+
+template <int W, int N, bool MASK, bool STATS, bool BUF>
+__global__ void __launch_bounds__(256) k_narrow_wave(FillArgs a, long long first_row, long long n_rows_total) {
+    narrow_wave_rows<W, N, MASK, STATS, BUF>(a, blockIdx.x, first_row, n_rows_total);
 }
 
 // Longer object rows: a block per (row, hop level), or per segment of a giant row, as k_pred_row; the
@@ -803,13 +808,13 @@ __global__ void __launch_bounds__(1024) k_narrow_row(FillArgs a, long long first
 // by entity), then every entity whose object row has at most 32 entries is walked by a W-lane group, U
 // entries gathered together and resolved in order.  Longer rows are left to the row kernels.
 template <int W, bool MASK, bool STATS>
-__global__ void __launch_bounds__(256) k_pred_narrow(FillArgs a) {
+__device__ __forceinline__ void narrow_tiles(const FillArgs &a, unsigned block, unsigned nblocks) {
     constexpr int TPB = 4 / W, U = MASK ? 2 : 8;  // (65 queries with whitelists, 20M triples: call 587 us with eight, 549 with four, 547 with two)
     static_assert(W == 1 || W == 4, "a block of four wavefronts");
     __shared__ unsigned long long mT[4][64];  // per wavefront, i.e. (tile, word): entities each query reached
     __shared__ long long base[4][64];         // and where its run of the tile starts in the lists
     const int t = threadIdx.x, wave = t >> 6, v = lane();
-    const long long tile_rel = xcd_contiguous(blockIdx.x, gridDim.x) * TPB + wave / W;
+    const long long tile_rel = xcd_contiguous(block, nblocks) * TPB + wave / W;
     const bool valid = tile_rel < a.tile_count;
     const long long tile = a.tile_begin + tile_rel;
     const int word = wave % W;
@@ -914,6 +919,106 @@ __global__ void __launch_bounds__(256) k_pred_narrow(FillArgs a) {
             if (n_edges) atomicAdd(&a.stats_pred[2], (unsigned long long)n_edges);
         }
     }
+}
+
+template <int W, bool MASK, bool STATS>
+__global__ void __launch_bounds__(256) k_pred_narrow(FillArgs a) { narrow_tiles<W, MASK, STATS>(a, blockIdx.x, gridDim.x); }
+
+// One level of one segment (kHubSegment entries) of a hub row, a block of four wavefronts; as k_narrow_row.  A row of one
+// segment is written to the lists.  Of a split row every segment leaves its smallest triple index per query (INT_MAX:
+// none) in a line of a.seg_pred, and k_split_lists takes the minimum over them: nothing to fill before, no atomics.
+template <int W, bool MASK>
+__device__ __forceinline__ void narrow_hub_segment(const FillArgs &a, long long seg, int h) {
+    constexpr int Qp = 64 * W, C = kNarrowChunks, NW = 4;
+    __shared__ long long slot[Qp];
+    __shared__ unsigned int smin[Qp];
+    __shared__ unsigned long long srem[W];
+    long long row_i = 0, row_end = a.n_hub_rows;  // the last row whose first segment is <= seg
+    while (row_end - row_i > 1) {
+        const long long m = (row_i + row_end) >> 1;
+        if (a.hub_seg_first[m] <= (unsigned long long)seg) row_i = m; else row_end = m;
+    }
+    const int ev = a.rows[row_i], t = threadIdx.x, wave = t >> 6, v = lane();
+    unsigned long long lev[W];
+    if (!narrow_level<W, W>(a, ev, h, 0, lev)) return;  // block-uniform
+    const bool split = row_i < a.n_split_rows;
+    if (!split) row_slots<W>(a, ev, wave, NW, slot, W, 0);
+    const uint32_t row_hi = a.in_off[ev + 1];
+    const uint32_t lo = a.in_off[ev] + (uint32_t)(seg - a.hub_seg_first[row_i]) * (uint32_t)kHubSegment;
+    const uint32_t hi = min(row_hi, lo + (uint32_t)kHubSegment);
+    if (t < Qp) smin[t] = ~0u;  // (Qp <= 256 threads)
+    if (t < W) {
+        unsigned long long x = lev[0];
+#pragma unroll
+        for (int w = 1; w < W; ++w)
+            if (w == t) x = lev[w];
+        srem[t] = x;
+    }
+    __syncthreads();
+    const unsigned long long *prev = a.levels + (size_t)(h - 1) * a.plane;
+    uint32_t span = 64u * NW;  // the first step is one chunk per wavefront: on a dense frontier it resolves most queries
+    for (uint32_t s0 = lo; s0 < hi; s0 += span, span = 64u * C * NW) {
+        unsigned long long rem[W];
+        uint32_t best[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            rem[w] = uniform64(srem[w]);
+            best[w] = ~0u;
+        }
+        if (!any_left<W>(rem)) break;  // the same words in every wavefront
+        const uint32_t step_hi = min(hi, s0 + span), first = s0 + 64u * wave;
+        if (first < step_hi) narrow_resolve<W, W, MASK>(a, prev, 0, first, 64u * NW, step_hi, rem, best);
+#pragma unroll
+        for (int w = 0; w < W; ++w)
+            if (best[w] != ~0u) atomicMin(&smin[w * 64 + v], best[w]);
+        __syncthreads();
+        if (v == 0) {
+#pragma unroll
+            for (int w = 0; w < W; ++w) atomicAnd(&srem[w], rem[w]);
+        }
+        __syncthreads();
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        if ((w % NW) != wave || !((lev[w] >> v) & 1ull)) continue;
+        const int32_t eid = entry_id(a, smin[w * 64 + v]);
+        if (split) a.seg_pred[(size_t)seg * Qp + w * 64 + v] = eid;
+        else a.pred[slot[w * 64 + v]] = eid;
+    }
+}
+
+// The whole fetch of a narrow batch: hub rows (a block per segment and level, the longest first), rows of 33 .. hub_min - 1
+// entries (four per block), tiles.  All three are chains of dependent loads over data that the caches hold and write
+// different places of the lists, and none fills the GPU: in launches of their own the five kernels of one question on
+// 3.4M triples took 60 us, those of 200 questions with whitelists 195.
+template <int W, bool MASK>
+__global__ void __launch_bounds__(256) k_fetch_narrow(FillArgs a, unsigned hub_blocks, unsigned mid_blocks, long long n_mid) {
+    if (blockIdx.x < hub_blocks) narrow_hub_segment<W, MASK>(a, blockIdx.x / (unsigned)a.k, (int)(blockIdx.x % (unsigned)a.k) + 1);
+    else if (blockIdx.x < hub_blocks + mid_blocks) narrow_wave_rows<W, W, MASK, false, false>(a, blockIdx.x - hub_blocks, a.n_hub_rows, n_mid);
+    else narrow_tiles<W, MASK, false>(a, blockIdx.x - hub_blocks - mid_blocks, gridDim.x - hub_blocks - mid_blocks);
+}
+
+// The split rows' predecessors: a block per row.
+template <int W>
+__global__ void __launch_bounds__(256) k_split_lists(FillArgs a) {
+    constexpr int Qp = 64 * W;
+    __shared__ long long slot[Qp];
+    __shared__ int best[Qp];
+    const int ev = a.rows[blockIdx.x], t = threadIdx.x, q = t % Qp, w = q >> 6;
+    const unsigned long long x = a.visited[(size_t)ev * W + w] & ~a.levels[(size_t)ev * W + w] & range_bits(a.q0, a.q1, w);
+    const bool on = (x >> (q & 63)) & 1ull;  // (seeds have their -1 from the tiles)
+    if (t < Qp) best[t] = INT_MAX;
+    row_slots<W>(a, ev, t >> 6, 4, slot);
+    __syncthreads();
+    const uint32_t s0 = a.hub_seg_first[blockIdx.x], s1 = a.hub_seg_first[blockIdx.x + 1];
+    int m = INT_MAX;
+    if (on)
+#pragma unroll 8
+        for (uint32_t s = s0 + t / Qp; s < s1; s += 256 / Qp) m = min(m, a.seg_pred[(size_t)s * Qp + q]);
+    if (m != INT_MAX) atomicMin(&best[q], m);
+    __syncthreads();
+    if (t < Qp && on) a.pred[slot[q]] = best[q];
 }
 
 // 16-word planes without the bit-sliced pass (k > 6, or no room for its buffer).
@@ -1776,6 +1881,14 @@ static logoskg_status count_plane(logoskg_result *r, const unsigned long long *p
     return LOGOSKG_OK;
 }
 
+void set_hub_segments(FillArgs *a, const RowClasses &rows) {
+    a->hub_seg_first = rows.hub_seg_first;
+    a->n_hub_rows = rows.n_hub;
+    a->n_hub_segs = rows.n_hub_segs;
+    a->n_split_rows = rows.n_split;
+    a->n_split_segs = rows.n_split_segs;
+}
+
 logoskg_status count_reached(logoskg_result *r, hipStream_t st) {
     LKG_TRY(count_plane(r, r->visited, &r->tile_base, &r->super_base, &r->mega_base, &r->d_reached_off,
                         &r->reached_off, st));
@@ -2009,10 +2122,41 @@ static void launch_rows(Profiler &prof, const FillArgs &a, long long n_hub_rows,
     if (hubs > 0) rows(a, giants, hubs, hubs * levels < 2048 ? 1024u : 256u);
 }
 
+// A narrow batch's fetch in two launches: true when it was issued.  Split rows merge in a buffer of the pool; without one
+// (no room, or a capture) the kernels run one by one.
+template <int W, bool MASK>
+static bool launch_fetch_narrow(Profiler &prof, FillArgs a, long long n_hub_rows, long long n_other_rows, hipStream_t st) {
+    logoskg_graph *g = static_cast<logoskg_graph *>(a.host_graph);
+    if (!a.hub_seg_first || n_hub_rows != a.n_hub_rows) return false;
+    const bool rows = a.k > 0;  // (seeds only: no level 1, no predecessors)
+    void *buf = nullptr;
+    if (rows && a.n_split_rows > 0) {
+        if (captured(st) || g->pool.alloc(&buf, (size_t)a.n_split_segs * Qp_of<W>() * sizeof(int32_t), st) != LOGOSKG_OK) return false;
+        a.seg_pred = static_cast<int32_t *>(buf);
+    }
+    {
+        ProfScope ps(prof, KK_PRED, st);
+        const long long hub = rows ? a.n_hub_segs * a.k : 0;
+        const long long mid = ((rows ? (n_other_rows + 3) / 4 : 0) + hub + 7) / 8 * 8 - hub;  // (the tiles' XCDs)
+        const long long tiles = ((a.tile_count * W + 3) / 4 + 7) / 8 * 8;
+        k_fetch_narrow<W, MASK><<<dim3((unsigned)(hub + mid + tiles)), dim3(256), 0, st>>>(a, (unsigned)hub, (unsigned)mid,
+                                                                                        rows ? n_other_rows : 0);
+    }
+    if (buf) {
+        ProfScope ps(prof, KK_PRED_HUB, st);
+        k_split_lists<W><<<dim3((unsigned)a.n_split_rows), dim3(256), 0, st>>>(a);
+        const bool zeroed[1] = {false};
+        g->pool.release_after(&buf, zeroed, 1, st);
+    }
+    return true;
+}
+
 template <int W, bool MASK, bool STATS>
 static void launch_pred_wms(Profiler &prof, const FillArgs &a0, long long n_hub_rows, long long n_other_rows,
                             hipStream_t st_tiles, hipStream_t st_hub) {
     FillArgs a = a0;
+    if constexpr (W <= 4 && !STATS)
+        if (st_tiles == st_hub && launch_fetch_narrow<W, MASK>(prof, a, n_hub_rows, n_other_rows, st_tiles)) return;
     const bool mt = pred_uses_staged_kernel(a, W);
     if (!mt) a.row_pred = nullptr;
     if (!mt || W != 16 || STATS) a.push_levels = 0;
@@ -2235,6 +2379,7 @@ extern "C" logoskg_status logoskg_result_fetch(logoskg_result *r, int32_t q0, in
     a.n_giant_rows = g->in_rows.n_giant;  // (a sharded graph: set per object range)
     a.giant_seg_first = g->in_rows.giant_seg_first;
     a.n_giant_segs = g->in_rows.n_giant_segs;
+    if (g->num_shards <= 1) set_hub_segments(&a, g->in_rows);
     a.host_graph = g;
     a.host_result = r;
     if (pred && W == 16) {

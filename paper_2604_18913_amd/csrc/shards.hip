@@ -240,7 +240,7 @@ void free_shards(logoskg_graph *g) {
         for (auto p : ss->slot_rel) if (p) (void)hipFree(p);
     }
     for (void *p : {(void *)ss->all_obj, (void *)ss->all_sub, (void *)ss->all_eid, (void *)ss->all_out_rel,
-                    (void *)ss->all_in_rel, (void *)ss->sorted_longrows, (void *)ss->sorted_giant_first})
+                    (void *)ss->all_in_rel, (void *)ss->sorted_longrows, (void *)ss->sorted_giant_first, (void *)ss->all_rows.hub_seg_first})
         if (p) (void)hipFree(p);
     for (auto e : ss->slot_ready) if (e) (void)hipEventDestroy(e);
     for (auto e : ss->slot_idle) if (e) (void)hipEventDestroy(e);
@@ -447,6 +447,10 @@ static logoskg_status build_in_chunks(logoskg_graph *g, ShardSet *ss, const int3
         g->static_bytes += longrows.size() * sizeof(int32_t) + first.size() * sizeof(uint32_t);
         ss->all_rows.longrows = ss->sorted_longrows;
         ss->all_rows.giant_seg_first = ss->sorted_giant_first;
+        const std::vector<uint32_t> hub_first = hub_segments(longrows, ioff, &ss->all_rows);
+        LKG_HIP(hipMalloc((void **)&ss->all_rows.hub_seg_first, hub_first.size() * sizeof(uint32_t)));
+        LKG_HIP(hipMemcpy(ss->all_rows.hub_seg_first, hub_first.data(), hub_first.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
+        g->static_bytes += hub_first.size() * sizeof(uint32_t);
     }
     return LOGOSKG_OK;
 }
@@ -527,6 +531,7 @@ logoskg_status sharded_pred(logoskg_graph *g, FillArgs *a, int W, bool mask, hip
         x.n_giant_rows = all->n_giant;
         x.giant_seg_first = all->giant_seg_first;
         x.n_giant_segs = all->n_giant_segs;
+        set_hub_segments(&x, *all);
         launch_pred(g->prof, x, W, all->n_hub, all->n_long - all->n_hub, mask, st, st);
         return LOGOSKG_OK;
     }

@@ -1,0 +1,39 @@
+"""Lists of narrow batches (one and four words per entity) where hub rows are cut into segments: rows at the edges of a
+segment and of the classes, every hop level in one launch, pages, joined shards, and a recorded fetch."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+ROWS = [33, 1023, 1024, 2047, 2048, 2049, 4096, 4097, 9000, 20481]
+
+
+@pytest.mark.parametrize("shards", [0, 3])
+@pytest.mark.parametrize("hub_min", [0, 40, 3000])
+@pytest.mark.parametrize("Q, k, masked", [(1, 3, False), (64, 0, False), (64, 2, True), (65, 3, False), (256, 3, True)])
+def test_hub_rows_in_segments(Q, k, masked, hub_min, shards):
+    import paper_2604_18913_amd as lkg
+    rng = np.random.default_rng(Q + hub_min)
+    E, R = 6007, 11
+    o = np.concatenate([np.repeat(rng.permutation(E)[:len(ROWS)], ROWS), rng.integers(0, E, 9000)]).astype(np.int32)
+    s = np.where(rng.random(o.size) < 0.2, rng.integers(0, 40, o.size), rng.integers(0, E, o.size)).astype(np.int32)
+    p = rng.permutation(o.size)
+    s, o = s[p], o[p]
+    r = rng.integers(0, R, o.size).astype(np.int32)
+    off = np.arange(Q + 1, dtype=np.int64)
+    seeds = rng.integers(0, E, Q).astype(np.int32)
+    mask = rng.integers(0, 2**R, (Q, 1)).astype(np.uint64) if masked else None
+    g = lkg.Graph(s, r, o, E, R, hub_min_degree=hub_min, num_shards=shards)
+    res = g.khop(off, seeds, k, mask, direction="pull")  # (a small search would not come by here)
+    want = oracle.khop(E, s, r, o, off, seeds, k, mask)
+    assert np.array_equal(res.offsets(), want[0])
+    for q0, q1 in {(0, Q), (Q // 2, Q), (Q // 3, Q // 3 + 1)}:
+        a, b = want[0][q0], want[0][q1]
+        for got, w in zip(res.fetch(q0, q1), want[1:]):
+            assert np.array_equal(got.cpu().numpy(), w[a:b])
+    _, hop, pred = res.fetch(want_hop=False)
+    assert hop is None and np.array_equal(pred.cpu().numpy(), want[3])
+    res.close()
+    g.close()
