@@ -416,6 +416,12 @@ extern "C" logoskg_status logoskg_build(const int32_t *subj, const int32_t *rel,
     if ((st = dev_alloc((void **)&g->fr_tail, (size_t)E * sizeof(int32_t))) != LOGOSKG_OK) return fail(st);
     if ((st = dev_alloc((void **)&g->fr_seg, (size_t)g->fr_seg_cap * sizeof(RowSegment))) != LOGOSKG_OK) return fail(st);
     if ((st = dev_alloc((void **)&g->d_ctr, (C_TOTAL + kCensusWords * kCensusBlocks) * sizeof(unsigned long long))) != LOGOSKG_OK) return fail(st);
+    const size_t ticket_bytes = (size_t)(g->Epad / (kTileEntities * kSuperTiles * kMegaSupers) + 2) * sizeof(unsigned int);
+    if ((st = dev_alloc((void **)&g->count_tickets, ticket_bytes)) != LOGOSKG_OK) return fail(st);
+    if (hipMemset(g->count_tickets, 0, ticket_bytes) != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess) {
+        set_error("hipMemset failed");
+        return fail(LOGOSKG_EDEVICE);
+    }
     constexpr size_t ctr_bytes = (C_TOTAL + 1 + 2 * kCensusSlot) * sizeof(unsigned long long), off_bytes = (LOGOSKG_MAX_QUERIES + 1) * sizeof(long long);
     static_assert(alignof(SmallReport) <= 8, "it lies behind 8-byte words");
     if (hipHostMalloc((void **)&g->h_ctr, ctr_bytes + off_bytes + sizeof(SmallReport), hipHostMallocDefault) != hipSuccess) {
@@ -457,7 +463,7 @@ extern "C" void logoskg_graph_free(logoskg_graph *g) {
 
     void *ptrs[] = {g->out_off, g->out_obj, g->out_rel, g->in_off, g->in_sub, g->in_rel, g->in_eid,
                     g->in_rows.tail, g->in_rows.seg, g->in_rows.multi, g->in_rows.longrows, g->in_rows.giant_seg_first, g->in_rows.hub_seg_first, g->fr_tail,
-                    g->fr_seg, g->d_ctr, g->long_index, g->row_pred, g->out_eid, g->plane_buf};
+                    g->fr_seg, g->d_ctr, g->count_tickets, g->long_index, g->row_pred, g->out_eid, g->plane_buf};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     if (g->h_ctr) (void)hipHostFree(g->h_ctr);

@@ -225,6 +225,7 @@ struct logoskg_graph {
     lkg::RowSegment *fr_seg = nullptr;   // [fr_seg_cap] segments of the longer frontier rows
     int64_t fr_seg_cap = 0;
     unsigned long long *d_ctr = nullptr;  // device counters (see khop.hip)
+    unsigned int *count_tickets = nullptr;  // [mega tiles + 1] zero between two counts (result.hip)
     // pinned host memory, one block (three allocations: 0.44 ms for a graph of 50,000 triples, 0.41 with one):
     unsigned long long *h_ctr = nullptr;  // mirror of the counters
     long long *h_off = nullptr;           // [LOGOSKG_MAX_QUERIES + 1]: offsets of the last count
