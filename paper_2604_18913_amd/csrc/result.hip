@@ -1369,7 +1369,7 @@ k_page_planes(const unsigned long long *__restrict__ levels, long long plane, co
 template <int NB, bool MASK, bool STATS, int G>
 __global__ void __launch_bounds__(256)
 k_pred_walk(FillArgs a, unsigned long long *__restrict__ codes, unsigned long long *__restrict__ visbuf,
-            long long tile0, long long ntile, int w0, int nw, int wb) {
+            long long tile0, long long ntile, int w0, int nw, int wb, int sparse) {
     constexpr int W = 16;
     constexpr int EPB = 256 / G;         // entities per block (a divisor of 64: one tile per block)
     constexpr unsigned GMASK = (1u << G) - 1u;
@@ -1517,6 +1517,8 @@ k_pred_walk(FillArgs a, unsigned long long *__restrict__ codes, unsigned long lo
 #pragma unroll
         for (int b = 0; b < NB; ++b) reached |= H[b];
         visbuf[((size_t)tile_rel * nw + (lw - w0)) * 64 + vi] = reached;
+        if (!sparse || reached)  // (k_emit_sparse reads no codes of words that hold nothing)
+        {
         unsigned long long P[8];
 #pragma unroll
         for (int b = 0; b < 8; ++b) P[b] = 0;
@@ -1549,6 +1551,7 @@ k_pred_walk(FillArgs a, unsigned long long *__restrict__ codes, unsigned long lo
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) out[i] = make_uint4(d[4 * i], d[4 * i + 1], d[4 * i + 2], d[4 * i + 3]);
+        }
     }
     if (STATS) {
         n_rows = wave_sum(n_rows);
@@ -1801,6 +1804,92 @@ k_pred_emit(FillArgs a, const unsigned long long *__restrict__ codes, const unsi
             }
         }
         __syncthreads();  // rp_tab is rewritten for the next word
+    }
+}
+
+// The lists of a batch whose words are mostly empty (whitelists, early hops): a wavefront per word of a tile, lane = entity,
+// nothing shared between the wavefronts.  k_pred_emit goes through all queries of a word for all of a block's 1,024
+// entities, whoever reached what, and reads every code byte; here a lane takes the set bits of its own word one after the
+// other (where a query reached eight and more of the tile's entities, the wavefront takes the query), four at a time so
+// that their codes, and then their triple indices, are requested together.  It is bound by these chains and by the
+// scattered pieces of the lists it writes, which is why it loses to k_pred_emit where words are full.
+// Fetches of 1,024 queries, us k_pred_emit / k_emit_sparse, by the share of (listed entity, query) pairs that are reached:
+// 0.3 % 1,154 / 580, 0.4 % 614 / 450, 0.7 % 1,447 / 911, 3.9 % 1,473 / 1,396, 5.2 % 1,766 / 1,764, 8 % 1,059 / 1,162,
+// 22 % 1,885 / 2,164, 58 % 1,669 / 2,377: the line lies at 5 %.  (30M triples with whitelists, 3.9 %: lists 684 -> 482 us, and
+// the row walk, which writes no codes of empty words, 793 -> 749.)
+constexpr int kSparseShare = 20;   // reached pairs: at most one in this many
+constexpr int kHeavyEntities = 8;  // (4 and 16: within 2 %)
+
+__global__ void __launch_bounds__(256)
+k_emit_sparse(FillArgs a, const uint8_t *__restrict__ codes, const unsigned long long *__restrict__ visbuf, long long tile0,
+              long long ntile, int w0, int nw) {
+    constexpr int Qp = 1024, U = 4;
+    __shared__ unsigned long long mT[4][64];  // entities of the tile each query reached
+    __shared__ long long base[4][64];         // where its run of the tile starts in the lists
+    const int wave = threadIdx.x >> 6, v = lane();
+    const long long item = xcd_contiguous(blockIdx.x, gridDim.x) * 4 + wave;  // neighbouring tiles of a word together
+    if (item >= ntile * nw) return;  // wavefront-uniform
+    const long long tile_rel = item % ntile, tile = tile0 + tile_rel;
+    const int wi = (int)(item / ntile), w = w0 + wi;
+    const size_t at = ((size_t)tile_rel * nw + wi) * 64 + v;
+    const unsigned long long vis = visbuf[at];
+    if (!wave_any(vis != 0)) return;
+    const unsigned long long reached = transpose64(vis);
+    const int ql = w * 64 + v;
+    if (reached) base[wave][v] = super_start(a, tile / kSuperTiles, Qp, ql) + a.tile_base[(size_t)tile * Qp + ql];
+    mT[wave][v] = reached;
+    __builtin_amdgcn_wave_barrier();
+    const int32_t ev = (int32_t)tile_entity(a.tile_ent, tile, v, a.E);
+    uint32_t lo = 0, hi = 0;
+    if (vis) {
+        lo = a.in_off[ev];
+        hi = a.in_off[ev + 1];
+    }
+    const bool longrow = hi - lo > (uint32_t)kTailMaxDegree;
+    // a lane's predecessors: by place in its short row, or by query in its line of row_pred, or written by the row kernels
+    const int32_t *from = a.in_eid + lo;
+    if (longrow) from = a.row_pred && vis ? a.row_pred + (size_t)(a.long_index[ev] - a.row_base) * Qp + w * 64 : nullptr;
+    const unsigned long long below = (1ull << v) - 1ull;
+    const uint8_t *my_codes = codes + at * 64;
+    auto put = [&](const int (&qq)[U]) {  // (-1: nothing)
+        uint32_t code[U];
+        int32_t val[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) code[u] = qq[u] >= 0 ? my_codes[qq[u]] : 1u;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            val[u] = -1;  // seeds
+            if ((code[u] & 7u) > 1u && from) val[u] = from[longrow ? qq[u] : (int)(code[u] >> 3)];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (qq[u] < 0) continue;
+            const long long p = base[wave][qq[u]] + __popcll(mT[wave][qq[u]] & below);
+            a.entity[p] = ev;
+            if (a.hop) a.hop[p] = (uint8_t)((code[u] & 7u) - 1u);
+            if (from || (code[u] & 7u) == 1u) a.pred[p] = val[u];
+        }
+    };
+    // queries that reached many of the tile's entities: a lane per entity; the others: every lane its own
+    const unsigned long long heavy = __ballot(__popcll(reached) >= kHeavyEntities);
+    for (unsigned long long m = heavy; m;) {
+        int qq[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int q = m ? __ffsll((long long)m) - 1 : -1;
+            m &= m - 1;
+            qq[u] = q >= 0 && ((vis >> (q & 63)) & 1ull) ? q : -1;
+        }
+        put(qq);
+    }
+    for (unsigned long long left = vis & ~heavy; left;) {
+        int qq[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            qq[u] = left ? __ffsll((long long)left) - 1 : -1;
+            left &= left - 1;
+        }
+        put(qq);
     }
 }
 
@@ -2413,24 +2502,27 @@ static void launch_pred_wms(Profiler &prof, const FillArgs &a0, long long n_hub_
                 const int wb = w0 & ~3;
                 if (nw == 1) {  // one word: a lane per entity (64 entities per wavefront)
                     dim3 g1((unsigned)(((n + 3) / 4 + 7) / 8 * 8));  // 256 entities per block
-                    if (a.k <= 2) k_pred_walk<2, MASK, STATS, 1><<<g1, dim3(256), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, w0);
-                    else k_pred_walk<3, MASK, STATS, 1><<<g1, dim3(256), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, w0);
+                    if (a.k <= 2) k_pred_walk<2, MASK, STATS, 1><<<g1, dim3(256), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, w0, a.sparse);
+                    else k_pred_walk<3, MASK, STATS, 1><<<g1, dim3(256), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, w0, a.sparse);
                 } else if (w0 >> 1 == (w0 + nw - 1) >> 1) {  // two aligned words
                     dim3 g2((unsigned)(((n + 1) / 2 + 7) / 8 * 8));  // 128 entities per block
-                    if (a.k <= 2) k_pred_walk<2, MASK, STATS, 2><<<g2, dim3(256), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, w0 & ~1);
-                    else k_pred_walk<3, MASK, STATS, 2><<<g2, dim3(256), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, w0 & ~1);
+                    if (a.k <= 2) k_pred_walk<2, MASK, STATS, 2><<<g2, dim3(256), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, w0 & ~1, a.sparse);
+                    else k_pred_walk<3, MASK, STATS, 2><<<g2, dim3(256), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, w0 & ~1, a.sparse);
                 } else if (w0 + nw <= wb + 4) {
                     dim3 g4((unsigned)((n + 7) / 8 * 8));  // 64 entities per block
-                    if (a.k <= 2) k_pred_walk<2, MASK, STATS, 4><<<g4, dim3(256), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, wb);
-                    else k_pred_walk<3, MASK, STATS, 4><<<g4, dim3(256), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, wb);
+                    if (a.k <= 2) k_pred_walk<2, MASK, STATS, 4><<<g4, dim3(256), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, wb, a.sparse);
+                    else k_pred_walk<3, MASK, STATS, 4><<<g4, dim3(256), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, wb, a.sparse);
                 } else {
-                    if (a.k <= 2) k_pred_walk<2, MASK, STATS, 16><<<gw, dim3(256), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, 0);
-                    else k_pred_walk<3, MASK, STATS, 16><<<gw, dim3(256), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, 0);
+                    if (a.k <= 2) k_pred_walk<2, MASK, STATS, 16><<<gw, dim3(256), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, 0, a.sparse);
+                    else k_pred_walk<3, MASK, STATS, 16><<<gw, dim3(256), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, 0, a.sparse);
                 }
             }
             if (rows_first && c0 == 0) (void)hipStreamWaitEvent(st_tiles, (hipEvent_t)a.ev_rows, 0);
             ProfScope ps(prof, KK_PRED, st_tiles);
-            k_pred_emit<<<ge, dim3(kEmitTiles * 64), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, wsplit,
+            if (a.sparse)
+                k_emit_sparse<<<dim3((unsigned)(((n * nw + 3) / 4 + 7) / 8 * 8)), dim3(256), 0, st_tiles>>>(
+                    a, reinterpret_cast<const uint8_t *>(a.plane_buf), visbuf, t0, n, w0, nw);
+            else k_pred_emit<<<ge, dim3(kEmitTiles * 64), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, wsplit,
                                                                    a.emit_eid_cap, a.emit_line_cap);
             if (prof.on) {  // entities x words whose code bytes pass from the first kernel to the second
                 prof.acc[KK_PRED_WALK].units[3] += n * 64 * nw;
@@ -2568,6 +2660,10 @@ extern "C" logoskg_status logoskg_result_fetch(logoskg_result *r, int32_t q0, in
         }
     }
     a.entity = entity; a.hop = hop; a.pred = pred;
+    {   // mostly empty words: the lists by k_emit_sparse
+        const long long words = (q1 - 1) / 64 - q0 / 64 + 1;
+        a.sparse = need * kSparseShare <= a.ntiles * 64 * 64 * words;
+    }
     const bool counting = g->prof.counters;
     // levels whose frontier holds at most a quarter of the triples: their long rows are resolved from the
     // subject side (resident graphs, row buffer in use, minimum-hop search); needs the triple index of
