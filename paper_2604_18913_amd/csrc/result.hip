@@ -2385,6 +2385,10 @@ static bool launch_fetch_narrow(Profiler &prof, FillArgs a, long long n_hub_rows
     logoskg_graph *g = static_cast<logoskg_graph *>(a.host_graph);
     if (!a.hub_seg_first || n_hub_rows != a.n_hub_rows) return false;
     const bool rows = a.k > 0;  // (seeds only: no level 1, no predecessors)
+    const long long hub = rows ? a.n_hub_segs * a.k : 0;
+    const long long mid = ((rows ? (n_other_rows + 3) / 4 : 0) + hub + 7) / 8 * 8 - hub;  // (the tiles' XCDs)
+    const long long tiles = ((a.tile_count * W + 3) / 4 + 7) / 8 * 8;
+    if ((hub + mid + tiles) * 256 > (long long)UINT32_MAX) return false;  // (a launch holds fewer threads; deep searches)
     void *buf = nullptr;
     if (rows && a.n_split_rows > 0) {
         if (captured(st) || g->pool.alloc(&buf, (size_t)a.n_split_segs * Qp_of<W>() * sizeof(int32_t), st) != LOGOSKG_OK) return false;
@@ -2392,9 +2396,6 @@ static bool launch_fetch_narrow(Profiler &prof, FillArgs a, long long n_hub_rows
     }
     {
         ProfScope ps(prof, KK_PRED, st);
-        const long long hub = rows ? a.n_hub_segs * a.k : 0;
-        const long long mid = ((rows ? (n_other_rows + 3) / 4 : 0) + hub + 7) / 8 * 8 - hub;  // (the tiles' XCDs)
-        const long long tiles = ((a.tile_count * W + 3) / 4 + 7) / 8 * 8;
         k_fetch_narrow<W, MASK><<<dim3((unsigned)(hub + mid + tiles)), dim3(256), 0, st>>>(a, (unsigned)hub, (unsigned)mid,
                                                                                         rows ? n_other_rows : 0);
     }

@@ -37,3 +37,21 @@ def test_hub_rows_in_segments(Q, k, masked, hub_min, shards):
     assert hop is None and np.array_equal(pred.cpu().numpy(), want[3])
     res.close()
     g.close()
+
+
+def test_more_threads_than_a_launch_takes():
+    """Every row is a hub row and has a block per hop level: 66,100 rows x 254 hops x 256 threads pass 2^32."""
+    import paper_2604_18913_amd as lkg
+    n, d, k = 66_100, 33, 254
+    s = np.repeat(np.arange(d, dtype=np.int32), n)
+    o = np.tile(np.arange(d, d + n, dtype=np.int32), d)
+    r = np.zeros(s.size, dtype=np.int32)
+    off, seeds = np.array([0, 2], dtype=np.int64), np.array([3, 20], dtype=np.int32)
+    g = lkg.Graph(s, r, o, d + n, 1, hub_min_degree=d)
+    res = g.khop(off, seeds, k, direction="pull")
+    want = oracle.khop(d + n, s, r, o, off, seeds, k)
+    assert np.array_equal(res.offsets(), want[0])
+    for got, w in zip(res.fetch(), want[1:]):
+        assert np.array_equal(got.cpu().numpy(), w)
+    res.close()
+    g.close()
