@@ -226,18 +226,23 @@ static void classify_rows(const std::vector<uint32_t> &off, int32_t E, int hub_m
     }
 }
 
-std::vector<uint32_t> hub_segments(const std::vector<int32_t> &longer, const std::vector<uint32_t> &off, RowClasses *rows) {
-    std::vector<uint32_t> first((size_t)rows->n_hub + 1, 0);
+std::vector<uint32_t> append_hub_segments(std::vector<uint32_t> table, const std::vector<int32_t> &longer,
+                                          const std::vector<uint32_t> &off, RowClasses *rows) {
     rows->n_split = 0;
-    for (size_t i = 0; i + 1 < first.size(); ++i) {
-        const int32_t v = longer[i];
+    rows->n_split_segs = 0;
+    uint32_t first = 0;
+    table.push_back(first);
+    for (int64_t i = 0; i < rows->n_hub; ++i) {
+        const int32_t v = longer[(size_t)i];
         const uint32_t n = (off[(size_t)v + 1] - off[v] + kHubSegment - 1) / kHubSegment;
-        first[i + 1] = first[i] + n;
-        rows->n_split += n > 1;
+        table.push_back(first += n);
+        if (n > 1) {
+            ++rows->n_split;
+            rows->n_split_segs = first;  // (longest first: the split rows come before the others)
+        }
     }
-    rows->n_hub_segs = first.back();
-    rows->n_split_segs = first[(size_t)rows->n_split];
-    return first;
+    rows->n_hub_segs = first;
+    return table;
 }
 
 }  // namespace lkg
@@ -320,8 +325,8 @@ extern "C" logoskg_status logoskg_build(const int32_t *subj, const int32_t *rel,
                     first[(size_t)i + 1] = first[(size_t)i] + (ioff[(size_t)v + 1] - ioff[v] + kGiantSegment - 1) / kGiantSegment;
                 }
                 g->in_rows.n_giant_segs = first.back();
-                LKG_TRY(upload(&g->in_rows.giant_seg_first, first, &g->static_bytes));
-                LKG_TRY(upload(&g->in_rows.hub_seg_first, hub_segments(longer, ioff, &g->in_rows), &g->static_bytes));
+                LKG_TRY(upload(&g->in_rows.giant_seg_first, append_hub_segments(first, longer, ioff, &g->in_rows), &g->static_bytes));
+                g->in_rows.hub_seg_first = g->in_rows.giant_seg_first + g->in_rows.n_giant + 1;
             }
             g->in_rows.n_tail = (int64_t)tail.size();
             g->in_rows.n_seg = (int64_t)seg.size();
@@ -415,9 +420,10 @@ extern "C" logoskg_status logoskg_build(const int32_t *subj, const int32_t *rel,
     g->fr_seg_cap = (int64_t)E + T / kPushSegment + 64;  // every long row adds < deg/segment + 1 items
     if ((st = dev_alloc((void **)&g->fr_tail, (size_t)E * sizeof(int32_t))) != LOGOSKG_OK) return fail(st);
     if ((st = dev_alloc((void **)&g->fr_seg, (size_t)g->fr_seg_cap * sizeof(RowSegment))) != LOGOSKG_OK) return fail(st);
-    if ((st = dev_alloc((void **)&g->d_ctr, (C_TOTAL + kCensusWords * kCensusBlocks) * sizeof(unsigned long long))) != LOGOSKG_OK) return fail(st);
+    constexpr size_t dev_ctr = C_TOTAL + kCensusWords * kCensusBlocks;
     const size_t ticket_bytes = (size_t)(g->Epad / (kTileEntities * kSuperTiles * kMegaSupers) + 2) * sizeof(unsigned int);
-    if ((st = dev_alloc((void **)&g->count_tickets, ticket_bytes)) != LOGOSKG_OK) return fail(st);
+    if ((st = dev_alloc((void **)&g->d_ctr, dev_ctr * sizeof(unsigned long long) + ticket_bytes)) != LOGOSKG_OK) return fail(st);
+    g->count_tickets = reinterpret_cast<unsigned int *>(g->d_ctr + dev_ctr);
     if (hipMemset(g->count_tickets, 0, ticket_bytes) != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess) {
         set_error("hipMemset failed");
         return fail(LOGOSKG_EDEVICE);
@@ -462,8 +468,8 @@ extern "C" void logoskg_graph_free(logoskg_graph *g) {
     if (g->ev_rows) (void)hipEventDestroy(g->ev_rows);
 
     void *ptrs[] = {g->out_off, g->out_obj, g->out_rel, g->in_off, g->in_sub, g->in_rel, g->in_eid,
-                    g->in_rows.tail, g->in_rows.seg, g->in_rows.multi, g->in_rows.longrows, g->in_rows.giant_seg_first, g->in_rows.hub_seg_first, g->fr_tail,
-                    g->fr_seg, g->d_ctr, g->count_tickets, g->long_index, g->row_pred, g->out_eid, g->plane_buf};
+                    g->in_rows.tail, g->in_rows.seg, g->in_rows.multi, g->in_rows.longrows, g->in_rows.giant_seg_first, g->fr_tail,
+                    g->fr_seg, g->d_ctr, g->long_index, g->row_pred, g->out_eid, g->plane_buf};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     if (g->h_ctr) (void)hipHostFree(g->h_ctr);

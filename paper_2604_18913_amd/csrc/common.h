@@ -148,7 +148,7 @@ struct RowClasses {             // device work lists over the object rows, split
     int64_t n_giant = 0;  // the first n_giant long rows have >= kGiantRowMin entries
     uint32_t *giant_seg_first = nullptr;  // [n_giant + 1] segments of kGiantSegment entries before every giant row
     int64_t n_giant_segs = 0;
-    uint32_t *hub_seg_first = nullptr;  // [n_hub + 1] segments of kHubSegment entries before every hub row
+    uint32_t *hub_seg_first = nullptr;  // (behind it) [n_hub + 1] segments of kHubSegment entries before every hub row
     int64_t n_hub_segs = 0, n_split = 0, n_split_segs = 0;  // all; rows of several segments (the first ones), and theirs
 };
 
@@ -225,7 +225,7 @@ struct logoskg_graph {
     lkg::RowSegment *fr_seg = nullptr;   // [fr_seg_cap] segments of the longer frontier rows
     int64_t fr_seg_cap = 0;
     unsigned long long *d_ctr = nullptr;  // device counters (see khop.hip)
-    unsigned int *count_tickets = nullptr;  // [mega tiles + 1] zero between two counts (result.hip)
+    unsigned int *count_tickets = nullptr;  // (behind d_ctr) [mega tiles + 1] zero between two counts (result.hip)
     // pinned host memory, one block (three allocations: 0.44 ms for a graph of 50,000 triples, 0.41 with one):
     unsigned long long *h_ctr = nullptr;  // mirror of the counters
     long long *h_off = nullptr;           // [LOGOSKG_MAX_QUERIES + 1]: offsets of the last count
@@ -469,8 +469,9 @@ logoskg_status small_search(logoskg_graph *g, logoskg_result *r, const logoskg_q
                             bool force_push, int *next_hop, hipStream_t st);
 logoskg_status small_fetch(logoskg_result *r, int q0, int q1, int32_t *entity, uint8_t *hop, int32_t *pred,
                            hipStream_t st);
-// the hub rows' segments: the table for rows of these lengths (longest first) and its counts; into the arguments of a fetch
-std::vector<uint32_t> hub_segments(const std::vector<int32_t> &longer, const std::vector<uint32_t> &off, RowClasses *rows);
+// the hub rows' segments: `table` with theirs behind it (rows longest first), and their counts; into the arguments of a fetch
+std::vector<uint32_t> append_hub_segments(std::vector<uint32_t> table, const std::vector<int32_t> &longer,
+                                          const std::vector<uint32_t> &off, RowClasses *rows);
 void set_hub_segments(FillArgs *a, const RowClasses &rows);
 void drop_walk_tables(logoskg_result *r);
 void launch_lists(Profiler &prof, const FillArgs &a, int W, hipStream_t st);

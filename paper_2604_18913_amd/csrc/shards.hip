@@ -240,7 +240,7 @@ void free_shards(logoskg_graph *g) {
         for (auto p : ss->slot_rel) if (p) (void)hipFree(p);
     }
     for (void *p : {(void *)ss->all_obj, (void *)ss->all_sub, (void *)ss->all_eid, (void *)ss->all_out_rel,
-                    (void *)ss->all_in_rel, (void *)ss->sorted_longrows, (void *)ss->sorted_giant_first, (void *)ss->all_rows.hub_seg_first})
+                    (void *)ss->all_in_rel, (void *)ss->sorted_longrows, (void *)ss->sorted_giant_first})
         if (p) (void)hipFree(p);
     for (auto e : ss->slot_ready) if (e) (void)hipEventDestroy(e);
     for (auto e : ss->slot_idle) if (e) (void)hipEventDestroy(e);
@@ -439,6 +439,7 @@ static logoskg_status build_in_chunks(logoskg_graph *g, ShardSet *ss, const int3
         ss->all_rows.n_hub = g->in_rows.n_hub;
         ss->all_rows.n_giant = (int64_t)first.size() - 1;
         ss->all_rows.n_giant_segs = first.back();
+        first = append_hub_segments(std::move(first), longrows, ioff, &ss->all_rows);
         LKG_HIP(hipMalloc((void **)&ss->sorted_longrows, std::max<size_t>(longrows.size(), 1) * sizeof(int32_t)));
         LKG_HIP(hipMalloc((void **)&ss->sorted_giant_first, first.size() * sizeof(uint32_t)));
         if (!longrows.empty())
@@ -447,10 +448,7 @@ static logoskg_status build_in_chunks(logoskg_graph *g, ShardSet *ss, const int3
         g->static_bytes += longrows.size() * sizeof(int32_t) + first.size() * sizeof(uint32_t);
         ss->all_rows.longrows = ss->sorted_longrows;
         ss->all_rows.giant_seg_first = ss->sorted_giant_first;
-        const std::vector<uint32_t> hub_first = hub_segments(longrows, ioff, &ss->all_rows);
-        LKG_HIP(hipMalloc((void **)&ss->all_rows.hub_seg_first, hub_first.size() * sizeof(uint32_t)));
-        LKG_HIP(hipMemcpy(ss->all_rows.hub_seg_first, hub_first.data(), hub_first.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
-        g->static_bytes += hub_first.size() * sizeof(uint32_t);
+        ss->all_rows.hub_seg_first = ss->sorted_giant_first + ss->all_rows.n_giant + 1;
     }
     return LOGOSKG_OK;
 }
