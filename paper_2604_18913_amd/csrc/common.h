@@ -412,7 +412,7 @@ struct FillArgs {
     unsigned long long *plane_buf;  // bit-sliced plane words between k_pred_walk and k_pred_emit, or NULL
     size_t plane_buf_bytes;
     int sparse;             // 16-word planes: mostly empty words (k_emit_sparse)
-    int emit_eid_cap, emit_line_cap;  // capacities of k_pred_emit's two LDS tables (entries / lines)
+    int emit_eid_cap, emit_line_cap;  // most that k_pred_emit puts in LDS (edge ids / lines)
     uint32_t push_levels;   // bit h: level h of the long rows is resolved from the subject side (k_pred_push), the row
                             // kernels leave it out; host_graph / host_result are what the host code needs for that
     void *host_graph, *host_result;

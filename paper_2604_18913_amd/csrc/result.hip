@@ -1307,21 +1307,23 @@ __global__ void __launch_bounds__(1024) k_pred(FillArgs a) {
 // in the row - is kept bit-sliced: NB words H[b] hold bit b of (hop + 1) of each of the lane's 64
 // queries (so H[0] | H[1] | .. is the visited word) and five words J[b] hold bit b of the row
 // position.  A resolving line costs a fixed fifteen instructions for up to 64 pairs, whatever
-// the number of set bits.  At the end the planes of a lane are turned into one code byte per
-// query, (row position << 3) | (hop + 1), with eight 8 x 8 bit transposes, and the 64 bytes of
-// every (entity, word) go to a buffer laid out [tile][word][entity][query], which a chunk of
-// tiles fills and the second kernel empties while it is still in the caches.
+// the number of set bits.  The planes of every (entity, word) go to a buffer laid out
+// [tile][word][entity][plane], which a chunk of tiles fills and the second kernel empties.
 //
-// k_pred_emit: a block = one tile, its four wavefronts share the words of the fetched range; lane =
-// entity, with the lane's 64 code bytes of the current word in registers.  A wavefront walks the
-// queries of the word that reached the tile in a scalar loop; per query the lanes pick their code
-// byte, a ballot ranks the reached ones inside the tile's piece of the query's run, and the lanes
-// store (entity, hop, predecessor edge) at consecutive list positions: every lane issues the same
-// few instructions and a store instruction covers one contiguous piece of a list.  The loop holds
-// no load from memory (the edge ids of the tile's short rows are staged in LDS once per block), so
-// nothing in it waits for its own stores.  Rows of more than 32 entries belong to the row
+// k_pred_emit: a block = 16 tiles x one word of the range, a wavefront per tile; lane = entity.  The lane turns its
+// planes into one code byte per query, (row position << 3) | (hop + 1), with eight 8 x 8 bit transposes: here and not
+// in the walk, which is bound by the instructions it issues (walk of 1,024 queries on 30M triples 753 -> 686 us)
+// while this kernel waits for memory.  A wavefront walks the queries of the word that reached the block in a
+// scalar loop; per query the lanes pick their code byte, a ballot ranks the reached ones inside the tile's piece of
+// the query's run, and the lanes store (entity, hop, predecessor edge) at consecutive list positions: every lane issues
+// the same few instructions and a store instruction covers one contiguous piece of a list.  The loop holds
+// no load from memory (the edge ids of the reached short rows and the reached long rows' predecessors lie in LDS),
+// so nothing in it waits for its own stores.  Rows of more than 32 entries belong to the row
 // kernels: such an entity's predecessors come from row_pred, which those kernels fill before
 // this one starts (or, without that buffer, the row kernels write them to the lists themselves).
+// What bounds it is HBM: 1.57 ms for 633M pairs of 1,024 queries (1,663 us with two words per block, a chain of seven
+// dependent loads ahead of the loop and the visited words written and read beside the codes), 2.48 ms for 930M pairs of 64
+// queries on 20M entities (3,344 us; there the ids of nine entries a row did not fit the half of the LDS that was theirs).
 constexpr int kSlicedMaxK = 6;     // hop + 1 <= 7 fits three bits
 
 constexpr int kPageEntries = 2;  // entries one lane per entity gathers together (on packed planes 1: 2.4, 2: 2.4, 4: 2.7, 8: 3.3 ms)
@@ -1360,6 +1362,33 @@ k_page_planes(const unsigned long long *__restrict__ levels, long long plane, co
 #pragma unroll
             for (int w = 0; w < N; w += 2) *reinterpret_cast<ulonglong2 *>(dst + w) = make_ulonglong2(x[w], x[w + 1]);
         }
+    }
+}
+
+// From bit planes to one byte per query: plane b = bit b of the code, so byte g of every plane forms an 8 x 8 bit matrix
+// (row = plane, column = query 8 g + j) whose transpose holds the codes of those 8 queries.
+__device__ __forceinline__ void planes_to_codes(const unsigned long long (&P)[8], uint32_t (&d)[16]) {
+#pragma unroll
+    for (int g = 0; g < 8; ++g) {
+        // byte b of x = byte g of plane b, picked with byte permutes (two planes per permute, then
+        // the two pairs): six instructions instead of a shift, a mask and an or per plane and half
+        uint32_t src[8];
+#pragma unroll
+        for (int b = 0; b < 8; ++b) src[b] = g < 4 ? (uint32_t)P[b] : (uint32_t)(P[b] >> 32);
+        const uint32_t pick = 0x0c0c0000u | (uint32_t)((4 + (g & 3)) << 8) | (uint32_t)(g & 3);  // [b.byte, a.byte, 0, 0]
+        const uint32_t t01 = __builtin_amdgcn_perm(src[1], src[0], pick), t23 = __builtin_amdgcn_perm(src[3], src[2], pick);
+        const uint32_t t45 = __builtin_amdgcn_perm(src[5], src[4], pick), t67 = __builtin_amdgcn_perm(src[7], src[6], pick);
+        const uint32_t xlo = __builtin_amdgcn_perm(t23, t01, 0x05040100u), xhi = __builtin_amdgcn_perm(t67, t45, 0x05040100u);
+        unsigned long long x = ((unsigned long long)xhi << 32) | xlo;
+        unsigned long long t;
+        t = (x ^ (x >> 7)) & 0x00AA00AA00AA00AAull;
+        x = x ^ t ^ (t << 7);
+        t = (x ^ (x >> 14)) & 0x0000CCCC0000CCCCull;
+        x = x ^ t ^ (t << 14);
+        t = (x ^ (x >> 28)) & 0x00000000F0F0F0F0ull;
+        x = x ^ t ^ (t << 28);
+        d[2 * g] = (uint32_t)x;
+        d[2 * g + 1] = (uint32_t)(x >> 32);
     }
 }
 
@@ -1509,48 +1538,28 @@ k_pred_walk(FillArgs a, unsigned long long *__restrict__ codes, unsigned long lo
         }
     }
     if (lw >= w0 && lw < w0 + nw) {
-        // From bit planes to one byte per query: plane b = bit b of the code, NB bits of (hop + 1)
-        // below five bits of the row position.  Byte g of every plane forms an 8 x 8 bit matrix
-        // (row = plane, column = query 8 g + j); its transpose holds the codes of those 8 queries.
-        uint4 *out = reinterpret_cast<uint4 *>(codes) + (((size_t)tile_rel * nw + (lw - w0)) * 64 + vi) * 4;
-        unsigned long long reached = 0;  // H[0] | H[1] | ..: the queries of the word that reached the entity
+        // plane b = bit b of the code: NB bits of (hop + 1) below five bits of the row position, which always starts at
+        // bit 3.  k_pred_emit reads the planes as they are, k_emit_sparse one byte per query, and only of words that
+        // hold something.
+        const size_t at = ((size_t)tile_rel * nw + (lw - w0)) * 64 + vi;
+        unsigned long long P[8], reached = 0;  // reached: the queries of the word that reached the entity
+#pragma unroll
+        for (int b = 0; b < 8; ++b) P[b] = b < NB ? H[b] : b < 3 ? 0ull : J[b - 3];
 #pragma unroll
         for (int b = 0; b < NB; ++b) reached |= H[b];
-        visbuf[((size_t)tile_rel * nw + (lw - w0)) * 64 + vi] = reached;
-        if (!sparse || reached)  // (k_emit_sparse reads no codes of words that hold nothing)
-        {
-        unsigned long long P[8];
+        if (!sparse) {
+            ulonglong2 *out = reinterpret_cast<ulonglong2 *>(codes + at * 8);
 #pragma unroll
-        for (int b = 0; b < 8; ++b) P[b] = 0;
+            for (int i = 0; i < 4; ++i) out[i] = make_ulonglong2(P[2 * i], P[2 * i + 1]);
+        } else {
+            visbuf[at] = reached;
+            if (reached) {
+                uint32_t d[16];
+                planes_to_codes(P, d);
+                uint4 *out = reinterpret_cast<uint4 *>(codes + at * 8);
 #pragma unroll
-        for (int b = 0; b < NB; ++b) P[b] = H[b];
-#pragma unroll
-        for (int b = 0; b < 5; ++b) P[3 + b] = J[b];  // the position always starts at bit 3
-        uint32_t d[16];
-#pragma unroll
-        for (int g = 0; g < 8; ++g) {
-            // byte b of x = byte g of plane b, picked with byte permutes (two planes per permute, then
-            // the two pairs): six instructions instead of a shift, a mask and an or per plane and half
-            uint32_t src[8];
-#pragma unroll
-            for (int b = 0; b < 8; ++b) src[b] = g < 4 ? (uint32_t)P[b] : (uint32_t)(P[b] >> 32);
-            const uint32_t pick = 0x0c0c0000u | (uint32_t)((4 + (g & 3)) << 8) | (uint32_t)(g & 3);  // [b.byte, a.byte, 0, 0]
-            const uint32_t t01 = __builtin_amdgcn_perm(src[1], src[0], pick), t23 = __builtin_amdgcn_perm(src[3], src[2], pick);
-            const uint32_t t45 = __builtin_amdgcn_perm(src[5], src[4], pick), t67 = __builtin_amdgcn_perm(src[7], src[6], pick);
-            const uint32_t xlo = __builtin_amdgcn_perm(t23, t01, 0x05040100u), xhi = __builtin_amdgcn_perm(t67, t45, 0x05040100u);
-            unsigned long long x = ((unsigned long long)xhi << 32) | xlo;
-            unsigned long long t;
-            t = (x ^ (x >> 7)) & 0x00AA00AA00AA00AAull;
-            x = x ^ t ^ (t << 7);
-            t = (x ^ (x >> 14)) & 0x0000CCCC0000CCCCull;
-            x = x ^ t ^ (t << 14);
-            t = (x ^ (x >> 28)) & 0x00000000F0F0F0F0ull;
-            x = x ^ t ^ (t << 28);
-            d[2 * g] = (uint32_t)x;
-            d[2 * g + 1] = (uint32_t)(x >> 32);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) out[i] = make_uint4(d[4 * i], d[4 * i + 1], d[4 * i + 2], d[4 * i + 3]);
+                for (int i = 0; i < 4; ++i) out[i] = make_uint4(d[4 * i], d[4 * i + 1], d[4 * i + 2], d[4 * i + 3]);
+            }
         }
     }
     if (STATS) {
@@ -1565,15 +1574,15 @@ k_pred_walk(FillArgs a, unsigned long long *__restrict__ codes, unsigned long lo
     }
 }
 
-// A block = 16 consecutive tiles (one wavefront each) x every wsplit-th word of the fetched range.
+// A block = 16 consecutive tiles (one wavefront each) x one word of the fetched range.
 // 8 wavefronts per SIMD = at most 64 vector registers.
 constexpr int kEmitTiles = 16;
-constexpr int kEmitEids = 9216;   // LDS: edge ids of the short rows of the block's 1,024 entities
-constexpr int kEmitLines = 160;   // LDS: row_pred values (64 queries each) of the block's entities with longer rows
-// (36 KB + 40 KB: two blocks per CU)
+constexpr int kEmitPool = 19'456;  // LDS words, two blocks per CU: edge ids of the short rows of the block's 1,024 entities,
+                                   // behind them the row_pred values (64 queries each) of those with longer rows
+constexpr int kEmitLines = kEmitPool / 64;
 
-// STAGED: the edge ids of the block's short rows fit eid_tab; LINES: the block's row_pred entities
-// fit rp_tab.  Otherwise the loop reads the edge ids from memory / a pass of its own moves the
+// STAGED: the edge ids of the block's short rows are in LDS; LINES: the values of its row_pred entities
+// are.  Otherwise the loop reads the edge ids from memory / a pass of its own moves the
 // row_pred values with lanes = queries.
 template <bool STAGED, bool LINES>
 __device__ __forceinline__ void emit_word(const FillArgs &a, const uint32_t (&c)[16], unsigned long long live,
@@ -1628,182 +1637,174 @@ __device__ __forceinline__ void emit_word(const FillArgs &a, const uint32_t (&c)
 }
 
 __global__ void __launch_bounds__(kEmitTiles * 64) __attribute__((amdgpu_waves_per_eu(8, 8)))
-k_pred_emit(FillArgs a, const unsigned long long *__restrict__ codes, const unsigned long long *__restrict__ visbuf,
-            long long tile0, long long ntile, int w0, int nw, int wsplit, int eid_cap, int line_cap) {
+k_pred_emit(FillArgs a, const unsigned long long *__restrict__ planes, long long tile0, long long ntile, int w0, int nw,
+            int eid_cap, int line_cap) {
     constexpr int Qp = 1024, TPB = kEmitTiles;
-    __shared__ int eid_tab[kEmitEids];
-    __shared__ int rp_tab[kEmitLines * 64];
-    __shared__ unsigned long long s_live[2];
-    __shared__ int s_wsum[2][TPB];
+    __shared__ int pool[kEmitPool];
+    __shared__ unsigned long long s_live;
+    __shared__ int s_need[TPB];
     const long long L = xcd_contiguous(blockIdx.x, gridDim.x);
     const long long nsup = (ntile + TPB - 1) / TPB;
-    if (L >= nsup * wsplit) return;  // block-uniform
-    const int part = (int)(L % wsplit);
-    const int t = threadIdx.x, wave = t >> 6, v = lane();
-    const long long tile_rel = (L / wsplit) * TPB + wave, tile = tile0 + tile_rel;
-    const bool valid = tile_rel < ntile;  // wave-uniform
-    if (t < 2) s_live[t] = 0ull;
-    // ---- once per block: the tiles' entities (lane = entity)
-    const long long ew = valid ? tile_entity(a.tile_ent, tile, v, a.E) : -1;
-    uint32_t wlo = 0, whi = 0;
-    if (ew >= 0) {
-        wlo = a.in_off[ew];
-        whi = a.in_off[ew + 1];
+    if (L >= nsup * nw) return;  // block-uniform
+    const int wi = (int)(L % nw), w = w0 + wi;
+    const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), v = lane(), ql = w * 64 + v;
+    const bool valid = (L / nw) * TPB + wave < ntile;  // (behind the last tile: its loads again, nothing written)
+    const long long tile_rel = min((L / nw) * TPB + wave, ntile - 1), tile = tile0 + tile_rel;
+    if (t == 0) s_live = 0ull;
+    // What depends on nothing is requested first: the tile's entities, the planes of (entity, word) (lane = entity; zero
+    // where there is no entity), and where query 64 w + v continues in this tile (lane = query)
+    const long long ew = tile_entity(a.tile_ent, tile, v, a.E);
+    unsigned long long P[8];
+    {
+        const ulonglong2 *in = reinterpret_cast<const ulonglong2 *>(planes) + (((size_t)tile_rel * nw + wi) * 64 + v) * 4;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const ulonglong2 x = in[i];
+            P[2 * i] = x.x;
+            P[2 * i + 1] = x.y;
+        }
     }
-    const uint32_t wdeg = whi - wlo;
+    const long long list_q = a.reached_off[ql];
+    const uint32_t mega_q = a.mega_base[(size_t)(tile / kSuperTiles / kMegaSupers) * Qp + ql];
+    const uint32_t super_q = a.super_base[(size_t)(tile / kSuperTiles) * Qp + ql], tile_q = a.tile_base[(size_t)tile * Qp + ql];
+    const size_t eo = ew >= 0 ? (size_t)ew : 0;
+    const uint32_t wlo = a.in_off[eo], wdeg = a.in_off[eo + 1] - wlo;
+    const unsigned long long vis = valid && ew >= 0 ? P[0] | P[1] | P[2] : 0ull;
     // where a lane's predecessors come from: the edge ids of its own short row (by row position),
     // its line of row_pred (by query), or nowhere (the block-per-row kernel writes them).  Seeds
     // get their -1 in the loop.
     const bool longrow = wdeg > (uint32_t)kTailMaxDegree;
-    const bool by_query = longrow && a.row_pred;
+    const bool by_query = longrow && a.row_pred && vis != 0;
     int li = 0;
     if (by_query) li = (int)(a.long_index[ew] - a.row_base);
-    const int n_stage = longrow ? 0 : (int)wdeg;
-    int wtot, ltot;
-    int off = wave_excl_scan(n_stage, wtot);
-    const unsigned long long bq_wave = __ballot(by_query);
-    int slot = __popcll(bq_wave & ((1ull << v) - 1ull));
-    ltot = __popcll(bq_wave);
-    if (v == 0) {
-        s_wsum[0][wave] = wtot;
-        s_wsum[1][wave] = ltot;
+    const int n_stage = longrow || vis == 0 ? 0 : (int)wdeg;
+    const unsigned long long below = (1ull << v) - 1ull;
+    int off = 0, wtot = 0;  // prefix and sum of n_stage (at most 32) over the wavefront
+#pragma unroll
+    for (int b = 0; b < 6; ++b) {
+        const unsigned long long m = __ballot((n_stage >> b) & 1);
+        off += __popcll(m & below) << b;
+        wtot += __popcll(m) << b;
     }
+    const unsigned long long bq_wave = __ballot(by_query);
+    if (v == 0) s_need[wave] = wtot | (__popcll(bq_wave) << 16);  // (at most 2,048 and 64)
+    const unsigned long long live_wave = wave_or64(vis);
     __syncthreads();
+    if (v == 0 && live_wave) atomicOr(&s_live, live_wave);
+    const int need = s_need[v & (TPB - 1)];
     int total = 0, lines = 0, line0 = 0;
 #pragma unroll
     for (int x = 0; x < TPB; ++x) {
+        const int n = __builtin_amdgcn_readlane(need, x);
         if (x < wave) {
-            off += s_wsum[0][x];
-            line0 += s_wsum[1][x];
+            off += n & 0xffff;
+            line0 += n >> 16;
         }
-        total += s_wsum[0][x];
-        lines += s_wsum[1][x];
+        total += n & 0xffff;
+        lines += n >> 16;
     }
-    slot += line0;
-    const bool staged = total <= eid_cap, lined = lines <= line_cap;  // block-uniform
-    if (staged)  // eight entries of the lane's row are requested before the first is stored
+    const bool staged = total <= eid_cap;  // block-uniform
+    int *const eid_tab = pool, *const rp_tab = pool + (staged ? total : 0);
+    const bool lined = lines <= line_cap && lines * 64 + (staged ? total : 0) <= kEmitPool;
+    if (staged)  // eight entries of the lane's row are requested before the first is stored (the last one again behind it)
         for (int i0 = 0; i0 < n_stage; i0 += 8) {
             int e[8];
 #pragma unroll
-            for (int x = 0; x < 8; ++x) e[x] = i0 + x < n_stage ? a.in_eid[wlo + i0 + x] : 0;
+            for (int x = 0; x < 8; ++x) e[x] = a.in_eid[wlo + min(i0 + x, n_stage - 1)];
 #pragma unroll
-            for (int x = 0; x < 8; ++x)
-                if (i0 + x < n_stage) eid_tab[off + i0 + x] = e[x];
+            for (int x = 0; x < 8; ++x) eid_tab[off + min(i0 + x, n_stage - 1)] = e[x];
         }
+    // the row_pred values of this word: 64 queries x the wavefront's entities of that kind, eight
+    // lines requested together (lanes = queries)
+    if (lined) {
+        unsigned long long bq = bq_wave;
+        int s_at = line0;
+        while (bq) {
+            int val[8], at[8], Lx = 0, n = -1;
+#pragma unroll
+            for (int x = 0; x < 8; ++x) {  // (the last one again where there are fewer)
+                if (bq) {
+                    Lx = __builtin_ctzll(bq);
+                    bq &= bq - 1;
+                    ++n;
+                }
+                at[x] = s_at + n;
+                val[x] = a.row_pred[(size_t)__builtin_amdgcn_readlane(li, Lx) * Qp + ql];
+            }
+#pragma unroll
+            for (int x = 0; x < 8; ++x) rp_tab[at[x] * 64 + v] = val[x];
+            s_at += n + 1;
+        }
+    }
+    // lane = entity: one code byte per query of the word, (row position << 3) | (hop + 1), zero where
+    // the query did not reach the entity
+    if (vis == 0) {
+#pragma unroll
+        for (int b = 0; b < 8; ++b) P[b] = 0;
+    }
+    uint32_t c[16];
+    planes_to_codes(P, c);
+    const long long pos = list_q - a.reached_off[a.q0] + mega_q + super_q + tile_q;
+    uint32_t pos_lo = (uint32_t)(unsigned long long)pos, pos_hi = (uint32_t)((unsigned long long)pos >> 32);
+    __syncthreads();
+    const unsigned long long live = s_live;
+    if (live == 0ull) return;  // block-uniform
+    if (!lined) {
+        // Entities whose predecessors wait in row_pred, too many for rp_tab: lanes = queries.
+        // Lane i knows where query i's run of this tile starts (pos) and, after a 64 x 64
+        // transpose of the visited words, which of the tile's entities query i reached: the
+        // rank of entity L in the run is the number of those below L.  Four lines are
+        // requested before the first is stored.  Seeds (hop + 1 == 1) are left to the loop.
+        unsigned long long bq = bq_wave;
+        if (bq) {
+            const unsigned long long mT = transpose64(vis);
+            unsigned long long seed_w = 0;
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    seed_w |= (unsigned long long)(((c[i] >> (8 * j)) & 7u) == 1u) << (4 * i + j);
+            const uint32_t seed_lo = (uint32_t)seed_w, seed_hi = (uint32_t)(seed_w >> 32);
+            const int32_t *const rp = a.row_pred + ql;
+            int32_t *const pp = a.pred + pos;
+            while (bq) {
+                int Lx[4], val[4];
+                bool on[4];
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    Lx[x] = -1;
+                    on[x] = false;
+                    val[x] = 0;
+                    if (bq) {
+                        Lx[x] = __builtin_ctzll(bq);
+                        bq &= bq - 1;
+                        const int liL = __builtin_amdgcn_readlane(li, Lx[x]);
+                        const unsigned long long seedL =
+                            ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)seed_hi, Lx[x]) << 32) |
+                            (uint32_t)__builtin_amdgcn_readlane((int)seed_lo, Lx[x]);
+                        on[x] = ((mT >> Lx[x]) & 1ull) && !((seedL >> v) & 1ull);
+                        if (on[x]) val[x] = rp[(size_t)liL * Qp];
+                    }
+                }
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+                    if (on[x]) pp[__popcll(mT & ((1ull << Lx[x]) - 1ull))] = val[x];
+            }
+        }
+    }
+    // Everything requested from memory so far is consumed here, so that the loop holds stores
+    // only: a wait on a load inside it would also wait for the loop's own stores.
+    asm volatile("" : "+v"(pos_lo), "+v"(pos_hi));
     const int ent_id = (int)ew;
     const int *const my_eids = eid_tab + (staged ? off : 0);
     const int32_t *const my_row = a.in_eid + wlo;
-    const int *const my_line = rp_tab + (lined ? slot : 0) * 64;
-    int turn = 0;
-    for (int wi = part; wi < nw; wi += wsplit, turn ^= 1) {  // block-uniform trip count
-        const int w = w0 + wi;
-        // where query 64 w + v continues in this tile (lane = query here)
-        long long pos = 0;
-        const int ql = w * 64 + v;
-        if (valid && ql >= a.q0 && ql < a.q1)
-            pos = super_start(a, tile / kSuperTiles, Qp, ql) + a.tile_base[(size_t)tile * Qp + ql];
-        // lane = entity: one code byte per query of the word, (row position << 3) | (hop + 1), zero where
-        // the query did not reach the entity; vis = the queries that reached it
-        uint32_t c[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) c[i] = 0;
-        unsigned long long vis = 0;
-        if (ew >= 0) {
-            const size_t at = ((size_t)tile_rel * nw + wi) * 64 + v;
-            const uint4 *in = reinterpret_cast<const uint4 *>(codes) + at * 4;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint4 x = in[i];
-                c[4 * i] = x.x; c[4 * i + 1] = x.y; c[4 * i + 2] = x.z; c[4 * i + 3] = x.w;
-            }
-            vis = visbuf[at];
-        }
-        // the row_pred values of this word: 64 queries x the wavefront's entities of that kind, eight
-        // lines requested together (lanes = queries)
-        if (lined) {
-            unsigned long long bq = bq_wave;
-            int s_at = line0;
-            while (bq) {
-                int val[8];
-                int n = 0;
-#pragma unroll
-                for (int x = 0; x < 8; ++x) {
-                    val[x] = 0;
-                    if (bq) {
-                        const int Lx = __builtin_ctzll(bq);
-                        bq &= bq - 1;
-                        val[x] = a.row_pred[(size_t)__builtin_amdgcn_readlane(li, Lx) * Qp + ql];
-                        ++n;
-                    }
-                }
-#pragma unroll
-                for (int x = 0; x < 8; ++x)
-                    if (x < n) rp_tab[(s_at + x) * 64 + v] = val[x];
-                s_at += n;
-            }
-        }
-        const unsigned long long live_wave = wave_or64(vis);
-        if (v == 0 && live_wave) atomicOr(&s_live[turn], live_wave);
-        __syncthreads();
-        const unsigned long long live = s_live[turn];
-        if (t == 0) s_live[turn ^ 1] = 0ull;  // for the next word (read again only after its barrier)
-        uint32_t pos_lo = (uint32_t)(unsigned long long)pos, pos_hi = (uint32_t)((unsigned long long)pos >> 32);
-        if (live != 0ull) {  // block-uniform
-            if (!lined) {
-                // Entities whose predecessors wait in row_pred, too many for rp_tab: lanes = queries.
-                // Lane i knows where query i's run of this tile starts (pos) and, after a 64 x 64
-                // transpose of the visited words, which of the tile's entities query i reached: the
-                // rank of entity L in the run is the number of those below L.  Four lines are
-                // requested before the first is stored.  Seeds (hop + 1 == 1) are left to the loop.
-                unsigned long long bq = bq_wave;
-                if (bq) {
-                    const unsigned long long mT = transpose64(vis);
-                    unsigned long long seed_w = 0;
-#pragma unroll
-                    for (int i = 0; i < 16; ++i)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            seed_w |= (unsigned long long)(((c[i] >> (8 * j)) & 7u) == 1u) << (4 * i + j);
-                    const uint32_t seed_lo = (uint32_t)seed_w, seed_hi = (uint32_t)(seed_w >> 32);
-                    const int32_t *const rp = a.row_pred + ql;
-                    int32_t *const pp = a.pred + pos;
-                    while (bq) {
-                        int Lx[4], val[4];
-                        bool on[4];
-#pragma unroll
-                        for (int x = 0; x < 4; ++x) {
-                            Lx[x] = -1;
-                            on[x] = false;
-                            val[x] = 0;
-                            if (bq) {
-                                Lx[x] = __builtin_ctzll(bq);
-                                bq &= bq - 1;
-                                const int liL = __builtin_amdgcn_readlane(li, Lx[x]);
-                                const unsigned long long seedL =
-                                    ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)seed_hi, Lx[x]) << 32) |
-                                    (uint32_t)__builtin_amdgcn_readlane((int)seed_lo, Lx[x]);
-                                on[x] = ((mT >> Lx[x]) & 1ull) && !((seedL >> v) & 1ull);
-                                if (on[x]) val[x] = rp[(size_t)liL * Qp];
-                            }
-                        }
-#pragma unroll
-                        for (int x = 0; x < 4; ++x)
-                            if (on[x]) pp[__popcll(mT & ((1ull << Lx[x]) - 1ull))] = val[x];
-                    }
-                }
-            }
-            // Everything requested from memory so far is consumed here, so that the loop holds stores
-            // only: a wait on a load inside it would also wait for the loop's own stores.
-            asm volatile("" : "+v"(pos_lo), "+v"(pos_hi));
-            if (staged) {
-                if (lined) emit_word<true, true>(a, c, live, pos_lo, pos_hi, ent_id, longrow, by_query, my_eids, my_row, my_line);
-                else emit_word<true, false>(a, c, live, pos_lo, pos_hi, ent_id, longrow, by_query, my_eids, my_row, my_line);
-            } else {
-                if (lined) emit_word<false, true>(a, c, live, pos_lo, pos_hi, ent_id, longrow, by_query, my_eids, my_row, my_line);
-                else emit_word<false, false>(a, c, live, pos_lo, pos_hi, ent_id, longrow, by_query, my_eids, my_row, my_line);
-            }
-        }
-        __syncthreads();  // rp_tab is rewritten for the next word
+    const int *const my_line = rp_tab + (lined ? line0 + __popcll(bq_wave & below) : 0) * 64;
+    if (staged) {
+        if (lined) emit_word<true, true>(a, c, live, pos_lo, pos_hi, ent_id, longrow, by_query, my_eids, my_row, my_line);
+        else emit_word<true, false>(a, c, live, pos_lo, pos_hi, ent_id, longrow, by_query, my_eids, my_row, my_line);
+    } else {
+        if (lined) emit_word<false, true>(a, c, live, pos_lo, pos_hi, ent_id, longrow, by_query, my_eids, my_row, my_line);
+        else emit_word<false, false>(a, c, live, pos_lo, pos_hi, ent_id, longrow, by_query, my_eids, my_row, my_line);
     }
 }
 
@@ -2481,22 +2482,18 @@ static void launch_pred_wms(Profiler &prof, const FillArgs &a0, long long n_hub_
     const bool rows_first = n_hub_rows > 0 && a.row_pred && mt && st_hub != st_tiles && a.ev_rows;
     if (rows_first) (void)hipEventRecord((hipEvent_t)a.ev_rows, st_hub);
     if (a.tile_count > 0 && mt) {
-        // in chunks of tiles whose code bytes (64 per entity and word) and visited words fit the buffer
+        // in chunks of tiles whose planes or code bytes (64 bytes per entity and word) and, for the sparse writer, visited
+        // words fit the buffer
         const int w0 = a.q0 / 64, nw = (a.q1 - 1) / 64 - w0 + 1;
-        const size_t per_tile = (size_t)nw * 64 * (64 + 8);
+        const size_t per_tile = (size_t)nw * 64 * (64 + (a.sparse ? 8 : 0));
         long long chunk = (long long)(a.plane_buf_bytes / per_tile);
         chunk = std::max<long long>(kEmitTiles, chunk / kEmitTiles * kEmitTiles);
         for (long long c0 = 0; c0 < a.tile_count; c0 += chunk) {
             const long long n = std::min(chunk, a.tile_count - c0), t0 = a.tile_begin + c0;
             unsigned long long *visbuf = a.plane_buf + (size_t)n * nw * 64 * 8;  // behind the codes
-            // each block of the second kernel takes every wsplit-th word: enough blocks to go
-            // round the GPU a few times, as many words per block as that allows
             const long long nsup = (n + kEmitTiles - 1) / kEmitTiles;
-            int wsplit = 1;
-            while (wsplit < nw && nsup * wsplit < 8192) wsplit *= 2;
-            wsplit = std::min(wsplit, nw);
             dim3 gw((unsigned)((n * 4 + 7) / 8 * 8));
-            dim3 ge((unsigned)((nsup * wsplit + 7) / 8 * 8));
+            dim3 ge((unsigned)((nsup * nw + 7) / 8 * 8));
             {
                 ProfScope ps(prof, KK_PRED_WALK, st_tiles);
                 // a range inside four aligned words takes four lanes per entity (16 entities per wavefront)
@@ -2523,8 +2520,7 @@ static void launch_pred_wms(Profiler &prof, const FillArgs &a0, long long n_hub_
             if (a.sparse)
                 k_emit_sparse<<<dim3((unsigned)(((n * nw + 3) / 4 + 7) / 8 * 8)), dim3(256), 0, st_tiles>>>(
                     a, reinterpret_cast<const uint8_t *>(a.plane_buf), visbuf, t0, n, w0, nw);
-            else k_pred_emit<<<ge, dim3(kEmitTiles * 64), 0, st_tiles>>>(a, a.plane_buf, visbuf, t0, n, w0, nw, wsplit,
-                                                                   a.emit_eid_cap, a.emit_line_cap);
+            else k_pred_emit<<<ge, dim3(kEmitTiles * 64), 0, st_tiles>>>(a, a.plane_buf, t0, n, w0, nw, a.emit_eid_cap, a.emit_line_cap);
             if (prof.on) {  // entities x words whose code bytes pass from the first kernel to the second
                 prof.acc[KK_PRED_WALK].units[3] += n * 64 * nw;
                 prof.acc[KK_PRED].units[0] += n * 64 * nw;
@@ -2649,13 +2645,13 @@ extern "C" logoskg_status logoskg_result_fetch(logoskg_result *r, int32_t q0, in
         a.plane_buf = g->plane_buf;
         a.plane_buf_bytes = g->plane_buf_bytes;
         a.ev_rows = g->ev_rows;
-        // (LOGOSKG_EMIT_CAPS="e,l" shrinks the two LDS tables of k_pred_emit so that tests reach its other paths)
-        a.emit_eid_cap = kEmitEids;
+        // (LOGOSKG_EMIT_CAPS="e,l" shrinks what k_pred_emit puts in LDS so that tests reach its other paths)
+        a.emit_eid_cap = kEmitPool;
         a.emit_line_cap = kEmitLines;
         if (const char *caps = getenv("LOGOSKG_EMIT_CAPS")) {
-            int e = kEmitEids, l = kEmitLines;
+            int e = kEmitPool, l = kEmitLines;
             if (sscanf(caps, "%d,%d", &e, &l) == 2) {
-                a.emit_eid_cap = std::max(0, std::min(e, kEmitEids));
+                a.emit_eid_cap = std::max(0, std::min(e, kEmitPool));
                 a.emit_line_cap = std::max(0, std::min(l, kEmitLines));
             }
         }
