@@ -314,30 +314,88 @@ __device__ __forceinline__ void scan_counts(const ScanArgs &a, long long st) {
     if (q == 0 && a.n_active) *a.host_n_active = *a.n_active;
 }
 
-// 16-word planes: one block per super tile, one wavefront per word: tile_base[tile][q] = entities
-// query q reached in the earlier tiles of the super tile, super_sum[st][q] = in
-// the whole super tile.
+// Bit-sliced sums of 64 counters side by side: sum and carry of three words.
+__device__ __forceinline__ void full_add(unsigned long long a, unsigned long long b, unsigned long long c, unsigned long long &sum,
+                                         unsigned long long &carry) {
+    sum = a ^ b ^ c;
+    carry = (a & b) | (c & (a | b));
+}
+
+// 16-word planes: one block per super tile, a wavefront per tile: tile_base[tile][q] = entities query q reached in the
+// earlier tiles of the super tile, super_sum[st][q] = in the whole super tile.
 // With a list the number of tiles follows from *n_active (the grid covers the largest possible
 // number of super tiles; those behind the list write zero sums).
-__global__ void __launch_bounds__(1024)
+// A 16-lane group takes 16 of the tile's entities, lane = word, all lines requested together, and adds them up bit-sliced:
+// five words say for 64 queries how many of the 16 entities each reached, seven when the four groups have been added.
+// Only those are turned into a number per query (lane = query: a word is the mask of a select).  A
+// wavefront per word that transposed 64 x 64 bits per tile, the lines handed over through LDS, was a chain of latencies and
+// twelve LDS permutes per (tile, word): 20M entities 1,338 -> 620 us (2.6 GB read, 0.6 GB written), 30M triples' 0.9M listed
+// ones 72 -> 35 us.
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8)))
 k_count(const unsigned long long *__restrict__ visited, long long ntiles, int32_t E, const int32_t *__restrict__ tile_ent,
         const unsigned long long *__restrict__ n_active, uint16_t *tile_base, uint32_t *super_sum) {
     constexpr int W = 16, Qp = 64 * W;
-    __shared__ unsigned long long stage[64][W + 1];
-    const long long st = blockIdx.x;
-    const int wave = threadIdx.x >> 6;
+    __shared__ uint8_t cnt[kSuperTiles][Qp];  // (at most 64)
+    const long long st = blockIdx.x, first = st * kSuperTiles;
+    const int t = threadIdx.x, wave = t >> 6, v = lane(), lw = v & (W - 1), g = v / W;
     if (tile_ent) ntiles = (long long)((*n_active + 63) / 64);
-    int run = 0;
-    for (int i = 0; i < kSuperTiles; ++i) {
-        long long tile = st * kSuperTiles + i;
-        if (tile >= ntiles) break;
-        unsigned long long x = stage_word<W>(stage, visited, tile_ent, tile, E, wave);
-        tile_base[(size_t)tile * Qp + threadIdx.x] = (uint16_t)run;
-        int mine = 0;
-        if (wave_any(x != 0)) mine = __popcll(transpose64(x));  // lane qq: entities of the tile query qq reached
-        run += mine;
+    const int n = (int)max(0ll, min((long long)kSuperTiles, ntiles - first));  // block-uniform
+    if (wave < n) {
+        const long long tile = first + wave;
+        int32_t e[16];
+        if (tile_ent) {
+#pragma unroll
+            for (int i = 0; i < 16; i += 4) {
+                const int4 y = *reinterpret_cast<const int4 *>(tile_ent + tile * 64 + g * 16 + i);
+                e[i] = y.x; e[i + 1] = y.y; e[i + 2] = y.z; e[i + 3] = y.w;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) e[i] = (int32_t)tile_entity(nullptr, tile, g * 16 + i, E);
+        }
+        unsigned long long x[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) x[i] = visited[(size_t)max(e[i], 0) * W + lw];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) x[i] = e[i] >= 0 ? x[i] : 0ull;
+        // p[b]: bit b of the sums
+        unsigned long long p[7] = {}, c2[8], c4[4], c8[2];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) full_add(x[2 * i], x[2 * i + 1], p[0], p[0], c2[i]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) full_add(c2[2 * i], c2[2 * i + 1], p[1], p[1], c4[i]);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) full_add(c4[2 * i], c4[2 * i + 1], p[2], p[2], c8[i]);
+        full_add(c8[0], c8[1], 0ull, p[3], p[4]);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {  // the four groups
+            unsigned long long carry = 0;
+#pragma unroll
+            for (int b = 0; b < 5 + s; ++b) full_add(p[b], shfl_xor64(p[b], W << s), carry, p[b], carry);
+            p[5 + s] = carry;
+        }
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            int c = 0;
+#pragma unroll
+            for (int b = 0; b < 7; ++b) {
+                const unsigned long long m =
+                    ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(p[b] >> 32), w) << 32) |
+                    (uint32_t)__builtin_amdgcn_readlane((int)p[b], w);
+                c |= __builtin_amdgcn_inverse_ballot_w64(m) ? 1 << b : 0;
+            }
+            cnt[wave][w * 64 + v] = (uint8_t)c;
+        }
     }
-    super_sum[(size_t)st * Qp + threadIdx.x] = (uint32_t)run;
+    __syncthreads();
+    int run = 0;
+#pragma unroll
+    for (int k = 0; k < kSuperTiles; ++k) {
+        if (k >= n) continue;
+        tile_base[(size_t)(first + k) * Qp + t] = (uint16_t)run;
+        run += cnt[k][t];
+    }
+    super_sum[(size_t)st * Qp + t] = (uint32_t)run;
 }
 
 // The same for planes of one and four words: a wavefront per tile of the super tile, the sixteen counts of a

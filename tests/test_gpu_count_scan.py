@@ -34,3 +34,23 @@ def test_counts(E, Q):
             assert np.array_equal(at, np.concatenate([[0], np.cumsum(on)])[want[0]])
         res.close()
     g.close()
+
+
+@pytest.mark.parametrize("E", [64, 1000, 3 * 1024 + 70])
+@pytest.mark.parametrize("Q", [64, 256, 700, 1024])
+def test_counts_of_full_tiles(E, Q):
+    """Every second query reaches every entity: all bits of a tile's counts."""
+    import paper_2604_18913_amd as lkg
+    s = np.concatenate([np.zeros(E), np.ones(E // 2)]).astype(np.int32)
+    o = np.concatenate([np.arange(E), np.arange(E // 2) * 2 + 1]).astype(np.int32)
+    r = np.zeros(s.size, dtype=np.int32)
+    off = np.arange(Q + 1, dtype=np.int64)
+    seeds = (np.arange(Q) % 5 % 2).astype(np.int32)
+    g = lkg.Graph(s, r, o, E, 1)
+    want = oracle.khop(E, s, r, o, off, seeds, 1)
+    res = g.khop(off, seeds, 1)
+    assert np.array_equal(res.offsets(), want[0])
+    for got, w in zip(res.fetch(), want[1:]):
+        assert np.array_equal(got.cpu().numpy(), w)
+    res.close()
+    g.close()
