@@ -412,8 +412,41 @@ __device__ __forceinline__ void mark_active(uint32_t *act, int e) {
 }
 
 // `known` = the bits that need not be set again: the visited plane (minimum-hop search: an entity
-// keeps its first level) or, for walk-exact levels, the level under construction itself.
-// One W-lane group per short frontier row; its edges are walked one after another.
+// keeps its first level) or, for walk-exact levels, the level under construction itself.  NULL in the first hop, where
+// visited holds nothing but the seeds: k_update_visited takes out the few pairs that are seeds, and an edge costs
+// an atomic and no read of a line in front of it.
+//
+// Lines of at most kFewWords non-zero words (the seeds' nearly always) go lane = edge: every lane sets the words of its
+// own edge's object, 64 edges of a segment or G of a short row in flight.  With lane = word, four edges of a segment and
+// one of a short row were in flight, most lanes idle, and the kernels were chains of as many turns (first hop, us,
+// segments / short rows: 1,024 queries on 30M triples 23 / 30 -> 8 / 6, 200 with whitelists on 3.4M 6 / 17 -> 4 / 6, 25M
+// edges of hub subjects on 20M entities 1,396 -> 1,095, where the atomics on 2.5 GB of lines remain).
+constexpr int kFewWords = 4;
+
+// one edge per lane: the words `words` (bits; the caller's lanes agree on how many) of a line into object o's
+template <int W, bool MASK, typename Line>
+__device__ __forceinline__ void push_edge(bool on, int o, int r, unsigned words, Line word_of, const unsigned long long *__restrict__ allow,
+                                          const unsigned long long *known, unsigned long long *cur, uint32_t *act_cur) {
+    bool any = false;
+    while (words) {
+        const int w = __ffs((int)words) - 1;
+        words &= words - 1;
+        unsigned long long m = word_of(w);
+        if (!on) continue;
+        if (MASK) m &= allow[(size_t)r * W + w];
+        if (m && known) m &= ~known[(size_t)o * W + w];
+        if (m) {
+            atomicOr(&cur[(size_t)o * W + w], m);
+            any = true;
+        }
+    }
+    if (any) mark_active(act_cur, o);
+}
+
+// A group of G lanes per short frontier row.
+template <int W>
+constexpr int push_tail_lanes() { return W == 16 ? 16 : 8; }
+
 template <int W, bool MASK>
 __global__ void __launch_bounds__(256)
 k_push_tail(const int32_t *__restrict__ rows, const unsigned long long *__restrict__ ctr,
@@ -422,73 +455,36 @@ k_push_tail(const int32_t *__restrict__ rows, const unsigned long long *__restri
             const uint16_t *__restrict__ rel, const unsigned long long *__restrict__ allow,
             const unsigned long long *__restrict__ prev, const unsigned long long *known,
             unsigned long long *cur, uint32_t *act_cur) {
-    long long gidx = ((long long)blockIdx.x * blockDim.x + threadIdx.x) / W;
-    int lw = threadIdx.x & (W - 1);
-    long long n = (long long)ctr[C_NTAIL];
-    uint32_t lo = 0, hi = 0;
-    unsigned long long line = 0;
-    if (gidx < n) {
-        int s = rows[gidx];
-        lo = row_begin[s];
-        hi = lo + (off[s + 1] - off[s]);
-        line = prev[(size_t)s * W + lw];
+    constexpr int G = push_tail_lanes<W>();
+    const long long gidx = ((long long)blockIdx.x * blockDim.x + threadIdx.x) / G;
+    const int gl = threadIdx.x & (G - 1), g0 = lane() & ~(G - 1);
+    if (gidx >= (long long)ctr[C_NTAIL]) return;  // the lanes of a group together
+    const int s = rows[gidx];
+    const uint32_t lo = row_begin[s], hi = lo + (off[s + 1] - off[s]);
+    const unsigned long long line = gl < W ? prev[(size_t)s * W + gl] : 0ull;
+    const unsigned words = (unsigned)((__ballot(line != 0) >> g0) & ((1u << G) - 1u));
+    if (W <= kFewWords || __popc(words) <= kFewWords) {
+        for (uint32_t j0 = lo; j0 < hi; j0 += G) {  // the lanes of a group together: they hold each other's words
+            const uint32_t j = j0 + gl;
+            const bool on = j < hi;
+            const int o = on ? obj[j] : 0, r = MASK && on ? rel[j] : 0;
+            push_edge<W, MASK>(on, o, r, words, [&](int w) { return __shfl(line, g0 + w); }, allow, known, cur, act_cur);
+        }
+        return;
     }
-    for (uint32_t j = lo; j < hi; ++j) {
-        int o = obj[j];
+    for (uint32_t j = lo; j < hi; ++j) {  // 16 words: lane = word, an edge after the other
+        const int o = obj[j];
         unsigned long long m = line;
-        if (MASK) m &= allow[(size_t)rel[j] * W + lw];
-        if (m) m &= ~known[(size_t)o * W + lw];
-        if (m) atomicOr(&cur[(size_t)o * W + lw], m);
-        bool any = group_any<W>(m != 0);
-        if (any && lw == 0) mark_active(act_cur, o);
+        if (MASK) m &= allow[(size_t)rel[j] * W + gl];
+        if (m && known) m &= ~known[(size_t)o * W + gl];
+        if (m) atomicOr(&cur[(size_t)o * W + gl], m);
+        const bool any = group_any<G>(m != 0);
+        if (any && gl == 0) mark_active(act_cur, o);
     }
 }
 
-// 64 consecutive edges of one subject row, handled by a whole wavefront: every
-// lane loads one edge, then the 64/W groups take the edges in turn.
-template <int W, bool MASK>
-__device__ __forceinline__ void push_chunk(uint32_t j0, uint32_t hi, unsigned long long line,
-                                           const int32_t *__restrict__ obj, const uint16_t *__restrict__ rel,
-                                           const unsigned long long *__restrict__ allow,
-                                           const unsigned long long *known,
-                                           unsigned long long *cur, uint32_t *act_cur) {
-    constexpr int GPW = 64 / W;
-    int lw = lane() & (W - 1), g = lane() / W;
-    uint32_t j = j0 + lane();
-    int o = -1, r = 0;
-    if (j < hi) {
-        o = obj[j];
-        if (MASK) r = rel[j];
-    }
-    int n = (int)min((uint32_t)64, hi - j0);
-    if constexpr (W == 1) {
-        if (o >= 0) {
-            unsigned long long m = line;
-            if (MASK) m &= allow[r];
-            if (m) m &= ~known[o];
-            if (m) {
-                atomicOr(&cur[o], m);
-                mark_active(act_cur, o);
-            }
-        }
-    } else {
-        for (int i = 0; i < n; i += GPW) {
-            int idx = i + g;
-            int oc = __shfl(o, idx & 63);
-            int rc = MASK ? __shfl(r, idx & 63) : 0;
-            if (idx < n) {
-                unsigned long long m = line;
-                if (MASK) m &= allow[(size_t)rc * W + lw];
-                if (m) m &= ~known[(size_t)oc * W + lw];
-                if (m) atomicOr(&cur[(size_t)oc * W + lw], m);
-                bool any = group_any<W>(m != 0);
-                if (any && lw == 0) mark_active(act_cur, oc);
-            }
-        }
-    }
-}
-
-// One wavefront per segment of a long frontier row.
+// One wavefront per segment (64 consecutive edges) of a long frontier row, a lane per edge; where many words of the line
+// hold something the 64/W groups take the edges in turn, lane = word.
 template <int W, bool MASK>
 __global__ void __launch_bounds__(256)
 k_push_seg(const RowSegment *__restrict__ segs, const unsigned long long *__restrict__ ctr,
@@ -497,25 +493,49 @@ k_push_seg(const RowSegment *__restrict__ segs, const unsigned long long *__rest
            const uint16_t *__restrict__ rel, const unsigned long long *__restrict__ allow,
            const unsigned long long *__restrict__ prev, const unsigned long long *known,
            unsigned long long *cur, uint32_t *act_cur) {
-    long long item = (long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    const long long item = (long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     if (item >= (long long)ctr[C_NSEG]) return;
-    RowSegment sg = segs[item];
-    int lw = lane() & (W - 1);
-    unsigned long long line = prev[(size_t)sg.row * W + lw];
-    uint32_t row_end = row_begin[sg.row] + (off[sg.row + 1] - off[sg.row]);
-    uint32_t hi = min(sg.begin + (uint32_t)kPushSegment, row_end);
-    for (uint32_t j0 = sg.begin; j0 < hi; j0 += 64)
-        push_chunk<W, MASK>(j0, hi, line, obj, rel, allow, known, cur, act_cur);
+    const RowSegment sg = segs[item];
+    const int lw = lane() & (W - 1), g = lane() / W;
+    const unsigned long long line = prev[(size_t)sg.row * W + lw];
+    const uint32_t row_end = row_begin[sg.row] + (off[sg.row + 1] - off[sg.row]);
+    const uint32_t hi = min(sg.begin + (uint32_t)kPushSegment, row_end);
+    static_assert(kPushSegment == 64, "an edge per lane");
+    const uint32_t j = sg.begin + lane();
+    const bool on = j < hi;
+    const int o = on ? obj[j] : 0, r = MASK && on ? rel[j] : 0;
+    const unsigned words = (unsigned)__ballot(line != 0) & ((1u << W) - 1u);
+    if (W <= kFewWords || __popc(words) <= kFewWords) {  // wavefront-uniform
+        push_edge<W, MASK>(on, o, r, words, [&](int w) {
+            return ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(line >> 32), w) << 32) |
+                   (uint32_t)__builtin_amdgcn_readlane((int)line, w);
+        }, allow, known, cur, act_cur);
+        return;
+    }
+    const int n = (int)(hi - sg.begin);
+    for (int i = 0; i < n; i += 64 / W) {
+        const int idx = i + g;
+        const int oc = __shfl(o, idx & 63), rc = MASK ? __shfl(r, idx & 63) : 0;
+        if (idx < n) {
+            unsigned long long m = line;
+            if (MASK) m &= allow[(size_t)rc * W + lw];
+            if (m && known) m &= ~known[(size_t)oc * W + lw];
+            if (m) atomicOr(&cur[(size_t)oc * W + lw], m);
+            const bool any = group_any<W>(m != 0);
+            if (any && lw == 0) mark_active(act_cur, oc);
+        }
+    }
 }
 
 // visited |= level[h] on the lines the push kernels touched.
 // One wavefront per 64 entities: it reads their two words of the active bitmap once and touches
 // only the lines of the active ones (after a push from a small frontier almost none), W lanes per
 // line, so a dense level is still updated with contiguous accesses.
-template <int W>
+// FIRST: the hop has set bits without asking visited; those that were there (the seeds) leave the level, and so do lines
+// and active bits that held nothing else.
+template <int W, bool FIRST>
 __global__ void __launch_bounds__(256)
-k_update_visited(long long Epad, const uint32_t *__restrict__ act_cur, const unsigned long long *__restrict__ cur,
-                 unsigned long long *visited) {
+k_update_visited(long long Epad, uint32_t *act_cur, unsigned long long *cur, unsigned long long *visited) {
     const long long base = ((long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 64;
     if (base >= Epad) return;  // Epad is a multiple of 64
     const unsigned long long m =
@@ -523,13 +543,27 @@ k_update_visited(long long Epad, const uint32_t *__restrict__ act_cur, const uns
     if (m == 0) return;
     constexpr int GPW = 64 / W;
     const int g = lane() / W, lw = lane() & (W - 1);
+    unsigned long long gone = 0;
 #pragma unroll
     for (int i = 0; i < W; ++i) {
         const int e = i * GPW + g;
-        if ((m >> e) & 1ull) {
-            const size_t x = ((size_t)base + e) * W + lw;
-            visited[x] |= cur[x];
+        const bool on = (m >> e) & 1ull;
+        const size_t x = ((size_t)base + e) * W + lw;
+        unsigned long long c = 0;
+        if (on) {
+            const unsigned long long was = visited[x], set = cur[x];
+            c = FIRST ? set & ~was : set;
+            if (FIRST && c != set) cur[x] = c;
+            if (c) visited[x] = was | c;
         }
+        const bool any = group_any<W>(c != 0);
+        if (FIRST && on && !any) gone |= 1ull << e;
+    }
+    if constexpr (FIRST) {
+        if (!wave_any(gone != 0)) return;
+#pragma unroll
+        for (int x = 32; x >= 1; x >>= 1) gone |= shfl_xor64(gone, x);
+        if (lane() < 2) act_cur[base / 32 + lane()] = (uint32_t)((m & ~gone) >> (32 * lane()));
     }
 }
 
@@ -1140,7 +1174,7 @@ static void launch_push(logoskg_graph *g, logoskg_result *r, int h, const unsign
     unsigned long long *cur = r->levels + plane * h;
     uint32_t *act_cur = r->act + (size_t)(r->Epad / 32) * h;
     long long nt = (long long)hc[C_NTAIL], ns = (long long)hc[C_NSEG];
-    const unsigned long long *known = r->walk_exact ? cur : r->visited;
+    const unsigned long long *known = r->walk_exact ? cur : h == 1 ? nullptr : r->visited;
     if (ns > 0) {
         ProfScope ps(g->prof, KK_PUSH_SEG, st);
         k_push_seg<W, MASK><<<dim3(blocks_for(ns, 4)), dim3(256), 0, st>>>(
@@ -1149,13 +1183,15 @@ static void launch_push(logoskg_graph *g, logoskg_result *r, int h, const unsign
     }
     if (nt > 0) {
         ProfScope ps(g->prof, KK_PUSH_TAIL, st);
-        k_push_tail<W, MASK><<<dim3(blocks_for(nt * W, 256)), dim3(256), 0, st>>>(
+        k_push_tail<W, MASK><<<dim3(blocks_for(nt * push_tail_lanes<W>(), 256)), dim3(256), 0, st>>>(
             list_tail, ctr, g->out_off, g->row_begin, obj, rel, r->allow, prev, known, cur, act_cur);
         g->prof.acc[KK_PUSH_TAIL].units[0] += g->prof.on ? nt : 0;
     }
     if (!update) return;
     ProfScope ps(g->prof, KK_UPDATE, st);
-    k_update_visited<W><<<dim3(blocks_for(r->Epad / 64, 4)), dim3(256), 0, st>>>(r->Epad, act_cur, cur, r->visited);
+    const dim3 grid(blocks_for(r->Epad / 64, 4)), block(256);
+    if (known) k_update_visited<W, false><<<grid, block, 0, st>>>(r->Epad, act_cur, cur, r->visited);
+    else k_update_visited<W, true><<<grid, block, 0, st>>>(r->Epad, act_cur, cur, r->visited);
 }
 
 // STATS: the counting mode runs instantiations of its own, so that kernel statistics of the
