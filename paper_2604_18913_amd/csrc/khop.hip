@@ -167,7 +167,7 @@ template <int LW, bool PULLED>
 __global__ void __launch_bounds__(LW ? 512 : 1024)
 k_census(uint32_t *act, int32_t E, const uint32_t *__restrict__ out_off, unsigned long long *ctr,
          unsigned long long *sums, unsigned long long *host, const unsigned long long *__restrict__ lines,
-         unsigned long long *live, const unsigned long long *go, long long T) {
+         unsigned long long *live, const unsigned long long *go, long long T, int Q) {
     if constexpr (PULLED)
         if (go && *go == kHopNotPulled) return;  // launched ahead for a hop that is not taken this way
     static_assert(!PULLED || LW > 0, "16-word lines are not read for their bits");
@@ -282,6 +282,11 @@ k_census(uint32_t *act, int32_t E, const uint32_t *__restrict__ out_off, unsigne
     __syncthreads();
     if constexpr (LW > 0)
         if (threadIdx.x >= 3 && threadIdx.x < NS) live[threadIdx.x - 3] = total((int)threadIdx.x);
+    // 16-word planes: every query counts as live where the next hop gathers all lines (hardly any query has nothing
+    // left then, and one wrongly taken as live only keeps a row from stopping early: its bit is in no frontier line);
+    // otherwise k_live finds them
+    if constexpr (LW == 0)
+        if (threadIdx.x < 16 && dense_rule((long long)total(2), T)) live[threadIdx.x] = query_bits(Q, (int)threadIdx.x);
     if (threadIdx.x != 0) return;
     lists = total(0);
     rows = total(1);
@@ -291,11 +296,9 @@ k_census(uint32_t *act, int32_t E, const uint32_t *__restrict__ out_off, unsigne
     host[C_NACTIVE] = rows >> 32;
     host[C_FEDGES] = edges = total(2);
     host[C_ERR] = __hip_atomic_load(&ctr[L_ERR], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if constexpr (LW > 0) {
-        ctr[L_PULL] = !pull_rule((long long)edges, T) ? kHopNotPulled : dense_rule((long long)edges, T) ? kHopPulledDense : kHopPulled;
-        __threadfence_system();
-        __hip_atomic_store(&host[kCensusDone], 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
+    if constexpr (LW > 0) ctr[L_PULL] = !pull_rule((long long)edges, T) ? kHopNotPulled : dense_rule((long long)edges, T) ? kHopPulledDense : kHopPulled;
+    __threadfence_system();
+    __hip_atomic_store(&host[kCensusDone], 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // The push lists of a level; ctr[L_CUR_TAIL] and ctr[L_CUR_SEG] are the append cursors (zero before) and then the
@@ -396,13 +399,6 @@ k_live(const uint32_t *__restrict__ act, int32_t E, const uint32_t *__restrict__
         unsigned long long x = sl[threadIdx.x];
         if (x & ~live[threadIdx.x]) atomicOr(&live[threadIdx.x], x);
     }
-}
-
-// Every query counts as live: used instead of k_live where the frontier holds most of the
-// graph's triples (then hardly any query has none, and a query wrongly taken as live only keeps
-// a row from stopping early: its bit is in no frontier line).
-__global__ void k_live_all(int Q, int W, unsigned long long *live) {
-    if ((int)threadIdx.x < W) live[threadIdx.x] = query_bits(Q, (int)threadIdx.x);
 }
 
 // ---------------------------------------------------------------- push
@@ -1206,15 +1202,14 @@ static inline bool dense_pull(const logoskg_graph *g, const unsigned long long *
     return !want_stats && dense_rule((long long)hc[C_FEDGES], g->T);
 }
 
-// live[h-1] of 16-word planes: the queries this hop can still reach something for (once per hop).
-static void launch_live(logoskg_graph *g, logoskg_result *r, int h, bool dense, hipStream_t st) {
+// live[h-1] of 16-word planes: the queries this hop can still reach something for (once per hop; of a dense one by the census).
+static void launch_live(logoskg_graph *g, logoskg_result *r, int h, hipStream_t st) {
     const size_t plane = (size_t)r->Epad * 16;
     ProfScope ps(g->prof, KK_LIVE, st);
     unsigned nb = std::min<unsigned>(2048u, std::max(1u, blocks_for(g->E, 256)));
     unsigned long long *live = r->live + (size_t)16 * (h - 1);
-    if (dense) k_live_all<<<dim3(1), dim3(64), 0, st>>>(r->Q, 16, live);
-    else k_live<16><<<dim3(nb), dim3(256), 0, st>>>(r->act + (size_t)(r->Epad / 32) * (h - 1), g->E, g->out_off,
-                                                    r->levels + plane * (h - 1), live);
+    k_live<16><<<dim3(nb), dim3(256), 0, st>>>(r->act + (size_t)(r->Epad / 32) * (h - 1), g->E, g->out_off,
+                                               r->levels + plane * (h - 1), live);
 }
 
 // Pull over the object rows of the work lists `rc`, whose entries index in_sub / in_rel (the whole
@@ -1299,7 +1294,7 @@ void launch_pull_range(logoskg_graph *g, logoskg_result *r, int h, const RowClas
             pull_rows_w<4>(g, r, h, rc, in_sub, in_rel, dense, want_stats, st);
             break;
         default:
-            if (first) launch_live(g, r, h, dense, st);
+            if (first && !dense) launch_live(g, r, h, st);
             pull_rows_w<16>(g, r, h, rc, in_sub, in_rel, dense, want_stats, st);
             break;
     }
@@ -1382,7 +1377,7 @@ static logoskg_status launch_census(logoskg_graph *g, logoskg_result *r, int h, 
         kernel<<<dim3(nb), dim3((unsigned)threads), 0, st>>>(r->act + (size_t)(r->Epad / 32) * h, g->E, g->out_off,
                                                              level_counters(r, h), g->d_ctr + C_TOTAL, host,
                                                              r->levels + (size_t)r->Epad * r->W * h, r->live + (size_t)16 * h,
-                                                             go, (long long)g->T);
+                                                             go, (long long)g->T, g->prof.counters ? 0 : r->Q);
     };
     if (r->W == 16) launch(k_census<0, false>, 1024, kCensusEntities);
     else if (pulled) launch(r->W == 1 ? k_census<1, true> : k_census<4, true>, 512, 4);
@@ -1391,35 +1386,42 @@ static logoskg_status launch_census(logoskg_graph *g, logoskg_result *r, int h, 
     return LOGOSKG_OK;
 }
 
-// ... into g->h_ctr; synchronises the stream.
+// The counters that a census has written to `host`: waits for its word kCensusDone and not for the stream, behind whose
+// census the next hop may be running.  After a few milliseconds the host stops polling and waits for the stream, which
+// also ends where a launch failed.
+constexpr int kCensusPolls = 1 << 18;  // some 10 ns each
+
+static logoskg_status await_census(const unsigned long long *host, hipStream_t st) {
+    auto done = [&]() { return __atomic_load_n(&host[kCensusDone], __ATOMIC_ACQUIRE) != 0; };
+    for (int turn = 0; turn < kCensusPolls; ++turn) {
+        if (done()) return LOGOSKG_OK;
+        __builtin_ia32_pause();
+    }
+    LKG_HIP(hipStreamSynchronize(st));
+    if (done()) return LOGOSKG_OK;
+    set_error("the frontier census did not run");
+    return LOGOSKG_EINTERNAL;
+}
+
+static unsigned long long *census_slot(logoskg_graph *g, int h) { return g->h_census + (h & 1) * kCensusSlot; }
+
+// ... into g->h_ctr, when everything in front of it is done.  (Waiting for the word instead of the stream: the host is back
+// and the next hop on its way while the census kernel ends.)
 static logoskg_status census(logoskg_graph *g, logoskg_result *r, int h, bool pulled, hipStream_t st) {
-    LKG_TRY(launch_census(g, r, h, pulled, g->h_ctr, nullptr, st));
-    if (g->prof.counters)
+    unsigned long long *host = census_slot(g, h);
+    host[kCensusDone] = 0;
+    LKG_TRY(launch_census(g, r, h, pulled, host, nullptr, st));
+    if (g->prof.counters) {
         LKG_HIP(hipMemcpyAsync(g->h_ctr + C_STATS, g->d_ctr + C_STATS, 4 * KK_NUM * sizeof(unsigned long long),
                                hipMemcpyDeviceToHost, st));
-    LKG_HIP(hipStreamSynchronize(st));
+        LKG_HIP(hipStreamSynchronize(st));
+    }
+    LKG_TRY(await_census(host, st));
+    memcpy(g->h_ctr, host, C_STATS * sizeof(host[0]));
     return LOGOSKG_OK;
 }
 
 logoskg_status count_reached(logoskg_result *r, hipStream_t st);  // result.hip
-
-// The counters that a census has written to `host`: waits for its word kCensusDone and not for the stream, behind whose
-// census the next hop may be running.  (The stream is asked now and then: a launch that failed ends the wait.)
-static logoskg_status await_census(const unsigned long long *host, hipStream_t st) {
-    for (long long turn = 1; !__atomic_load_n(&host[kCensusDone], __ATOMIC_ACQUIRE); ++turn) {
-        if (turn % 2048) continue;
-        const hipError_t e = hipStreamQuery(st);
-        if (e == hipErrorNotReady) {
-            (void)hipGetLastError();  // (launches have been checked)
-            continue;
-        }
-        LKG_HIP(e);
-        if (__atomic_load_n(&host[kCensusDone], __ATOMIC_ACQUIRE)) break;
-        set_error("the frontier census did not run");
-        return LOGOSKG_EINTERNAL;
-    }
-    return LOGOSKG_OK;
-}
 
 // The hops of a narrow batch on a resident graph (direction by rule).  The host needs each level's counters to choose the
 // next hop's direction, and on a graph of a few million triples a hop is 20 us of kernels, about what a wait, a
@@ -1430,7 +1432,7 @@ static logoskg_status await_census(const unsigned long long *host, hipStream_t s
 static logoskg_status narrow_hops(logoskg_graph *g, logoskg_result *r, int first_hop, bool *pending, hipStream_t st) {
     unsigned long long hc[C_TOTAL] = {};
     memcpy(hc, g->h_ctr, C_STATS * sizeof(hc[0]));
-    auto slot = [&](int h) { return g->h_census + (h & 1) * kCensusSlot; };
+    auto slot = [&](int h) { return census_slot(g, h); };
     bool running = false;  // hop h is on its way already
     for (int h = first_hop; h <= r->k; ++h) {
         logoskg_hop_stats &hs = r->stats[(size_t)h - 1];
@@ -1624,8 +1626,14 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
             launch_resident_hop(g, r, h, pull, want_stats, hc, st);
             KH(hipGetLastError());
         }
-        if ((s = census(g, r, h, pull, st)) != LOGOSKG_OK) return fail(s);
-        hs.entities_reached = (long long)g->h_ctr[C_NACTIVE];
+        if (h == k && !want_stats) {  // (its counters only feed the statistics: read behind the counts)
+            census_slot(g, h)[kCensusDone] = 0;
+            if ((s = launch_census(g, r, h, pull, census_slot(g, h), nullptr, st)) != LOGOSKG_OK) return fail(s);
+            pending = true;
+        } else {
+            if ((s = census(g, r, h, pull, st)) != LOGOSKG_OK) return fail(s);
+            hs.entities_reached = (long long)g->h_ctr[C_NACTIVE];
+        }
         if (hs.direction == LOGOSKG_DIR_PULL) {
             if (want_stats) for (int kind : {KK_PULL_TAIL, KK_PULL_SEG}) {
                 const unsigned long long *c = g->h_ctr + C_STATS + 4 * kind;
@@ -1645,7 +1653,7 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
         if ((s = count_reached(r, st)) != LOGOSKG_OK) return fail(s);
     }
     if (pending) {
-        const unsigned long long *host = g->h_census + (k & 1) * kCensusSlot;
+        const unsigned long long *host = census_slot(g, k);
         if ((s = await_census(host, st)) != LOGOSKG_OK) return fail(s);
         r->stats[(size_t)k - 1].entities_reached = (long long)host[C_NACTIVE];
     }
