@@ -20,7 +20,7 @@
 //           row of the entity with a mask of still unresolved queries, so every
 //           (query, entity) pair is written once.  Object rows of up to 32
 //           entries belong to the tile kernels that walk them in ascending
-//           edge id and write the entity and hop lists as well (k_pred_narrow
+//           edge id and write the entity and hop lists as well (k_fetch_narrow
 //           on planes of one and four words, the pair k_pred_walk / k_pred_emit
 //           on 16-word planes with k <= 6; k_pred, beside k_lists, for deeper
 //           searches there); rows of 33 .. hub_min-1 entries belong to
@@ -1902,19 +1902,19 @@ k_emit_sparse(FillArgs a, const uint8_t *__restrict__ codes, const unsigned long
     const long long tile_rel = item % ntile, tile = tile0 + tile_rel;
     const int wi = (int)(item / ntile), w = w0 + wi;
     const size_t at = ((size_t)tile_rel * nw + wi) * 64 + v;
+    const int ql = w * 64 + v;
+    // requested together: the reached pairs, the tile's entities (lane = entity), where a query's run starts (lane = query)
+    // (one behind the other: 1,000 queries with whitelists 534 us, 523 now; over two hops 117 and 106)
     const unsigned long long vis = visbuf[at];
+    const int32_t ev = (int32_t)tile_entity(a.tile_ent, tile, v, a.E);
+    const long long run = super_start(a, tile / kSuperTiles, Qp, ql) + a.tile_base[(size_t)tile * Qp + ql];
+    const size_t eo = ev >= 0 ? (size_t)ev : 0;
+    const uint32_t lo = a.in_off[eo], hi = a.in_off[eo + 1];
     if (!wave_any(vis != 0)) return;
     const unsigned long long reached = transpose64(vis);
-    const int ql = w * 64 + v;
-    if (reached) base[wave][v] = super_start(a, tile / kSuperTiles, Qp, ql) + a.tile_base[(size_t)tile * Qp + ql];
+    base[wave][v] = run;
     mT[wave][v] = reached;
     __builtin_amdgcn_wave_barrier();
-    const int32_t ev = (int32_t)tile_entity(a.tile_ent, tile, v, a.E);
-    uint32_t lo = 0, hi = 0;
-    if (vis) {
-        lo = a.in_off[ev];
-        hi = a.in_off[ev + 1];
-    }
     const bool longrow = hi - lo > (uint32_t)kTailMaxDegree;
     // a lane's predecessors: by place in its short row, or by query in its line of row_pred, or written by the row kernels
     const int32_t *from = a.in_eid + lo;
@@ -2233,7 +2233,7 @@ __global__ void k_long_index(const int32_t *__restrict__ rows, long long n, int3
 logoskg_status prepare_row_pred(logoskg_graph *g, hipStream_t st) {
     if (g->row_pred_tried) return LOGOSKG_OK;
     g->row_pred_tried = true;
-    // code bytes and visited words between the two kernels of the bit-sliced predecessor pass: room
+    // planes, or code bytes and visited words, between the two kernels of the bit-sliced predecessor pass: room
     // for every tile of the graph and 16 words, but not more than 1.25 GiB
     g->plane_buf_bytes = std::min<size_t>((size_t)5 << 28, (size_t)(g->Epad / 64 + kEmitTiles) * 16 * 64 * (64 + 8));
     if (hipMalloc((void **)&g->plane_buf, g->plane_buf_bytes) != hipSuccess) {
@@ -2590,7 +2590,7 @@ static void launch_pred_wms(Profiler &prof, const FillArgs &a0, long long n_hub_
                 k_emit_sparse<<<dim3((unsigned)(((n * nw + 3) / 4 + 7) / 8 * 8)), dim3(256), 0, st_tiles>>>(
                     a, reinterpret_cast<const uint8_t *>(a.plane_buf), visbuf, t0, n, w0, nw);
             else k_pred_emit<<<ge, dim3(kEmitTiles * 64), 0, st_tiles>>>(a, a.plane_buf, t0, n, w0, nw, a.emit_eid_cap, a.emit_line_cap);
-            if (prof.on) {  // entities x words whose code bytes pass from the first kernel to the second
+            if (prof.on) {  // entities x words whose planes pass from the first kernel to the second
                 prof.acc[KK_PRED_WALK].units[3] += n * 64 * nw;
                 prof.acc[KK_PRED].units[0] += n * 64 * nw;
             }
