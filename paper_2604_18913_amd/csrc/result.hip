@@ -1379,7 +1379,7 @@ __global__ void __launch_bounds__(1024) k_pred(FillArgs a) {
 // so nothing in it waits for its own stores.  Rows of more than 32 entries belong to the row
 // kernels: such an entity's predecessors come from row_pred, which those kernels fill before
 // this one starts (or, without that buffer, the row kernels write them to the lists themselves).
-// What bounds it is HBM: 1.57 ms for 633M pairs of 1,024 queries (1,663 us with two words per block, a chain of seven
+// What bounds it is HBM: 1.57 ms for 506M pairs of 1,024 queries (1,663 us with two words per block, a chain of seven
 // dependent loads ahead of the loop and the visited words written and read beside the codes), 2.48 ms for 930M pairs of 64
 // queries on 20M entities (3,344 us; there the ids of nine entries a row did not fit the half of the LDS that was theirs).
 constexpr int kSlicedMaxK = 6;     // hop + 1 <= 7 fits three bits
