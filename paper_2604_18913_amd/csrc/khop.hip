@@ -1536,7 +1536,14 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
     const size_t plane = (size_t)r->Epad * W;
     const size_t actw = (size_t)r->Epad / 32;
     logoskg_status s;
-    auto fail = [&](logoskg_status e) { logoskg_result_free(r); return e; };
+    // From the first census on a failed call ends with its stream idle, like one that succeeds: what is still queued
+    // writes the graph's pinned words and would be taken for the next call's census.
+    bool censused = false;
+    auto fail = [&](logoskg_status e) {
+        if (censused) (void)hipStreamSynchronize(st);
+        logoskg_result_free(r);
+        return e;
+    };
     // visited and the level planes are one allocation, the active bitmaps, the live words and the levels'
     // counters another: each is cleared by one fill
     const size_t act_bytes = actw * 4 * (size_t)(k + 1), live_bytes = (size_t)(16 + kLevelCounters) * 8 * (size_t)(k + 1);
@@ -1590,6 +1597,7 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
                                                                r->seed_off, r->seeds);
         g->prof.end(st);
         KH(hipGetLastError());
+        censused = true;
         if ((s = census(g, r, 0, false, st)) != LOGOSKG_OK) return fail(s);
         if (g->h_ctr[C_ERR]) {
             set_error("seed_off / seeds are inconsistent or out of range (device check, code %llu)", g->h_ctr[C_ERR]);
@@ -1598,10 +1606,8 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
     }
     const bool narrow = W <= 4 && g->num_shards <= 1 && !want_stats && dir == LOGOSKG_DIR_AUTO;
     bool pending = false;
-    if (narrow && (s = narrow_hops(g, r, first_hop, &pending, st)) != LOGOSKG_OK) {
-        (void)hipStreamSynchronize(st);  // (kernels launched ahead may still run on the result's planes)
-        return fail(s);
-    }
+    censused = true;
+    if (narrow && (s = narrow_hops(g, r, first_hop, &pending, st)) != LOGOSKG_OK) return fail(s);
     for (int h = first_hop; !narrow && h <= k; ++h) {
         logoskg_hop_stats &hs = r->stats[h - 1];
         long long rows = (long long)g->h_ctr[C_NROWS];
