@@ -1658,6 +1658,9 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
     if (want_counts && !r->has_counts) {
         if ((s = count_reached(r, st)) != LOGOSKG_OK) return fail(s);
     }
+    // Without counts nothing has waited for the stream yet: a census is polled while its kernel ends, and what the kernel's
+    // other blocks have written (a pulled level's bitmap) other streams see behind its end only.
+    if (!want_counts) KH(hipStreamSynchronize(st));
     if (pending) {
         const unsigned long long *host = census_slot(g, k);
         if ((s = await_census(host, st)) != LOGOSKG_OK) return fail(s);

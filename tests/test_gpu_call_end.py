@@ -1,4 +1,4 @@
-"""How a k-hop call ends: what a call that fails behind its hops leaves to the next one."""
+"""How a k-hop call ends: what a call that fails behind its hops leaves to the next one, and that its stream is idle."""
 import numpy as np
 import pytest
 
@@ -84,4 +84,42 @@ def test_a_call_behind_one_without_room_for_its_counts(triples, Q, direction, k)
         torch.cuda.synchronize()
         g.close()
         g = lkg.Graph(s, r, o, E, R, dev_alloc=mem.alloc, dev_free=mem.free)
+    g.close()
+
+
+@pytest.mark.parametrize("shards", [0, 3])
+@pytest.mark.parametrize("Q, direction, walk", [(1, "auto", False), (3, "auto", False), (3, "pull", True), (64, "push", False),
+                                                (200, "auto", False), (200, "auto", True), (200, "pull", False),
+                                                (400, "auto", False), (400, "pull", True)])
+def test_a_call_without_counts_leaves_its_stream_idle(Q, direction, walk, shards):
+    """... and its levels to whoever reads them on another stream."""
+    import torch
+    import paper_2604_18913_amd as lkg
+    rng = np.random.default_rng(Q)
+    E, T, R, k = 1_000_003, 3_000_000, 4, 3
+    s, r, o = (rng.integers(0, n, T).astype(np.int32) for n in (E, R, E))
+    s[:T // 2] = rng.integers(0, 5, T // 2)  # (some hubs: the first hops pull)
+    off, seeds = np.arange(Q + 1, dtype=np.int64), rng.integers(0, E, Q).astype(np.int32)
+    seeds[0] = 3
+    if walk:
+        w_off, w_ent = oracle.walk_levels(E, s, r, o, off, seeds, k)
+    else:
+        want = oracle.khop(E, s, r, o, off, seeds, k)
+    g = lkg.Graph(s, r, o, E, R, num_shards=shards)
+    inputs = [torch.from_numpy(x).cuda() for x in (off, seeds)]
+    one, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for h in range(k, -1, -1):
+        res = g.khop(*inputs, k, direction=direction, counts=False, walk_exact=walk, stream=one)
+        assert one.query()
+        at, ent = res.level(h, stream=other)
+        other.synchronize()
+        if walk:
+            a = w_off[h * Q:(h + 1) * Q + 1]
+            assert np.array_equal(at, a - a[0]) and np.array_equal(ent.cpu().numpy(), w_ent[a[0]:a[-1]])
+        else:
+            on = want[2] == h
+            assert np.array_equal(at, np.concatenate([[0], np.cumsum(on)])[want[0]])
+            assert np.array_equal(ent.cpu().numpy(), want[1][on])
+        res.close()
     g.close()
