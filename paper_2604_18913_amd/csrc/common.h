@@ -399,6 +399,15 @@ __device__ __forceinline__ unsigned long long query_bits(int Q, int w) {
     return (1ull << (Q - lo)) - 1ull;
 }
 
+// A launch holds at most UINT32_MAX threads.  Items whose kernels take several lanes each go in ranges, launch(first, n), of
+// per_block items to a block of 256 threads; nearly always there is one.
+constexpr long long kMaxBlocks = (long long)UINT32_MAX / 256;
+
+template <typename Launch>
+inline void launch_ranges(long long n, long long per_block, Launch launch, long long max_blocks = kMaxBlocks) {
+    for (long long first = 0, most = max_blocks * per_block; first < n; first += most) launch(first, n - first < most ? n - first : most);
+}
+
 inline int words_for_queries(int Q) { return Q <= 64 ? 1 : (Q <= 256 ? 4 : 16); }
 
 // arguments of the list / predecessor kernels (result.hip)

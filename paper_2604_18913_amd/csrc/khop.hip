@@ -445,14 +445,14 @@ constexpr int push_tail_lanes() { return W == 16 ? 16 : 8; }
 
 template <int W, bool MASK>
 __global__ void __launch_bounds__(256)
-k_push_tail(const int32_t *__restrict__ rows, const unsigned long long *__restrict__ ctr,
+k_push_tail(const int32_t *__restrict__ rows, long long first, const unsigned long long *__restrict__ ctr,
             const uint32_t *__restrict__ off, const uint32_t *__restrict__ row_begin,
             const int32_t *__restrict__ obj,
             const uint16_t *__restrict__ rel, const unsigned long long *__restrict__ allow,
             const unsigned long long *__restrict__ prev, const unsigned long long *known,
             unsigned long long *cur, uint32_t *act_cur) {
     constexpr int G = push_tail_lanes<W>();
-    const long long gidx = ((long long)blockIdx.x * blockDim.x + threadIdx.x) / G;
+    const long long gidx = first + ((long long)blockIdx.x * blockDim.x + threadIdx.x) / G;
     const int gl = threadIdx.x & (G - 1), g0 = lane() & ~(G - 1);
     if (gidx >= (long long)ctr[C_NTAIL]) return;  // the lanes of a group together
     const int s = rows[gidx];
@@ -1183,8 +1183,11 @@ static void launch_push(logoskg_graph *g, logoskg_result *r, int h, const unsign
     }
     if (nt > 0) {
         ProfScope ps(g->prof, KK_PUSH_TAIL, st);
-        k_push_tail<W, MASK><<<dim3(blocks_for(nt * push_tail_lanes<W>(), 256)), dim3(256), 0, st>>>(
-            list_tail, ctr, g->out_off, g->row_begin, obj, rel, r->allow, prev, known, cur, act_cur);
+        constexpr int G = push_tail_lanes<W>();
+        launch_ranges(nt, 256 / G, [&](long long first, long long n) {
+            k_push_tail<W, MASK><<<dim3(blocks_for(n * G, 256)), dim3(256), 0, st>>>(
+                list_tail, first, ctr, g->out_off, g->row_begin, obj, rel, r->allow, prev, known, cur, act_cur);
+        });
         g->prof.acc[KK_PUSH_TAIL].units[0] += g->prof.on ? nt : 0;
     }
     if (!update) return;
@@ -1228,10 +1231,19 @@ static void launch_pull_rows(logoskg_graph *g, logoskg_result *r, int h, const R
     if constexpr (W <= 4 && !STATS) {
         if (rc.n_seg + rc.n_tail == 0) return;
         ProfScope ps(g->prof, KK_PULL_TAIL, st);
-        const unsigned seg_blocks = blocks_for(rc.n_seg, 4);
-        const dim3 grid(seg_blocks + blocks_for(rc.n_tail * kNarrowTailLanes, 256)), block(256);
-        k_pull_narrow<W, MASK><<<grid, block, 0, st>>>(rc.seg, rc.n_seg, seg_blocks, rc.tail, rc.n_tail, in_sub, in_rel,
-                                                       r->allow, act_prev, prev, live, r->visited, cur, walk, dense, go);
+        constexpr int rows_per_block = 256 / kNarrowTailLanes;
+        auto launch = [&](long long n_seg, long long first, long long n_rows) {
+            const unsigned seg_blocks = blocks_for(n_seg, 4);
+            const dim3 grid(seg_blocks + blocks_for(n_rows, rows_per_block)), block(256);
+            k_pull_narrow<W, MASK><<<grid, block, 0, st>>>(rc.seg, n_seg, seg_blocks, rc.tail + first, n_rows, in_sub, in_rel,
+                                                           r->allow, act_prev, prev, live, r->visited, cur, walk, dense, go);
+        };
+        if ((rc.n_seg + 3) / 4 + (rc.n_tail + rows_per_block - 1) / rows_per_block <= kMaxBlocks) {
+            launch(rc.n_seg, 0, rc.n_tail);
+        } else {  // (as many segments as triple indices allow fit one launch)
+            if (rc.n_seg > 0) launch(rc.n_seg, 0, 0);
+            launch_ranges(rc.n_tail, rows_per_block, [&](long long first, long long n) { launch(0, first, n); });
+        }
         return;
     } else {
     if (rc.n_seg > 0) {
