@@ -25,12 +25,13 @@ const char *get_error() { return g_err.c_str(); }
 
 logoskg_status DevPool::alloc(void **out, size_t bytes, hipStream_t st, bool have_stream, bool *zeroed) {
     if (zeroed) *zeroed = false;
+    const size_t asked = bytes;
     if (bytes == 0) bytes = 256;
     bytes = (bytes + 255) & ~size_t(255);
     auto it = free_.lower_bound(bytes);
     if (it != free_.end() && it->first <= bytes * 2) {
         Block b = it->second;
-        live_[b.p] = it->first;
+        live_[b.p] = Live{it->first, asked, b.zeros};
         free_.erase(it);
         if (b.after) {  // released behind work that may still run
             hipError_t e = hipSuccess;
@@ -41,7 +42,7 @@ logoskg_status DevPool::alloc(void **out, size_t bytes, hipStream_t st, bool hav
                 return LOGOSKG_EDEVICE;
             }
         }
-        if (zeroed) *zeroed = b.zeroed;
+        if (zeroed) *zeroed = b.zeros >= asked;
         *out = b.p;
         return LOGOSKG_OK;
     }
@@ -54,7 +55,7 @@ logoskg_status DevPool::alloc(void **out, size_t bytes, hipStream_t st, bool hav
         }
     }
     held_ += bytes;
-    live_[p] = bytes;
+    live_[p] = Live{bytes, asked, 0};
     *out = p;
     return LOGOSKG_OK;
 }
@@ -79,7 +80,7 @@ void DevPool::release(void *p) {
     if (!p) return;
     auto it = live_.find(p);
     if (it == live_.end()) return;
-    free_.emplace(it->second, Block{p, nullptr, false});
+    free_.emplace(it->second.size, Block{p, nullptr, 0});
     live_.erase(it);
 }
 
@@ -109,7 +110,8 @@ void DevPool::release_after(void *const *ptrs, const bool *zeroed, int n, hipStr
         if (!ptrs[i]) continue;
         auto it = live_.find(ptrs[i]);
         if (it == live_.end()) continue;
-        free_.emplace(it->second, Block{ptrs[i], after, zeroed ? zeroed[i] : false});
+        const Live &l = it->second;  // (cleared: at least what was asked for; bytes behind it that were zero have stayed so)
+        free_.emplace(l.size, Block{ptrs[i], after, zeroed && zeroed[i] ? std::max(l.asked, l.zeros) : 0});
         live_.erase(it);
     }
 }

@@ -50,7 +50,9 @@ const char *get_error();
 // enough and at most 2x the request).  A block released behind work that may
 // still run (release_after) carries an event recorded on that work's stream: a
 // later user on another stream waits for it, a user without a stream waits on
-// the host.  Such a block can also be marked as holding zeros only.
+// the host.  Such a block can also be marked as cleared: the bytes that its user had asked for are zero (a block may be
+// larger, and what lies behind them, also up to the next multiple of 256, is not), and only requests that
+// these bytes hold are told so.
 class DevPool {
 public:
     logoskg_status alloc(void **out, size_t bytes) { return alloc(out, bytes, nullptr, false, nullptr); }
@@ -71,10 +73,11 @@ public:
 
 private:
     struct After { hipEvent_t ev; hipStream_t stream; };
-    struct Block { void *p; std::shared_ptr<After> after; bool zeroed; };
+    struct Block { void *p; std::shared_ptr<After> after; size_t zeros; };  // zeros: so many bytes from its start are zero
+    struct Live { size_t size, asked, zeros; };                             // of the block, of the request; zeros when handed out
     logoskg_status alloc(void **out, size_t bytes, hipStream_t st, bool have_stream, bool *zeroed);
     std::multimap<size_t, Block> free_;
-    std::unordered_map<void *, size_t> live_;
+    std::unordered_map<void *, Live> live_;
     std::vector<hipEvent_t> spare_events_;
     size_t held_ = 0;
     void *(*alloc_fn_)(size_t, void *) = nullptr;
