@@ -158,9 +158,12 @@ k_active_fill(const uint32_t *__restrict__ act, long long actw, int levels, long
     write_listed(active_word(act, actw, levels, first + lane()), first, (long long)chunk_base[chunk], tile_ent, cpos);
 }
 
-// The three in one launch for graphs of up to kActiveOneLaunch entities: a block (a thread per bitmap word) counts what
-// lies before it by itself.  The blocks' common reading grows with the square of the graph.
-constexpr long long kActiveOneLaunch = 1ll << 20;
+// The three in one launch: a block (a thread per bitmap word) counts what lies before it by itself.  The blocks' common
+// reading grows with the square of the graph and with the levels, so only bitmaps of few words go this way.  Searches of one
+// question, one launch less three, us, by entities and levels: 16,384 x 4 -4, x 32 -3; 65,536 x 8 -2, x 16 +7; 131,072 x 4
+// -1, x 12 +5; 262,144 x 4 0, x 8 +7; 407,000 x 4 +4, x 12 +19; 1M x 2 +14, x 32 +129.
+constexpr long long kActiveOneLaunch = 1ll << 19;  // entities times levels
+inline bool active_in_one_launch(long long Epad, int levels) { return Epad * levels <= kActiveOneLaunch; }
 constexpr int kActiveListThreads = 256;
 
 __global__ void __launch_bounds__(kActiveListThreads)
@@ -2156,7 +2159,7 @@ static logoskg_status ensure_active_list(logoskg_result *r, hipStream_t st) {
     r->d_nact = reinterpret_cast<unsigned long long *>(r->act_chunk + (nchunks + 1) / 2 * 2);
     r->n_active = -1;
     ProfScope ps(g->prof, KK_SCAN, st);
-    if (r->Epad <= kActiveOneLaunch) {
+    if (active_in_one_launch(r->Epad, r->k + 1)) {
         k_active_list<<<dim3((unsigned)((actw + kActiveListThreads - 1) / kActiveListThreads)), dim3(kActiveListThreads), 0, st>>>(r->act, actw, r->k + 1, r->d_nact, r->tile_ent, r->cpos);
         LKG_HIP(hipGetLastError());
         return LOGOSKG_OK;
