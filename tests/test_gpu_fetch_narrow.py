@@ -55,3 +55,32 @@ def test_more_threads_than_a_launch_takes():
         assert np.array_equal(got.cpu().numpy(), w)
     res.close()
     g.close()
+
+
+@pytest.mark.parametrize("Q, masked", [(40, False), (200, True)])
+def test_a_recorded_fetch_of_rows_in_segments(Q, masked):
+    """A capture takes no memory for the segments: the kernels run one by one, and a fetch behind them in one launch."""
+    import paper_2604_18913_amd as lkg
+    from test_gpu_capture import Arena, captured_fetch
+    rng = np.random.default_rng(Q)
+    E, R, k = 6007, 11, 3
+    rows = [33, 1024, 2048, 2049, 4097, 8191]
+    o = np.concatenate([np.repeat(rng.permutation(E)[:len(rows)], rows), rng.integers(0, E, 9000)]).astype(np.int32)
+    s, r = rng.integers(0, E, o.size).astype(np.int32), rng.integers(0, R, o.size).astype(np.int32)
+    s[rng.random(o.size) < 0.2] = 5
+    off = np.arange(Q + 1, dtype=np.int64)
+    seeds = rng.integers(0, E, Q).astype(np.int32)
+    seeds[0] = 5
+    mask = rng.integers(0, 2**R, (Q, 1)).astype(np.uint64) if masked else None
+    want = oracle.khop(E, s, r, o, off, seeds, k, mask)
+    arena = Arena(256 << 20)
+    g = lkg.Graph(s, r, o, E, R, dev_alloc=arena.alloc, dev_free=arena.free)
+    res = g.khop(off, seeds, k, mask, direction="pull")
+    for q0, q1 in ((0, Q), (7, Q - 5)):
+        for got in captured_fetch(res, arena, q0, q1):
+            for x, y in zip(got, want[1:4]):
+                assert np.array_equal(x, y[want[0][q0]:want[0][q1]])
+        for x, y in zip(res.fetch(q0, q1), want[1:4]):
+            assert np.array_equal(x.cpu().numpy(), y[want[0][q0]:want[0][q1]])
+    res.close()
+    g.close()
