@@ -268,7 +268,8 @@ typedef struct {
     int64_t frontier_edges;   /* sum of their out-degrees                                               */
     int64_t rows_scanned;     /* pull: object rows visited that were not already complete (profiling on) */
     int64_t edges_scanned;    /* CSR entries read by the expansion kernels (pull: profiling on)          */
-    int64_t lines_gathered;   /* pull: frontier lines read (profiling on); push: visited lines read      */
+    int64_t lines_gathered;   /* pull: frontier lines read (profiling on); push: edges_scanned, a visited
+                                 line per triple at most (the first hop reads none)                     */
     int64_t entities_reached; /* entities with at least one new query bit at this hop                   */
 } logoskg_hop_stats;
 
@@ -299,8 +300,14 @@ logoskg_status logoskg_result_offsets(const logoskg_result *r, int64_t *reached_
  * them from the start, logoskg_graph_info.device_bytes; without room for them
  * the call does without).  From the graph's pool, given back to it behind the
  * call's work, a call with pred_edge takes
- *   - with at most 256 queries, or k > 6: 256, 1,024 or 4,096 bytes (for 64, 256
- *     and more queries) per object row of at least 8,192 entries;
+ *   - with at most 256 queries: 256 bytes (64 queries) or 1,024 (more) per 2,048
+ *     entries, rounded up, of every object row that has more than 2,048 entries
+ *     and at least hub_min_degree.  Where that has no room, under
+ *     LOGOSKG_OVERLAP_FETCH, where the shard cache holds the graph in part only
+ *     and in searches so deep that rows times hops pass one launch: as much
+ *     per object row of at least 8,192 entries;
+ *   - with more queries and k > 6: 4,096 bytes per object row of at least 8,192
+ *     entries;
  *   - for a page of more than 256 queries whose words are one, two or four
  *     aligned ones, on a result that lists at least 4 M entities: 8, 16 or 32
  *     bytes per entity and level (no more than 4 GiB; not packed otherwise).

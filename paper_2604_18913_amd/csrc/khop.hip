@@ -92,7 +92,7 @@ __host__ __device__ inline bool dense_rule(long long edges, long long T) { retur
 // and writes the totals to pinned host memory, so that no copy runs between the census and the host's wait.  The
 // tickets and cursors lie behind the live words and come zeroed with them: no fill either.  With an entity per thread and step, five atomics per
 // block of 1,024 and a fill before and a copy behind, a census took 17 .. 33 us and its fill and copy 13 us;
-// 12 us now for 3M entities, 7 us for 407,000 (a chain of a few reads and the tickets).
+// 12 us now for 3M entities, 9 us for 407,000 with the live words of narrow planes (a chain of a few reads and the tickets).
 constexpr int kCensusEntities = 8;  // per thread
 
 // the degrees of the active ones among entities e0 .. e0 + 7 (0 elsewhere), and their bits

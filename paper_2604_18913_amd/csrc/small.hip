@@ -91,7 +91,7 @@ struct SmallArgs {
 // ids[0 .. n) in ascending order (different ids, n <= kSmallEntities), by all threads of a block of kSmallThreads; behind it
 // the block has met at a barrier.  tmp: kSmallEntities ints, count: 2 kSmallThreads ints.  The ids are dealt to one bucket per
 // thread by their place between the smallest and the largest, and ranked inside their bucket: eight barriers where
-// a bitonic sort of 2,048 ids has 66 (64 questions on 10,000 entities: k_small_search 41 -> 22 us).  That sort remains for ids
+// a bitonic sort of 2,048 ids has 66 (64 questions on 10,000 entities: k_small_search 41 -> 27 us).  That sort remains for ids
 // so uneven that a bucket gets more than kSortBucket.
 constexpr int kSortBucket = 32;
 
