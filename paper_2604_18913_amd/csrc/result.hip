@@ -1382,10 +1382,12 @@ __global__ void __launch_bounds__(1024) k_pred(FillArgs a) {
 // so nothing in it waits for its own stores.  Rows of more than 32 entries belong to the row
 // kernels: such an entity's predecessors come from row_pred, which those kernels fill before
 // this one starts (or, without that buffer, the row kernels write them to the lists themselves).
-// What bounds it is HBM: 1.57 ms for 506M pairs of 1,024 queries (1,663 us with two words per block, a chain of seven
-// dependent loads ahead of the loop and the visited words written and read beside the codes), 2.48 ms for 930M pairs of 64
-// queries on 20M entities (3,344 us; there the ids of nine entries a row did not fit the half of the LDS that was theirs).
-// (On the benchmark's graph, 633M pairs, this kernel takes 1.89 ms instead of 1.81 and the walk 0.74 instead of 0.84.)
+// It waits for memory, short of a copy's rate (4.86 TB/s): a store covers the entities of one tile that one query reached, 55 %
+// and 78 % of its lanes in the two calls that follow.  1.57 ms for 516M pairs of 1,024 queries, 5.9 GB by the counters, 3.8 TB/s (1,663 us with two words per
+// block, a chain of seven dependent loads ahead of the loop and the visited words written and read beside the codes); 2.48 ms for
+// 993M pairs of 64 queries on 20M entities, 11.3 GB, 4.5 TB/s (3,344 us; there the ids of nine entries a row did not fit the
+// half of the LDS that was theirs).  (On the benchmark's graph, 633M pairs, 7.1 GB instead of 8.7, this kernel takes 1.89 ms
+// instead of 1.81 and the walk 0.74 instead of 0.84.)
 constexpr int kSlicedMaxK = 6;     // hop + 1 <= 7 fits three bits
 
 constexpr int kPageEntries = 2;  // entries one lane per entity gathers together (on packed planes 1: 2.4, 2: 2.4, 4: 2.7, 8: 3.3 ms)
