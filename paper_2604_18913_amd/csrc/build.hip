@@ -201,42 +201,14 @@ static logoskg_status upload(T **dst, const std::vector<T> &src, size_t *acct) {
     return LOGOSKG_OK;
 }
 
-// Object rows with >= 1 entry: short rows, segments of the longer ones (longest
-// rows first), rows with several segments, and the hub rows.
-static void classify_rows(const std::vector<uint32_t> &off, int32_t E, int hub_min,
-                          std::vector<ShortRow> &tail, std::vector<PullSegment> &seg,
-                          std::vector<int32_t> &multi, std::vector<int32_t> &longer, int64_t *n_hub) {
-    std::vector<std::vector<int32_t>> bucket(kTailMaxDegree + 1);
-    *n_hub = 0;
-    for (int32_t v = 0; v < E; ++v) {
-        uint32_t d = off[v + 1] - off[v];
-        if (d == 0) continue;
-        if (d >= (uint32_t)hub_min) ++*n_hub;
-        if (d > (uint32_t)kTailMaxDegree) longer.push_back(v);
-        else bucket[d].push_back(v);
-    }
-    for (int d = kTailMaxDegree; d >= 1; --d)
-        for (int32_t v : bucket[d]) tail.push_back({v, off[v], off[v + 1]});
-    std::stable_sort(longer.begin(), longer.end(), [&](int32_t a, int32_t b) {
-        return off[a + 1] - off[a] > off[b + 1] - off[b];
-    });
-    for (int32_t v : longer) {
-        const bool several = off[v + 1] - off[v] > (uint32_t)kPullSegment;
-        if (several) multi.push_back(v);
-        for (uint32_t j = off[v]; j < off[v + 1]; j += kPullSegment)
-            seg.push_back({v, j, std::min(j + (uint32_t)kPullSegment, off[v + 1]), several ? 1u : 0u});
-    }
-}
-
-std::vector<uint32_t> append_hub_segments(std::vector<uint32_t> table, const std::vector<int32_t> &longer,
-                                          const std::vector<uint32_t> &off, RowClasses *rows) {
+std::vector<uint32_t> append_hub_segments(std::vector<uint32_t> table, const std::vector<ShortRow> &longer, RowClasses *rows) {
     rows->n_split = 0;
     rows->n_split_segs = 0;
     uint32_t first = 0;
     table.push_back(first);
     for (int64_t i = 0; i < rows->n_hub; ++i) {
-        const int32_t v = longer[(size_t)i];
-        const uint32_t n = (off[(size_t)v + 1] - off[v] + kHubSegment - 1) / kHubSegment;
+        const ShortRow &r = longer[(size_t)i];
+        const uint32_t n = (r.end - r.begin + kHubSegment - 1) / kHubSegment;
         table.push_back(first += n);
         if (n > 1) {
             ++rows->n_split;
@@ -245,6 +217,52 @@ std::vector<uint32_t> append_hub_segments(std::vector<uint32_t> table, const std
     }
     rows->n_hub_segs = first;
     return table;
+}
+
+static void drop_pairs(logoskg_graph *g) {
+    PairRows &p = g->pairs;
+    for (void *x : {(void *)p.off, (void *)p.pull_sub, (void *)p.sub, (void *)p.eid, (void *)p.long_index, (void *)p.rows.tail,
+                    (void *)p.rows.seg, (void *)p.rows.multi, (void *)p.rows.longrows, (void *)p.rows.giant_seg_first})
+        if (x) (void)hipFree(x);
+    p = PairRows();
+}
+
+// Work lists over the rows of a CSR: short rows (on the device), segments of the longer ones (longest rows first; by_place:
+// the first segments of all rows, then the second ones, ..), rows with several segments, giant and hub rows' segments.
+static logoskg_status row_classes(logoskg_graph *g, const uint32_t *d_off, bool by_place, RowClasses *rc) {
+    std::vector<ShortRow> longer;
+    LKG_TRY(classify_on_device(d_off, g->E, g->hub_min, rc, &longer, &g->static_bytes));
+    std::stable_sort(longer.begin(), longer.end(), [](const ShortRow &a, const ShortRow &b) { return a.end - a.begin > b.end - b.begin; });
+    std::vector<int32_t> rows, multi;
+    std::vector<PullSegment> seg;
+    std::vector<uint32_t> first(1, 0);  // segments of the giant rows, for the predecessor pass
+    const uint32_t giant_min = (uint32_t)std::max(kGiantRowMin, g->hub_min);
+    rows.reserve(longer.size());
+    for (const ShortRow &r : longer) {
+        const uint32_t d = r.end - r.begin;
+        rows.push_back(r.row);
+        if (d > (uint32_t)kPullSegment) multi.push_back(r.row);
+        if (d >= giant_min) first.push_back(first.back() + (d + kGiantSegment - 1) / kGiantSegment);
+        for (uint32_t j = r.begin; j < r.end && (!by_place || j == r.begin); j += kPullSegment)
+            seg.push_back({r.row, j, std::min(j + (uint32_t)kPullSegment, r.end), d > (uint32_t)kPullSegment ? 1u : 0u});
+    }
+    for (uint32_t place = kPullSegment; by_place && !longer.empty() && place < longer[0].end - longer[0].begin; place += kPullSegment)
+        for (const ShortRow &r : longer) {
+            if (r.end - r.begin <= place) break;
+            seg.push_back({r.row, r.begin + place, std::min(r.begin + place + (uint32_t)kPullSegment, r.end), 1u});
+        }
+    rc->n_giant = (int64_t)first.size() - 1;
+    rc->n_giant_segs = first.back();
+    rc->n_seg = (int64_t)seg.size();
+    rc->n_multi = (int64_t)multi.size();
+    rc->n_long = (int64_t)longer.size();
+    if (!longer.empty()) rc->longest = longer[0].end - longer[0].begin;
+    LKG_TRY(upload(&rc->giant_seg_first, append_hub_segments(std::move(first), longer, rc), &g->static_bytes));
+    rc->hub_seg_first = rc->giant_seg_first + rc->n_giant + 1;
+    LKG_TRY(upload(&rc->seg, seg, &g->static_bytes));
+    LKG_TRY(upload(&rc->multi, multi, &g->static_bytes));
+    LKG_TRY(upload(&rc->longrows, rows, &g->static_bytes));
+    return LOGOSKG_OK;
 }
 
 }  // namespace lkg
@@ -310,50 +328,28 @@ extern "C" logoskg_status logoskg_build(const int32_t *subj, const int32_t *rel,
     logoskg_status st = LOGOSKG_OK;
     auto fail = [&](logoskg_status s) { logoskg_graph_free(g); return s; };
     try {
-        // row classes of the object-sorted CSR (pull and predecessor work lists)
-        auto object_row_classes = [&](const std::vector<uint32_t> &ioff) -> logoskg_status {
-            std::vector<int32_t> multi, longer;
-            std::vector<ShortRow> tail;
-            std::vector<PullSegment> seg;
-            classify_rows(ioff, E, g->hub_min, tail, seg, multi, longer, &g->in_rows.n_hub);
-            g->in_rows.n_giant = 0;
-            for (int32_t v : longer)  // longest first
-                if (ioff[(size_t)v + 1] - ioff[v] >= (uint32_t)std::max(kGiantRowMin, g->hub_min)) g->in_rows.n_giant++;
-                else break;
-            {   // segments of the giant rows, for the predecessor pass
-                std::vector<uint32_t> first((size_t)g->in_rows.n_giant + 1, 0);
-                for (int64_t i = 0; i < g->in_rows.n_giant; ++i) {
-                    const int32_t v = longer[(size_t)i];
-                    first[(size_t)i + 1] = first[(size_t)i] + (ioff[(size_t)v + 1] - ioff[v] + kGiantSegment - 1) / kGiantSegment;
-                }
-                g->in_rows.n_giant_segs = first.back();
-                LKG_TRY(upload(&g->in_rows.giant_seg_first, append_hub_segments(first, longer, ioff, &g->in_rows), &g->static_bytes));
-                g->in_rows.hub_seg_first = g->in_rows.giant_seg_first + g->in_rows.n_giant + 1;
+        // work lists over the rows of OBJ (pull and predecessor kernels), and the rows of distinct pairs with theirs
+        auto object_rows = [&]() -> logoskg_status {
+            LKG_TRY(row_classes(g, g->in_off, false, &g->in_rows));
+            LKG_TRY(build_pairs_on_device(g));
+            if (g->pairs.off && row_classes(g, g->pairs.off, true, &g->pairs.rows) != LOGOSKG_OK) {
+                (void)hipGetLastError();  // (the graph works without them)
+                drop_pairs(g);
             }
-            g->in_rows.n_tail = (int64_t)tail.size();
-            g->in_rows.n_seg = (int64_t)seg.size();
-            g->in_rows.n_multi = (int64_t)multi.size();
-            g->in_rows.n_long = (int64_t)longer.size();
-            if (!longer.empty()) g->in_rows.longest = ioff[(size_t)longer[0] + 1] - ioff[longer[0]];
-            LKG_TRY(upload(&g->in_rows.tail, tail, &g->static_bytes));
-            LKG_TRY(upload(&g->in_rows.seg, seg, &g->static_bytes));
-            LKG_TRY(upload(&g->in_rows.multi, multi, &g->static_bytes));
-            LKG_TRY(upload(&g->in_rows.longrows, longer, &g->static_bytes));
             return LOGOSKG_OK;
         };
-        auto subject_row_counts = [&](const std::vector<uint32_t> &ooff) {
-            for (int32_t e = 0; e < E; ++e) {
-                uint32_t d = ooff[(size_t)e + 1] - ooff[e];
-                if (d > 0) g->n_out_rows++;
-                if (d >= (uint32_t)g->hub_min) g->n_out_hubs++;
-            }
+        auto subject_row_counts = [&]() -> logoskg_status {
+            unsigned int n[3];
+            LKG_TRY(count_rows_on_device(g->out_off, E, g->hub_min, n));
+            g->n_out_rows = n[0];
+            g->n_out_hubs = n[2];
+            return LOGOSKG_OK;
         };
         if (device_build) {
-            std::vector<uint32_t> ooff, ioff;
-            if ((st = build_csr_on_device(g, subj, rel, obj, &ooff, &ioff)) != LOGOSKG_OK) return fail(st);
+            if ((st = build_csr_on_device(g, subj, rel, obj)) != LOGOSKG_OK) return fail(st);
             g->row_begin = g->out_off;
-            subject_row_counts(ooff);
-            if ((st = object_row_classes(ioff)) != LOGOSKG_OK) return fail(st);
+            if ((st = subject_row_counts()) != LOGOSKG_OK) return fail(st);
+            if ((st = object_rows()) != LOGOSKG_OK) return fail(st);
         } else if (device_sorts) {
             // a sharded graph whose two sorts run on the device; the sorted arrays go to pinned host memory
             TripleSorter *sorter = nullptr;
@@ -361,16 +357,16 @@ extern "C" logoskg_status logoskg_build(const int32_t *subj, const int32_t *rel,
             std::unique_ptr<TripleSorter, void (*)(TripleSorter *)> guard(sorter, sorter_destroy);
             std::vector<uint32_t> ooff;
             if ((st = sorter_offsets(sorter, false, &ooff)) != LOGOSKG_OK) return fail(st);
-            subject_row_counts(ooff);
             if ((st = upload(&g->out_off, ooff, &g->static_bytes)) != LOGOSKG_OK) return fail(st);
+            if ((st = subject_row_counts()) != LOGOSKG_OK) return fail(st);
             if ((st = build_shards(g, subj, rel, obj, &o, ooff, sorter)) != LOGOSKG_OK) return fail(st);
         } else {
         // out-degrees are needed by both the resident and the sharded form
         std::vector<uint32_t> ooff((size_t)E + 1, 0);
         for (int64_t t = 0; t < T; ++t) ooff[(size_t)subj[t] + 1]++;
         for (int32_t e = 0; e < E; ++e) ooff[(size_t)e + 1] += ooff[e];
-        subject_row_counts(ooff);
         if ((st = upload(&g->out_off, ooff, &g->static_bytes)) != LOGOSKG_OK) return fail(st);
+        if ((st = subject_row_counts()) != LOGOSKG_OK) return fail(st);
 
         if (g->num_shards > 1) {
             if ((st = build_shards(g, subj, rel, obj, &o, ooff, nullptr)) != LOGOSKG_OK) return fail(st);
@@ -405,7 +401,7 @@ extern "C" logoskg_status logoskg_build(const int32_t *subj, const int32_t *rel,
                 if ((st = upload(&g->in_sub, isub, &g->static_bytes)) != LOGOSKG_OK) return fail(st);
                 if ((st = upload(&g->in_rel, irel, &g->static_bytes)) != LOGOSKG_OK) return fail(st);
                 if ((st = upload(&g->in_eid, ieid, &g->static_bytes)) != LOGOSKG_OK) return fail(st);
-                if ((st = object_row_classes(ioff)) != LOGOSKG_OK) return fail(st);
+                if ((st = object_rows()) != LOGOSKG_OK) return fail(st);
             }
         }
         }
@@ -474,6 +470,7 @@ extern "C" void logoskg_graph_free(logoskg_graph *g) {
                     g->fr_seg, g->d_ctr, g->long_index, g->row_pred, g->out_eid, g->plane_buf};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
+    drop_pairs(g);
     if (g->h_ctr) (void)hipHostFree(g->h_ctr);
     g->pool.trim();
     delete g;

@@ -102,10 +102,8 @@ logoskg_status sort_by(const int32_t *d_key, int64_t T, int32_t E, unsigned key_
 
 }  // namespace
 
-// Fills g->out_off/out_obj/out_rel/out_eid and g->in_off/in_sub/in_rel/in_eid from host triple arrays;
-// returns the two offset arrays to the host as well (row classes are built there).
-logoskg_status build_csr_on_device(logoskg_graph *g, const int32_t *subj, const int32_t *rel, const int32_t *obj,
-                                   std::vector<uint32_t> *ooff, std::vector<uint32_t> *ioff) {
+// Fills g->out_off/out_obj/out_rel/out_eid and g->in_off/in_sub/in_rel/in_eid from host triple arrays.
+logoskg_status build_csr_on_device(logoskg_graph *g, const int32_t *subj, const int32_t *rel, const int32_t *obj) {
     const int64_t T = g->T;
     const int32_t E = g->E;
     Scratch tmp;
@@ -172,10 +170,225 @@ logoskg_status build_csr_on_device(logoskg_graph *g, const int32_t *subj, const 
     if (T > 0)
         k_gather_obj_rows<<<dim3(grid_for(T)), dim3(kBlock)>>>(d_in_eid, T, d_subj, d_rel, g->in_sub, g->in_rel, nullptr);
     LKG_HIP(hipGetLastError());
-    ooff->resize((size_t)E + 1);
-    ioff->resize((size_t)E + 1);
-    LKG_HIP(hipMemcpy(ooff->data(), g->out_off, ((size_t)E + 1) * 4, hipMemcpyDeviceToHost));
-    LKG_HIP(hipMemcpy(ioff->data(), g->in_off, ((size_t)E + 1) * 4, hipMemcpyDeviceToHost));
+    LKG_HIP(hipDeviceSynchronize());
+    return LOGOSKG_OK;
+}
+
+// ---------------------------------------------------------------- distinct pairs
+// One stable radix sort of (object, rank of the subject by in-degree) keys with the positions of OBJ as values: equal
+// keys are parallel triples, the first of them has the smallest triple index, and the keys' order is pull_sub's.  A row
+// keeps its extent in the sorted order, so prefix sums over the first ones of each run give the rows of both orders.
+__global__ void k_row_starts(const uint32_t *__restrict__ off, int32_t E, uint32_t *obj_of) {
+    const int32_t e = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (e < E && off[e + 1] > off[e]) obj_of[off[e]] = (uint32_t)e;
+}
+
+__global__ void k_in_degrees(const uint32_t *__restrict__ off, int32_t E, uint32_t *deg) {
+    const int32_t e = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (e < E) deg[e] = off[e + 1] - off[e];
+}
+
+__global__ void k_rank_of(const uint32_t *__restrict__ by_rank, int32_t E, uint32_t *rank_of) {
+    const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (i < E) rank_of[by_rank[i]] = (uint32_t)i;
+}
+
+__global__ void k_pair_keys(const uint32_t *__restrict__ obj_of, const int32_t *__restrict__ in_sub,
+                            const uint32_t *__restrict__ rank_of, long long T, unsigned bits, unsigned long long *key, uint32_t *pos) {
+    const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= T) return;
+    key[p] = ((unsigned long long)obj_of[p] << bits) | rank_of[in_sub[p]];
+    pos[p] = (uint32_t)p;
+}
+
+// is_new[i]: the i-th key differs from the one before; is_first[p]: position p of OBJ holds the first triple of its pair
+__global__ void k_pair_flags(const unsigned long long *__restrict__ key, const uint32_t *__restrict__ pos, long long T,
+                             uint32_t *is_new, uint32_t *is_first) {
+    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= T) return;
+    const uint32_t n = i == 0 || key[i] != key[i - 1];
+    is_new[i] = n;
+    is_first[pos[i]] = n;
+}
+
+// (the flags have become inclusive prefix sums)
+__global__ void k_pair_rows(const uint32_t *__restrict__ off, int32_t E, const uint32_t *__restrict__ new_upto, uint32_t *pair_off) {
+    const int32_t e = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (e <= E) pair_off[e] = off[e] ? new_upto[off[e] - 1] : 0u;
+}
+
+__global__ void k_pair_fill(const unsigned long long *__restrict__ key, const uint32_t *__restrict__ new_upto,
+                            const uint32_t *__restrict__ first_upto, long long T, unsigned bits,
+                            const uint32_t *__restrict__ by_rank, const int32_t *__restrict__ in_sub,
+                            const int32_t *__restrict__ in_eid, int32_t *pull_sub, int32_t *sub, int32_t *eid) {
+    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= T) return;
+    const uint32_t n = new_upto[i], f = first_upto[i];
+    if (n != (i ? new_upto[i - 1] : 0u)) pull_sub[n - 1] = (int32_t)by_rank[key[i] & ((1ull << bits) - 1ull)];
+    if (f != (i ? first_upto[i - 1] : 0u)) {
+        sub[f - 1] = in_sub[i];
+        eid[f - 1] = in_eid[i];
+    }
+}
+
+logoskg_status build_pairs_on_device(logoskg_graph *g) {
+    const int64_t T = g->T;
+    const int32_t E = g->E;
+    if (T == 0) return LOGOSKG_OK;
+    unsigned bits = 1;
+    while (bits < 32 && (1ull << bits) < (unsigned long long)E) ++bits;
+    rocprim::double_buffer<unsigned long long> keys(nullptr, nullptr);
+    rocprim::double_buffer<uint32_t> vals(nullptr, nullptr), degrees(nullptr, nullptr), ids(nullptr, nullptr);
+    size_t bytes[3] = {};
+    LKG_HIP(rocprim::radix_sort_pairs(nullptr, bytes[0], keys, vals, (size_t)T, 0u, 2 * bits));
+    LKG_HIP(rocprim::radix_sort_pairs_desc(nullptr, bytes[1], degrees, ids, (size_t)E, 0u, 32u));
+    LKG_HIP(rocprim::inclusive_scan(nullptr, bytes[2], (uint32_t *)nullptr, (uint32_t *)nullptr, (size_t)T, rocprim::plus<uint32_t>()));
+    // one block: keys and positions twice, ranks and ids twice, the sorts' own
+    Scratch tmp;
+    char *at = nullptr;
+    const size_t sort_bytes = std::max({bytes[0], bytes[1], bytes[2]});
+    if (tmp.get(&at, ((size_t)T * 24 + (size_t)E * 16 + 256 * 9) + sort_bytes) != LOGOSKG_OK) {
+        (void)hipGetLastError();  // (without them the graph works as well)
+        return LOGOSKG_OK;
+    }
+    auto take = [&](auto **p, size_t n) {
+        *p = reinterpret_cast<std::remove_reference_t<decltype(*p)>>(at);
+        at += (n * sizeof(**p) + 255) / 256 * 256;
+    };
+    unsigned long long *key[2];
+    uint32_t *pos[2], *rank[4];
+    for (auto &p : key) take(&p, (size_t)T);
+    for (auto &p : pos) take(&p, (size_t)T);
+    for (auto &p : rank) take(&p, (size_t)E);
+    char *const d_tmp = at;
+    keys = rocprim::double_buffer<unsigned long long>(key[0], key[1]);
+    vals = rocprim::double_buffer<uint32_t>(pos[0], pos[1]);
+    degrees = rocprim::double_buffer<uint32_t>(rank[0], rank[1]);
+    ids = rocprim::double_buffer<uint32_t>(rank[2], rank[3]);
+
+    const dim3 block(kBlock), per_triple(grid_for(T)), per_entity(grid_for((int64_t)E + 1));
+    uint32_t *const obj_of = pos[1];
+    LKG_HIP(hipMemsetAsync(obj_of, 0, (size_t)T * 4, nullptr));
+    k_row_starts<<<per_entity, block>>>(g->in_off, E, obj_of);
+    LKG_HIP(rocprim::inclusive_scan(d_tmp, bytes[2], obj_of, obj_of, (size_t)T, rocprim::maximum<uint32_t>()));
+    k_in_degrees<<<per_entity, block>>>(g->in_off, E, degrees.current());
+    k_iota<<<per_entity, block>>>(ids.current(), E);
+    LKG_HIP(rocprim::radix_sort_pairs_desc(d_tmp, bytes[1], degrees, ids, (size_t)E, 0u, 32u));
+    const uint32_t *const by_rank = ids.current();
+    k_rank_of<<<per_entity, block>>>(by_rank, E, degrees.current());
+    k_pair_keys<<<per_triple, block>>>(obj_of, g->in_sub, degrees.current(), T, bits, key[0], pos[0]);
+    LKG_HIP(rocprim::radix_sort_pairs(d_tmp, bytes[0], keys, vals, (size_t)T, 0u, 2 * bits));
+    uint32_t *const is_new = reinterpret_cast<uint32_t *>(keys.alternate()), *const is_first = is_new + T;
+    k_pair_flags<<<per_triple, block>>>(keys.current(), vals.current(), T, is_new, is_first);
+    LKG_HIP(rocprim::inclusive_scan(d_tmp, bytes[2], is_new, is_new, (size_t)T, rocprim::plus<uint32_t>()));
+    LKG_HIP(rocprim::inclusive_scan(d_tmp, bytes[2], is_first, is_first, (size_t)T, rocprim::plus<uint32_t>()));
+    LKG_HIP(hipGetLastError());
+    uint32_t n = 0;
+    LKG_HIP(hipMemcpy(&n, is_new + T - 1, sizeof(n), hipMemcpyDeviceToHost));
+    if ((int64_t)n * 100 > T * kPairShare) return LOGOSKG_OK;
+
+    PairRows p;
+    bool room = true;
+    auto keep = [&](auto **out, size_t count) {
+        if (room && hipMalloc((void **)out, count * 4) != hipSuccess) {
+            (void)hipGetLastError();
+            *out = nullptr;
+            room = false;
+        }
+    };
+    keep(&p.pull_sub, n);
+    keep(&p.sub, n);
+    keep(&p.eid, n);
+    keep(&p.off, (size_t)E + 1);
+    if (!room) {
+        for (void *x : {(void *)p.pull_sub, (void *)p.sub, (void *)p.eid})
+            if (x) (void)hipFree(x);
+        return LOGOSKG_OK;
+    }
+    g->pairs = p;
+    g->static_bytes += (3 * (size_t)n + (size_t)E + 1) * 4;
+    k_pair_rows<<<per_entity, block>>>(g->in_off, E, is_new, p.off);
+    k_pair_fill<<<per_triple, block>>>(keys.current(), is_new, is_first, T, bits, by_rank, g->in_sub, g->in_eid, p.pull_sub,
+                                       p.sub, p.eid);
+    LKG_HIP(hipGetLastError());
+    LKG_HIP(hipDeviceSynchronize());  // (the scratch goes)
+    return LOGOSKG_OK;
+}
+
+// ---------------------------------------------------------------- row classes
+// counts[0 .. 2] += rows with an entry, of more than kTailMaxDegree, of at least hub_min
+__global__ void __launch_bounds__(kBlock) k_row_counts(const uint32_t *__restrict__ off, int32_t E, uint32_t hub_min, unsigned int *counts) {
+    unsigned n[3] = {};
+    for (long long e = (long long)blockIdx.x * kBlock + threadIdx.x; e < E; e += (long long)gridDim.x * kBlock) {
+        const uint32_t d = off[e + 1] - off[e];
+        n[0] += d > 0;
+        n[1] += d > (uint32_t)kTailMaxDegree;
+        n[2] += d >= hub_min;
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const unsigned x = (unsigned)wave_sum(n[i]);
+        if (lane() == 0 && x) atomicAdd(&counts[i], x);
+    }
+}
+
+logoskg_status count_rows_on_device(const uint32_t *d_off, int32_t E, int hub_min, unsigned int (&n)[3]) {
+    Scratch tmp;
+    unsigned int *d_n = nullptr;
+    LKG_TRY(tmp.get(&d_n, 3));
+    LKG_HIP(hipMemsetAsync(d_n, 0, sizeof(n), nullptr));
+    k_row_counts<<<dim3(std::min(1024u, grid_for(E))), dim3(kBlock)>>>(d_off, E, (uint32_t)hub_min, d_n);
+    LKG_HIP(hipMemcpy(n, d_n, sizeof(n), hipMemcpyDeviceToHost));
+    return LOGOSKG_OK;
+}
+
+// short rows by descending length, then the longer ones, then the empty ones
+__global__ void k_row_class(const uint32_t *__restrict__ off, int32_t E, uint8_t *key, int32_t *id) {
+    const long long e = (long long)blockIdx.x * kBlock + threadIdx.x;
+    if (e >= E) return;
+    const uint32_t d = off[e + 1] - off[e];
+    key[e] = d == 0 ? kTailMaxDegree + 1 : d > (uint32_t)kTailMaxDegree ? kTailMaxDegree : kTailMaxDegree - d;
+    id[e] = (int32_t)e;
+}
+
+__global__ void k_row_records(const int32_t *__restrict__ id, long long n, const uint32_t *__restrict__ off, ShortRow *out) {
+    const long long i = (long long)blockIdx.x * kBlock + threadIdx.x;
+    if (i < n) out[i] = ShortRow{id[i], off[id[i]], off[id[i] + 1]};
+}
+
+// rc->tail and rc->n_tail / n_hub of the rows behind d_off; the longer rows, ascending, to the host.  (A stable sort of one
+// digit.  On the host, with the offsets copied back, 20M rows were a quarter of a second.)
+logoskg_status classify_on_device(const uint32_t *d_off, int32_t E, int hub_min, RowClasses *rc, std::vector<ShortRow> *longer, size_t *acct) {
+    unsigned int n[3];
+    LKG_TRY(count_rows_on_device(d_off, E, hub_min, n));
+    rc->n_tail = (int64_t)n[0] - n[1];
+    rc->n_hub = n[2];
+    longer->resize(n[1]);
+    const size_t tail_bytes = std::max<size_t>((size_t)rc->n_tail, 1) * sizeof(ShortRow);
+    LKG_HIP(hipMalloc((void **)&rc->tail, tail_bytes));
+    *acct += tail_bytes;
+    if (n[0] == 0) return LOGOSKG_OK;
+    Scratch tmp;
+    uint8_t *key[2] = {};
+    int32_t *id[2] = {};
+    for (auto &p : key) LKG_TRY(tmp.get(&p, (size_t)E));
+    for (auto &p : id) LKG_TRY(tmp.get(&p, (size_t)E));
+    rocprim::double_buffer<uint8_t> keys(key[0], key[1]);
+    rocprim::double_buffer<int32_t> ids(id[0], id[1]);
+    size_t bytes = 0;
+    LKG_HIP(rocprim::radix_sort_pairs(nullptr, bytes, keys, ids, (size_t)E, 0u, 6u));
+    char *d_tmp = nullptr;
+    LKG_TRY(tmp.get(&d_tmp, bytes));
+    k_row_class<<<dim3(grid_for(E)), dim3(kBlock)>>>(d_off, E, key[0], id[0]);
+    LKG_HIP(rocprim::radix_sort_pairs(d_tmp, bytes, keys, ids, (size_t)E, 0u, 6u));
+    if (rc->n_tail) k_row_records<<<dim3(grid_for(rc->n_tail)), dim3(kBlock)>>>(ids.current(), rc->n_tail, d_off, rc->tail);
+    if (n[1]) {
+        ShortRow *d_long = nullptr;
+        LKG_TRY(tmp.get(&d_long, n[1]));
+        k_row_records<<<dim3(grid_for(n[1])), dim3(kBlock)>>>(ids.current() + rc->n_tail, n[1], d_off, d_long);
+        LKG_HIP(hipMemcpy(longer->data(), d_long, (size_t)n[1] * sizeof(ShortRow), hipMemcpyDeviceToHost));
+    }
+    LKG_HIP(hipGetLastError());
     LKG_HIP(hipDeviceSynchronize());
     return LOGOSKG_OK;
 }

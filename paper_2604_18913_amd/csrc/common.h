@@ -155,6 +155,20 @@ struct RowClasses {             // device work lists over the object rows, split
     int64_t n_hub_segs = 0, n_split = 0, n_split_segs = 0;  // all; rows of several segments (the first ones), and theirs
 };
 
+// OBJ without its parallel triples: the rows' distinct subjects, for calls without whitelists, where a triple that repeats
+// another's subject and object in a larger index adds nothing to a level and is never a predecessor.  Two orders of the
+// same rows (off): `sub` / `eid` by triple index, for the predecessor pass; `pull_sub` by the in-degree of the subject,
+// largest first, for pulled hops, which may take a row in any order and stop when nothing is missing: the subjects that
+// most queries have reached come first.  Built where at most kPairShare percent of the triples are left and there is
+// room; off is NULL otherwise.  (Distinct pairs of 30M triples of concepts 65 %, 3.4M 52 %, 300M hub-heavy ones 85 %.)
+constexpr int kPairShare = 90;
+struct PairRows {
+    uint32_t *off = nullptr;
+    int32_t *pull_sub = nullptr, *sub = nullptr, *eid = nullptr;
+    RowClasses rows;  // (segments by their place in the row: the first ones of all rows, the second ones, ..)
+    int32_t *long_index = nullptr;  // as logoskg_graph::long_index
+};
+
 // ---------------------------------------------------------------- profiling
 enum KernelKind {
     KK_CLEAR = 0, KK_SEED, KK_CENSUS, KK_LIVE, KK_PUSH_TAIL, KK_PUSH_SEG, KK_UPDATE, KK_PULL_TAIL,
@@ -221,6 +235,7 @@ struct logoskg_graph {
     int32_t *out_eid = nullptr;  // [T] triple index of every entry of the subject-sorted CSR: what the
                                  // device build sorts by; else built on first use (ensure_out_eid)
     lkg::RowClasses in_rows;     // static row lists for the pull kernels
+    lkg::PairRows pairs;         // the same rows without the parallel triples
     int64_t n_out_rows = 0, n_out_hubs = 0;
 
     // frontier work lists rebuilt every hop from the level's active bitmap
@@ -466,8 +481,12 @@ struct FillArgs {
     int32_t *seg_pred;  // [n_split_segs][64 W]
 };
 
-logoskg_status build_csr_on_device(logoskg_graph *g, const int32_t *subj, const int32_t *rel, const int32_t *obj,
-                                   std::vector<uint32_t> *ooff, std::vector<uint32_t> *ioff);
+logoskg_status build_csr_on_device(logoskg_graph *g, const int32_t *subj, const int32_t *rel, const int32_t *obj);
+// rows of a CSR on the device: with an entry, of more than kTailMaxDegree, of at least hub_min
+logoskg_status count_rows_on_device(const uint32_t *d_off, int32_t E, int hub_min, unsigned int (&n)[3]);
+logoskg_status classify_on_device(const uint32_t *d_off, int32_t E, int hub_min, RowClasses *rc, std::vector<ShortRow> *longer, size_t *acct);
+// g->pairs' arrays (not its work lists) from the object-sorted ones; pairs.off stays NULL where they are not kept
+logoskg_status build_pairs_on_device(logoskg_graph *g);
 struct TripleSorter;  // the triple list on the device during a sharded build (build_device.hip)
 logoskg_status sorter_create(logoskg_graph *g, const int32_t *subj, const int32_t *rel, const int32_t *obj,
                              TripleSorter **out);
@@ -482,8 +501,7 @@ logoskg_status small_search(logoskg_graph *g, logoskg_result *r, const logoskg_q
 logoskg_status small_fetch(logoskg_result *r, int q0, int q1, int32_t *entity, uint8_t *hop, int32_t *pred,
                            hipStream_t st);
 // the hub rows' segments: `table` with theirs behind it (rows longest first), and their counts; into the arguments of a fetch
-std::vector<uint32_t> append_hub_segments(std::vector<uint32_t> table, const std::vector<int32_t> &longer,
-                                          const std::vector<uint32_t> &off, RowClasses *rows);
+std::vector<uint32_t> append_hub_segments(std::vector<uint32_t> table, const std::vector<ShortRow> &longer, RowClasses *rows);
 void set_hub_segments(FillArgs *a, const RowClasses &rows);
 void drop_walk_tables(logoskg_result *r);
 void launch_lists(Profiler &prof, const FillArgs &a, int W, hipStream_t st);

@@ -937,7 +937,9 @@ k_pull_seg(const PullSegment *__restrict__ segs, long long n,
             e0 = e1;
             c0 = c1;
             e1 = e2;
-            if ((it & 3) == 3) {  // early exit is rare: test it every fourth chunk
+            // Early exit: behind the first two chunks, which of a row in pull_sub's order hold what most queries have
+            // reached, then rarely: every fourth.
+            if ((it & 3) == 3 || (!MASK && it < 2)) {
                 acc = fold_gathered<W>(a0, a1);
                 if (multi) acc |= __atomic_load_n(&cur[(size_t)v * W + lw], __ATOMIC_RELAXED);
                 if (!wave_any((need & ~acc) != 0)) break;
@@ -1312,11 +1314,16 @@ void launch_pull_range(logoskg_graph *g, logoskg_result *r, int h, const RowClas
     }
 }
 
+// A pulled hop without whitelists takes the distinct pairs.
+static bool pulls_pairs(const logoskg_graph *g, const logoskg_result *r) { return !r->has_mask && g->pairs.off; }
+static const RowClasses &pull_lists(const logoskg_graph *g, const logoskg_result *r) { return pulls_pairs(g, r) ? g->pairs.rows : g->in_rows; }
+static const int32_t *pull_subjects(const logoskg_graph *g, const logoskg_result *r) { return pulls_pairs(g, r) ? g->pairs.pull_sub : g->in_sub; }
+
 template <int W>
 static void run_hop(logoskg_graph *g, logoskg_result *r, int h, bool pull, bool want_stats,
                     const unsigned long long *hc, hipStream_t st) {
     if (pull) {
-        launch_pull_range(g, r, h, g->in_rows, g->in_sub, g->in_rel, hc, want_stats, true, st);
+        launch_pull_range(g, r, h, pull_lists(g, r), pull_subjects(g, r), g->in_rel, hc, want_stats, true, st);
     } else {
         if (r->has_mask) launch_push<W, true>(g, r, h, hc, g->out_obj, g->out_rel, true, g->fr_tail, g->fr_seg, level_counters(r, h - 1), st);
         else launch_push<W, false>(g, r, h, hc, g->out_obj, g->out_rel, true, g->fr_tail, g->fr_seg, level_counters(r, h - 1), st);
@@ -1356,8 +1363,8 @@ void launch_resident_hop(logoskg_graph *g, logoskg_result *r, int h, bool pull, 
 
 // A pulled hop of a resident graph on narrow planes, for the case that *go says so.
 static void launch_pull_ahead(logoskg_graph *g, logoskg_result *r, int h, const unsigned long long *go, hipStream_t st) {
-    if (r->W == 1) pull_rows_w<1>(g, r, h, g->in_rows, g->in_sub, g->in_rel, false, false, st, go);
-    else pull_rows_w<4>(g, r, h, g->in_rows, g->in_sub, g->in_rel, false, false, st, go);
+    if (r->W == 1) pull_rows_w<1>(g, r, h, pull_lists(g, r), pull_subjects(g, r), g->in_rel, false, false, st, go);
+    else pull_rows_w<4>(g, r, h, pull_lists(g, r), pull_subjects(g, r), g->in_rel, false, false, st, go);
 }
 
 __global__ void k_clear_cursors(unsigned long long *ctr) { ctr[threadIdx.x] = 0ull; }

@@ -2262,6 +2262,16 @@ logoskg_status prepare_row_pred(logoskg_graph *g, hipStream_t st) {
     LKG_HIP(hipMemsetAsync(g->long_index, 0xFF, (size_t)g->E * sizeof(int32_t), st));  // -1: not a long row
     k_long_index<<<dim3((unsigned)((g->in_rows.n_long + 255) / 256)), dim3(256), 0, st>>>(
         joined ? joined->longrows : g->in_rows.longrows, g->in_rows.n_long, g->long_index);
+    if (g->pairs.off) {  // (no more rows than in_rows has; without room for it a fetch goes by all triples)
+        if (hipMalloc((void **)&g->pairs.long_index, (size_t)g->E * sizeof(int32_t)) == hipSuccess) {
+            LKG_HIP(hipMemsetAsync(g->pairs.long_index, 0xFF, (size_t)g->E * sizeof(int32_t), st));
+            const long long n = (long long)g->pairs.rows.n_long;
+            if (n > 0) k_long_index<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st>>>(g->pairs.rows.longrows, n, g->pairs.long_index);
+        } else {
+            (void)hipGetLastError();
+            g->pairs.long_index = nullptr;
+        }
+    }
     LKG_HIP(hipGetLastError());
     return LOGOSKG_OK;
 }
@@ -2699,23 +2709,29 @@ extern "C" logoskg_status logoskg_result_fetch(logoskg_result *r, int32_t q0, in
     a.plv = a.levels; a.pplane = a.plane; a.pstride = W; a.pfirst = 0;
     a.act = r->act; a.tile_base = r->tile_base; a.super_base = r->super_base; a.mega_base = r->mega_base;
     a.reached_off = r->d_reached_off;
-    a.in_off = g->in_off; a.in_sub = g->in_sub; a.in_eid = g->in_eid; a.in_rel = g->in_rel;
-    a.rows = g->in_rows.longrows;
+    if (pred && W == 16) LKG_TRY(prepare_row_pred(g, st));
+    // without whitelists the rows of distinct pairs (where the row buffer is used they need their own index)
+    const bool pairs = !r->has_mask && g->pairs.off && !(pred && W == 16 && g->row_pred && !g->pairs.long_index);
+    const RowClasses &in_rows = pairs ? g->pairs.rows : g->in_rows;
+    a.in_off = pairs ? g->pairs.off : g->in_off;
+    a.in_sub = pairs ? g->pairs.sub : g->in_sub;
+    a.in_eid = pairs ? g->pairs.eid : g->in_eid;
+    a.in_rel = g->in_rel;
+    a.rows = in_rows.longrows;
     a.row_base = 0; a.long_index = nullptr; a.row_pred = nullptr; a.fuse_lists = 0;
     a.plane_buf = nullptr; a.plane_buf_bytes = 0; a.ev_rows = nullptr;
     // levels whose frontier (the level below) holds most of the triples: the same rule as the pull hops
     for (int h = 1; h <= r->k && h < 32; ++h)
         if ((long long)r->stats[(size_t)h - 1].frontier_edges * 100 >= g->T * (long long)kDensePullPercent)
             a.dense_levels |= 1u << h;
-    a.n_giant_rows = g->in_rows.n_giant;  // (a sharded graph: set per object range)
-    a.giant_seg_first = g->in_rows.giant_seg_first;
-    a.n_giant_segs = g->in_rows.n_giant_segs;
-    if (g->num_shards <= 1) set_hub_segments(&a, g->in_rows);
+    a.n_giant_rows = in_rows.n_giant;  // (a sharded graph: set per object range)
+    a.giant_seg_first = in_rows.giant_seg_first;
+    a.n_giant_segs = in_rows.n_giant_segs;
+    if (g->num_shards <= 1) set_hub_segments(&a, in_rows);
     a.host_graph = g;
     a.host_result = r;
     if (pred && W == 16) {
-        LKG_TRY(prepare_row_pred(g, st));
-        a.long_index = g->long_index;
+        a.long_index = pairs ? g->pairs.long_index : g->long_index;
         a.row_pred = g->row_pred;
         a.plane_buf = g->plane_buf;
         a.plane_buf_bytes = g->plane_buf_bytes;
@@ -2766,7 +2782,7 @@ extern "C" logoskg_status logoskg_result_fetch(logoskg_result *r, int32_t q0, in
     // With predecessors the tile kernel writes all three lists, except on 16-word planes without the
     // bit-sliced pass, where the list kernel runs beside the predecessor kernels.
     a.fuse_lists = pred && (W <= 4 || pred_uses_staged_kernel(a, W));
-    const long long n_hub = g->in_rows.n_hub, n_mid = g->in_rows.n_long - g->in_rows.n_hub;
+    const long long n_hub = in_rows.n_hub, n_mid = in_rows.n_long - in_rows.n_hub;
     // (nothing to fork for when the fused tile pass has no hub rows beside it)
     if (pred && g->num_shards <= 1 && !serial && (n_hub > 0 || !a.fuse_lists)) {
         LKG_HIP(hipEventRecord(g->ev_fork, st));

@@ -398,7 +398,7 @@ static logoskg_status build_in_chunks(logoskg_graph *g, ShardSet *ss, const int3
         ss->all_rows.n_seg = g->in_rows.n_seg;
         ss->all_rows.n_multi = g->in_rows.n_multi;
     }
-    {   // segments of every chunk's giant rows, for the predecessor pass (as object_row_classes does for a resident graph)
+    {   // segments of every chunk's giant rows, for the predecessor pass (as row_classes does for a resident graph)
         std::vector<uint32_t> first;
         const uint32_t giant_min = (uint32_t)std::max(kGiantRowMin, g->hub_min);
         for (ShardSet::Chunk &c : ss->chunks) {
@@ -439,7 +439,9 @@ static logoskg_status build_in_chunks(logoskg_graph *g, ShardSet *ss, const int3
         ss->all_rows.n_hub = g->in_rows.n_hub;
         ss->all_rows.n_giant = (int64_t)first.size() - 1;
         ss->all_rows.n_giant_segs = first.back();
-        first = append_hub_segments(std::move(first), longrows, ioff, &ss->all_rows);
+        std::vector<ShortRow> records;
+        for (int32_t v : longrows) records.push_back({v, ioff[(size_t)v], ioff[(size_t)v + 1]});
+        first = append_hub_segments(std::move(first), records, &ss->all_rows);
         LKG_HIP(hipMalloc((void **)&ss->sorted_longrows, std::max<size_t>(longrows.size(), 1) * sizeof(int32_t)));
         LKG_HIP(hipMalloc((void **)&ss->sorted_giant_first, first.size() * sizeof(uint32_t)));
         if (!longrows.empty())
