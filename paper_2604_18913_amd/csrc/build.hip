@@ -201,14 +201,28 @@ static logoskg_status upload(T **dst, const std::vector<T> &src, size_t *acct) {
     return LOGOSKG_OK;
 }
 
-std::vector<uint32_t> append_hub_segments(std::vector<uint32_t> table, const std::vector<ShortRow> &longer, RowClasses *rows) {
-    rows->n_split = 0;
-    rows->n_split_segs = 0;
+std::vector<uint32_t> segment_tables(const std::vector<ShortRow> &longer, uint32_t giant_min, RowClasses *rows) {
+    std::vector<uint32_t> table(1, 0);
+    auto count = [&](int64_t i, int segment) { return (longer[(size_t)i].end - longer[(size_t)i].begin + (uint32_t)segment - 1) / (uint32_t)segment; };
+    rows->n_giant = 0;
+    for (const ShortRow &r : longer) {
+        if (r.end - r.begin < giant_min) break;
+        table.push_back(table.back() + count(rows->n_giant++, kGiantSegment));
+    }
+    rows->n_giant_segs = table.back();
+    rows->n_giant_places = rows->n_giant ? count(0, kGiantSegment) : 0;
     uint32_t first = 0;
     table.push_back(first);
+    int64_t in = rows->n_giant;  // rows that reach a place
+    for (int64_t place = 0; place < rows->n_giant_places; ++place) {
+        while (count(in - 1, kGiantSegment) <= place) --in;
+        table.push_back(first += (uint32_t)in);
+    }
+    rows->n_split = 0;
+    rows->n_split_segs = 0;
+    table.push_back(first = 0);
     for (int64_t i = 0; i < rows->n_hub; ++i) {
-        const ShortRow &r = longer[(size_t)i];
-        const uint32_t n = (r.end - r.begin + kHubSegment - 1) / kHubSegment;
+        const uint32_t n = count(i, kHubSegment);
         table.push_back(first += n);
         if (n > 1) {
             ++rows->n_split;
@@ -217,6 +231,12 @@ std::vector<uint32_t> append_hub_segments(std::vector<uint32_t> table, const std
     }
     rows->n_hub_segs = first;
     return table;
+}
+
+void set_segment_tables(RowClasses *rows, uint32_t *table) {
+    rows->giant_seg_first = table;
+    rows->giant_place_first = table + rows->n_giant + 1;
+    rows->hub_seg_first = rows->giant_place_first + rows->n_giant_places + 1;
 }
 
 static void drop_pairs(logoskg_graph *g) {
@@ -235,14 +255,11 @@ static logoskg_status row_classes(logoskg_graph *g, const uint32_t *d_off, bool 
     std::stable_sort(longer.begin(), longer.end(), [](const ShortRow &a, const ShortRow &b) { return a.end - a.begin > b.end - b.begin; });
     std::vector<int32_t> rows, multi;
     std::vector<PullSegment> seg;
-    std::vector<uint32_t> first(1, 0);  // segments of the giant rows, for the predecessor pass
-    const uint32_t giant_min = (uint32_t)std::max(kGiantRowMin, g->hub_min);
     rows.reserve(longer.size());
     for (const ShortRow &r : longer) {
         const uint32_t d = r.end - r.begin;
         rows.push_back(r.row);
         if (d > (uint32_t)kPullSegment) multi.push_back(r.row);
-        if (d >= giant_min) first.push_back(first.back() + (d + kGiantSegment - 1) / kGiantSegment);
         for (uint32_t j = r.begin; j < r.end && (!by_place || j == r.begin); j += kPullSegment)
             seg.push_back({r.row, j, std::min(j + (uint32_t)kPullSegment, r.end), d > (uint32_t)kPullSegment ? 1u : 0u});
     }
@@ -251,14 +268,13 @@ static logoskg_status row_classes(logoskg_graph *g, const uint32_t *d_off, bool 
             if (r.end - r.begin <= place) break;
             seg.push_back({r.row, r.begin + place, std::min(r.begin + place + (uint32_t)kPullSegment, r.end), 1u});
         }
-    rc->n_giant = (int64_t)first.size() - 1;
-    rc->n_giant_segs = first.back();
     rc->n_seg = (int64_t)seg.size();
     rc->n_multi = (int64_t)multi.size();
     rc->n_long = (int64_t)longer.size();
     if (!longer.empty()) rc->longest = longer[0].end - longer[0].begin;
-    LKG_TRY(upload(&rc->giant_seg_first, append_hub_segments(std::move(first), longer, rc), &g->static_bytes));
-    rc->hub_seg_first = rc->giant_seg_first + rc->n_giant + 1;
+    uint32_t *table = nullptr;
+    LKG_TRY(upload(&table, segment_tables(longer, (uint32_t)std::max(kGiantRowMin, g->hub_min), rc), &g->static_bytes));
+    set_segment_tables(rc, table);
     LKG_TRY(upload(&rc->seg, seg, &g->static_bytes));
     LKG_TRY(upload(&rc->multi, multi, &g->static_bytes));
     LKG_TRY(upload(&rc->longrows, rows, &g->static_bytes));

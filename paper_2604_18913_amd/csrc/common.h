@@ -151,6 +151,9 @@ struct RowClasses {             // device work lists over the object rows, split
     int64_t n_giant = 0;  // the first n_giant long rows have >= kGiantRowMin entries
     uint32_t *giant_seg_first = nullptr;  // [n_giant + 1] segments of kGiantSegment entries before every giant row
     int64_t n_giant_segs = 0;
+    // (behind it) [n_giant_places + 1] the same segments by their place in the row, first ones first: before every place
+    uint32_t *giant_place_first = nullptr;
+    int64_t n_giant_places = 0;  // segments of the longest row
     uint32_t *hub_seg_first = nullptr;  // (behind it) [n_hub + 1] segments of kHubSegment entries before every hub row
     int64_t n_hub_segs = 0, n_split = 0, n_split_segs = 0;  // all; rows of several segments (the first ones), and theirs
 };
@@ -475,6 +478,8 @@ struct FillArgs {
     long long n_giant_rows;  // hub rows of the launch that get a 16-wave block per segment (the first ones)
     const uint32_t *giant_seg_first;  // [n_giant_rows + 1]
     long long n_giant_segs;
+    const uint32_t *giant_place_first;  // [n_giant_places + 1], or NULL (rows that come range by range)
+    long long n_giant_places;
     // the hub rows' segments for k_fetch_narrow (hub_seg_first NULL: rows that come range by range)
     const uint32_t *hub_seg_first;
     long long n_hub_rows, n_hub_segs, n_split_rows, n_split_segs;
@@ -500,9 +505,11 @@ logoskg_status small_search(logoskg_graph *g, logoskg_result *r, const logoskg_q
                             bool force_push, int *next_hop, hipStream_t st);
 logoskg_status small_fetch(logoskg_result *r, int q0, int q1, int32_t *entity, uint8_t *hop, int32_t *pred,
                            hipStream_t st);
-// the hub rows' segments: `table` with theirs behind it (rows longest first), and their counts; into the arguments of a fetch
-std::vector<uint32_t> append_hub_segments(std::vector<uint32_t> table, const std::vector<ShortRow> &longer, RowClasses *rows);
-void set_hub_segments(FillArgs *a, const RowClasses &rows);
+// Tables of the segments that the predecessor pass cuts long rows (longest first) into, one behind the other, with their
+// counts; where they lie on the device; into the arguments of a fetch
+std::vector<uint32_t> segment_tables(const std::vector<ShortRow> &longer, uint32_t giant_min, RowClasses *rows);
+void set_segment_tables(RowClasses *rows, uint32_t *table);
+void set_row_segments(FillArgs *a, const RowClasses &rows);
 void drop_walk_tables(logoskg_result *r);
 void launch_lists(Profiler &prof, const FillArgs &a, int W, hipStream_t st);
 void launch_pred(Profiler &prof, const FillArgs &a, int W, long long n_hub_rows, long long n_other_rows, bool mask,

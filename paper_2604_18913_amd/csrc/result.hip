@@ -945,6 +945,27 @@ __global__ void __launch_bounds__(256) k_narrow_wave(FillArgs a, long long first
     narrow_wave_rows<W, N, MASK, STATS, BUF>(a, blockIdx.x, first_row, n_rows_total);
 }
 
+// The segment of a giant row that block b takes: the first segments of all rows, then the second ones, ..; row by row where
+// the rows come range by range.
+__device__ __forceinline__ void giant_segment(const FillArgs &a, uint32_t b, long long &row, uint32_t &seg) {
+    const uint32_t *first = a.giant_place_first ? a.giant_place_first : a.giant_seg_first;
+    long long lo = 0, hi = a.giant_place_first ? a.n_giant_places : a.n_giant_rows;  // the last one that begins at or before b
+    while (hi - lo > 1) {
+        const long long m = (lo + hi) >> 1;
+        if (first[m] <= b) lo = m; else hi = m;
+    }
+    const uint32_t in = b - first[lo];
+    row = a.giant_place_first ? (long long)in : lo;
+    seg = a.giant_place_first ? (uint32_t)lo : in;
+}
+
+// Which of queries 64 w .. 64 w + 63 (lane = query, *kept = its place in the row's line of the row buffer) an earlier segment
+// of the row has resolved: triple indices ascend, so a smaller one than this segment's first is another segment's.  (What
+// others store meanwhile may or may not be seen; a query that is walked again only costs time.)
+__device__ __forceinline__ unsigned long long resolved_before(const int32_t *kept, int32_t first_eid) {
+    return __ballot(__hip_atomic_load(kept, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < first_eid);
+}
+
 // Longer object rows: a block per (row, hop level), or per segment of a giant row, as k_pred_row; the
 // wavefronts take chunks in turn and keep the smallest entry per query in LDS after every step.
 template <int W, int N, bool MASK, bool STATS, bool BUF, bool SEG>
@@ -956,15 +977,7 @@ __global__ void __launch_bounds__(1024) k_narrow_row(FillArgs a, long long first
     __shared__ unsigned long long srem[N];
     long long row_i = blockIdx.x;
     uint32_t seg = 0;
-    if (SEG) {  // the giant row this segment belongs to: last row whose first segment is <= blockIdx.x
-        long long lo_r = 0, hi_r = a.n_giant_rows;
-        while (hi_r - lo_r > 1) {
-            const long long m = (lo_r + hi_r) >> 1;
-            if (a.giant_seg_first[m] <= blockIdx.x) lo_r = m; else hi_r = m;
-        }
-        row_i = lo_r;
-        seg = blockIdx.x - a.giant_seg_first[lo_r];
-    }
+    if (SEG) giant_segment(a, blockIdx.x, row_i, seg);
     const int ev = a.rows[first_row + row_i];
     const int t = threadIdx.x, wave = t >> 6, nw = blockDim.x >> 6, v = lane(), h = (int)blockIdx.y + 1;
     const int off = W == 16 ? (a.q0 >> 6) & ~(N - 1) : 0;
@@ -976,12 +989,13 @@ __global__ void __launch_bounds__(1024) k_narrow_row(FillArgs a, long long first
     const uint32_t lo = SEG ? row_lo + seg * (uint32_t)kGiantSegment : row_lo;
     const uint32_t hi = SEG ? min(row_hi, lo + (uint32_t)kGiantSegment) : row_hi;
     for (int q = t; q < 64 * N; q += blockDim.x) smin[q] = ~0u;
-    if (t < N) {
+    if (wave < N) {  // (a block has four wavefronts at least)
         unsigned long long x = lev[0];
 #pragma unroll
         for (int w = 1; w < N; ++w)
-            if (w == t) x = lev[w];
-        srem[t] = x;
+            if (w == wave) x = lev[w];
+        if (SEG && seg > 0) x &= ~resolved_before(&out[(off + wave) * 64 + v], a.in_eid[lo]);
+        if (v == 0) srem[wave] = x;
     }
     __syncthreads();
     const unsigned long long *prev = a.plv + (size_t)(h - 1) * a.pplane;
@@ -1993,15 +2007,7 @@ __global__ void __launch_bounds__(1024) k_pred_row(FillArgs a, long long first_r
     __shared__ unsigned long long srem[W], slevel[W];
     long long row_i = blockIdx.x;
     uint32_t seg = 0;
-    if (SEG) {  // the giant row this segment belongs to: last row whose first segment is <= blockIdx.x
-        long long lo_r = 0, hi_r = a.n_giant_rows;
-        while (hi_r - lo_r > 1) {
-            const long long m = (lo_r + hi_r) >> 1;
-            if (a.giant_seg_first[m] <= blockIdx.x) lo_r = m; else hi_r = m;
-        }
-        row_i = lo_r;
-        seg = blockIdx.x - a.giant_seg_first[lo_r];
-    }
+    if (SEG) giant_segment(a, blockIdx.x, row_i, seg);
     const int ev = a.rows[first_row + row_i];
     const int t = threadIdx.x, wave = t >> 6, nw = blockDim.x >> 6, v = lane(), lw = v & (W - 1);
     // gridDim.y > 1: one block per (row, hop level), so the levels of a long row run side by side
@@ -2026,6 +2032,11 @@ __global__ void __launch_bounds__(1024) k_pred_row(FillArgs a, long long first_r
         for (int q = t; q < Qp; q += blockDim.x) smin[(q >> 6) * kClaimStride + (q & 63)] = ~0u;
         __syncthreads();
         if (!wave_any(slevel[lw] != 0) || ((a.push_levels >> h) & 1u)) continue;  // block-uniform
+        if (SEG && seg > 0) {  // (sixteen wavefronts: one per word)
+            const unsigned long long done = resolved_before(&out[t], a.in_eid[lo]);
+            if (v == 0) srem[wave] &= ~done;
+            __syncthreads();
+        }
         const uint32_t *act_prev = a.act + (size_t)(h - 1) * a.actw;
         const unsigned long long *prev = a.levels + (size_t)(h - 1) * a.plane;
         const bool dense = !STATS && ((a.dense_levels >> h) & 1u);  // the line of an entity outside the level is zero
@@ -2213,7 +2224,12 @@ static logoskg_status count_plane(logoskg_result *r, const unsigned long long *p
     return LOGOSKG_OK;
 }
 
-void set_hub_segments(FillArgs *a, const RowClasses &rows) {
+void set_row_segments(FillArgs *a, const RowClasses &rows) {
+    a->n_giant_rows = rows.n_giant;
+    a->giant_seg_first = rows.giant_seg_first;
+    a->n_giant_segs = rows.n_giant_segs;
+    a->giant_place_first = rows.giant_place_first;
+    a->n_giant_places = rows.n_giant_places;
     a->hub_seg_first = rows.hub_seg_first;
     a->n_hub_rows = rows.n_hub;
     a->n_hub_segs = rows.n_hub_segs;
@@ -2724,10 +2740,7 @@ extern "C" logoskg_status logoskg_result_fetch(logoskg_result *r, int32_t q0, in
     for (int h = 1; h <= r->k && h < 32; ++h)
         if ((long long)r->stats[(size_t)h - 1].frontier_edges * 100 >= g->T * (long long)kDensePullPercent)
             a.dense_levels |= 1u << h;
-    a.n_giant_rows = in_rows.n_giant;  // (a sharded graph: set per object range)
-    a.giant_seg_first = in_rows.giant_seg_first;
-    a.n_giant_segs = in_rows.n_giant_segs;
-    if (g->num_shards <= 1) set_hub_segments(&a, in_rows);
+    if (g->num_shards <= 1) set_row_segments(&a, in_rows);  // (a sharded graph: per object range, or of its joined rows)
     a.host_graph = g;
     a.host_result = r;
     if (pred && W == 16) {

@@ -428,20 +428,11 @@ static logoskg_status build_in_chunks(logoskg_graph *g, ShardSet *ss, const int3
         std::stable_sort(longrows.begin(), longrows.end(), [&](int32_t x, int32_t y) {
             return ioff[(size_t)x + 1] - ioff[x] > ioff[(size_t)y + 1] - ioff[y];
         });
-        std::vector<uint32_t> first(1, 0);
-        const uint32_t giant_min = (uint32_t)std::max(kGiantRowMin, g->hub_min);
-        for (int32_t v : longrows) {
-            const uint32_t d = ioff[(size_t)v + 1] - ioff[v];
-            if (d < giant_min) break;
-            first.push_back(first.back() + (d + kGiantSegment - 1) / kGiantSegment);
-        }
-        ss->all_rows.n_long = g->in_rows.n_long;
-        ss->all_rows.n_hub = g->in_rows.n_hub;
-        ss->all_rows.n_giant = (int64_t)first.size() - 1;
-        ss->all_rows.n_giant_segs = first.back();
         std::vector<ShortRow> records;
         for (int32_t v : longrows) records.push_back({v, ioff[(size_t)v], ioff[(size_t)v + 1]});
-        first = append_hub_segments(std::move(first), records, &ss->all_rows);
+        ss->all_rows.n_long = g->in_rows.n_long;
+        ss->all_rows.n_hub = g->in_rows.n_hub;
+        const std::vector<uint32_t> first = segment_tables(records, (uint32_t)std::max(kGiantRowMin, g->hub_min), &ss->all_rows);
         LKG_HIP(hipMalloc((void **)&ss->sorted_longrows, std::max<size_t>(longrows.size(), 1) * sizeof(int32_t)));
         LKG_HIP(hipMalloc((void **)&ss->sorted_giant_first, first.size() * sizeof(uint32_t)));
         if (!longrows.empty())
@@ -449,8 +440,7 @@ static logoskg_status build_in_chunks(logoskg_graph *g, ShardSet *ss, const int3
         LKG_HIP(hipMemcpy(ss->sorted_giant_first, first.data(), first.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
         g->static_bytes += longrows.size() * sizeof(int32_t) + first.size() * sizeof(uint32_t);
         ss->all_rows.longrows = ss->sorted_longrows;
-        ss->all_rows.giant_seg_first = ss->sorted_giant_first;
-        ss->all_rows.hub_seg_first = ss->sorted_giant_first + ss->all_rows.n_giant + 1;
+        set_segment_tables(&ss->all_rows, ss->sorted_giant_first);
     }
     return LOGOSKG_OK;
 }
@@ -528,10 +518,7 @@ logoskg_status sharded_pred(logoskg_graph *g, FillArgs *a, int W, bool mask, hip
         x.in_rel = ss->all_in_rel;
         x.rows = all->longrows;
         x.row_base = 0;
-        x.n_giant_rows = all->n_giant;
-        x.giant_seg_first = all->giant_seg_first;
-        x.n_giant_segs = all->n_giant_segs;
-        set_hub_segments(&x, *all);
+        set_row_segments(&x, *all);
         launch_pred(g->prof, x, W, all->n_hub, all->n_long - all->n_hub, mask, st, st);
         return LOGOSKG_OK;
     }
