@@ -189,22 +189,39 @@ def _stream_handle(stream) -> int:
 class Result:
     """Device-resident state of one k-hop call (level planes, counts)."""
 
-    def __init__(self, graph: "Graph", handle: int):
+    def __init__(self, graph: "Graph", handle: int, num_queries: int, k: int, counted: bool):
         self._g = graph
         self._h = ctypes.c_void_p(handle)
+        self.num_queries = num_queries
+        self.k = k
+        self.words_per_entity = 1 if num_queries <= 64 else 4 if num_queries <= 256 else 16
+        self.padded_entities = (graph.num_entities + 63) // 64 * 64
+        self.total_reached = -1
+        self._off = None  # the offsets, copied from the handle once
+        if counted:
+            self._off = (ctypes.c_int64 * (num_queries + 1))()
+            _check(_load().logoskg_result_offsets(self._h, ctypes.addressof(self._off)))
+            self.total_reached = self._off[num_queries]
+
+    def _info(self):
+        """``logoskg_result_get_info``, which makes the visited plane where the search has not."""
         info = _ResultInfo()
         _check(_load().logoskg_result_get_info(self._h, ctypes.byref(info)))
-        self.num_queries = info.num_queries
-        self.k = info.k
-        self.words_per_entity = info.words_per_entity
-        self.padded_entities = info.padded_entities
-        self.total_reached = info.total_reached
-        self._levels_ptr = info.levels
-        self._visited_ptr = info.visited
+        return info
+
+    @property
+    def _levels_ptr(self):
+        return self._info().levels
+
+    @property
+    def _visited_ptr(self):
+        return self._info().visited
 
     def offsets(self) -> np.ndarray:
         off = np.zeros(self.num_queries + 1, dtype=np.int64)
-        _check(_load().logoskg_result_offsets(self._h, off.ctypes.data_as(ctypes.c_void_p)))
+        if self._off is None or not self._h:  # (refused by the library)
+            _check(_load().logoskg_result_offsets(self._h, off.ctypes.data_as(ctypes.c_void_p)))
+        off[:] = self._off
         return off
 
     def hop_stats(self):
@@ -413,7 +430,7 @@ class Graph:
                             mask_d.data_ptr() if mask_d is not None else None, _stream_handle(stream))
         h = ctypes.c_void_p()
         _check(_load().logoskg_khop(self._h, ctypes.byref(batch), ctypes.byref(h)))
-        res = Result(self, h.value)
+        res = Result(self, h.value, batch.num_queries, int(k), bool(counts))
         self._results.add(res)
         return res
 

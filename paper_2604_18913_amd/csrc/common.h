@@ -8,6 +8,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <array>
+#include <atomic>
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -285,7 +286,11 @@ struct logoskg_result {
     bool has_mask = false;
     bool has_counts = false;
     bool walk_exact = false;  // levels hold q^(h) of the plain iteration (no visited filter)
-    unsigned long long *visited = nullptr;  // [Epad][W]
+    unsigned long long *visited = nullptr;  // [Epad][W]; 16-word planes: the OR of the levels below vis_levels only
+    // 16-word planes: pulled hops do not keep visited (they ask the levels, see Seen), fold_visited makes it where it is
+    // read.  vis_dirty: the levels that may have left something in it (at least vis_levels).
+    std::atomic<int> vis_levels{0}, vis_dirty{0};
+    int n_levels = 0;  // levels the search has got to; what lies behind is empty
     unsigned long long *levels = nullptr;   // [k+1][Epad][W]
     uint32_t *act = nullptr;      // [k+1][Epad/32]: entity has a non-zero line in that level
     unsigned long long *allow = nullptr;    // [R][W] relation -> queries that may follow it
@@ -420,6 +425,31 @@ __device__ __forceinline__ unsigned long long query_bits(int Q, int w) {
     return (1ull << (Q - lo)) - 1ull;
 }
 
+// Where a kernel on 16-word planes finds what the queries have reached so far: a line of `base` where the entity is active in
+// one of the first `gate` levels (0: everywhere; base NULL: nowhere), and of the levels first .. last - 1 where it is
+// active there.  Pulled hops that kept the visited plane read and wrote a line of it per object row, for rows that most
+// hops reach once: four of the ten lines that such a row moved in a search of three hops with the counts and the clearing
+// behind it.
+struct Seen {
+    const unsigned long long *base, *levels;
+    const uint32_t *act;
+    long long plane, actw;
+    int gate, first, last;
+};
+
+__device__ __forceinline__ bool active_in(const Seen &s, int level, int e) {
+    return (s.act[(size_t)level * s.actw + (e >> 5)] >> (e & 31)) & 1u;
+}
+
+constexpr int kSeenGate = 3;  // at most so many levels gate the base
+
+__device__ __forceinline__ bool active_in_base(const Seen &s, int e) {
+    bool on = s.gate == 0;
+#pragma unroll
+    for (int l = 0; l < kSeenGate; ++l) on |= l < s.gate && active_in(s, l, e);
+    return on;
+}
+
 // A launch holds at most UINT32_MAX threads.  Items whose kernels take several lanes each go in ranges, launch(first, n), of
 // per_block items to a block of 256 threads; nearly always there is one.
 constexpr long long kMaxBlocks = (long long)UINT32_MAX / 256;
@@ -492,6 +522,9 @@ logoskg_status count_rows_on_device(const uint32_t *d_off, int32_t E, int hub_mi
 logoskg_status classify_on_device(const uint32_t *d_off, int32_t E, int hub_min, RowClasses *rc, std::vector<ShortRow> *longer, size_t *acct);
 // g->pairs' arrays (not its work lists) from the object-sorted ones; pairs.off stays NULL where they are not kept
 logoskg_status build_pairs_on_device(logoskg_graph *g);
+Seen seen_levels(const logoskg_result *r, int upto);
+// khop.hip: visited becomes the OR of the levels below `upto` where it does not hold them yet (a captured launch leaves that open)
+logoskg_status fold_visited(logoskg_result *r, int upto, hipStream_t st);
 struct TripleSorter;  // the triple list on the device during a sharded build (build_device.hip)
 logoskg_status sorter_create(logoskg_graph *g, const int32_t *subj, const int32_t *rel, const int32_t *obj,
                              TripleSorter **out);

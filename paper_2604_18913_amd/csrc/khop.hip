@@ -739,12 +739,46 @@ __device__ __forceinline__ unsigned group_ballot(bool p) {
 constexpr int kTailRows = 2;
 constexpr int kTailLines = 2;  // candidate lines of each row requested together
 
+// Word lw of what has reached the entities v[0 .. N - 1].  The bits of the base and of two levels, then the lines that they
+// ask for, are requested for all of them together.  DENSE: nearly every entity is active in the last level, whose lines
+// (zero elsewhere) are read without asking.
+template <int N, bool DENSE>
+__device__ __forceinline__ void seen_words(const Seen &s, const int (&v)[N], const bool (&have)[N], int lw, unsigned long long (&x)[N]) {
+    constexpr int W = 16, L = 2;
+    bool base[N];
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+        x[r] = 0ull;
+        base[r] = have[r] && s.base && active_in_base(s, v[r]);
+    }
+    int l0 = s.first;
+    do {
+        bool on[N][L];
+#pragma unroll
+        for (int i = 0; i < L; ++i)
+#pragma unroll
+            for (int r = 0; r < N; ++r)
+                on[r][i] = have[r] && l0 + i < s.last && ((DENSE && l0 + i == s.last - 1) || active_in(s, l0 + i, v[r]));
+#pragma unroll
+        for (int r = 0; r < N; ++r) {
+            if (base[r]) x[r] |= s.base[(size_t)v[r] * W + lw];
+            base[r] = false;
+        }
+#pragma unroll
+        for (int i = 0; i < L; ++i)
+#pragma unroll
+            for (int r = 0; r < N; ++r)
+                if (on[r][i]) x[r] |= s.levels[(size_t)(l0 + i) * s.plane + (size_t)v[r] * W + lw];
+        l0 += L;
+    } while (l0 < s.last);
+}
+
 template <int W, bool MASK, bool STATS, bool DENSE>
 __global__ void __launch_bounds__(256)
 k_pull_tail(const ShortRow *__restrict__ rows, long long n, const int32_t *__restrict__ in_sub, const uint16_t *__restrict__ in_rel,
             const unsigned long long *__restrict__ allow, const uint32_t *__restrict__ act_prev,
             const unsigned long long *__restrict__ prev, const unsigned long long *__restrict__ live,
-            unsigned long long *visited, unsigned long long *cur, uint32_t *act_cur,
+            unsigned long long *visited, Seen seen, unsigned long long *cur, uint32_t *act_cur,
             unsigned long long *stats, int walk_exact) {
     constexpr int NR = kTailRows;
     const long long group = ((long long)blockIdx.x * blockDim.x + threadIdx.x) / W;
@@ -767,12 +801,12 @@ k_pull_tail(const ShortRow *__restrict__ rows, long long n, const int32_t *__res
     }
     int s_next[NR], rel_next[NR];  // subject (and relation) ids of the next W entries, loaded one stage ahead
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {  // the visited line and the first entries are requested together
+    for (int r = 0; r < NR; ++r) {  // what has reached the row and the first entries are requested together
         vis[r] = need[r] = acc[r] = 0;
         s_next[r] = -1;
         rel_next[r] = 0;
         if (have[r]) {
-            vis[r] = visited[(size_t)v[r] * W + lw];
+            if (W < 16) vis[r] = visited[(size_t)v[r] * W + lw];
             if (lo[r] + lw < hi[r]) {
                 s_next[r] = in_sub[lo[r] + lw];
                 if (MASK) rel_next[r] = in_rel[lo[r] + lw];
@@ -780,6 +814,7 @@ k_pull_tail(const ShortRow *__restrict__ rows, long long n, const int32_t *__res
         }
     }
     const unsigned long long live_w = live[lw];
+    if constexpr (W == 16) seen_words<NR, DENSE>(seen, v, have, lw, vis);
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
         need[r] = (walk_exact ? ~0ull : ~vis[r]) & live_w;
@@ -873,7 +908,7 @@ k_pull_tail(const ShortRow *__restrict__ rows, long long n, const int32_t *__res
         const unsigned long long nw = acc[r] & need[r];
         if (row_end[r] > lo[r] && group_any<W>(nw != 0)) {
             cur[(size_t)v[r] * W + lw] = nw;
-            visited[(size_t)v[r] * W + lw] = vis[r] | nw;
+            if (W < 16) visited[(size_t)v[r] * W + lw] = vis[r] | nw;
             if (lw == 0) atomicOr(&act_cur[v[r] >> 5], 1u << (v[r] & 31));
         }
     }
@@ -896,7 +931,7 @@ k_pull_seg(const PullSegment *__restrict__ segs, long long n,
            const int32_t *__restrict__ in_sub, const uint16_t *__restrict__ in_rel,
            const unsigned long long *__restrict__ allow, const uint32_t *__restrict__ act_prev,
            const unsigned long long *__restrict__ prev, const unsigned long long *__restrict__ live,
-           unsigned long long *visited, unsigned long long *cur, uint32_t *act_cur,
+           unsigned long long *visited, Seen seen, unsigned long long *cur, uint32_t *act_cur,
            unsigned long long *stats, int walk_exact) {
     __shared__ int queue_s[4][64];
     __shared__ uint16_t queue_r[4][64];
@@ -913,7 +948,15 @@ k_pull_seg(const PullSegment *__restrict__ segs, long long n,
         lo = sg.begin;
         hi = sg.end;
         multi = sg.multi != 0;
-        vis = visited[(size_t)v * W + lw];
+        if constexpr (W < 16) {
+            vis = visited[(size_t)v * W + lw];
+        } else {
+            const int vs[1] = {v};
+            const bool all[1] = {true};
+            unsigned long long x[1];
+            seen_words<1, DENSE>(seen, vs, all, lw, x);
+            vis = x[0];
+        }
         need = (walk_exact ? ~0ull : ~vis) & live[lw];
         if (multi) need &= ~__atomic_load_n(&cur[(size_t)v * W + lw], __ATOMIC_RELAXED);
     }
@@ -951,7 +994,7 @@ k_pull_seg(const PullSegment *__restrict__ segs, long long n,
             if (!multi) {
                 if (lane() < W) {
                     cur[(size_t)v * W + lane()] = nb;
-                    visited[(size_t)v * W + lane()] = vis | nb;
+                    if (W < 16) visited[(size_t)v * W + lane()] = vis | nb;
                 }
                 if (lane() == 0) atomicOr(&act_cur[v >> 5], 1u << (v & 31));
             } else if (lane() < W && nb) {
@@ -965,7 +1008,7 @@ k_pull_seg(const PullSegment *__restrict__ segs, long long n,
     }
 }
 
-// Rows that were expanded by several segments: visited |= level[h], mark active.
+// Rows that were expanded by several segments: mark active, and on narrow planes visited |= level[h].
 template <int W>
 __global__ void __launch_bounds__(256)
 k_pull_finish(const int32_t *__restrict__ rows, long long n, unsigned long long *visited,
@@ -979,7 +1022,7 @@ k_pull_finish(const int32_t *__restrict__ rows, long long n, unsigned long long 
         c = cur[(size_t)v * W + lw];
     }
     if (group_any<W>(c != 0)) {
-        visited[(size_t)v * W + lw] |= c;
+        if (W < 16) visited[(size_t)v * W + lw] |= c;
         if (lw == 0) atomicOr(&act_cur[v >> 5], 1u << (v & 31));
     }
 }
@@ -1125,9 +1168,10 @@ k_pull_narrow(const PullSegment *__restrict__ segs, long long n_seg, unsigned se
 // the bitmaps are cleared, so that the next call that gets the block starts from zeros without a
 // fill of all k + 2 planes.  One wavefront per 64 entities, 16 bytes per lane (0.9M lines of three levels and as many of
 // visited: 78 us, 100 with 8 bytes).
+// (vis_levels: visited holds something only where one of the first so many levels does)
 template <int W>
 __global__ void __launch_bounds__(256)
-k_sparse_clear(long long Epad, int levels, uint32_t *act, long long actw, unsigned long long *visited,
+k_sparse_clear(long long Epad, int levels, int vis_levels, uint32_t *act, long long actw, unsigned long long *visited,
                unsigned long long *level_planes, long long plane, unsigned long long *live) {
     if (blockIdx.x == 0)
         for (int i = threadIdx.x; i < levels * (16 + kLevelCounters); i += blockDim.x) live[i] = 0ull;  // (and the counters behind them)
@@ -1142,7 +1186,7 @@ k_sparse_clear(long long Epad, int levels, uint32_t *act, long long actw, unsign
         if (h < levels) {
             uint32_t *a = act + (size_t)h * actw + base / 32;
             m = ((unsigned long long)a[1] << 32) | (unsigned long long)a[0];
-            any |= m;
+            any |= h < vis_levels ? m : 0ull;
             dst = level_planes + (size_t)h * plane;
             if (m && lane() < 2) a[lane()] = 0u;
         }
@@ -1158,6 +1202,35 @@ k_sparse_clear(long long Epad, int levels, uint32_t *act, long long actw, unsign
     }
 }
 
+// visited = the OR of the first n levels, on the lines of entities that are active in one of them.  Every line is written
+// whole, so that two that run at once agree.
+__global__ void __launch_bounds__(256)
+k_fold_visited(long long Epad, int n, const uint32_t *__restrict__ act, long long actw, const unsigned long long *__restrict__ levels,
+               long long plane, unsigned long long *visited) {
+    const long long base = ((long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 64;
+    if (base >= Epad) return;  // Epad is a multiple of 64
+    const int g = lane() >> 3, l = lane() & 7;  // eight lanes of 16 bytes per line
+    unsigned long long any = 0;
+    for (int h = 0; h < n; ++h) any |= *reinterpret_cast<const unsigned long long *>(act + (size_t)h * actw + base / 32);
+    if (any == 0) return;
+    ulonglong2 x[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = make_ulonglong2(0ull, 0ull);
+    for (int h = 0; h < n; ++h) {
+        const unsigned long long m = *reinterpret_cast<const unsigned long long *>(act + (size_t)h * actw + base / 32);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (!((m >> (8 * i + g)) & 1ull)) continue;
+            const ulonglong2 y = reinterpret_cast<const ulonglong2 *>(levels + (size_t)h * plane + ((size_t)base + 8 * i + g) * 16)[l];
+            x[i].x |= y.x;
+            x[i].y |= y.y;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        if ((any >> (8 * i + g)) & 1ull) reinterpret_cast<ulonglong2 *>(visited + ((size_t)base + 8 * i + g) * 16)[l] = x[i];
+}
+
 // ---------------------------------------------------------------- host side
 static inline unsigned blocks_for(long long threads, int block) {
     return (unsigned)((threads + block - 1) / block);
@@ -1165,6 +1238,26 @@ static inline unsigned blocks_for(long long threads, int block) {
 
 static unsigned long long *level_counters(const logoskg_result *r, int h) {
     return r->live + (size_t)16 * (r->k + 1) + (size_t)kLevelCounters * h;
+}
+
+constexpr int kSeenLevels = 5;  // pulled hops in a row: at most so many levels are asked one by one, then visited is made
+
+Seen seen_levels(const logoskg_result *r, int upto) {
+    const int have = std::min(r->vis_levels.load(), upto);
+    return Seen{have ? r->visited : nullptr, r->levels, r->act, r->Epad * (long long)r->W, r->Epad / 32, have <= kSeenGate ? have : 0, have, upto};
+}
+
+logoskg_status fold_visited(logoskg_result *r, int upto, hipStream_t st) {
+    if (r->W != 16 || r->vis_levels.load() >= upto) return LOGOSKG_OK;
+    ProfScope ps(r->g->prof, KK_UPDATE, st);
+    if (r->vis_dirty.load() < upto) r->vis_dirty.store(upto);
+    k_fold_visited<<<dim3(blocks_for(r->Epad / 64, 4)), dim3(256), 0, st>>>(r->Epad, upto, r->act, r->Epad / 32, r->levels,
+                                                                          r->Epad * 16, r->visited);
+    LKG_HIP(hipGetLastError());
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &s) != hipSuccess) (void)hipGetLastError();
+    else if (s == hipStreamCaptureStatusNone) r->vis_levels.store(upto);  // (a recorded one has not run)
+    return LOGOSKG_OK;
 }
 
 template <int W, bool MASK>
@@ -1192,7 +1285,7 @@ static void launch_push(logoskg_graph *g, logoskg_result *r, int h, const unsign
         });
         g->prof.acc[KK_PUSH_TAIL].units[0] += g->prof.on ? nt : 0;
     }
-    if (!update) return;
+    if (!update || (W == 16 && r->walk_exact)) return;  // (walk-exact levels ask for nothing that was reached)
     ProfScope ps(g->prof, KK_UPDATE, st);
     const dim3 grid(blocks_for(r->Epad / 64, 4)), block(256);
     if (known) k_update_visited<W, false><<<grid, block, 0, st>>>(r->Epad, act_cur, cur, r->visited);
@@ -1230,6 +1323,7 @@ static void launch_pull_rows(logoskg_graph *g, logoskg_result *r, int h, const R
     const unsigned long long *live = r->live + (size_t)16 * (h - 1);
     auto stats = [&](int kind) { return STATS ? g->d_ctr + C_STATS + 4 * kind : nullptr; };
     const int walk = r->walk_exact ? 1 : 0;
+    const Seen seen = W == 16 && !walk ? seen_levels(r, h) : Seen{};
     if constexpr (W <= 4 && !STATS) {
         if (rc.n_seg + rc.n_tail == 0) return;
         ProfScope ps(g->prof, KK_PULL_TAIL, st);
@@ -1253,11 +1347,11 @@ static void launch_pull_rows(logoskg_graph *g, logoskg_result *r, int h, const R
         const dim3 grid(blocks_for(rc.n_seg, 4)), block(256);
         if (dense)
             k_pull_seg<W, MASK, STATS, true><<<grid, block, 0, st>>>(rc.seg, rc.n_seg, in_sub, in_rel,
-                                                                     r->allow, act_prev, prev, live, r->visited, cur,
+                                                                     r->allow, act_prev, prev, live, r->visited, seen, cur,
                                                                      act_cur, stats(KK_PULL_SEG), walk);
         else
             k_pull_seg<W, MASK, STATS, false><<<grid, block, 0, st>>>(rc.seg, rc.n_seg, in_sub, in_rel,
-                                                                      r->allow, act_prev, prev, live, r->visited, cur,
+                                                                      r->allow, act_prev, prev, live, r->visited, seen, cur,
                                                                       act_cur, stats(KK_PULL_SEG), walk);
     }
     if (rc.n_tail > 0) {
@@ -1266,11 +1360,11 @@ static void launch_pull_rows(logoskg_graph *g, logoskg_result *r, int h, const R
         const dim3 grid(blocks_for(groups * W, 256)), block(256);
         if (dense)
             k_pull_tail<W, MASK, STATS, true><<<grid, block, 0, st>>>(rc.tail, rc.n_tail, in_sub, in_rel, r->allow,
-                                                                      act_prev, prev, live, r->visited, cur, act_cur,
+                                                                      act_prev, prev, live, r->visited, seen, cur, act_cur,
                                                                       stats(KK_PULL_TAIL), walk);
         else
             k_pull_tail<W, MASK, STATS, false><<<grid, block, 0, st>>>(rc.tail, rc.n_tail, in_sub, in_rel, r->allow,
-                                                                       act_prev, prev, live, r->visited, cur, act_cur,
+                                                                       act_prev, prev, live, r->visited, seen, cur, act_cur,
                                                                        stats(KK_PULL_TAIL), walk);
     }
     if (rc.n_multi > 0) {
@@ -1510,13 +1604,14 @@ extern "C" void logoskg_result_free(logoskg_result *r) {
         ProfScope ps(g->prof, KK_CLEAR, st);
         const long long plane = r->Epad * r->W, actw = r->Epad / 32;
         const dim3 grid(blocks_for(r->Epad / 64, 4)), block(256);
+        const int vis = r->W == 16 ? r->vis_dirty.load() : r->k + 1;
         switch (r->W) {
-            case 1: k_sparse_clear<1><<<grid, block, 0, st>>>(r->Epad, r->k + 1, r->act, actw, r->visited, r->levels, plane, r->live); break;
-            case 4: k_sparse_clear<4><<<grid, block, 0, st>>>(r->Epad, r->k + 1, r->act, actw, r->visited, r->levels, plane, r->live); break;
-            default: k_sparse_clear<16><<<grid, block, 0, st>>>(r->Epad, r->k + 1, r->act, actw, r->visited, r->levels, plane, r->live); break;
+            case 1: k_sparse_clear<1><<<grid, block, 0, st>>>(r->Epad, r->k + 1, vis, r->act, actw, r->visited, r->levels, plane, r->live); break;
+            case 4: k_sparse_clear<4><<<grid, block, 0, st>>>(r->Epad, r->k + 1, vis, r->act, actw, r->visited, r->levels, plane, r->live); break;
+            default: k_sparse_clear<16><<<grid, block, 0, st>>>(r->Epad, r->k + 1, vis, r->act, actw, r->visited, r->levels, plane, r->live); break;
         }
         if (hipGetLastError() == hipSuccess) zeroed[0] = zeroed[1] = true;
-        if (g->prof.on && r->n_active > 0) g->prof.acc[KK_CLEAR].units[3] += 2 * r->n_active * r->W;
+        if (g->prof.on && r->n_active > 0) g->prof.acc[KK_CLEAR].units[3] += (vis > r->k ? 2 : 1) * r->n_active * r->W;
     }
     // the blocks may still be in use by work on the stream of the result's last call
     g->pool.release_after(ptrs, zeroed, n, st);
@@ -1606,6 +1701,8 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
                                                                           (unsigned long long *)r->allow);
     }
     int first_hop = 1;
+    r->vis_levels = r->vis_dirty = W == 16 ? 1 : k + 1;  // the seeds
+    r->n_levels = 1;
     if (small && (s = small_search(g, r, b, want_counts, dir == LOGOSKG_DIR_PUSH, &first_hop, st)) != LOGOSKG_OK) return fail(s);
     if (!small) {
         g->prof.begin(KK_SEED, st);
@@ -1638,6 +1735,11 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
         hs.direction = pull ? LOGOSKG_DIR_PULL : LOGOSKG_DIR_PUSH;
         unsigned long long hc[C_TOTAL] = {};
         memcpy(hc, g->h_ctr, C_STATS * sizeof(hc[0]));
+        if (W == 16 && !walk_exact) {
+            // a push asks visited, and so does a pulled hop with many levels behind it
+            const bool fold = !pull || h - r->vis_levels > kSeenLevels;
+            if (fold && (s = fold_visited(r, h, st)) != LOGOSKG_OK) return fail(s);
+        }
         if (want_stats)
             KH(hipMemsetAsync(g->d_ctr + C_STATS, 0, 4 * KK_NUM * sizeof(unsigned long long), st));
         if (g->num_shards > 1) {
@@ -1651,6 +1753,8 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
             launch_resident_hop(g, r, h, pull, want_stats, hc, st);
             KH(hipGetLastError());
         }
+        r->n_levels = h + 1;
+        if (W == 16 && !walk_exact && !pull) r->vis_levels = r->vis_dirty = h + 1;
         if (h == k && !want_stats) {  // (its counters only feed the statistics: read behind the counts)
             census_slot(g, h)[kCensusDone] = 0;
             if ((s = launch_census(g, r, h, pull, census_slot(g, h), nullptr, st)) != LOGOSKG_OK) return fail(s);
@@ -1698,6 +1802,12 @@ extern "C" logoskg_status logoskg_result_get_info(const logoskg_result *r, logos
     o->words_per_entity = r->W;
     o->num_levels = r->k + 1;
     o->padded_entities = r->Epad;
+    if (r->W == 16 && r->vis_levels.load() < r->n_levels) {
+        // on a stream of its own: the search has ended, and nothing that may run on others reads the plane
+        LKG_HIP(hipSetDevice(r->g->device));
+        LKG_TRY(fold_visited(const_cast<logoskg_result *>(r), r->n_levels, r->g->side[0]));
+        LKG_HIP(hipStreamSynchronize(r->g->side[0]));
+    }
     o->visited = (const uint64_t *)r->visited;
     o->levels = (const uint64_t *)r->levels;
     o->total_reached = r->has_counts ? r->reached_off.back() : -1;

@@ -334,8 +334,10 @@ __device__ __forceinline__ void full_add(unsigned long long a, unsigned long lon
 // wavefront per word that transposed 64 x 64 bits per tile, the lines handed over through LDS, was a chain of latencies and
 // twelve LDS permutes per (tile, word): 20M entities 1,338 -> 620 us (2.6 GB read, 0.6 GB written), 30M triples' 0.9M listed
 // ones 72 -> 35 us.
+constexpr int kCountLevels = 3;  // levels whose active bits are asked for ahead of the first line
+
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8)))
-k_count(const unsigned long long *__restrict__ visited, long long ntiles, int32_t E, const int32_t *__restrict__ tile_ent,
+k_count(Seen s, long long ntiles, int32_t E, const int32_t *__restrict__ tile_ent,
         const unsigned long long *__restrict__ n_active, uint16_t *tile_base, uint32_t *super_sum) {
     constexpr int W = 16, Qp = 64 * W;
     __shared__ uint8_t cnt[kSuperTiles][Qp];  // (at most 64)
@@ -345,31 +347,44 @@ k_count(const unsigned long long *__restrict__ visited, long long ntiles, int32_
     const int n = (int)max(0ll, min((long long)kSuperTiles, ntiles - first));  // block-uniform
     if (wave < n) {
         const long long tile = first + wave;
-        int32_t e[16];
-        if (tile_ent) {
+        // lane v asks for the tile's entity v; group g's lanes take the lines of entities 16 g .. 16 g + 15, four at a time
+        // (sixteen, and their words of another level beside them, are more registers than two blocks per CU have)
+        const int32_t own = (int32_t)tile_entity(tile_ent, tile, v, E);
+        auto in_level = [&](int l) { return __ballot(l < s.last && own >= 0 && active_in(s, l, own)); };
+        unsigned long long on[1 + kCountLevels];
+        on[0] = __ballot(s.base && own >= 0 && active_in_base(s, own));
 #pragma unroll
-            for (int i = 0; i < 16; i += 4) {
-                const int4 y = *reinterpret_cast<const int4 *>(tile_ent + tile * 64 + g * 16 + i);
-                e[i] = y.x; e[i + 1] = y.y; e[i + 2] = y.z; e[i + 3] = y.w;
-            }
-        } else {
+        for (int l = 0; l < kCountLevels; ++l) on[1 + l] = in_level(s.first + l);
+        unsigned long long p[7] = {};  // p[b]: bit b of the sums
+#pragma unroll 1
+        for (int i0 = 0; i0 < 16; i0 += 4) {
+            int32_t e[4];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) e[i] = (int32_t)tile_entity(nullptr, tile, g * 16 + i, E);
+            for (int i = 0; i < 4; ++i) e[i] = __shfl(max(own, 0), g * 16 + i0 + i);
+            unsigned long long x[4] = {};
+            auto add_lines = [&](const unsigned long long *__restrict__ lines, unsigned long long active) {
+                const unsigned mine = (unsigned)(active >> (g * 16 + i0));
+                if (!(active & (0x000f000f000f000full << i0))) return;  // wavefront-uniform
+                unsigned long long y[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) y[i] = lines[(size_t)e[i] * W + lw];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) x[i] |= (mine >> i) & 1u ? y[i] : 0ull;
+            };
+            add_lines(s.base, on[0]);
+#pragma unroll
+            for (int l = 0; l < kCountLevels; ++l) add_lines(s.levels + (size_t)(s.first + l) * s.plane, on[1 + l]);
+            for (int l = s.first + kCountLevels; l < s.last; ++l) add_lines(s.levels + (size_t)l * s.plane, in_level(l));
+            unsigned long long c2[2], c4;
+            full_add(x[0], x[1], p[0], p[0], c2[0]);
+            full_add(x[2], x[3], p[0], p[0], c2[1]);
+            full_add(c2[0], c2[1], p[1], p[1], c4);
+            unsigned long long carry = p[2] & c4;
+            p[2] ^= c4;
+            c4 = p[3] & carry;
+            p[3] ^= carry;
+            p[4] ^= c4;  // (16 at most)
         }
-        unsigned long long x[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) x[i] = visited[(size_t)max(e[i], 0) * W + lw];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) x[i] = e[i] >= 0 ? x[i] : 0ull;
-        // p[b]: bit b of the sums
-        unsigned long long p[7] = {}, c2[8], c4[4], c8[2];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) full_add(x[2 * i], x[2 * i + 1], p[0], p[0], c2[i]);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) full_add(c2[2 * i], c2[2 * i + 1], p[1], p[1], c4[i]);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) full_add(c4[2 * i], c4[2 * i + 1], p[2], p[2], c8[i]);
-        full_add(c8[0], c8[1], 0ull, p[3], p[4]);
 #pragma unroll
         for (int s = 0; s < 2; ++s) {  // the four groups
             unsigned long long carry = 0;
@@ -1497,8 +1512,8 @@ k_pred_walk(FillArgs a, unsigned long long *__restrict__ codes, unsigned long lo
     };
     if (ev >= 0) {
         lv0 = level_word(0, ev) & range_w;
-        if (G > 4 || a.pstride == W) visw = a.visited[(size_t)ev * W + lw] & range_w;
-        else visw = ~0ull & range_w;  // (packed planes: the level words below decide)
+        if (a.visited && (G > 4 || a.pstride == W)) visw = a.visited[(size_t)ev * W + lw] & range_w;
+        else visw = ~0ull & range_w;  // (the level words below decide)
         lo = a.in_off[ev];
         hi = a.in_off[ev + 1];
     }
@@ -2185,9 +2200,9 @@ static logoskg_status ensure_active_list(logoskg_result *r, hipStream_t st) {
     return LOGOSKG_OK;
 }
 
-// Per-query counts of the set bits of one plane (visited, or a level) as three nested exclusive
+// Per-query counts of the set bits of one plane (visited, or a level; 16-word planes: what `seen` names) as three nested exclusive
 // prefixes plus the offsets of the query-major lists; the tables are allocated on first use.
-static logoskg_status count_plane(logoskg_result *r, const unsigned long long *plane_bits, uint16_t **tile_base,
+static logoskg_status count_plane(logoskg_result *r, const unsigned long long *plane_bits, const Seen &seen, uint16_t **tile_base,
                                   uint32_t **super_base, uint32_t **mega_base, long long **d_off,
                                   std::vector<int64_t> *off, hipStream_t st) {
     logoskg_graph *g = r->g;
@@ -2208,7 +2223,7 @@ static logoskg_status count_plane(logoskg_result *r, const unsigned long long *p
                                r->tile_ent ? r->d_nact : nullptr, g->h_ctr + C_TOTAL};
         if (W == 1) k_count_narrow<1><<<grid, block, 0, st>>>(plane_bits, ntiles, g->E, r->tile_ent, r->d_nact, *tile_base, scan);
         else if (W == 4) k_count_narrow<4><<<grid, block, 0, st>>>(plane_bits, ntiles, g->E, r->tile_ent, r->d_nact, *tile_base, scan);
-        else k_count<<<grid, block, 0, st>>>(plane_bits, ntiles, g->E, r->tile_ent, r->d_nact, *tile_base, *super_base);
+        else k_count<<<grid, block, 0, st>>>(seen, ntiles, g->E, r->tile_ent, r->d_nact, *tile_base, *super_base);
     }
     if (W == 16) {
         ProfScope ps(g->prof, KK_SCAN, st);
@@ -2238,8 +2253,8 @@ void set_row_segments(FillArgs *a, const RowClasses &rows) {
 }
 
 logoskg_status count_reached(logoskg_result *r, hipStream_t st) {
-    LKG_TRY(count_plane(r, r->visited, &r->tile_base, &r->super_base, &r->mega_base, &r->d_reached_off,
-                        &r->reached_off, st));
+    LKG_TRY(count_plane(r, r->visited, r->W == 16 ? seen_levels(r, r->n_levels) : Seen{}, &r->tile_base, &r->super_base,
+                        &r->mega_base, &r->d_reached_off, &r->reached_off, st));
     r->has_counts = true;
     return LOGOSKG_OK;
 }
@@ -2766,6 +2781,11 @@ extern "C" logoskg_status logoskg_result_fetch(logoskg_result *r, int32_t q0, in
         a.sparse = need * kSparseShare <= a.ntiles * 64 * 64 * words;
     }
     const bool counting = g->prof.counters;
+    // 16-word planes: the kernels that ask visited (all but the pair of walk and writer on a list of active entities)
+    if (W == 16 && r->vis_levels.load() < r->n_levels) {
+        if (pred && a.row_pred && a.tile_ent && pred_uses_staged_kernel(a, W)) a.visited = nullptr;
+        else LKG_TRY(fold_visited(r, r->n_levels, st));
+    }
     // levels whose frontier holds at most a quarter of the triples: their long rows are resolved from the
     // subject side (resident graphs, row buffer in use, minimum-hop search); needs the triple index of
     // every entry of SUB
@@ -2839,7 +2859,8 @@ extern "C" logoskg_status logoskg_result_level_offsets(logoskg_result *r, int32_
     if (h < 0 || h > r->k) { set_error("level %d outside [0, %d]", h, r->k); return LOGOSKG_EINVAL; }
     LKG_HIP(hipSetDevice(r->g->device));
     r->level_counted = -1;
-    LKG_TRY(count_plane(r, r->levels + (size_t)h * r->Epad * r->W, &r->lvl_tile_base, &r->lvl_super_base,
+    const unsigned long long *level = r->levels + (size_t)h * r->Epad * r->W;
+    LKG_TRY(count_plane(r, level, Seen{level}, &r->lvl_tile_base, &r->lvl_super_base,
                         &r->lvl_mega_base, &r->d_level_off, &r->level_off, (hipStream_t)stream));
     r->level_counted = h;
     memcpy(level_off, r->level_off.data(), (size_t)(r->Q + 1) * sizeof(int64_t));
