@@ -1740,6 +1740,55 @@ __device__ __forceinline__ void emit_word(const FillArgs &a, const uint32_t (&c)
     }
 }
 
+// The code byte of query qq, and its predecessor where all of them lie in the pool (`at`: the lane's byte offset there; stride:
+// 4 for a row_pred line, which has an entry per query, 0 for edge ids, by row position, which is 0 for long rows).  seeds: the
+// queries with a seed in this tile, hardly ever any.
+struct Emitted {
+    uint32_t hc;  // hop + 1
+    int val;
+};
+
+__device__ __forceinline__ bool bit_of(unsigned long long x, int qq) { return ((qq < 32 ? (uint32_t)x : (uint32_t)(x >> 32)) >> (qq & 31)) & 1u; }
+
+__device__ __forceinline__ Emitted emit_pooled(uint32_t c, int qq, unsigned long long seeds, const int *pool, uint32_t at, uint32_t stride) {
+    const uint32_t hc = __builtin_amdgcn_ubfe(c, (unsigned)(8 * (qq & 3)), 3u), jp = __builtin_amdgcn_ubfe(c, (unsigned)(8 * (qq & 3) + 3), 5u);
+    int val = *reinterpret_cast<const int *>(reinterpret_cast<const char *>(pool) + (at + (uint32_t)qq * stride + 4u * jp));
+    if (bit_of(seeds, qq)) val = hc == 1u ? -1 : val;
+    return Emitted{hc, val};
+}
+
+__device__ __forceinline__ uint32_t rank_in(unsigned long long m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// All predecessors in the pool, hop numbers asked for: what nearly every block does.  The 64 queries are written out (36
+// vector and 33 scalar instructions per tile and query with the general form, 30 and 27 so), and the tiles keep together
+// by a barrier per eight queries: 516M pairs 1,490 us with the general form, 1,425 with a barrier per query, 1,373 so.
+// (The tiles' pieces put together in LDS and stored as whole aligned groups: 1,514.)
+__device__ __forceinline__ void emit_word_pooled(const FillArgs &a, const uint32_t (&c)[16], unsigned long long live, unsigned long long seeds,
+                                                 uint32_t pos_lo, uint32_t pos_hi, int ent_id, const int *pool, uint32_t at, uint32_t stride) {
+    live = uniform64(live);
+#pragma unroll
+    for (int qq = 0; qq < 64; ++qq) {
+        if (bit_of(live, qq)) {
+            const Emitted e = emit_pooled(c[qq >> 2], qq, seeds, pool, at, stride);
+            const unsigned long long m = __ballot(e.hc != 0u);
+            const unsigned long long base = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)pos_hi, qq) << 32) |
+                                            (uint32_t)__builtin_amdgcn_readlane((int)pos_lo, qq);
+            if (e.hc != 0u) {
+                const uint32_t rank = rank_in(m);
+                int32_t *const pe = a.entity + base;
+                uint8_t *const ph = a.hop + base;
+                int32_t *const pp = a.pred + base;
+                pe[rank] = ent_id;
+                ph[rank] = (uint8_t)(e.hc - 1u);
+                pp[rank] = e.val;
+            }
+        }
+        if ((qq & 7) == 7) __builtin_amdgcn_s_barrier();
+    }
+}
+
 __global__ void __launch_bounds__(kEmitTiles * 64) __attribute__((amdgpu_waves_per_eu(8, 8)))
 k_pred_emit(FillArgs a, const unsigned long long *__restrict__ planes, long long tile0, long long ntile, int w0, int nw,
             int eid_cap, int line_cap) {
@@ -1774,6 +1823,8 @@ k_pred_emit(FillArgs a, const unsigned long long *__restrict__ planes, long long
     const size_t eo = ew >= 0 ? (size_t)ew : 0;
     const uint32_t wlo = a.in_off[eo], wdeg = a.in_off[eo + 1] - wlo;
     const unsigned long long vis = valid && ew >= 0 ? P[0] | P[1] | P[2] : 0ull;
+    unsigned long long seeds = vis & P[0] & ~(P[1] | P[2]);  // hop + 1 == 1
+    seeds = wave_any(seeds != 0) ? uniform64(wave_or64(seeds)) : 0ull;
     // where a lane's predecessors come from: the edge ids of its own short row (by row position),
     // its line of row_pred (by query), or nowhere (the block-per-row kernel writes them).  Seeds
     // get their -1 in the loop.
@@ -1903,7 +1954,10 @@ k_pred_emit(FillArgs a, const unsigned long long *__restrict__ planes, long long
     const int *const my_eids = eid_tab + (staged ? off : 0);
     const int32_t *const my_row = a.in_eid + wlo;
     const int *const my_line = rp_tab + (lined ? line0 + __popcll(bq_wave & below) : 0) * 64;
-    if (staged) {
+    if (staged && lined && a.row_pred && a.hop) {  // block-uniform
+        const uint32_t at = 4u * (uint32_t)((longrow ? my_line : my_eids) - pool);
+        emit_word_pooled(a, c, live, seeds, pos_lo, pos_hi, ent_id, pool, at, longrow ? 4u : 0u);
+    } else if (staged) {
         if (lined) emit_word<true, true>(a, c, live, pos_lo, pos_hi, ent_id, longrow, by_query, my_eids, my_row, my_line);
         else emit_word<true, false>(a, c, live, pos_lo, pos_hi, ent_id, longrow, by_query, my_eids, my_row, my_line);
     } else {
