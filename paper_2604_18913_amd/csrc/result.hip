@@ -1594,50 +1594,58 @@ k_pred_walk(FillArgs a, unsigned long long *__restrict__ codes, unsigned long lo
                 }
                 continue;
             }
-            for (uint32_t j0 = lo; j0 < hi; j0 += G) {
-                const uint32_t j = j0 + gl;
+            // The four groups go through their rows' positions in step, four at a time, so that a position's bits are the same in
+            // all lanes: a resolving line costs ten instructions (some forty where every group took its own next candidate).
+            for (int half = 0; half < kTailMaxDegree; half += G) {
                 int s = s_row, r = r_row;
-                bool cand = false;
-                if (j < hi) {
-                    if (j0 != lo) {
-                        s = a.in_sub[j];
-                        if (MASK) r = a.in_rel[j];
+                bool cand = group_any<G>(rem != 0) && half + gl < (int)deg;
+                if (cand) {
+                    if (half > 0) {
+                        s = a.in_sub[lo + half + gl];
+                        if (MASK) r = a.in_rel[lo + half + gl];
                     }
                     cand = dense || ((act_prev[s >> 5] >> (s & 31)) & 1u);
                 }
-                unsigned gm = (unsigned)((__ballot(cand) >> g0) & GMASK);
+                const unsigned long long all = __ballot(cand);
+                if (all == 0) continue;  // (wavefront-uniform among the lanes of the level)
+                unsigned mine = (unsigned)(all >> g0) & GMASK;
+                const unsigned any = (unsigned)(all | (all >> 16) | (all >> 32) | (all >> 48)) & GMASK;
                 if (STATS && gl == 0) {
-                    n_edges += min((uint32_t)G, hi - j0);
-                    n_lines += __popc(gm);
+                    n_edges += max(0, min(G, (int)deg - half));
+                    n_lines += __popc(mine);
                 }
-                while (gm) {  // two candidate lines in flight, resolved in edge order
-                    const int d0 = __ffs((int)gm) - 1;
-                    gm &= gm - 1;
-                    int d1 = -1;
-                    if (gm) {
-                        d1 = __ffs((int)gm) - 1;
-                        gm &= gm - 1;
-                    }
-                    const int s0 = __shfl(s, g0 + d0), s1 = __shfl(s, g0 + (d1 < 0 ? d0 : d1));
-                    unsigned long long l0 = prev[(size_t)s0 * W + lw], l1 = 0;
-                    if (d1 >= 0) l1 = prev[(size_t)s1 * W + lw];
-                    if (MASK) {
-                        const int r0 = __shfl(r, g0 + d0), r1 = __shfl(r, g0 + (d1 < 0 ? d0 : d1));
-                        l0 &= a.allow[(size_t)r0 * W + lw];
-                        if (d1 >= 0) l1 &= a.allow[(size_t)r1 * W + lw];
-                    }
-                    const unsigned long long hit0 = l0 & rem, hit1 = l1 & rem & ~l0;
-                    rem &= ~(l0 | l1);
-                    const int p0 = (int)(j0 - lo) + d0, p1 = (int)(j0 - lo) + (d1 < 0 ? 0 : d1);
 #pragma unroll
-                    for (int b = 0; b < 5; ++b) {  // all-ones or zero from bit b of the position
-                        const unsigned long long m0 = (unsigned long long)(long long)(-((p0 >> b) & 1));
-                        const unsigned long long m1 = (unsigned long long)(long long)(-((p1 >> b) & 1));
-                        J[b] |= (hit0 & m0) | (hit1 & m1);
+                for (int i0 = 0; i0 < G; i0 += 4) {
+                    if (!((any >> i0) & 15u)) continue;
+                    unsigned long long l[4];
+                    int sx[4], rx[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        sx[u] = __shfl(s, g0 + i0 + u);
+                        rx[u] = MASK ? __shfl(r, g0 + i0 + u) : 0;
                     }
-                    if (!group_any<G>(rem != 0)) break;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        l[u] = 0;
+                        if ((mine >> (i0 + u)) & 1u) {
+                            l[u] = prev[(size_t)sx[u] * W + lw];
+                            if (MASK) l[u] &= a.allow[(size_t)rx[u] * W + lw];
+                        }
+                    }
+                    unsigned long long found = 0;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const unsigned long long hit = l[u] & rem;
+                        rem &= ~l[u];
+                        found |= hit;
+                        if (u & 1) J[0] |= hit;
+                        if (u & 2) J[1] |= hit;
+                    }
+                    if (i0 & 4) J[2] |= found;
+                    if (i0 & 8) J[3] |= found;
+                    if (half) J[4] |= found;
+                    if (!group_any<G>(rem != 0)) mine = 0;
                 }
-                if (!group_any<G>(rem != 0)) break;
             }
         }
     }
