@@ -241,7 +241,7 @@ void set_segment_tables(RowClasses *rows, uint32_t *table) {
 
 static void drop_pairs(logoskg_graph *g) {
     PairRows &p = g->pairs;
-    for (void *x : {(void *)p.off, (void *)p.pull_sub, (void *)p.sub, (void *)p.eid, (void *)p.long_index, (void *)p.rows.tail,
+    for (void *x : {(void *)p.off, (void *)p.pull_sub, (void *)p.sub, (void *)p.eid, (void *)p.all_sub, (void *)p.all_rel, (void *)p.long_index, (void *)p.rows.tail,
                     (void *)p.rows.seg, (void *)p.rows.multi, (void *)p.rows.longrows, (void *)p.rows.giant_seg_first})
         if (x) (void)hipFree(x);
     p = PairRows();

@@ -220,11 +220,15 @@ __global__ void k_pair_rows(const uint32_t *__restrict__ off, int32_t E, const u
 __global__ void k_pair_fill(const unsigned long long *__restrict__ key, const uint32_t *__restrict__ new_upto,
                             const uint32_t *__restrict__ first_upto, long long T, unsigned bits,
                             const uint32_t *__restrict__ by_rank, const int32_t *__restrict__ in_sub,
-                            const int32_t *__restrict__ in_eid, int32_t *pull_sub, int32_t *sub, int32_t *eid) {
+                            const int32_t *__restrict__ in_eid, int32_t *pull_sub, int32_t *sub, int32_t *eid,
+                            const uint32_t *__restrict__ pos, const uint16_t *__restrict__ in_rel, int32_t *all_sub, uint16_t *all_rel) {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= T) return;
     const uint32_t n = new_upto[i], f = first_upto[i];
-    if (n != (i ? new_upto[i - 1] : 0u)) pull_sub[n - 1] = (int32_t)by_rank[key[i] & ((1ull << bits) - 1ull)];
+    const int32_t s = (int32_t)by_rank[key[i] & ((1ull << bits) - 1ull)];
+    all_sub[i] = s;
+    all_rel[i] = in_rel[pos[i]];
+    if (n != (i ? new_upto[i - 1] : 0u)) pull_sub[n - 1] = s;
     if (f != (i ? first_upto[i - 1] : 0u)) {
         sub[f - 1] = in_sub[i];
         eid[f - 1] = in_eid[i];
@@ -290,7 +294,7 @@ logoskg_status build_pairs_on_device(logoskg_graph *g) {
     PairRows p;
     bool room = true;
     auto keep = [&](auto **out, size_t count) {
-        if (room && hipMalloc((void **)out, count * 4) != hipSuccess) {
+        if (room && hipMalloc((void **)out, count * sizeof(**out)) != hipSuccess) {
             (void)hipGetLastError();
             *out = nullptr;
             room = false;
@@ -299,17 +303,19 @@ logoskg_status build_pairs_on_device(logoskg_graph *g) {
     keep(&p.pull_sub, n);
     keep(&p.sub, n);
     keep(&p.eid, n);
+    keep(&p.all_sub, (size_t)T);
+    keep(&p.all_rel, (size_t)T);
     keep(&p.off, (size_t)E + 1);
     if (!room) {
-        for (void *x : {(void *)p.pull_sub, (void *)p.sub, (void *)p.eid})
+        for (void *x : {(void *)p.pull_sub, (void *)p.sub, (void *)p.eid, (void *)p.all_sub, (void *)p.all_rel})
             if (x) (void)hipFree(x);
         return LOGOSKG_OK;
     }
     g->pairs = p;
-    g->static_bytes += (3 * (size_t)n + (size_t)E + 1) * 4;
+    g->static_bytes += (3 * (size_t)n + (size_t)E + 1) * 4 + (size_t)T * 6;
     k_pair_rows<<<per_entity, block>>>(g->in_off, E, is_new, p.off);
     k_pair_fill<<<per_triple, block>>>(keys.current(), is_new, is_first, T, bits, by_rank, g->in_sub, g->in_eid, p.pull_sub,
-                                       p.sub, p.eid);
+                                       p.sub, p.eid, vals.current(), g->in_rel, p.all_sub, p.all_rel);
     LKG_HIP(hipGetLastError());
     LKG_HIP(hipDeviceSynchronize());  // (the scratch goes)
     return LOGOSKG_OK;

@@ -169,6 +169,10 @@ constexpr int kPairShare = 90;
 struct PairRows {
     uint32_t *off = nullptr;
     int32_t *pull_sub = nullptr, *sub = nullptr, *eid = nullptr;
+    // every triple in pull_sub's order (rows as in_off has them), for pulled hops under whitelists: the first entries of all
+    // rows are the same few subjects, and parallel triples ask for one line after the other
+    int32_t *all_sub = nullptr;
+    uint16_t *all_rel = nullptr;
     RowClasses rows;  // (segments by their place in the row: the first ones of all rows, the second ones, ..)
     int32_t *long_index = nullptr;  // as logoskg_graph::long_index
 };

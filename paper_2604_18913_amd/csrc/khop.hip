@@ -1408,16 +1408,26 @@ void launch_pull_range(logoskg_graph *g, logoskg_result *r, int h, const RowClas
     }
 }
 
-// A pulled hop without whitelists takes the distinct pairs.
-static bool pulls_pairs(const logoskg_graph *g, const logoskg_result *r) { return !r->has_mask && g->pairs.off; }
-static const RowClasses &pull_lists(const logoskg_graph *g, const logoskg_result *r) { return pulls_pairs(g, r) ? g->pairs.rows : g->in_rows; }
-static const int32_t *pull_subjects(const logoskg_graph *g, const logoskg_result *r) { return pulls_pairs(g, r) ? g->pairs.pull_sub : g->in_sub; }
+// What a pulled hop of a resident graph walks: the distinct pairs, under whitelists all triples, both with the subjects that
+// most queries have reached first (where the graph has them so).
+struct PullArrays {
+    const RowClasses &rows;
+    const int32_t *sub;
+    const uint16_t *rel;
+};
+
+static PullArrays pull_arrays(const logoskg_graph *g, const logoskg_result *r) {
+    if (!g->pairs.off) return {g->in_rows, g->in_sub, g->in_rel};
+    if (r->has_mask) return {g->in_rows, g->pairs.all_sub, g->pairs.all_rel};
+    return {g->pairs.rows, g->pairs.pull_sub, nullptr};
+}
 
 template <int W>
 static void run_hop(logoskg_graph *g, logoskg_result *r, int h, bool pull, bool want_stats,
                     const unsigned long long *hc, hipStream_t st) {
     if (pull) {
-        launch_pull_range(g, r, h, pull_lists(g, r), pull_subjects(g, r), g->in_rel, hc, want_stats, true, st);
+        const PullArrays p = pull_arrays(g, r);
+        launch_pull_range(g, r, h, p.rows, p.sub, p.rel, hc, want_stats, true, st);
     } else {
         if (r->has_mask) launch_push<W, true>(g, r, h, hc, g->out_obj, g->out_rel, true, g->fr_tail, g->fr_seg, level_counters(r, h - 1), st);
         else launch_push<W, false>(g, r, h, hc, g->out_obj, g->out_rel, true, g->fr_tail, g->fr_seg, level_counters(r, h - 1), st);
@@ -1457,8 +1467,9 @@ void launch_resident_hop(logoskg_graph *g, logoskg_result *r, int h, bool pull, 
 
 // A pulled hop of a resident graph on narrow planes, for the case that *go says so.
 static void launch_pull_ahead(logoskg_graph *g, logoskg_result *r, int h, const unsigned long long *go, hipStream_t st) {
-    if (r->W == 1) pull_rows_w<1>(g, r, h, pull_lists(g, r), pull_subjects(g, r), g->in_rel, false, false, st, go);
-    else pull_rows_w<4>(g, r, h, pull_lists(g, r), pull_subjects(g, r), g->in_rel, false, false, st, go);
+    const PullArrays p = pull_arrays(g, r);
+    if (r->W == 1) pull_rows_w<1>(g, r, h, p.rows, p.sub, p.rel, false, false, st, go);
+    else pull_rows_w<4>(g, r, h, p.rows, p.sub, p.rel, false, false, st, go);
 }
 
 __global__ void k_clear_cursors(unsigned long long *ctr) { ctr[threadIdx.x] = 0ull; }
