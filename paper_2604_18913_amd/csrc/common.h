@@ -467,7 +467,7 @@ inline int words_for_queries(int Q) { return Q <= 64 ? 1 : (Q <= 256 ? 4 : 16); 
 
 // arguments of the list / predecessor kernels (result.hip)
 struct FillArgs {
-    int32_t E;
+    int32_t E, R;
     int Q, k, q0, q1, hub_min;
     long long ntiles;
     const int32_t *tile_ent;  // the tiles' entities (list of active entities) or NULL: tile i = ids 64 i ..

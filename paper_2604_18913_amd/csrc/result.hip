@@ -2109,6 +2109,10 @@ k_emit_sparse(FillArgs a, const uint8_t *__restrict__ codes, const unsigned long
 // (atomicMin; the line starts at INT_MAX).  A block that walks a whole 140,000-entry row is a chain
 // of dependent gathers that outlasts everything else in the launch; the segments of a row run side
 // by side, at the price of the early exit between them (it saved a quarter of the entries).
+// Under whitelists: where at most kFilterQueries queries are left, entries whose relation none of them may follow are left out
+// before their lines are asked for.
+constexpr int kFilterQueries = 24, kFilterRelations = 4096;
+
 template <bool MASK, bool STATS, bool BUF, bool SEG = false>
 __global__ void __launch_bounds__(1024) k_pred_row(FillArgs a, long long first_row) {
     static_assert(!SEG || BUF, "segments merge in the row buffer");
@@ -2118,6 +2122,7 @@ __global__ void __launch_bounds__(1024) k_pred_row(FillArgs a, long long first_r
     __shared__ unsigned int smin[W * kClaimStride];  // smallest entry per query (index into in_sub)
     __shared__ PredQueue queue[16];
     __shared__ unsigned long long srem[W], slevel[W];
+    __shared__ unsigned long long usable[MASK ? kFilterRelations / 64 : 1];  // relations that a query that is left may follow
     long long row_i = blockIdx.x;
     uint32_t seg = 0;
     if (SEG) giant_segment(a, blockIdx.x, row_i, seg);
@@ -2163,6 +2168,27 @@ __global__ void __launch_bounds__(1024) k_pred_row(FillArgs a, long long first_r
             unsigned long long rem = srem[lw];
             if (!wave_any(rem != 0)) break;  // same decision in every wave
             const unsigned long long before = rem;
+            bool by_relation = false;  // block-uniform
+            if constexpr (MASK) {
+                int left = v < W ? __popcll(rem) : 0;
+#pragma unroll
+                for (int m = W / 2; m >= 1; m >>= 1) left += __shfl_xor(left, m);
+                by_relation = a.R <= kFilterRelations && __builtin_amdgcn_readfirstlane(left) <= kFilterQueries;
+                if (by_relation) {
+                    for (int r0 = 64 * wave; r0 < a.R; r0 += 64 * nw) {  // lane = relation
+                        const int r = min(r0 + v, a.R - 1);
+                        unsigned long long any = 0;
+#pragma unroll
+                        for (int w = 0; w < W; w += 2) {
+                            const ulonglong2 x = *reinterpret_cast<const ulonglong2 *>(a.allow + (size_t)r * W + w);
+                            any |= (x.x & srem[w]) | (x.y & srem[w + 1]);
+                        }
+                        const unsigned long long bits = __ballot(any != 0);
+                        if (v == 0) usable[r0 / 64] = bits;
+                    }
+                    __syncthreads();
+                }
+            }
             // chunk c of this wavefront is chunk c * nw + wave of the step: a row shorter than a
             // step still spreads over all wavefronts
             const uint32_t w0 = s0 + 64u * wave;
@@ -2177,6 +2203,7 @@ __global__ void __launch_bounds__(1024) k_pred_row(FillArgs a, long long first_r
                     sj[c] = a.in_sub[j];
                     if (MASK) rj[c] = a.in_rel[j];
                     cj[c] = dense || ((act_prev[sj[c] >> 5] >> (sj[c] & 31)) & 1u);
+                    if (MASK && by_relation) cj[c] = cj[c] && ((usable[rj[c] >> 6] >> (rj[c] & 63)) & 1u);
                 }
             }
 #pragma unroll
@@ -2829,7 +2856,7 @@ extern "C" logoskg_status logoskg_result_fetch(logoskg_result *r, int32_t q0, in
     }
     const int W = r->W;
     FillArgs a = {};
-    a.E = g->E; a.Q = r->Q; a.k = r->k; a.q0 = q0; a.q1 = q1; a.hub_min = g->hub_min;
+    a.E = g->E; a.R = g->R; a.Q = r->Q; a.k = r->k; a.q0 = q0; a.q1 = q1; a.hub_min = g->hub_min;
     a.tile_ent = r->tile_ent; a.cpos = r->cpos; a.n_listed = r->n_active;
     a.ntiles = r->tile_ent ? (r->n_active + 63) / 64 : r->Epad / kTileEntities;
     a.tile_begin = 0; a.tile_count = a.ntiles;
@@ -2986,7 +3013,7 @@ extern "C" logoskg_status logoskg_result_level_fetch(logoskg_result *r, int32_t 
     const int W = r->W;
     FillArgs a = {};
     // the level plane plays the part of the visited plane; no hop numbers are asked for
-    a.E = g->E; a.Q = r->Q; a.k = 0; a.q0 = q0; a.q1 = q1; a.hub_min = g->hub_min;
+    a.E = g->E; a.R = g->R; a.Q = r->Q; a.k = 0; a.q0 = q0; a.q1 = q1; a.hub_min = g->hub_min;
     a.tile_ent = r->tile_ent; a.cpos = r->cpos; a.n_listed = r->n_active;
     a.ntiles = r->tile_ent ? (r->n_active + 63) / 64 : r->Epad / kTileEntities;
     a.tile_begin = 0; a.tile_count = a.ntiles;
