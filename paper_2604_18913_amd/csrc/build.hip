@@ -240,18 +240,17 @@ void set_segment_tables(RowClasses *rows, uint32_t *table) {
 }
 
 static void drop_pairs(logoskg_graph *g) {
-    PairRows &p = g->pairs;
-    for (void *x : {(void *)p.off, (void *)p.pull_sub, (void *)p.sub, (void *)p.eid, (void *)p.all_sub, (void *)p.all_rel, (void *)p.long_index, (void *)p.rows.tail,
-                    (void *)p.rows.seg, (void *)p.rows.multi, (void *)p.rows.longrows, (void *)p.rows.giant_seg_first})
+    for (void *x : {g->pairs.block, g->pairs.rows.block, (void *)g->pairs.long_index})
         if (x) (void)hipFree(x);
-    p = PairRows();
+    g->pairs = PairRows();
 }
 
-// Work lists over the rows of a CSR: short rows (on the device), segments of the longer ones (longest rows first; by_place:
+// Work lists over the rows of a CSR: short rows, segments of the longer ones (longest rows first; by_place:
 // the first segments of all rows, then the second ones, ..), rows with several segments, giant and hub rows' segments.
-static logoskg_status row_classes(logoskg_graph *g, const uint32_t *d_off, bool by_place, RowClasses *rc) {
+static logoskg_status row_classes(logoskg_graph *g, const uint32_t *d_off, bool by_place, Scratch &tmp, RowClasses *rc) {
     std::vector<ShortRow> longer;
-    LKG_TRY(classify_on_device(d_off, g->E, g->hub_min, rc, &longer, &g->static_bytes));
+    ShortRow *records = nullptr;
+    LKG_TRY(classify_on_device(d_off, g->E, g->hub_min, tmp, rc, &records, &longer));
     std::stable_sort(longer.begin(), longer.end(), [](const ShortRow &a, const ShortRow &b) { return a.end - a.begin > b.end - b.begin; });
     std::vector<int32_t> rows, multi;
     std::vector<PullSegment> seg;
@@ -268,16 +267,32 @@ static logoskg_status row_classes(logoskg_graph *g, const uint32_t *d_off, bool 
             if (r.end - r.begin <= place) break;
             seg.push_back({r.row, r.begin + place, std::min(r.begin + place + (uint32_t)kPullSegment, r.end), 1u});
         }
+    const std::vector<uint32_t> table = segment_tables(longer, (uint32_t)std::max(kGiantRowMin, g->hub_min), rc);
     rc->n_seg = (int64_t)seg.size();
     rc->n_multi = (int64_t)multi.size();
     rc->n_long = (int64_t)longer.size();
     if (!longer.empty()) rc->longest = longer[0].end - longer[0].begin;
-    uint32_t *table = nullptr;
-    LKG_TRY(upload(&table, segment_tables(longer, (uint32_t)std::max(kGiantRowMin, g->hub_min), rc), &g->static_bytes));
-    set_segment_tables(rc, table);
-    LKG_TRY(upload(&rc->seg, seg, &g->static_bytes));
-    LKG_TRY(upload(&rc->multi, multi, &g->static_bytes));
-    LKG_TRY(upload(&rc->longrows, rows, &g->static_bytes));
+    // one block: what comes from the host in one copy, behind it the short rows
+    std::vector<char> image;
+    auto put = [&](const void *p, size_t bytes) {
+        const size_t at = image.size();
+        image.resize(at + (std::max<size_t>(bytes, 4) + 15) / 16 * 16);
+        if (bytes) memcpy(image.data() + at, p, bytes);
+        return at;
+    };
+    const size_t at_seg = put(seg.data(), seg.size() * sizeof(PullSegment)), at_table = put(table.data(), table.size() * 4),
+                 at_multi = put(multi.data(), multi.size() * 4), at_rows = put(rows.data(), rows.size() * 4);
+    const size_t bytes = image.size() + (size_t)rc->n_tail * sizeof(ShortRow);
+    LKG_HIP(hipMalloc(&rc->block, bytes));
+    g->static_bytes += bytes;
+    char *const base = static_cast<char *>(rc->block);
+    rc->seg = reinterpret_cast<PullSegment *>(base + at_seg);
+    set_segment_tables(rc, reinterpret_cast<uint32_t *>(base + at_table));
+    rc->multi = reinterpret_cast<int32_t *>(base + at_multi);
+    rc->longrows = reinterpret_cast<int32_t *>(base + at_rows);
+    rc->tail = reinterpret_cast<ShortRow *>(base + image.size());
+    if (rc->n_tail) LKG_HIP(hipMemcpyAsync(rc->tail, records, (size_t)rc->n_tail * sizeof(ShortRow), hipMemcpyDeviceToDevice, nullptr));
+    LKG_HIP(hipMemcpy(base, image.data(), image.size(), hipMemcpyHostToDevice));
     return LOGOSKG_OK;
 }
 
@@ -344,11 +359,17 @@ extern "C" logoskg_status logoskg_build(const int32_t *subj, const int32_t *rel,
     logoskg_status st = LOGOSKG_OK;
     auto fail = [&](logoskg_status s) { logoskg_graph_free(g); return s; };
     try {
+        std::unique_ptr<Scratch, void (*)(Scratch *)> scratch(nullptr, scratch_destroy);
+        {
+            Scratch *x = nullptr;
+            if ((st = scratch_create(g, device_build, &x)) != LOGOSKG_OK) return fail(st);
+            scratch.reset(x);
+        }
         // work lists over the rows of OBJ (pull and predecessor kernels), and the rows of distinct pairs with theirs
         auto object_rows = [&]() -> logoskg_status {
-            LKG_TRY(row_classes(g, g->in_off, false, &g->in_rows));
-            LKG_TRY(build_pairs_on_device(g));
-            if (g->pairs.off && row_classes(g, g->pairs.off, true, &g->pairs.rows) != LOGOSKG_OK) {
+            LKG_TRY(row_classes(g, g->in_off, false, *scratch, &g->in_rows));
+            LKG_TRY(build_pairs_on_device(g, *scratch));
+            if (g->pairs.off && row_classes(g, g->pairs.off, true, *scratch, &g->pairs.rows) != LOGOSKG_OK) {
                 (void)hipGetLastError();  // (the graph works without them)
                 drop_pairs(g);
             }
@@ -356,13 +377,13 @@ extern "C" logoskg_status logoskg_build(const int32_t *subj, const int32_t *rel,
         };
         auto subject_row_counts = [&]() -> logoskg_status {
             unsigned int n[3];
-            LKG_TRY(count_rows_on_device(g->out_off, E, g->hub_min, n));
+            LKG_TRY(count_rows_on_device(g->out_off, E, g->hub_min, *scratch, n));
             g->n_out_rows = n[0];
             g->n_out_hubs = n[2];
             return LOGOSKG_OK;
         };
         if (device_build) {
-            if ((st = build_csr_on_device(g, subj, rel, obj)) != LOGOSKG_OK) return fail(st);
+            if ((st = build_csr_on_device(g, subj, rel, obj, *scratch)) != LOGOSKG_OK) return fail(st);
             g->row_begin = g->out_off;
             if ((st = subject_row_counts()) != LOGOSKG_OK) return fail(st);
             if ((st = object_rows()) != LOGOSKG_OK) return fail(st);
@@ -482,7 +503,7 @@ extern "C" void logoskg_graph_free(logoskg_graph *g) {
     if (g->ev_rows) (void)hipEventDestroy(g->ev_rows);
 
     void *ptrs[] = {g->out_off, g->out_obj, g->out_rel, g->in_off, g->in_sub, g->in_rel, g->in_eid,
-                    g->in_rows.tail, g->in_rows.seg, g->in_rows.multi, g->in_rows.longrows, g->in_rows.giant_seg_first, g->fr_tail,
+                    g->in_rows.block, g->in_rows.block ? nullptr : (void *)g->in_rows.longrows, g->fr_tail,
                     g->fr_seg, g->d_ctr, g->long_index, g->row_pred, g->out_eid, g->plane_buf};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);

@@ -15,6 +15,41 @@
 
 namespace lkg {
 
+// Device temporaries, freed on every way out.  With an arena they are pieces of one block, which the steps of a build use
+// one after the other (restart): taking and giving back each by itself was a millisecond on 3.4M triples.
+struct Scratch {
+    std::vector<void *> ptrs;
+    char *arena = nullptr;
+    size_t size = 0, used = 0;
+    ~Scratch() {
+        for (void *p : ptrs)
+            if (p) (void)hipFree(p);
+    }
+    void reserve(size_t bytes) {  // (without room for it the pieces are taken by themselves)
+        if (hipMalloc((void **)&arena, bytes) == hipSuccess) {
+            ptrs.push_back(arena);
+            size = bytes;
+        } else {
+            (void)hipGetLastError();
+            arena = nullptr;
+        }
+    }
+    void restart() { used = 0; }
+    static size_t rounded(size_t bytes) { return (std::max<size_t>(bytes, 1) + 255) / 256 * 256; }
+    template <typename T>
+    logoskg_status get(T **p, size_t n) {
+        const size_t bytes = rounded(n * sizeof(T));
+        if (used + bytes <= size) {
+            *p = reinterpret_cast<T *>(arena + used);
+            used += bytes;
+            return LOGOSKG_OK;
+        }
+        LKG_HIP(hipMalloc((void **)p, bytes));
+        ptrs.push_back(*p);
+        return LOGOSKG_OK;
+    }
+};
+
 namespace {
 
 constexpr int kBlock = 256;
@@ -70,20 +105,6 @@ __global__ void k_subject_of_triple(const int32_t *__restrict__ in_sub, const in
     if (p < T) subject_of[in_eid[p]] = (uint32_t)in_sub[p];
 }
 
-struct Scratch {  // device temporaries, freed on every way out
-    std::vector<void *> ptrs;
-    ~Scratch() {
-        for (void *p : ptrs)
-            if (p) (void)hipFree(p);
-    }
-    template <typename T>
-    logoskg_status get(T **p, size_t n) {
-        LKG_HIP(hipMalloc((void **)p, std::max<size_t>(n, 1) * sizeof(T)));
-        ptrs.push_back(*p);
-        return LOGOSKG_OK;
-    }
-};
-
 // sorted_eid = triple indices in (key, index) order; off = row offsets of that order
 logoskg_status sort_by(const int32_t *d_key, int64_t T, int32_t E, unsigned key_bits, uint32_t *d_iota,
                        uint32_t *d_keys_out, uint32_t *d_sorted_eid, uint32_t *d_off, void *d_tmp, size_t tmp_bytes) {
@@ -102,11 +123,57 @@ logoskg_status sort_by(const int32_t *d_key, int64_t T, int32_t E, unsigned key_
 
 }  // namespace
 
+static unsigned bits_for(int32_t E) {
+    unsigned bits = 1;
+    while (bits < 32 && (1ull << bits) < (unsigned long long)E) ++bits;
+    return bits;
+}
+
+static logoskg_status csr_sort_bytes(int64_t T, int32_t E, size_t *bytes) {
+    size_t sort_bytes = 0, scan_bytes = 0;
+    uint32_t *none = nullptr;
+    LKG_HIP(rocprim::radix_sort_pairs(nullptr, sort_bytes, (const uint32_t *)nullptr, none, none, none, (size_t)std::max<int64_t>(T, 1), 0u, bits_for(E)));
+    LKG_HIP(rocprim::inclusive_scan(nullptr, scan_bytes, none, none, (size_t)E + 1, rocprim::plus<uint32_t>()));
+    *bytes = std::max(sort_bytes, scan_bytes);
+    return LOGOSKG_OK;
+}
+
+struct PairBuffers {
+    rocprim::double_buffer<unsigned long long> keys{nullptr, nullptr};
+    rocprim::double_buffer<uint32_t> vals{nullptr, nullptr}, degrees{nullptr, nullptr}, ids{nullptr, nullptr};
+};
+
+static logoskg_status pair_sort_bytes(int64_t T, int32_t E, size_t (&bytes)[3]) {
+    PairBuffers b;
+    uint32_t *none = nullptr;
+    LKG_HIP(rocprim::radix_sort_pairs(nullptr, bytes[0], b.keys, b.vals, (size_t)T, 0u, 2 * bits_for(E)));
+    LKG_HIP(rocprim::radix_sort_pairs_desc(nullptr, bytes[1], b.degrees, b.ids, (size_t)E, 0u, 32u));
+    LKG_HIP(rocprim::inclusive_scan(nullptr, bytes[2], none, none, (size_t)T, rocprim::plus<uint32_t>()));
+    return LOGOSKG_OK;
+}
+
+// One block for the temporaries of a resident graph's build: the two sorts' (where they run here), then the distinct pairs'.
+logoskg_status scratch_create(logoskg_graph *g, bool sorts, Scratch **out) {
+    *out = nullptr;
+    std::unique_ptr<Scratch> s(new (std::nothrow) Scratch());
+    if (!s) { set_error("out of host memory"); return LOGOSKG_ENOMEM; }
+    const int64_t T = g->T;
+    size_t csr = 0, pair[3] = {};
+    if (sorts) LKG_TRY(csr_sort_bytes(T, g->E, &csr));
+    if (T > 0) LKG_TRY(pair_sort_bytes(T, g->E, pair));
+    const size_t for_sorts = sorts ? (size_t)T * 20 + csr : 0, for_pairs = (size_t)T * 24 + (size_t)g->E * 16 + std::max({pair[0], pair[1], pair[2]});
+    s->reserve(std::max(for_sorts, for_pairs) + 16 * 256);
+    *out = s.release();
+    return LOGOSKG_OK;
+}
+
+void scratch_destroy(Scratch *s) { delete s; }
+
 // Fills g->out_off/out_obj/out_rel/out_eid and g->in_off/in_sub/in_rel/in_eid from host triple arrays.
-logoskg_status build_csr_on_device(logoskg_graph *g, const int32_t *subj, const int32_t *rel, const int32_t *obj) {
+logoskg_status build_csr_on_device(logoskg_graph *g, const int32_t *subj, const int32_t *rel, const int32_t *obj, Scratch &tmp) {
     const int64_t T = g->T;
     const int32_t E = g->E;
-    Scratch tmp;
+    tmp.restart();
     int32_t *d_subj = nullptr, *d_rel = nullptr, *d_obj = nullptr;
     uint32_t *d_iota = nullptr, *d_keys = nullptr;
     unsigned long long *d_bad = nullptr;
@@ -133,15 +200,9 @@ logoskg_status build_csr_on_device(logoskg_graph *g, const int32_t *subj, const 
         set_error("triple %llu = (%d, %d, %d) is out of range", bad, subj[bad], rel[bad], obj[bad]);
         return LOGOSKG_EINVAL;
     }
-    unsigned key_bits = 1;
-    while (key_bits < 32 && (1ull << key_bits) < (unsigned long long)E) ++key_bits;
-    // one temporary buffer that serves the sort and the scan
-    size_t sort_bytes = 0, scan_bytes = 0;
-    LKG_HIP(rocprim::radix_sort_pairs(nullptr, sort_bytes, reinterpret_cast<const uint32_t *>(d_subj), d_keys, d_iota,
-                                      d_iota, (size_t)std::max<int64_t>(T, 1), 0u, key_bits));
-    LKG_HIP(rocprim::inclusive_scan(nullptr, scan_bytes, (uint32_t *)nullptr, (uint32_t *)nullptr, (size_t)E + 1,
-                                    rocprim::plus<uint32_t>()));
-    const size_t tmp_bytes = std::max(sort_bytes, scan_bytes);
+    const unsigned key_bits = bits_for(E);
+    size_t tmp_bytes = 0;  // one temporary buffer that serves the sort and the scan
+    LKG_TRY(csr_sort_bytes(T, E, &tmp_bytes));
     char *d_tmp = nullptr;
     LKG_TRY(tmp.get(&d_tmp, tmp_bytes));
 
@@ -235,40 +296,31 @@ __global__ void k_pair_fill(const unsigned long long *__restrict__ key, const ui
     }
 }
 
-logoskg_status build_pairs_on_device(logoskg_graph *g) {
+logoskg_status build_pairs_on_device(logoskg_graph *g, Scratch &tmp) {
     const int64_t T = g->T;
     const int32_t E = g->E;
     if (T == 0) return LOGOSKG_OK;
-    unsigned bits = 1;
-    while (bits < 32 && (1ull << bits) < (unsigned long long)E) ++bits;
-    rocprim::double_buffer<unsigned long long> keys(nullptr, nullptr);
-    rocprim::double_buffer<uint32_t> vals(nullptr, nullptr), degrees(nullptr, nullptr), ids(nullptr, nullptr);
+    const unsigned bits = bits_for(E);
     size_t bytes[3] = {};
-    LKG_HIP(rocprim::radix_sort_pairs(nullptr, bytes[0], keys, vals, (size_t)T, 0u, 2 * bits));
-    LKG_HIP(rocprim::radix_sort_pairs_desc(nullptr, bytes[1], degrees, ids, (size_t)E, 0u, 32u));
-    LKG_HIP(rocprim::inclusive_scan(nullptr, bytes[2], (uint32_t *)nullptr, (uint32_t *)nullptr, (size_t)T, rocprim::plus<uint32_t>()));
-    // one block: keys and positions twice, ranks and ids twice, the sorts' own
-    Scratch tmp;
-    char *at = nullptr;
-    const size_t sort_bytes = std::max({bytes[0], bytes[1], bytes[2]});
-    if (tmp.get(&at, ((size_t)T * 24 + (size_t)E * 16 + 256 * 9) + sort_bytes) != LOGOSKG_OK) {
-        (void)hipGetLastError();  // (without them the graph works as well)
-        return LOGOSKG_OK;
-    }
-    auto take = [&](auto **p, size_t n) {
-        *p = reinterpret_cast<std::remove_reference_t<decltype(*p)>>(at);
-        at += (n * sizeof(**p) + 255) / 256 * 256;
+    LKG_TRY(pair_sort_bytes(T, E, bytes));
+    tmp.restart();
+    bool room = true;
+    auto get = [&](auto **p, size_t n) {  // (without them the graph works as well)
+        if (room && tmp.get(p, n) != LOGOSKG_OK) {
+            (void)hipGetLastError();
+            room = false;
+        }
     };
-    unsigned long long *key[2];
-    uint32_t *pos[2], *rank[4];
-    for (auto &p : key) take(&p, (size_t)T);
-    for (auto &p : pos) take(&p, (size_t)T);
-    for (auto &p : rank) take(&p, (size_t)E);
-    char *const d_tmp = at;
-    keys = rocprim::double_buffer<unsigned long long>(key[0], key[1]);
-    vals = rocprim::double_buffer<uint32_t>(pos[0], pos[1]);
-    degrees = rocprim::double_buffer<uint32_t>(rank[0], rank[1]);
-    ids = rocprim::double_buffer<uint32_t>(rank[2], rank[3]);
+    unsigned long long *key[2] = {};
+    uint32_t *pos[2] = {}, *rank[4] = {};
+    char *d_tmp = nullptr;
+    for (auto &p : key) get(&p, (size_t)T);
+    for (auto &p : pos) get(&p, (size_t)T);
+    for (auto &p : rank) get(&p, (size_t)E);
+    get(&d_tmp, std::max({bytes[0], bytes[1], bytes[2]}));
+    if (!room) return LOGOSKG_OK;
+    rocprim::double_buffer<unsigned long long> keys(key[0], key[1]);
+    rocprim::double_buffer<uint32_t> vals(pos[0], pos[1]), degrees(rank[0], rank[1]), ids(rank[2], rank[3]);
 
     const dim3 block(kBlock), per_triple(grid_for(T)), per_entity(grid_for((int64_t)E + 1));
     uint32_t *const obj_of = pos[1];
@@ -292,27 +344,25 @@ logoskg_status build_pairs_on_device(logoskg_graph *g) {
     if ((int64_t)n * 100 > T * kPairShare) return LOGOSKG_OK;
 
     PairRows p;
-    bool room = true;
-    auto keep = [&](auto **out, size_t count) {
-        if (room && hipMalloc((void **)out, count * sizeof(**out)) != hipSuccess) {
-            (void)hipGetLastError();
-            *out = nullptr;
-            room = false;
-        }
-    };
-    keep(&p.pull_sub, n);
-    keep(&p.sub, n);
-    keep(&p.eid, n);
-    keep(&p.all_sub, (size_t)T);
-    keep(&p.all_rel, (size_t)T);
-    keep(&p.off, (size_t)E + 1);
-    if (!room) {
-        for (void *x : {(void *)p.pull_sub, (void *)p.sub, (void *)p.eid, (void *)p.all_sub, (void *)p.all_rel})
-            if (x) (void)hipFree(x);
+    const size_t of_pairs = Scratch::rounded((size_t)n * 4), of_triples = Scratch::rounded((size_t)T * 4), of_rels = Scratch::rounded((size_t)T * 2),
+                 of_rows = Scratch::rounded(((size_t)E + 1) * 4), all = 3 * of_pairs + of_triples + of_rels + of_rows;
+    if (hipMalloc(&p.block, all) != hipSuccess) {
+        (void)hipGetLastError();
         return LOGOSKG_OK;
     }
+    char *at = static_cast<char *>(p.block);
+    auto piece = [&](auto **out, size_t size) {
+        *out = reinterpret_cast<std::remove_reference_t<decltype(*out)>>(at);
+        at += size;
+    };
+    piece(&p.pull_sub, of_pairs);
+    piece(&p.sub, of_pairs);
+    piece(&p.eid, of_pairs);
+    piece(&p.all_sub, of_triples);
+    piece(&p.all_rel, of_rels);
+    piece(&p.off, of_rows);
     g->pairs = p;
-    g->static_bytes += (3 * (size_t)n + (size_t)E + 1) * 4 + (size_t)T * 6;
+    g->static_bytes += all;
     k_pair_rows<<<per_entity, block>>>(g->in_off, E, is_new, p.off);
     k_pair_fill<<<per_triple, block>>>(keys.current(), is_new, is_first, T, bits, by_rank, g->in_sub, g->in_eid, p.pull_sub,
                                        p.sub, p.eid, vals.current(), g->in_rel, p.all_sub, p.all_rel);
@@ -338,8 +388,7 @@ __global__ void __launch_bounds__(kBlock) k_row_counts(const uint32_t *__restric
     }
 }
 
-logoskg_status count_rows_on_device(const uint32_t *d_off, int32_t E, int hub_min, unsigned int (&n)[3]) {
-    Scratch tmp;
+logoskg_status count_rows_on_device(const uint32_t *d_off, int32_t E, int hub_min, Scratch &tmp, unsigned int (&n)[3]) {
     unsigned int *d_n = nullptr;
     LKG_TRY(tmp.get(&d_n, 3));
     LKG_HIP(hipMemsetAsync(d_n, 0, sizeof(n), nullptr));
@@ -362,19 +411,18 @@ __global__ void k_row_records(const int32_t *__restrict__ id, long long n, const
     if (i < n) out[i] = ShortRow{id[i], off[id[i]], off[id[i] + 1]};
 }
 
-// rc->tail and rc->n_tail / n_hub of the rows behind d_off; the longer rows, ascending, to the host.  (A stable sort of one
-// digit.  On the host, with the offsets copied back, 20M rows were a quarter of a second.)
-logoskg_status classify_on_device(const uint32_t *d_off, int32_t E, int hub_min, RowClasses *rc, std::vector<ShortRow> *longer, size_t *acct) {
+// The rows behind d_off: counts into rc, the short ones by descending length and then the longer ones as records on the
+// device (*records, in the scratch), the longer ones on the host as well.  (A stable sort of one digit.  On the host, with
+// the offsets copied back, 20M rows were a quarter of a second.)
+logoskg_status classify_on_device(const uint32_t *d_off, int32_t E, int hub_min, Scratch &tmp, RowClasses *rc, ShortRow **records, std::vector<ShortRow> *longer) {
+    tmp.restart();
     unsigned int n[3];
-    LKG_TRY(count_rows_on_device(d_off, E, hub_min, n));
+    LKG_TRY(count_rows_on_device(d_off, E, hub_min, tmp, n));
     rc->n_tail = (int64_t)n[0] - n[1];
     rc->n_hub = n[2];
     longer->resize(n[1]);
-    const size_t tail_bytes = std::max<size_t>((size_t)rc->n_tail, 1) * sizeof(ShortRow);
-    LKG_HIP(hipMalloc((void **)&rc->tail, tail_bytes));
-    *acct += tail_bytes;
+    *records = nullptr;
     if (n[0] == 0) return LOGOSKG_OK;
-    Scratch tmp;
     uint8_t *key[2] = {};
     int32_t *id[2] = {};
     for (auto &p : key) LKG_TRY(tmp.get(&p, (size_t)E));
@@ -385,17 +433,12 @@ logoskg_status classify_on_device(const uint32_t *d_off, int32_t E, int hub_min,
     LKG_HIP(rocprim::radix_sort_pairs(nullptr, bytes, keys, ids, (size_t)E, 0u, 6u));
     char *d_tmp = nullptr;
     LKG_TRY(tmp.get(&d_tmp, bytes));
+    LKG_TRY(tmp.get(records, n[0]));
     k_row_class<<<dim3(grid_for(E)), dim3(kBlock)>>>(d_off, E, key[0], id[0]);
     LKG_HIP(rocprim::radix_sort_pairs(d_tmp, bytes, keys, ids, (size_t)E, 0u, 6u));
-    if (rc->n_tail) k_row_records<<<dim3(grid_for(rc->n_tail)), dim3(kBlock)>>>(ids.current(), rc->n_tail, d_off, rc->tail);
-    if (n[1]) {
-        ShortRow *d_long = nullptr;
-        LKG_TRY(tmp.get(&d_long, n[1]));
-        k_row_records<<<dim3(grid_for(n[1])), dim3(kBlock)>>>(ids.current() + rc->n_tail, n[1], d_off, d_long);
-        LKG_HIP(hipMemcpy(longer->data(), d_long, (size_t)n[1] * sizeof(ShortRow), hipMemcpyDeviceToHost));
-    }
+    k_row_records<<<dim3(grid_for(n[0])), dim3(kBlock)>>>(ids.current(), n[0], d_off, *records);
     LKG_HIP(hipGetLastError());
-    LKG_HIP(hipDeviceSynchronize());
+    if (n[1]) LKG_HIP(hipMemcpy(longer->data(), *records + rc->n_tail, (size_t)n[1] * sizeof(ShortRow), hipMemcpyDeviceToHost));
     return LOGOSKG_OK;
 }
 

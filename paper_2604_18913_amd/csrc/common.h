@@ -141,6 +141,7 @@ struct SmallReport {
 };
 
 struct RowClasses {             // device work lists over the object rows, split by degree
+    void *block = nullptr;      // holds all of them, or NULL (lists that are owned one by one)
     ShortRow *tail = nullptr;   // rows with 1 .. kTailMaxDegree entries, descending degree
     PullSegment *seg = nullptr;  // segments of the longer rows, longest rows first
     int32_t *multi = nullptr;   // rows cut into more than one segment
@@ -167,6 +168,7 @@ struct RowClasses {             // device work lists over the object rows, split
 // room; off is NULL otherwise.  (Distinct pairs of 30M triples of concepts 65 %, 3.4M 52 %, 300M hub-heavy ones 85 %.)
 constexpr int kPairShare = 90;
 struct PairRows {
+    void *block = nullptr;  // holds the arrays
     uint32_t *off = nullptr;
     int32_t *pull_sub = nullptr, *sub = nullptr, *eid = nullptr;
     // every triple in pull_sub's order (rows as in_off has them), for pulled hops under whitelists: the first entries of all
@@ -520,12 +522,15 @@ struct FillArgs {
     int32_t *seg_pred;  // [n_split_segs][64 W]
 };
 
-logoskg_status build_csr_on_device(logoskg_graph *g, const int32_t *subj, const int32_t *rel, const int32_t *obj);
+struct Scratch;  // a build's device temporaries (build_device.hip)
+logoskg_status scratch_create(logoskg_graph *g, bool sorts, Scratch **out);
+void scratch_destroy(Scratch *s);
+logoskg_status build_csr_on_device(logoskg_graph *g, const int32_t *subj, const int32_t *rel, const int32_t *obj, Scratch &tmp);
 // rows of a CSR on the device: with an entry, of more than kTailMaxDegree, of at least hub_min
-logoskg_status count_rows_on_device(const uint32_t *d_off, int32_t E, int hub_min, unsigned int (&n)[3]);
-logoskg_status classify_on_device(const uint32_t *d_off, int32_t E, int hub_min, RowClasses *rc, std::vector<ShortRow> *longer, size_t *acct);
+logoskg_status count_rows_on_device(const uint32_t *d_off, int32_t E, int hub_min, Scratch &tmp, unsigned int (&n)[3]);
+logoskg_status classify_on_device(const uint32_t *d_off, int32_t E, int hub_min, Scratch &tmp, RowClasses *rc, ShortRow **records, std::vector<ShortRow> *longer);
 // g->pairs' arrays (not its work lists) from the object-sorted ones; pairs.off stays NULL where they are not kept
-logoskg_status build_pairs_on_device(logoskg_graph *g);
+logoskg_status build_pairs_on_device(logoskg_graph *g, Scratch &tmp);
 Seen seen_levels(const logoskg_result *r, int upto);
 // khop.hip: visited becomes the OR of the levels below `upto` where it does not hold them yet (a captured launch leaves that open)
 logoskg_status fold_visited(logoskg_result *r, int upto, hipStream_t st);
