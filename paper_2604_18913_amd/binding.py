@@ -168,6 +168,8 @@ def _torch():
 def _dev_tensor(x, dtype, device):
     torch = _torch()
     if isinstance(x, torch.Tensor):
+        if x.dtype is dtype and x.device == device and x.is_contiguous():
+            return x
         return x.to(device=device, dtype=dtype).contiguous()
     return torch.from_numpy(np.ascontiguousarray(x).astype(_NP[dtype], copy=False)).to(device)
 
@@ -180,10 +182,21 @@ def _init_np():
     _NP.update({torch.int32: np.int32, torch.int64: np.int64, torch.uint8: np.uint8})
 
 
+_raw_stream = None  # (device index) -> handle of its current stream; False: this torch does not have it
+
+
 def _stream_handle(stream) -> int:
+    """The stream's handle, or that of torch's current one.  The raw handle without a Stream object around it: 0.2 instead
+    of 2.9 us, of which a question to a small graph (two calls, 60 us) pays two."""
+    global _raw_stream
+    if stream is not None:
+        return int(stream.cuda_stream)
     torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return int(s.cuda_stream)
+    if _raw_stream is None:
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", False) if hasattr(torch._C, "_cuda_getDevice") else False
+    if _raw_stream and torch.cuda.is_initialized():
+        return _raw_stream(torch._C._cuda_getDevice())
+    return int(torch.cuda.current_stream().cuda_stream)
 
 
 class Result:
