@@ -344,10 +344,8 @@ k_census_lists(const uint32_t *__restrict__ act, int32_t E, const uint32_t *__re
             const int32_t e = (int32_t)(e0 + i);
             if (d[i] > 0 && d[i] <= (uint32_t)kTailMaxDegree) list_tail[bt++] = e;
             const unsigned n = segments_of(d[i]);
-            if (n) {
-                const uint32_t lo = out_off[e];
-                for (unsigned x = 0; x < n; ++x) list_seg[bs++] = RowSegment{e, lo + x * kPushSegment};
-            }
+            if (wave_any(n != 0)) write_segments(list_seg, bs, n, e, n ? out_off[e] : 0u);
+            bs += n;
         }
         __syncthreads();  // (the counts are rewritten by the next turn)
     }

@@ -149,13 +149,36 @@ __device__ __forceinline__ void write_listed(uint32_t u, long long first, long l
     }
 }
 
+// SUM: the chunks' counts are still that, and a block adds up those before its own (instead of a launch of k_active_scan
+// between: 4 us and its gap).  What the blocks read together grows with the square of the graph, so it ends at kActSumChunks.
+constexpr long long kActSumChunks = 16384;  // 33M entities: 0.3 GB through the L2s
+
+template <bool SUM>
 __global__ void __launch_bounds__(256)
 k_active_fill(const uint32_t *__restrict__ act, long long actw, int levels, long long nchunks,
-              const uint32_t *__restrict__ chunk_base, int32_t *tile_ent, int32_t *cpos) {
-    const long long chunk = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+              const uint32_t *__restrict__ chunk_base, unsigned long long *n_active, int32_t *tile_ent, int32_t *cpos) {
+    __shared__ uint32_t part[4];
+    const int wave = threadIdx.x >> 6;
+    const long long chunk0 = (long long)blockIdx.x * 4, chunk = chunk0 + wave, first = chunk * kActChunkWords;
+    const uint32_t mine = active_word(act, actw, levels, first + lane());  // (0 behind the last chunk)
+    long long at = 0;
+    if constexpr (SUM) {
+        uint32_t sum = 0;
+        for (long long i = threadIdx.x; i < chunk0; i += 256) sum += chunk_base[i];
+        sum = (uint32_t)wave_sum(sum);
+        if (lane() == 0) part[wave] = sum;
+        __syncthreads();
+        at = (long long)part[0] + part[1] + part[2] + part[3];
+        for (long long c = chunk0; c < min(chunk, nchunks); ++c) at += chunk_base[c];
+        if (blockIdx.x + 1 == gridDim.x && wave == 3) {  // behind this block's last chunk
+            const long long end = at + (chunk < nchunks ? chunk_base[chunk] : 0u);
+            if (lane() == 0) *n_active = (unsigned long long)end;
+            tile_ent[end + lane()] = -1;
+        }
+    }
     if (chunk >= nchunks) return;
-    const long long first = chunk * kActChunkWords;
-    write_listed(active_word(act, actw, levels, first + lane()), first, (long long)chunk_base[chunk], tile_ent, cpos);
+    if constexpr (!SUM) at = chunk_base[chunk];
+    write_listed(mine, first, at, tile_ent, cpos);
 }
 
 // The three in one launch: a block (a thread per bitmap word) counts what lies before it by itself.  The blocks' common
@@ -2319,8 +2342,12 @@ static logoskg_status ensure_active_list(logoskg_result *r, hipStream_t st) {
     }
     const unsigned nb = (unsigned)((nchunks + 3) / 4);
     k_active_count<<<dim3(nb), dim3(256), 0, st>>>(r->act, actw, r->k + 1, nchunks, r->act_chunk);
-    k_active_scan<<<dim3(1), dim3(1024), 0, st>>>(nchunks, r->act_chunk, r->d_nact, r->tile_ent);
-    k_active_fill<<<dim3(nb), dim3(256), 0, st>>>(r->act, actw, r->k + 1, nchunks, r->act_chunk, r->tile_ent, r->cpos);
+    if (nchunks <= kActSumChunks) {
+        k_active_fill<true><<<dim3(nb), dim3(256), 0, st>>>(r->act, actw, r->k + 1, nchunks, r->act_chunk, r->d_nact, r->tile_ent, r->cpos);
+    } else {
+        k_active_scan<<<dim3(1), dim3(1024), 0, st>>>(nchunks, r->act_chunk, r->d_nact, r->tile_ent);
+        k_active_fill<false><<<dim3(nb), dim3(256), 0, st>>>(r->act, actw, r->k + 1, nchunks, r->act_chunk, r->d_nact, r->tile_ent, r->cpos);
+    }
     LKG_HIP(hipGetLastError());
     return LOGOSKG_OK;
 }

@@ -222,11 +222,7 @@ k_route_lists(const uint32_t *__restrict__ act, int32_t E, const uint32_t *__res
             const unsigned long long at = first[0][s0] + (unsigned)__shfl((int)bt, leader);
             const unsigned long long as = first[1][s0] + (unsigned)__shfl((int)bs, leader);
             if (mine && tail) list_tail[at + __popcll(tmask & ((1ull << lane()) - 1ull))] = (int32_t)e;
-            if (mine && segs) {
-                const uint32_t lo = row_begin[e];
-                for (int i = 0; i < segs; ++i)
-                    list_seg[as + ps + i] = RowSegment{(int32_t)e, lo + (uint32_t)i * kPushSegment};
-            }
+            write_segments(list_seg, as + ps, mine ? (unsigned)segs : 0u, (int32_t)e, mine && segs ? row_begin[e] : 0u);
         });
     }
 }
