@@ -78,8 +78,7 @@ k_allow(int Q, int R, int W, int rel_words, const unsigned long long *__restrict
     if (r < R) allow[(size_t)r * W + w] = x;
 }
 
-// A hop pulls when more than a twelfth of the triples leave its frontier, and is dense from kDensePullPercent of them.
-__host__ __device__ inline bool pull_rule(long long edges, long long T) { return edges * 12 > T; }
+// A hop is dense from kDensePullPercent of the triples leaving its frontier; from how many of them it pulls: push_most().
 __host__ __device__ inline bool dense_rule(long long edges, long long T) { return edges * 100 >= T * kDensePullPercent; }
 
 // ---------------------------------------------------------------- frontier census
@@ -167,7 +166,7 @@ template <int LW, bool PULLED>
 __global__ void __launch_bounds__(LW ? 512 : 1024)
 k_census(uint32_t *act, int32_t E, const uint32_t *__restrict__ out_off, unsigned long long *ctr,
          unsigned long long *sums, unsigned long long *host, const unsigned long long *__restrict__ lines,
-         unsigned long long *live, const unsigned long long *go, long long T, int Q) {
+         unsigned long long *live, const unsigned long long *go, long long T, long long push_most, int Q) {
     if constexpr (PULLED)
         if (go && *go == kHopNotPulled) return;  // launched ahead for a hop that is not taken this way
     static_assert(!PULLED || LW > 0, "16-word lines are not read for their bits");
@@ -296,7 +295,7 @@ k_census(uint32_t *act, int32_t E, const uint32_t *__restrict__ out_off, unsigne
     host[C_NACTIVE] = rows >> 32;
     host[C_FEDGES] = edges = total(2);
     host[C_ERR] = __hip_atomic_load(&ctr[L_ERR], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if constexpr (LW > 0) ctr[L_PULL] = !pull_rule((long long)edges, T) ? kHopNotPulled : dense_rule((long long)edges, T) ? kHopPulledDense : kHopPulled;
+    if constexpr (LW > 0) ctr[L_PULL] = (long long)edges <= push_most ? kHopNotPulled : dense_rule((long long)edges, T) ? kHopPulledDense : kHopPulled;
     __threadfence_system();
     __hip_atomic_store(&host[kCensusDone], 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
@@ -1234,6 +1233,22 @@ static inline unsigned blocks_for(long long threads, int block) {
     return (unsigned)((threads + block - 1) / block);
 }
 
+// Most triples that may leave the frontier of a hop that pushes (direction by rule).  A twelfth of all where a pulled hop is three
+// kernels over whole lines.  On planes of one and four words it is one kernel, which without whitelists takes 1 ns per 25 triples
+// of the graph and more where the planes leave the caches, against two launches more and 0.4 ns per triple of the frontier for a
+// push: the times cross at 5,000 .. 10,000 triples of 3.4M, 50,000 .. 100,000 of 10M, 700,000 .. 900,000 of 30M
+// (one to 200 questions; 200 on 3.4M with 99,000 triples in the frontier: pushed 110 us, pulled 59), which is the square of the
+// graph's triples over 2^30.  Under whitelists most triples push nothing (the same: 72 and 67), and only four-word planes of
+// small graphs gain (0.8M: 70 and 59, 10M: 74 and 103).  Below kFewTriples searches hardly leave k_small_search.
+constexpr long long kFewTriples = 1 << 18, kMaskedPullTriples = 1 << 22;
+
+static long long push_most(const logoskg_graph *g, const logoskg_result *r) {
+    const long long T = g->T, twelfth = T / 12;
+    if (r->W == 16 || g->num_shards > 1 || T < kFewTriples) return twelfth;
+    if (r->has_mask) return r->W == 4 && T <= kMaskedPullTriples ? 0 : twelfth;
+    return std::min(twelfth, T * T >> 30);  // (T < 2^31)
+}
+
 static unsigned long long *level_counters(const logoskg_result *r, int h) {
     return r->live + (size_t)16 * (r->k + 1) + (size_t)kLevelCounters * h;
 }
@@ -1499,7 +1514,7 @@ static logoskg_status launch_census(logoskg_graph *g, logoskg_result *r, int h, 
         kernel<<<dim3(nb), dim3((unsigned)threads), 0, st>>>(r->act + (size_t)(r->Epad / 32) * h, g->E, g->out_off,
                                                              level_counters(r, h), g->d_ctr + C_TOTAL, host,
                                                              r->levels + (size_t)r->Epad * r->W * h, r->live + (size_t)16 * h,
-                                                             go, (long long)g->T, g->prof.counters ? 0 : r->Q);
+                                                             go, (long long)g->T, push_most(g, r), g->prof.counters ? 0 : r->Q);
     };
     if (r->W == 16) launch(k_census<0, false>, 1024, kCensusEntities);
     else if (pulled) launch(r->W == 1 ? k_census<1, true> : k_census<4, true>, 512, 4);
@@ -1548,7 +1563,7 @@ logoskg_status count_reached(logoskg_result *r, hipStream_t st);  // result.hip
 // The hops of a narrow batch on a resident graph (direction by rule).  The host needs each level's counters to choose the
 // next hop's direction, and on a graph of a few million triples a hop is 20 us of kernels, about what a wait, a
 // launch and the GPU's way back to work take.  Behind a pulled hop, whose successor nearly always pulls as well, the next
-// one is therefore launched before its turn is known: the census leaves its decision on the device (pull_rule, dense_rule:
+// one is therefore launched before its turn is known: the census leaves its decision on the device (push_most, dense_rule:
 // the host's own), and kernels launched ahead of a hop that is not pulled return at once (about 4 us).  The last level's
 // counters, which only feed the statistics, are read behind the counts of the lists.  `pending`: that is still to be done.
 static logoskg_status narrow_hops(logoskg_graph *g, logoskg_result *r, int first_hop, bool *pending, hipStream_t st) {
@@ -1562,7 +1577,7 @@ static logoskg_status narrow_hops(logoskg_graph *g, logoskg_result *r, int first
         hs.active_rows = (long long)hc[C_NROWS];
         hs.frontier_edges = (long long)hc[C_FEDGES];
         hs.shards_touched = 1;
-        const bool pull = pull_rule(hs.frontier_edges, g->T);
+        const bool pull = hs.frontier_edges > push_most(g, r);
         hs.direction = pull ? LOGOSKG_DIR_PULL : LOGOSKG_DIR_PUSH;
         if (!pull) hs.edges_scanned = hs.lines_gathered = hs.frontier_edges;
         if (!running) {
@@ -1587,7 +1602,7 @@ static logoskg_status narrow_hops(logoskg_graph *g, logoskg_result *r, int first
         LKG_TRY(await_census(slot(h), st));
         memcpy(hc, slot(h), C_STATS * sizeof(hc[0]));
         hs.entities_reached = (long long)hc[C_NACTIVE];
-        running = ahead && pull_rule((long long)hc[C_FEDGES], g->T);
+        running = ahead && (long long)hc[C_FEDGES] > push_most(g, r);
     }
     return LOGOSKG_OK;
 }
@@ -1740,7 +1755,7 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
         if (rows == 0) break;  // nothing can be reached any more: the remaining levels stay empty
         hs.active_rows = rows;
         hs.frontier_edges = fedges;
-        const bool pull = dir == LOGOSKG_DIR_PULL || (dir == LOGOSKG_DIR_AUTO && pull_rule(fedges, g->T));
+        const bool pull = dir == LOGOSKG_DIR_PULL || (dir == LOGOSKG_DIR_AUTO && fedges > push_most(g, r));
         hs.direction = pull ? LOGOSKG_DIR_PULL : LOGOSKG_DIR_PUSH;
         unsigned long long hc[C_TOTAL] = {};
         memcpy(hc, g->h_ctr, C_STATS * sizeof(hc[0]));
