@@ -520,12 +520,41 @@ k_push_seg(const RowSegment *__restrict__ segs, const unsigned long long *__rest
     }
 }
 
+// The first hop of 16-word planes: pairs that are seeds leave its level, and so do active bits of lines that held nothing
+// else.  Only an entity that is active in both levels can hold one, of which there are as many as seeds: a thread per 64
+// entities reads their two bitmap words.  (With visited kept as on narrow planes, 11M lines of 20M entities were read twice
+// and written: 514 us, 24 us now, and as many lines less to clear.)
+__global__ void __launch_bounds__(256)
+k_drop_seeds(long long words, const uint32_t *__restrict__ act0, uint32_t *act1, const unsigned long long *__restrict__ level0,
+             unsigned long long *level1) {
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (i >= words) return;
+    unsigned long long *const bits = reinterpret_cast<unsigned long long *>(act1) + i;
+    const unsigned long long was = *bits;
+    unsigned long long gone = 0;
+    for (unsigned long long m = was & reinterpret_cast<const unsigned long long *>(act0)[i]; m; m &= m - 1) {
+        const int b = __ffsll((long long)m) - 1;
+        const ulonglong2 *seeds = reinterpret_cast<const ulonglong2 *>(level0 + ((size_t)i * 64 + b) * 16);
+        ulonglong2 *line = reinterpret_cast<ulonglong2 *>(level1 + ((size_t)i * 64 + b) * 16);
+        unsigned long long any = 0;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) {
+            const ulonglong2 x = line[w], y = seeds[w];
+            const ulonglong2 z = make_ulonglong2(x.x & ~y.x, x.y & ~y.y);
+            if (z.x != x.x || z.y != x.y) line[w] = z;
+            any |= z.x | z.y;
+        }
+        if (any == 0) gone |= 1ull << b;
+    }
+    if (gone) *bits = was & ~gone;
+}
+
 // visited |= level[h] on the lines the push kernels touched.
 // One wavefront per 64 entities: it reads their two words of the active bitmap once and touches
 // only the lines of the active ones (after a push from a small frontier almost none), W lanes per
 // line, so a dense level is still updated with contiguous accesses.
-// FIRST: the hop has set bits without asking visited; those that were there (the seeds) leave the level, and so do lines
-// and active bits that held nothing else.
+// FIRST (narrow planes): the hop has set bits without asking visited; those that were there (the seeds) leave the level, and
+// so do lines and active bits that held nothing else.
 template <int W, bool FIRST>
 __global__ void __launch_bounds__(256)
 k_update_visited(long long Epad, uint32_t *act_cur, unsigned long long *cur, unsigned long long *visited) {
@@ -1301,6 +1330,10 @@ static void launch_push(logoskg_graph *g, logoskg_result *r, int h, const unsign
     if (!update || (W == 16 && r->walk_exact)) return;  // (walk-exact levels ask for nothing that was reached)
     ProfScope ps(g->prof, KK_UPDATE, st);
     const dim3 grid(blocks_for(r->Epad / 64, 4)), block(256);
+    if (W == 16 && !known) {
+        k_drop_seeds<<<dim3(blocks_for((long long)(r->Epad / 64), 256)), block, 0, st>>>(r->Epad / 64, r->act, act_cur, r->levels, cur);
+        return;
+    }
     if (known) k_update_visited<W, false><<<grid, block, 0, st>>>(r->Epad, act_cur, cur, r->visited);
     else k_update_visited<W, true><<<grid, block, 0, st>>>(r->Epad, act_cur, cur, r->visited);
 }
@@ -1778,7 +1811,7 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
             KH(hipGetLastError());
         }
         r->n_levels = h + 1;
-        if (W == 16 && !walk_exact && !pull) r->vis_levels = r->vis_dirty = h + 1;
+        if (W == 16 && !walk_exact && !pull && h > 1) r->vis_levels = r->vis_dirty = h + 1;
         if (h == k && !want_stats) {  // (its counters only feed the statistics: read behind the counts)
             census_slot(g, h)[kCensusDone] = 0;
             if ((s = launch_census(g, r, h, pull, census_slot(g, h), nullptr, st)) != LOGOSKG_OK) return fail(s);
