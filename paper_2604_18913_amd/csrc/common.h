@@ -457,6 +457,7 @@ struct Seen {
     const uint32_t *act;
     long long plane, actw;
     int gate, first, last;
+    bool sure;  // most rows are active in the last level: its lines (zero elsewhere) are read without asking
 };
 
 __device__ __forceinline__ bool active_in(const Seen &s, int level, int e) {

@@ -766,9 +766,8 @@ constexpr int kTailRows = 2;
 constexpr int kTailLines = 2;  // candidate lines of each row requested together
 
 // Word lw of what has reached the entities v[0 .. N - 1].  The bits of the base and of two levels, then the lines that they
-// ask for, are requested for all of them together.  DENSE: nearly every entity is active in the last level, whose lines
-// (zero elsewhere) are read without asking.
-template <int N, bool DENSE>
+// ask for, are requested for all of them together.
+template <int N>
 __device__ __forceinline__ void seen_words(const Seen &s, const int (&v)[N], const bool (&have)[N], int lw, unsigned long long (&x)[N]) {
     constexpr int W = 16, L = 2;
     bool base[N];
@@ -784,7 +783,7 @@ __device__ __forceinline__ void seen_words(const Seen &s, const int (&v)[N], con
         for (int i = 0; i < L; ++i)
 #pragma unroll
             for (int r = 0; r < N; ++r)
-                on[r][i] = have[r] && l0 + i < s.last && ((DENSE && l0 + i == s.last - 1) || active_in(s, l0 + i, v[r]));
+                on[r][i] = have[r] && l0 + i < s.last && ((s.sure && l0 + i == s.last - 1) || active_in(s, l0 + i, v[r]));
 #pragma unroll
         for (int r = 0; r < N; ++r) {
             if (base[r]) x[r] |= s.base[(size_t)v[r] * W + lw];
@@ -840,7 +839,7 @@ k_pull_tail(const ShortRow *__restrict__ rows, long long n, const int32_t *__res
         }
     }
     const unsigned long long live_w = live[lw];
-    if constexpr (W == 16) seen_words<NR, DENSE>(seen, v, have, lw, vis);
+    if constexpr (W == 16) seen_words<NR>(seen, v, have, lw, vis);
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
         need[r] = (walk_exact ? ~0ull : ~vis[r]) & live_w;
@@ -980,7 +979,7 @@ k_pull_seg(const PullSegment *__restrict__ segs, long long n,
             const int vs[1] = {v};
             const bool all[1] = {true};
             unsigned long long x[1];
-            seen_words<1, DENSE>(seen, vs, all, lw, x);
+            seen_words<1>(seen, vs, all, lw, x);
             vis = x[0];
         }
         need = (walk_exact ? ~0ull : ~vis) & live[lw];
@@ -1286,7 +1285,7 @@ constexpr int kSeenLevels = 5;  // pulled hops in a row: at most so many levels 
 
 Seen seen_levels(const logoskg_result *r, int upto) {
     const int have = std::min(r->vis_levels.load(), upto);
-    return Seen{have ? r->visited : nullptr, r->levels, r->act, r->Epad * (long long)r->W, r->Epad / 32, have <= kSeenGate ? have : 0, have, upto};
+    return Seen{have ? r->visited : nullptr, r->levels, r->act, r->Epad * (long long)r->W, r->Epad / 32, have <= kSeenGate ? have : 0, have, upto, false};
 }
 
 logoskg_status fold_visited(logoskg_result *r, int upto, hipStream_t st) {
@@ -1369,7 +1368,8 @@ static void launch_pull_rows(logoskg_graph *g, logoskg_result *r, int h, const R
     const unsigned long long *live = r->live + (size_t)16 * (h - 1);
     auto stats = [&](int kind) { return STATS ? g->d_ctr + C_STATS + 4 * kind : nullptr; };
     const int walk = r->walk_exact ? 1 : 0;
-    const Seen seen = W == 16 && !walk ? seen_levels(r, h) : Seen{};
+    Seen seen = W == 16 && !walk ? seen_levels(r, h) : Seen{};
+    seen.sure = h > 1 && 2 * r->stats[(size_t)h - 2].entities_reached > (long long)(g->in_rows.n_tail + g->in_rows.n_long);
     if constexpr (W <= 4 && !STATS) {
         if (rc.n_seg + rc.n_tail == 0) return;
         ProfScope ps(g->prof, KK_PULL_TAIL, st);
