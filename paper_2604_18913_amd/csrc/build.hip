@@ -296,6 +296,16 @@ static logoskg_status row_classes(logoskg_graph *g, const uint32_t *d_off, bool 
     return LOGOSKG_OK;
 }
 
+// The rows of distinct pairs with their work lists, where they are worth their room and there is some.
+static logoskg_status pair_rows(logoskg_graph *g, const int32_t *in_sub, const uint16_t *in_rel, const int32_t *in_eid, Scratch &tmp) {
+    LKG_TRY(build_pairs_on_device(g, in_sub, in_rel, in_eid, tmp));
+    if (g->pairs.off && row_classes(g, g->pairs.off, true, tmp, &g->pairs.rows) != LOGOSKG_OK) {
+        (void)hipGetLastError();  // (the graph works without them)
+        drop_pairs(g);
+    }
+    return LOGOSKG_OK;
+}
+
 }  // namespace lkg
 
 using namespace lkg;
@@ -362,18 +372,13 @@ extern "C" logoskg_status logoskg_build(const int32_t *subj, const int32_t *rel,
         std::unique_ptr<Scratch, void (*)(Scratch *)> scratch(nullptr, scratch_destroy);
         {
             Scratch *x = nullptr;
-            if ((st = scratch_create(g, device_build, &x)) != LOGOSKG_OK) return fail(st);
+            if ((st = scratch_create(g, device_build, g->num_shards <= 1, &x)) != LOGOSKG_OK) return fail(st);
             scratch.reset(x);
         }
         // work lists over the rows of OBJ (pull and predecessor kernels), and the rows of distinct pairs with theirs
         auto object_rows = [&]() -> logoskg_status {
             LKG_TRY(row_classes(g, g->in_off, false, *scratch, &g->in_rows));
-            LKG_TRY(build_pairs_on_device(g, *scratch));
-            if (g->pairs.off && row_classes(g, g->pairs.off, true, *scratch, &g->pairs.rows) != LOGOSKG_OK) {
-                (void)hipGetLastError();  // (the graph works without them)
-                drop_pairs(g);
-            }
-            return LOGOSKG_OK;
+            return pair_rows(g, g->in_sub, g->in_rel, g->in_eid, *scratch);
         };
         auto subject_row_counts = [&]() -> logoskg_status {
             unsigned int n[3];
@@ -397,6 +402,12 @@ extern "C" logoskg_status logoskg_build(const int32_t *subj, const int32_t *rel,
             if ((st = upload(&g->out_off, ooff, &g->static_bytes)) != LOGOSKG_OK) return fail(st);
             if ((st = subject_row_counts()) != LOGOSKG_OK) return fail(st);
             if ((st = build_shards(g, subj, rel, obj, &o, ooff, sorter)) != LOGOSKG_OK) return fail(st);
+            if (pairs_beside_shards(g, &o)) {  // (a cache of everything: its joined arrays are walked like a resident graph's)
+                const int32_t *sub = nullptr, *eid = nullptr;
+                const uint16_t *in_rel = nullptr;
+                sorter_object_arrays(sorter, &sub, &in_rel, &eid);
+                if ((st = pair_rows(g, sub, in_rel, eid, *scratch)) != LOGOSKG_OK) return fail(st);
+            }
         } else {
         // out-degrees are needed by both the resident and the sharded form
         std::vector<uint32_t> ooff((size_t)E + 1, 0);

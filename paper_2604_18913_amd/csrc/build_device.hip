@@ -153,16 +153,17 @@ static logoskg_status pair_sort_bytes(int64_t T, int32_t E, size_t (&bytes)[3]) 
 }
 
 // One block for the temporaries of a resident graph's build: the two sorts' (where they run here), then the distinct pairs'.
-logoskg_status scratch_create(logoskg_graph *g, bool sorts, Scratch **out) {
+logoskg_status scratch_create(logoskg_graph *g, bool sorts, bool pairs, Scratch **out) {
     *out = nullptr;
     std::unique_ptr<Scratch> s(new (std::nothrow) Scratch());
     if (!s) { set_error("out of host memory"); return LOGOSKG_ENOMEM; }
     const int64_t T = g->T;
     size_t csr = 0, pair[3] = {};
     if (sorts) LKG_TRY(csr_sort_bytes(T, g->E, &csr));
-    if (T > 0) LKG_TRY(pair_sort_bytes(T, g->E, pair));
-    const size_t for_sorts = sorts ? (size_t)T * 20 + csr : 0, for_pairs = (size_t)T * 24 + (size_t)g->E * 16 + std::max({pair[0], pair[1], pair[2]});
-    s->reserve(std::max(for_sorts, for_pairs) + 16 * 256);
+    if (pairs && T > 0) LKG_TRY(pair_sort_bytes(T, g->E, pair));
+    const size_t for_sorts = sorts ? (size_t)T * 20 + csr : 0;
+    const size_t for_pairs = pairs ? (size_t)T * 24 + (size_t)g->E * 16 + std::max({pair[0], pair[1], pair[2]}) : 0;
+    if (sorts || pairs) s->reserve(std::max(for_sorts, for_pairs) + 16 * 256);
     *out = s.release();
     return LOGOSKG_OK;
 }
@@ -296,7 +297,7 @@ __global__ void k_pair_fill(const unsigned long long *__restrict__ key, const ui
     }
 }
 
-logoskg_status build_pairs_on_device(logoskg_graph *g, Scratch &tmp) {
+logoskg_status build_pairs_on_device(logoskg_graph *g, const int32_t *in_sub, const uint16_t *in_rel, const int32_t *in_eid, Scratch &tmp) {
     const int64_t T = g->T;
     const int32_t E = g->E;
     if (T == 0) return LOGOSKG_OK;
@@ -332,7 +333,7 @@ logoskg_status build_pairs_on_device(logoskg_graph *g, Scratch &tmp) {
     LKG_HIP(rocprim::radix_sort_pairs_desc(d_tmp, bytes[1], degrees, ids, (size_t)E, 0u, 32u));
     const uint32_t *const by_rank = ids.current();
     k_rank_of<<<per_entity, block>>>(by_rank, E, degrees.current());
-    k_pair_keys<<<per_triple, block>>>(obj_of, g->in_sub, degrees.current(), T, bits, key[0], pos[0]);
+    k_pair_keys<<<per_triple, block>>>(obj_of, in_sub, degrees.current(), T, bits, key[0], pos[0]);
     LKG_HIP(rocprim::radix_sort_pairs(d_tmp, bytes[0], keys, vals, (size_t)T, 0u, 2 * bits));
     uint32_t *const is_new = reinterpret_cast<uint32_t *>(keys.alternate()), *const is_first = is_new + T;
     k_pair_flags<<<per_triple, block>>>(keys.current(), vals.current(), T, is_new, is_first);
@@ -364,8 +365,8 @@ logoskg_status build_pairs_on_device(logoskg_graph *g, Scratch &tmp) {
     g->pairs = p;
     g->static_bytes += all;
     k_pair_rows<<<per_entity, block>>>(g->in_off, E, is_new, p.off);
-    k_pair_fill<<<per_triple, block>>>(keys.current(), is_new, is_first, T, bits, by_rank, g->in_sub, g->in_eid, p.pull_sub,
-                                       p.sub, p.eid, vals.current(), g->in_rel, p.all_sub, p.all_rel);
+    k_pair_fill<<<per_triple, block>>>(keys.current(), is_new, is_first, T, bits, by_rank, in_sub, in_eid, p.pull_sub,
+                                       p.sub, p.eid, vals.current(), in_rel, p.all_sub, p.all_rel);
     LKG_HIP(hipGetLastError());
     LKG_HIP(hipDeviceSynchronize());  // (the scratch goes)
     return LOGOSKG_OK;
@@ -555,6 +556,12 @@ logoskg_status sorter_object_order(TripleSorter *s, int32_t *h_sub, uint16_t *h_
     LKG_HIP(hipMemcpy(h_rel, s->d_r, (size_t)T * 2, hipMemcpyDeviceToHost));
     LKG_HIP(hipMemcpy(h_eid, s->d_b, (size_t)T * 4, hipMemcpyDeviceToHost));
     return LOGOSKG_OK;
+}
+
+void sorter_object_arrays(const TripleSorter *s, const int32_t **sub, const uint16_t **rel, const int32_t **eid) {
+    *sub = s->d_a;
+    *rel = s->d_r;
+    *eid = s->d_b;
 }
 
 // g->out_eid[p] = index of the triple behind entry p of the subject-sorted CSR (SUB's rows, Eq. 1).

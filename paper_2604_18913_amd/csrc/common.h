@@ -540,14 +540,15 @@ struct FillArgs {
 };
 
 struct Scratch;  // a build's device temporaries (build_device.hip)
-logoskg_status scratch_create(logoskg_graph *g, bool sorts, Scratch **out);
+logoskg_status scratch_create(logoskg_graph *g, bool sorts, bool pairs, Scratch **out);
 void scratch_destroy(Scratch *s);
 logoskg_status build_csr_on_device(logoskg_graph *g, const int32_t *subj, const int32_t *rel, const int32_t *obj, Scratch &tmp);
 // rows of a CSR on the device: with an entry, of more than kTailMaxDegree, of at least hub_min
 logoskg_status count_rows_on_device(const uint32_t *d_off, int32_t E, int hub_min, Scratch &tmp, unsigned int (&n)[3]);
 logoskg_status classify_on_device(const uint32_t *d_off, int32_t E, int hub_min, Scratch &tmp, RowClasses *rc, ShortRow **records, std::vector<ShortRow> *longer);
 // g->pairs' arrays (not its work lists) from the object-sorted ones; pairs.off stays NULL where they are not kept
-logoskg_status build_pairs_on_device(logoskg_graph *g, Scratch &tmp);
+// (of the object-sorted triples on the device, rows by g->in_off)
+logoskg_status build_pairs_on_device(logoskg_graph *g, const int32_t *in_sub, const uint16_t *in_rel, const int32_t *in_eid, Scratch &tmp);
 Seen seen_levels(const logoskg_result *r, int upto);
 // khop.hip: visited becomes the OR of the levels below `upto` where it does not hold them yet (a captured launch leaves that open)
 logoskg_status fold_visited(logoskg_result *r, int upto, hipStream_t st);
@@ -558,6 +559,8 @@ void sorter_destroy(TripleSorter *s);
 logoskg_status sorter_offsets(TripleSorter *s, bool by_object, std::vector<uint32_t> *off);
 logoskg_status sorter_subject_order(TripleSorter *s, const uint32_t *d_row_begin, int32_t *h_obj, uint16_t *h_rel);
 logoskg_status sorter_object_order(TripleSorter *s, int32_t *h_sub, uint16_t *h_rel, int32_t *h_eid);
+void sorter_object_arrays(const TripleSorter *s, const int32_t **sub, const uint16_t **rel, const int32_t **eid);  // behind it, on the device
+bool pairs_beside_shards(const logoskg_graph *g, const logoskg_build_opts *opts);  // shards.hip: room for them by the caller's limits
 logoskg_status ensure_out_eid(logoskg_graph *g, hipStream_t st);
 // small.hip: *next_hop = the hop the general path goes on with (k + 1: none), the frontier's counters in g->h_ctr
 logoskg_status small_search(logoskg_graph *g, logoskg_result *r, const logoskg_query_batch *b, bool want_counts,

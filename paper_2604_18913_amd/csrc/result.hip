@@ -2894,7 +2894,7 @@ extern "C" logoskg_status logoskg_result_fetch(logoskg_result *r, int32_t q0, in
     a.reached_off = r->d_reached_off;
     if (pred && W == 16) LKG_TRY(prepare_row_pred(g, st));
     // without whitelists the rows of distinct pairs (where the row buffer is used they need their own index)
-    const bool pairs = !r->has_mask && g->pairs.off && !(pred && W == 16 && g->row_pred && !g->pairs.long_index);
+    const bool pairs = !r->has_mask && g->pairs.off && g->num_shards <= 1 && !(pred && W == 16 && g->row_pred && !g->pairs.long_index);
     const RowClasses &in_rows = pairs ? g->pairs.rows : g->in_rows;
     a.in_off = pairs ? g->pairs.off : g->in_off;
     a.in_sub = pairs ? g->pairs.sub : g->in_sub;

@@ -443,6 +443,15 @@ static logoskg_status build_in_chunks(logoskg_graph *g, ShardSet *ss, const int3
 
 // The work lists over all object ranges when the predecessor pass runs over them in one piece: the cache
 // holds every unit and the row buffer of all long rows stays within its limit.  NULL otherwise.
+// The distinct pairs of a sharded graph: 18 bytes per triple at most, beside a cache that holds everything, unless the caller's
+// limits leave no room for them.
+bool pairs_beside_shards(const logoskg_graph *g, const logoskg_build_opts *opts) {
+    const ShardSet *ss = (const ShardSet *)g->shards;
+    if (!ss || !ss->joined || opts->max_resident_shards > 0) return false;
+    const uint64_t units = ss->slot_edges * 6 * (uint64_t)ss->units();  // (as the budget counts them)
+    return opts->hbm_shard_budget_bytes == 0 || units + 18 * (uint64_t)g->T <= opts->hbm_shard_budget_bytes;
+}
+
 const RowClasses *joined_rows(const logoskg_graph *g) {
     const ShardSet *ss = (const ShardSet *)g->shards;
     if (!ss || !ss->joined || (size_t)ss->all_rows.n_long * 4096 > kRowPredBytes) return nullptr;
@@ -514,6 +523,14 @@ logoskg_status sharded_pred(logoskg_graph *g, FillArgs *a, int W, bool mask, hip
         x.in_rel = ss->all_in_rel;
         x.rows = all->longrows;
         x.row_base = 0;
+        if (!mask && g->pairs.off && (g->pairs.long_index || !x.row_pred)) {  // as on a resident graph
+            all = &g->pairs.rows;
+            x.in_off = g->pairs.off;
+            x.in_sub = g->pairs.sub;
+            x.in_eid = g->pairs.eid;
+            x.rows = all->longrows;
+            x.long_index = g->pairs.long_index;
+        }
         set_row_segments(&x, *all);
         launch_pred(g->prof, x, W, all->n_hub, all->n_long - all->n_hub, mask, st, st);
         return LOGOSKG_OK;
@@ -888,7 +905,9 @@ static logoskg_status run_sharded_pull(logoskg_graph *g, ShardSet *ss, logoskg_r
             LKG_TRY(acquire(g, ss, ss->range_unit(order[i]), st, &slot_of[i]));
             LKG_HIP(hipStreamWaitEvent(st, ss->slot_ready[slot_of[i]], 0));
         }
-        launch_pull_range(g, r, h, ss->all_rows, ss->all_sub, ss->all_in_rel, hc, want_stats, true, st);
+        if (!g->pairs.off) launch_pull_range(g, r, h, ss->all_rows, ss->all_sub, ss->all_in_rel, hc, want_stats, true, st);
+        else if (r->has_mask) launch_pull_range(g, r, h, ss->all_rows, g->pairs.all_sub, g->pairs.all_rel, hc, want_stats, true, st);
+        else launch_pull_range(g, r, h, g->pairs.rows, g->pairs.pull_sub, nullptr, hc, want_stats, true, st);
         LKG_HIP(hipGetLastError());
         return LOGOSKG_OK;
     }

@@ -43,7 +43,7 @@ def test_parallel_triples(Q, k, share):
     E, R = 12_000, 30
     s, r, o = parallel_graph(rng, E, R, (1, 31, 32, 33, 64, 65, 1023, 1024, 1025, 2047, 2049, 8191, 8192, 9000), 20_000, share)
     off, seeds = seed_lists([rng.integers(0, E, 1 + q % 3) for q in range(Q)])
-    for opts in ({}, {"host_build": True, "hub_min_degree": 60}):
+    for opts in ({}, {"host_build": True, "hub_min_degree": 60}, {"num_shards": 3}, {"num_shards": 3, "max_resident_shards": 2}):
         g = lkg.Graph(s, r, o, E, R, **opts)
         compare(g, E, s, r, o, off, seeds, k)
         res = g.khop(off, seeds, 2, direction="pull")
