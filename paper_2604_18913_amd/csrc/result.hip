@@ -1856,6 +1856,17 @@ __device__ __forceinline__ void emit_word_pooled(const FillArgs &a, const uint32
     }
 }
 
+// inclusive maximum over the lanes up to each one (values of at least 0)
+__device__ __forceinline__ int wave_max_scan(int x) {
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));  // row_shr 1, 2, 4, 8: within sixteen lanes
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));  // the last lane of rows 0 and 2 to rows 1 and 3
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));  // lane 31 to the upper half
+    return x;
+}
+
 __global__ void __launch_bounds__(kEmitTiles * 64) __attribute__((amdgpu_waves_per_eu(8, 8)))
 k_pred_emit(FillArgs a, const unsigned long long *__restrict__ planes, long long tile0, long long ntile, int w0, int nw,
             int eid_cap, int line_cap) {
@@ -1928,14 +1939,33 @@ k_pred_emit(FillArgs a, const unsigned long long *__restrict__ planes, long long
     const bool staged = total <= eid_cap;  // block-uniform
     int *const eid_tab = pool, *const rp_tab = pool + (staged ? total : 0);
     const bool lined = lines <= line_cap && lines * 64 + (staged ? total : 0) <= kEmitPool;
-    if (staged)  // eight entries of the lane's row are requested before the first is stored (the last one again behind it)
-        for (int i0 = 0; i0 < n_stage; i0 += 8) {
-            int e[8];
+    if (staged && wtot > 0) {  // wavefront-uniform
+        // Lane = entry of the wavefront's rows one behind the other, which lie so in memory as well, but for long rows
+        // and entities that were not reached between them.  Every row leaves its lane at its first place, the largest one
+        // so far is the row a place belongs to.  (Every lane its own row was a gather of 64 lines per entry of the longest.)
+        int *const tab = eid_tab + __builtin_amdgcn_readfirstlane(off);  // (lane 0's prefix: where the wavefront begins)
+        const int mine = off - __builtin_amdgcn_readfirstlane(off);
+        for (int i = v; i < wtot; i += 64) tab[i] = 0;
+        __builtin_amdgcn_wave_barrier();
+        if (n_stage > 0) tab[mine] = v + 1;
+        __builtin_amdgcn_wave_barrier();
+        int before = 0;
+        for (int i0 = 0; i0 < wtot; i0 += 256) {
+            int e[4];
 #pragma unroll
-            for (int x = 0; x < 8; ++x) e[x] = a.in_eid[wlo + min(i0 + x, n_stage - 1)];
+            for (int x = 0; x < 4; ++x) {
+                const int i = i0 + 64 * x + v;
+                const int row = max(before, wave_max_scan(i < wtot ? tab[i] : 0));
+                before = __builtin_amdgcn_readlane(row, 63);
+                e[x] = __shfl((int)wlo - mine, row - 1) + i;
+            }
 #pragma unroll
-            for (int x = 0; x < 8; ++x) eid_tab[off + min(i0 + x, n_stage - 1)] = e[x];
+            for (int x = 0; x < 4; ++x) e[x] = i0 + 64 * x + v < wtot ? a.in_eid[(uint32_t)e[x]] : 0;
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                if (i0 + 64 * x + v < wtot) tab[i0 + 64 * x + v] = e[x];
         }
+    }
     // the row_pred values of this word: 64 queries x the wavefront's entities of that kind, eight
     // lines requested together (lanes = queries)
     if (lined) {
