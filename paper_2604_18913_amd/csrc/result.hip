@@ -560,7 +560,7 @@ __device__ __forceinline__ long long super_start(const FillArgs &a, long long st
 // keeps its word of all the block's tiles in registers (visited and the bit-sliced hop
 // number), and for one query at a time compacts the reached entities into LDS,
 // then streams them out with full-width stores.
-// NB = words of the bit-sliced hop number (0: entity ids only); TILES = tiles per block
+// NB = words of the bit-sliced hop number (0: entity ids only, planes of 1 and 4 words: see k_word_lists); TILES = tiles per block
 // (launch_lists_w), at most half a super tile on 16-word planes, where the registers of a whole one
 // would not leave room for two blocks per CU.
 template <int W, int NB, int TILES>
@@ -2489,6 +2489,49 @@ logoskg_status prepare_row_pred(logoskg_graph *g, hipStream_t st) {
     return LOGOSKG_OK;
 }
 
+// Entity lists of 16-word planes without hop numbers (level lists among them): a block = 16 tiles x one word of the range, a
+// wavefront per tile, lane = entity, as k_pred_emit writes its lists.  A wavefront per word of the whole line left fourteen of
+// sixteen idle where a page holds two words, and its compaction in LDS and three accesses there per entry were more than what
+// unaligned pieces cost (a level page of 96 of 1,024 queries on 30M triples: 115 us, 67 so).  Bound by the number of stores.
+constexpr int kWordTiles = 16;
+
+__global__ void __launch_bounds__(kWordTiles * 64) __attribute__((amdgpu_waves_per_eu(8, 8)))
+k_word_lists(FillArgs a, int w0, int nw) {
+    constexpr int Qp = 1024;
+    __shared__ unsigned long long s_live;
+    const long long L = xcd_contiguous(blockIdx.x, gridDim.x), nsup = (a.ntiles + kWordTiles - 1) / kWordTiles;
+    if (L >= nsup * nw) return;  // block-uniform
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), v = lane(), w = w0 + (int)(L % nw), ql = w * 64 + v;
+    const long long at = (L / nw) * kWordTiles + wave, tile = min(at, a.ntiles - 1);
+    if (threadIdx.x == 0) s_live = 0ull;
+    // what depends on nothing is requested together: the entities, and where query 64 w + v goes on (lane = query)
+    const int32_t ew = (int32_t)tile_entity(a.tile_ent, tile, v, a.E);
+    const long long pos = super_start(a, tile / kSuperTiles, Qp, ql) + a.tile_base[(size_t)tile * Qp + ql];
+    const uint32_t pos_lo = (uint32_t)(unsigned long long)pos, pos_hi = (uint32_t)((unsigned long long)pos >> 32);
+    const unsigned long long vis = at < a.ntiles && ew >= 0 ? a.visited[(size_t)ew * 16 + w] & range_bits(a.q0, a.q1, w) : 0ull;
+    const unsigned long long mine = wave_or64(vis);
+    __syncthreads();
+    if (v == 0 && mine) atomicOr(&s_live, mine);
+    __syncthreads();
+    const unsigned long long live = uniform64(s_live);
+    if (live == 0ull) return;  // block-uniform
+    const uint32_t lo = (uint32_t)vis, hi = (uint32_t)(vis >> 32);
+#pragma unroll
+    for (int qq = 0; qq < 64; ++qq) {
+        if (bit_of(live, qq)) {
+            const bool bit = ((qq < 32 ? lo : hi) >> (qq & 31)) & 1u;
+            const unsigned long long m = __ballot(bit);
+            const unsigned long long base = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)pos_hi, qq) << 32) |
+                                            (uint32_t)__builtin_amdgcn_readlane((int)pos_lo, qq);
+            if (bit) {
+                int32_t *const pe = a.entity + base;
+                pe[rank_in(m)] = ew;
+            }
+        }
+        if ((qq & 7) == 7) __builtin_amdgcn_s_barrier();  // the tiles write their pieces of a query about together
+    }
+}
+
 template <int W, int TILES>
 static void launch_lists_t(Profiler &prof, const FillArgs &a, hipStream_t st) {
     const long long nblocks = (a.ntiles + TILES - 1) / TILES;
@@ -2496,7 +2539,7 @@ static void launch_lists_t(Profiler &prof, const FillArgs &a, hipStream_t st) {
     int nb = 1;
     while ((1 << nb) <= a.k) ++nb;
     dim3 grid((unsigned)nblocks), block(64 * W);
-    if (!a.hop) k_lists<W, 0, TILES><<<grid, block, 0, st>>>(a);
+    if (W < 16 && !a.hop) k_lists<W, W < 16 ? 0 : 2, TILES><<<grid, block, 0, st>>>(a);
     else if (nb <= 2) k_lists<W, 2, TILES><<<grid, block, 0, st>>>(a);
     else if (nb <= 4) k_lists<W, 4, TILES><<<grid, block, 0, st>>>(a);
     else k_lists<W, 8, TILES><<<grid, block, 0, st>>>(a);
@@ -2520,6 +2563,16 @@ constexpr long long kListsWaves = 8192;
 template <int W>
 static void launch_lists_w(Profiler &prof, const FillArgs &a, hipStream_t st) {
     constexpr int most = W == 16 ? kSuperTiles / 2 : W == 4 ? kSuperTiles : 4;
+    if constexpr (W == 16) {
+        if (!a.hop) {
+            if (a.ntiles == 0) return;
+            ProfScope ps(prof, KK_LISTS, st);
+            const int w0 = a.q0 / 64, nw = (a.q1 - 1) / 64 - w0 + 1;
+            const long long blocks = (a.ntiles + kWordTiles - 1) / kWordTiles * nw;
+            k_word_lists<<<dim3((unsigned)((blocks + 7) / 8 * 8)), dim3(kWordTiles * 64), 0, st>>>(a, w0, nw);
+            return;
+        }
+    }
     if (a.ntiles * W <= kListsWaves) launch_lists_t<W, 1>(prof, a, st);
     else if (a.ntiles * W <= 4 * kListsWaves) launch_lists_t<W, 4>(prof, a, st);
     else launch_lists_t<W, most>(prof, a, st);
