@@ -431,22 +431,6 @@ __device__ __forceinline__ unsigned long long query_bits(int Q, int w) {
     return (1ull << (Q - lo)) - 1ull;
 }
 
-// The segments of the lanes' subject rows (n of them from edge lo on; 0: none) to out[at ..].  Called by a whole wavefront, which
-// writes the many segments of a hub row together: listed by one lane, those of 200,000 edges were 40 us.
-__device__ __forceinline__ void write_segments(RowSegment *out, unsigned long long at, unsigned n, int32_t row, uint32_t lo) {
-    constexpr unsigned kAlone = 4;
-    if (n <= kAlone)
-        for (unsigned x = 0; x < n; ++x) out[at + x] = RowSegment{row, lo + x * (uint32_t)kPushSegment};
-    for (unsigned long long m = __ballot(n > kAlone); m; m &= m - 1) {
-        const int from = __ffsll((long long)m) - 1;
-        const unsigned long long to = shfl64(at, from);
-        const unsigned all = (unsigned)__shfl((int)n, from);
-        const int32_t r = __shfl(row, from);
-        const uint32_t first = (uint32_t)__shfl((int)lo, from);
-        for (unsigned x = (unsigned)lane(); x < all; x += 64) out[to + x] = RowSegment{r, first + x * (uint32_t)kPushSegment};
-    }
-}
-
 // Where a kernel on 16-word planes finds what the queries have reached so far: a line of `base` where the entity is active in
 // one of the first `gate` levels (0: everywhere; base NULL: nowhere), and of the levels first .. last - 1 where it is
 // active there.  Pulled hops that kept the visited plane read and wrote a line of it per object row, for rows that most
@@ -483,6 +467,22 @@ inline void launch_ranges(long long n, long long per_block, Launch launch, long 
 }
 
 inline int words_for_queries(int Q) { return Q <= 64 ? 1 : (Q <= 256 ? 4 : 16); }
+
+// The segments of the lanes' subject rows (n of them from edge lo on; 0: none) to out[at ..].  Called by a whole wavefront, which
+// writes the many segments of a hub row together: listed by one lane, those of 200,000 edges were 40 us.
+__device__ __forceinline__ void write_segments(RowSegment *out, unsigned long long at, unsigned n, int32_t row, uint32_t lo) {
+    constexpr unsigned kAlone = 4;
+    if (n <= kAlone)
+        for (unsigned x = 0; x < n; ++x) out[at + x] = RowSegment{row, lo + x * (uint32_t)kPushSegment};
+    for (unsigned long long m = __ballot(n > kAlone); m; m &= m - 1) {
+        const int from = __ffsll((long long)m) - 1;
+        const unsigned long long to = shfl64(at, from);
+        const unsigned all = (unsigned)__shfl((int)n, from);
+        const int32_t r = __shfl(row, from);
+        const uint32_t first = (uint32_t)__shfl((int)lo, from);
+        for (unsigned x = (unsigned)lane(); x < all; x += 64) out[to + x] = RowSegment{r, first + x * (uint32_t)kPushSegment};
+    }
+}
 
 // arguments of the list / predecessor kernels (result.hip)
 struct FillArgs {
