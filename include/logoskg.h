@@ -122,7 +122,12 @@ typedef struct {
     int32_t hub_min_degree;
     int64_t num_out_rows, num_out_hubs; /* subjects with >= 1 triple / in the hub class */
     int64_t num_in_rows, num_in_hubs;   /* objects  with >= 1 triple / in the hub class */
-    int64_t device_bytes;               /* HBM held by the graph (CSR, lists, shard cache) */
+    int64_t device_bytes;               /* HBM held by the graph (CSR, lists, shard cache; where
+                                           parallel triples are a tenth and more of all and there is
+                                           room also the object rows without them: 12 bytes per
+                                           distinct (subject, object) pair, 6 per triple; beside a
+                                           sharded graph's cache only when that is uncapped or its
+                                           budget holds them too)                          */
     int64_t pinned_host_bytes;          /* pinned host memory held by the shards            */
     int64_t shard_loads, shard_evictions, shard_hits; /* cache counters since build (Sec. 3.4) */
     int64_t shard_bytes_h2d;
@@ -208,7 +213,9 @@ logoskg_status logoskg_prefetch_shards(logoskg_graph *g, const int32_t *shards, 
 
 /* ------------------------------------------------------------------- khop */
 
-#define LOGOSKG_DIR_AUTO 0u       /* choose push or pull per hop from the frontier's edge count */
+#define LOGOSKG_DIR_AUTO 0u       /* choose push or pull per hop from the frontier's edge count,
+                                     the number of triples and of queries, and whether whitelists
+                                     are given                                                  */
 #define LOGOSKG_DIR_PUSH 1u       /* always expand from the frontier's subject rows             */
 #define LOGOSKG_DIR_PULL 2u       /* always gather over the object rows                         */
 #define LOGOSKG_DIR_MASK 3u
@@ -268,7 +275,8 @@ typedef struct {
     int64_t active_rows;      /* subjects in the frontier with >= 1 triple                              */
     int64_t frontier_edges;   /* sum of their out-degrees                                               */
     int64_t rows_scanned;     /* pull: object rows visited that were not already complete (profiling on) */
-    int64_t edges_scanned;    /* CSR entries read by the expansion kernels (pull: profiling on)          */
+    int64_t edges_scanned;    /* CSR entries read by the expansion kernels (pull: profiling on; without
+                                 whitelists parallel triples may be read once)                          */
     int64_t lines_gathered;   /* pull: frontier lines read (profiling on); push: edges_scanned, a visited
                                  line per triple at most (the first hop reads none)                     */
     int64_t entities_reached; /* entities with at least one new query bit at this hop                   */

@@ -3,8 +3,8 @@
 // State (paper Sec. 3.3): the query vectors q^(h) of up to 1024 queries are
 // packed entity-major, W uint64 words per entity (bit j%64 of word j/64 =
 // query j).  level[h] holds the bits that become set for the first time at hop
-// h, visited = OR of all levels so far, act[h] has one bit per entity whose
-// level[h] line is non-zero.
+// h, visited = OR of all levels so far (on 16-word planes made when something asks for the plane: see Seen), act[h] has one
+// bit per entity whose level[h] line is non-zero.
 //
 // One hop (Eq. 4, q.SUB.OBJ with the relation whitelist applied to the active
 // triples of Eq. 5) is evaluated in one of two directions:
@@ -13,14 +13,17 @@
 //   pull: for every object row that still misses a query whose frontier is
 //         alive, OR the lines of its subjects that are in the frontier, and
 //         stop as soon as nothing is missing; no atomics on short rows, and
-//         visited is updated in the same kernel.
+//         visited is updated in the same kernel (planes of one and four words)
+//         or the levels themselves are asked what was reached before (16 words).
+//         Without whitelists the rows are those of the distinct (subject,
+//         object) pairs where these are built.
 // Both give the same level[h].  Rows of up to 32 entries are handled by a
 // W-lane group each; longer rows are cut into fixed-size segments, one
 // wavefront per segment, so a 100,000-entry hub spreads over many CUs.
 //
 // With LOGOSKG_WALK_EXACT the visited filter is dropped (Eq. 4 iterated as
 // written): level[h] = image of level[h-1], an entity may be in several levels;
-// visited still collects their union.
+// visited is still their union.
 #include <algorithm>
 
 #include "common.h"
@@ -753,7 +756,7 @@ __device__ __forceinline__ unsigned group_ballot(bool p) {
 }
 
 // Short object rows (<= 32 entries): a W-lane group works on kTailRows rows at
-// once.  A row is a chain of dependent loads (row record -> visited line and
+// once.  A row is a chain of dependent loads (row record -> what has reached the row and its
 // subject ids -> frontier bits -> frontier lines), and with all wavefront
 // slots of a CU taken the kernel is bound by that latency, so the work list carries
 // the row bounds (no look-up in the offsets) and every group keeps
@@ -949,7 +952,7 @@ k_pull_tail(const ShortRow *__restrict__ rows, long long n, const int32_t *__res
 // One wavefront per segment (<= 1024 entries) of a longer object row.  A row
 // with one segment is finished here; segments of a multi-segment row merge
 // through atomicOr on level[h] and look at what the others have found so far
-// to stop early; k_pull_finish then folds those rows into visited.
+// to stop early; k_pull_finish then marks those rows active (and folds them into visited on planes that keep it).
 template <int W, bool MASK, bool STATS, bool DENSE>
 __global__ void __launch_bounds__(256)
 k_pull_seg(const PullSegment *__restrict__ segs, long long n,

@@ -13,7 +13,8 @@
 //   count : per (query, tile) counts -> nested exclusive prefixes -> offsets
 //           (of the visited plane, or of one level plane for the per-level lists)
 //   lists : one block per super tile compacts the (entity, hop) entries of each
-//           query in LDS and writes them as whole 64-lane stores
+//           query in LDS and writes them as whole 64-lane stores; entity lists
+//           of 16-word planes a wavefront per word of a tile, lane = entity
 //   pred  : the predecessor edge (smallest edge id whose subject sits one hop
 //           closer and whose relation the query allows - the first active
 //           triple of Eq. 5-7 in edge-id order) is found by walking the object
@@ -1435,11 +1436,8 @@ __global__ void __launch_bounds__(1024) k_pred(FillArgs a) {
 // kernels: such an entity's predecessors come from row_pred, which those kernels fill before
 // this one starts (or, without that buffer, the row kernels write them to the lists themselves).
 // It waits for memory, short of a copy's rate (4.86 TB/s): a store covers the entities of one tile that one query reached, 55 %
-// and 78 % of its lanes in the two calls that follow.  1.57 ms for 516M pairs of 1,024 queries, 5.9 GB by the counters, 3.8 TB/s (1,663 us with two words per
-// block, a chain of seven dependent loads ahead of the loop and the visited words written and read beside the codes); 2.48 ms for
-// 993M pairs of 64 queries on 20M entities, 11.3 GB, 4.5 TB/s (3,344 us; there the ids of nine entries a row did not fit the
-// half of the LDS that was theirs).  (On the benchmark's graph, 633M pairs, 7.1 GB instead of 8.7, this kernel takes 1.89 ms
-// instead of 1.81 and the walk 0.74 instead of 0.84.)
+// and 78 % of its lanes in the two calls that follow.  1.30 ms for 516M pairs of 1,024 queries, 5.9 GB, 4.5 TB/s (1.57 ms
+// with a rolled loop and edge ids staged row by row); 2.3 ms for 993M pairs of 64 queries on 20M entities (2.48).
 constexpr int kSlicedMaxK = 6;     // hop + 1 <= 7 fits three bits
 
 constexpr int kPageEntries = 2;  // entries one lane per entity gathers together (on packed planes 1: 2.4, 2: 2.4, 4: 2.7, 8: 3.3 ms)
@@ -2069,11 +2067,12 @@ k_pred_emit(FillArgs a, const unsigned long long *__restrict__ planes, long long
 // other (where a query reached eight and more of the tile's entities, the wavefront takes the query), four at a time so
 // that their codes, and then their triple indices, are requested together.  It is bound by these chains and by the
 // scattered pieces of the lists it writes, which is why it loses to k_pred_emit where words are full.
-// Fetches of 1,024 queries, us k_pred_emit / k_emit_sparse, by the share of (listed entity, query) pairs that are reached:
-// 0.3 % 1,154 / 580, 0.4 % 614 / 450, 0.7 % 1,447 / 911, 3.9 % 1,473 / 1,396, 5.2 % 1,766 / 1,764, 8 % 1,059 / 1,162,
-// 22 % 1,885 / 2,164, 58 % 1,669 / 2,377: the line lies at 5 %.  (30M triples with whitelists, 3.9 %: lists 684 -> 482 us, and
-// the row walk, which writes no codes of empty words, 793 -> 749.)
-constexpr int kSparseShare = 20;   // reached pairs: at most one in this many
+// Fetches of 1,024 queries with whitelists on 30M triples, whole fetch, us k_pred_emit / k_emit_sparse, by the share of (listed
+// entity, query) pairs that are reached: 0.4 % 1,211 / 1,051, 0.8 % 1,463 / 1,301, 1.2 % 1,686 / 1,540, 1.4 % 2,064 / 1,974,
+// 2.4 % 2,013 / 2,009, 4.2 % 2,264 / 2,458, 4.6 % 2,275 / 2,434, 7.2 % 2,253 / 2,619, 11 % 2,437 / 3,069; two hops 0.5 %
+// 1,012 / 877, 1.1 % 1,252 / 1,198, 5.6 % 2,109 / 2,471; pages of 128 queries 2.7 % 757 / 751, 8.4 % 842 / 887: the line lies at
+// 2.5 % (at 5 % before k_pred_emit's loop was written out).
+constexpr int kSparseShare = 40;   // reached pairs: at most one in this many
 constexpr int kHeavyEntities = 8;  // (4 and 16: within 2 %)
 
 __global__ void __launch_bounds__(256)
