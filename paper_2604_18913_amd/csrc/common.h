@@ -296,6 +296,8 @@ struct logoskg_result {
     // 16-word planes: pulled hops do not keep visited (they ask the levels, see Seen), fold_visited makes it where it is
     // read.  vis_dirty: the levels that may have left something in it (at least vis_levels).
     std::atomic<int> vis_levels{0}, vis_dirty{0};
+    std::mutex vis_mutex;        // what makes visited behind the search: share_visited
+    hipEvent_t vis_made = nullptr;  // visited is made behind the search, complete behind this (on whichever stream)
     int n_levels = 0;  // levels the search has got to; what lies behind is empty
     unsigned long long *levels = nullptr;   // [k+1][Epad][W]
     uint32_t *act = nullptr;      // [k+1][Epad/32]: entity has a non-zero line in that level
@@ -552,6 +554,10 @@ logoskg_status build_pairs_on_device(logoskg_graph *g, const int32_t *in_sub, co
 Seen seen_levels(const logoskg_result *r, int upto);
 // khop.hip: visited becomes the OR of the levels below `upto` where it does not hold them yet (a captured launch leaves that open)
 logoskg_status fold_visited(logoskg_result *r, int upto, hipStream_t st);
+// the same for all levels behind the search, for a call on any stream and thread: work on st that follows finds the plane complete
+logoskg_status share_visited(logoskg_result *r, hipStream_t st);
+bool visited_by_search(const logoskg_result *r);  // .. and whether it is so without
+bool captured(hipStream_t st);  // result.hip
 struct TripleSorter;  // the triple list on the device during a sharded build (build_device.hip)
 logoskg_status sorter_create(logoskg_graph *g, const int32_t *subj, const int32_t *rel, const int32_t *obj,
                              TripleSorter **out);

@@ -526,7 +526,7 @@ k_push_seg(const RowSegment *__restrict__ segs, const unsigned long long *__rest
 // The first hop of 16-word planes: pairs that are seeds leave its level, and so do active bits of lines that held nothing
 // else.  Only an entity that is active in both levels can hold one, of which there are as many as seeds: a thread per 64
 // entities reads their two bitmap words.  (With visited kept as on narrow planes, 11M lines of 20M entities were read twice
-// and written: 514 us, 24 us now, and as many lines less to clear.)
+// and written: 514 us, 5 us now, and as many lines less to clear.)
 __global__ void __launch_bounds__(256)
 k_drop_seeds(long long words, const uint32_t *__restrict__ act0, uint32_t *act1, const unsigned long long *__restrict__ level0,
              unsigned long long *level1) {
@@ -1231,7 +1231,7 @@ k_sparse_clear(long long Epad, int levels, int vis_levels, uint32_t *act, long l
 }
 
 // visited = the OR of the first n levels, on the lines of entities that are active in one of them.  Every line is written
-// whole, so that two that run at once agree.
+// whole and from the levels alone: one that runs again beside a reader of the plane changes nothing.
 __global__ void __launch_bounds__(256)
 k_fold_visited(long long Epad, int n, const uint32_t *__restrict__ act, long long actw, const unsigned long long *__restrict__ levels,
                long long plane, unsigned long long *visited) {
@@ -1291,16 +1291,41 @@ Seen seen_levels(const logoskg_result *r, int upto) {
     return Seen{have ? r->visited : nullptr, r->levels, r->act, r->Epad * (long long)r->W, r->Epad / 32, have <= kSeenGate ? have : 0, have, upto, false};
 }
 
-logoskg_status fold_visited(logoskg_result *r, int upto, hipStream_t st) {
-    if (r->W != 16 || r->vis_levels.load() >= upto) return LOGOSKG_OK;
+static logoskg_status launch_fold(logoskg_result *r, int upto, hipStream_t st) {
     ProfScope ps(r->g->prof, KK_UPDATE, st);
     if (r->vis_dirty.load() < upto) r->vis_dirty.store(upto);
     k_fold_visited<<<dim3(blocks_for(r->Epad / 64, 4)), dim3(256), 0, st>>>(r->Epad, upto, r->act, r->Epad / 32, r->levels,
                                                                           r->Epad * 16, r->visited);
     LKG_HIP(hipGetLastError());
-    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &s) != hipSuccess) (void)hipGetLastError();
-    else if (s == hipStreamCaptureStatusNone) r->vis_levels.store(upto);  // (a recorded one has not run)
+    return LOGOSKG_OK;
+}
+
+logoskg_status fold_visited(logoskg_result *r, int upto, hipStream_t st) {
+    if (r->W != 16 || r->vis_levels.load() >= upto) return LOGOSKG_OK;
+    LKG_TRY(launch_fold(r, upto, st));
+    r->vis_levels.store(upto);
+    return LOGOSKG_OK;
+}
+
+bool visited_by_search(const logoskg_result *r) { return r->W != 16 || r->vis_levels.load() >= r->n_levels; }
+
+// vis_levels stays where the search left it: what tells later calls that the plane is whole is the event, for which their
+// streams wait.  A launch that a capture records has not run and cannot wait for what ran outside: every such call folds.
+logoskg_status share_visited(logoskg_result *r, hipStream_t st) {
+    if (visited_by_search(r)) return LOGOSKG_OK;
+    if (captured(st)) return launch_fold(r, r->n_levels, st);
+    std::lock_guard<std::mutex> lock(r->vis_mutex);
+    if (r->vis_made) {
+        LKG_HIP(hipStreamWaitEvent(st, r->vis_made, 0));
+        return LOGOSKG_OK;
+    }
+    LKG_TRY(launch_fold(r, r->n_levels, st));
+    hipEvent_t made = nullptr;  // (without one the next call folds again, the same values)
+    if (hipEventCreateWithFlags(&made, hipEventDisableTiming) == hipSuccess && hipEventRecord(made, st) == hipSuccess) r->vis_made = made;
+    else {
+        (void)hipGetLastError();
+        if (made) (void)hipEventDestroy(made);
+    }
     return LOGOSKG_OK;
 }
 
@@ -1660,6 +1685,10 @@ extern "C" void logoskg_result_free(logoskg_result *r) {
     constexpr int n = (int)(sizeof(ptrs) / sizeof(ptrs[0]));
     bool zeroed[n] = {};
     const hipStream_t st = r->last_stream;
+    if (r->vis_made) {
+        if (hipStreamWaitEvent(st, r->vis_made, 0) != hipSuccess) (void)hipGetLastError();
+        (void)hipEventDestroy(r->vis_made);
+    }
     if (r->complete && r->visited && r->act) {  // hand the planes and the bitmaps back as zeros
         ProfScope ps(g->prof, KK_CLEAR, st);
         const long long plane = r->Epad * r->W, actw = r->Epad / 32;
@@ -1862,10 +1891,9 @@ extern "C" logoskg_status logoskg_result_get_info(const logoskg_result *r, logos
     o->words_per_entity = r->W;
     o->num_levels = r->k + 1;
     o->padded_entities = r->Epad;
-    if (r->W == 16 && r->vis_levels.load() < r->n_levels) {
-        // on a stream of its own: the search has ended, and nothing that may run on others reads the plane
+    if (!visited_by_search(r)) {  // on a stream of its own: the search has ended
         LKG_HIP(hipSetDevice(r->g->device));
-        LKG_TRY(fold_visited(const_cast<logoskg_result *>(r), r->n_levels, r->g->side[0]));
+        LKG_TRY(share_visited(const_cast<logoskg_result *>(r), r->g->side[0]));
         LKG_HIP(hipStreamSynchronize(r->g->side[0]));
     }
     o->visited = (const uint64_t *)r->visited;

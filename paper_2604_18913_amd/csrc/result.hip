@@ -2658,7 +2658,7 @@ constexpr long long Qp_of() { return 64 * W; }
 
 // A block of the pool may not be taken or given back inside a sequence that a stream capture records: the replays
 // would use it after the pool has handed it on.  Kernels that are better with one have a form without.
-static bool captured(hipStream_t st) {
+bool captured(hipStream_t st) {
     hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &s) == hipSuccess) return s != hipStreamCaptureStatusNone;
     (void)hipGetLastError();
@@ -3016,9 +3016,9 @@ extern "C" logoskg_status logoskg_result_fetch(logoskg_result *r, int32_t q0, in
     }
     const bool counting = g->prof.counters;
     // 16-word planes: the kernels that ask visited (all but the pair of walk and writer on a list of active entities)
-    if (W == 16 && r->vis_levels.load() < r->n_levels) {
+    if (!visited_by_search(r)) {
         if (pred && a.row_pred && a.tile_ent && pred_uses_staged_kernel(a, W)) a.visited = nullptr;
-        else LKG_TRY(fold_visited(r, r->n_levels, st));
+        else LKG_TRY(share_visited(r, st));
     }
     // levels whose frontier holds at most a quarter of the triples: their long rows are resolved from the
     // subject side (resident graphs, row buffer in use, minimum-hop search); needs the triple index of

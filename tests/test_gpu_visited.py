@@ -90,3 +90,31 @@ def test_a_recorded_fetch_makes_it_at_every_replay():
         assert np.array_equal(x.cpu().numpy(), y)
     res.close()
     g.close()
+
+
+def test_calls_on_other_streams_wait_for_the_plane():
+    """Lists without predecessors make the plane on their stream, held back here; the next ones, on other streams, read it."""
+    import torch
+    import paper_2604_18913_amd as lkg
+    E, s, r, o, off, seeds = problem(6)
+    g = lkg.Graph(s, r, o, E, 8)
+    want = oracle.khop(E, s, r, o, off, seeds, 3)
+    outs = [[torch.zeros(want[0][-1], dtype=t, device="cuda") for t in (torch.int32, torch.uint8)] + [None] for _ in range(3)]
+    res = g.khop(off, seeds, 3, direction="pull")
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in outs]
+    with torch.cuda.stream(streams[0]):
+        torch.cuda._sleep(20_000_000)
+    for out, stream in zip(outs, streams):
+        res.fetch(out=out, stream=stream, want_pred=False)
+    info = res._info()  # (synchronises by itself)
+    levels = plane(info.levels, info.padded_entities * 64).reshape(4, -1)
+    assert np.array_equal(plane(info.visited, levels.shape[1]), np.bitwise_or.reduce(levels, 0))
+    for out in outs:
+        assert np.array_equal(out[0].cpu().numpy(), want[1]) and np.array_equal(out[1].cpu().numpy(), want[2])
+    res.close()
+    res = g.khop(off, seeds, 3, direction="pull")  # the block, given back cleared
+    for x, y in zip(res.fetch(), want[1:4]):
+        assert np.array_equal(x.cpu().numpy(), y)
+    res.close()
+    g.close()
