@@ -2050,8 +2050,9 @@ k_pred_emit(FillArgs a, const unsigned long long *__restrict__ planes, long long
     const int32_t *const my_row = a.in_eid + wlo;
     const int *const my_line = rp_tab + (lined ? line0 + __popcll(bq_wave & below) : 0) * 64;
     if (staged && lined && a.row_pred && a.hop) {  // block-uniform
-        const uint32_t at = 4u * (uint32_t)((longrow ? my_line : my_eids) - pool);
-        emit_word_pooled(a, c, live, seeds, pos_lo, pos_hi, ent_id, pool, at, longrow ? 4u : 0u);
+        // (a lane with neither, whose value is not stored or a seed's, reads the pool's first place: its own may lie behind the end)
+        const uint32_t at = by_query ? 4u * (uint32_t)(my_line - pool) : n_stage > 0 ? 4u * (uint32_t)(my_eids - pool) : 0u;
+        emit_word_pooled(a, c, live, seeds, pos_lo, pos_hi, ent_id, pool, at, by_query ? 4u : 0u);
     } else if (staged) {
         if (lined) emit_word<true, true>(a, c, live, pos_lo, pos_hi, ent_id, longrow, by_query, my_eids, my_row, my_line);
         else emit_word<true, false>(a, c, live, pos_lo, pos_hi, ent_id, longrow, by_query, my_eids, my_row, my_line);
