@@ -324,30 +324,54 @@ __global__ void __launch_bounds__(64 * NW) k_paths(PathArgs a) {
         }
         const unsigned long long *lv = a.levels + (size_t)(l - 1) * a.plane;
         const uint32_t *act = a.act + (size_t)(l - 1) * a.actw;
-        int steps = 1;  // entries per lane of the next step
+        // The first step after a descent takes an entry per lane, the next ones U; from the second on the ids of the step
+        // behind it are on their way while the bits of this one are gathered.  With many pairs the longest rows outlast
+        // everything else, and their steps are chains of gathers: a row of 123,361 entries by four wavefronts 306 -> 236 us.
+        int steps = 1, s_next[U], r_next[U];
+        auto request = [&](uint32_t j0, int n) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t jj = j0 + (uint32_t)(u * NT + t);
+                const uint32_t at = u < n && jj < hi ? jj : j;  // (an entry of the row in any case)
+                s_next[u] = a.in_sub[at];
+                r_next[u] = a.allow ? a.in_rel[at] : 0;
+            }
+        };
+        request(j, 1);
         while (j < hi && found < max_paths) {
-            int32_t s[U];
+            int32_t s[U], r[U];
             bool ok[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const uint32_t jj = j + (uint32_t)(u * NT + t);
-                ok[u] = u < steps && jj < hi;
-                s[u] = ok[u] ? a.in_sub[jj] : 0;
+                s[u] = s_next[u];
+                r[u] = r_next[u];
+                ok[u] = u < steps && j + (uint32_t)(u * NT + t) < hi;
             }
+            const uint32_t j_next = j + (uint32_t)(steps * NT);
+            if (steps > 1) request(j_next, j_next < hi ? U : 0);
+            // Lanes that are out read what stands for entity or relation 0: with a branch around every gather, the U gathers
+            // of a kind waited for each other.
             if (a.allow) {
-                int r[U];
+                unsigned long long x[U];
 #pragma unroll
-                for (int u = 0; u < U; ++u) r[u] = ok[u] ? a.in_rel[j + (uint32_t)(u * NT + t)] : 0;
+                for (int u = 0; u < U; ++u) x[u] = lds_allow ? s_allow[r[u] >> 6] >> (r[u] & 63) : a.allow[(size_t)r[u] * W + w] >> (q & 63);
 #pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (ok[u]) ok[u] = allowed(r[u]);
+                for (int u = 0; u < U; ++u) ok[u] &= (x[u] & 1ull) != 0ull;
             }
+            {
+                uint32_t x[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (ok[u]) ok[u] = (act[s[u] >> 5] >> (s[u] & 31)) & 1u;
+                for (int u = 0; u < U; ++u) x[u] = act[(ok[u] ? s[u] : 0) >> 5] >> (s[u] & 31);
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (ok[u]) ok[u] = (lv[(size_t)s[u] * W + w] & bit) != 0ull;
+                for (int u = 0; u < U; ++u) ok[u] &= (x[u] & 1u) != 0u;
+            }
+            {
+                unsigned long long x[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) x[u] = lv[(size_t)(ok[u] ? s[u] : 0) * W + w];
+#pragma unroll
+                for (int u = 0; u < U; ++u) ok[u] &= (x[u] & bit) != 0ull;
+            }
             unsigned long long mine[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -394,7 +418,8 @@ __global__ void __launch_bounds__(64 * NW) k_paths(PathArgs a) {
                 }
             }
             buf ^= 1;
-            j += (uint32_t)(steps * NT);
+            if (steps == 1) request(j_next, U);
+            j = j_next;
             steps = U;
         }
         if (!descended) ++l;  // this vertex's row is exhausted: back to the vertex after it

@@ -128,3 +128,42 @@ def test_graphs_of_short_rows(longest, shards, share):
             assert np.array_equal(edges.cpu().numpy().reshape(edges_o[at].shape), edges_o[at])
     res.close()
     g.close()
+
+
+@pytest.mark.parametrize("share", [None, 0.3])
+@pytest.mark.parametrize("exact", [False, True])
+def test_seeds_with_rows_of_all_lengths(share, exact):
+    """Rows of the seeds around the numbers of threads and matches of a block, long rows on levels 1, 2 and 3 above them."""
+    import paper_2604_18913_amd as lkg
+    rng = np.random.default_rng(5)
+    degrees = [1, 63, 64, 65, 255, 256, 257, 300, 850, 1023, 1024, 1025, 4096, 4097, 16384, 16385]
+    Q, R, mid, tops = len(degrees), 40, 50, 6
+    m0, t0 = Q, Q + mid  # seeds | middles | tops
+    E = t0 + tops + 200
+    s = [np.repeat(np.arange(Q), degrees), m0 + rng.integers(0, mid, 2400), t0 + rng.integers(0, 3, 900), rng.integers(t0 + tops, E, 9000)]
+    o = [m0 + rng.integers(0, mid, sum(degrees)), t0 + rng.integers(0, 3, 2400), t0 + 3 + rng.integers(0, 3, 900), rng.integers(m0, t0, 9000)]
+    s, o = np.concatenate(s).astype(np.int32), np.concatenate(o).astype(np.int32)
+    perm = rng.permutation(len(s))
+    s, o = s[perm], o[perm]
+    r = rng.integers(0, R, len(s)).astype(np.int32)
+    mask = None
+    if share is not None:
+        mask = ((rng.random((Q, R)) < share).astype(np.uint64) << np.arange(R, dtype=np.uint64)).sum(1, dtype=np.uint64)[:, None]
+    off, seeds = 2 * np.arange(Q + 1, dtype=np.int64), np.repeat(np.arange(Q), 2).astype(np.int32)  # (every seed twice)
+    g = lkg.Graph(s, r, o, E, R)
+    res = g.khop(off, seeds, 3, mask, walk_exact=exact)
+    pq, pt = (x.ravel().astype(np.int32) for x in np.meshgrid(np.arange(Q), np.arange(m0, t0 + tops), indexing="ij"))
+    length = np.where(pt < t0, 1, np.where(pt < t0 + 3, 2, 3)).astype(np.int32)
+    for max_paths in (3, 16):
+        if exact:
+            cnt_o, edges_o = oracle.walk_paths(E, s, r, o, off, seeds, 3, pq, pt, length, max_paths, mask)
+        else:
+            cnt_o, edges_o = oracle.paths(E, s, r, o, off, seeds, 3, pq, pt, max_paths, mask)
+        assert cnt_o.max() == max_paths
+        for n in (len(pq), 1025, 65536 + 1):  # 16, 4 and 1 wavefronts per pair
+            at = np.arange(n) % len(pq)
+            cnt, edges = g.walks(res, pq[at], pt[at], length[at], max_paths) if exact else g.paths(res, pq[at], pt[at], max_paths)
+            assert np.array_equal(cnt.cpu().numpy(), cnt_o[at])
+            assert np.array_equal(edges.cpu().numpy(), edges_o[at])
+    res.close()
+    g.close()
