@@ -693,22 +693,22 @@ __device__ __forceinline__ int pull_gather(const PullEdges &e, bool cand, const 
             }
         }
         if (base < ncand) {
-            ulonglong2 l[NR];
+            ulonglong2 l[NR], ok[NR];  // (put together behind all loads: in the branch, each round waited for its own)
 #pragma unroll
             for (int x = 0; x < NR; ++x) {
                 const int i = base + x * GPW + g;
-                l[x] = make_ulonglong2(0, 0);
+                l[x] = ok[x] = make_ulonglong2(0, 0);
                 if (i < ncand) {
                     l[x] = prev2[(size_t)queue_s[i] * LW + lw];
-                    if (MASK) {
-                        const ulonglong2 m = allow2[(size_t)queue_r[i] * LW + lw];
-                        l[x].x &= m.x;
-                        l[x].y &= m.y;
-                    }
+                    if (MASK) ok[x] = allow2[(size_t)queue_r[i] * LW + lw];
                 }
             }
 #pragma unroll
             for (int x = 0; x < NR; ++x) {
+                if (MASK) {
+                    l[x].x &= ok[x].x;
+                    l[x].y &= ok[x].y;
+                }
                 a0 |= l[x].x;
                 a1 |= l[x].y;
             }
@@ -894,7 +894,7 @@ k_pull_tail(const ShortRow *__restrict__ rows, long long n, const int32_t *__res
         constexpr int NL = kTailLines;
         while (any_candidate()) {  // two candidate lines of each row in flight
             int c[NR][NL];
-            unsigned long long l[NR][NL];
+            unsigned long long l[NR][NL], ok[NR][NL];
 #pragma unroll
             for (int r = 0; r < NR; ++r)
 #pragma unroll
@@ -911,13 +911,19 @@ k_pull_tail(const ShortRow *__restrict__ rows, long long n, const int32_t *__res
                 for (int x = 0; x < NL; ++x) {
                     const int src = g0 + (c[r][x] < 0 ? 0 : c[r][x]);
                     const int sx = __shfl(s[r], src);
-                    l[r][x] = 0;
+                    l[r][x] = ok[r][x] = 0;  // (put together behind all loads)
                     if (c[r][x] >= 0) l[r][x] = prev[(size_t)sx * W + lw];
                     if (MASK) {
                         const int rx = __shfl(rl[r], src);
-                        if (c[r][x] >= 0) l[r][x] &= allow[(size_t)rx * W + lw];
+                        if (c[r][x] >= 0) ok[r][x] = allow[(size_t)rx * W + lw];
                     }
                 }
+            if (MASK) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r)
+#pragma unroll
+                    for (int x = 0; x < NL; ++x) l[r][x] &= ok[r][x];
+            }
 #pragma unroll
             for (int r = 0; r < NR; ++r)
 #pragma unroll
@@ -1362,7 +1368,7 @@ static void launch_push(logoskg_graph *g, logoskg_result *r, int h, const unsign
         return;
     }
     if (known) k_update_visited<W, false><<<grid, block, 0, st>>>(r->Epad, act_cur, cur, r->visited);
-    else k_update_visited<W, true><<<grid, block, 0, st>>>(r->Epad, act_cur, cur, r->visited);
+    else if constexpr (W < 16) k_update_visited<W, true><<<grid, block, 0, st>>>(r->Epad, act_cur, cur, r->visited);
 }
 
 // STATS: the counting mode runs instantiations of its own, so that kernel statistics of the

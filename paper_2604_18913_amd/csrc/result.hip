@@ -696,18 +696,19 @@ __device__ __forceinline__ int pred_resolve_unordered(int s, int r, bool cand, c
     constexpr int NR = 4, GPW = 64 / W;
     int base = 0;
     for (; base < n; base += NR * GPW) {
-        unsigned long long l[NR];
+        unsigned long long l[NR], ok[NR];  // (put together behind all loads: in the branch, each round waited for its own)
 #pragma unroll
         for (int x = 0; x < NR; ++x) {
             const int i = base + x * GPW + g;
-            l[x] = 0;
+            l[x] = ok[x] = 0;
             if (i < n) {
                 l[x] = prev[(size_t)queue.s[i] * W + lw];
-                if (MASK) l[x] &= a.allow[(size_t)queue.r[i] * W + lw];
+                if (MASK) ok[x] = a.allow[(size_t)queue.r[i] * W + lw];
             }
         }
 #pragma unroll
         for (int x = 0; x < NR; ++x) {
+            if (MASK) l[x] &= ok[x];
             const unsigned long long hit = l[x] & rem;
             rem &= ~l[x];
             if (hit) emit(hit, (int)queue.at[base + x * GPW + g]);
@@ -1161,7 +1162,7 @@ __device__ __forceinline__ void narrow_tiles(const FillArgs &a, unsigned block, 
             if (lw == 0) ++n_rows;
             for (uint32_t j0 = lo; j0 < hi; j0 += U) {
                 int s[U], rl[U];
-                unsigned long long l[U];
+                unsigned long long l[U], ok[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     s[u] = j0 + u < hi ? a.in_sub[j0 + u] : -1;
@@ -1170,10 +1171,11 @@ __device__ __forceinline__ void narrow_tiles(const FillArgs &a, unsigned block, 
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     l[u] = s[u] >= 0 ? prev[(size_t)s[u] * W + lw] : 0ull;
-                    if (MASK && s[u] >= 0) l[u] &= a.allow[(size_t)rl[u] * W + lw];
+                    ok[u] = MASK && s[u] >= 0 ? a.allow[(size_t)rl[u] * W + lw] : 0ull;
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
+                    if (MASK) l[u] &= ok[u];
                     const unsigned long long hit = l[u] & rem;
                     rem &= ~l[u];
                     if (hit) {
@@ -1627,7 +1629,7 @@ k_pred_walk(FillArgs a, unsigned long long *__restrict__ codes, unsigned long lo
                 constexpr int U = G == 1 || MASK ? kPageEntries : 8;
                 for (int i0 = 0; i0 < (int)deg; i0 += U) {  // (i0 is the same in all lanes that are still in the loop)
                     int sx[U], rx[U];
-                    unsigned long long l[U];
+                    unsigned long long l[U], ok[U];
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         const bool in = i0 + u < (int)deg;
@@ -1637,10 +1639,11 @@ k_pred_walk(FillArgs a, unsigned long long *__restrict__ codes, unsigned long lo
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         l[u] = sx[u] >= 0 ? level_word(h - 1, sx[u]) : 0ull;
-                        if (MASK && sx[u] >= 0) l[u] &= a.allow[(size_t)rx[u] * W + lw];
+                        ok[u] = MASK && sx[u] >= 0 ? a.allow[(size_t)rx[u] * W + lw] : 0ull;
                     }
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
+                        if (MASK) l[u] &= ok[u];
                         const unsigned long long hit = l[u] & rem;
                         rem &= ~l[u];
                         const int at = i0 + u;
@@ -1679,7 +1682,7 @@ k_pred_walk(FillArgs a, unsigned long long *__restrict__ codes, unsigned long lo
 #pragma unroll
                 for (int i0 = 0; i0 < G; i0 += 4) {
                     if (!((any >> i0) & 15u)) continue;
-                    unsigned long long l[4];
+                    unsigned long long l[4], ok[4];
                     int sx[4], rx[4];
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
@@ -1688,15 +1691,16 @@ k_pred_walk(FillArgs a, unsigned long long *__restrict__ codes, unsigned long lo
                     }
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
-                        l[u] = 0;
+                        l[u] = ok[u] = 0;
                         if ((mine >> (i0 + u)) & 1u) {
                             l[u] = prev[(size_t)sx[u] * W + lw];
-                            if (MASK) l[u] &= a.allow[(size_t)rx[u] * W + lw];
+                            if (MASK) ok[u] = a.allow[(size_t)rx[u] * W + lw];
                         }
                     }
                     unsigned long long found = 0;
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
+                        if (MASK) l[u] &= ok[u];
                         const unsigned long long hit = l[u] & rem;
                         rem &= ~l[u];
                         found |= hit;
@@ -2249,15 +2253,22 @@ __global__ void __launch_bounds__(1024) k_pred_row(FillArgs a, long long first_r
             bool cj[C];
 #pragma unroll
             for (int c = 0; c < C; ++c) {  // all loads of the step first
-                uint32_t j = w0 + 64u * nw * c + v;
-                sj[c] = rj[c] = 0;
-                cj[c] = false;
-                if (j < step_hi) {
-                    sj[c] = a.in_sub[j];
-                    if (MASK) rj[c] = a.in_rel[j];
-                    cj[c] = dense || ((act_prev[sj[c] >> 5] >> (sj[c] & 31)) & 1u);
-                    if (MASK && by_relation) cj[c] = cj[c] && ((usable[rj[c] >> 6] >> (rj[c] & 63)) & 1u);
-                }
+                const uint32_t j = w0 + 64u * nw * c + v;
+                cj[c] = j < step_hi;
+                const uint32_t at = cj[c] ? j : s0;  // (no branch, which the next chunk's loads would wait behind)
+                sj[c] = a.in_sub[at];
+                rj[c] = MASK ? a.in_rel[at] : 0;
+            }
+            if (MASK && by_relation) {
+#pragma unroll
+                for (int c = 0; c < C; ++c) cj[c] = cj[c] && ((usable[rj[c] >> 6] >> (rj[c] & 63)) & 1u);
+            }
+            if (!dense) {
+                uint32_t bits[C];
+#pragma unroll
+                for (int c = 0; c < C; ++c) bits[c] = act_prev[sj[c] >> 5] >> (sj[c] & 31);
+#pragma unroll
+                for (int c = 0; c < C; ++c) cj[c] = cj[c] && (bits[c] & 1u);
             }
 #pragma unroll
             for (int c = 0; c < C; ++c) {
