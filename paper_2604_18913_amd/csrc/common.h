@@ -490,6 +490,7 @@ __device__ __forceinline__ void write_segments(RowSegment *out, unsigned long lo
 struct FillArgs {
     int32_t E, R;
     int Q, k, q0, q1, hub_min;
+    long long entries;  // of all lists asked for
     long long ntiles;
     const int32_t *tile_ent;  // the tiles' entities (list of active entities) or NULL: tile i = ids 64 i ..
     const int32_t *cpos;      // entity -> place in tile_ent (garbage for entities not in the list), or NULL

@@ -2501,10 +2501,27 @@ logoskg_status prepare_row_pred(logoskg_graph *g, hipStream_t st) {
 }
 
 // Entity lists of 16-word planes without hop numbers (level lists among them): a block = 16 tiles x one word of the range, a
-// wavefront per tile, lane = entity, as k_pred_emit writes its lists.  A wavefront per word of the whole line left fourteen of
-// sixteen idle where a page holds two words, and its compaction in LDS and three accesses there per entry were more than what
-// unaligned pieces cost (a level page of 96 of 1,024 queries on 30M triples: 115 us, 67 so).  Bound by the number of stores.
-constexpr int kWordTiles = 16;
+// wavefront per tile, lane = entity, as k_pred_emit writes its lists.  A wavefront per word of the whole line leaves fourteen
+// of sixteen idle where a page holds two words (a level page of 96 of 1,024 queries on 30M triples: 115 us, 67 so).  Bound by
+// the number of stores, which are pieces of a tile; for more words than four (word_lists) the runs that k_lists puts together
+// in LDS are worth more, unless the pieces are nearly whole or the tiles few.  us, k_lists / this kernel, by words of the page
+// (tiles; share of their pairs that is listed):
+//    30M triples        (13,958; .43)    2: 131 /  88    4: 164 / 147    5: 191 / 179    6: 213 / 213    8: 263 / 297    16:   479 /   582
+//    under whitelists   (13,227; .02)    2:  57 /  39    4:  58 /  51    5:  59 /  58    6:  62 /  67    8:  61 /  80    16:    87 /   152
+//    hub-heavy 20M      (30,447; .38)    2: 242 / 170    4: 323 / 310    5: 388 / 383    6: 455 / 461    8: 524 / 641    16: 1,025 / 1,282
+//    three hops of it   (30,550; .83)    2: 327 / 243    4: 517 / 430    5: 637 / 528    6: 785 / 630    8: 1,033 / 884  16: 2,203 / 1,811
+//    under whitelists   (30,360; .08)    2: 168 / 107    4: 188 / 187    5: 208 / 223    6: 237 / 266    8: 248 / 352    16:   406 /   675
+//    hub-heavy 4M        (6,111; .78)    2:  86 /  45    4: 118 / 102    5: 141 / 118    6: 164 / 136    8: 213 / 176    16:   407 /   358
+//    3.4M triples        (1,598; .42)    2:  38 /  23    4:  39 /  27    5:  42 /  28    6:  44 /  33    8:  48 /  38    16:    58 /    50
+//    under whitelists    (1,562; .03)    2:  22 /  19    4:  23 /  21    5:  23 /  21    6:  23 /  24    8:  24 /  26    16:    30 /    34
+//    hub-heavy 0.8M      (1,403; .05)    2:  31 /  21    4:  32 /  25    5:  34 /  25    6:  35 /  29    8:  36 /  30    16:    47 /    42
+constexpr int kWordTiles = 16, kWordListWords = 4, kWordListPercent = 70, kWordListFewTiles = 2048, kWordListShare = 24;
+
+static bool word_lists(const FillArgs &a, int words) {
+    const long long pairs = a.ntiles * 64 * 64 * words;
+    return words <= kWordListWords || a.entries * 100 >= pairs * kWordListPercent ||
+           (a.ntiles <= kWordListFewTiles && a.entries * kWordListShare >= pairs);
+}
 
 __global__ void __launch_bounds__(kWordTiles * 64) __attribute__((amdgpu_waves_per_eu(8, 8)))
 k_word_lists(FillArgs a, int w0, int nw) {
@@ -2550,7 +2567,7 @@ static void launch_lists_t(Profiler &prof, const FillArgs &a, hipStream_t st) {
     int nb = 1;
     while ((1 << nb) <= a.k) ++nb;
     dim3 grid((unsigned)nblocks), block(64 * W);
-    if (W < 16 && !a.hop) k_lists<W, W < 16 ? 0 : 2, TILES><<<grid, block, 0, st>>>(a);
+    if (!a.hop) k_lists<W, 0, TILES><<<grid, block, 0, st>>>(a);
     else if (nb <= 2) k_lists<W, 2, TILES><<<grid, block, 0, st>>>(a);
     else if (nb <= 4) k_lists<W, 4, TILES><<<grid, block, 0, st>>>(a);
     else k_lists<W, 8, TILES><<<grid, block, 0, st>>>(a);
@@ -2575,10 +2592,10 @@ template <int W>
 static void launch_lists_w(Profiler &prof, const FillArgs &a, hipStream_t st) {
     constexpr int most = W == 16 ? kSuperTiles / 2 : W == 4 ? kSuperTiles : 4;
     if constexpr (W == 16) {
-        if (!a.hop) {
+        const int w0 = a.q0 / 64, nw = (a.q1 - 1) / 64 - w0 + 1;
+        if (!a.hop && word_lists(a, nw)) {
             if (a.ntiles == 0) return;
             ProfScope ps(prof, KK_LISTS, st);
-            const int w0 = a.q0 / 64, nw = (a.q1 - 1) / 64 - w0 + 1;
             const long long blocks = (a.ntiles + kWordTiles - 1) / kWordTiles * nw;
             k_word_lists<<<dim3((unsigned)((blocks + 7) / 8 * 8)), dim3(kWordTiles * 64), 0, st>>>(a, w0, nw);
             return;
@@ -3142,7 +3159,7 @@ extern "C" logoskg_status logoskg_result_level_fetch(logoskg_result *r, int32_t 
     a.visited = r->levels + (size_t)h * r->Epad * W; a.levels = a.visited; a.allow = r->allow;
     a.act = r->act; a.tile_base = r->lvl_tile_base; a.super_base = r->lvl_super_base; a.mega_base = r->lvl_mega_base;
     a.reached_off = r->d_level_off;
-    a.entity = entity;
+    a.entity = entity; a.entries = need;
     launch_lists(g->prof, a, W, (hipStream_t)stream);
     LKG_HIP(hipGetLastError());
     if (g->prof.on) g->prof.acc[KK_LISTS].units[3] += need;

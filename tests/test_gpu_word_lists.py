@@ -37,3 +37,28 @@ def test_entity_lists(E, Q, walk):
         assert np.array_equal(got.cpu().numpy(), want_ent[want_off[q0]:want_off[q1]]), (q0, q1)
     res.close()
     g.close()
+
+
+@pytest.mark.parametrize("E, degree", [(700, 2), (700, 60), (140_000, 3)])
+def test_pages_on_both_sides_of_the_rule(E, degree):
+    """Four and five words; few tiles and many; nearly all pairs reached and few of them."""
+    import paper_2604_18913_amd as lkg
+    rng = np.random.default_rng(E + degree)
+    Q, R, k = 1024, 3, 2
+    s, o = rng.integers(0, E, (2, E * degree)).astype(np.int32)
+    r = rng.integers(0, R, len(s)).astype(np.int32)
+    off = np.arange(Q + 1, dtype=np.int64)
+    seeds = rng.integers(0, E, Q).astype(np.int32)
+    want_off, want_ent = oracle.khop(E, s, r, o, off, seeds, k)[:2]
+    level_off, level_ent = oracle.walk_levels(E, s, r, o, off, seeds, k)
+    a = level_off[k * Q:(k + 1) * Q + 1]
+    g = lkg.Graph(s, r, o, E, R)
+    res, walk = g.khop(off, seeds, k), g.khop(off, seeds, k, walk_exact=True)
+    for q0, q1 in ((0, 256), (0, 257), (63, 257), (64, 320), (70, 390), (1, 1024)):
+        got = res.fetch(q0, q1, want_hop=False, want_pred=False)[0]
+        assert np.array_equal(got.cpu().numpy(), want_ent[want_off[q0]:want_off[q1]]), (q0, q1)
+        got = walk.level(k, q0, q1)[1]
+        assert np.array_equal(got.cpu().numpy(), level_ent[a[q0]:a[q1]]), (q0, q1)
+    res.close()
+    walk.close()
+    g.close()
