@@ -261,7 +261,8 @@ typedef struct {
     int32_t num_levels;          /* k + 1 */
     int64_t padded_entities;     /* rows per plane (num_entities rounded up to 64) */
     const uint64_t *visited;     /* device uint64[padded_entities][W]; on 16-word planes made by this call where the
-                                    search has not needed it (some 0.1 ms for 3M entities), and ready on return */
+                                    search has not kept it (0.15 ms for 3M entities; the graph's next search keeps it),
+                                    and ready on return */
     const uint64_t *levels;      /* device uint64[k+1][padded_entities][W]         */
     int64_t total_reached;       /* sum over queries (-1 with LOGOSKG_NO_COUNTS)   */
 } logoskg_result_info;

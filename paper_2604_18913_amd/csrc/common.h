@@ -270,6 +270,7 @@ struct logoskg_graph {
     int32_t *row_pred = nullptr;    // [row_pred_rows][1024]
     int64_t row_pred_rows = 0;
     bool row_pred_tried = false;
+    bool visited_asked = false;     // the last search's result was asked for its visited plane: the next one keeps it
     unsigned long long *plane_buf = nullptr;  // plane words of the bit-sliced predecessor pass (same first use)
     size_t plane_buf_bytes = 0;
     hipEvent_t ev_rows = nullptr;
@@ -293,8 +294,9 @@ struct logoskg_result {
     bool has_counts = false;
     bool walk_exact = false;  // levels hold q^(h) of the plain iteration (no visited filter)
     unsigned long long *visited = nullptr;  // [Epad][W]; 16-word planes: the OR of the levels below vis_levels only
-    // 16-word planes: pulled hops do not keep visited (they ask the levels, see Seen), fold_visited makes it where it is
-    // read.  vis_dirty: the levels that may have left something in it (at least vis_levels).
+    // 16-word planes: hops do not keep visited unless keep_visited says so (they ask the levels, see Seen), fold_visited makes
+    // it where it is read.  vis_dirty: the levels that may have left something in it (at least vis_levels).
+    bool keep_visited = false;
     std::atomic<int> vis_levels{0}, vis_dirty{0};
     std::mutex vis_mutex;        // what makes visited behind the search: share_visited
     hipEvent_t vis_made = nullptr;  // visited is made behind the search, complete behind this (on whichever stream)
@@ -444,6 +446,7 @@ struct Seen {
     long long plane, actw;
     int gate, first, last;
     bool sure;  // most rows are active in the last level: its lines (zero elsewhere) are read without asking
+    bool keep;  // base is the plane that the hop keeps: it holds all levels, and its line is written where something is reached
 };
 
 __device__ __forceinline__ bool active_in(const Seen &s, int level, int e) {

@@ -14,7 +14,8 @@
 //         alive, OR the lines of its subjects that are in the frontier, and
 //         stop as soon as nothing is missing; no atomics on short rows, and
 //         visited is updated in the same kernel (planes of one and four words)
-//         or the levels themselves are asked what was reached before (16 words).
+//         or the levels themselves are asked what was reached before (16 words,
+//         searches of few hops: keeps_visited).
 //         Without whitelists the rows are those of the distinct (subject,
 //         object) pairs where these are built.
 // Both give the same level[h].  Rows of up to 32 entries are handled by a
@@ -523,7 +524,7 @@ k_push_seg(const RowSegment *__restrict__ segs, const unsigned long long *__rest
     }
 }
 
-// The first hop of 16-word planes: pairs that are seeds leave its level, and so do active bits of lines that held nothing
+// The first hop of searches that do not keep visited: pairs that are seeds leave its level, and so do active bits of lines that held nothing
 // else.  Only an entity that is active in both levels can hold one, of which there are as many as seeds: a thread per 64
 // entities reads their two bitmap words.  (With visited kept as on narrow planes, 11M lines of 20M entities were read twice
 // and written: 514 us, 5 us now, and as many lines less to clear.)
@@ -556,7 +557,7 @@ k_drop_seeds(long long words, const uint32_t *__restrict__ act0, uint32_t *act1,
 // One wavefront per 64 entities: it reads their two words of the active bitmap once and touches
 // only the lines of the active ones (after a push from a small frontier almost none), W lanes per
 // line, so a dense level is still updated with contiguous accesses.
-// FIRST (narrow planes): the hop has set bits without asking visited; those that were there (the seeds) leave the level, and
+// FIRST: the hop has set bits without asking visited; those that were there (the seeds) leave the level, and
 // so do lines and active bits that held nothing else.
 template <int W, bool FIRST>
 __global__ void __launch_bounds__(256)
@@ -942,7 +943,7 @@ k_pull_tail(const ShortRow *__restrict__ rows, long long n, const int32_t *__res
         const unsigned long long nw = acc[r] & need[r];
         if (row_end[r] > lo[r] && group_any<W>(nw != 0)) {
             cur[(size_t)v[r] * W + lw] = nw;
-            if (W < 16) visited[(size_t)v[r] * W + lw] = vis[r] | nw;
+            if (W < 16 || seen.keep) visited[(size_t)v[r] * W + lw] = vis[r] | nw;
             if (lw == 0) atomicOr(&act_cur[v[r] >> 5], 1u << (v[r] & 31));
         }
     }
@@ -1028,7 +1029,7 @@ k_pull_seg(const PullSegment *__restrict__ segs, long long n,
             if (!multi) {
                 if (lane() < W) {
                     cur[(size_t)v * W + lane()] = nb;
-                    if (W < 16) visited[(size_t)v * W + lane()] = vis | nb;
+                    if (W < 16 || seen.keep) visited[(size_t)v * W + lane()] = vis | nb;
                 }
                 if (lane() == 0) atomicOr(&act_cur[v >> 5], 1u << (v & 31));
             } else if (lane() < W && nb) {
@@ -1042,11 +1043,11 @@ k_pull_seg(const PullSegment *__restrict__ segs, long long n,
     }
 }
 
-// Rows that were expanded by several segments: mark active, and on narrow planes visited |= level[h].
+// Rows that were expanded by several segments: mark active, and where the plane is kept visited |= level[h].
 template <int W>
 __global__ void __launch_bounds__(256)
 k_pull_finish(const int32_t *__restrict__ rows, long long n, unsigned long long *visited,
-              const unsigned long long *__restrict__ cur, uint32_t *act_cur) {
+              const unsigned long long *__restrict__ cur, uint32_t *act_cur, bool keep) {
     long long gidx = ((long long)blockIdx.x * blockDim.x + threadIdx.x) / W;
     const int lw = threadIdx.x & (W - 1);
     unsigned long long c = 0;
@@ -1056,7 +1057,7 @@ k_pull_finish(const int32_t *__restrict__ rows, long long n, unsigned long long 
         c = cur[(size_t)v * W + lw];
     }
     if (group_any<W>(c != 0)) {
-        if (W < 16) visited[(size_t)v * W + lw] |= c;
+        if (keep) visited[(size_t)v * W + lw] |= c;
         if (lw == 0) atomicOr(&act_cur[v >> 5], 1u << (v & 31));
     }
 }
@@ -1290,11 +1291,29 @@ static unsigned long long *level_counters(const logoskg_result *r, int h) {
     return r->live + (size_t)16 * (r->k + 1) + (size_t)kLevelCounters * h;
 }
 
-constexpr int kSeenLevels = 5;  // pulled hops in a row: at most so many levels are asked one by one, then visited is made
+// A search on 16-word planes whose hops keep visited, as those on narrow planes do: one of many hops (hop h of the others asks up
+// to h levels, and so does the count), one on planes that stay in the L2s (visited 32 MB, 4 MB for walk-exact ones, which ask
+// for nothing), and one on a graph whose last result was asked for the plane, which would be made from the levels each time.
+// us of a search of 1,024 queries, without / with it:
+//    30M triples, 3M entities       k = 2:   471 /   533    3:   812 /   859    4: 1,210 / 1,189    5: 1,453 / 1,317    8: 1,696 / 1,444
+//    hub-heavy 20M, 2M entities     k = 2:   913 / 1,067    3: 1,425 / 1,512    4: 2,011 / 1,958    5: 2,663 / 2,392    8: 3,499 / 2,770
+//    under whitelists               k = 2: 1,033 / 1,196    3: 1,706 / 1,842    4: 2,435 / 2,464    5: 3,137 / 2,965    8: 4,721 / 3,730
+//    with lists, 1M entities        k = 2:   777 /   800    3: 1,206 / 1,225    4: 1,436 / 1,427    407,000:  3: 680 / 682    4: 764 / 766
+//    200,000 entities               k = 2:   387 /   391    3:   500 /   494    4:   571 /   561    20,000:   3: 208 / 188    4: 270 / 244
+//    walk-exact, 3M                 k = 3:   752 /   860    6: 1,672 / 1,836    100,000: 3: 190 / 211    20,000: 3: 164 / 162    6: 262 / 249
+constexpr int kSeenMaxK = 4;
+constexpr long long kSeenMinEntities = 1 << 18, kSeenMinWalkEntities = 1 << 15;
+
+static bool keeps_visited(const logoskg_graph *g, const logoskg_result *r) {
+    if (r->W != 16) return false;
+    if (g->visited_asked) return true;
+    return r->walk_exact ? r->Epad < kSeenMinWalkEntities : r->k > kSeenMaxK || r->Epad < kSeenMinEntities;
+}
 
 Seen seen_levels(const logoskg_result *r, int upto) {
     const int have = std::min(r->vis_levels.load(), upto);
-    return Seen{have ? r->visited : nullptr, r->levels, r->act, r->Epad * (long long)r->W, r->Epad / 32, have <= kSeenGate ? have : 0, have, upto, false};
+    const int gate = r->keep_visited || have > kSeenGate ? 0 : have;
+    return Seen{have ? r->visited : nullptr, r->levels, r->act, r->Epad * (long long)r->W, r->Epad / 32, gate, have, upto, false, r->keep_visited};
 }
 
 static logoskg_status launch_fold(logoskg_result *r, int upto, hipStream_t st) {
@@ -1360,15 +1379,16 @@ static void launch_push(logoskg_graph *g, logoskg_result *r, int h, const unsign
         });
         g->prof.acc[KK_PUSH_TAIL].units[0] += g->prof.on ? nt : 0;
     }
-    if (!update || (W == 16 && r->walk_exact)) return;  // (walk-exact levels ask for nothing that was reached)
+    const bool keep = W < 16 || r->keep_visited;
+    if (!update || (!keep && r->walk_exact)) return;  // (walk-exact levels ask for nothing that was reached)
     ProfScope ps(g->prof, KK_UPDATE, st);
     const dim3 grid(blocks_for(r->Epad / 64, 4)), block(256);
-    if (W == 16 && !known) {
+    if (!keep && !known) {
         k_drop_seeds<<<dim3(blocks_for((long long)(r->Epad / 64), 256)), block, 0, st>>>(r->Epad / 64, r->act, act_cur, r->levels, cur);
         return;
     }
     if (known) k_update_visited<W, false><<<grid, block, 0, st>>>(r->Epad, act_cur, cur, r->visited);
-    else if constexpr (W < 16) k_update_visited<W, true><<<grid, block, 0, st>>>(r->Epad, act_cur, cur, r->visited);
+    else k_update_visited<W, true><<<grid, block, 0, st>>>(r->Epad, act_cur, cur, r->visited);
 }
 
 // STATS: the counting mode runs instantiations of its own, so that kernel statistics of the
@@ -1402,7 +1422,7 @@ static void launch_pull_rows(logoskg_graph *g, logoskg_result *r, int h, const R
     const unsigned long long *live = r->live + (size_t)16 * (h - 1);
     auto stats = [&](int kind) { return STATS ? g->d_ctr + C_STATS + 4 * kind : nullptr; };
     const int walk = r->walk_exact ? 1 : 0;
-    Seen seen = W == 16 && !walk ? seen_levels(r, h) : Seen{};
+    Seen seen = W == 16 && (!walk || r->keep_visited) ? seen_levels(r, h) : Seen{};
     seen.sure = h > 1 && 2 * r->stats[(size_t)h - 2].entities_reached > (long long)(g->in_rows.n_tail + g->in_rows.n_long);
     if constexpr (W <= 4 && !STATS) {
         if (rc.n_seg + rc.n_tail == 0) return;
@@ -1450,7 +1470,7 @@ static void launch_pull_rows(logoskg_graph *g, logoskg_result *r, int h, const R
     if (rc.n_multi > 0) {
         ProfScope ps(g->prof, KK_PULL_FINISH, st);
         k_pull_finish<W><<<dim3(blocks_for(rc.n_multi * W, 256)), dim3(256), 0, st>>>(rc.multi, rc.n_multi,
-                                                                                      r->visited, cur, act_cur);
+                                                                                      r->visited, cur, act_cur, W < 16 || r->keep_visited);
     }
     }
 }
@@ -1797,6 +1817,8 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
     }
     int first_hop = 1;
     r->vis_levels = r->vis_dirty = W == 16 ? 1 : k + 1;  // the seeds
+    r->keep_visited = keeps_visited(g, r);
+    g->visited_asked = false;
     r->n_levels = 1;
     if (small && (s = small_search(g, r, b, want_counts, dir == LOGOSKG_DIR_PUSH, &first_hop, st)) != LOGOSKG_OK) return fail(s);
     if (!small) {
@@ -1830,11 +1852,7 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
         hs.direction = pull ? LOGOSKG_DIR_PULL : LOGOSKG_DIR_PUSH;
         unsigned long long hc[C_TOTAL] = {};
         memcpy(hc, g->h_ctr, C_STATS * sizeof(hc[0]));
-        if (W == 16 && !walk_exact) {
-            // a push asks visited, and so does a pulled hop with many levels behind it
-            const bool fold = !pull || h - r->vis_levels > kSeenLevels;
-            if (fold && (s = fold_visited(r, h, st)) != LOGOSKG_OK) return fail(s);
-        }
+        if (W == 16 && !walk_exact && !pull && (s = fold_visited(r, h, st)) != LOGOSKG_OK) return fail(s);
         if (want_stats)
             KH(hipMemsetAsync(g->d_ctr + C_STATS, 0, 4 * KK_NUM * sizeof(unsigned long long), st));
         if (g->num_shards > 1) {
@@ -1849,7 +1867,7 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
             KH(hipGetLastError());
         }
         r->n_levels = h + 1;
-        if (W == 16 && !walk_exact && !pull && h > 1) r->vis_levels = r->vis_dirty = h + 1;
+        if (W == 16 && (r->keep_visited || (!walk_exact && !pull && h > 1))) r->vis_levels = r->vis_dirty = h + 1;
         if (h == k && !want_stats) {  // (its counters only feed the statistics: read behind the counts)
             census_slot(g, h)[kCensusDone] = 0;
             if ((s = launch_census(g, r, h, pull, census_slot(g, h), nullptr, st)) != LOGOSKG_OK) return fail(s);
@@ -1897,6 +1915,7 @@ extern "C" logoskg_status logoskg_result_get_info(const logoskg_result *r, logos
     o->words_per_entity = r->W;
     o->num_levels = r->k + 1;
     o->padded_entities = r->Epad;
+    if (r->W == 16) r->g->visited_asked = true;
     if (!visited_by_search(r)) {  // on a stream of its own: the search has ended
         LKG_HIP(hipSetDevice(r->g->device));
         LKG_TRY(share_visited(const_cast<logoskg_result *>(r), r->g->side[0]));

@@ -561,7 +561,7 @@ __device__ __forceinline__ long long super_start(const FillArgs &a, long long st
 // keeps its word of all the block's tiles in registers (visited and the bit-sliced hop
 // number), and for one query at a time compacts the reached entities into LDS,
 // then streams them out with full-width stores.
-// NB = words of the bit-sliced hop number (0: entity ids only, planes of 1 and 4 words: see k_word_lists); TILES = tiles per block
+// NB = words of the bit-sliced hop number (0: entity ids only; of few words of 16-word planes: see k_word_lists); TILES = tiles per block
 // (launch_lists_w), at most half a super tile on 16-word planes, where the registers of a whole one
 // would not leave room for two blocks per CU.
 template <int W, int NB, int TILES>
@@ -3038,16 +3038,20 @@ extern "C" logoskg_status logoskg_result_fetch(logoskg_result *r, int32_t q0, in
             }
         }
     }
-    a.entity = entity; a.hop = hop; a.pred = pred;
+    a.entity = entity; a.hop = hop; a.pred = pred; a.entries = need;
     {   // mostly empty words: the lists by k_emit_sparse
         const long long words = (q1 - 1) / 64 - q0 / 64 + 1;
         a.sparse = need * kSparseShare <= a.ntiles * 64 * 64 * words;
     }
     const bool counting = g->prof.counters;
     // 16-word planes: the kernels that ask visited (all but the pair of walk and writer on a list of active entities)
-    if (!visited_by_search(r)) {
-        if (pred && a.row_pred && a.tile_ent && pred_uses_staged_kernel(a, W)) a.visited = nullptr;
-        else LKG_TRY(share_visited(r, st));
+    if (W == 16) {
+        if (pred && a.row_pred && a.tile_ent && pred_uses_staged_kernel(a, W)) {
+            a.visited = nullptr;
+        } else {
+            g->visited_asked = true;
+            LKG_TRY(share_visited(r, st));
+        }
     }
     // levels whose frontier holds at most a quarter of the triples: their long rows are resolved from the
     // subject side (resident graphs, row buffer in use, minimum-hop search); needs the triple index of
