@@ -1271,19 +1271,30 @@ static inline unsigned blocks_for(long long threads, int block) {
     return (unsigned)((threads + block - 1) / block);
 }
 
-// Most triples that may leave the frontier of a hop that pushes (direction by rule).  A twelfth of all where a pulled hop is three
-// kernels over whole lines.  On planes of one and four words it is one kernel, which without whitelists takes 1 ns per 25 triples
-// of the graph and more where the planes leave the caches, against two launches more and 0.4 ns per triple of the frontier for a
-// push: the times cross at 5,000 .. 10,000 triples of 3.4M, 50,000 .. 100,000 of 10M, 700,000 .. 900,000 of 30M
-// (one to 200 questions; 200 on 3.4M with 99,000 triples in the frontier: pushed 110 us, pulled 59), which is the square of the
-// graph's triples over 2^30.  Under whitelists most triples push nothing (the same: 72 and 67), and only four-word planes of
-// small graphs gain (0.8M: 70 and 59, 10M: 74 and 103).  Below kFewTriples searches hardly leave k_small_search.
-constexpr long long kFewTriples = 1 << 18, kMaskedPullTriples = 1 << 22;
+// Most triples that may leave the frontier of hop h where it pushes (direction by rule).  A twelfth of all where a pulled hop is three
+// kernels over whole lines.  On planes of one and four words it is one kernel over the graph, against two launches more and
+// what the frontier's triples cost for a push.  us of a search of one hop, 200 questions on concept graphs, pushed / pulled, by
+// triples in the frontier:
+//    triples     without whitelists                                                     with them
+//      0.3M      66:  87 /  72    1,001:  94 /  77    10,013: 110 /  90    30,000: 145 / 108      66:  91 /  75    30,000: 127 / 118
+//      0.8M      31:  84 /  72    1,021:  96 /  76    10,014: 113 /  89   100,069: 272 / 180      31:  85 /  75   100,069: 199 / 188
+//      1.6M      59:  85 /  77    1,003:  98 /  80    10,005: 114 /  94   100,000: 265 / 190      59:  88 /  81   100,000: 203 / 198
+//      3.4M      56:  88 /  85    1,000:  98 /  88    10,011: 113 / 100   100,019: 272 / 204      56:  90 / 100   100,019: 209 / 215
+//      3.4M hub   4:  85 /  93    1,029: 103 /  98    10,027: 110 / 110   100,001: 257 / 222       4:  89 / 110   100,001: 232 / 235
+//        6M       2:  92 /  99    1,000: 105 / 102    10,000: 113 / 113   100,008: 248 / 209       2:  99 / 116   100,008: 206 / 215
+//       10M       4: 104 / 118    1,019: 111 / 120    30,005: 149 / 153   100,008: 250 / 230       4: 105 / 141   100,008: 218 / 243
+// Without whitelists the line is the square of the graph's triples over 2^30, at or behind the crossings (30M: 700,000 ..
+// 900,000).  With them only four-word planes pull earlier: up to kMaskedPullTriples every frontier gains, from there to twice as
+// many a hop that is not the last, whose successor is then launched ahead of the host's turn (three hops on 3.4M, 7,107 triples
+// in the first frontier: 338 us pushed, 333 pulled), unless its frontier is next to nothing.  Below kFewTriples
+// one-word searches hardly leave k_small_search; four-word ones would gain as at 0.3M.
+constexpr long long kFewTriples = 1 << 18, kMaskedPullTriples = 1 << 21, kMaskedPullEdges = 1024;
 
-static long long push_most(const logoskg_graph *g, const logoskg_result *r) {
+static long long push_most(const logoskg_graph *g, const logoskg_result *r, int h) {
     const long long T = g->T, twelfth = T / 12;
     if (r->W == 16 || g->num_shards > 1 || T < kFewTriples) return twelfth;
-    if (r->has_mask) return r->W == 4 && T <= kMaskedPullTriples ? 0 : twelfth;
+    if (r->has_mask && (r->W == 1 || T > 2 * kMaskedPullTriples)) return twelfth;
+    if (r->has_mask) return T <= kMaskedPullTriples ? 0 : h < r->k ? kMaskedPullEdges : twelfth;
     return std::min(twelfth, T * T >> 30);  // (T < 2^31)
 }
 
@@ -1601,7 +1612,7 @@ static logoskg_status launch_census(logoskg_graph *g, logoskg_result *r, int h, 
         kernel<<<dim3(nb), dim3((unsigned)threads), 0, st>>>(r->act + (size_t)(r->Epad / 32) * h, g->E, g->out_off,
                                                              level_counters(r, h), g->d_ctr + C_TOTAL, host,
                                                              r->levels + (size_t)r->Epad * r->W * h, r->live + (size_t)16 * h,
-                                                             go, (long long)g->T, push_most(g, r), g->prof.counters ? 0 : r->Q);
+                                                             go, (long long)g->T, push_most(g, r, h + 1), g->prof.counters ? 0 : r->Q);
     };
     if (r->W == 16) launch(k_census<0, false>, 1024, kCensusEntities);
     else if (pulled) launch(r->W == 1 ? k_census<1, true> : k_census<4, true>, 512, 4);
@@ -1664,7 +1675,7 @@ static logoskg_status narrow_hops(logoskg_graph *g, logoskg_result *r, int first
         hs.active_rows = (long long)hc[C_NROWS];
         hs.frontier_edges = (long long)hc[C_FEDGES];
         hs.shards_touched = 1;
-        const bool pull = hs.frontier_edges > push_most(g, r);
+        const bool pull = hs.frontier_edges > push_most(g, r, h);
         hs.direction = pull ? LOGOSKG_DIR_PULL : LOGOSKG_DIR_PUSH;
         if (!pull) hs.edges_scanned = hs.lines_gathered = hs.frontier_edges;
         if (!running) {
@@ -1689,7 +1700,7 @@ static logoskg_status narrow_hops(logoskg_graph *g, logoskg_result *r, int first
         LKG_TRY(await_census(slot(h), st));
         memcpy(hc, slot(h), C_STATS * sizeof(hc[0]));
         hs.entities_reached = (long long)hc[C_NACTIVE];
-        running = ahead && (long long)hc[C_FEDGES] > push_most(g, r);
+        running = ahead && (long long)hc[C_FEDGES] > push_most(g, r, h + 1);
     }
     return LOGOSKG_OK;
 }
@@ -1848,7 +1859,7 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
         if (rows == 0) break;  // nothing can be reached any more: the remaining levels stay empty
         hs.active_rows = rows;
         hs.frontier_edges = fedges;
-        const bool pull = dir == LOGOSKG_DIR_PULL || (dir == LOGOSKG_DIR_AUTO && fedges > push_most(g, r));
+        const bool pull = dir == LOGOSKG_DIR_PULL || (dir == LOGOSKG_DIR_AUTO && fedges > push_most(g, r, h));
         hs.direction = pull ? LOGOSKG_DIR_PULL : LOGOSKG_DIR_PUSH;
         unsigned long long hc[C_TOTAL] = {};
         memcpy(hc, g->h_ctr, C_STATS * sizeof(hc[0]));

@@ -47,3 +47,28 @@ def test_rule(T, Q, masked):
             assert np.array_equal(at, a - a[0]) and np.array_equal(ent.cpu().numpy(), w_ent[a[0]:a[-1]])
         res.close()
     g.close()
+
+
+@pytest.mark.parametrize("T", [1 << 21, 3 << 20, 1 << 22, (1 << 22) + 1])
+def test_whitelists_about_the_size_up_to_which_four_words_pull(T):
+    import paper_2604_18913_amd as lkg
+    E, R, Q, k = 600_000, 6, 65, 3
+    rng = np.random.default_rng(T)
+    s, o = rng.integers(0, E, (2, T)).astype(np.int32)
+    r = rng.integers(0, R, T).astype(np.int32)
+    off = np.arange(Q + 1, dtype=np.int64)
+    seeds = rng.integers(0, E, Q).astype(np.int32)
+    mask = rng.integers(1, 2**R, (Q, 1)).astype(np.uint64)
+    want = oracle.khop(E, s, r, o, off, seeds, k, mask)
+    degree = np.bincount(s, minlength=E)
+    g = lkg.Graph(s, r, o, E, R)
+    res = g.khop(off, seeds, k, mask)
+    assert np.array_equal(res.offsets(), want[0])
+    for got, w in zip(res.fetch(), want[1:4]):
+        assert np.array_equal(got.cpu().numpy(), w)
+    for h, st in enumerate(res.hop_stats()):
+        edges = int(degree[np.unique(want[1][want[2] == h])].sum())
+        line = 0 if T == 1 << 21 else T // 12 if T > 1 << 22 or h == k - 1 else 1024
+        assert st["direction"] == lkg.binding.DIRECTIONS["pull" if edges > line else "push"], (h, edges)
+    res.close()
+    g.close()
