@@ -943,7 +943,8 @@ k_pull_tail(const ShortRow *__restrict__ rows, long long n, const int32_t *__res
         const unsigned long long nw = acc[r] & need[r];
         if (row_end[r] > lo[r] && group_any<W>(nw != 0)) {
             cur[(size_t)v[r] * W + lw] = nw;
-            if (W < 16 || seen.keep) visited[(size_t)v[r] * W + lw] = vis[r] | nw;
+            if (W < 16) visited[(size_t)v[r] * W + lw] = vis[r] | nw;
+            else if (seen.keep) visited[(size_t)v[r] * W + lw] |= nw;  // (read again: no register holds it through the row)
             if (lw == 0) atomicOr(&act_cur[v[r] >> 5], 1u << (v[r] & 31));
         }
     }
@@ -1029,7 +1030,8 @@ k_pull_seg(const PullSegment *__restrict__ segs, long long n,
             if (!multi) {
                 if (lane() < W) {
                     cur[(size_t)v * W + lane()] = nb;
-                    if (W < 16 || seen.keep) visited[(size_t)v * W + lane()] = vis | nb;
+                    if (W < 16) visited[(size_t)v * W + lane()] = vis | nb;
+                    else if (seen.keep) visited[(size_t)v * W + lane()] |= nb;
                 }
                 if (lane() == 0) atomicOr(&act_cur[v >> 5], 1u << (v & 31));
             } else if (lane() < W && nb) {
