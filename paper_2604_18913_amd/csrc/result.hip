@@ -2167,8 +2167,13 @@ k_emit_sparse(FillArgs a, const uint8_t *__restrict__ codes, const unsigned long
 // of dependent gathers that outlasts everything else in the launch; the segments of a row run side
 // by side, at the price of the early exit between them (it saved a quarter of the entries).
 // Under whitelists: where at most kFilterQueries queries are left, entries whose relation none of them may follow are left out
-// before their lines are asked for.
-constexpr int kFilterQueries = 24, kFilterRelations = 4096;
+// before their lines are asked for.  us of a fetch of 1,000 queries by that number (0: never); the relations' bits are what a
+// block has LDS for beside its queues (half a KB):
+//    30M triples        k = 2   0:   710    4:   712    12:   714    24:   730    48:   757    128:   784
+//                       k = 3   0: 2,027    4: 1,943    12: 1,944    24: 1,959    48: 1,982    128: 2,029
+//    hub-heavy 20M      k = 3   0: 3,302    4: 3,260    12: 3,231    24: 3,226    48: 3,232    128: 3,244
+//    3.4M               k = 3   0:   391    4:   373    12:   363    24:   361    48:   365    128:   371
+constexpr int kFilterQueries = 12, kFilterRelations = 4096;
 
 template <bool MASK, bool STATS, bool BUF, bool SEG = false>
 __global__ void __launch_bounds__(1024) k_pred_row(FillArgs a, long long first_row) {
