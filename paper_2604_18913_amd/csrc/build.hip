@@ -242,6 +242,7 @@ void set_segment_tables(RowClasses *rows, uint32_t *table) {
 static void drop_pairs(logoskg_graph *g) {
     for (void *x : {g->pairs.block, g->pairs.rows.block, (void *)g->pairs.long_index})
         if (x) (void)hipFree(x);
+    g->static_bytes -= g->pairs.bytes;
     g->pairs = PairRows();
 }
 
@@ -298,8 +299,11 @@ static logoskg_status row_classes(logoskg_graph *g, const uint32_t *d_off, bool 
 
 // The rows of distinct pairs with their work lists, where they are worth their room and there is some.
 static logoskg_status pair_rows(logoskg_graph *g, const int32_t *in_sub, const uint16_t *in_rel, const int32_t *in_eid, Scratch &tmp) {
+    const size_t before = g->static_bytes;
     LKG_TRY(build_pairs_on_device(g, in_sub, in_rel, in_eid, tmp));
-    if (g->pairs.off && row_classes(g, g->pairs.off, true, tmp, &g->pairs.rows) != LOGOSKG_OK) {
+    const bool listed = !g->pairs.off || row_classes(g, g->pairs.off, true, tmp, &g->pairs.rows) == LOGOSKG_OK;
+    g->pairs.bytes = g->static_bytes - before;
+    if (!listed) {
         (void)hipGetLastError();  // (the graph works without them)
         drop_pairs(g);
     }

@@ -169,6 +169,7 @@ struct RowClasses {             // device work lists over the object rows, split
 constexpr int kPairShare = 90;
 struct PairRows {
     void *block = nullptr;  // holds the arrays
+    size_t bytes = 0;       // of all that is held for them, counted in the graph's static_bytes
     uint32_t *off = nullptr;
     int32_t *pull_sub = nullptr, *sub = nullptr, *eid = nullptr;
     // every triple in pull_sub's order (rows as in_off has them), for pulled hops under whitelists: the first entries of all

@@ -2492,7 +2492,10 @@ logoskg_status prepare_row_pred(logoskg_graph *g, hipStream_t st) {
     k_long_index<<<dim3((unsigned)((g->in_rows.n_long + 255) / 256)), dim3(256), 0, st>>>(
         joined ? joined->longrows : g->in_rows.longrows, g->in_rows.n_long, g->long_index);
     if (g->pairs.off) {  // (no more rows than in_rows has; without room for it a fetch goes by all triples)
-        if (hipMalloc((void **)&g->pairs.long_index, (size_t)g->E * sizeof(int32_t)) == hipSuccess) {
+        const size_t bytes = (size_t)g->E * sizeof(int32_t);
+        if (hipMalloc((void **)&g->pairs.long_index, bytes) == hipSuccess) {
+            g->pairs.bytes += bytes;
+            g->static_bytes += bytes;
             LKG_HIP(hipMemsetAsync(g->pairs.long_index, 0xFF, (size_t)g->E * sizeof(int32_t), st));
             const long long n = (long long)g->pairs.rows.n_long;
             if (n > 0) k_long_index<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st>>>(g->pairs.rows.longrows, n, g->pairs.long_index);

@@ -1,0 +1,92 @@
+"""Memory of the rows of distinct (subject, object) pairs, which a graph can do without: what is counted for them, and calls that
+find no room but theirs.  Each test is a process of its own, with hip_memory.cpp or hip_limit.cpp in front of the runtime."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+HEAD = """
+import ctypes, sys
+sys.path[:0] = [sys.argv[2], sys.argv[3]]
+import numpy as np
+import torch
+torch.cuda.init()
+mem = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+for f in ("memory_watch", "memory_limit"):
+    if hasattr(mem, f):
+        getattr(mem, f).argtypes = [ctypes.c_size_t]
+for f in ("memory_peak", "memory_live"):
+    if hasattr(mem, f):
+        getattr(mem, f).restype = ctypes.c_size_t
+import oracle
+import paper_2604_18913_amd as lkg
+
+def graph(E, T, seed, share=0.5):  # a share of the triples repeats others' subject and object
+    rng = np.random.default_rng(seed)
+    n = int(T * (1 - share))
+    s, o = rng.integers(0, E, n), (E * rng.random(n) ** 4).astype(np.int64)  # rows of all lengths
+    again = rng.integers(0, n, T - n)
+    p = rng.permutation(T)
+    return rng, np.concatenate([s, s[again]])[p].astype(np.int32), rng.integers(0, 9, T).astype(np.int32), np.concatenate([o, o[again]])[p].astype(np.int32)
+
+def batch(rng, E, Q):
+    return np.arange(Q + 1, dtype=np.int64), rng.integers(0, E, Q).astype(np.int32)
+
+def same(res, want):
+    assert np.array_equal(res.offsets(), want[0])
+    assert all(np.array_equal(x.cpu().numpy(), y) for x, y in zip(res.fetch(), want[1:4]))
+"""
+
+
+def run(tmp_path, shim_source, code):
+    shim = tmp_path / "shim.so"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-o", str(shim), os.path.join(HERE, shim_source), "-ldl"],
+                   check=True, timeout=120)
+    p = subprocess.run([sys.executable, "-c", HEAD + code, str(shim), os.path.dirname(HERE), HERE], capture_output=True,
+                       text=True, timeout=110)
+    assert p.returncode == 0, p.stdout[-2000:] + p.stderr[-4000:]
+
+
+def test_device_bytes_follow_them(tmp_path):
+    run(tmp_path, "hip_memory.cpp", """
+E, T, Q, k = 30_000, 300_000, 300, 2
+rng, s, r, o = graph(E, T, 1)
+off, seeds = batch(rng, E, Q)
+want = oracle.khop(E, s, r, o, off, seeds, k)
+lkg.Graph(s, r, o, E, 9).close()
+mem.memory_watch(0)
+live = mem.memory_live()
+g = lkg.Graph(s, r, o, E, 9)
+held, counted = mem.memory_live() - live, g.info()["device_bytes"]
+assert 30 * T < counted <= held < counted + 64 * 1024, (held, counted)
+pairs = len(np.unique(s.astype(np.int64) * E + o))
+assert counted > 20 * T + 6 * T + 12 * pairs
+before = g.info()["device_bytes"]
+res = g.khop(off, seeds, k)
+pool = g.info()["device_bytes"]
+res.fetch()
+assert g.info()["device_bytes"] == pool + 4 * E  # their index
+same(res, want)
+res.close()
+g.close()
+# their work lists turned down: none of their bytes is left in what is counted
+hist = np.bincount(np.unique(s.astype(np.int64) * E + o) % E, minlength=E)
+seg, long_rows, multi = int(np.ceil(hist[hist > 32] / 1024).sum()), int((hist > 32).sum()), int((hist > 1024).sum())
+giant = hist[hist >= 8192]
+hubs = hist[hist >= 1024]
+table = 1 + len(giant) + 1 + (int(np.ceil(giant.max() / 8192)) if len(giant) else 0) + 1 + len(hubs)
+up = lambda b: (max(b, 4) + 15) // 16 * 16
+bytes_ = up(16 * seg) + up(4 * table) + up(4 * multi) + up(4 * long_rows) + 12 * int(((hist > 0) & (hist <= 32)).sum())
+mem.memory_watch(bytes_)
+live = mem.memory_live()
+g = lkg.Graph(s, r, o, E, 9)
+assert mem.memory_refusals() > 0, bytes_
+held, counted = mem.memory_live() - live, g.info()["device_bytes"]
+assert counted <= held < counted + 64 * 1024, (held, counted)
+same(g.khop(off, seeds, k), want)
+""")
