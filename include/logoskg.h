@@ -125,9 +125,11 @@ typedef struct {
     int64_t device_bytes;               /* HBM held by the graph (CSR, lists, shard cache; where
                                            parallel triples are a tenth and more of all and there is
                                            room also the object rows without them: 12 bytes per
-                                           distinct (subject, object) pair, 6 per triple; beside a
-                                           sharded graph's cache only when that is uncapped or its
-                                           budget holds them too)                          */
+                                           distinct (subject, object) pair, 6 per triple; an eighth
+                                           of the free memory at most, and given back for good when
+                                           an allocation of the graph finds no other, unless a
+                                           recorded fetch reads them; beside a sharded graph's cache
+                                           only when that is uncapped or its budget holds them too) */
     int64_t pinned_host_bytes;          /* pinned host memory held by the shards            */
     int64_t shard_loads, shard_evictions, shard_hits; /* cache counters since build (Sec. 3.4) */
     int64_t shard_bytes_h2d;

@@ -48,8 +48,8 @@ logoskg_status DevPool::alloc(void **out, size_t bytes, hipStream_t st, bool hav
     }
     void *p = nullptr;
     if (!raw_alloc(&p, bytes)) {
-        trim();  // give cached blocks back and retry once
-        if (!raw_alloc(&p, bytes)) {
+        trim();  // give cached blocks back and retry once, then what else there is
+        if (!raw_alloc(&p, bytes) && !(give_up_ && give_up_(give_up_ctx_) && raw_alloc(&p, bytes))) {
             set_error("device allocation of %zu bytes failed%s", bytes, alloc_fn_ ? " (caller's allocator)" : "");
             return LOGOSKG_ENOMEM;
         }
@@ -246,6 +246,28 @@ static void drop_pairs(logoskg_graph *g) {
     g->pairs = PairRows();
 }
 
+size_t most_pair_bytes(const logoskg_graph *g) { return (size_t)g->T * 18 + (size_t)g->E * 24; }
+
+bool give_up_pairs(logoskg_graph *g) {
+    if (!g->pairs.off || g->pairs.in_use || g->pairs.recorded) return false;
+    if (hipDeviceSynchronize() != hipSuccess) {  // (kernels that read them may be queued on any stream)
+        (void)hipGetLastError();
+        return false;
+    }
+    drop_pairs(g);
+    return true;
+}
+
+logoskg_status graph_alloc(logoskg_graph *g, void **p, size_t bytes) {
+    if (hipMalloc(p, bytes) == hipSuccess) return LOGOSKG_OK;
+    (void)hipGetLastError();
+    if (give_up_pairs(g) && hipMalloc(p, bytes) == hipSuccess) return LOGOSKG_OK;
+    (void)hipGetLastError();
+    *p = nullptr;
+    set_error("device allocation of %zu bytes failed", bytes);
+    return LOGOSKG_ENOMEM;
+}
+
 // Work lists over the rows of a CSR: short rows, segments of the longer ones (longest rows first; by_place:
 // the first segments of all rows, then the second ones, ..), rows with several segments, giant and hub rows' segments.
 static logoskg_status row_classes(logoskg_graph *g, const uint32_t *d_off, bool by_place, Scratch &tmp, RowClasses *rc) {
@@ -299,6 +321,12 @@ static logoskg_status row_classes(logoskg_graph *g, const uint32_t *d_off, bool 
 
 // The rows of distinct pairs with their work lists, where they are worth their room and there is some.
 static logoskg_status pair_rows(logoskg_graph *g, const int32_t *in_sub, const uint16_t *in_rel, const int32_t *in_eid, Scratch &tmp) {
+    constexpr size_t kNeverShort = (size_t)64 << 20;  // (a question to the runtime is 10 us)
+    if (most_pair_bytes(g) > kNeverShort) {
+        size_t free_bytes = 0, all_bytes = 0;
+        if (hipMemGetInfo(&free_bytes, &all_bytes) != hipSuccess) (void)hipGetLastError();
+        if (most_pair_bytes(g) > (free_bytes + scratch_bytes(&tmp)) / kPairRoom) return LOGOSKG_OK;
+    }
     const size_t before = g->static_bytes;
     LKG_TRY(build_pairs_on_device(g, in_sub, in_rel, in_eid, tmp));
     const bool listed = !g->pairs.off || row_classes(g, g->pairs.off, true, tmp, &g->pairs.rows) == LOGOSKG_OK;
@@ -368,6 +396,7 @@ extern "C" logoskg_status logoskg_build(const int32_t *subj, const int32_t *rel,
     g->Epad = ((int64_t)E + 63) / 64 * 64;
     g->hub_min = o.hub_min_degree > 0 ? std::max(o.hub_min_degree, kTailMaxDegree + 1) : kDefaultHubMin;
     g->num_shards = o.num_shards > 1 ? o.num_shards : 1;
+    g->pool.set_spare([](void *x) { return give_up_pairs(static_cast<logoskg_graph *>(x)); }, g);
     if (o.dev_alloc) g->pool.set_allocator(o.dev_alloc, o.dev_free, o.alloc_ctx);
 
     logoskg_status st = LOGOSKG_OK;
@@ -381,7 +410,13 @@ extern "C" logoskg_status logoskg_build(const int32_t *subj, const int32_t *rel,
         }
         // work lists over the rows of OBJ (pull and predecessor kernels), and the rows of distinct pairs with theirs
         auto object_rows = [&]() -> logoskg_status {
-            LKG_TRY(row_classes(g, g->in_off, false, *scratch, &g->in_rows));
+            logoskg_status s = row_classes(g, g->in_off, false, *scratch, &g->in_rows);
+            if (s == LOGOSKG_ENOMEM) {  // without the sorts' block, which is larger than what is left to do needs
+                (void)hipGetLastError();
+                scratch_release(scratch.get());
+                s = row_classes(g, g->in_off, false, *scratch, &g->in_rows);
+            }
+            LKG_TRY(s);
             return pair_rows(g, g->in_sub, g->in_rel, g->in_eid, *scratch);
         };
         auto subject_row_counts = [&]() -> logoskg_status {
@@ -463,7 +498,7 @@ extern "C" logoskg_status logoskg_build(const int32_t *subj, const int32_t *rel,
     }
 
     auto dev_alloc = [&](void **p, size_t bytes) -> logoskg_status {
-        LKG_HIP(hipMalloc(p, bytes));
+        LKG_TRY(graph_alloc(g, p, bytes));
         g->static_bytes += bytes;
         return LOGOSKG_OK;
     };

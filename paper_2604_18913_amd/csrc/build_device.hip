@@ -21,10 +21,7 @@ struct Scratch {
     std::vector<void *> ptrs;
     char *arena = nullptr;
     size_t size = 0, used = 0;
-    ~Scratch() {
-        for (void *p : ptrs)
-            if (p) (void)hipFree(p);
-    }
+    ~Scratch() { release(); }
     void reserve(size_t bytes) {  // (without room for it the pieces are taken by themselves)
         if (hipMalloc((void **)&arena, bytes) == hipSuccess) {
             ptrs.push_back(arena);
@@ -35,6 +32,13 @@ struct Scratch {
         }
     }
     void restart() { used = 0; }
+    void release() {
+        for (void *p : ptrs)
+            if (p) (void)hipFree(p);
+        ptrs.clear();
+        arena = nullptr;
+        size = used = 0;
+    }
     static size_t rounded(size_t bytes) { return (std::max<size_t>(bytes, 1) + 255) / 256 * 256; }
     template <typename T>
     logoskg_status get(T **p, size_t n) {
@@ -163,12 +167,22 @@ logoskg_status scratch_create(logoskg_graph *g, bool sorts, bool pairs, Scratch 
     if (pairs && T > 0) LKG_TRY(pair_sort_bytes(T, g->E, pair));
     const size_t for_sorts = sorts ? (size_t)T * 20 + csr : 0;
     const size_t for_pairs = pairs ? (size_t)T * 24 + (size_t)g->E * 16 + std::max({pair[0], pair[1], pair[2]}) : 0;
-    if (sorts || pairs) s->reserve(std::max(for_sorts, for_pairs) + 16 * 256);
+    size_t bytes = std::max(for_sorts, for_pairs) + 16 * 256;
+    constexpr size_t kNeverShort = (size_t)256 << 20;
+    if (bytes > kNeverShort) {  // no more than the sorts take where the graph's own arrays need the room
+        const size_t arrays = (size_t)T * 20 + (size_t)g->E * 40;
+        size_t free_bytes = 0, all_bytes = 0;
+        if (hipMemGetInfo(&free_bytes, &all_bytes) != hipSuccess) (void)hipGetLastError();
+        if (bytes + arrays + arrays / 8 > free_bytes) bytes = for_sorts ? for_sorts + 16 * 256 : 0;
+    }
+    if (bytes && (sorts || pairs)) s->reserve(bytes);
     *out = s.release();
     return LOGOSKG_OK;
 }
 
 void scratch_destroy(Scratch *s) { delete s; }
+void scratch_release(Scratch *s) { s->release(); }
+size_t scratch_bytes(const Scratch *s) { return s->size; }
 
 // Fills g->out_off/out_obj/out_rel/out_eid and g->in_off/in_sub/in_rel/in_eid from host triple arrays.
 logoskg_status build_csr_on_device(logoskg_graph *g, const int32_t *subj, const int32_t *rel, const int32_t *obj, Scratch &tmp) {
@@ -618,7 +632,11 @@ static logoskg_status build_out_eid(logoskg_graph *g, hipStream_t st) {
 // last error finds.
 logoskg_status ensure_out_eid(logoskg_graph *g, hipStream_t st) {
     if (g->out_eid) return LOGOSKG_OK;
-    const logoskg_status s = build_out_eid(g, st);
+    logoskg_status s = build_out_eid(g, st);
+    if (s == LOGOSKG_ENOMEM) {
+        (void)hipGetLastError();
+        if (give_up_pairs(g)) s = build_out_eid(g, st);
+    }
     if (s != LOGOSKG_OK) (void)hipGetLastError();
     return s;
 }

@@ -70,6 +70,11 @@ public:
         free_fn_ = free_fn;
         ctx_ = ctx;
     }
+    // what gives other memory back, true if there was any: asked when an allocation fails with nothing cached left
+    void set_spare(bool (*give_up)(void *), void *ctx) {
+        give_up_ = give_up;
+        give_up_ctx_ = ctx;
+    }
     ~DevPool();
 
 private:
@@ -84,6 +89,8 @@ private:
     void *(*alloc_fn_)(size_t, void *) = nullptr;
     void (*free_fn_)(void *, void *) = nullptr;
     void *ctx_ = nullptr;
+    bool (*give_up_)(void *) = nullptr;
+    void *give_up_ctx_ = nullptr;
     bool raw_alloc(void **p, size_t bytes);
     void raw_free(void *p);
 };
@@ -165,8 +172,10 @@ struct RowClasses {             // device work lists over the object rows, split
 // same rows (off): `sub` / `eid` by triple index, for the predecessor pass; `pull_sub` by the in-degree of the subject,
 // largest first, for pulled hops, which may take a row in any order and stop when nothing is missing: the subjects that
 // most queries have reached come first.  Built where at most kPairShare percent of the triples are left and there is
-// room; off is NULL otherwise.  (Distinct pairs of 30M triples of concepts 65 %, 3.4M 52 %, 300M hub-heavy ones 85 %.)
+// room (kPairRoom); off is NULL otherwise, also from when an allocation of the graph has found no memory but theirs
+// (give_up_pairs).  (Distinct pairs of 30M triples of concepts 65 %, 3.4M 52 %, 300M hub-heavy ones 85 %.)
 constexpr int kPairShare = 90;
+constexpr int kPairRoom = 8;  // they take at most this part of the device memory that is free when they are made
 struct PairRows {
     void *block = nullptr;  // holds the arrays
     size_t bytes = 0;       // of all that is held for them, counted in the graph's static_bytes
@@ -176,6 +185,8 @@ struct PairRows {
     // rows are the same few subjects, and parallel triples ask for one line after the other
     int32_t *all_sub = nullptr;
     uint16_t *all_rel = nullptr;
+    bool in_use = false;    // a call is about to launch what reads them
+    bool recorded = false;  // a recorded sequence reads them: they stay as long as the graph
     RowClasses rows;  // (segments by their place in the row: the first ones of all rows, the second ones, ..)
     int32_t *long_index = nullptr;  // as logoskg_graph::long_index
 };
@@ -549,6 +560,13 @@ struct FillArgs {
 struct Scratch;  // a build's device temporaries (build_device.hip)
 logoskg_status scratch_create(logoskg_graph *g, bool sorts, bool pairs, Scratch **out);
 void scratch_destroy(Scratch *s);
+void scratch_release(Scratch *s);  // gives its memory back
+size_t scratch_bytes(const Scratch *s);  // .. that it holds in one block
+// build.hip: the rows of distinct pairs go, where nothing needs them any more that has been launched or recorded: true if so
+bool give_up_pairs(logoskg_graph *g);
+size_t most_pair_bytes(const logoskg_graph *g);  // of the arrays, the work lists and the index
+// hipMalloc, with the memory of the distinct pairs where there is no other
+logoskg_status graph_alloc(logoskg_graph *g, void **p, size_t bytes);
 logoskg_status build_csr_on_device(logoskg_graph *g, const int32_t *subj, const int32_t *rel, const int32_t *obj, Scratch &tmp);
 // rows of a CSR on the device: with an entry, of more than kTailMaxDegree, of at least hub_min
 logoskg_status count_rows_on_device(const uint32_t *d_off, int32_t E, int hub_min, Scratch &tmp, unsigned int (&n)[3]);

@@ -1309,7 +1309,7 @@ static unsigned long long *level_counters(const logoskg_result *r, int h) {
 // for nothing), and one on a graph whose last result was asked for the plane, which would be made from the levels each time.
 // us of a search of 1,024 queries, without / with it:
 //    30M triples, 3M entities       k = 2:   471 /   533    3:   812 /   859    4: 1,210 / 1,189    5: 1,453 / 1,317    8: 1,696 / 1,444
-//    hub-heavy 20M, 2M entities     k = 2:   913 / 1,067    3: 1,425 / 1,512    4: 2,011 / 1,958    5: 2,663 / 2,392    8: 3,499 / 2,770
+//    hub-heavy 20M, 2M entities     k = 2:   913 / 1,067    3: 1,425 / 1,512    4: 2,011 / 1,958    5: 2,663 / 2,392    8: 3,499 / 2,860
 //    under whitelists               k = 2: 1,033 / 1,196    3: 1,706 / 1,842    4: 2,435 / 2,464    5: 3,137 / 2,965    8: 4,721 / 3,730
 //    with lists, 1M entities        k = 2:   777 /   800    3: 1,206 / 1,225    4: 1,436 / 1,427    407,000:  3: 680 / 682    4: 764 / 766
 //    200,000 entities               k = 2:   387 /   391    3:   500 /   494    4:   571 /   561    20,000:   3: 208 / 188    4: 270 / 244

@@ -2471,22 +2471,14 @@ logoskg_status prepare_row_pred(logoskg_graph *g, hipStream_t st) {
     // planes, or code bytes and visited words, between the two kernels of the bit-sliced predecessor pass: room
     // for every tile of the graph and 16 words, but not more than 1.25 GiB
     g->plane_buf_bytes = std::min<size_t>((size_t)5 << 28, (size_t)(g->Epad / 64 + kEmitTiles) * 16 * 64 * (64 + 8));
-    if (hipMalloc((void **)&g->plane_buf, g->plane_buf_bytes) != hipSuccess) {
-        (void)hipGetLastError();
-        g->plane_buf = nullptr;
-        g->plane_buf_bytes = 0;
-    }
+    if (graph_alloc(g, (void **)&g->plane_buf, g->plane_buf_bytes) != LOGOSKG_OK) g->plane_buf_bytes = 0;
     LKG_HIP(hipEventCreateWithFlags(&g->ev_rows, hipEventDisableTiming));
 
     const RowClasses *joined = joined_rows(g);  // (of a sharded graph)
     const long long rows = g->num_shards > 1 && !joined ? max_chunk_rows(g) : (long long)g->in_rows.n_long;
     if (rows <= 0 || (size_t)rows * 4096 > kRowPredBytes) return LOGOSKG_OK;
-    LKG_HIP(hipMalloc((void **)&g->long_index, (size_t)g->E * sizeof(int32_t)));
-    if (hipMalloc((void **)&g->row_pred, (size_t)rows * 4096) != hipSuccess) {
-        (void)hipGetLastError();
-        g->row_pred = nullptr;
-        return LOGOSKG_OK;
-    }
+    LKG_TRY(graph_alloc(g, (void **)&g->long_index, (size_t)g->E * sizeof(int32_t)));
+    if (graph_alloc(g, (void **)&g->row_pred, (size_t)rows * 4096) != LOGOSKG_OK) return LOGOSKG_OK;
     g->row_pred_rows = rows;
     LKG_HIP(hipMemsetAsync(g->long_index, 0xFF, (size_t)g->E * sizeof(int32_t), st));  // -1: not a long row
     k_long_index<<<dim3((unsigned)((g->in_rows.n_long + 255) / 256)), dim3(256), 0, st>>>(
@@ -3014,6 +3006,13 @@ extern "C" logoskg_status logoskg_result_fetch(logoskg_result *r, int32_t q0, in
     if (pred && W == 16) LKG_TRY(prepare_row_pred(g, st));
     // without whitelists the rows of distinct pairs (where the row buffer is used they need their own index)
     const bool pairs = !r->has_mask && g->pairs.off && g->num_shards <= 1 && !(pred && W == 16 && g->row_pred && !g->pairs.long_index);
+    // what is launched from here on may read the pairs: allocations on the way go without them, not the pairs
+    struct InUse {
+        bool &flag;
+        ~InUse() { flag = false; }
+    } in_use{g->pairs.in_use};
+    in_use.flag = true;
+    if (g->pairs.off && !r->has_mask && captured(st)) g->pairs.recorded = true;
     const RowClasses &in_rows = pairs ? g->pairs.rows : g->in_rows;
     a.in_off = pairs ? g->pairs.off : g->in_off;
     a.in_sub = pairs ? g->pairs.sub : g->in_sub;

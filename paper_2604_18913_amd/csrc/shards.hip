@@ -441,17 +441,16 @@ static logoskg_status build_in_chunks(logoskg_graph *g, ShardSet *ss, const int3
     return LOGOSKG_OK;
 }
 
-// The work lists over all object ranges when the predecessor pass runs over them in one piece: the cache
-// holds every unit and the row buffer of all long rows stays within its limit.  NULL otherwise.
-// The distinct pairs of a sharded graph: 18 bytes per triple at most, beside a cache that holds everything, unless the caller's
-// limits leave no room for them.
+// The distinct pairs of a sharded graph, beside a cache that holds everything, unless the caller's limits leave no room for them.
 bool pairs_beside_shards(const logoskg_graph *g, const logoskg_build_opts *opts) {
     const ShardSet *ss = (const ShardSet *)g->shards;
     if (!ss || !ss->joined || opts->max_resident_shards > 0) return false;
     const uint64_t units = ss->slot_edges * 6 * (uint64_t)ss->units();  // (as the budget counts them)
-    return opts->hbm_shard_budget_bytes == 0 || units + 18 * (uint64_t)g->T <= opts->hbm_shard_budget_bytes;
+    return opts->hbm_shard_budget_bytes == 0 || units + most_pair_bytes(g) <= opts->hbm_shard_budget_bytes;
 }
 
+// The work lists over all object ranges when the predecessor pass runs over them in one piece: the cache
+// holds every unit and the row buffer of all long rows stays within its limit.  NULL otherwise.
 const RowClasses *joined_rows(const logoskg_graph *g) {
     const ShardSet *ss = (const ShardSet *)g->shards;
     if (!ss || !ss->joined || (size_t)ss->all_rows.n_long * 4096 > kRowPredBytes) return nullptr;

@@ -90,3 +90,91 @@ held, counted = mem.memory_live() - live, g.info()["device_bytes"]
 assert counted <= held < counted + 64 * 1024, (held, counted)
 same(g.khop(off, seeds, k), want)
 """)
+
+
+LIMITED = """
+E, T, k = 60_000, 1_200_000, 3
+rng, s, r, o = graph(E, T, 2)
+"""
+
+
+@pytest.mark.parametrize("Q", [40, 200, 300])
+def test_calls_that_find_no_room_but_theirs(tmp_path, Q):
+    run(tmp_path, "hip_limit.cpp", f"Q = {Q}" + LIMITED + """
+off, seeds = batch(rng, E, Q)
+want = oracle.khop(E, s, r, o, off, seeds, k)
+out = [torch.empty(want[0][-1], dtype=t, device="cuda") for t in (torch.int32, torch.uint8, torch.int32)]
+off, seeds = torch.from_numpy(off).cuda(), torch.from_numpy(seeds).cuda()
+pairs = 6 * T + 12 * len(np.unique(s.astype(np.int64) * E + o))
+
+def search_and_fetch(g):
+    res = g.khop(off, seeds, k)
+    res.fetch(out=out)
+    torch.cuda.synchronize()
+    assert np.array_equal(res.offsets(), want[0])
+    assert all(np.array_equal(x.cpu().numpy(), y) for x, y in zip(out, want[1:4]))
+    res.close()
+
+g = lkg.Graph(s, r, o, E, 9)
+mem.memory_limit(0)
+live = mem.memory_live()
+search_and_fetch(g)
+needs = mem.memory_peak() - live
+g.close()
+for short in (1 << 16, min(pairs, needs) * 3 // 4):
+    g = lkg.Graph(s, r, o, E, 9)
+    held = g.info()["device_bytes"]
+    assert held > 20 * T + pairs
+    mem.memory_limit(mem.memory_live() + needs - short)
+    for _ in range(3):
+        search_and_fetch(g)
+    mem.memory_limit(0)
+    g.close()
+""")
+
+
+def test_recorded_fetches_keep_them(tmp_path):
+    run(tmp_path, "hip_limit.cpp", LIMITED + """
+Q = 300
+off, seeds = batch(rng, E, Q)
+want = oracle.khop(E, s, r, o, off, seeds, k)
+g = lkg.Graph(s, r, o, E, 9)
+res = g.khop(off, seeds, k)
+same(res, want)
+out = [torch.zeros(want[0][-1], dtype=t, device="cuda") for t in (torch.int32, torch.uint8, torch.int32)]
+torch.cuda.synchronize()
+stream, recorded = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+with torch.cuda.graph(recorded, stream=stream):
+    res.fetch(out=out, stream=stream)
+held = g.info()["device_bytes"]
+mem.memory_limit(mem.memory_live() + (1 << 20))
+try:
+    g.khop(off, seeds, k)
+    raise SystemExit("a second result had no room")
+except lkg.LogosKGError as e:
+    assert e.status == 2, e
+mem.memory_limit(0)
+assert g.info()["device_bytes"] > 20 * T + 12 * T // 2
+for _ in range(3):
+    for x in out:
+        x.zero_()
+    recorded.replay()
+    torch.cuda.synchronize()
+    assert all(np.array_equal(x.cpu().numpy(), y) for x, y in zip(out, want[1:4]))
+""")
+
+
+def test_builds_on_a_small_device(tmp_path):
+    run(tmp_path, "hip_limit.cpp", """
+E, T, Q, k = 100_000, 6_000_000, 100, 2
+rng, s, r, o = graph(E, T, 3)
+off, seeds = batch(rng, E, Q)
+want = oracle.khop(E, s, r, o, off, seeds, k)
+for per_triple, kept in ((70, False), (400, True)):   # the sorts and the arrays need fifty bytes per triple
+    mem.memory_limit(mem.memory_live() + per_triple * T)
+    g = lkg.Graph(s, r, o, E, 9)
+    assert (g.info()["device_bytes"] > 26 * T) == kept, g.info()["device_bytes"] / T
+    same(g.khop(off, seeds, k), want)
+    g.close()
+    mem.memory_limit(0)
+""")
