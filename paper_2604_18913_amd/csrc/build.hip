@@ -177,12 +177,13 @@ void Profiler::release() {
     spare.clear();
 }
 
-// The helper streams (two for the fetch's side work, one for shard copies) are made once per
+// The helper streams (two for the fetch's side work, one for shard copies, one for a plane that is
+// made while those are part of a recorded sequence) are made once per
 // device and shared by every graph on it; they live until the process ends.  Work of different
 // graphs on one helper stream is only serialised: every dependency goes through events.
 hipStream_t helper_stream(int device, int which) {
     static std::mutex mu;
-    static std::map<int, std::array<hipStream_t, 3>> table;
+    static std::map<int, std::array<hipStream_t, 4>> table;
     std::lock_guard<std::mutex> lock(mu);
     auto &row = table[device];  // value-initialised to null handles
     if (!row[which] && hipStreamCreateWithFlags(&row[which], hipStreamNonBlocking) != hipSuccess) {

@@ -1367,6 +1367,25 @@ logoskg_status share_visited(logoskg_result *r, hipStream_t st) {
     return LOGOSKG_OK;
 }
 
+// The same for the host, on a helper stream: the search has ended.  Callers may be recording a sequence meanwhile, to which
+// nothing of this belongs and which a wait would end in the runtime's usual mode; a recorded fetch may have drawn the
+// helper streams into it.
+static logoskg_status finish_visited(logoskg_result *r) {
+    LKG_HIP(hipSetDevice(r->g->device));
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    LKG_HIP(hipThreadExchangeStreamCaptureMode(&mode));
+    hipStream_t st = r->g->side[0];
+    if (captured(st)) st = helper_stream(r->g->device, 3);
+    logoskg_status s = LOGOSKG_EDEVICE;
+    if (!st) set_error("could not create a helper stream");
+    else s = share_visited(r, st);
+    const hipError_t e = s == LOGOSKG_OK ? hipStreamSynchronize(st) : hipSuccess;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    LKG_TRY(s);
+    LKG_HIP(e);
+    return LOGOSKG_OK;
+}
+
 template <int W, bool MASK>
 static void launch_push(logoskg_graph *g, logoskg_result *r, int h, const unsigned long long *hc,
                         const int32_t *obj, const uint16_t *rel, bool update, const int32_t *list_tail,
@@ -1929,11 +1948,7 @@ extern "C" logoskg_status logoskg_result_get_info(const logoskg_result *r, logos
     o->num_levels = r->k + 1;
     o->padded_entities = r->Epad;
     if (r->W == 16) r->g->visited_asked = true;
-    if (!visited_by_search(r)) {  // on a stream of its own: the search has ended
-        LKG_HIP(hipSetDevice(r->g->device));
-        LKG_TRY(share_visited(const_cast<logoskg_result *>(r), r->g->side[0]));
-        LKG_HIP(hipStreamSynchronize(r->g->side[0]));
-    }
+    if (!visited_by_search(r)) LKG_TRY(finish_visited(const_cast<logoskg_result *>(r)));
     o->visited = (const uint64_t *)r->visited;
     o->levels = (const uint64_t *)r->levels;
     o->total_reached = r->has_counts ? r->reached_off.back() : -1;

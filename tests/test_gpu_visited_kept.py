@@ -105,3 +105,35 @@ def test_lists_without_predecessors_and_a_recorded_fetch():
         assert np.array_equal(out[0].cpu().numpy(), want[1]) and np.array_equal(out[1].cpu().numpy(), want[2])
     res.close()
     g.close()
+
+
+@pytest.mark.parametrize("overlap", ["0", "1"])
+def test_get_info_while_a_fetch_is_recorded(monkeypatch, overlap):
+    import torch
+    import paper_2604_18913_amd as lkg
+    monkeypatch.setenv("LOGOSKG_OVERLAP_FETCH", overlap)
+    E, k = 1 << 18, 3
+    s, r, o, off, seeds = problem(13, E, 40_000)
+    g = lkg.Graph(s, r, o, E, 8)
+    want = oracle.khop(E, s, r, o, off, seeds, k)
+    g.khop(off, seeds, k).fetch()
+    res = g.khop(off, seeds, k)  # (its plane is not kept)
+    out = [torch.zeros(want[0][-1], dtype=t, device="cuda") for t in (torch.int32, torch.uint8, torch.int32)]
+    torch.cuda.synchronize()
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        res.fetch(out=out, stream=stream)
+        info = res._info()
+    n = (E + 63) // 64 * 64 * 16
+    levels = plane(info.levels, n * (k + 1)).reshape(k + 1, n)
+    assert np.array_equal(plane(info.visited, n), np.bitwise_or.reduce(levels, 0))
+    for _ in range(3):
+        for x in out:
+            x.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        for x, y in zip(out, want[1:4]):
+            assert np.array_equal(x.cpu().numpy(), y)
+    del graph
+    res.close()
+    g.close()
