@@ -269,12 +269,62 @@ logoskg_status graph_alloc(logoskg_graph *g, void **p, size_t bytes) {
     return LOGOSKG_ENOMEM;
 }
 
+// The rows of small graphs are counted and classified here: the device's way is a dozen launches and three waits.  us of a build
+// with them on the device / here, by entities: 5,000: 738 / 598; 10,000: 909 / 816; 25,000: 1,237 / 1,252 and (hub-heavy)
+// 1,577 / 1,491; 60,000: 1,026 / 1,127; 407,000: 7,614 / 11,019.
+constexpr int32_t kHostRows = 1 << 14;
+
+static logoskg_status read_offsets(const uint32_t *d_off, int32_t E, std::vector<uint32_t> *off) {
+    off->resize((size_t)E + 1);
+    LKG_HIP(hipMemcpy(off->data(), d_off, ((size_t)E + 1) * 4, hipMemcpyDeviceToHost));
+    return LOGOSKG_OK;
+}
+
+// rows with an entry, of more than kTailMaxDegree, of at least hub_min
+static logoskg_status count_rows(const logoskg_graph *g, const uint32_t *d_off, Scratch &tmp, unsigned int (&n)[3]) {
+    if (g->E > kHostRows) return count_rows_on_device(d_off, g->E, g->hub_min, tmp, n);
+    std::vector<uint32_t> off;
+    LKG_TRY(read_offsets(d_off, g->E, &off));
+    n[0] = n[1] = n[2] = 0;
+    for (int32_t e = 0; e < g->E; ++e) {
+        const uint32_t d = off[(size_t)e + 1] - off[e];
+        n[0] += d > 0;
+        n[1] += d > (uint32_t)kTailMaxDegree;
+        n[2] += d >= (uint32_t)g->hub_min;
+    }
+    return LOGOSKG_OK;
+}
+
+// classify_on_device's lists, the short rows on the host as well
+static logoskg_status classify_on_host(const logoskg_graph *g, const uint32_t *d_off, RowClasses *rc, std::vector<ShortRow> *tail, std::vector<ShortRow> *longer) {
+    std::vector<uint32_t> off;
+    LKG_TRY(read_offsets(d_off, g->E, &off));
+    uint32_t at[kTailMaxDegree + 2] = {};  // of the rows of d entries at [kTailMaxDegree - d + 1], then where they begin
+    rc->n_hub = 0;
+    for (int32_t e = 0; e < g->E; ++e) {
+        const uint32_t d = off[(size_t)e + 1] - off[e];
+        if (d > (uint32_t)kTailMaxDegree) longer->push_back({e, off[e], off[(size_t)e + 1]});
+        else if (d > 0) ++at[kTailMaxDegree - d + 1];
+        rc->n_hub += d >= (uint32_t)g->hub_min;
+    }
+    for (int i = 1; i <= kTailMaxDegree; ++i) at[i] += at[i - 1];
+    rc->n_tail = at[kTailMaxDegree];
+    tail->resize((size_t)rc->n_tail);
+    for (int32_t e = 0; e < g->E; ++e) {
+        const uint32_t d = off[(size_t)e + 1] - off[e];
+        if (d > 0 && d <= (uint32_t)kTailMaxDegree) (*tail)[at[kTailMaxDegree - d]++] = {e, off[e], off[(size_t)e + 1]};
+    }
+    return LOGOSKG_OK;
+}
+
 // Work lists over the rows of a CSR: short rows, segments of the longer ones (longest rows first; by_place:
 // the first segments of all rows, then the second ones, ..), rows with several segments, giant and hub rows' segments.
 static logoskg_status row_classes(logoskg_graph *g, const uint32_t *d_off, bool by_place, Scratch &tmp, RowClasses *rc) {
-    std::vector<ShortRow> longer;
+    std::vector<ShortRow> longer, tail;
     ShortRow *records = nullptr;
-    LKG_TRY(classify_on_device(d_off, g->E, g->hub_min, tmp, rc, &records, &longer));
+    const bool on_host = g->E <= kHostRows;
+    if (on_host) LKG_TRY(classify_on_host(g, d_off, rc, &tail, &longer));
+    else LKG_TRY(classify_on_device(d_off, g->E, g->hub_min, tmp, rc, &records, &longer));
     std::stable_sort(longer.begin(), longer.end(), [](const ShortRow &a, const ShortRow &b) { return a.end - a.begin > b.end - b.begin; });
     std::vector<int32_t> rows, multi;
     std::vector<PullSegment> seg;
@@ -305,17 +355,18 @@ static logoskg_status row_classes(logoskg_graph *g, const uint32_t *d_off, bool 
         return at;
     };
     const size_t at_seg = put(seg.data(), seg.size() * sizeof(PullSegment)), at_table = put(table.data(), table.size() * 4),
-                 at_multi = put(multi.data(), multi.size() * 4), at_rows = put(rows.data(), rows.size() * 4);
-    const size_t bytes = image.size() + (size_t)rc->n_tail * sizeof(ShortRow);
-    LKG_HIP(hipMalloc(&rc->block, bytes));
-    g->static_bytes += bytes;
+                 at_multi = put(multi.data(), multi.size() * 4), at_rows = put(rows.data(), rows.size() * 4), at_tail = image.size();
+    const size_t bytes = at_tail + (size_t)rc->n_tail * sizeof(ShortRow);
+    if (on_host) put(tail.data(), tail.size() * sizeof(ShortRow));
+    LKG_HIP(hipMalloc(&rc->block, std::max(bytes, image.size())));
+    g->static_bytes += std::max(bytes, image.size());
     char *const base = static_cast<char *>(rc->block);
     rc->seg = reinterpret_cast<PullSegment *>(base + at_seg);
     set_segment_tables(rc, reinterpret_cast<uint32_t *>(base + at_table));
     rc->multi = reinterpret_cast<int32_t *>(base + at_multi);
     rc->longrows = reinterpret_cast<int32_t *>(base + at_rows);
-    rc->tail = reinterpret_cast<ShortRow *>(base + image.size());
-    if (rc->n_tail) LKG_HIP(hipMemcpyAsync(rc->tail, records, (size_t)rc->n_tail * sizeof(ShortRow), hipMemcpyDeviceToDevice, nullptr));
+    rc->tail = reinterpret_cast<ShortRow *>(base + at_tail);
+    if (rc->n_tail && !on_host) LKG_HIP(hipMemcpyAsync(rc->tail, records, (size_t)rc->n_tail * sizeof(ShortRow), hipMemcpyDeviceToDevice, nullptr));
     LKG_HIP(hipMemcpy(base, image.data(), image.size(), hipMemcpyHostToDevice));
     return LOGOSKG_OK;
 }
@@ -406,7 +457,7 @@ extern "C" logoskg_status logoskg_build(const int32_t *subj, const int32_t *rel,
         std::unique_ptr<Scratch, void (*)(Scratch *)> scratch(nullptr, scratch_destroy);
         {
             Scratch *x = nullptr;
-            if ((st = scratch_create(g, device_build, g->num_shards <= 1, &x)) != LOGOSKG_OK) return fail(st);
+            if ((st = scratch_create(g, device_build, &x)) != LOGOSKG_OK) return fail(st);
             scratch.reset(x);
         }
         // work lists over the rows of OBJ (pull and predecessor kernels), and the rows of distinct pairs with theirs
@@ -418,11 +469,12 @@ extern "C" logoskg_status logoskg_build(const int32_t *subj, const int32_t *rel,
                 s = row_classes(g, g->in_off, false, *scratch, &g->in_rows);
             }
             LKG_TRY(s);
-            return pair_rows(g, g->in_sub, g->in_rel, g->in_eid, *scratch);
+            // (a build on the host takes no more of the device than its arrays; the sort of the pairs is 24 bytes per triple)
+            return device_build ? pair_rows(g, g->in_sub, g->in_rel, g->in_eid, *scratch) : LOGOSKG_OK;
         };
         auto subject_row_counts = [&]() -> logoskg_status {
             unsigned int n[3];
-            LKG_TRY(count_rows_on_device(g->out_off, E, g->hub_min, *scratch, n));
+            LKG_TRY(count_rows(g, g->out_off, *scratch, n));
             g->n_out_rows = n[0];
             g->n_out_hubs = n[2];
             return LOGOSKG_OK;
@@ -498,17 +550,18 @@ extern "C" logoskg_status logoskg_build(const int32_t *subj, const int32_t *rel,
         return fail(LOGOSKG_ENOMEM);
     }
 
-    auto dev_alloc = [&](void **p, size_t bytes) -> logoskg_status {
-        LKG_TRY(graph_alloc(g, p, bytes));
-        g->static_bytes += bytes;
-        return LOGOSKG_OK;
-    };
     g->fr_seg_cap = (int64_t)E + T / kPushSegment + 64;  // every long row adds < deg/segment + 1 items
-    if ((st = dev_alloc((void **)&g->fr_tail, (size_t)E * sizeof(int32_t))) != LOGOSKG_OK) return fail(st);
-    if ((st = dev_alloc((void **)&g->fr_seg, (size_t)g->fr_seg_cap * sizeof(RowSegment))) != LOGOSKG_OK) return fail(st);
     constexpr size_t dev_ctr = C_TOTAL + kCensusWords * kCensusBlocks;
     const size_t ticket_bytes = (size_t)(g->Epad / (kTileEntities * kSuperTiles * kMegaSupers) + 2) * sizeof(unsigned int);
-    if ((st = dev_alloc((void **)&g->d_ctr, dev_ctr * sizeof(unsigned long long) + ticket_bytes)) != LOGOSKG_OK) return fail(st);
+    auto rounded = [](size_t bytes) { return (bytes + 255) / 256 * 256; };
+    const size_t of_ctr = rounded(dev_ctr * sizeof(unsigned long long) + ticket_bytes), of_tail = rounded((size_t)E * sizeof(int32_t)),
+                 of_lists = of_ctr + of_tail + (size_t)g->fr_seg_cap * sizeof(RowSegment);
+    char *lists = nullptr;
+    if ((st = graph_alloc(g, (void **)&lists, of_lists)) != LOGOSKG_OK) return fail(st);
+    g->static_bytes += of_lists;
+    g->d_ctr = reinterpret_cast<unsigned long long *>(lists);
+    g->fr_tail = reinterpret_cast<int32_t *>(lists + of_ctr);
+    g->fr_seg = reinterpret_cast<RowSegment *>(lists + of_ctr + of_tail);
     g->count_tickets = reinterpret_cast<unsigned int *>(g->d_ctr + dev_ctr);
     if (hipMemset(g->count_tickets, 0, ticket_bytes) != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess) {
         set_error("hipMemset failed");
@@ -553,9 +606,15 @@ extern "C" void logoskg_graph_free(logoskg_graph *g) {
     if (g->ev_fork) (void)hipEventDestroy(g->ev_fork);
     if (g->ev_rows) (void)hipEventDestroy(g->ev_rows);
 
+    if (g->csr_block) {
+        (void)hipFree(g->csr_block);
+        g->out_off = g->in_off = nullptr;
+        g->out_obj = g->out_eid = g->in_sub = g->in_eid = nullptr;
+        g->out_rel = g->in_rel = nullptr;
+    }
     void *ptrs[] = {g->out_off, g->out_obj, g->out_rel, g->in_off, g->in_sub, g->in_rel, g->in_eid,
-                    g->in_rows.block, g->in_rows.block ? nullptr : (void *)g->in_rows.longrows, g->fr_tail,
-                    g->fr_seg, g->d_ctr, g->long_index, g->row_pred, g->out_eid, g->plane_buf};
+                    g->in_rows.block, g->in_rows.block ? nullptr : (void *)g->in_rows.longrows,
+                    g->d_ctr, g->long_index, g->row_pred, g->out_eid, g->plane_buf};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     drop_pairs(g);

@@ -152,30 +152,34 @@ static logoskg_status pair_sort_bytes(int64_t T, int32_t E, size_t (&bytes)[3]) 
     uint32_t *none = nullptr;
     LKG_HIP(rocprim::radix_sort_pairs(nullptr, bytes[0], b.keys, b.vals, (size_t)T, 0u, 2 * bits_for(E)));
     LKG_HIP(rocprim::radix_sort_pairs_desc(nullptr, bytes[1], b.degrees, b.ids, (size_t)E, 0u, 32u));
-    LKG_HIP(rocprim::inclusive_scan(nullptr, bytes[2], none, none, (size_t)T, rocprim::plus<uint32_t>()));
+    LKG_HIP(rocprim::inclusive_scan(nullptr, bytes[2], none, none, 2 * (size_t)T, rocprim::plus<uint32_t>()));
     return LOGOSKG_OK;
 }
 
-// One block for the temporaries of a resident graph's build: the two sorts' (where they run here), then the distinct pairs'.
-logoskg_status scratch_create(logoskg_graph *g, bool sorts, bool pairs, Scratch **out) {
+// One block for the temporaries of a resident graph's build on the device: the two sorts', then the distinct pairs'.
+logoskg_status scratch_create(logoskg_graph *g, bool resident, Scratch **out) {
     *out = nullptr;
     std::unique_ptr<Scratch> s(new (std::nothrow) Scratch());
     if (!s) { set_error("out of host memory"); return LOGOSKG_ENOMEM; }
     const int64_t T = g->T;
+    if (!resident) {
+        *out = s.release();
+        return LOGOSKG_OK;
+    }
     size_t csr = 0, pair[3] = {};
-    if (sorts) LKG_TRY(csr_sort_bytes(T, g->E, &csr));
-    if (pairs && T > 0) LKG_TRY(pair_sort_bytes(T, g->E, pair));
-    const size_t for_sorts = sorts ? (size_t)T * 20 + csr : 0;
-    const size_t for_pairs = pairs ? (size_t)T * 24 + (size_t)g->E * 16 + std::max({pair[0], pair[1], pair[2]}) : 0;
+    LKG_TRY(csr_sort_bytes(T, g->E, &csr));
+    if (T > 0) LKG_TRY(pair_sort_bytes(T, g->E, pair));
+    const size_t for_sorts = (size_t)T * 20 + csr;
+    const size_t for_pairs = (size_t)T * 24 + (size_t)g->E * 16 + std::max({pair[0], pair[1], pair[2]});
     size_t bytes = std::max(for_sorts, for_pairs) + 16 * 256;
     constexpr size_t kNeverShort = (size_t)256 << 20;
     if (bytes > kNeverShort) {  // no more than the sorts take where the graph's own arrays need the room
         const size_t arrays = (size_t)T * 20 + (size_t)g->E * 40;
         size_t free_bytes = 0, all_bytes = 0;
         if (hipMemGetInfo(&free_bytes, &all_bytes) != hipSuccess) (void)hipGetLastError();
-        if (bytes + arrays + arrays / 8 > free_bytes) bytes = for_sorts ? for_sorts + 16 * 256 : 0;
+        if (bytes + arrays + arrays / 8 > free_bytes) bytes = for_sorts + 16 * 256;
     }
-    if (bytes && (sorts || pairs)) s->reserve(bytes);
+    s->reserve(bytes);
     *out = s.release();
     return LOGOSKG_OK;
 }
@@ -221,11 +225,25 @@ logoskg_status build_csr_on_device(logoskg_graph *g, const int32_t *subj, const 
     char *d_tmp = nullptr;
     LKG_TRY(tmp.get(&d_tmp, tmp_bytes));
 
+    // (the arrays of a small graph are one allocation: eight of them are 60 us of a build of half a millisecond)
+    constexpr size_t kSmallArrays = (size_t)16 << 20;
+    const size_t all = 2 * Scratch::rounded(((size_t)E + 1) * 4) + 4 * Scratch::rounded((size_t)T * 4) + 2 * Scratch::rounded((size_t)T * 2);
+    char *at = nullptr;
     auto keep = [&](void **p, size_t bytes) -> logoskg_status {
+        if (g->csr_block) {
+            *p = at;
+            at += Scratch::rounded(bytes);
+            return LOGOSKG_OK;
+        }
         LKG_HIP(hipMalloc(p, std::max<size_t>(bytes, 4)));
         g->static_bytes += std::max<size_t>(bytes, 4);
         return LOGOSKG_OK;
     };
+    if (all <= kSmallArrays) {
+        LKG_HIP(hipMalloc(&g->csr_block, all));
+        g->static_bytes += all;
+        at = static_cast<char *>(g->csr_block);
+    }
     // Both sorts leave the triple indices where the graph keeps them, so that they need no column of their own beside
     // it (40 bytes per triple and the sort's buffers at the peak; 44 with one).
     // SUB: rows by subject
@@ -269,11 +287,22 @@ __global__ void k_rank_of(const uint32_t *__restrict__ by_rank, int32_t E, uint3
     if (i < E) rank_of[by_rank[i]] = (uint32_t)i;
 }
 
-__global__ void k_pair_keys(const uint32_t *__restrict__ obj_of, const int32_t *__restrict__ in_sub,
+// (obj_of NULL: the last row that begins at or before p; rank_of NULL: the subjects by id)
+__global__ void k_pair_keys(const uint32_t *__restrict__ obj_of, const uint32_t *__restrict__ off, int32_t E, const int32_t *__restrict__ in_sub,
                             const uint32_t *__restrict__ rank_of, long long T, unsigned bits, unsigned long long *key, uint32_t *pos) {
     const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= T) return;
-    key[p] = ((unsigned long long)obj_of[p] << bits) | rank_of[in_sub[p]];
+    uint32_t o = 0;
+    if (obj_of) {
+        o = obj_of[p];
+    } else {
+        for (uint32_t hi = (uint32_t)E; hi - o > 1;) {
+            const uint32_t m = o + (hi - o) / 2;
+            if (off[m] <= p) o = m; else hi = m;
+        }
+    }
+    const uint32_t s = (uint32_t)in_sub[p];
+    key[p] = ((unsigned long long)o << bits) | (rank_of ? rank_of[s] : s);
     pos[p] = (uint32_t)p;
 }
 
@@ -287,7 +316,7 @@ __global__ void k_pair_flags(const unsigned long long *__restrict__ key, const u
     is_first[pos[i]] = n;
 }
 
-// (the flags have become inclusive prefix sums)
+// (the flags have become inclusive prefix sums, is_first's behind is_new's)
 __global__ void k_pair_rows(const uint32_t *__restrict__ off, int32_t E, const uint32_t *__restrict__ new_upto, uint32_t *pair_off) {
     const int32_t e = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
     if (e <= E) pair_off[e] = off[e] ? new_upto[off[e] - 1] : 0u;
@@ -300,16 +329,22 @@ __global__ void k_pair_fill(const unsigned long long *__restrict__ key, const ui
                             const uint32_t *__restrict__ pos, const uint16_t *__restrict__ in_rel, int32_t *all_sub, uint16_t *all_rel) {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= T) return;
-    const uint32_t n = new_upto[i], f = first_upto[i];
-    const int32_t s = (int32_t)by_rank[key[i] & ((1ull << bits) - 1ull)];
+    const uint32_t pairs = new_upto[T - 1], n = new_upto[i], f = first_upto[i] - pairs;
+    const uint32_t of_key = (uint32_t)(key[i] & ((1ull << bits) - 1ull));
+    const int32_t s = (int32_t)(by_rank ? by_rank[of_key] : of_key);
     all_sub[i] = s;
     all_rel[i] = in_rel[pos[i]];
     if (n != (i ? new_upto[i - 1] : 0u)) pull_sub[n - 1] = s;
-    if (f != (i ? first_upto[i - 1] : 0u)) {
+    if (f != (i ? first_upto[i - 1] - pairs : 0u)) {
         sub[f - 1] = in_sub[i];
         eid[f - 1] = in_eid[i];
     }
 }
+
+// Graphs up to so many triples have pull_sub by id, which takes a dozen launches less; the rows' first subjects matter where a
+// hop's lines come from far.  Build of 80,000 / 400,000 / 1.6M triples 804 / 1,881 / 4,091 us by in-degree, 748 / 1,822 / 4,003
+// by id; searches of 1 .. 1,024 questions with their lists the same within 1 % (20,000 triples, 1,024 questions: 3 % longer by id).
+constexpr int64_t kFewPairTriples = 1 << 21;
 
 logoskg_status build_pairs_on_device(logoskg_graph *g, const int32_t *in_sub, const uint16_t *in_rel, const int32_t *in_eid, Scratch &tmp) {
     const int64_t T = g->T;
@@ -339,20 +374,22 @@ logoskg_status build_pairs_on_device(logoskg_graph *g, const int32_t *in_sub, co
 
     const dim3 block(kBlock), per_triple(grid_for(T)), per_entity(grid_for((int64_t)E + 1));
     uint32_t *const obj_of = pos[1];
-    LKG_HIP(hipMemsetAsync(obj_of, 0, (size_t)T * 4, nullptr));
-    k_row_starts<<<per_entity, block>>>(g->in_off, E, obj_of);
-    LKG_HIP(rocprim::inclusive_scan(d_tmp, bytes[2], obj_of, obj_of, (size_t)T, rocprim::maximum<uint32_t>()));
-    k_in_degrees<<<per_entity, block>>>(g->in_off, E, degrees.current());
-    k_iota<<<per_entity, block>>>(ids.current(), E);
-    LKG_HIP(rocprim::radix_sort_pairs_desc(d_tmp, bytes[1], degrees, ids, (size_t)E, 0u, 32u));
-    const uint32_t *const by_rank = ids.current();
-    k_rank_of<<<per_entity, block>>>(by_rank, E, degrees.current());
-    k_pair_keys<<<per_triple, block>>>(obj_of, in_sub, degrees.current(), T, bits, key[0], pos[0]);
+    const bool few = T <= kFewPairTriples;
+    if (!few) {
+        LKG_HIP(hipMemsetAsync(obj_of, 0, (size_t)T * 4, nullptr));
+        k_row_starts<<<per_entity, block>>>(g->in_off, E, obj_of);
+        LKG_HIP(rocprim::inclusive_scan(d_tmp, bytes[2], obj_of, obj_of, (size_t)T, rocprim::maximum<uint32_t>()));
+        k_in_degrees<<<per_entity, block>>>(g->in_off, E, degrees.current());
+        k_iota<<<per_entity, block>>>(ids.current(), E);
+        LKG_HIP(rocprim::radix_sort_pairs_desc(d_tmp, bytes[1], degrees, ids, (size_t)E, 0u, 32u));
+        k_rank_of<<<per_entity, block>>>(ids.current(), E, degrees.current());
+    }
+    const uint32_t *const by_rank = few ? nullptr : ids.current();
+    k_pair_keys<<<per_triple, block>>>(few ? nullptr : obj_of, g->in_off, E, in_sub, few ? nullptr : degrees.current(), T, bits, key[0], pos[0]);
     LKG_HIP(rocprim::radix_sort_pairs(d_tmp, bytes[0], keys, vals, (size_t)T, 0u, 2 * bits));
     uint32_t *const is_new = reinterpret_cast<uint32_t *>(keys.alternate()), *const is_first = is_new + T;
     k_pair_flags<<<per_triple, block>>>(keys.current(), vals.current(), T, is_new, is_first);
-    LKG_HIP(rocprim::inclusive_scan(d_tmp, bytes[2], is_new, is_new, (size_t)T, rocprim::plus<uint32_t>()));
-    LKG_HIP(rocprim::inclusive_scan(d_tmp, bytes[2], is_first, is_first, (size_t)T, rocprim::plus<uint32_t>()));
+    LKG_HIP(rocprim::inclusive_scan(d_tmp, bytes[2], is_new, is_new, 2 * (size_t)T, rocprim::plus<uint32_t>()));
     LKG_HIP(hipGetLastError());
     uint32_t n = 0;
     LKG_HIP(hipMemcpy(&n, is_new + T - 1, sizeof(n), hipMemcpyDeviceToHost));
@@ -407,7 +444,8 @@ logoskg_status count_rows_on_device(const uint32_t *d_off, int32_t E, int hub_mi
     unsigned int *d_n = nullptr;
     LKG_TRY(tmp.get(&d_n, 3));
     LKG_HIP(hipMemsetAsync(d_n, 0, sizeof(n), nullptr));
-    k_row_counts<<<dim3(std::min(1024u, grid_for(E))), dim3(kBlock)>>>(d_off, E, (uint32_t)hub_min, d_n);
+    // (its wavefronts' sums meet in three words: 1,024 blocks over 407,000 rows were 91 us, 128 are 22)
+    k_row_counts<<<dim3(std::min(128u, grid_for(E))), dim3(kBlock)>>>(d_off, E, (uint32_t)hub_min, d_n);
     LKG_HIP(hipMemcpy(n, d_n, sizeof(n), hipMemcpyDeviceToHost));
     return LOGOSKG_OK;
 }

@@ -170,10 +170,15 @@ struct RowClasses {             // device work lists over the object rows, split
 // OBJ without its parallel triples: the rows' distinct subjects, for calls without whitelists, where a triple that repeats
 // another's subject and object in a larger index adds nothing to a level and is never a predecessor.  Two orders of the
 // same rows (off): `sub` / `eid` by triple index, for the predecessor pass; `pull_sub` by the in-degree of the subject,
-// largest first, for pulled hops, which may take a row in any order and stop when nothing is missing: the subjects that
-// most queries have reached come first.  Built where at most kPairShare percent of the triples are left and there is
-// room (kPairRoom); off is NULL otherwise, also from when an allocation of the graph has found no memory but theirs
-// (give_up_pairs).  (Distinct pairs of 30M triples of concepts 65 %, 3.4M 52 %, 300M hub-heavy ones 85 %.)
+// largest first (small graphs: by id), for pulled hops, which may take a row in any order and stop when nothing is missing:
+// the subjects that most queries have reached come first.  Made by builds that sort on the device, where at most kPairShare
+// percent of the triples are left and there is room (kPairRoom); off is NULL otherwise, also from when an allocation of the
+// graph has found no memory but theirs (give_up_pairs).  (Distinct pairs of 30M triples of concepts 65 %, 3.4M 52 %, 300M
+// hub-heavy ones 85 %.)  Worth 130 .. 330 us of a build of up to 0.8M triples (0.5 .. 2.5 ms), 2 ms of 7.5 with 3.4M: us of
+// three hops with lists, 1 / 64 / 200 / 1,024 questions, without and with them:
+//    80,000 triples   115 / 190 / 196 / 379    107 / 178 / 186 / 340       0.4M   115 / 201 / 178 / 416    114 / 202 / 183 / 373
+//    0.2M             115 / 221 / 197 / 436    115 / 225 / 199 / 393       1.6M   135 / 227 / 243 / 506    133 / 211 / 228 / 497
+//    0.2M hub-heavy   115 / 230 / 219 / 331    113 / 223 / 215 / 321       3.4M   161 / 287 / 358 / 694    157 / 266 / 323 / 693
 constexpr int kPairShare = 90;
 constexpr int kPairRoom = 8;  // they take at most this part of the device memory that is free when they are made
 struct PairRows {
@@ -242,6 +247,7 @@ struct logoskg_graph {
     int hub_min = lkg::kDefaultHubMin;
     int num_shards = 1;
 
+    void *csr_block = nullptr;    // small resident graphs: holds the arrays of both CSRs
     // subject-sorted CSR (SUB): row s -> objects / relations of its triples
     uint32_t *out_off = nullptr;  // [E+1]
     uint32_t *row_begin = nullptr;    // [E] start of each subject's triples in the edge arrays
@@ -260,7 +266,7 @@ struct logoskg_graph {
     lkg::PairRows pairs;         // the same rows without the parallel triples
     int64_t n_out_rows = 0, n_out_hubs = 0;
 
-    // frontier work lists rebuilt every hop from the level's active bitmap
+    // frontier work lists rebuilt every hop from the level's active bitmap (one block: d_ctr, fr_tail, fr_seg)
     int32_t *fr_tail = nullptr;          // [E] frontier rows of degree <= kTailMaxDegree
     lkg::RowSegment *fr_seg = nullptr;   // [fr_seg_cap] segments of the longer frontier rows
     int64_t fr_seg_cap = 0;
@@ -558,7 +564,7 @@ struct FillArgs {
 };
 
 struct Scratch;  // a build's device temporaries (build_device.hip)
-logoskg_status scratch_create(logoskg_graph *g, bool sorts, bool pairs, Scratch **out);
+logoskg_status scratch_create(logoskg_graph *g, bool resident, Scratch **out);
 void scratch_destroy(Scratch *s);
 void scratch_release(Scratch *s);  // gives its memory back
 size_t scratch_bytes(const Scratch *s);  // .. that it holds in one block

@@ -54,7 +54,7 @@ def run(tmp_path, shim_source, code):
 
 def test_device_bytes_follow_them(tmp_path):
     run(tmp_path, "hip_memory.cpp", """
-E, T, Q, k = 30_000, 300_000, 300, 2
+E, T, Q, k = 70_000, 700_000, 300, 2
 rng, s, r, o = graph(E, T, 1)
 off, seeds = batch(rng, E, Q)
 want = oracle.khop(E, s, r, o, off, seeds, k)
