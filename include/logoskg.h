@@ -123,7 +123,8 @@ typedef struct {
     int64_t num_out_rows, num_out_hubs; /* subjects with >= 1 triple / in the hub class */
     int64_t num_in_rows, num_in_hubs;   /* objects  with >= 1 triple / in the hub class */
     int64_t device_bytes;               /* HBM held by the graph (CSR, lists, shard cache; where
-                                           parallel triples are a tenth and more of all and there is
+                                           parallel triples are a fifth and more of all (a tenth from
+                                           8M triples on), the build sorts on the device and there is
                                            room also the object rows without them: 12 bytes per
                                            distinct (subject, object) pair, 6 per triple; an eighth
                                            of the free memory at most, and given back for good when

@@ -393,7 +393,7 @@ logoskg_status build_pairs_on_device(logoskg_graph *g, const int32_t *in_sub, co
     LKG_HIP(hipGetLastError());
     uint32_t n = 0;
     LKG_HIP(hipMemcpy(&n, is_new + T - 1, sizeof(n), hipMemcpyDeviceToHost));
-    if ((int64_t)n * 100 > T * kPairShare) return LOGOSKG_OK;
+    if ((int64_t)n * 100 > T * (T < kPairManyTriples ? kPairShareFew : kPairShare)) return LOGOSKG_OK;
 
     PairRows p;
     const size_t of_pairs = Scratch::rounded((size_t)n * 4), of_triples = Scratch::rounded((size_t)T * 4), of_rels = Scratch::rounded((size_t)T * 2),

@@ -179,7 +179,11 @@ struct RowClasses {             // device work lists over the object rows, split
 //    80,000 triples   115 / 190 / 196 / 379    107 / 178 / 186 / 340       0.4M   115 / 201 / 178 / 416    114 / 202 / 183 / 373
 //    0.2M             115 / 221 / 197 / 436    115 / 225 / 199 / 393       1.6M   135 / 227 / 243 / 506    133 / 211 / 228 / 497
 //    0.2M hub-heavy   115 / 230 / 219 / 331    113 / 223 / 215 / 321       3.4M   161 / 287 / 358 / 694    157 / 266 / 323 / 693
-constexpr int kPairShare = 90;
+// By the share that is left (1,024 questions, three hops with lists, without and with them; on 20M also under whitelists):
+//    3.4M    92 %   870 /   888    88 %   864 /   885    80 %   852 /   860    65 %   831 /   822
+//     20M    92 % 3,280 / 3,209    88 % 3,226 / 3,118    80 % 3,125 / 2,952    65 % 2,860 / 2,593    whitelists 80 % 2,230 / 2,200
+constexpr int kPairShare = 90, kPairShareFew = 80;  // .. of graphs of fewer triples than kPairManyTriples
+constexpr long long kPairManyTriples = 1 << 23;
 constexpr int kPairRoom = 8;  // they take at most this part of the device memory that is free when they are made
 struct PairRows {
     void *block = nullptr;  // holds the arrays

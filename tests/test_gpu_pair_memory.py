@@ -178,3 +178,33 @@ for per_triple, kept in ((70, False), (400, True)):   # the sorts and the arrays
     g.close()
     mem.memory_limit(0)
 """)
+
+
+@pytest.mark.parametrize("opts", [{}, {"num_shards": 2}])
+def test_no_room_for_their_index(tmp_path, opts):
+    """The last thing that the first fetch of a large batch takes: it then goes by all triples."""
+    run(tmp_path, "hip_limit.cpp", f"opts = {opts!r}" + LIMITED + """
+Q = 300
+off, seeds = batch(rng, E, Q)
+want = oracle.khop(E, s, r, o, off, seeds, k)
+out = [torch.zeros(want[0][-1], dtype=t, device="cuda") for t in (torch.int32, torch.uint8, torch.int32)]
+off, seeds = torch.from_numpy(off).cuda(), torch.from_numpy(seeds).cuda()
+for limited in (False, True):
+    g = lkg.Graph(s, r, o, E, 9, **opts)
+    g.khop(off, seeds, k, direction="pull").close()  # (a cache holds every unit from here on)
+    res = g.khop(off, seeds, k)
+    live, held = mem.memory_live(), g.info()["device_bytes"]
+    assert held > 26 * T
+    if limited:
+        mem.memory_limit(live + needs - 1024)
+    res.fetch(out=out)
+    torch.cuda.synchronize()
+    mem.memory_limit(0)
+    needs = mem.memory_live() - live
+    assert g.info()["device_bytes"] == held + (0 if limited else 4 * E), (g.info()["device_bytes"] - held, E)
+    assert all(np.array_equal(x.cpu().numpy(), y) for x, y in zip(out, want[1:4]))
+    res.fetch(out=out)
+    assert all(np.array_equal(x.cpu().numpy(), y) for x, y in zip(out, want[1:4]))
+    res.close()
+    g.close()
+""")

@@ -82,3 +82,34 @@ def test_tiny_graphs(T, pairs):
     g = lkg.Graph(s, r, o, 41, 3)
     compare(g, 41, s, r, o, off, seeds, 3)
     g.close()
+
+
+@pytest.mark.parametrize("share, kept", [(0.02, False), (0.18, False), (0.22, True), (0.9, True)])
+def test_which_graphs_hold_them(share, kept):
+    """.. and that calls without whitelists then walk them: by the entries that a pulled hop reads in the counting mode."""
+    import paper_2604_18913_amd as lkg
+    rng = np.random.default_rng(int(100 * share))
+    E, R = 12_000, 30
+    s, r, o = parallel_graph(rng, E, R, (1, 31, 32, 33, 64, 65, 1023, 1024, 1025), 60_000, share)
+    T, pairs = len(s), len(np.unique(s.astype(np.int64) * E + o))
+    off, seeds = seed_lists([rng.integers(0, E, 2) for _ in range(300)])
+    for opts, kept_here in (({}, kept), ({"num_shards": 3}, kept), ({"num_shards": 3, "max_resident_shards": 2}, False), ({"host_build": True}, False)):
+        g, none = lkg.Graph(s, r, o, E, R, **opts), lkg.Graph(s[:0], r[:0], o[:0], E, R, **opts)
+        if not opts:
+            held = g.info()["device_bytes"] - none.info()["device_bytes"]
+            assert (held > 20 * T + 6 * T + 12 * pairs) == kept, held / T
+            assert kept or held < 23 * T
+        g.khop(off, seeds, 1, direction="pull").close()  # (a cache holds every unit from here on)
+        g.profile_enable(2)
+        res = g.khop(off, seeds, 1, walk_exact=True, direction="pull")  # (every row is read to its end, or for what is live)
+        read = res.hop_stats()[0]["edges_scanned"]
+        assert read <= (pairs if kept_here else T), (opts, read, pairs, T)
+        res.close()
+        res = g.khop(off, seeds, 1, np.full((300, 1), (1 << R) - 1, np.uint64), walk_exact=True, direction="pull")
+        read_all = res.hop_stats()[0]["edges_scanned"]
+        assert (read < read_all) == kept_here, (opts, read, read_all)
+        res.close()
+        g.profile_enable(0)
+        compare(g, E, s, r, o, off, seeds, 2)
+        g.close()
+        none.close()
