@@ -340,7 +340,7 @@ struct logoskg_result {
     // tiles of the count / list / predecessor kernels are cut from it (resident graphs)
     int32_t *tile_ent = nullptr;   // [Epad + 64], -1 behind the last id
     int32_t *cpos = nullptr;       // [Epad], defined for the listed entities
-    uint32_t *act_chunk = nullptr; // per 2,048-entity chunk: listed entities before it; then *d_nact
+    uint32_t *act_chunk = nullptr; // per 2,048-entity chunk: listed entities in it (many chunks: before it); then *d_nact
     unsigned long long *d_nact = nullptr;
     long long n_active = -1;       // length of the list (known after the count pass)
     std::vector<int64_t> reached_off;  // host copy [Q+1]

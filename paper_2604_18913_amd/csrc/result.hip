@@ -151,8 +151,10 @@ __device__ __forceinline__ void write_listed(uint32_t u, long long first, long l
 }
 
 // SUM: the chunks' counts are still that, and a block adds up those before its own (instead of a launch of k_active_scan
-// between: 4 us and its gap).  What the blocks read together grows with the square of the graph, so it ends at kActSumChunks.
-constexpr long long kActSumChunks = 16384;  // 33M entities: 0.3 GB through the L2s
+// between: 4 us and its gap).  What the blocks read together grows with the square of the graph, so it ends at kActSumChunks,
+// well before that shows: us of a search of one question by entities, with the scan / without: 1M 1,380 / 1,376, 16M 1,587 /
+// 1,586, 33M 1,835 / 1,829, 100M 2,959 / 2,953 (1.2 GB through the L2s).
+constexpr long long kActSumChunks = 16384;  // 33M entities: 0.13 GB
 
 template <bool SUM>
 __global__ void __launch_bounds__(256)
@@ -2388,7 +2390,9 @@ static logoskg_status ensure_active_list(logoskg_result *r, hipStream_t st) {
     }
     const unsigned nb = (unsigned)((nchunks + 3) / 4);
     k_active_count<<<dim3(nb), dim3(256), 0, st>>>(r->act, actw, r->k + 1, nchunks, r->act_chunk);
-    if (nchunks <= kActSumChunks) {
+    long long sum_chunks = kActSumChunks;
+    if (const char *most = getenv("LOGOSKG_ACTIVE_SUM_CHUNKS")) sum_chunks = std::max(0, atoi(most));  // (tests reach the scan's form so)
+    if (nchunks <= sum_chunks) {
         k_active_fill<true><<<dim3(nb), dim3(256), 0, st>>>(r->act, actw, r->k + 1, nchunks, r->act_chunk, r->d_nact, r->tile_ent, r->cpos);
     } else {
         k_active_scan<<<dim3(1), dim3(1024), 0, st>>>(nchunks, r->act_chunk, r->d_nact, r->tile_ent);

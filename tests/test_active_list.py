@@ -48,3 +48,28 @@ def test_deep_searches(E, k, Q):
         assert np.array_equal(got.cpu().numpy(), w)
     res.close()
     g.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("E", [300_000, 1 << 20, (1 << 20) + 2_049])
+@pytest.mark.parametrize("Q", [2, 200, 300])
+@pytest.mark.parametrize("sum_chunks", [0, 512, 1 << 20])
+def test_prefixes_by_a_scan_or_by_the_blocks(monkeypatch, E, Q, sum_chunks):
+    """512 chunks hold 1,048,576 entities: both sides of the rule, and either form for all."""
+    import paper_2604_18913_amd as lkg
+    monkeypatch.setenv("LOGOSKG_ACTIVE_SUM_CHUNKS", str(sum_chunks))
+    rng = np.random.default_rng(E + Q)
+    s, o = rng.integers(0, E, (2, 60_000)).astype(np.int32)
+    o[:40_000] = np.sort(rng.choice(E, 40_000, replace=False))
+    s[:40_000] = rng.integers(0, 40, 40_000)
+    r = np.zeros(s.size, np.int32)
+    off = np.arange(Q + 1, dtype=np.int64)
+    seeds = rng.integers(0, 40, Q).astype(np.int32)
+    want = oracle.khop(E, s, r, o, off, seeds, 2)
+    g = lkg.Graph(s, r, o, E, 1)
+    res = g.khop(off, seeds, 2)
+    assert np.array_equal(res.offsets(), want[0])
+    for got, w in zip(res.fetch(), want[1:]):
+        assert np.array_equal(got.cpu().numpy(), w)
+    res.close()
+    g.close()
