@@ -467,7 +467,9 @@ struct Seen {
     const uint32_t *act;
     long long plane, actw;
     int gate, first, last;
-    bool sure;  // most rows are active in the last level: its lines (zero elsewhere) are read without asking
+    // more than half of the object rows are active in the last level: its lines (zero elsewhere) are read without asking (three
+    // hops on hub-heavy 20M 1,482 -> 1,441 us, four 2,090 -> 2,029, 30M triples 839 -> 829, 3.4M the same)
+    bool sure;
     bool keep;  // base is the plane that the hop keeps: it holds all levels, and its line is written where something is reached
 };
 

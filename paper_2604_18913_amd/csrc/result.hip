@@ -354,13 +354,15 @@ __device__ __forceinline__ void full_add(unsigned long long a, unsigned long lon
 // earlier tiles of the super tile, super_sum[st][q] = in the whole super tile.
 // With a list the number of tiles follows from *n_active (the grid covers the largest possible
 // number of super tiles; those behind the list write zero sums).
-// A 16-lane group takes 16 of the tile's entities, lane = word, all lines requested together, and adds them up bit-sliced:
-// five words say for 64 queries how many of the 16 entities each reached, seven when the four groups have been added.
-// Only those are turned into a number per query (lane = query: a word is the mask of a select).  A
-// wavefront per word that transposed 64 x 64 bits per tile, the lines handed over through LDS, was a chain of latencies and
-// twelve LDS permutes per (tile, word): 20M entities 1,338 -> 620 us (2.6 GB read, 0.6 GB written), 30M triples' 0.9M listed
-// ones 72 -> 35 us.
-constexpr int kCountLevels = 3;  // levels whose active bits are asked for ahead of the first line
+// A 16-lane group takes 16 of the tile's entities, lane = word, the lines of four requested together from the base and then from
+// every level they are active in, and adds the unions up bit-sliced: five words say for 64 queries how many of the 16
+// entities each reached, seven when the four groups have been added.  Only those are turned into a number per query
+// (lane = query: a word is the mask of a select).  A wavefront per word that transposed 64 x 64 bits per tile, the lines
+// handed over through LDS, was a chain of latencies and twelve LDS permutes per (tile, word): 20M entities 1,338 -> 620 us
+// over one plane with all sixteen lines of a group on their way, which the unions of levels have no registers for.  One
+// plane now / the levels of three hops, us: 30M triples' 0.9M listed entities 36 / 66 (31 / 33, the second over a plane that
+// the hops kept), 2M hub-heavy ones 94 / 173 (82 / 64).
+constexpr int kCountLevels = 3;  // levels whose active bits are asked for ahead of the first line: those of three hops
 
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8)))
 k_count(Seen s, long long ntiles, int32_t E, const int32_t *__restrict__ tile_ent,
@@ -1440,8 +1442,9 @@ __global__ void __launch_bounds__(1024) k_pred(FillArgs a) {
 // kernels: such an entity's predecessors come from row_pred, which those kernels fill before
 // this one starts (or, without that buffer, the row kernels write them to the lists themselves).
 // It waits for memory, short of a copy's rate (4.86 TB/s): a store covers the entities of one tile that one query reached, 55 %
-// and 78 % of its lanes in the two calls that follow.  1.30 ms for 516M pairs of 1,024 queries, 5.9 GB, 4.5 TB/s (1.57 ms
-// with a rolled loop and edge ids staged row by row); 2.3 ms for 993M pairs of 64 queries on 20M entities (2.48).
+// and 78 % of its lanes in the two calls that follow.  1.32 ms for 516M pairs of 1,024 queries, 5.96 GB by the counters,
+// 4.5 TB/s (1.49 ms with a rolled loop and edge ids staged row by row, 1.37 with the loop written out); 2.47 ms for 993M pairs of
+// 64 queries on 20M entities, 11.2 GB, 4.5 TB/s (2.47).
 constexpr int kSlicedMaxK = 6;     // hop + 1 <= 7 fits three bits
 
 constexpr int kPageEntries = 2;  // entries one lane per entity gathers together (on packed planes 1: 2.4, 2: 2.4, 4: 2.7, 8: 3.3 ms)

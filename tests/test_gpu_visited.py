@@ -1,5 +1,6 @@
-"""The visited plane of 16-word batches, which pulled hops do not keep: what get_info hands out, lists that ask for it, and
-that a block given back cleared is clear."""
+"""The visited plane of 16-word batches: what get_info hands out, lists that ask for it, and that a block given back cleared is
+clear.  (Hops keep it on graphs of this size; where they do not, on larger ones, it is made where it is asked
+for: test_gpu_visited_kept.py.)"""
 import ctypes
 
 import numpy as np
