@@ -301,6 +301,7 @@ static logoskg_status classify_on_host(const logoskg_graph *g, const uint32_t *d
     LKG_TRY(read_offsets(d_off, g->E, &off));
     uint32_t at[kTailMaxDegree + 2] = {};  // of the rows of d entries at [kTailMaxDegree - d + 1], then where they begin
     rc->n_hub = 0;
+    longer->clear();
     for (int32_t e = 0; e < g->E; ++e) {
         const uint32_t d = off[(size_t)e + 1] - off[e];
         if (d > (uint32_t)kTailMaxDegree) longer->push_back({e, off[e], off[(size_t)e + 1]});
@@ -322,9 +323,14 @@ static logoskg_status classify_on_host(const logoskg_graph *g, const uint32_t *d
 static logoskg_status row_classes(logoskg_graph *g, const uint32_t *d_off, bool by_place, Scratch &tmp, RowClasses *rc) {
     std::vector<ShortRow> longer, tail;
     ShortRow *records = nullptr;
-    const bool on_host = g->E <= kHostRows;
+    bool on_host = g->E <= kHostRows;
+    if (!on_host) {
+        const logoskg_status s = classify_on_device(d_off, g->E, g->hub_min, tmp, rc, &records, &longer);
+        if (s != LOGOSKG_OK && s != LOGOSKG_ENOMEM) return s;
+        on_host = s == LOGOSKG_ENOMEM;  // no room for the device's temporaries
+        if (on_host) (void)hipGetLastError();
+    }
     if (on_host) LKG_TRY(classify_on_host(g, d_off, rc, &tail, &longer));
-    else LKG_TRY(classify_on_device(d_off, g->E, g->hub_min, tmp, rc, &records, &longer));
     std::stable_sort(longer.begin(), longer.end(), [](const ShortRow &a, const ShortRow &b) { return a.end - a.begin > b.end - b.begin; });
     std::vector<int32_t> rows, multi;
     std::vector<PullSegment> seg;

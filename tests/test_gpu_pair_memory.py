@@ -208,3 +208,19 @@ for limited in (False, True):
     res.close()
     g.close()
 """)
+
+
+def test_a_build_without_room_for_the_classification_on_the_device(tmp_path):
+    run(tmp_path, "hip_memory.cpp", """
+E, T, Q, k = 70_001, 400_000, 90, 2
+rng, s, r, o = graph(E, T, 5)
+off, seeds = batch(rng, E, Q)
+want = oracle.khop(E, s, r, o, off, seeds, k)
+degree = np.bincount(o, minlength=E)
+mem.memory_watch((E + 255) // 256 * 256)  # a byte per row
+g = lkg.Graph(s, r, o, E, 9, host_build=True)
+assert mem.memory_refusals() > 0
+info = g.info()
+assert info["num_in_rows"] == np.count_nonzero(degree) and info["num_in_hubs"] == np.count_nonzero(degree >= 1024)
+same(g.khop(off, seeds, k), want)
+""")
