@@ -250,7 +250,11 @@ static void drop_pairs(logoskg_graph *g) {
 size_t most_pair_bytes(const logoskg_graph *g) { return (size_t)g->T * 18 + (size_t)g->E * 24; }
 
 bool give_up_pairs(logoskg_graph *g) {
-    if (!g->pairs.off || g->pairs.in_use || g->pairs.recorded) return false;
+    if (!g->pairs.off || g->pairs.recorded) return false;
+    if (g->pairs.in_use) {
+        g->pairs.wanted = true;
+        return false;
+    }
     if (hipDeviceSynchronize() != hipSuccess) {  // (kernels that read them may be queued on any stream)
         (void)hipGetLastError();
         return false;

@@ -195,6 +195,7 @@ struct PairRows {
     int32_t *all_sub = nullptr;
     uint16_t *all_rel = nullptr;
     bool in_use = false;    // a call is about to launch what reads them
+    bool wanted = false;    // .. and has done without memory that they hold: they go with the next search
     bool recorded = false;  // a recorded sequence reads them: they stay as long as the graph
     RowClasses rows;  // (segments by their place in the row: the first ones of all rows, the second ones, ..)
     int32_t *long_index = nullptr;  // as logoskg_graph::long_index

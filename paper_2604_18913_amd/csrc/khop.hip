@@ -1809,6 +1809,7 @@ extern "C" logoskg_status logoskg_khop(logoskg_graph *g, const logoskg_query_bat
     // counters another: each is cleared by one fill
     const size_t act_bytes = actw * 4 * (size_t)(k + 1), live_bytes = (size_t)(16 + kLevelCounters) * 8 * (size_t)(k + 1);
     r->last_stream = st;
+    if (g->pairs.wanted) (void)give_up_pairs(g);
     bool planes_zero = false, act_zero = false;  // a block released by an earlier result comes back cleared
     if ((s = g->pool.alloc((void **)&r->visited, plane * 8 * (size_t)(k + 2), st, &planes_zero)) != LOGOSKG_OK) return fail(s);
     r->levels = r->visited + plane;

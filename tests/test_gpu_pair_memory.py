@@ -210,6 +210,40 @@ for limited in (False, True):
 """)
 
 
+def test_a_fetch_that_does_without_memory_has_them_go_with_the_next_search(tmp_path):
+    run(tmp_path, "hip_limit.cpp", LIMITED + """
+Q = 200
+o[:90_000] = 7  # object rows that are cut into segments
+o[90_000:120_000] = 8
+off, seeds = batch(rng, E, Q)
+want = oracle.khop(E, s, r, o, off, seeds, k)
+out = [torch.zeros(want[0][-1], dtype=t, device="cuda") for t in (torch.int32, torch.uint8, torch.int32)]
+off, seeds = torch.from_numpy(off).cuda(), torch.from_numpy(seeds).cuda()
+pairs = 6 * T + 12 * len(np.unique(s.astype(np.int64) * E + o))
+g = lkg.Graph(s, r, o, E, 9)
+held = g.info()["device_bytes"]
+assert held > 20 * T + pairs
+res = g.khop(off, seeds, k)
+pool = g.info()["device_bytes"] - held
+mem.memory_limit(mem.memory_live() + 256)
+for _ in range(2):
+    for x in out:
+        x.zero_()
+    res.fetch(out=out)
+    torch.cuda.synchronize()
+    assert all(np.array_equal(x.cpu().numpy(), y) for x, y in zip(out, want[1:4]))
+assert g.info()["device_bytes"] == held + pool
+res.close()
+for _ in range(2):
+    res = g.khop(off, seeds, k)
+    res.fetch(out=out)
+    torch.cuda.synchronize()
+    assert all(np.array_equal(x.cpu().numpy(), y) for x, y in zip(out, want[1:4]))
+    assert g.info()["device_bytes"] < held + pool - pairs // 2
+    res.close()
+""")
+
+
 def test_a_build_without_room_for_the_classification_on_the_device(tmp_path):
     run(tmp_path, "hip_memory.cpp", """
 E, T, Q, k = 70_001, 400_000, 90, 2
