@@ -109,6 +109,18 @@ __global__ void k_subject_of_triple(const int32_t *__restrict__ in_sub, const in
     if (p < T) subject_of[in_eid[p]] = (uint32_t)in_sub[p];
 }
 
+// The one instantiation of the 32-bit sort, for rows, in-degrees and classes.  The sorts are most of what a process's first
+// build on the device loads: with a byte-wide, a descending and a const-keyed one beside it they were 9.9 MB and a first build
+// of 500,000 / 3.4M triples took 48 / 55 ms; 5.5 MB and 31 / 36 ms, later builds the same.  (The sort only reads keys and vals.)
+hipError_t sort_u32(void *d_tmp, size_t &bytes, const uint32_t *keys, uint32_t *keys_out, const uint32_t *vals, uint32_t *vals_out, int64_t n, unsigned bits,
+                    hipStream_t stream = nullptr) {
+    return rocprim::radix_sort_pairs(d_tmp, bytes, const_cast<uint32_t *>(keys), keys_out, const_cast<uint32_t *>(vals), vals_out, (size_t)n, 0u, bits, stream);
+}
+
+hipError_t sort_u32(void *d_tmp, size_t &bytes, rocprim::double_buffer<uint32_t> &keys, rocprim::double_buffer<uint32_t> &vals, int64_t n, unsigned bits) {
+    return rocprim::radix_sort_pairs(d_tmp, bytes, keys, vals, (size_t)n, 0u, bits);
+}
+
 // sorted_eid = triple indices in (key, index) order; off = row offsets of that order
 logoskg_status sort_by(const int32_t *d_key, int64_t T, int32_t E, unsigned key_bits, uint32_t *d_iota,
                        uint32_t *d_keys_out, uint32_t *d_sorted_eid, uint32_t *d_off, void *d_tmp, size_t tmp_bytes) {
@@ -116,8 +128,7 @@ logoskg_status sort_by(const int32_t *d_key, int64_t T, int32_t E, unsigned key_
     if (T > 0) {
         k_degrees<<<dim3(grid_for(T)), dim3(kBlock)>>>(d_key, T, d_off);
         size_t need = tmp_bytes;
-        LKG_HIP(rocprim::radix_sort_pairs(d_tmp, need, reinterpret_cast<const uint32_t *>(d_key), d_keys_out, d_iota,
-                                          d_sorted_eid, (size_t)T, 0u, key_bits));
+        LKG_HIP(sort_u32(d_tmp, need, reinterpret_cast<const uint32_t *>(d_key), d_keys_out, d_iota, d_sorted_eid, T, key_bits));
     }
     size_t need = tmp_bytes;
     LKG_HIP(rocprim::inclusive_scan(d_tmp, need, d_off, d_off, (size_t)E + 1, rocprim::plus<uint32_t>()));
@@ -136,7 +147,7 @@ static unsigned bits_for(int32_t E) {
 static logoskg_status csr_sort_bytes(int64_t T, int32_t E, size_t *bytes) {
     size_t sort_bytes = 0, scan_bytes = 0;
     uint32_t *none = nullptr;
-    LKG_HIP(rocprim::radix_sort_pairs(nullptr, sort_bytes, (const uint32_t *)nullptr, none, none, none, (size_t)std::max<int64_t>(T, 1), 0u, bits_for(E)));
+    LKG_HIP(sort_u32(nullptr, sort_bytes, none, none, none, none, std::max<int64_t>(T, 1), bits_for(E)));
     LKG_HIP(rocprim::inclusive_scan(nullptr, scan_bytes, none, none, (size_t)E + 1, rocprim::plus<uint32_t>()));
     *bytes = std::max(sort_bytes, scan_bytes);
     return LOGOSKG_OK;
@@ -151,7 +162,7 @@ static logoskg_status pair_sort_bytes(int64_t T, int32_t E, size_t (&bytes)[3]) 
     PairBuffers b;
     uint32_t *none = nullptr;
     LKG_HIP(rocprim::radix_sort_pairs(nullptr, bytes[0], b.keys, b.vals, (size_t)T, 0u, 2 * bits_for(E)));
-    LKG_HIP(rocprim::radix_sort_pairs_desc(nullptr, bytes[1], b.degrees, b.ids, (size_t)E, 0u, 32u));
+    LKG_HIP(sort_u32(nullptr, bytes[1], b.degrees, b.ids, E, 32u));
     LKG_HIP(rocprim::inclusive_scan(nullptr, bytes[2], none, none, 2 * (size_t)T, rocprim::plus<uint32_t>()));
     return LOGOSKG_OK;
 }
@@ -277,9 +288,10 @@ __global__ void k_row_starts(const uint32_t *__restrict__ off, int32_t E, uint32
     if (e < E && off[e + 1] > off[e]) obj_of[off[e]] = (uint32_t)e;
 }
 
+// (inverted: the sort ascends, the highest degree comes first)
 __global__ void k_in_degrees(const uint32_t *__restrict__ off, int32_t E, uint32_t *deg) {
     const int32_t e = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (e < E) deg[e] = off[e + 1] - off[e];
+    if (e < E) deg[e] = ~(off[e + 1] - off[e]);
 }
 
 __global__ void k_rank_of(const uint32_t *__restrict__ by_rank, int32_t E, uint32_t *rank_of) {
@@ -381,7 +393,7 @@ logoskg_status build_pairs_on_device(logoskg_graph *g, const int32_t *in_sub, co
         LKG_HIP(rocprim::inclusive_scan(d_tmp, bytes[2], obj_of, obj_of, (size_t)T, rocprim::maximum<uint32_t>()));
         k_in_degrees<<<per_entity, block>>>(g->in_off, E, degrees.current());
         k_iota<<<per_entity, block>>>(ids.current(), E);
-        LKG_HIP(rocprim::radix_sort_pairs_desc(d_tmp, bytes[1], degrees, ids, (size_t)E, 0u, 32u));
+        LKG_HIP(sort_u32(d_tmp, bytes[1], degrees, ids, E, 32u));
         k_rank_of<<<per_entity, block>>>(ids.current(), E, degrees.current());
     }
     const uint32_t *const by_rank = few ? nullptr : ids.current();
@@ -451,17 +463,17 @@ logoskg_status count_rows_on_device(const uint32_t *d_off, int32_t E, int hub_mi
 }
 
 // short rows by descending length, then the longer ones, then the empty ones
-__global__ void k_row_class(const uint32_t *__restrict__ off, int32_t E, uint8_t *key, int32_t *id) {
+__global__ void k_row_class(const uint32_t *__restrict__ off, int32_t E, uint32_t *key, uint32_t *id) {
     const long long e = (long long)blockIdx.x * kBlock + threadIdx.x;
     if (e >= E) return;
     const uint32_t d = off[e + 1] - off[e];
     key[e] = d == 0 ? kTailMaxDegree + 1 : d > (uint32_t)kTailMaxDegree ? kTailMaxDegree : kTailMaxDegree - d;
-    id[e] = (int32_t)e;
+    id[e] = (uint32_t)e;
 }
 
-__global__ void k_row_records(const int32_t *__restrict__ id, long long n, const uint32_t *__restrict__ off, ShortRow *out) {
+__global__ void k_row_records(const uint32_t *__restrict__ id, long long n, const uint32_t *__restrict__ off, ShortRow *out) {
     const long long i = (long long)blockIdx.x * kBlock + threadIdx.x;
-    if (i < n) out[i] = ShortRow{id[i], off[id[i]], off[id[i] + 1]};
+    if (i < n) out[i] = ShortRow{(int32_t)id[i], off[id[i]], off[id[i] + 1]};
 }
 
 // The rows behind d_off: counts into rc, the short ones by descending length and then the longer ones as records on the
@@ -476,19 +488,17 @@ logoskg_status classify_on_device(const uint32_t *d_off, int32_t E, int hub_min,
     longer->resize(n[1]);
     *records = nullptr;
     if (n[0] == 0) return LOGOSKG_OK;
-    uint8_t *key[2] = {};
-    int32_t *id[2] = {};
+    uint32_t *key[2] = {}, *id[2] = {};
     for (auto &p : key) LKG_TRY(tmp.get(&p, (size_t)E));
     for (auto &p : id) LKG_TRY(tmp.get(&p, (size_t)E));
-    rocprim::double_buffer<uint8_t> keys(key[0], key[1]);
-    rocprim::double_buffer<int32_t> ids(id[0], id[1]);
+    rocprim::double_buffer<uint32_t> keys(key[0], key[1]), ids(id[0], id[1]);
     size_t bytes = 0;
-    LKG_HIP(rocprim::radix_sort_pairs(nullptr, bytes, keys, ids, (size_t)E, 0u, 6u));
+    LKG_HIP(sort_u32(nullptr, bytes, keys, ids, E, 6u));
     char *d_tmp = nullptr;
     LKG_TRY(tmp.get(&d_tmp, bytes));
     LKG_TRY(tmp.get(records, n[0]));
     k_row_class<<<dim3(grid_for(E)), dim3(kBlock)>>>(d_off, E, key[0], id[0]);
-    LKG_HIP(rocprim::radix_sort_pairs(d_tmp, bytes, keys, ids, (size_t)E, 0u, 6u));
+    LKG_HIP(sort_u32(d_tmp, bytes, keys, ids, E, 6u));
     k_row_records<<<dim3(grid_for(n[0])), dim3(kBlock)>>>(ids.current(), n[0], d_off, *records);
     LKG_HIP(hipGetLastError());
     if (n[1]) LKG_HIP(hipMemcpy(longer->data(), *records + rc->n_tail, (size_t)n[1] * sizeof(ShortRow), hipMemcpyDeviceToHost));
@@ -556,8 +566,7 @@ logoskg_status sorter_create(logoskg_graph *g, const int32_t *subj, const int32_
     }
     while (s->key_bits < 32 && (1ull << s->key_bits) < (unsigned long long)g->E) ++s->key_bits;
     size_t sort_bytes = 0, scan_bytes = 0;
-    LKG_HIP(rocprim::radix_sort_pairs(nullptr, sort_bytes, s->d_key_in, s->d_keys, s->d_iota, s->d_eid,
-                                      (size_t)std::max<int64_t>(T, 1), 0u, 32u));
+    LKG_HIP(sort_u32(nullptr, sort_bytes, s->d_key_in, s->d_keys, s->d_iota, s->d_eid, std::max<int64_t>(T, 1), 32u));
     LKG_HIP(rocprim::inclusive_scan(nullptr, scan_bytes, (uint32_t *)nullptr, (uint32_t *)nullptr, (size_t)g->E + 1,
                                     rocprim::plus<uint32_t>()));
     s->tmp_bytes = std::max(sort_bytes, scan_bytes);
@@ -587,7 +596,7 @@ logoskg_status sorter_subject_order(TripleSorter *s, const uint32_t *d_row_begin
     if (T == 0) return LOGOSKG_OK;
     k_row_keys<<<dim3(grid_for(T)), dim3(kBlock)>>>(s->d_subj, T, d_row_begin, s->d_key_in);
     size_t need = s->tmp_bytes;
-    LKG_HIP(rocprim::radix_sort_pairs(s->d_tmp, need, s->d_key_in, s->d_keys, s->d_iota, s->d_eid, (size_t)T, 0u, 32u));
+    LKG_HIP(sort_u32(s->d_tmp, need, s->d_key_in, s->d_keys, s->d_iota, s->d_eid, T, 32u));
     k_gather_sub_rows<<<dim3(grid_for(T)), dim3(kBlock)>>>(s->d_eid, T, s->d_obj, s->d_rel, s->d_a, s->d_r);
     LKG_HIP(hipGetLastError());
     LKG_HIP(hipMemcpy(h_obj, s->d_a, (size_t)T * 4, hipMemcpyDeviceToHost));
@@ -600,8 +609,7 @@ logoskg_status sorter_object_order(TripleSorter *s, int32_t *h_sub, uint16_t *h_
     const int64_t T = s->T;
     if (T == 0) return LOGOSKG_OK;
     size_t need = s->tmp_bytes;
-    LKG_HIP(rocprim::radix_sort_pairs(s->d_tmp, need, reinterpret_cast<const uint32_t *>(s->d_obj), s->d_keys, s->d_iota,
-                                      s->d_eid, (size_t)T, 0u, s->key_bits));
+    LKG_HIP(sort_u32(s->d_tmp, need, reinterpret_cast<const uint32_t *>(s->d_obj), s->d_keys, s->d_iota, s->d_eid, T, s->key_bits));
     k_gather_obj_rows<<<dim3(grid_for(T)), dim3(kBlock)>>>(s->d_eid, T, s->d_subj, s->d_rel, s->d_a, s->d_r, s->d_b);
     LKG_HIP(hipGetLastError());
     LKG_HIP(hipMemcpy(h_sub, s->d_a, (size_t)T * 4, hipMemcpyDeviceToHost));
@@ -648,13 +656,11 @@ static logoskg_status build_out_eid(logoskg_graph *g, hipStream_t st) {
                                                                    g->row_begin, d_subject);
         k_iota<<<dim3(grid_for(T)), dim3(kBlock), 0, st>>>(d_iota, T);
         size_t bytes = 0;
-        hipError_t e = rocprim::radix_sort_pairs(nullptr, bytes, d_subject, d_keys, d_iota, (uint32_t *)eid, (size_t)T,
-                                                 0u, key_bits, st);
+        hipError_t e = sort_u32(nullptr, bytes, d_subject, d_keys, d_iota, (uint32_t *)eid, T, key_bits, st);
         char *d_tmp = nullptr;
         if (e == hipSuccess && tmp.get(&d_tmp, bytes) != LOGOSKG_OK) return fail(LOGOSKG_ENOMEM);
         if (e == hipSuccess)
-            e = rocprim::radix_sort_pairs(d_tmp, bytes, d_subject, d_keys, d_iota, (uint32_t *)eid, (size_t)T, 0u,
-                                          key_bits, st);
+            e = sort_u32(d_tmp, bytes, d_subject, d_keys, d_iota, (uint32_t *)eid, T, key_bits, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);  // the temporaries are freed on return
         if (e != hipSuccess) {
             set_error("sort of the triple indices failed: %s", hipGetErrorString(e));

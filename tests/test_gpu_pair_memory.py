@@ -251,9 +251,10 @@ rng, s, r, o = graph(E, T, 5)
 off, seeds = batch(rng, E, Q)
 want = oracle.khop(E, s, r, o, off, seeds, k)
 degree = np.bincount(o, minlength=E)
-mem.memory_watch((E + 255) // 256 * 256)  # a byte per row
+mem.memory_watch((4 * E + 255) // 256 * 256)  # a word per row
 g = lkg.Graph(s, r, o, E, 9, host_build=True)
 assert mem.memory_refusals() > 0
+mem.memory_watch(0)  # (a search's planes may have the size)
 info = g.info()
 assert info["num_in_rows"] == np.count_nonzero(degree) and info["num_in_hubs"] == np.count_nonzero(degree >= 1024)
 same(g.khop(off, seeds, k), want)
